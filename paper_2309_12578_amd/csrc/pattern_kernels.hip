@@ -2,17 +2,28 @@
 //
 //   conv_pool_kernel      Eq. 3 + Eq. 4 fused: one streaming pass over A^s that splits every input
 //                         block's (fixed-point) scores over the <= 7 pooled blocks its diagonal filter
-//                         window touches and writes each of the seven sums into a slot of the record
-//                         of the pooled block it belongs to.  HBM bound: A^s is read exactly once,
-//                         nothing L x L is written, no atomics.
-//   pattern_finish_kernel one workgroup: adds the records up into pool_sum, then threshold (exact
-//                         order statistic / mean + k std),
-//                         successor bits, anti-diagonal wavefront flood fill, forced diagonal,
-//                         BSR + BSC compaction.  Latency bound (nb^2 <= ~1M cells).
+//                         window touches and writes the seven sums.  HBM bound: A^s is read exactly
+//                         once, nothing L x L is written, no atomics.
+//   pattern_finish_kernel L / block <= 64, one workgroup: adds the sums up into pool_sum, then
+//                         threshold (exact order statistic / mean + k std), flood fill, forced
+//                         diagonal, BSR + BSC compaction.  Latency bound (at most 4096 cells).
+//   grid_*_kernel         the same steps for larger grids (up to 1024 x 1024 cells), spread over the
+//                         machine: four grid-wide kernels and one of two workgroups for the serial
+//                         parts.
 //
 // Arithmetic: a_q = rint(a * 2^40) as an exact integer; all sums are integer, so any summation
-// order (tiling, partial records) gives the same bits.  This file is compiled with -ffp-contract=off: the
+// order (tiling, partial sums) gives the same bits.  This file is compiled with -ffp-contract=off: the
 // fp64 mean / std threshold must round exactly as its sequential definition.
+//
+// The fill works on rows of bits.  With D, R, G the sets of cells of row r whose down / right / diagonal
+// neighbour equals the maximum of the three, and E the expanded cells (reached, or a seed: row 0 and
+// column 0), row r gets its entries from the row above,
+//     entry = (E[r-1] & D[r-1]) | ((E[r-1] & G[r-1]) << 1),
+// and spreads them to the right along R.  Spreading a set x along runs of ones in R is a carry chain:
+// (x & R) + R carries from the lowest member of x in a run to the first position behind the run, so
+//     E = x | (((x & R) + R) ^ R),   x = entry | seeds.
+// A row is one addition, so the fill takes one short chain per row instead of one dependent step per
+// anti-diagonal.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -26,249 +37,203 @@ namespace spion {
 // Input block (I, J) of A^s (bs x bs scores).  conv_out(i, j) = sum_{g=-p..p} a(i+g, j+g), so the
 // score at local position (u, v) of this block is added to the outputs (u-g, v-g), g in [-p, p].
 // Those outputs fall into blocks (I+di, J+dj) with di, dj in {-1, 0, +1} (p < bs) and never into
-// (-1,+1) or (+1,-1) because g shifts both coordinates alike.  The number of g landing in
-// (di, dj) is the size of an interval intersection, a small integer weight w(di, dj); the seven
-// weights of an element add up to F.  Hence
-//     contribution to a neighbour block = sum w * a_q          (only near the block's edges)
-//     contribution to (I, J) itself     = F * sum a_q - (sum of the six neighbour contributions)
-// and elements at least p away from every edge cost one addition.
+// (-1,+1) or (+1,-1) because g shifts both coordinates alike.  With (x)+ = max(x, 0), u' = bs-1-u and
+// v' = bs-1-v, of the F = 2p+1 positions of the filter
+//     (p-u)+  leave the block upwards, (p-v)+ to the left, and min of the two do both,
+//     (p-u')+ leave it downwards, (p-v')+ to the right, and min of the two do both,
+// so the seven sums of a block follow from row-weighted sums, column-weighted sums (which are weighted
+// column sums), and two corner sums that only scores near the corners enter:
+//     (-1,-1) = C1 = sum min((p-u)+, (p-v)+) a_q       (-1,0) = sum (p-u)+ a_q - C1,  (0,-1) likewise
+//     (+1,+1) = C2 = sum min((p-u')+, (p-v')+) a_q     (+1,0) = sum (p-u')+ a_q - C2, (0,+1) likewise
+//     (0,0)   = F sum a_q - the six others.
 //
-// g-intervals for a local coordinate x in [0, bs): block offset -1: [x+1, p], 0: [max(x-bs+1,-p),
-// min(x,p)], +1: [-p, x-bs].
-//
-// Fixed point in fp64: for |a| <= 1, a_q = rint((double)a * 2^40) (ties to even) is an integer of at
-// most 41 bits, exact in fp64, and so are its products with the weights (< 2^7) and the sums of up
-// to 64 of them that a lane forms per block (< 2^53); see the kernel.
-// Build-time tunable of conv_pool_kernel: waves launched per compute unit (256 of them) at block 64; two
-// per SIMD are resident.  Measured at L = 4096, block 64 (cold map, whole call): 16 (every wave one
-// block) 45.0 us, 8 46.9 us, 4 49.5 us.
-#ifndef SPION_CONV_WAVES_PER_CU
-#define SPION_CONV_WAVES_PER_CU 16
-#endif
+// Fixed point: a * 2^40 is exact in fp32 (a power of two), so rint of it is a_q = rint(a * 2^40), ties to
+// even, an integer of at most 41 bits.  Per lane the sums stay in fp64: |a_q| <= 2^40, a lane owns at
+// most 64 scores of a block and the weights add up to F <= 127, so every partial sum is an integer below
+// 2^53 and exact.  (fp64 adds and fused multiply-adds issue at the rate of fp32 ones here.)
 
-__device__ __forceinline__ int isect(int lo_a, int hi_a, int lo_b, int hi_b) {
-    const int lo = lo_a > lo_b ? lo_a : lo_b;
-    const int hi = hi_a < hi_b ? hi_a : hi_b;
-    const int n = hi - lo + 1;
-    return n > 0 ? n : 0;
+// Slot s of the sums of input block (I, J) belongs to pooled block (I + di(s), J + dj(s)):
+// 0 (0,0)  1 (-1,0)  2 (+1,0)  3 (0,-1)  4 (0,+1)  5 (-1,-1)  6 (+1,+1)
+constexpr int kSlots = 7;
+
+// Sum of the slots 2a and 2b (64-bit) over lane pairs that differ in bit 5 (SWAP32) or bit 4 of the lane
+// number: lanes with the bit clear end up with a's sum, the others with b's.  The swap exchanges half of
+// one register with the other half of the other in the VALU, without the LDS crossbar.
+template <bool SWAP32>
+__device__ __forceinline__ long long pair_sum(long long a, long long b) {
+    const unsigned al = (unsigned)a, ah = (unsigned)(a >> 32), bl = (unsigned)b, bh = (unsigned)(b >> 32);
+    unsigned x0, x1, y0, y1;
+    if constexpr (SWAP32) {
+        const auto l = __builtin_amdgcn_permlane32_swap(al, bl, false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap(ah, bh, false, false);
+        x0 = l[0], y0 = l[1], x1 = h[0], y1 = h[1];
+    } else {
+        const auto l = __builtin_amdgcn_permlane16_swap(al, bl, false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
+        x0 = l[0], y0 = l[1], x1 = h[0], y1 = h[1];
+    }
+    return (long long)((unsigned long long)x1 << 32 | x0) + (long long)((unsigned long long)y1 << 32 | y0);
 }
 
 __device__ __forceinline__ long long shfl_xor_i64(long long v, int mask) { return __shfl_xor(v, mask); }
 
-// Slot s of the sums of input block (I, J) belongs to pooled block (I + di(s), J + dj(s)):
-// 0 (0,0)  1 (-1,0)  2 (+1,0)  3 (0,-1)  4 (0,+1)  5 (-1,-1)  6 (+1,+1)  7 unused
-__device__ __forceinline__ int slot_di(int s) { return (s == 1 || s == 5) ? -1 : ((s == 2 || s == 6) ? 1 : 0); }
-__device__ __forceinline__ int slot_dj(int s) { return (s == 3 || s == 5) ? -1 : ((s == 4 || s == 6) ? 1 : 0); }
-
-// One wave per input block: the wave walks the block's 16 x 16 sub-tiles (one float4 per lane each) in
-// two halves, and requests the next half (of this block or of its next block) before it works on the
-// current one, so half a block's worth of loads per wave is in flight at all times.  Which neighbours
-// a sub-tile can reach is known per sub-tile, so the edge work is skipped with scalar branches.  The
-// wave's seven slot sums are written, without atomics, into the records of the pooled blocks they
-// belong to: pooled block (ti, tj) owns the 64-byte record part[8 (ti nb + tj) .. + 7], and its slot s is
-// written by exactly one input block, (ti - di(s), tj - dj(s)), if that block exists.  Nothing has to be
-// zeroed beforehand.  Waves take the blocks wave_id, wave_id + n_waves, ...
+// One wave per tile of BS rows x 64 columns (one block of 64, two of 32 or four of 16): every load
+// instruction covers 4 rows of 256 bytes, all of a tile's loads are requested before the first is used,
+// and 16 waves per compute unit are resident.  Lane (k, j) owns rows 4 i + k and columns 4 j .. 4 j + 3.
+// Slot sums go to part[slot][I * nb + J] (index of the SOURCE block), so that the waves of a workgroup
+// write neighbouring words and the readers read whole rows of them.
+// Measured: 64 MiB map, block 64: 13.5 us = 5.0 TB/s (17.7 with one wave per block, general weights per score
+// and 210 registers); 256 MiB map, block 16: 48.9 us = 5.5 TB/s (172: a whole wave per block of 1 KB).
 template <int BS>
-__global__ __launch_bounds__(256, BS == 64 ? 2 : 4) void conv_pool_kernel(const float* __restrict__ A, int L,
-                                                                          int p_arg,
-                                                                          long long* __restrict__ part) {
-    // sub-tile of one wave instruction: SH rows x SW columns, 256 scores
-    constexpr int SW = 16, SH = 256 / SW;
-    constexpr int NSC = BS / SW, NSUB = (BS / SH) * NSC;
-    constexpr int NH = NSUB >= 2 ? 2 : 1, HS = NSUB / NH;   // halves per block, sub-tiles per half
-    const int nb = L / BS;
-    const int n_blocks = nb * nb;
+__global__ __launch_bounds__(256, 4) void conv_pool_kernel(const float* __restrict__ A, int L, int p,
+                                                           long long* __restrict__ part, unsigned* __restrict__ zero,
+                                                           int n_zero) {
+    constexpr int NL = BS / 4;     // loads (row groups) per lane
+    constexpr int BPT = 64 / BS;   // blocks side by side in a tile
+    const int gid = blockIdx.x * 256 + threadIdx.x;
+    if (gid < n_zero) zero[gid] = 0u;   // counters that the kernels after this one add to
+    const int nb = L / BS, tiles_x = (nb + BPT - 1) / BPT;
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int n_waves = gridDim.x * (blockDim.x >> 6);
-    const int first = blockIdx.x * (blockDim.x >> 6) + wave;
-    const int lr = lane / (SW / 4), lc = (lane % (SW / 4)) << 2;
+    const int tile = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+    if (tile >= nb * tiles_x) return;
+    const int I = tile / tiles_x, tx = tile % tiles_x;
+    const int k = lane >> 4, j = lane & 15;
+    const int J = tx * BPT + (4 * j) / BS;
+    const bool live = J < nb;      // the last tile of a row may reach past the matrix
+    const float* src = A + (size_t)I * BS * L + tx * 64;   // wave-uniform, the lane's part is a 32-bit offset
+    const unsigned off = (unsigned)(k * L + 4 * j);
+    float4 a[NL];
+    if (BPT == 1 || live) {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) a[i] = *reinterpret_cast<const float4*>(src + (size_t)(4 * i) * L + off);
+    } else {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) a[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
 
-    auto load_half = [&](int blk, int half, float4 (&dst)[HS]) {
-        const float* base = A + (size_t)(blk / nb) * BS * L + (size_t)(blk % nb) * BS;
+    int pl[4], pr[4];              // (p - v)+ and (p - v')+ of the lane's columns
 #pragma unroll
-        for (int k = 0; k < HS; ++k) {
-            const int st = half * HS + k;
-            const int u = (st / NSC) * SH + lr, v0 = (st % NSC) * SW + lc;
-            dst[k] = *reinterpret_cast<const float4*>(base + (size_t)u * L + v0);
+    for (int e = 0; e < 4; ++e) {
+        const int v = (4 * j) % BS + e;
+        pl[e] = max(p - v, 0);
+        pr[e] = max(p - (BS - 1 - v), 0);
+    }
+    double cs[4] = {0.0, 0.0, 0.0, 0.0}, rt = 0.0, rb = 0.0, c1 = 0.0, c2 = 0.0;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+        // The weights depend only on the lane and the filter; left to itself the compiler makes those of
+        // all row groups while it waits for the loads, and spills them.  Hiding the filter's half-width
+        // and the lane's row makes them per-group work.
+        int ph = p, kh = k;
+        asm volatile("" : "+s"(ph), "+v"(kh));
+        __builtin_amdgcn_sched_barrier(0);
+        const float av[4] = {a[i].x, a[i].y, a[i].z, a[i].w};
+        double q[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            q[e] = (double)__builtin_rintf(av[e] * 1099511627776.0f);
+            cs[e] += q[e];
+            asm volatile("" : "+v"(cs[e]));   // added now: the compiler would keep the terms for the end
         }
-    };
-
-    // Per lane and block the sums stay in fp64: every term is an integer (a quantised score below 2^41
-    // in magnitude times a weight below 2^7), at most 64 of them go into one sum, so every partial sum
-    // is an integer below 2^53 and the fp64 additions are exact.  (fp64 adds and fused multiply-adds
-    // issue at the rate of fp32 ones here; the same sums in 64-bit integer arithmetic take three to
-    // four instructions per term.)
-    double tot[8];
-    double s_all;
-    // sub-tiles [half * HS, half * HS + HS) of the current block, scores in src
-    auto work_half = [&](int half, const float4 (&src)[HS]) {
-        // The edge weights and the coordinates they are made from depend only on the lane, the sub-tile
-        // and the filter, not on the block; left to itself the compiler computes all of them once and
-        // keeps several hundred values in registers (and in scratch memory) across the loop.  Hiding
-        // the filter's half-width and the lane's coordinates here makes them per-sub-tile work.
+        if (4 * i < ph) {                         // some of these rows lie within p of the top edge
+            const int pu = max(ph - 4 * i - kh, 0);
+            rt = __builtin_fma((double)pu, (q[0] + q[1]) + (q[2] + q[3]), rt);
 #pragma unroll
-        for (int k = 0; k < HS; ++k) {
-            int p = p_arg, lrow = lr, lcol = lc;
-            asm volatile("" : "+s"(p), "+v"(lrow), "+v"(lcol));
-            __builtin_amdgcn_sched_barrier(0);   // one sub-tile at a time: their temporaries do not pile up
-            const int st = half * HS + k;
-            const int su = (st / NSC) * SH, sv = (st % NSC) * SW;
-            const int u = su + lrow, v0 = sv + lcol;
-            const bool top = su < p, bottom = su + SH - 1 > BS - 1 - p;
-            const bool left = sv < p, right = sv + SW - 1 > BS - 1 - p;
-            const int rm_lo = u + 1, rm_hi = p;
-            const int r0_lo = (u - BS + 1) > -p ? (u - BS + 1) : -p, r0_hi = u < p ? u : p;
-            const int rp_lo = -p, rp_hi = u - BS;
-            const float av[4] = {src[k].x, src[k].y, src[k].z, src[k].w};
-            double q[4];   // a_q = rint(a * 2^40), ties to even: an integer, exact in fp64
-            int c0_lo[4], c0_hi[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int v = v0 + e;
-                q[e] = __builtin_rint((double)av[e] * 1099511627776.0);
-                c0_lo[e] = (v - BS + 1) > -p ? (v - BS + 1) : -p;
-                c0_hi[e] = v < p ? v : p;
-            }
-            s_all += (q[0] + q[1]) + (q[2] + q[3]);
-            auto edge = [&](int slot, auto weight) {
-                double acc = tot[slot];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) acc = __builtin_fma((double)weight(e), q[e], acc);
-                tot[slot] = acc;
-            };
-            if (top) edge(1, [&](int e) { return isect(rm_lo, rm_hi, c0_lo[e], c0_hi[e]); });
-            if (bottom) edge(2, [&](int e) { return isect(rp_lo, rp_hi, c0_lo[e], c0_hi[e]); });
-            if (left) edge(3, [&](int e) { return isect(r0_lo, r0_hi, v0 + e + 1, p); });
-            if (right) edge(4, [&](int e) { return isect(r0_lo, r0_hi, -p, v0 + e - BS); });
-            if (top && left) edge(5, [&](int e) { return isect(rm_lo, rm_hi, v0 + e + 1, p); });
-            if (bottom && right) edge(6, [&](int e) { return isect(rp_lo, rp_hi, -p, v0 + e - BS); });
+            for (int e = 0; e < 4; ++e) c1 = __builtin_fma((double)min(pu, pl[e]), q[e], c1);
         }
-    };
-
-    float4 a[HS], b[HS];
-    if (first < n_blocks) load_half(first, 0, a);
-    for (int blk = first; blk < n_blocks; blk += n_waves) {
-        const bool more = blk + n_waves < n_blocks;
+        if (4 * i + 3 > BS - 1 - ph) {            // ... of the bottom edge
+            const int pd = max(ph - (BS - 1 - 4 * i - kh), 0);
+            rb = __builtin_fma((double)pd, (q[0] + q[1]) + (q[2] + q[3]), rb);
 #pragma unroll
-        for (int t = 0; t < 8; ++t) tot[t] = 0.0;
-        s_all = 0.0;
-        if constexpr (NH == 2) {
-            load_half(blk, 1, b);
-            work_half(0, a);
-            if (more) load_half(blk + n_waves, 0, a);
-            work_half(1, b);
-        } else {
-            if (more) load_half(blk + n_waves, 0, b);
-            work_half(0, a);
+            for (int e = 0; e < 4; ++e) c2 = __builtin_fma((double)min(pd, pr[e]), q[e], c2);
+        }
+    }
+    double cl = 0.0, cr = 0.0;
 #pragma unroll
-            for (int k = 0; k < HS; ++k) a[k] = b[k];
-        }
-        // from here on in 64-bit integers: the sums over the wave's lanes can exceed 2^53
-        long long ti64[8];
-        long long others = 0;
+    for (int e = 0; e < 4; ++e) {
+        cl = __builtin_fma((double)pl[e], cs[e], cl);
+        cr = __builtin_fma((double)pr[e], cs[e], cr);
+    }
+    const double all = (double)(2 * p + 1) * ((cs[0] + cs[1]) + (cs[2] + cs[3]));
+    // from here on in 64-bit integers: the sums over a block's lanes can exceed 2^53
+    long long t[8];
+    t[1] = (long long)(rt - c1);
+    t[2] = (long long)(rb - c2);
+    t[3] = (long long)(cl - c1);
+    t[4] = (long long)(cr - c2);
+    t[5] = (long long)c1;
+    t[6] = (long long)c2;
+    t[0] = (long long)(all - ((rt + cl - c1) + (rb + cr - c2)));
+    t[7] = 0;
+    // reduce-scatter over the lanes of a block (lane bits 5 and 4 are its rows; of bits 0..3 the lowest
+    // log2(BS / 4) are its columns): 8 slots -> 4 -> 2 -> 1, then plain steps over the bits left
+    constexpr int kThird = BS == 64 ? 8 : (BS == 32 ? 4 : 2);
 #pragma unroll
-        for (int t = 1; t < 7; ++t) {
-            ti64[t] = (long long)tot[t];
-            others += ti64[t];
-        }
-        ti64[0] = (long long)(2 * p_arg + 1) * (long long)s_all - others;
-        ti64[7] = 0;
-
-        // reduce-scatter butterfly over the wave: 8 slots -> 4 -> 2 -> 1, then 3 plain steps
+    for (int s = 0; s < 4; ++s) t[s] = pair_sum<true>(t[s], t[s + 4]);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const bool up = lane & 32;
-            const long long send = up ? ti64[k] : ti64[k + 4];
-            const long long keep = up ? ti64[k + 4] : ti64[k];
-            ti64[k] = keep + shfl_xor_i64(send, 32);
-        }
+    for (int s = 0; s < 2; ++s) t[s] = pair_sum<false>(t[s], t[s + 2]);
+    const bool up = (lane & kThird) != 0;
+    const long long send = up ? t[0] : t[1], keep = up ? t[1] : t[0];
+    long long sum = keep + shfl_xor_i64(send, kThird);
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const bool up = lane & 16;
-            const long long send = up ? ti64[k] : ti64[k + 2];
-            const long long keep = up ? ti64[k + 2] : ti64[k];
-            ti64[k] = keep + shfl_xor_i64(send, 16);
-        }
-        {
-            const bool up = lane & 8;
-            const long long send = up ? ti64[0] : ti64[1];
-            const long long keep = up ? ti64[1] : ti64[0];
-            ti64[0] = keep + shfl_xor_i64(send, 8);
-        }
-        long long s = ti64[0];
-        s += shfl_xor_i64(s, 4);
-        s += shfl_xor_i64(s, 2);
-        s += shfl_xor_i64(s, 1);
-        if ((lane & 7) == 0) {
-            const int slot = ((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1);
-            const int ti = blk / nb + slot_di(slot), tj = blk % nb + slot_dj(slot);
-            if (slot < 7 && ti >= 0 && ti < nb && tj >= 0 && tj < nb) part[((size_t)ti * nb + tj) * 8 + slot] = s;
-        }
+    for (int m = kThird >> 1; m > 0; m >>= 1) sum += shfl_xor_i64(sum, m);
+    if ((lane & (kThird - 1)) == 0 && live) {
+        const int slot = ((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + (up ? 1 : 0);
+        if (slot < kSlots) part[(size_t)slot * ((size_t)nb * nb) + (size_t)I * nb + J] = sum;
     }
 }
 
-// pool_sum of cell (ti, tj): the sum of the slots of its record whose source block exists (the
-// other slots were never written).
-struct PoolRecord {
-    uint4 q[4];
+// pool_sum of cell (ti, tj): slot s of its source block (ti - di(s), tj - dj(s)), for the source blocks that
+// exist.  The loads of the others are redirected to the cell itself and dropped, so that all seven are
+// requested at once.
+struct PoolParts {
+    long long v[kSlots];
 };
-__device__ __forceinline__ PoolRecord load_record(const long long* __restrict__ part, size_t cell) {
-    PoolRecord rec;
-    const uint4* src = reinterpret_cast<const uint4*>(part + cell * 8);
-#pragma unroll
-    for (int h = 0; h < 4; ++h) rec.q[h] = src[h];
-    return rec;
-}
-__device__ __forceinline__ long long sum_record(const PoolRecord& rec, int nb, int ti, int tj) {
-    // slot s was written by input block (ti - di(s), tj - dj(s)): it exists iff the pooled block has a
-    // neighbour on that side
+__device__ __forceinline__ PoolParts load_parts(const long long* __restrict__ part, int nb, int ti, int tj) {
+    const int n = nb * nb, i = ti * nb + tj;
     const bool up = ti >= 1, down = ti + 1 < nb, left = tj >= 1, right = tj + 1 < nb;
-    const bool ok[7] = {true, down, up, right, left, down && right, up && left};
-    long long acc = 0;
-#pragma unroll
-    for (int s = 0; s < 7; ++s) {
-        const uint4 q = rec.q[s >> 1];
-        const unsigned long long v = (s & 1) ? ((unsigned long long)q.w << 32 | q.z) : ((unsigned long long)q.y << 32 | q.x);
-        acc += ok[s] ? (long long)v : 0ll;
-    }
-    return acc;
+    PoolParts r;
+    r.v[0] = part[i];
+    r.v[1] = part[(size_t)n + (down ? i + nb : i)];
+    r.v[2] = part[(size_t)2 * n + (up ? i - nb : i)];
+    r.v[3] = part[(size_t)3 * n + (right ? i + 1 : i)];
+    r.v[4] = part[(size_t)4 * n + (left ? i - 1 : i)];
+    r.v[5] = part[(size_t)5 * n + (down && right ? i + nb + 1 : i)];
+    r.v[6] = part[(size_t)6 * n + (up && left ? i - nb - 1 : i)];
+    return r;
+}
+__device__ __forceinline__ long long sum_parts(const PoolParts& r, int nb, int ti, int tj) {
+    const bool up = ti >= 1, down = ti + 1 < nb, left = tj >= 1, right = tj + 1 < nb;
+    return r.v[0] + (down ? r.v[1] : 0) + (up ? r.v[2] : 0) + (right ? r.v[3] : 0) + (left ? r.v[4] : 0) +
+           (down && right ? r.v[5] : 0) + (up && left ? r.v[6] : 0);
 }
 
 // pool_sum alone (the convolution + pooling stage run on its own)
 __global__ __launch_bounds__(256) void pool_gather_kernel(const long long* __restrict__ part, int nb,
                                                           long long* __restrict__ pool) {
     const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < nb * nb) pool[i] = sum_record(load_record(part, (size_t)i), nb, i / nb, i % nb);
+    if (i < nb * nb) pool[i] = sum_parts(load_parts(part, nb, i / nb, i % nb), nb, i / nb, i % nb);
 }
 
 // ------------------------------------------------------------------------------------------------
-// threshold + fill + compaction (one workgroup)
+// helpers of the threshold, fill and compaction steps
 // ------------------------------------------------------------------------------------------------
 constexpr int kFinishThreads = 1024;
 constexpr int kFinishWaves = kFinishThreads / 64;
-constexpr int SPION_MAX_NB_INTERNAL = 1024;   // same bound as SPION_MAX_NB of the public header
-constexpr unsigned kDown = 1u, kRight = 2u, kDiag = 4u, kAbove = 8u;
-constexpr unsigned kExpanded = 1u, kReached = 2u;
 
 struct Thresh {
     int is_int;
     long long ti;
     double td;
 };
-
-__device__ __forceinline__ int wave_inclusive_scan(int v, int lane) {
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int o = __shfl_up(v, off);
-        if (lane >= off) v += o;
-    }
-    return v;
+__device__ __forceinline__ bool above(long long x, const Thresh& t) {
+    return t.is_int ? x > t.ti : (double)x > t.td;
 }
 
-// The same scan with DPP moves (VALU speed, no LDS crossbar): shifts of 1, 2, 4, 8 inside each row of
-// 16 lanes, then lane 15 of rows 0 and 2 added to rows 1 and 3, then lane 31 added to rows 2 and 3.
-// A lane whose source is outside its row, or whose row is masked off, adds the 0 given as old value.
+// Inclusive prefix sum over the wave with DPP moves (VALU speed, no LDS crossbar): shifts of 1, 2, 4, 8
+// inside each row of 16 lanes, then lane 15 of rows 0 and 2 added to rows 1 and 3, then lane 31 added to
+// rows 2 and 3.  A lane whose source is outside its row, or whose row is masked off, adds the 0 given as
+// old value.
 template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ int dpp_fetch(int v) {
     return __builtin_amdgcn_update_dpp(0, v, CTRL, ROW_MASK, 0xf, false);
@@ -298,48 +263,54 @@ __device__ __forceinline__ int wave_min_dpp(int v) {
     return v;
 }
 
-// Exclusive prefix sum over one value per thread.  Returns the exclusive prefix of this thread's
-// value; *total gets the sum.  All threads call.  scratch: kFinishWaves + 1 ints of LDS.
-__device__ int block_exclusive_scan(int v, int* total, int* scratch) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int incl = wave_inclusive_scan(v, lane);
-    if (lane == 63) scratch[wave] = incl;
-    __syncthreads();
-    if (wave == 0) {
-        const int c = lane < kFinishWaves ? scratch[lane] : 0;
-        const int inc = wave_inclusive_scan(c, lane);
-        if (lane < kFinishWaves) scratch[lane] = inc - c;
-        if (lane == kFinishWaves - 1) scratch[kFinishWaves] = inc;
-    }
-    __syncthreads();
-    const int res = incl - v + scratch[wave];
-    *total = scratch[kFinishWaves];
-    __syncthreads();
-    return res;
+// Successor bits of a cell: which of down / right / diagonal equal the maximum of the three (none in the
+// last row and column, where walks stop).
+struct Succ {
+    bool down, right, diag;
+};
+__device__ __forceinline__ Succ successors(long long dn, long long rt, long long dg, bool inner) {
+    long long mx = dn > rt ? dn : rt;
+    mx = mx > dg ? mx : dg;
+    return {inner && dn == mx, inner && rt == mx, inner && dg == mx};
 }
 
-// Number of kept cells in a run of nb cells starting at f with the given element stride, counted by
-// one wave; with WRITE, also emits the compacted positions.
-template <bool WRITE>
-__device__ __forceinline__ int wave_compact(const uint8_t* f, int stride, int nb, int lane, int start,
-                                            int* idx_out, int* pos_rw, long long pos_base,
-                                            int pos_stride, int* bsr_pos_out) {
-    int offset = start;
-    for (int seg = 0; seg < nb; seg += 64) {
-        const int c = seg + lane;
-        const bool keep = c < nb && f[(long long)c * stride] != 0;
-        const unsigned long long b = __ballot(keep);
-        if (WRITE && keep) {
-            const int k = offset + __popcll(b & ((1ull << lane) - 1ull));
-            idx_out[k] = c;
-            if (bsr_pos_out)
-                bsr_pos_out[k] = pos_rw[pos_base + (long long)c * pos_stride];
-            else
-                pos_rw[pos_base + (long long)c * pos_stride] = k;
+// Sum of n doubles in index order, s = ((x[0] + x[1]) + x[2]) + ...: the order is the definition of the
+// mean / std threshold, so the additions are one dependent chain.  x is in LDS, 16-byte aligned; 16 values
+// are requested ahead of the 16 being added, so that the chain never waits for a load.  Every lane of the
+// calling wave computes the same value.
+__device__ __forceinline__ double ordered_sum(const double* x, int n) {
+    double s = 0.0;
+    double2 even[8], odd[8];
+    const double2* v = reinterpret_cast<const double2*>(x);
+    const int groups = n >> 4, last = groups > 0 ? groups - 1 : 0;
+    auto request = [&](double2 (&dst)[8], int g) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) dst[e] = v[(g < last ? g : last) * 8 + e];
+        __builtin_amdgcn_sched_barrier(0);   // before the additions of the other group
+    };
+    auto add = [&](const double2 (&src)[8]) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            s = s + src[e].x;
+            s = s + src[e].y;
         }
-        offset += __popcll(b);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    if (groups > 0) request(even, 0);
+    for (int g = 0; g < groups; g += 2) {
+        request(odd, g + 1);
+        add(even);
+        request(even, g + 2);
+        if (g + 1 < groups) add(odd);
     }
-    return offset - start;
+    for (int i = groups << 4; i < n; ++i) s = s + x[i];
+    return s;
+}
+
+__device__ __forceinline__ unsigned long long read_lane_u64(unsigned long long w, int l) {
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)w, l);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(w >> 32), l);
+    return (unsigned long long)hi << 32 | lo;
 }
 
 // Radix selection: digits of kDigitBits bits, most significant first; 64-bit keys need kSelPasses.
@@ -351,271 +322,420 @@ static_assert(kBins == 32 * 64, "one wave scans a histogram with 32 bins per lan
 // contiguous, so that the wave reads it without bank conflicts.
 __device__ __forceinline__ int bin_slot(unsigned D) { return (int)(((D >> 2) & 7u) * 256u + (D >> 5) * 4u + (D & 3u)); }
 
+struct SelectShared {
+    int digit, below, count, cand_n, common_lz;
+    int n_below, shift;                       // sampled selection (nb <= 64)
+    unsigned long long cand[64], key, lo, hi;
+};
+
+// One wave: the digit whose bin holds rank k, how many keys lie below it and in it (nothing is written if the
+// histogram holds no more than k keys).  Lane owns digits 32 lane .. 32 lane + 31 as 8 groups of 4.
+__device__ __forceinline__ void scan_histogram(const unsigned* h, int k, SelectShared* sh) {
+    const int lane = threadIdx.x & 63;
+    const uint4* const h4 = reinterpret_cast<const uint4*>(h);
+    int s4[8], s32 = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const uint4 v = h4[j * 64 + lane];
+        s4[j] = (int)(v.x + v.y + v.z + v.w);
+        s32 += s4[j];
+    }
+    const int incl = wave_inclusive_scan_dpp(s32);
+    int e = incl - s32, qj = 0;
+    const bool hit = k >= e && k < incl;   // at most one lane
+#pragma unroll
+    for (int j = 0; j < 7; ++j) {
+        const bool adv = qj == j && k >= e + s4[j];
+        e = adv ? e + s4[j] : e;
+        qj = adv ? j + 1 : qj;
+    }
+    const uint4 v = h4[qj * 64 + lane];
+    const int c3[3] = {(int)v.x, (int)v.y, (int)v.z};
+    int qt = 0;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const bool adv = qt == j && k >= e + c3[j];
+        e = adv ? e + c3[j] : e;
+        qt = adv ? j + 1 : qt;
+    }
+    if (hit) {
+        sh->digit = 32 * lane + 4 * qj + qt;
+        sh->below = e;
+        sh->count = (int)(qt == 0 ? v.x : (qt == 1 ? v.y : (qt == 2 ? v.z : v.w)));
+    }
+}
+
+// All waves: the k-th smallest of the sh->cand_n <= 64 collected keys, into sh->key.  A wave ranks every 16th
+// of them: one ballot counts the smaller ones.
+__device__ __forceinline__ void rank_candidates(int k, SelectShared* sh) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), cn = sh->cand_n;
+    const unsigned long long mine = lane < cn ? sh->cand[lane] : ~0ull;
+    for (int t = wave; t < cn; t += kFinishWaves) {
+        const unsigned long long other = read_lane_u64(mine, t);
+        const int less = __popcll(__ballot(mine < other)), same = __popcll(__ballot(lane < cn && mine == other));
+        if (lane == 0 && k >= less && k < less + same) sh->key = other;   // equal keys write the same value
+    }
+}
+
+// Exact k-th smallest (0-based) of a set of 64-bit keys held by a workgroup of kFinishThreads threads, by
+// radix selection.  each(f) calls f(key, active) for every key of the calling thread, all lanes of a wave
+// together; `ref` is any one of the keys (the same in all threads).  hist: 3 * kBins counters, cleared here.
+// A pass: every wave counts its keys' digits into a histogram; one wave scans it (32 bins per lane, a DPP
+// prefix sum) and publishes the digit that holds rank k; three histograms rotate, the other waves clear
+// the one of the pass before meanwhile.  Leading bits that all keys share need no pass, and as soon as at
+// most 64 keys share the selected prefix they are collected and one wave ranks them against each other.
+template <class Each>
+__device__ __forceinline__ unsigned long long select_kth(Each&& each, unsigned long long ref, int k, unsigned* hist,
+                                                         SelectShared* sh) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int i = tid; i < 3 * kBins; i += kFinishThreads) hist[i] = 0u;
+    if (tid == 0) {
+        sh->common_lz = 64;
+        sh->cand_n = 0;
+    }
+    __syncthreads();
+    unsigned long long differ = 0ull;
+    each([&](unsigned long long u, bool active) { differ |= active ? u ^ ref : 0ull; });
+    const int lz = wave_min_dpp(differ ? __clzll((long long)differ) : 64);
+    if (lane == 63) atomicMin(&sh->common_lz, lz);
+    __syncthreads();
+    const int n_passes = (64 - sh->common_lz + kDigitBits - 1) / kDigitBits;   // 0: all keys are equal
+    unsigned long long prefix = 0ull;
+    if (kDigitBits * n_passes < 64) prefix = ref & ~((1ull << (kDigitBits * n_passes)) - 1ull);
+#pragma unroll 1
+    for (int pass = 0; pass < n_passes; ++pass) {
+        const int shift = kDigitBits * (n_passes - 1 - pass);   // without shared bits: 55, 44, ..., 0
+        const int top = shift + kDigitBits;                     // bits >= top are already decided
+        unsigned* const h = hist + (pass % 3) * kBins;
+        each([&](unsigned long long u, bool active) {
+            const bool match = active && (top >= 64 || (u >> top) == (prefix >> top));
+            const unsigned digit = (unsigned)(u >> shift) & (unsigned)(kBins - 1);
+            // the leading digits are usually equal for the whole wave: one atomic instead of 64
+            const unsigned long long m = __ballot(match);
+            if (m == 0ull) return;
+            const unsigned first = (unsigned)__builtin_amdgcn_readlane((int)digit, __ffsll((long long)m) - 1);
+            if (__ballot(match && digit == first) == m) {
+                if (lane == 0) atomicAdd(&h[bin_slot(first)], (unsigned)__popcll(m));
+            } else if (match) {
+                atomicAdd(&h[bin_slot(digit)], 1u);
+            }
+        });
+        __syncthreads();
+        if (wave != 0) {
+            // the histogram of the pass before (last read before the barrier above) is cleared for the
+            // pass after the next, off the path of the wave that scans
+            unsigned* const hz = hist + ((pass + 2) % 3) * kBins;
+            for (int i = tid - 64; i < kBins; i += kFinishThreads - 64) hz[i] = 0u;
+        } else {
+            scan_histogram(h, k, sh);
+        }
+        __syncthreads();
+        k -= sh->below;
+        prefix |= (unsigned long long)(unsigned)sh->digit << shift;
+        if (pass + 1 < n_passes && sh->count <= 64) {
+            // few keys are left (typically after the second pass); k is the rank among them
+            each([&](unsigned long long u, bool active) {
+                if (active && (u >> shift) == (prefix >> shift)) sh->cand[atomicAdd(&sh->cand_n, 1)] = u;
+            });
+            __syncthreads();
+            rank_candidates(k, sh);
+            __syncthreads();
+            prefix = sh->key;
+            break;
+        }
+    }
+    return prefix;
+}
+
+constexpr unsigned long long kSign = 0x8000000000000000ull;   // int64 order as unsigned order: flip the sign bit
+
+// ------------------------------------------------------------------------------------------------
+// threshold + fill + compaction, nb <= 64 (one workgroup)
+// ------------------------------------------------------------------------------------------------
+// Thread (wave, lane) owns the cells (4 wave + j, lane), j < 4, and keeps their values in registers: a wave
+// owns whole rows, so a ballot is a row of bits.  Which cells a walk reaches does not depend on the
+// threshold, so wave 1 fills (scalar 64-bit words, one short chain per row) while the others select; its own
+// four rows are selected from by the waves 2 to 5.
+// Order statistic: 64 sampled cells are ranked against each other and bracket the wanted rank; one
+// histogram of 2048 bins over the bracket, and the few keys of one bin are ranked.  A bracket of a fifth of
+// the cells spreads them over the bins, where a radix digit piles most of them into a few counters, whose
+// LDS atomics then queue up.  Where the bracket misses (or a bin holds more than 64 keys: ties) the radix
+// selection above decides.
+// Bound by latency: of 14 us at nb = 64, the loads of the slot sums (just written by other XCDs) are 4.3,
+// the selection with the fill beside it 6, the rest short steps between barriers.  (22.4 us with three radix
+// passes and an anti-diagonal fill of 127 steps behind them; with mean + k std at nb = 16, 51 -> 11.4 us,
+// the additions being taken from LDS instead of from memory one by one.)
 // mode: 0 = threshold given in t_abs, 1 = quantile rank k_rank, 2 = mean + kval * std.
-// part: partial records of conv_pool_kernel, from which pool[] is first computed; nullptr: pool[] is given.
-// mask_g / expd_g / pos: scratch arrays of nb*nb entries in global memory; when use_lds is set the
-// byte arrays live in dynamic LDS instead (3 * nb * nb bytes).  mask_g holds 2 * nb * nb bytes.
+// part: sums of conv_pool_kernel, from which pool[] is first computed; nullptr: pool[] is given.
+// nnzb_host: nullptr, or a word of host memory that receives nnzb after everything else is written.
 __global__ __launch_bounds__(kFinishThreads) void pattern_finish_kernel(
     const long long* __restrict__ part, long long* pool, int nb, int mode, int k_rank, double kval,
-    double t_abs, int no_fill, int use_lds, uint8_t* mask_g, uint8_t* expd_g, int* pos,
-    uint8_t* __restrict__ fl, int* __restrict__ row_ptr, int* __restrict__ col_idx,
+    double t_abs, int no_fill, uint8_t* __restrict__ fl, int* __restrict__ row_ptr, int* __restrict__ col_idx,
     int* __restrict__ col_ptr, int* __restrict__ row_idx, int* __restrict__ bsr_pos,
-    int* __restrict__ nnzb_out) {
-    extern __shared__ uint8_t dyn_lds[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int n = nb * nb;   // at most 2^20 cells: 32-bit index arithmetic throughout (no 64-bit divisions)
-    uint8_t* mask = use_lds ? dyn_lds : mask_g;
-    uint8_t* expd = use_lds ? dyn_lds + n : expd_g;
-    uint8_t* mask_t = use_lds ? dyn_lds + 2 * n : mask_g + n;   // final mask, transposed (step 5)
-    if (use_lds > 1) pos = reinterpret_cast<int*>(dyn_lds + 4 * n);   // 3n rounded up to a multiple of 4
-    // nb <= 64: the steps after the threshold use neither expd, mask_t nor pos; pool_sum lives there
-    // instead, so that the three neighbours of every cell are read from LDS
-    long long* const pool_s = reinterpret_cast<long long*>(dyn_lds + ((n + 7) & ~7));
-    // One block of LDS, used twice: three histograms while the quantile is selected; afterwards the
-    // arrays of the fill and the compaction.
-    __shared__ __attribute__((aligned(16))) unsigned char sh[3 * kBins * 4];
-    unsigned* const hist = reinterpret_cast<unsigned*>(sh);
-    // nb <= 64 only: successor bits of row r in anti-diagonal order, skew[r][s] = bits of cell
-    // (r, s - r), zero where s - r is outside the row; the "reached" bit of every cell as one 128-bit
-    // mask per row in the same order; the final mask as one 64-bit word per row and per column
-    uint8_t* const skew = sh;                                                   // 64 * 128
-    int* const line_start = reinterpret_cast<int*>(sh + 8192);                  // SPION_MAX_NB ints
-    int* const col_start = reinterpret_cast<int*>(sh + 12288);                  // SPION_MAX_NB ints
-    unsigned* const rbits = reinterpret_cast<unsigned*>(sh + 16384);            // 64 * 4
-    unsigned long long* const rowmask = reinterpret_cast<unsigned long long*>(sh + 17408);   // 64
-    unsigned long long* const colmask = reinterpret_cast<unsigned long long*>(sh + 17920);   // 64
-    static_assert(17920 + 512 <= 3 * kBins * 4 && SPION_MAX_NB_INTERNAL * 4 == 4096, "LDS carving");
+    int* __restrict__ nnzb_out, int* nnzb_host) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = nb * nb;
+    __shared__ __attribute__((aligned(16))) long long pool_s[64 * 64];   // every 4th row of pool_sum; later doubles
+    __shared__ __attribute__((aligned(16))) unsigned hist[3 * kBins];
+    __shared__ unsigned long long down[64], right[64], diag[64], reached[64], rowmask[64], colmask[64];
+    __shared__ int line_start[64], col_start[64];
     __shared__ Thresh th;
-    __shared__ int scan_scratch[kFinishWaves + 1];
-    __shared__ int sel_digit, sel_below, sel_count, cand_n, common_lz;
-    __shared__ unsigned long long cand[64], sel_key;
-    const bool small = nb <= 64;
+    __shared__ SelectShared sel;
 
-    // ---- 0. pool_sum from the partial records.  nb <= 64: thread (wave, lane) owns the cells
-    //         (wave + 16 j, lane), j < 4, and keeps their values in registers (no division is needed to
-    //         find a cell's row and column); larger grids walk the cells with a stride ------------------
-    if (tid == 0) common_lz = 64;   // (read after the barrier that ends this step)
     constexpr int kCached = 4;
     static_assert(kCached * kFinishWaves == 64, "the owned cells of a thread cover 64 rows");
+    const int row0 = kCached * wave;   // this wave's rows: row0 .. row0 + 3
     auto own_cell = [&](int j, int& i) {
-        const int r = wave + kFinishWaves * j;
-        i = r * nb + lane;
-        return r < nb && lane < nb;
+        i = (row0 + j) * nb + lane;
+        return row0 + j < nb && lane < nb;
     };
+
+    // ---- 0. pool_sum: all of a thread's loads are requested before the first is used --------------------
     long long val[kCached] = {0, 0, 0, 0};
     if (part) {
-        if (small) {
-            // all records are requested before the first is used
-            PoolRecord rec[kCached];
+        PoolParts rec[kCached];
 #pragma unroll
-            for (int j = 0; j < kCached; ++j) {
-                int i;
-                const bool ok = own_cell(j, i);
-                rec[j] = load_record(part, (size_t)(ok ? i : 0));
-            }
-#pragma unroll
-            for (int j = 0; j < kCached; ++j) {
-                int i;
-                if (own_cell(j, i)) {
-                    const long long v = sum_record(rec[j], nb, wave + kFinishWaves * j, lane);
-                    pool[i] = v;
-                    val[j] = v;
-                    pool_s[i] = v;
-                }
-            }
-        } else {
-            for (int base = 0; base < n; base += kCached * kFinishThreads) {
-                PoolRecord rec[kCached];
-#pragma unroll
-                for (int j = 0; j < kCached; ++j) {
-                    const int i = base + j * kFinishThreads + tid;
-                    rec[j] = load_record(part, (size_t)(i < n ? i : n - 1));
-                }
-#pragma unroll
-                for (int j = 0; j < kCached; ++j) {
-                    const int i = base + j * kFinishThreads + tid;
-                    if (i < n) pool[i] = sum_record(rec[j], nb, i / nb, i % nb);
-                }
-            }
+        for (int j = 0; j < kCached; ++j) {
+            int i;
+            const bool ok = own_cell(j, i);
+            rec[j] = load_parts(part, nb, ok ? row0 + j : 0, ok ? lane : 0);
         }
-        __syncthreads();   // pool[] is read by other threads from here on
-    } else if (small) {
+        for (int i = tid; i < kBins; i += kFinishThreads) hist[i] = 0u;
 #pragma unroll
         for (int j = 0; j < kCached; ++j) {
             int i;
             if (own_cell(j, i)) {
-                val[j] = pool[i];
-                pool_s[i] = val[j];
+                val[j] = sum_parts(rec[j], nb, row0 + j, lane);
+                pool[i] = val[j];
             }
         }
-        __syncthreads();
-    }
-
-    // ---- 1. threshold ------------------------------------------------------------------------
-    if (mode == 1) {
-        // Exact k-th smallest (0-based) by radix selection on key = value with the sign bit flipped.
-        // A pass: every wave counts its keys' digits into a histogram; one wave scans it (32 bins per
-        // lane, a DPP prefix sum) and publishes the digit that holds rank k; three histograms rotate,
-        // the other waves clear the one of the pass before meanwhile.
-        for (int i = tid; i < 3 * kBins; i += kFinishThreads) hist[i] = 0u;
-        if (tid == 0) cand_n = 0;
-        unsigned long long key[kCached];
-        bool alive[kCached];   // still equal to the selected prefix
-        // The leading bits that all keys share need no pass: pooled sums of scores in [0, 1] share their
-        // first 14 bits or more.  Every key is compared with the key of cell (0, 0); the smallest number
-        // of leading bits any key shares with it is what all keys share.  (nb <= 64 only.)
-        const unsigned long long ref = small ? ((unsigned long long)pool_s[0] ^ 0x8000000000000000ull) : 0ull;
-        unsigned long long differ = 0ull;
+    } else {
+        for (int i = tid; i < kBins; i += kFinishThreads) hist[i] = 0u;
 #pragma unroll
         for (int j = 0; j < kCached; ++j) {
-            key[j] = (unsigned long long)val[j] ^ 0x8000000000000000ull;
             int i;
-            alive[j] = small && own_cell(j, i);
-            if (alive[j]) differ |= key[j] ^ ref;
+            if (own_cell(j, i)) val[j] = pool[i];
         }
-        if (small) {
-            const int lz = wave_min_dpp(differ ? __clzll((long long)differ) : 64);
-            if (lane == 63) atomicMin(&common_lz, lz);
+    }
+    if (tid == 0) {
+        sel.n_below = 0;
+        sel.cand_n = 0;
+        sel.count = -1;
+    }
+    pool_s[wave * 64 + lane] = val[0];   // the row below the last of wave - 1
+    if (wave == 1) {
+#pragma unroll
+        for (int j = 0; j < kCached; ++j) pool_s[(kFinishWaves + j) * 64 + lane] = val[j];
+    }
+    __syncthreads();
+
+    // ---- 1. successor bits, one 64-bit word per row and direction; row r + 1 is this wave's next row, or
+    //         the first of the next wave; right neighbours come from the next lane -----------------------------
+    if (!no_fill) {
+        auto from_right = [&](long long v) {
+            const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)v, 0x130 /* wave_shl:1 */, 0xf, 0xf, false);
+            const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(v >> 32), 0x130, 0xf, 0xf, false);
+            return (long long)((unsigned long long)hi << 32 | lo);
+        };
+        const long long next_first = pool_s[(wave + 1 < kFinishWaves ? wave + 1 : wave) * 64 + lane];
+        long long dg_of[kCached + 1];
+#pragma unroll
+        for (int j = 0; j < kCached; ++j) dg_of[j] = from_right(val[j]);
+        dg_of[kCached] = from_right(next_first);
+#pragma unroll
+        for (int j = 0; j < kCached; ++j) {
+            const int r = row0 + j;
+            if (r >= nb) continue;   // wave-uniform
+            const bool inner = r + 1 < nb && lane + 1 < nb;
+            const Succ s = successors(j + 1 < kCached ? val[j + 1 < kCached ? j + 1 : j] : next_first, dg_of[j],
+                                      dg_of[j + 1], inner);
+            const unsigned long long bd = __ballot(s.down), br = __ballot(s.right), bg = __ballot(s.diag);
+            if (lane == 0) {
+                down[r] = bd;
+                right[r] = br;
+                diag[r] = bg;
+            }
+        }
+    }
+    __syncthreads();
+
+    // ---- 2. fill: one wave; the words of row r sit in lane r and move through scalar registers, eight rows at
+    //         a time (rows past the last have no bits and lead nowhere).  Every cell of row 0 and the first of
+    //         every row is a seed: with the down bit of column 0 set throughout, the latter needs no step of
+    //         its own, and whether a walk REACHED column 0 is the down bit as it was. ------------------------------
+    unsigned long long E = nb == 64 ? ~0ull : (1ull << nb) - 1ull, D = ~0ull, G = 0ull;   // "row -1": seeds row 0
+    unsigned long long dw = 0ull, rw = 0ull, gw = 0ull;
+    if (wave == 1 && !no_fill && lane < nb) {
+        dw = down[lane];
+        rw = right[lane];
+        gw = diag[lane];
+    }
+    auto fill_rows = [&](int first, int end) {   // multiples of 8
+        if (no_fill) return;
+        for (int base = first; base < end && base < nb; base += 8) {
+            unsigned long long d8[8], r8[8], g8[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                d8[u] = read_lane_u64(dw | 1ull, base + u);
+                r8[u] = read_lane_u64(rw, base + u);
+                g8[u] = read_lane_u64(gw, base + u);
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const unsigned long long x = (E & D) | ((E & G) << 1);
+                E = x | (((x & r8[u]) + r8[u]) ^ r8[u]);
+                reached[base + u] = E;   // the expanded cells, for fill_done (all lanes the same word)
+                D = d8[u];
+                G = g8[u];
+            }
+        }
+    };
+    auto fill_done = [&]() {   // lane r: the reached word of row r
+        if (no_fill) {
+            reached[lane] = ~0ull;
+            return;
+        }
+        const unsigned long long e = reached[lane];   // written by this wave
+        const unsigned down0 = (unsigned)__builtin_amdgcn_update_dpp(0, (int)((unsigned)dw & 1u), 0x138 /* wave_shr:1 */,
+                                                                     0xf, 0xf, false);
+        reached[lane] = lane == 0 ? rw << 1 : ((e & ~1ull) | down0);
+    };
+
+    // ---- 3. threshold ----------------------------------------------------------------------------------------
+    if (mode == 1) {
+        unsigned long long key = 0ull;
+        auto each = [&](auto&& f) {
+#pragma unroll
+            for (int j = 0; j < kCached; ++j) {
+                int i;
+                const bool ok = own_cell(j, i);
+                f((unsigned long long)val[j] ^ kSign, ok);
+            }
+        };
+        // the same keys, those of wave 1 handed to four other waves
+        const int extra_row = kCached + (wave - 2);   // wave 1 owns rows 4 .. 7
+        const bool extra = wave >= 2 && wave < 2 + kCached && extra_row < nb && lane < nb;
+        const unsigned long long extra_key =
+            extra ? (unsigned long long)pool_s[(kFinishWaves + wave - 2) * 64 + lane] ^ kSign : 0ull;
+        auto each_shared = [&](auto&& f) {
+            each(f);
+            if (wave >= 2 && wave < 2 + kCached) f(extra_key, extra);
+        };
+        {
+            // four cells of each of the rows 0, 4, 8, ..., spread over the columns; wave w ranks samples w, w + 16, ..
+            const int rows4 = (nb + 3) >> 2, r = ((lane >> 2) * rows4) >> 4, c = ((lane & 3) * nb + (((lane >> 2) * nb) >> 4)) >> 2;
+            const unsigned long long mine = (unsigned long long)pool_s[r * 64 + c] ^ kSign;
+            // the wanted rank falls on sample `mid`; seven samples to either side are 2.7 standard deviations
+            // of a sample's rank or more
+            const int mid = (int)((unsigned)k_rank * 64u / (unsigned)n), from = mid - 7, to = mid + 7;
+            if (wave != 1) {
+                for (int t = wave == 0 ? 0 : wave - 1; t < 64; t += kFinishWaves - 1) {
+                    const unsigned long long other = read_lane_u64(mine, t);
+                    const int rank = __popcll(__ballot(mine < other || (mine == other && lane < t)));
+                    if (lane == 0 && rank == from) sel.lo = other;
+                    if (lane == 0 && rank == to) sel.hi = other;
+                }
+                if (tid == 0 && from < 0) sel.lo = 0ull;
+                if (tid == 0 && to > 63) sel.hi = ~0ull;
+            } else {
+                fill_rows(0, 8);
+            }
         }
         __syncthreads();
-        const int shared_bits = small ? common_lz : 0;
-        const int n_passes = (64 - shared_bits + kDigitBits - 1) / kDigitBits;   // 0: all keys are equal
-        unsigned long long prefix = 0ull;
-        if (small && kDigitBits * n_passes < 64) prefix = ref & ~((1ull << (kDigitBits * n_passes)) - 1ull);
-        int k = k_rank;
-#pragma unroll 1
-        for (int pass = 0; pass < n_passes; ++pass) {
-            const int shift = kDigitBits * (n_passes - 1 - pass);   // without shared bits: 55, 44, ..., 0
-            const int top = shift + kDigitBits;                     // bits >= top are already decided
-            unsigned* const h = hist + (pass % 3) * kBins;
-            auto count = [&](unsigned long long u, bool match) {
-                const unsigned digit = (unsigned)(u >> shift) & (unsigned)(kBins - 1);
-                // the leading digits are usually equal for the whole wave: one atomic instead of 64
-                const unsigned long long m = __ballot(match);
-                if (m == 0ull) return;
-                const unsigned first = (unsigned)__builtin_amdgcn_readlane((int)digit, __ffsll((long long)m) - 1);
-                if (__ballot(match && digit == first) == m) {
-                    if (lane == 0) atomicAdd(&h[bin_slot(first)], (unsigned)__popcll(m));
-                } else if (match) {
-                    atomicAdd(&h[bin_slot(digit)], 1u);
-                }
-            };
-            if (small) {
-#pragma unroll
-                for (int j = 0; j < kCached; ++j) count(key[j], alive[j]);
+        const unsigned long long lo = sel.lo, width = sel.hi - lo;
+        const int shift = width >> kDigitBits ? 64 - kDigitBits - __clzll((long long)width) : 0;
+        if (wave != 1) {
+            int n_below = 0;
+            each_shared([&](unsigned long long u, bool active) {
+                n_below += __popcll(__ballot(active && u < lo));
+                if (active && u - lo <= width) atomicAdd(&hist[bin_slot((unsigned)((u - lo) >> shift))], 1u);
+            });
+            if (lane == 0 && n_below) atomicAdd(&sel.n_below, n_below);
+        } else {
+            fill_rows(8, 24);
+        }
+        __syncthreads();
+        const int k = k_rank - sel.n_below;
+        if (wave == 0) {
+            if (k >= 0) scan_histogram(hist, k, &sel);
+        } else if (wave == 1) {
+            fill_rows(24, 40);
+        }
+        __syncthreads();
+        if (sel.count > 0 && sel.count <= 64) {   // the bracket holds the rank, in a bin of few keys
+            const unsigned digit = (unsigned)sel.digit;
+            if (wave != 1) {
+                each_shared([&](unsigned long long u, bool active) {
+                    if (active && u - lo <= width && (unsigned)((u - lo) >> shift) == digit)
+                        sel.cand[atomicAdd(&sel.cand_n, 1)] = u;
+                });
             } else {
-                for (int base = 0; base < n; base += kFinishThreads) {
-                    const int i = base + tid;
-                    const unsigned long long u =
-                        i < n ? ((unsigned long long)pool[i] ^ 0x8000000000000000ull) : 0ull;
-                    count(u, i < n && (top >= 64 || (u >> top) == (prefix >> top)));
-                }
+                fill_rows(40, 56);
             }
             __syncthreads();
-            if (wave != 0) {
-                // the histogram of the pass before (last read before the barrier above) is cleared for the
-                // pass after the next, off the path of the wave that scans
-                unsigned* const hz = hist + ((pass + 2) % 3) * kBins;
-                for (int i = tid - 64; i < kBins; i += kFinishThreads - 64) hz[i] = 0u;
-            } else {
-                // the digit whose bin holds rank k: lane owns digits 32 lane .. 32 lane + 31 as 8 groups of 4
-                const uint4* const h4 = reinterpret_cast<const uint4*>(h);
-                int s4[8], s32 = 0;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const uint4 v = h4[j * 64 + lane];
-                    s4[j] = (int)(v.x + v.y + v.z + v.w);
-                    s32 += s4[j];
-                }
-                const int incl = wave_inclusive_scan_dpp(s32);
-                int e = incl - s32, qj = 0;
-                const bool hit = k >= e && k < incl;   // exactly one lane: the matching keys number more than k
-#pragma unroll
-                for (int j = 0; j < 7; ++j) {
-                    const bool adv = qj == j && k >= e + s4[j];
-                    e = adv ? e + s4[j] : e;
-                    qj = adv ? j + 1 : qj;
-                }
-                const uint4 v = h4[qj * 64 + lane];
-                const int c3[3] = {(int)v.x, (int)v.y, (int)v.z};
-                int qt = 0;
-#pragma unroll
-                for (int j = 0; j < 3; ++j) {
-                    const bool adv = qt == j && k >= e + c3[j];
-                    e = adv ? e + c3[j] : e;
-                    qt = adv ? j + 1 : qt;
-                }
-                if (hit) {
-                    sel_digit = 32 * lane + 4 * qj + qt;
-                    sel_below = e;   // matching keys below that digit
-                    sel_count = (int)(qt == 0 ? v.x : (qt == 1 ? v.y : (qt == 2 ? v.z : v.w)));   // matching keys with that digit
-                }
+            if (wave == 1) {
+                fill_rows(56, 64);
+                fill_done();
             }
+            rank_candidates(k - sel.below, &sel);
             __syncthreads();
-            const unsigned digit = (unsigned)sel_digit;
-            k -= sel_below;
-            prefix |= (unsigned long long)digit << shift;
-#pragma unroll
-            for (int j = 0; j < kCached; ++j)
-                alive[j] = alive[j] && ((unsigned)(key[j] >> shift) & (unsigned)(kBins - 1)) == digit;
-            if (pass + 1 < n_passes && sel_count <= 64) {
-                // Few keys are left (typically after the third pass): instead of the remaining passes they
-                // are collected and one wave ranks them against each other.  k is the rank among them.
-                if (small) {
-#pragma unroll
-                    for (int j = 0; j < kCached; ++j)
-                        if (alive[j]) cand[atomicAdd(&cand_n, 1)] = key[j];
-                } else {
-                    for (int base = 0; base < n; base += kFinishThreads) {
-                        const int i = base + tid;
-                        if (i < n) {
-                            const unsigned long long u = (unsigned long long)pool[i] ^ 0x8000000000000000ull;
-                            if ((u >> shift) == (prefix >> shift)) cand[atomicAdd(&cand_n, 1)] = u;
-                        }
-                    }
-                }
-                __syncthreads();
-                if (wave == 0) {
-                    const int cn = cand_n;   // == sel_count
-                    const unsigned long long mine = lane < cn ? cand[lane] : ~0ull;
-                    int less = 0, same = 0;
-                    for (int t = 0; t < cn; ++t) {
-                        const unsigned long long other = cand[t];
-                        less += other < mine ? 1 : 0;
-                        same += other == mine ? 1 : 0;
-                    }
-                    if (lane < cn && k >= less && k < less + same) sel_key = mine;   // equal keys write the same value
-                }
-                __syncthreads();
-                prefix = sel_key;
-                break;
+            key = sel.key;
+        } else {
+            if (wave == 1) {
+                fill_rows(40, 64);
+                fill_done();
             }
+            key = select_kth(each, (unsigned long long)pool_s[0] ^ kSign, k_rank, hist, &sel);
         }
         if (tid == 0) {
             th.is_int = 1;
-            th.ti = (long long)(prefix ^ 0x8000000000000000ull);
+            th.ti = (long long)(key ^ kSign);
             th.td = (double)th.ti;
         }
     } else if (mode == 2) {
-        // sequential fp64 sums in row-major order: this is the definition, not an optimisation target
-        if (tid == 0) {
-            double sum = 0.0;
-            for (int i = 0; i < n; ++i) sum = sum + (double)pool[i];
-            const double mean = sum / (double)n;
-            double ss = 0.0;
-            for (int i = 0; i < n; ++i) {
-                const double dlt = (double)pool[i] - mean;
-                const double sq = dlt * dlt;
-                ss = ss + sq;
+        // both sums in row-major order: the order is the definition.  pool_s is free from here on (its
+        // rows have been compared): it holds the doubles to be added.
+        double* const xs = reinterpret_cast<double*>(pool_s);
+        if (wave == 1) {
+            fill_rows(0, 64);
+            fill_done();
+        }
+#pragma unroll
+        for (int j = 0; j < kCached; ++j) {
+            int i;
+            if (own_cell(j, i)) xs[i] = (double)val[j];
+        }
+        __syncthreads();
+        if (wave == 0) {
+            const double mean = ordered_sum(xs, n) / (double)n;
+            if (lane == 0) th.td = mean;
+        }
+        __syncthreads();
+        const double mean = th.td;
+#pragma unroll
+        for (int j = 0; j < kCached; ++j) {
+            int i;
+            if (own_cell(j, i)) {
+                const double dlt = (double)val[j] - mean;
+                xs[i] = dlt * dlt;
             }
-            const double var = ss / (double)n;
+        }
+        __syncthreads();
+        if (wave == 0) {
+            const double var = ordered_sum(xs, n) / (double)n;
             const double sd = sqrt(var);
             const double ks = kval * sd;
-            th.is_int = 0;
-            th.ti = 0;
-            th.td = mean + ks;
+            if (lane == 0) {
+                th.is_int = 0;
+                th.ti = 0;
+                th.td = mean + ks;
+            }
         }
     } else {
+        if (wave == 1) {
+            fill_rows(0, 64);
+            fill_done();
+        }
         if (tid == 0) {
             th.is_int = 0;
             th.ti = 0;
@@ -624,233 +744,547 @@ __global__ __launch_bounds__(kFinishThreads) void pattern_finish_kernel(
     }
     __syncthreads();
     const Thresh t = th;
-    if (small) {
-        // the histograms are done with: their LDS now holds the arrays of the steps below
-        for (int i = tid; i < 64 * 128 / 4; i += kFinishThreads) reinterpret_cast<unsigned*>(skew)[i] = 0u;
-        __syncthreads();
-    }
-
-    // ---- 2. per cell: successor bits (which of down / right / diag equal their maximum), the
-    //         "above threshold" bit, and the seed flag (first row and first column) ------------------
-    auto cell_bits = [&](long long x, long long dn, long long rt, long long dg, bool inner) {
-        bool ab;
-        if (t.is_int) ab = x > t.ti;
-        else ab = (double)x > t.td;
-        unsigned m = ab ? kAbove : 0u;
-        if (inner) {
-            long long mx = dn > rt ? dn : rt;
-            mx = mx > dg ? mx : dg;
-            m |= (dn == mx ? kDown : 0u) | (rt == mx ? kRight : 0u) | (dg == mx ? kDiag : 0u);
-        }
-        return m;
-    };
-    if (small) {
-#pragma unroll
-        for (int j = 0; j < kCached; ++j) {
-            int i;
-            if (!own_cell(j, i)) continue;
-            const int r = wave + kFinishWaves * j, c = lane;
-            const bool inner = r + 1 < nb && c + 1 < nb;
-            long long dn = 0, rt = 0, dg = 0;
-            if (inner) {
-                dn = pool_s[i + nb];
-                rt = pool_s[i + 1];
-                dg = pool_s[i + nb + 1];
-            }
-            const unsigned m = cell_bits(val[j], dn, rt, dg, inner);
-            mask[i] = (uint8_t)m;
-            skew[r * 128 + r + c] = (uint8_t)(m & 7u);
-        }
-    } else {
-        for (int i = tid; i < n; i += kFinishThreads) {
-            const int r = i / nb, c = i % nb;
-            const bool inner = r + 1 < nb && c + 1 < nb;
-            long long dn = 0, rt = 0, dg = 0;
-            if (inner) {
-                dn = pool[i + nb];
-                rt = pool[i + 1];
-                dg = pool[i + nb + 1];
-            }
-            mask[i] = (uint8_t)cell_bits(pool[i], dn, rt, dg, inner);
-            expd[i] = no_fill ? (uint8_t)kReached : ((r == 0 || c == 0) ? (uint8_t)kExpanded : (uint8_t)0);
-        }
-    }
-    __syncthreads();
-
-    // ---- 3. fill: every move raises r + c, so anti-diagonal s depends only on s-1 and s-2.  A cell is
-    //         reached iff an expanded predecessor lists it as a successor; reached cells are expanded
-    //         in turn whether or not they exceed the threshold. -------------------------------------
-    if (!no_fill) {
-        if (small) {
-            // One wave, lane = row r.  The row's successor bits sit in 32 registers in anti-diagonal
-            // order, so level s reads a compile-time register; the outgoing bits of the previous
-            // two levels travel in registers and the neighbour row's bits arrive by a one-lane
-            // shift.  Cells outside the matrix have no bits and can neither be reached nor expand.
-            if (wave == 0) {
-                const int r = lane;
-                unsigned sk[32];
-#pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    const uint4 v = reinterpret_cast<const uint4*>(skew + r * 128)[q];
-                    sk[4 * q] = v.x;
-                    sk[4 * q + 1] = v.y;
-                    sk[4 * q + 2] = v.z;
-                    sk[4 * q + 3] = v.w;
-                }
-                unsigned out1 = 0u, out2 = 0u;
-                unsigned rb[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-                for (int s = 0; s < 127; ++s) {
-                    const unsigned m = (sk[s >> 2] >> (8 * (s & 3))) & 7u;
-                    const unsigned both = out1 | (out2 << 8);
-                    const unsigned up = __builtin_amdgcn_update_dpp(0u, both, 0x138 /* wave_shr:1 */,
-                                                                    0xf, 0xf, false);
-                    const unsigned hit = (out1 & kRight) | (up & kDown) | ((up >> 8) & kDiag);
-                    const bool reached = hit != 0u;
-                    const bool expanded = reached || r == 0 || s == r;   // seeds: row 0, column 0
-                    rb[s >> 5] |= (reached ? 1u : 0u) << (s & 31);
-                    out2 = out1;
-                    out1 = expanded ? m : 0u;
-                }
-#pragma unroll
-                for (int q = 0; q < 4; ++q) rbits[r * 4 + q] = rb[q];
-            }
-        } else {
-            for (int s = 1; s <= 2 * nb - 2; ++s) {
-                const int r = tid, c = s - tid;
-                if (r < nb && c >= 0 && c < nb) {
-                    const int i = r * nb + c;
-                    bool reached = false;
-                    if (r >= 1) reached |= (expd[i - nb] & kExpanded) && (mask[i - nb] & kDown);
-                    if (c >= 1) reached |= (expd[i - 1] & kExpanded) && (mask[i - 1] & kRight);
-                    if (r >= 1 && c >= 1)
-                        reached |= (expd[i - nb - 1] & kExpanded) && (mask[i - nb - 1] & kDiag);
-                    if (reached) expd[i] = (uint8_t)(kExpanded | kReached);
-                }
-                __syncthreads();
-            }
-        }
-    }
-    __syncthreads();
     const bool want_bsc = col_ptr != nullptr;
 
-    if (small) {
-        // ---- 4 + 5, nb <= 64: the final mask as one 64-bit word per row (a wave's ballot over the
-        //      row's cells) and per column; every kept cell then finds its place in BSR and BSC from
-        //      population counts of those words, with no pass over the matrix in between -------------
-        auto kept = [&](int r, int c) {
-            if (c >= nb) return false;
-            const bool reached = no_fill || ((rbits[r * 4 + ((r + c) >> 5)] >> ((r + c) & 31)) & 1u) != 0u;
-            return (reached && (mask[r * nb + c] & kAbove)) || r == c;
-        };
-        for (int r = wave; r < nb; r += kFinishWaves) {
-            const bool f = kept(r, lane);
-            if (lane < nb) fl[r * nb + lane] = f ? 1 : 0;
-            const unsigned long long m = __ballot(f);
-            if (lane == 0) rowmask[r] = m;
-        }
-        __syncthreads();
-        {
-            // the column words: lane r holds row r's word, a ballot over bit c is column c; wave w makes the
-            // columns w, w + 16, ...
-            const unsigned long long rm = lane < nb ? rowmask[lane] : 0ull;
-            for (int c = wave; c < nb; c += kFinishWaves) {
-                const unsigned long long cm = __ballot(((rm >> c) & 1ull) != 0ull);
-                if (lane == 0) colmask[c] = cm;
-            }
-        }
-        __syncthreads();
-        if (wave == 0) {
-            const int v = lane < nb ? __popcll(rowmask[lane]) : 0;
-            const int incl = wave_inclusive_scan_dpp(v);
-            if (lane < nb) {
-                line_start[lane] = incl - v;
-                row_ptr[lane] = incl - v;
-            }
-            if (lane == 63) {
-                row_ptr[nb] = incl;
-                *nnzb_out = incl;
-            }
-        } else if (wave == 1 && want_bsc) {
-            const int v = lane < nb ? __popcll(colmask[lane]) : 0;
-            const int incl = wave_inclusive_scan_dpp(v);
-            if (lane < nb) {
-                col_start[lane] = incl - v;
-                col_ptr[lane] = incl - v;
-            }
-            if (lane == 63) col_ptr[nb] = incl;
-        }
-        __syncthreads();
-        for (int r = wave; r < nb; r += kFinishWaves) {
-            const int c = lane;
-            const unsigned long long rm = rowmask[r];
-            if (c < nb && ((rm >> c) & 1ull)) {
-                const int k = line_start[r] + __popcll(rm & ((1ull << c) - 1ull));
-                col_idx[k] = c;
-                if (want_bsc) {
-                    const int k2 = col_start[c] + __popcll(colmask[c] & ((1ull << r) - 1ull));
-                    row_idx[k2] = r;
-                    bsr_pos[k2] = k;
-                }
-            }
-        }
-        return;
-    }
-
-    // ---- 4. fl_out = reached and above the threshold, or on the diagonal; kept in expd for step 5 ---
-    for (int i = tid; i < n; i += kFinishThreads) {
-        const int r = i / nb, c = i % nb;
-        const bool reached = (expd[i] & kReached) != 0;
-        const uint8_t f = ((reached && (mask[i] & kAbove)) || r == c) ? 1 : 0;
-        fl[i] = f;
-        mask[i] = f;
-        mask_t[(long long)c * nb + r] = f;
-    }
-    __syncthreads();
-
-    // ---- 5. compaction: BSR (rows) and BSC (columns); one wave per row / column -------------------
-    for (int r = wave; r < nb; r += kFinishWaves) {
-        const int k = wave_compact<false>(mask + (long long)r * nb, 1, nb, lane, 0, nullptr, nullptr, 0, 0,
-                                          nullptr);
-        if (lane == 0) line_start[r] = k;
-        if (want_bsc) {
-            const int kc = wave_compact<false>(mask_t + (long long)r * nb, 1, nb, lane, 0, nullptr, nullptr,
-                                               0, 0, nullptr);
-            if (lane == 0) col_start[r] = kc;
-        }
+    // ---- 4. fl_out = reached and above the threshold, or on the diagonal: a word per row and per column -------
+#pragma unroll
+    for (int j = 0; j < kCached; ++j) {
+        const int r = row0 + j;
+        if (r >= nb) continue;   // wave-uniform
+        const unsigned long long ab = __ballot(lane < nb && above(val[j], t));
+        const unsigned long long f = (ab & reached[r]) | (1ull << r);
+        if (lane < nb) fl[r * nb + lane] = (uint8_t)((f >> lane) & 1ull);
+        if (lane == 0) rowmask[r] = f;
     }
     __syncthreads();
     {
-        int total = 0;
-        int cnt = tid < nb ? line_start[tid] : 0;   // nb <= 1024 == kFinishThreads
-        int start = block_exclusive_scan(cnt, &total, scan_scratch);
-        if (tid < nb) {
-            line_start[tid] = start;
-            row_ptr[tid] = start;
+        // the column words: lane r holds row r's word, a ballot over bit c is column c; wave w makes the
+        // columns w, w + 16, ...
+        const unsigned long long rm = lane < nb ? rowmask[lane] : 0ull;
+        for (int c = wave; c < nb; c += kFinishWaves) {
+            const unsigned long long cm = __ballot(((rm >> c) & 1ull) != 0ull);
+            if (lane == 0) colmask[c] = cm;
         }
-        if (tid == 0) {
-            row_ptr[nb] = total;
-            *nnzb_out = total;
+    }
+    __syncthreads();
+
+    // ---- 5. compaction: every kept cell finds its place in BSR and BSC from population counts ------------------
+    int total = 0;
+    if (wave == 0) {
+        const int v = lane < nb ? __popcll(rowmask[lane]) : 0;
+        const int incl = wave_inclusive_scan_dpp(v);
+        total = __builtin_amdgcn_readlane(incl, 63);
+        if (lane < nb) {
+            line_start[lane] = incl - v;
+            row_ptr[lane] = incl - v;
         }
-        if (want_bsc) {
-            cnt = tid < nb ? col_start[tid] : 0;
-            start = block_exclusive_scan(cnt, &total, scan_scratch);
-            if (tid < nb) {
-                col_start[tid] = start;
-                col_ptr[tid] = start;
+        if (lane == 63) {
+            row_ptr[nb] = incl;
+            *nnzb_out = incl;
+        }
+    } else if (wave == 1 && want_bsc) {
+        const int v = lane < nb ? __popcll(colmask[lane]) : 0;
+        const int incl = wave_inclusive_scan_dpp(v);
+        if (lane < nb) {
+            col_start[lane] = incl - v;
+            col_ptr[lane] = incl - v;
+        }
+        if (lane == 63) col_ptr[nb] = incl;
+    }
+    __syncthreads();
+    for (int r = wave; r < nb; r += kFinishWaves) {
+        const int c = lane;
+        const unsigned long long rm = rowmask[r];
+        if (c < nb && ((rm >> c) & 1ull)) {
+            const int k = line_start[r] + __popcll(rm & ((1ull << c) - 1ull));
+            col_idx[k] = c;
+            if (want_bsc) {
+                const int k2 = col_start[c] + __popcll(colmask[c] & ((1ull << r) - 1ull));
+                row_idx[k2] = r;
+                bsr_pos[k2] = k;
             }
-            if (tid == 0) col_ptr[nb] = total;
         }
+    }
+    if (nnzb_host) {
+        __syncthreads();   // every wave's stores are out
+        if (tid == 0) __hip_atomic_store(nnzb_host, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+// threshold + fill + compaction, 64 < nb <= 1024 (several kernels)
+// ------------------------------------------------------------------------------------------------
+// Words of 64 columns: W = ceil(nb / 64) per row.  Scratch of the stages, all in the workspace:
+//   cells      grid_pool_kernel: pool_sum; for a quantile also a histogram over 4096 bins that grow with
+//              the value (sign, position of the leading bit, next five bits)
+//   candidates grid_bits_kernel: successor bits of every row; the cells of the bin that holds the wanted
+//              rank, in any order
+//   serial     grid_serial_kernel: workgroup 0 the threshold (order statistic of the candidates), workgroup
+//              1 the fill (the expanded cells of every row): neither needs the other
+//   words      grid_words_kernel: kept bits per row and, transposed, per column, and their counts
+//   index      grid_index_kernel: BSR and BSC
+// Measured at nb = 512: the five
+// kernels take 10 + 9 + 49 + 12 + 10 us, one workgroup with a barrier per anti-diagonal took 2454; the fill's chain, 225 cycles per row, is the longest part.
+constexpr int kGridBins = 4096;
+constexpr int kGridMax = 1024;   // same bound as SPION_MAX_NB of the public header
+
+struct GridScratch {
+    unsigned* hist;              // kGridBins + 4 (counter of the candidates, rank inside the bin), then
+    int* row_cnt;                // kGridMax
+    int* col_cnt;                // kGridMax: one zeroed run of words with hist
+    Thresh* th;
+    unsigned long long* cand;    // nb * nb keys (over the slot sums, which are used up by then)
+    unsigned long long *down, *right, *diag, *reached, *kept, *kept_t;   // nb * W words each
+};
+constexpr int kGridZeroWords = kGridBins + 4 + 2 * kGridMax;
+
+static size_t grid_aux_bytes(size_t nb) {
+    const size_t words = nb * ((nb + 63) / 64);
+    return (kGridZeroWords * 4 + 255) / 256 * 256 + 256 + 6 * words * 8;
+}
+static GridScratch grid_carve(char* aux, void* part, size_t nb) {
+    const size_t words = nb * ((nb + 63) / 64);
+    GridScratch s;
+    s.hist = reinterpret_cast<unsigned*>(aux);
+    s.row_cnt = reinterpret_cast<int*>(s.hist + kGridBins + 4);
+    s.col_cnt = s.row_cnt + kGridMax;
+    char* p = aux + (kGridZeroWords * 4 + 255) / 256 * 256;
+    s.th = reinterpret_cast<Thresh*>(p);
+    s.down = reinterpret_cast<unsigned long long*>(p + 256);
+    s.right = s.down + words;
+    s.diag = s.right + words;
+    s.reached = s.diag + words;
+    s.kept = s.reached + words;
+    s.kept_t = s.kept + words;
+    s.cand = static_cast<unsigned long long*>(part);
+    return s;
+}
+
+// Position of v among 4096 bins that are ordered like the values.
+__device__ __forceinline__ int grid_bin(long long v) {
+    const unsigned long long m = v < 0 ? 0ull - (unsigned long long)v : (unsigned long long)v;
+    int idx = 0;
+    if (m != 0ull) {
+        const int lz = __clzll((long long)m);
+        const unsigned next5 = (unsigned)(((m << lz) << 1) >> 59);
+        idx = (63 - lz) * 32 + (int)next5 + 1;   // 1 .. 2048; 2048 is the most negative value alone
+    }
+    return v < 0 ? 2048 - idx : (idx < 2048 ? 2048 + idx : 4095);
+}
+
+__global__ __launch_bounds__(256) void grid_zero_kernel(unsigned* __restrict__ zero) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < kGridZeroWords) zero[i] = 0u;
+}
+
+// A workgroup takes 1024 cells, 4 per thread, all their loads in flight together.
+__global__ __launch_bounds__(256) void grid_pool_kernel(const long long* __restrict__ part, long long* pool, int nb,
+                                                        int want_hist, unsigned* __restrict__ hist) {
+    __shared__ unsigned h[kGridBins];
+    const int tid = threadIdx.x, n = nb * nb;
+    if (want_hist) {
+        for (int i = tid; i < kGridBins; i += 256) h[i] = 0u;
         __syncthreads();
     }
-    for (int r = wave; r < nb; r += kFinishWaves)
-        wave_compact<true>(mask + (long long)r * nb, 1, nb, lane, line_start[r], col_idx, pos,
-                           (long long)r * nb, 1, nullptr);
-    if (want_bsc) {
-        __syncthreads();   // pos[] of every kept cell is written
-        for (int c = wave; c < nb; c += kFinishWaves)
-            wave_compact<true>(mask_t + (long long)c * nb, 1, nb, lane, col_start[c], row_idx, pos,
-                               (long long)c, nb, bsr_pos);
+    long long v[4];
+    if (part) {
+        PoolParts rec[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int i = blockIdx.x * 1024 + j * 256 + tid, c = i < n ? i : n - 1;
+            rec[j] = load_parts(part, nb, c / nb, c % nb);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int i = blockIdx.x * 1024 + j * 256 + tid, c = i < n ? i : n - 1;
+            v[j] = sum_parts(rec[j], nb, c / nb, c % nb);
+            if (i < n) pool[i] = v[j];
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int i = blockIdx.x * 1024 + j * 256 + tid;
+            v[j] = pool[i < n ? i : n - 1];
+        }
+    }
+    if (!want_hist) return;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const bool ok = blockIdx.x * 1024 + j * 256 + tid < n;
+        const int b = grid_bin(v[j]);
+        const unsigned long long m = __ballot(ok);
+        if (m == 0ull) continue;
+        const int first = __builtin_amdgcn_readlane(b, __ffsll((long long)m) - 1);
+        if (__ballot(ok && b == first) == m) {   // one bin for the whole wave: one atomic
+            if ((tid & 63) == 0) atomicAdd(&h[first], (unsigned)__popcll(m));
+        } else if (ok) {
+            atomicAdd(&h[b], 1u);
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < kGridBins; i += 256)
+        if (h[i]) atomicAdd(&hist[i], h[i]);
+}
+
+// One wave per word (64 cells of a row).  Every workgroup finds the bin of the wanted rank itself: 16
+// bins per thread and two scans.
+__global__ __launch_bounds__(256) void grid_bits_kernel(const long long* __restrict__ pool, int nb, int mode,
+                                                        int k_rank, int no_fill, GridScratch s) {
+    __shared__ int wave_sum[4], sel_bin;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int W = (nb + 63) >> 6;
+    int bin = -1;
+    if (mode == 1) {
+        uint4 q[4];
+        int cnt = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            q[e] = reinterpret_cast<const uint4*>(s.hist)[tid * 4 + e];
+            cnt += (int)(q[e].x + q[e].y + q[e].z + q[e].w);
+        }
+        int incl = wave_inclusive_scan_dpp(cnt);
+        if (lane == 63) wave_sum[wave] = incl;
+        __syncthreads();
+        for (int w = 0; w < wave; ++w) incl += wave_sum[w];
+        int e0 = incl - cnt;
+        if (k_rank >= e0 && k_rank < incl) {   // exactly one thread
+            const unsigned c[16] = {q[0].x, q[0].y, q[0].z, q[0].w, q[1].x, q[1].y, q[1].z, q[1].w,
+                                    q[2].x, q[2].y, q[2].z, q[2].w, q[3].x, q[3].y, q[3].z, q[3].w};
+            int b = 0;
+            bool found = false;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const bool here = !found && k_rank < e0 + (int)c[e];
+                b = here ? e : b;
+                found = found || here;
+                e0 = found ? e0 : e0 + (int)c[e];
+            }
+            sel_bin = tid * 16 + b;
+            if (blockIdx.x == 0) s.hist[kGridBins + 1] = (unsigned)(k_rank - e0);   // rank among the candidates
+        }
+        __syncthreads();
+        bin = sel_bin;
+    }
+    const int word = blockIdx.x * 4 + wave;
+    if (word >= nb * W) return;
+    const int r = word / W, seg = word % W, c = seg * 64 + lane;
+    const bool ok = c < nb, inner = c + 1 < nb && r + 1 < nb;
+    const int i = r * nb + (ok ? c : 0);
+    const long long v = pool[i];
+    if (!no_fill) {
+        const Succ sc = successors(inner ? pool[i + nb] : 0, inner ? pool[i + 1] : 0, inner ? pool[i + nb + 1] : 0, inner);
+        const unsigned long long bd = __ballot(sc.down), br = __ballot(sc.right), bg = __ballot(sc.diag);
+        if (lane == 0) {
+            s.down[word] = bd;
+            s.right[word] = br;
+            s.diag[word] = bg;
+        }
+    }
+    if (mode == 1) {
+        const bool mine = ok && grid_bin(v) == bin;
+        const unsigned long long m = __ballot(mine);
+        if (m != 0ull) {
+            unsigned base = 0;
+            if (lane == 0) base = atomicAdd(&s.hist[kGridBins], (unsigned)__popcll(m));
+            base = (unsigned)__builtin_amdgcn_readfirstlane((int)base);
+            if (mine) s.cand[base + (unsigned)__popcll(m & ((1ull << lane) - 1ull))] = (unsigned long long)v ^ kSign;
+        }
+    }
+}
+
+// The fill on rows of up to 1024 bits: lane l of wave 0 holds columns 32 l .. 32 l + 31.  The carries of a
+// row's addition cross lanes the same way they cross bits: lanes that generate one (the 32-bit sum
+// overflowed) and lanes that pass one on (the sum is all ones) are two bit sets in scalar registers, and
+// which lanes receive a carry is again x | (((x & P) + P) ^ P).  The other waves bring the words of the
+// next kFillRows rows into LDS meanwhile: a trip to memory takes longer than a row.
+constexpr int kFillRows = 32;
+constexpr int kFillWords = kFillRows * 3 * (kGridMax / 32);   // down, right, diagonal words of a piece
+
+__device__ void grid_fill(const GridScratch& s, int nb, unsigned* buf /* 2 * kFillWords, LDS */) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int W2 = 2 * ((nb + 63) >> 6);   // 32-bit words per row
+    const int plane = kFillRows * W2;
+    auto bring = [&](int piece, int first, int threads) {   // rows kFillRows * piece .. of the three arrays
+        const int words = min(kFillRows, nb - piece * kFillRows) * W2;
+        unsigned* const dst = buf + (piece & 1) * kFillWords;
+        const size_t from = (size_t)piece * plane;
+        for (int i = tid - first; i < words; i += threads) {
+            const unsigned d = reinterpret_cast<const unsigned*>(s.down)[from + i];
+            const unsigned r = reinterpret_cast<const unsigned*>(s.right)[from + i];
+            const unsigned g = reinterpret_cast<const unsigned*>(s.diag)[from + i];
+            dst[i] = d;
+            dst[plane + i] = r;
+            dst[2 * plane + i] = g;
+        }
+    };
+    auto meet = [&]() {   // LDS only: the stores of the words already found need not be waited for
+        __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    bring(0, 0, kFinishThreads);
+    meet();
+    const int first_col = 32 * lane;
+    // "row -1": every cell of row 0 is a seed; the first of every row is one too: down bits of column 0 set
+    unsigned E = first_col >= nb ? 0u : (nb - first_col >= 32 ? ~0u : (1u << (nb - first_col)) - 1u), D = ~0u, G = 0u;
+    const unsigned seed = lane == 0 ? 1u : 0u;
+    const int pieces = (nb + kFillRows - 1) / kFillRows;
+    for (int piece = 0; piece < pieces; ++piece) {
+        if (wave != 0) {
+            if (piece + 1 < pieces) bring(piece + 1, 64, kFinishThreads - 64);
+        } else if (lane < W2) {
+            const unsigned* const src = buf + (piece & 1) * kFillWords + lane;
+            unsigned* const out = reinterpret_cast<unsigned*>(s.reached) + (size_t)piece * plane + lane;
+            const int rows = min(kFillRows, nb - piece * kFillRows);
+            constexpr int U = 4;   // rows whose words are requested together, one group ahead
+            unsigned d[2][U], q[2][U], g[2][U];
+            auto request = [&](int h, int r0) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int at = ((r0 + u) & (kFillRows - 1)) * W2;   // behind the last group: row 0 again
+                    d[h][u] = src[at];
+                    q[h][u] = src[plane + at];
+                    g[h][u] = src[2 * plane + at];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            auto work = [&](int h, int r0) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const unsigned eg = E & G;
+                    const unsigned prev = (unsigned)__builtin_amdgcn_update_dpp(0, (int)eg, 0x138 /* wave_shr:1 */, 0xf, 0xf, false);
+                    const unsigned x = (E & D) | __builtin_amdgcn_alignbit(eg, prev, 31);
+                    const unsigned R = q[h][u];
+                    unsigned sum, sum2;
+                    unsigned long long gen, unused;
+                    asm("v_add_co_u32 %0, %1, %2, %3" : "=v"(sum), "=s"(gen) : "v"(x & R), "v"(R));
+                    const unsigned long long pass = __builtin_amdgcn_ballot_w64(sum == ~0u);
+                    gen <<= 1;
+                    const unsigned long long carry = gen | (((gen & pass) + pass) ^ pass);
+                    asm("v_addc_co_u32 %0, %1, %2, 0, %3" : "=v"(sum2), "=s"(unused) : "v"(sum), "s"(carry));
+                    E = x | (sum2 ^ R);
+                    if (r0 + u < rows) out[(size_t)(r0 + u) * W2] = E;   // uniform
+                    D = d[h][u] | seed;
+                    G = g[h][u];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            request(0, 0);
+            for (int r0 = 0; r0 < rows; r0 += 2 * U) {
+                request(1, r0 + U);
+                work(0, r0);
+                request(0, r0 + 2 * U);
+                work(1, r0 + U);   // rows past the last are worked on and not stored
+            }
+        }
+        meet();
+    }
+}
+
+__global__ __launch_bounds__(kFinishThreads) void grid_serial_kernel(const long long* __restrict__ pool, int nb, int mode,
+                                                                     double kval, double t_abs, int no_fill,
+                                                                     GridScratch s) {
+    __shared__ __attribute__((aligned(16))) unsigned hist[3 * kBins];
+    __shared__ SelectShared sel;
+    __shared__ double part_s;
+    const int tid = threadIdx.x, n = nb * nb;
+    if (blockIdx.x == 1) {
+        const int words = nb * ((nb + 63) >> 6);
+        if (no_fill) {
+            for (int i = tid; i < words; i += kFinishThreads) s.reached[i] = ~0ull;
+        } else {
+            static_assert(2 * kFillWords <= 3 * kBins, "the pieces share the histograms' LDS");
+            grid_fill(s, nb, hist);
+        }
+        return;
+    }
+    Thresh t = {0, 0, t_abs};
+    if (mode == 1) {
+        const int m = (int)s.hist[kGridBins];
+        const unsigned long long key = select_kth(
+            [&](auto&& f) {
+                constexpr int kFlight = 16;   // keys requested before the first is used
+                for (int base = 0; base < m; base += kFlight * kFinishThreads) {
+                    unsigned long long u[kFlight];
+#pragma unroll
+                    for (int e = 0; e < kFlight; ++e) {
+                        const int i = base + e * kFinishThreads + tid;
+                        u[e] = s.cand[i < m ? i : 0];
+                    }
+#pragma unroll
+                    for (int e = 0; e < kFlight; ++e) {
+                        const int i = base + e * kFinishThreads + tid;
+                        if (base + e * kFinishThreads < m) f(u[e], i < m);   // uniform
+                    }
+                }
+            },
+            s.cand[0], (int)s.hist[kGridBins + 1], hist, &sel);
+        t.is_int = 1;
+        t.ti = (long long)(key ^ kSign);
+        t.td = (double)t.ti;
+    } else if (mode == 2) {
+        // sequential sums in row-major order (the order is the definition), staged through LDS in pieces
+        double* const xs = reinterpret_cast<double*>(hist);
+        constexpr int kPiece = 3072;
+        static_assert(kPiece * 8 <= 3 * kBins * 4 && kPiece % 16 == 0, "the piece must fit");
+        double mean = 0.0, acc = 0.0;
+        for (int round = 0; round < 2; ++round) {
+            acc = 0.0;
+            for (int base = 0; base < n; base += kPiece) {
+                const int len = n - base < kPiece ? n - base : kPiece;
+                __syncthreads();
+                for (int i = tid; i < len; i += kFinishThreads) {
+                    const double x = (double)pool[base + i], dlt = x - mean;
+                    xs[i] = round == 0 ? x : dlt * dlt;
+                }
+                __syncthreads();
+                if (tid < 64) {
+                    for (int i = 0; i < len; i += 16) {
+                        double v[16];
+                        const int left = len - i;
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) v[e] = xs[i + (e < left ? e : 0)];
+                        if (left >= 16) {
+#pragma unroll
+                            for (int e = 0; e < 16; ++e) acc = acc + v[e];
+                        } else {
+                            for (int e = 0; e < left; ++e) acc = acc + xs[i + e];
+                        }
+                    }
+                }
+            }
+            if (tid == 0) part_s = acc;
+            __syncthreads();
+            acc = part_s / (double)n;
+            if (round == 0) mean = acc;
+        }
+        const double sd = sqrt(acc);
+        const double ks = kval * sd;
+        t.td = mean + ks;
+    }
+    if (tid == 0) *s.th = t;
+}
+
+// One workgroup per 64 x 64 tile of cells: wave w its rows 16 w .. 16 w + 15, one ballot each; the 64 words,
+// transposed by 64 more ballots, are 64 column words.
+__global__ __launch_bounds__(256) void grid_words_kernel(const long long* __restrict__ pool, int nb, int no_fill,
+                                                         GridScratch s, uint8_t* __restrict__ fl) {
+    __shared__ unsigned long long tile[64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int W = (nb + 63) >> 6, rs = blockIdx.x / W, cs = blockIdx.x % W;
+    const int c = cs * 64 + lane;
+    const Thresh t = *s.th;
+    long long v[16];
+    unsigned long long reached16 = 0ull;   // lane j: the word of this wave's row j
+    const int r_first = rs * 64 + wave * 16;
+    if (lane < 16 && r_first + lane < nb) {
+        // a seed is not reached by being one: row 0 is from its left neighbours, column 0 from above
+        const int r = r_first + lane;
+        reached16 = s.reached[r * W + cs];
+        if (!no_fill && r == 0)
+            reached16 = s.right[cs] << 1 | (cs > 0 ? s.right[cs - 1] >> 63 : 0ull);
+        else if (!no_fill && cs == 0)
+            reached16 = (reached16 & ~1ull) | (s.down[(r - 1) * W] & 1ull);
+    }
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        const int r = r_first + j;
+        v[j] = pool[r < nb && c < nb ? r * nb + c : 0];
+    }
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        const int r = rs * 64 + wave * 16 + j;
+        unsigned long long f = 0ull;
+        if (r < nb) {   // wave-uniform
+            const bool ab = c < nb && above(v[j], t);
+            f = __ballot(ab) & read_lane_u64(reached16, j);
+            if (r >> 6 == cs) f |= 1ull << (r & 63);
+            if (c < nb) fl[(size_t)r * nb + c] = (uint8_t)((f >> lane) & 1ull);
+            if (lane == 0) {
+                s.kept[r * W + cs] = f;
+                if (f) atomicAdd(&s.row_cnt[r], __popcll(f));
+            }
+        }
+        if (lane == 0) tile[wave * 16 + j] = f;
+    }
+    __syncthreads();
+    const unsigned long long rw = tile[lane];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        const int cc = cs * 64 + wave * 16 + j;
+        const unsigned long long m = __ballot(((rw >> (wave * 16 + j)) & 1ull) != 0ull);
+        if (lane == 0 && cc < nb) {
+            s.kept_t[cc * W + rs] = m;
+            if (m) atomicAdd(&s.col_cnt[cc], __popcll(m));
+        }
+    }
+}
+
+// One wave per row (BSR) and, behind them, one per column (BSC).  A wave adds up the counts of the lines
+// before its own.
+__global__ __launch_bounds__(256) void grid_index_kernel(int nb, GridScratch s, int* __restrict__ row_ptr,
+                                                         int* __restrict__ col_idx, int* __restrict__ col_ptr,
+                                                         int* __restrict__ row_idx, int* __restrict__ bsr_pos,
+                                                         int* __restrict__ nnzb_out, int* nnzb_host) {
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+    const int W = (nb + 63) >> 6;
+    if (w >= (col_ptr ? 2 * nb : nb)) return;
+    const bool cols = w >= nb;
+    const int line = cols ? w - nb : w;
+    const int* const cnt = cols ? s.col_cnt : s.row_cnt;
+    // everything the wave needs is requested at once: the counts (16 groups of 64 lines at most), its words
+    constexpr int kGroups = kGridMax / 64;
+    int c16[kGroups], rc16[kGroups], before = 0;
+#pragma unroll
+    for (int q = 0; q < kGroups; ++q) {
+        const int i = q * 64 + lane;
+        c16[q] = q < W && i < line ? cnt[i] : 0;
+        rc16[q] = cols && q < W && i < nb ? s.row_cnt[i] : 0;
+    }
+    const unsigned long long words = lane < W ? (cols ? s.kept_t : s.kept)[line * W + lane] : 0ull;
+    const int own = cnt[line];
+#pragma unroll
+    for (int q = 0; q < kGroups; ++q) before += c16[q];
+    int k = __builtin_amdgcn_readlane(wave_inclusive_scan_dpp(before), 63);
+    int* const ptr = cols ? col_ptr : row_ptr;
+    if (lane == 0) {
+        ptr[line] = k;
+        if (line == nb - 1) {
+            const int total = k + own;
+            ptr[nb] = total;
+            if (!cols) {
+                *nnzb_out = total;
+                if (nnzb_host) __hip_atomic_store(nnzb_host, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            }
+        }
+    }
+    int run = 0;   // rows before this group of 64 (columns only)
+#pragma unroll
+    for (int seg = 0; seg < kGroups; ++seg) {
+        if (seg >= W) break;   // uniform
+        const unsigned long long m = read_lane_u64(words, seg);
+        const bool bit = ((m >> lane) & 1ull) != 0ull;
+        const int pos = k + __popcll(m & ((1ull << lane) - 1ull));
+        const int other = seg * 64 + lane;
+        if (!cols) {
+            if (bit) col_idx[pos] = other;
+        } else {
+            // where the row-wise index holds cell (other, line): the row's start + its kept cells before
+            const int rc = rc16[seg];
+            const int incl = wave_inclusive_scan_dpp(rc);
+            if (bit) {
+                const unsigned long long* const row = s.kept + (size_t)other * W;
+                int p = run + incl - rc;
+                for (int q = 0; q < (line >> 6); ++q) p += __popcll(row[q]);
+                p += __popcll(row[line >> 6] & ((1ull << (line & 63)) - 1ull));
+                row_idx[pos] = other;
+                bsr_pos[pos] = p;
+            }
+            run += __builtin_amdgcn_readlane(incl, 63);
+        }
+        k += __popcll(m);
     }
 }
 
@@ -924,21 +1358,24 @@ __global__ __launch_bounds__(1024) void index_check_kernel(
 // ------------------------------------------------------------------------------------------------
 // host launchers
 // ------------------------------------------------------------------------------------------------
-hipError_t launch_conv_pool(const float* A, int L, int bs, int p, long long* part, hipStream_t st) {
-    const int nb = L / bs;
-    const unsigned blocks = (unsigned)nb * (unsigned)nb;
-    // SPION_CONV_WAVES_PER_CU waves per compute unit (256 of them) at block 64, each walking several
-    // input blocks; smaller blocks are fewer bytes per wave, so proportionally more waves
-    auto grid = [&](unsigned waves_per_cu) {
-        const unsigned wgs = (blocks + 3) / 4, cap = 256u * waves_per_cu / 4;
-        return dim3(wgs < cap ? wgs : cap);
-    };
+size_t pattern_part_bytes(size_t nb) { return kSlots * nb * nb * sizeof(long long); }
+size_t pattern_aux_bytes(size_t nb) { return nb > 64 ? grid_aux_bytes(nb) : 0; }
+
+hipError_t launch_conv_pool(const float* A, int L, int bs, int p, long long* part, void* aux, hipStream_t st) {
+    const int nb = L / bs, per_tile = 64 / bs;
+    const unsigned tiles = (unsigned)nb * (unsigned)((nb + per_tile - 1) / per_tile);
+    const dim3 grid((tiles + 3) / 4);
+    // the counters of the grid kernels are cleared on the way; with more than 64 block rows the grid has
+    // more than enough threads for that
+    unsigned* const zero = static_cast<unsigned*>(nb > 64 ? aux : nullptr);
+    const int n_zero = zero ? kGridZeroWords : 0;
+    static_assert(65 * ((65 + 3) / 4) / 4 * 256 >= kGridZeroWords, "one thread per cleared word");
     if (bs == 16)
-        conv_pool_kernel<16><<<grid(4 * SPION_CONV_WAVES_PER_CU), dim3(256), 0, st>>>(A, L, p, part);
+        conv_pool_kernel<16><<<grid, dim3(256), 0, st>>>(A, L, p, part, zero, n_zero);
     else if (bs == 32)
-        conv_pool_kernel<32><<<grid(2 * SPION_CONV_WAVES_PER_CU), dim3(256), 0, st>>>(A, L, p, part);
+        conv_pool_kernel<32><<<grid, dim3(256), 0, st>>>(A, L, p, part, zero, n_zero);
     else
-        conv_pool_kernel<64><<<grid(SPION_CONV_WAVES_PER_CU), dim3(256), 0, st>>>(A, L, p, part);
+        conv_pool_kernel<64><<<grid, dim3(256), 0, st>>>(A, L, p, part, zero, n_zero);
     return hipGetLastError();
 }
 
@@ -947,19 +1384,28 @@ hipError_t launch_pool_gather(const long long* part, int nb, long long* pool, hi
     return hipGetLastError();
 }
 
-hipError_t launch_pattern_finish(const long long* part, long long* pool, int nb, int mode, long long k_rank,
-                                 double kval, double t_abs, int no_fill, uint8_t* mask, uint8_t* expd, int* pos,
-                                 uint8_t* fl, int* row_ptr, int* col_idx, int* col_ptr, int* row_idx,
-                                 int* bsr_pos, int* nnzb, hipStream_t st) {
-    const size_t n = (size_t)nb * nb;
-    // keep static (~25 KB) + dynamic LDS under 64 KB: the three byte arrays if 3n fits, and the
-    // position array (4n more, placed at offset 4n) if 8n fits as well
-    const int use_lds = 8 * n <= 36 * 1024 ? 2 : (3 * n <= 36 * 1024 ? 1 : 0);
-    // nb <= 64: the byte map and, 8-byte aligned behind it, pool_sum itself (36 KB at nb = 64)
-    const size_t dyn = nb <= 64 ? ((n + 7) & ~(size_t)7) + 8 * n : (use_lds == 2 ? 8 * n : (use_lds == 1 ? 3 * n : 0));
-    pattern_finish_kernel<<<dim3(1), dim3(kFinishThreads), dyn, st>>>(
-        part, pool, nb, mode, (int)k_rank, kval, t_abs, no_fill, use_lds, mask, expd, pos, fl, row_ptr, col_idx,
-        col_ptr, row_idx, bsr_pos, nnzb);
+hipError_t launch_pattern_finish(bool from_part, long long* part, long long* pool, int nb, int mode, long long k_rank,
+                                 double kval, double t_abs, int no_fill, void* aux, uint8_t* fl, int* row_ptr,
+                                 int* col_idx, int* col_ptr, int* row_idx, int* bsr_pos, int* nnzb, int* nnzb_host,
+                                 hipStream_t st) {
+    const long long* const src = from_part ? part : nullptr;
+    if (nb <= 64) {   // one workgroup, a wave instruction per row: 64 columns are its limit
+        pattern_finish_kernel<<<dim3(1), dim3(kFinishThreads), 0, st>>>(src, pool, nb, mode, (int)k_rank, kval, t_abs,
+                                                                        no_fill, fl, row_ptr, col_idx, col_ptr,
+                                                                        row_idx, bsr_pos, nnzb, nnzb_host);
+        return hipGetLastError();
+    }
+    const GridScratch s = grid_carve(static_cast<char*>(aux), part, (size_t)nb);
+    const unsigned n = (unsigned)(nb * nb), W = (unsigned)((nb + 63) / 64), words = (unsigned)nb * W;
+    if (!from_part) grid_zero_kernel<<<dim3((kGridZeroWords + 255) / 256), dim3(256), 0, st>>>(s.hist);
+    if (from_part || mode == 1)
+        grid_pool_kernel<<<dim3((n + 1023) / 1024), dim3(256), 0, st>>>(src, pool, nb, mode == 1, s.hist);
+    grid_bits_kernel<<<dim3((words + 3) / 4), dim3(256), 0, st>>>(pool, nb, mode, (int)k_rank, no_fill, s);
+    grid_serial_kernel<<<dim3(2), dim3(kFinishThreads), 0, st>>>(pool, nb, mode, kval, t_abs, no_fill, s);
+    grid_words_kernel<<<dim3(W * W), dim3(256), 0, st>>>(pool, nb, no_fill, s, fl);
+    const unsigned lines = (unsigned)(col_ptr ? 2 * nb : nb);
+    grid_index_kernel<<<dim3((lines + 3) / 4), dim3(256), 0, st>>>(nb, s, row_ptr, col_idx, col_ptr, row_idx, bsr_pos,
+                                                                   nnzb, nnzb_host);
     return hipGetLastError();
 }
 

@@ -4,9 +4,11 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <atomic>
 #include <mutex>
 
 #include "../../include/spion.h"
+#include "spion_host.h"
 #include "spion_internal.h"
 
 // Built-in scratch of spion_pattern_static: the pattern workspace (pooled sums, cell bits, the
@@ -46,18 +48,47 @@ bool shape_ok(int32_t L, int32_t block) {
     return L / block <= SPION_MAX_NB;
 }
 
-// Layout of the pattern workspace for nb*nb = n cells.
+// Layout of the pattern workspace for nb x nb cells.
 struct PatternWs {
-    size_t part_off, pool_off, mask_off, expd_off, pos_off, total;
-    explicit PatternWs(size_t n) {
-        part_off = 0;                                             // one record of 8 int64 per input block
-        pool_off = part_off + align_up(8 * n * sizeof(int64_t));
-        mask_off = pool_off + align_up(n * sizeof(int64_t));
-        expd_off = mask_off + align_up(2 * n);   // cell bits, then the transposed final mask
-        pos_off = expd_off + align_up(n);
-        total = pos_off + align_up(n * sizeof(int32_t));
+    size_t part_off, pool_off, aux_off, total;
+    explicit PatternWs(size_t nb) {
+        part_off = 0;                                                   // slot sums of the input blocks
+        pool_off = part_off + align_up(spion::pattern_part_bytes(nb));
+        aux_off = pool_off + align_up(nb * nb * sizeof(int64_t));       // larger grids: counters and bit rows
+        total = aux_off + align_up(spion::pattern_aux_bytes(nb));
     }
 };
+
+// Words of host memory that the pattern kernels report nnzb to (spion_pattern_wait): one page per process,
+// 64 words a cache line apart, each lent to one call at a time.
+class NotifyWords {
+   public:
+    // nullptr: none free or no pinned memory to be had (the caller then copies nnzb back instead)
+    int32_t* take() {
+        std::lock_guard<std::mutex> lock(mutex_);
+        if (!page_ && !failed_) {
+            void* p = nullptr;
+            failed_ = hipHostMalloc(&p, kWords * kStride * sizeof(int32_t), hipHostMallocPortable | hipHostMallocCoherent) != hipSuccess;
+            page_ = failed_ ? nullptr : static_cast<int32_t*>(p);
+        }
+        if (!page_ || !free_) return nullptr;
+        const int i = __builtin_ctzll(free_);
+        free_ &= free_ - 1;
+        return page_ + i * kStride;
+    }
+    void give(int32_t* w) {
+        std::lock_guard<std::mutex> lock(mutex_);
+        free_ |= 1ull << ((w - page_) / kStride);
+    }
+
+   private:
+    static constexpr int kWords = 64, kStride = 16;
+    std::mutex mutex_;
+    int32_t* page_ = nullptr;
+    bool failed_ = false;
+    uint64_t free_ = ~0ull;
+};
+NotifyWords g_notify;
 
 int attn_params_ok(const spion_attn_params* p, int32_t nnzb) {
     if (p->dtype != SPION_F32 && p->dtype != SPION_BF16) return SPION_ERR_DTYPE;
@@ -112,13 +143,13 @@ const char* spion_strerror(int status) {
 size_t spion_pattern_workspace_bytes(int32_t L, int32_t block) {
     if (!shape_ok(L, block)) return 0;
     const size_t nb = (size_t)(L / block);
-    return PatternWs(nb * nb).total;
+    return PatternWs(nb).total;
 }
 
 static int pattern_impl(const float* A_s, const spion_pattern_params* p, uint8_t* fl_out, int32_t* row_ptr,
                         int32_t* col_idx, int32_t* col_ptr, int32_t* row_idx, int32_t* bsr_pos, int32_t* nnzb,
                         int64_t* pool_sum, void* workspace, size_t workspace_bytes, void* hip_stream,
-                        bool use_static_scratch) {
+                        bool use_static_scratch, int32_t* nnzb_host = nullptr) {
     if (!p) return SPION_ERR_NULL;
     const uint32_t known_flags = SPION_PATTERN_NO_FILL | SPION_PATTERN_POOL_ONLY | SPION_PATTERN_FROM_POOL;
     if (p->reserved != 0 || (p->flags & ~known_flags)) return SPION_ERR_PARAM;
@@ -162,7 +193,7 @@ static int pattern_impl(const float* A_s, const spion_pattern_params* p, uint8_t
             break;
         default: return SPION_ERR_PARAM;
     }
-    const PatternWs ws((size_t)n);
+    const PatternWs ws((size_t)nb);
     if (use_static_scratch) {
         // every argument has passed validation; only now is the device touched
         const int rc = static_scratch(&workspace);
@@ -176,16 +207,14 @@ static int pattern_impl(const float* A_s, const spion_pattern_params* p, uint8_t
                                : reinterpret_cast<long long*>(w + ws.pool_off);
     long long* part = reinterpret_cast<long long*>(w + ws.part_off);
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    if (!from_pool && spion::launch_conv_pool(A_s, p->L, bs, (p->filter - 1) / 2, part, st) != hipSuccess)
+    void* aux = w + ws.aux_off;
+    if (!from_pool && spion::launch_conv_pool(A_s, p->L, bs, (p->filter - 1) / 2, part, aux, st) != hipSuccess)
         return SPION_ERR_HIP;
     if (pool_only)
         return spion::launch_pool_gather(part, nb, pool, st) == hipSuccess ? SPION_OK : SPION_ERR_HIP;
-    if (spion::launch_pattern_finish(from_pool ? nullptr : part, pool, nb, mode, k_rank, kval, t_abs,
-                                     (p->flags & SPION_PATTERN_NO_FILL) ? 1 : 0,
-                                     reinterpret_cast<uint8_t*>(w + ws.mask_off),
-                                     reinterpret_cast<uint8_t*>(w + ws.expd_off),
-                                     reinterpret_cast<int*>(w + ws.pos_off), fl_out, row_ptr, col_idx,
-                                     col_ptr, row_idx, bsr_pos, nnzb, st) != hipSuccess)
+    if (spion::launch_pattern_finish(!from_pool, part, pool, nb, mode, k_rank, kval, t_abs,
+                                     (p->flags & SPION_PATTERN_NO_FILL) ? 1 : 0, aux, fl_out, row_ptr, col_idx,
+                                     col_ptr, row_idx, bsr_pos, nnzb, nnzb_host, st) != hipSuccess)
         return SPION_ERR_HIP;
     return SPION_OK;
 }
@@ -202,6 +231,47 @@ int spion_pattern_static(const float* A_s, const spion_pattern_params* p, uint8_
                          int32_t* nnzb, int64_t* pool_sum, void* hip_stream) {
     return pattern_impl(A_s, p, fl_out, row_ptr, col_idx, col_ptr, row_idx, bsr_pos, nnzb, pool_sum, nullptr, 0,
                         hip_stream, true);
+}
+
+// spion_pattern, then waits for it and returns nnzb in *nnzb_out.  With L / block <= 64 the one workgroup
+// that makes the index reports nnzb to a word of host memory as its last store, which saves the device-to-
+// host copy and the wait for its completion; larger grids end in many workgroups, so the stream is waited
+// for.
+int spion_pattern_wait(const float* A_s, const spion_pattern_params* p, uint8_t* fl_out, int32_t* row_ptr,
+                       int32_t* col_idx, int32_t* col_ptr, int32_t* row_idx, int32_t* bsr_pos, int32_t* nnzb,
+                       int64_t* pool_sum, void* workspace, size_t workspace_bytes, void* hip_stream,
+                       int32_t* nnzb_out) {
+    if (!p || !nnzb_out) return SPION_ERR_NULL;
+    if (p->flags & SPION_PATTERN_POOL_ONLY) return SPION_ERR_PARAM;   // makes no index
+    hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    int32_t* const word = g_notify.take();
+    if (word) __atomic_store_n(word, -1, __ATOMIC_SEQ_CST);
+    int rc = pattern_impl(A_s, p, fl_out, row_ptr, col_idx, col_ptr, row_idx, bsr_pos, nnzb, pool_sum, workspace,
+                          workspace_bytes, hip_stream, false, word);
+    if (rc == SPION_OK) {
+        if (!word) {
+            if (hipMemcpyAsync(nnzb_out, nnzb, sizeof(int32_t), hipMemcpyDeviceToHost, st) != hipSuccess ||
+                hipStreamSynchronize(st) != hipSuccess)
+                rc = SPION_ERR_HIP;
+        } else {
+            int32_t got = -1;
+            if (p->L / p->block <= 64) {
+                // the stream is asked now and then, so that a launch that failed ends the wait
+                for (unsigned spins = 1; (got = __atomic_load_n(word, __ATOMIC_ACQUIRE)) < 0; ++spins) {
+                    if ((spins & 4095u) == 0 && hipStreamQuery(st) != hipErrorNotReady) break;
+                    __builtin_ia32_pause();
+                }
+            }
+            if (got < 0) {
+                if (hipStreamSynchronize(st) != hipSuccess) rc = SPION_ERR_HIP;
+                got = __atomic_load_n(word, __ATOMIC_ACQUIRE);
+            }
+            if (rc == SPION_OK && got < 0) rc = SPION_ERR_HIP;
+            *nnzb_out = got;
+        }
+    }
+    if (word) g_notify.give(word);
+    return rc;
 }
 
 int spion_score_mean(const void* A_maps, int32_t n_maps, int32_t L, int32_t dtype, float* A_s,

@@ -1,0 +1,23 @@
+// Entry points of libspion that its own Python front end uses besides those of include/spion.h.
+#ifndef SPION_HOST_H_
+#define SPION_HOST_H_
+
+#include <stddef.h>
+#include <stdint.h>
+
+#include "../../include/spion.h"
+
+#ifdef __cplusplus
+extern "C" {
+#endif
+
+// spion_pattern, then waits for it on the host; *nnzb_out (HOST) receives nnzb.
+int spion_pattern_wait(const float* A_s, const spion_pattern_params* p, uint8_t* fl_out, int32_t* row_ptr,
+                       int32_t* col_idx, int32_t* col_ptr, int32_t* row_idx, int32_t* bsr_pos, int32_t* nnzb,
+                       int64_t* pool_sum, void* workspace, size_t workspace_bytes, void* hip_stream,
+                       int32_t* nnzb_out);
+
+#ifdef __cplusplus
+}
+#endif
+#endif

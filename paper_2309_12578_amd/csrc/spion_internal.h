@@ -8,15 +8,19 @@
 namespace spion {
 
 // pattern_kernels.hip
-// part: one record of 8 int64 per input block (nb * nb records), written by launch_conv_pool;
-// launch_pool_gather / launch_pattern_finish add them up into pool[nb * nb].  launch_pattern_finish
-// with part == nullptr starts from a given pool[].
-hipError_t launch_conv_pool(const float* A, int L, int bs, int p, long long* part, hipStream_t st);
+// part: the seven slot sums of every input block (pattern_part_bytes), written by launch_conv_pool and added
+// up by launch_pool_gather / launch_pattern_finish into pool[nb * nb].  launch_pattern_finish with
+// from_part == false starts from a given pool[]; part is scratch of the larger grids either way, and so is
+// aux (pattern_aux_bytes).  nnzb_host: nullptr, or a word of host memory that receives nnzb as well; with
+// nb <= 64 it is the last store of the call.
+size_t pattern_part_bytes(size_t nb);
+size_t pattern_aux_bytes(size_t nb);
+hipError_t launch_conv_pool(const float* A, int L, int bs, int p, long long* part, void* aux, hipStream_t st);
 hipError_t launch_pool_gather(const long long* part, int nb, long long* pool, hipStream_t st);
-hipError_t launch_pattern_finish(const long long* part, long long* pool, int nb, int mode, long long k_rank,
-                                 double kval, double t_abs, int no_fill, uint8_t* mask, uint8_t* expd, int* pos,
-                                 uint8_t* fl, int* row_ptr, int* col_idx, int* col_ptr, int* row_idx,
-                                 int* bsr_pos, int* nnzb, hipStream_t st);
+hipError_t launch_pattern_finish(bool from_part, long long* part, long long* pool, int nb, int mode, long long k_rank,
+                                 double kval, double t_abs, int no_fill, void* aux, uint8_t* fl, int* row_ptr,
+                                 int* col_idx, int* col_ptr, int* row_idx, int* bsr_pos, int* nnzb, int* nnzb_host,
+                                 hipStream_t st);
 
 // producer_kernels.hip
 hipError_t launch_index_check(const int* row_ptr, const int* col_idx, const int* col_ptr, const int* row_idx,
