@@ -1,4 +1,5 @@
-"""ctypes binding of libspion.so: same names as the C ABI, argument marshalling only.
+"""ctypes binding of libspion.so: same names as the C ABI, argument marshalling only.  The conveniences at
+the end go through the native call path (csrc/host_ext.cpp), which allocates and launches without ctypes.
 
 PyTorch is used for device memory (``torch.empty`` / ``data_ptr``) and the current HIP stream;
 every step of the path runs inside the library's kernels.
@@ -88,6 +89,20 @@ def load() -> ctypes.CDLL:
     lib.spion_attn_bwd.argtypes = [vp] * 14 + [i32, ctypes.POINTER(_AttnParams), vp, sz, vp]
     _lib = lib
     return lib
+
+
+_host = None
+
+
+def _native():
+    """The native call path (module _spion_host, built next to libspion.so); raise if absent."""
+    global _host
+    if _host is None:
+        load()
+        from . import _spion_host as host
+        host.set_error_class(SpionError)
+        _host = host
+    return _host
 
 
 def spion_version() -> int:
@@ -250,6 +265,11 @@ def generate_pattern(A_s: torch.Tensor, block: int, filt: int, thresh_mode: int,
                       torch.empty(nb + 1, **i32), torch.empty(nb * nb, **i32),
                       torch.empty(nb * nb, **i32), torch.empty(1, **i32),
                       torch.empty((nb, nb), dtype=torch.int64, device=dev))
+    if sync and not flags & SPION_PATTERN_POOL_ONLY:
+        out.nnzb = (_host or _native()).generate_pattern(
+            A_s, L, block, filt, thresh_mode, thresh_value, flags, out.fl_out, out.row_ptr, out.col_idx, out.col_ptr,
+            out.row_idx, out.bsr_pos, out.nnzb_dev, out.pool_sum, workspace)
+        return out
     if workspace is None:
         workspace = torch.empty(max(spion_pattern_workspace_bytes(L, block), 256), dtype=torch.uint8,
                                 device=dev)
@@ -292,26 +312,10 @@ def frobenius_distance(A_prev: torch.Tensor, A_cur: torch.Tensor, out: Optional[
 def attn_fwd(Q, K, V, pat: Pattern, scale: float = 0.0, flags: int = 0,
              O: Optional[torch.Tensor] = None, LSE: Optional[torch.Tensor] = None
              ) -> Tuple[torch.Tensor, torch.Tensor]:
-    B, H, L, d = Q.shape
-    if O is None:
-        O = torch.empty_like(Q)
-    if LSE is None:
-        LSE = torch.empty((B, H, L), dtype=torch.float32, device=Q.device)
-    spion_attn_fwd(Q, K, V, O, LSE, pat.row_ptr, pat.col_idx, pat.nnzb, B, H, L, d, pat.block,
-                   _dtype_code(Q.dtype), scale, flags)
-    return O, LSE
+    return (_host or _native()).attn_fwd(Q, K, V, pat.row_ptr, pat.col_idx, pat.nnzb, pat.block, scale, flags, O, LSE)
 
 
 def attn_bwd(Q, K, V, O, dO, LSE, pat: Pattern, scale: float = 0.0, flags: int = 0,
              dQ=None, dK=None, dV=None, workspace: Optional[torch.Tensor] = None):
-    B, H, L, d = Q.shape
-    dQ = torch.empty_like(Q) if dQ is None else dQ
-    dK = torch.empty_like(Q) if dK is None else dK
-    dV = torch.empty_like(Q) if dV is None else dV
-    code = _dtype_code(Q.dtype)
-    if workspace is None:
-        n = spion_attn_workspace_bytes(B, H, L, d, pat.block, code, pat.nnzb, True, scale, flags)
-        workspace = torch.empty(max(n, 256), dtype=torch.uint8, device=Q.device)
-    spion_attn_bwd(Q, K, V, O, dO, LSE, dQ, dK, dV, pat.row_ptr, pat.col_idx, pat.col_ptr, pat.row_idx,
-                   pat.bsr_pos, pat.nnzb, B, H, L, d, pat.block, code, scale, flags, workspace)
-    return dQ, dK, dV
+    return (_host or _native()).attn_bwd(Q, K, V, O, dO, LSE, pat.row_ptr, pat.col_idx, pat.col_ptr, pat.row_idx,
+                                         pat.bsr_pos, pat.nnzb, pat.block, scale, flags, dQ, dK, dV, workspace)

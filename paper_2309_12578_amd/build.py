@@ -1,14 +1,17 @@
-"""Build libspion.so (HIP, gfx950 only) in-tree with hipcc."""
+"""Build libspion.so (HIP, gfx950 only) with hipcc and the front end's call path (_spion_host.so, host code
+against torch's C++ headers) with g++, in-tree."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libspion.so")
+HOST = os.path.join(HERE, "_spion_host.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
@@ -32,8 +35,33 @@ SOURCES = [
 ]
 
 
+def host_object() -> str:
+    """Compile csrc/host_ext.cpp (no GPU code)."""
+    import torch
+    root = os.path.dirname(torch.__file__)
+    obj = os.path.join(CSRC, "host_ext.o")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-I" + sysconfig.get_paths()["include"], "-isystem", os.path.join(root, "include"), "-isystem",
+           os.path.join(root, "include", "torch", "csrc", "api", "include"), "-isystem", "/opt/rocm/include",
+           "-c", os.path.join(CSRC, "host_ext.cpp"), "-o", obj]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed for host_ext.cpp:\n" + res.stderr)
+    return obj
+
+
+def link_host(obj: str) -> None:
+    import torch
+    cmd = ["g++", "-shared", "-o", HOST, obj, LIB, "-L" + os.path.join(os.path.dirname(torch.__file__), "lib"),
+           "-ltorch_python", "-ltorch", "-ltorch_cpu", "-ltorch_hip", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("link of _spion_host.so failed:\n" + res.stderr)
+
+
 def build(verbose: bool = False) -> str:
-    """Compile every source and link the shared library; always recompiles."""
+    """Compile every source and link the two shared libraries; always recompiles."""
     objs = []
 
     def compile_one(item):
@@ -48,12 +76,15 @@ def build(verbose: bool = False) -> str:
             print(err, file=sys.stderr)
         return obj
 
-    with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
+    with ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as ex:
+        host = ex.submit(host_object)
         objs = list(ex.map(compile_one, SOURCES))
-    cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
+        host = host.result()
+    cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-Wl,-soname,libspion.so", "-o", LIB, *objs]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("link failed:\n" + res.stderr)
+    link_host(host)
     return LIB
 
 

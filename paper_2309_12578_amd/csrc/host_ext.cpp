@@ -1,0 +1,349 @@
+// Native call path of the Python front end (module _spion_host): argument checks, output and workspace
+// allocation from torch's caching allocator, and the autograd node, around the entry points of libspion.
+// A forward + backward of a small problem is bound by the host: through ctypes and a Python autograd
+// function it took 147 us of host time for 20 us of kernels.
+//
+// Plain CPython calling convention (METH_FASTCALL) and direct allocation: no dispatcher, no argument
+// parsing by format strings.
+#include <Python.h>
+
+#include <ATen/hip/EmptyTensor.h>
+#include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
+#include <torch/csrc/autograd/function.h>
+#include <torch/csrc/autograd/functions/utils.h>
+#include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/autograd/saved_variable.h>
+#include <torch/csrc/autograd/variable.h>
+
+#include "spion_host.h"
+
+namespace {
+
+PyObject* g_error_class = nullptr;   // SpionError
+
+// Sets SpionError(code, what); always returns nullptr.
+PyObject* spion_error(int code, const char* what) {
+    PyObject* e = g_error_class ? PyObject_CallFunction(g_error_class, "is", code, what) : nullptr;
+    if (e) {
+        PyErr_SetObject(g_error_class, e);
+        Py_DECREF(e);
+    } else if (!PyErr_Occurred()) {
+        PyErr_Format(PyExc_RuntimeError, "%s: %s (%d)", what, spion_strerror(code), code);
+    }
+    return nullptr;
+}
+
+struct SpionFailure {   // thrown with the Python error to set
+    int code;
+    const char* what;
+};
+
+struct BadValue {   // thrown for a ValueError
+    const char* msg;
+};
+[[noreturn]] void bad_value(const char* msg) { throw BadValue{msg}; }
+
+void* device_ptr(const at::Tensor& t) {
+    if (!t.is_cuda() || !t.is_contiguous()) bad_value("libspion needs contiguous device tensors");
+    return t.data_ptr();
+}
+
+const at::Tensor& tensor_arg(PyObject* o) {
+    if (!THPVariable_Check(o)) bad_value("libspion needs contiguous device tensors");
+    return THPVariable_Unpack(o);
+}
+at::Tensor optional_arg(PyObject* o) { return o == Py_None ? at::Tensor() : tensor_arg(o); }
+
+int int_arg(PyObject* o) {
+    const long v = PyLong_AsLong(o);
+    if (v == -1 && PyErr_Occurred()) throw python_error();
+    return (int)v;
+}
+double double_arg(PyObject* o) {
+    const double v = PyFloat_AsDouble(o);
+    if (v == -1.0 && PyErr_Occurred()) throw python_error();
+    return v;
+}
+
+void* current_stream() { return c10::hip::getCurrentHIPStream().stream(); }
+
+at::Tensor new_like(const at::Tensor& t) {
+    return at::Tensor(at::detail::empty_cuda(t.sizes(), t.scalar_type(), t.device(), std::nullopt));
+}
+at::Tensor new_bytes(size_t n, const at::Tensor& like) {
+    return at::Tensor(at::detail::empty_cuda({(int64_t)(n < 256 ? 256 : n)}, at::kByte, like.device(), std::nullopt));
+}
+
+// One pattern index and the parameters of a call.
+struct Index {
+    at::Tensor row_ptr, col_idx, col_ptr, row_idx, bsr_pos;
+    int nnzb = 0, block = 0;
+    float scale = 0.f;
+    unsigned flags = 0;
+};
+
+spion_attn_params params_of(const at::Tensor& q, const Index& ix) {
+    if (q.dim() != 4) bad_value("expected tensors of shape [B, H, L, d]");
+    spion_attn_params p;
+    p.B = (int32_t)q.size(0);
+    p.H = (int32_t)q.size(1);
+    p.L = (int32_t)q.size(2);
+    p.d = (int32_t)q.size(3);
+    p.block = ix.block;
+    if (q.scalar_type() == at::kFloat) p.dtype = SPION_F32;
+    else if (q.scalar_type() == at::kBFloat16) p.dtype = SPION_BF16;
+    else bad_value("unsupported dtype");
+    p.scale = ix.scale;
+    p.flags = ix.flags;
+    return p;
+}
+
+// The kernels take every size from Q: a smaller tensor beside it would be read or written past its end.
+void same_size(const at::Tensor& q, const at::Tensor& t) {
+    if (t.numel() != q.numel() || t.scalar_type() != q.scalar_type()) bad_value("Q, K, V and their companions must agree in shape and dtype");
+}
+void same_rows(const at::Tensor& q, const at::Tensor& lse) {
+    if (lse.numel() * q.size(3) != q.numel() || lse.scalar_type() != at::kFloat) bad_value("LSE must be fp32 [B, H, L]");
+}
+
+void forward(const at::Tensor& q, const at::Tensor& k, const at::Tensor& v, const Index& ix, at::Tensor& o, at::Tensor& lse) {
+    device_ptr(q);
+    const spion_attn_params p = params_of(q, ix);
+    same_size(q, k);
+    same_size(q, v);
+    if (!o.defined()) o = new_like(q);
+    else same_size(q, o);
+    if (!lse.defined())
+        lse = at::Tensor(at::detail::empty_cuda({q.size(0), q.size(1), q.size(2)}, at::kFloat, q.device(), std::nullopt));
+    else same_rows(q, lse);
+    const int rc = spion_attn_fwd(device_ptr(q), device_ptr(k), device_ptr(v), device_ptr(o), (float*)device_ptr(lse),
+                                  (const int32_t*)device_ptr(ix.row_ptr), (const int32_t*)device_ptr(ix.col_idx),
+                                  ix.nnzb, &p, nullptr, 0, current_stream());
+    if (rc != SPION_OK) throw SpionFailure{rc, "spion_attn_fwd"};
+}
+
+void backward(const at::Tensor& q, const at::Tensor& k, const at::Tensor& v, const at::Tensor& o, const at::Tensor& grad,
+              const at::Tensor& lse, const Index& ix, at::Tensor& dq, at::Tensor& dk, at::Tensor& dv, at::Tensor& ws) {
+    device_ptr(q);
+    const spion_attn_params p = params_of(q, ix);
+    for (const at::Tensor* t : {&k, &v, &o, &grad}) same_size(q, *t);
+    same_rows(q, lse);
+    for (at::Tensor* t : {&dq, &dk, &dv}) {
+        if (!t->defined()) *t = new_like(q);
+        else same_size(q, *t);
+    }
+    if (!ws.defined()) {
+        const size_t n = spion_attn_workspace_bytes(&p, ix.nnzb, 1);
+        if (n == (size_t)-1) throw SpionFailure{SPION_ERR_SHAPE, "spion_attn_workspace_bytes"};
+        ws = new_bytes(n, q);
+    }
+    const int rc = spion_attn_bwd(device_ptr(q), device_ptr(k), device_ptr(v), device_ptr(o), device_ptr(grad),
+                                  (const float*)device_ptr(lse), device_ptr(dq), device_ptr(dk), device_ptr(dv),
+                                  (const int32_t*)device_ptr(ix.row_ptr), (const int32_t*)device_ptr(ix.col_idx),
+                                  (const int32_t*)device_ptr(ix.col_ptr), (const int32_t*)device_ptr(ix.row_idx),
+                                  (const int32_t*)device_ptr(ix.bsr_pos), ix.nnzb, &p, device_ptr(ws),
+                                  (size_t)ws.nbytes(), current_stream());
+    if (rc != SPION_OK) throw SpionFailure{rc, "spion_attn_bwd"};
+}
+
+template <class F>
+PyObject* torch_guarded(F&& f) {
+    HANDLE_TH_ERRORS
+    return f();
+    END_HANDLE_TH_ERRORS
+}
+// Runs f with C++ failures turned into Python errors.
+template <class F>
+PyObject* guarded(F&& f) {
+    try {
+        return torch_guarded(f);
+    } catch (const SpionFailure& e) {
+        return spion_error(e.code, e.what);
+    } catch (const BadValue& e) {
+        PyErr_SetString(PyExc_ValueError, e.msg);
+        return nullptr;
+    }
+}
+
+bool arg_count(Py_ssize_t got, Py_ssize_t want, const char* name) {
+    if (got == want) return true;
+    PyErr_Format(PyExc_TypeError, "%s takes %zd arguments, got %zd", name, want, got);
+    return false;
+}
+
+PyObject* wrap(const at::Tensor& t) { return THPVariable_Wrap(t); }
+
+// attn_fwd(Q, K, V, row_ptr, col_idx, nnzb, block, scale, flags, O | None, LSE | None) -> (O, LSE)
+PyObject* py_attn_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    if (!arg_count(n, 11, "attn_fwd")) return nullptr;
+    return guarded([&]() -> PyObject* {
+        Index ix;
+        ix.row_ptr = tensor_arg(a[3]);
+        ix.col_idx = tensor_arg(a[4]);
+        ix.nnzb = int_arg(a[5]);
+        ix.block = int_arg(a[6]);
+        ix.scale = (float)double_arg(a[7]);
+        ix.flags = (unsigned)int_arg(a[8]);
+        at::Tensor o = optional_arg(a[9]), lse = optional_arg(a[10]);
+        forward(tensor_arg(a[0]), tensor_arg(a[1]), tensor_arg(a[2]), ix, o, lse);
+        PyObject* r = PyTuple_New(2);
+        if (!r) return nullptr;
+        PyTuple_SET_ITEM(r, 0, wrap(o));
+        PyTuple_SET_ITEM(r, 1, wrap(lse));
+        return r;
+    });
+}
+
+// attn_bwd(Q, K, V, O, dO, LSE, row_ptr, col_idx, col_ptr, row_idx, bsr_pos, nnzb, block, scale, flags,
+//          dQ | None, dK | None, dV | None, workspace | None) -> (dQ, dK, dV)
+PyObject* py_attn_bwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    if (!arg_count(n, 19, "attn_bwd")) return nullptr;
+    return guarded([&]() -> PyObject* {
+        Index ix;
+        ix.row_ptr = tensor_arg(a[6]);
+        ix.col_idx = tensor_arg(a[7]);
+        ix.col_ptr = tensor_arg(a[8]);
+        ix.row_idx = tensor_arg(a[9]);
+        ix.bsr_pos = tensor_arg(a[10]);
+        ix.nnzb = int_arg(a[11]);
+        ix.block = int_arg(a[12]);
+        ix.scale = (float)double_arg(a[13]);
+        ix.flags = (unsigned)int_arg(a[14]);
+        at::Tensor dq = optional_arg(a[15]), dk = optional_arg(a[16]), dv = optional_arg(a[17]), ws = optional_arg(a[18]);
+        backward(tensor_arg(a[0]), tensor_arg(a[1]), tensor_arg(a[2]), tensor_arg(a[3]), tensor_arg(a[4]),
+                 tensor_arg(a[5]), ix, dq, dk, dv, ws);
+        PyObject* r = PyTuple_New(3);
+        if (!r) return nullptr;
+        PyTuple_SET_ITEM(r, 0, wrap(dq));
+        PyTuple_SET_ITEM(r, 1, wrap(dk));
+        PyTuple_SET_ITEM(r, 2, wrap(dv));
+        return r;
+    });
+}
+
+// The gradient of sparse_attention.  Saves what the backward entry point takes; one pass computes all three.
+struct SparseAttentionBackward : public torch::autograd::Node {
+    torch::autograd::SavedVariable q, k, v, o, lse;
+    Index ix;
+
+    std::string name() const override { return "SparseAttentionBackward"; }
+
+    void release_variables() override {
+        for (torch::autograd::SavedVariable* s : {&q, &k, &v, &o, &lse}) s->reset_data();
+    }
+
+    torch::autograd::variable_list apply(torch::autograd::variable_list&& grads) override {
+        torch::autograd::variable_list out(3);
+        const at::Tensor& g = grads[0];
+        if (!g.defined()) return out;
+        at::NoGradGuard no_grad;   // the gradients are not differentiated again
+        at::Tensor ws;
+        try {
+            backward(q.unpack(), k.unpack(), v.unpack(), o.unpack(shared_from_this()), g.contiguous(), lse.unpack(), ix,
+                     out[0], out[1], out[2], ws);
+        } catch (const SpionFailure& e) {
+            PyGILState_STATE gil = PyGILState_Ensure();
+            spion_error(e.code, e.what);
+            python_error err;
+            err.persist();
+            PyGILState_Release(gil);
+            throw err;
+        } catch (const BadValue& e) {
+            TORCH_CHECK_VALUE(false, e.msg);
+        }
+        return out;
+    }
+};
+
+// sparse_attention(Q, K, V, row_ptr, col_idx, col_ptr, row_idx, bsr_pos, nnzb, block, scale, flags) -> O
+PyObject* py_sparse_attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    if (!arg_count(n, 12, "sparse_attention")) return nullptr;
+    return guarded([&]() -> PyObject* {
+        const at::Tensor &q = tensor_arg(a[0]), &k = tensor_arg(a[1]), &v = tensor_arg(a[2]);
+        Index ix;
+        ix.row_ptr = tensor_arg(a[3]);
+        ix.col_idx = tensor_arg(a[4]);
+        ix.nnzb = int_arg(a[8]);
+        ix.block = int_arg(a[9]);
+        ix.scale = (float)double_arg(a[10]);
+        ix.flags = (unsigned)int_arg(a[11]);
+        const bool grad = torch::autograd::compute_requires_grad(q, k, v);
+        at::Tensor o, lse, qc, kc, vc;
+        {
+            at::NoGradGuard no_grad;
+            qc = q.contiguous();
+            kc = k.contiguous();
+            vc = v.contiguous();
+            forward(qc, kc, vc, ix, o, lse);
+        }
+        if (grad) {
+            ix.col_ptr = tensor_arg(a[5]);
+            ix.row_idx = tensor_arg(a[6]);
+            ix.bsr_pos = tensor_arg(a[7]);
+            auto node = std::shared_ptr<SparseAttentionBackward>(new SparseAttentionBackward(), torch::autograd::deleteNode);
+            node->set_next_edges(torch::autograd::collect_next_edges(q, k, v));
+            node->q = torch::autograd::SavedVariable(qc, false);
+            node->k = torch::autograd::SavedVariable(kc, false);
+            node->v = torch::autograd::SavedVariable(vc, false);
+            node->lse = torch::autograd::SavedVariable(lse, false);
+            node->ix = std::move(ix);
+            torch::autograd::set_history(o, node);
+            node->o = torch::autograd::SavedVariable(o, true);
+        }
+        return wrap(o);
+    });
+}
+
+// generate_pattern(A_s, L, block, filter, mode, value, flags, fl_out, row_ptr, col_idx, col_ptr, row_idx, bsr_pos,
+//                  nnzb, pool_sum, workspace | None) -> nnzb, after the pattern is complete
+PyObject* py_generate_pattern(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    if (!arg_count(n, 16, "generate_pattern")) return nullptr;
+    return guarded([&]() -> PyObject* {
+        const at::Tensor& A = tensor_arg(a[0]);
+        device_ptr(A);
+        spion_pattern_params p;
+        p.L = int_arg(a[1]);
+        p.block = int_arg(a[2]);
+        p.filter = int_arg(a[3]);
+        p.thresh_mode = int_arg(a[4]);
+        p.thresh_value = double_arg(a[5]);
+        p.flags = (uint32_t)int_arg(a[6]);
+        p.reserved = 0;
+        void* ptr[8];
+        for (int i = 0; i < 8; ++i) ptr[i] = a[7 + i] == Py_None ? nullptr : device_ptr(tensor_arg(a[7 + i]));
+        at::Tensor ws = optional_arg(a[15]);
+        if (!ws.defined()) ws = new_bytes(spion_pattern_workspace_bytes(p.L, p.block), A);
+        void *score = device_ptr(A), *work = device_ptr(ws), *stream = current_stream();
+        const size_t work_bytes = (size_t)ws.nbytes();
+        int32_t nnzb = -1;
+        int rc;
+        Py_BEGIN_ALLOW_THREADS
+        rc = spion_pattern_wait((const float*)score, &p, (uint8_t*)ptr[0], (int32_t*)ptr[1], (int32_t*)ptr[2],
+                                (int32_t*)ptr[3], (int32_t*)ptr[4], (int32_t*)ptr[5], (int32_t*)ptr[6], (int64_t*)ptr[7],
+                                work, work_bytes, stream, &nnzb);
+        Py_END_ALLOW_THREADS
+        if (rc != SPION_OK) throw SpionFailure{rc, "spion_pattern"};
+        return PyLong_FromLong(nnzb);
+    });
+}
+
+PyObject* py_set_error_class(PyObject*, PyObject* cls) {
+    Py_INCREF(cls);
+    Py_XSETREF(g_error_class, cls);
+    Py_RETURN_NONE;
+}
+
+PyMethodDef kMethods[] = {
+    {"attn_fwd", (PyCFunction)(void*)py_attn_fwd, METH_FASTCALL, nullptr},
+    {"attn_bwd", (PyCFunction)(void*)py_attn_bwd, METH_FASTCALL, nullptr},
+    {"sparse_attention", (PyCFunction)(void*)py_sparse_attention, METH_FASTCALL, nullptr},
+    {"generate_pattern", (PyCFunction)(void*)py_generate_pattern, METH_FASTCALL, nullptr},
+    {"set_error_class", py_set_error_class, METH_O, nullptr},
+    {nullptr, nullptr, 0, nullptr},
+};
+PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_spion_host", nullptr, -1, kMethods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__spion_host(void) { return PyModule_Create(&kModule); }

@@ -1263,28 +1263,29 @@ __global__ __launch_bounds__(256) void grid_index_kernel(int nb, GridScratch s, 
     int run = 0;   // rows before this group of 64 (columns only)
 #pragma unroll
     for (int seg = 0; seg < kGroups; ++seg) {
-        if (seg >= W) break;   // uniform
-        const unsigned long long m = read_lane_u64(words, seg);
-        const bool bit = ((m >> lane) & 1ull) != 0ull;
-        const int pos = k + __popcll(m & ((1ull << lane) - 1ull));
-        const int other = seg * 64 + lane;
-        if (!cols) {
-            if (bit) col_idx[pos] = other;
-        } else {
-            // where the row-wise index holds cell (other, line): the row's start + its kept cells before
-            const int rc = rc16[seg];
-            const int incl = wave_inclusive_scan_dpp(rc);
-            if (bit) {
-                const unsigned long long* const row = s.kept + (size_t)other * W;
-                int p = run + incl - rc;
-                for (int q = 0; q < (line >> 6); ++q) p += __popcll(row[q]);
-                p += __popcll(row[line >> 6] & ((1ull << (line & 63)) - 1ull));
-                row_idx[pos] = other;
-                bsr_pos[pos] = p;
+        if (seg < W) {   // uniform
+            const unsigned long long m = read_lane_u64(words, seg);
+            const bool bit = ((m >> lane) & 1ull) != 0ull;
+            const int pos = k + __popcll(m & ((1ull << lane) - 1ull));
+            const int other = seg * 64 + lane;
+            if (!cols) {
+                if (bit) col_idx[pos] = other;
+            } else {
+                // where the row-wise index holds cell (other, line): the row's start + its kept cells before
+                const int rc = rc16[seg];
+                const int incl = wave_inclusive_scan_dpp(rc);
+                if (bit) {
+                    const unsigned long long* const row = s.kept + (size_t)other * W;
+                    int p = run + incl - rc;
+                    for (int q = 0; q < (line >> 6); ++q) p += __popcll(row[q]);
+                    p += __popcll(row[line >> 6] & ((1ull << (line & 63)) - 1ull));
+                    row_idx[pos] = other;
+                    bsr_pos[pos] = p;
+                }
+                run += __builtin_amdgcn_readlane(incl, 63);
             }
-            run += __builtin_amdgcn_readlane(incl, 63);
+            k += __popcll(m);
         }
-        k += __popcll(m);
     }
 }
 
