@@ -41,18 +41,71 @@ __device__ __forceinline__ void stage_ready(bool younger_in_flight) {
     asm volatile("" ::: "memory");
 }
 
+// Which block row the workgroup number l of the `heads` heads of an XCD takes, when there are more workgroups
+// than run at once: the rows with more than twice the mean number of kept blocks first, of all the heads (a
+// row of 80 blocks that starts last runs alone for as long as everything before it took), then head by
+// head the others, so that neighbours in time share K and V in the XCD's L2.
+// All lanes of the calling wave must be active.
+struct RowOfHead {
+    int row, head;
+};
+__device__ __forceinline__ RowOfHead long_rows_first(const int* __restrict__ row_ptr, int nb, int heads, int l, int lane) {
+    const int limit = 2 * row_ptr[nb] / nb;
+    int n_long = 0;
+    for (int base = 0; base < nb; base += 64) {
+        const int r = base + lane;
+        n_long += __popcll(__ballot(r < nb && row_ptr[r + 1] - row_ptr[r] > limit));
+    }
+    const bool want_long = l < heads * n_long;
+    int head, rank;
+    if (want_long) {
+        head = l % heads;
+        rank = l / heads;
+    } else {
+        head = (l - heads * n_long) / (nb - n_long);
+        rank = (l - heads * n_long) % (nb - n_long);
+    }
+    for (int base = 0; base < nb; base += 64) {   // the counts are in the cache by now
+        const int r = base + lane;
+        const unsigned long long mine = __ballot(r < nb && (row_ptr[r + 1] - row_ptr[r] > limit) == want_long);
+        const int cnt = __popcll(mine);
+        if (rank < cnt) {
+            const unsigned long long hit = __ballot(((mine >> lane) & 1ull) && lanes_below(mine) == rank);
+            return {base + __ffsll((long long)hit) - 1, head};
+        }
+        rank -= cnt;
+    }
+    return {0, head};
+}
+
+// How far (in log2 units) a score may lie above the value its row's exponentials are taken against before the
+// running sums are rescaled.  P = exp2(s - m) above 1 is as exact as below (bf16 keeps its relative
+// error, the fp32 sums have range to spare), so what a row's maximum does inside this slack need not be
+// known: a lane looks at its own 16 scores only, and the reduction over the lanes of a row, the rescaling and
+// the branch are left to the first block of a row and to scores that really run away.
+constexpr float kRescaleSlack = 30.f;
+
 template <int BS>
 __global__ __launch_bounds__(BS * 4) void attn_fwd_bf16_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     bf16_t* __restrict__ O, float* __restrict__ LSE, const int* __restrict__ row_ptr,
-    const int* __restrict__ col_idx, int L, int nb, int total, float scale_log2, int paper_denom) {
+    const int* __restrict__ col_idx, int L, int nb, int total, int sort_rows, float scale_log2, int paper_denom) {
     constexpr int NKT = BS / 16;
     __shared__ __attribute__((aligned(16))) KvSmem<BS> sm0, sm1;
 
-    const int vid = xcd_remap(blockIdx.x, total);
-    const int I = vid % nb, bh = vid / nb;
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int bh, I;
+    if (sort_rows) {
+        const int heads = total / nb, split = (heads & 7) == 0 ? 8 : 1;   // heads shared out over the XCDs, as below
+        const RowOfHead at = long_rows_first(row_ptr, nb, heads / split, blockIdx.x / split, lane);
+        bh = (int)(blockIdx.x % split) * (heads / split) + at.head;
+        I = at.row;
+    } else {
+        const int vid = xcd_remap(blockIdx.x, total);
+        bh = vid / nb;
+        I = vid % nb;
+    }
     const size_t head = (size_t)bh * L * kD;
     const int qrow = I * BS + wave * 16 + r;
     const SwzLane sl(r, g);
@@ -77,6 +130,14 @@ __global__ __launch_bounds__(BS * 4) void attn_fwd_bf16_kernel(
         const int j = walk_index(t < last ? t : last, pd);
         return j < 8 ? pick8(first, j) : cols[j];
     };
+    // the same for t >= 2: the first 64 blocks of the walk sit one per lane (one readlane instead of thirty
+    // scalar instructions a step); older than block 1's tiles, so the wait of step 0 covers the load
+    int walk_v = 0;
+    if (n > 2) walk_v = cols[walk_index(lane < last ? lane : last, pd)];
+    auto later_col = [&](int t) {
+        const int u = t < last ? t : last;
+        return u < 64 ? __builtin_amdgcn_readlane(walk_v, u) : cols[walk_index(u, pd)];
+    };
     if (pd < 0 && n > 0) {
         // no diagonal block in this row: once everyone's early load has landed, load block 0 over it
         __builtin_amdgcn_s_waitcnt(kWaitVm0);
@@ -86,9 +147,9 @@ __global__ __launch_bounds__(BS * 4) void attn_fwd_bf16_kernel(
     }
     // the second block goes out as soon as its index is known; it is the youngest load from here on
     if (n > 0) issue(sm1, col_at(1));   // (a one-block row loads its block twice: keeps the wait below uniform)
-    int Jnext = n > 0 ? col_at(2) : 0;   // block of step it + 1, for it >= 1
 
-    float m = -INFINITY;   // running row maximum in log2 units (score * scale * log2 e)
+    float m = -INFINITY;   // what the row's exponentials are taken against, log2 units (score * scale * log2 e)
+    float limit = -INFINITY;   // m + kRescaleSlack
     f32x4 lacc = f32x4{0.f, 0.f, 0.f, 0.f};   // running row sum, replicated in its 4 elements
     f32x4 oacc[4];
 #pragma unroll
@@ -102,8 +163,7 @@ __global__ __launch_bounds__(BS * 4) void attn_fwd_bf16_kernel(
         // four youngest loads: whatever else the prologue stored or loaded after them only adds waiting)
         stage_ready(it == 0);
         if (it > 0) {
-            if (it + 1 < n) issue(tgt, Jnext);
-            Jnext = col_at(it + 2);
+            if (it + 1 < n) issue(tgt, later_col(it + 1));
         }
         // S^T tile kt: [key 16 kt + 4 g + i][query r]; all K fragments are requested up front
         bf16x8 kfr[NKT][2];
@@ -113,7 +173,6 @@ __global__ __launch_bounds__(BS * 4) void attn_fwd_bf16_kernel(
             for (int c = 0; c < 2; ++c)
                 kfr[kt][c] = *reinterpret_cast<const bf16x8*>(cur.k + kt * 16 * kD + sl.frag[c]);
         f32x4 s[NKT];
-        float mx = -INFINITY;
 #pragma unroll
         for (int kt = 0; kt < NKT; ++kt) {
             s[kt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -130,14 +189,16 @@ __global__ __launch_bounds__(BS * 4) void attn_fwd_bf16_kernel(
             vop[j] = join(lds_read_tr(cur.v + o), lds_read_tr(cur.v + 16 * kD + o));
         }
         __builtin_amdgcn_sched_barrier(0);
+        float mx = s[0][0];
 #pragma unroll
         for (int kt = 0; kt < NKT; ++kt)
 #pragma unroll
             for (int i = 0; i < 4; ++i) mx = fmaxf(mx, s[kt][i]);
-        mx = group_max(mx);
-        const float m_new = fmaxf(m, mx * scale_log2);
-        if (__any(m_new > m)) {   // some row's running maximum moved: rescale what is accumulated
+        if (__any(mx * scale_log2 > limit)) {   // always at step 0
+            const float m_new = fmaxf(m, group_max(mx) * scale_log2);
             const float alpha = fast_exp2(m - m_new);
+            m = m_new;
+            limit = m_new + kRescaleSlack;
             lacc *= alpha;
 #pragma unroll
             for (int dt = 0; dt < 4; ++dt) oacc[dt] *= alpha;
@@ -146,14 +207,13 @@ __global__ __launch_bounds__(BS * 4) void attn_fwd_bf16_kernel(
 #pragma unroll
         for (int kt = 0; kt < NKT; ++kt) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) s[kt][i] = fast_exp2(fmaf(s[kt][i], scale_log2, -m_new));
+            for (int i = 0; i < 4; ++i) s[kt][i] = fast_exp2(fmaf(s[kt][i], scale_log2, -m));
             pq[kt] = to_quad<bf16_t>(s[kt]);
         }
         // row sums on the MFMA pipe: a tile of ones times P^T adds up each owned row's probabilities
         // (the bf16 values that also enter P V), every accumulator element holding the same sum
 #pragma unroll
         for (int pc = 0; pc < BS / 32; ++pc) lacc = mma_d(lacc, ones, join(pq[2 * pc], pq[2 * pc + 1]));
-        m = m_new;
 #pragma unroll
         for (int j = 0; j < NM; ++j) {
             const int pc = j >> 2;
@@ -196,9 +256,13 @@ template <int BS>
 hipError_t fwd_bf16(const AttnShape& s, const void* Q, const void* K, const void* V, void* O, float* LSE,
                     const int* row_ptr, const int* col_idx, hipStream_t st) {
     const int total = s.nb * s.BH;
+    // 4 (block 64) or 8 (block 32) workgroups fit a compute unit; where all run at once their order is immaterial,
+    // and finding a row by its rank costs a workgroup half a microsecond
+    const int sort_rows = total > 256 * (BS == 64 ? 4 : 8);
     attn_fwd_bf16_kernel<BS><<<dim3((unsigned)total), dim3(BS * 4), 0, st>>>(
         static_cast<const bf16_t*>(Q), static_cast<const bf16_t*>(K), static_cast<const bf16_t*>(V),
-        static_cast<bf16_t*>(O), LSE, row_ptr, col_idx, s.L, s.nb, total, s.scale * kLog2e, s.paper_denom);
+        static_cast<bf16_t*>(O), LSE, row_ptr, col_idx, s.L, s.nb, total, sort_rows, s.scale * kLog2e,
+        s.paper_denom);
     return hipGetLastError();
 }
 

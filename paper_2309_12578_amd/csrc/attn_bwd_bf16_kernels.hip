@@ -35,10 +35,6 @@ struct KeyItem {
     int slot;   // partial slot, -1: the item covers its whole column and writes dK / dV itself
 };
 
-__device__ __forceinline__ int lanes_below(unsigned long long mask) {
-    return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0));
-}
-
 // All lanes of the calling wave must be active; the result is wave-uniform.
 __device__ __forceinline__ KeyItem key_item_lookup(const int* __restrict__ col_ptr, int nb, int w, int lane) {
     KeyItem none = {-1, 0, 0, -1};

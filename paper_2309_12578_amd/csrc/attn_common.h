@@ -201,6 +201,11 @@ __device__ __forceinline__ int wave_incl_scan(int v, int /*lane*/) {
     return v;
 }
 
+// How many lanes below the calling one are set in `mask`.
+__device__ __forceinline__ int lanes_below(unsigned long long mask) {
+    return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0));
+}
+
 __device__ void build_key_schedule(const int* __restrict__ col_ptr, const int* __restrict__ row_idx, int nb,
                                    int w_max, int split_max, int4* __restrict__ sched,
                                    int4* __restrict__ split, int lane) {

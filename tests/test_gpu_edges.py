@@ -47,3 +47,38 @@ def test_pattern_at_the_edges_of_the_splits(sp, nb, block, ties):
     _same_pattern(sp, A, block, 1, si.T_MEAN_KSTD, 0.5)
     _same_pattern(sp, A, block, p_max, si.T_ABS, float(A.mean()) * p_max)
     _same_pattern(sp, A, block, 5, si.T_QUANTILE, 0.9, flags=sp.SPION_PATTERN_NO_FILL, variant="C")
+
+
+def _attention(sp, Q, K, V, dO, fl, block, dtype, heads, flags=0):
+    """Relative errors (2-norm and max) of O, dQ, dK, dV of the given heads against the fp64 oracle."""
+    from test_gpu_parity import _run_attention_case
+    return _run_attention_case(sp, Q, K, V, dO, fl, block, dtype, flags=flags, heads=heads)
+
+
+@pytest.mark.parametrize("block", [32, 64])
+def test_forward_scores_that_run_away_from_the_first_block(sp, block):
+    """Scores of later blocks far above everything in the block a row starts with (and, in other rows, far
+    below): the running sums are rescaled in the middle of the walk, once or several times."""
+    nb, BH, d = 6, 2, 64
+    L = nb * block
+    rng = np.random.default_rng(block)
+    Q, K, V, dO = [rng.standard_normal((BH, L, d), dtype=np.float32) for _ in range(4)]
+    Q[:, :, 0] = 8.0
+    for j in range(nb):                                     # scores 8 * K[..., 0] / 8: -60, -10, 0, 25, 70, 150
+        K[:, j * block:(j + 1) * block, 0] = (-60.0, -10.0, 0.0, 25.0, 70.0, 150.0)[j]
+    Q, K, V, dO = [si.round_to_dtype(t, "bf16") for t in (Q, K, V, dO)]
+    fl = np.tril(np.ones((nb, nb), dtype=np.uint8)) | np.eye(nb, k=2, dtype=np.uint8)
+    fl[1, :] = 1
+    _attention(sp, Q, K, V, dO, fl, block, "bf16", None)
+
+
+def test_forward_more_rows_than_run_at_once(sp):
+    # 130 x 16 workgroups of block 32: rows are started in the order of their length class, long ones first
+    nb, BH, block, d = 130, 16, 32, 64
+    rng = np.random.default_rng(4)
+    Q, K, V, dO = [si.round_to_dtype(rng.standard_normal((BH, nb * block, d), dtype=np.float32), "bf16") for _ in range(4)]
+    fl = si.random_block_mask(nb, 0.02, seed=3)
+    fl[[0, 63, 64, 129], :] = 1
+    fl[64, 64] = 0
+    fl[100, :] = 0
+    _attention(sp, Q, K, V, dO, fl, block, "bf16", [0, 9])
