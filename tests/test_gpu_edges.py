@@ -62,14 +62,22 @@ def test_forward_scores_that_run_away_from_the_first_block(sp, block):
     nb, BH, d = 6, 2, 64
     L = nb * block
     rng = np.random.default_rng(block)
-    Q, K, V, dO = [rng.standard_normal((BH, L, d), dtype=np.float32) for _ in range(4)]
+    Q, K, V = [rng.standard_normal((BH, L, d), dtype=np.float32) for _ in range(3)]
     Q[:, :, 0] = 8.0
     for j in range(nb):                                     # scores 8 * K[..., 0] / 8: -60, -10, 0, 25, 70, 150
         K[:, j * block:(j + 1) * block, 0] = (-60.0, -10.0, 0.0, 25.0, 70.0, 150.0)[j]
-    Q, K, V, dO = [si.round_to_dtype(t, "bf16") for t in (Q, K, V, dO)]
+    Q, K, V = [si.round_to_dtype(t, "bf16") for t in (Q, K, V)]
     fl = np.tril(np.ones((nb, nb), dtype=np.uint8)) | np.eye(nb, k=2, dtype=np.uint8)
     fl[1, :] = 1
-    _attention(sp, Q, K, V, dO, fl, block, "bf16", None)
+    # O and LSE only: with probabilities this close to 0 and 1 the gradients are differences of nearly equal
+    # bf16 numbers
+    from test_gpu_parity import _pattern_from_mask
+    q, k, v = [torch.from_numpy(t).cuda().to(torch.bfloat16).view(1, BH, L, d) for t in (Q, K, V)]
+    O, LSE = sp.attn_fwd(q, k, v, _pattern_from_mask(sp, fl, block))
+    rO, rLSE = oracle.attn_fwd(Q, K, V, oracle.upsample(fl, block))
+    x = O.float().cpu().numpy().reshape(BH, L, d)
+    assert np.linalg.norm(x - rO) <= 2e-2 * np.linalg.norm(rO) and np.abs(x - rO).max() <= 2e-2 * np.abs(rO).max()
+    assert np.abs(LSE.cpu().numpy().reshape(BH, L) - rLSE).max() <= 1e-3 * np.abs(rLSE).max()
 
 
 def test_forward_more_rows_than_run_at_once(sp):
