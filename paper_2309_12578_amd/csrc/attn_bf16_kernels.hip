@@ -78,13 +78,6 @@ __device__ __forceinline__ RowOfHead long_rows_first(const int* __restrict__ row
     return {0, head};
 }
 
-// How far (in log2 units) a score may lie above the value its row's exponentials are taken against before the
-// running sums are rescaled.  P = exp2(s - m) above 1 is as exact as below (bf16 keeps its relative
-// error, the fp32 sums have range to spare), so what a row's maximum does inside this slack need not be
-// known: a lane looks at its own 16 scores only, and the reduction over the lanes of a row, the rescaling and
-// the branch are left to the first block of a row and to scores that really run away.
-constexpr float kRescaleSlack = 30.f;
-
 template <int BS>
 __global__ __launch_bounds__(BS * 4) void attn_fwd_bf16_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,

@@ -19,8 +19,6 @@ __device__ __forceinline__ bf16x4 lds_read_tr(const bf16_t* p) {
     return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr)p);
 }
 
-__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-
 // Workgroups are dealt round-robin to the 8 XCDs in id order.  Give XCD x the x-th contiguous
 // eighth of the (head-major) work so that the K / V (or Q / dO) rows of a head stay in one L2.
 __device__ __forceinline__ int xcd_remap(int id, int total) {

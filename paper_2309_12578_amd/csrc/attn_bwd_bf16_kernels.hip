@@ -18,93 +18,10 @@
 
 #include "attn_bf16_tiles.h"
 #include "attn_common.h"
+#include "attn_key_items.h"
 #include "spion_internal.h"
 
 namespace spion {
-
-// ------------------------------------------------------------------------------------------------
-// Key-side work items, derived from col_ptr alone (the same list for every head).  A column with cnt
-// kept rows is cut into nch = ceil(cnt / kChunk) near-equal chunks if cnt > kChunk, else it is one
-// item (also when cnt == 0: its dK / dV must still be written as zeros).  Items are numbered with
-// the chunks of split columns first, in column order (they are the longest and start first), then
-// the unsplit columns in column order.  Chunk number w of that first group writes partial slot w.
-// ------------------------------------------------------------------------------------------------
-struct KeyItem {
-    int J;      // block column, -1: no such item
-    int kb, ke; // BSC entries [kb, ke)
-    int slot;   // partial slot, -1: the item covers its whole column and writes dK / dV itself
-};
-
-// All lanes of the calling wave must be active; the result is wave-uniform.
-__device__ __forceinline__ KeyItem key_item_lookup(const int* __restrict__ col_ptr, int nb, int w, int lane) {
-    KeyItem none = {-1, 0, 0, -1};
-    int run = 0;   // chunks of split columns in the column groups before this one
-    int c0_first = 0, cnt_first = 0;   // columns 0 .. 63, kept for the second search
-    for (int base = 0; base < nb; base += 64) {
-        const int J = base + lane;
-        const bool valid = J < nb;
-        const int c0 = valid ? col_ptr[J] : 0, cnt = valid ? col_ptr[J + 1] - c0 : 0;
-        if (base == 0) {
-            c0_first = c0;
-            cnt_first = cnt;
-        }
-        const int nch = cnt > kChunk ? (cnt + kChunk - 1) / kChunk : 0;
-        const int incl = wave_incl_scan(nch, lane);
-        const int lo = run + incl - nch;
-        const unsigned long long hit = __ballot(nch > 0 && w >= lo && w < lo + nch);
-        if (hit) {
-            const int src = __ffsll((long long)hit) - 1;
-            const int c0s = __builtin_amdgcn_readlane(c0, src), cnts = __builtin_amdgcn_readlane(cnt, src);
-            const int nchs = __builtin_amdgcn_readlane(nch, src);
-            int ci = w - __builtin_amdgcn_readlane(lo, src);
-            ci = ci < 0 ? 0 : (ci >= nchs ? nchs - 1 : ci);
-            KeyItem it = {base + src, c0s + (ci * cnts) / nchs, c0s + ((ci + 1) * cnts) / nchs, w};
-            return it;
-        }
-        run += __builtin_amdgcn_readlane(incl, 63);
-    }
-    int u = w - run;   // index among the unsplit columns
-    for (int base = 0; base < nb; base += 64) {
-        const int J = base + lane;
-        const bool valid = J < nb;
-        int c0 = c0_first, c1 = c0_first + cnt_first;
-        if (base != 0) {
-            c0 = valid ? col_ptr[J] : 0;
-            c1 = valid ? col_ptr[J + 1] : 0;
-        }
-        const unsigned long long whole = __ballot(valid && c1 - c0 <= kChunk);
-        const unsigned long long hit = __ballot(valid && c1 - c0 <= kChunk && lanes_below(whole) == u);
-        if (hit) {
-            const int src = __ffsll((long long)hit) - 1;
-            KeyItem it = {base + src, __builtin_amdgcn_readlane(c0, src), __builtin_amdgcn_readlane(c1, src), -1};
-            return it;
-        }
-        u -= __popcll(whole);
-    }
-    return none;
-}
-
-// The m-th split column: {J, first partial slot, chunks}; J < 0 if there are fewer.
-__device__ __forceinline__ int4 split_column_lookup(const int* __restrict__ col_ptr, int nb, int m, int lane) {
-    int run = 0;
-    for (int base = 0; base < nb; base += 64) {
-        const int J = base + lane;
-        const bool valid = J < nb;
-        const int cnt = valid ? col_ptr[J + 1] - col_ptr[J] : 0;
-        const int nch = cnt > kChunk ? (cnt + kChunk - 1) / kChunk : 0;
-        const int incl = wave_incl_scan(nch, lane);
-        const unsigned long long split = __ballot(nch > 0);
-        const unsigned long long hit = __ballot(nch > 0 && lanes_below(split) == m);
-        if (hit) {
-            const int src = __ffsll((long long)hit) - 1;
-            const int nchs = __builtin_amdgcn_readlane(nch, src);
-            return make_int4(base + src, run + __builtin_amdgcn_readlane(incl, src) - nchs, nchs, 0);
-        }
-        m -= __popcll(split);
-        run += __builtin_amdgcn_readlane(incl, 63);
-    }
-    return make_int4(-1, 0, 0, 0);
-}
 
 // Own loads landed (up to `younger` younger ones may stay in flight: 0 or 4), previous LDS reads done,
 // then meet the other waves.  A bare barrier: the fences of __syncthreads would wait for every load
@@ -303,7 +220,7 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
     // ============================================================================================
     // key side: work item idx of head bh.  {Q, dO, O} tiles and LSE of a block row in two stages.
     // ============================================================================================
-    const KeyItem item = key_item_lookup(col_ptr, nb, idx, lane);
+    const KeyItem item = key_item_lookup(col_ptr, nb, kChunk, idx, lane);
     if (item.J < 0) return;
     const int J = item.J, n = item.ke - item.kb, slot = item.slot;
     const int krow = J * BS + wave * 16 + r;
@@ -448,67 +365,34 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
     }
 }
 
-// Adds the partial tiles of every split block column, in chunk order.  Workgroup = (head, m-th split
-// column, part): 256 threads, one float4 of the output tile each, bs / 16 parts per tile, so that the
-// loads of all chunks of a float4 are in flight together.
-template <int BS>
-__global__ __launch_bounds__(256) void attn_bwd_bf16_reduce_kernel(
-    const float* __restrict__ partial, const int* __restrict__ col_ptr, int nb, int split_max, int n_slots,
-    bf16_t* __restrict__ dK, bf16_t* __restrict__ dV, int L, float scale) {
-    constexpr int PARTS = BS / 16;
-    const int part = blockIdx.x % PARTS, m = (blockIdx.x / PARTS) % split_max;
-    const int bh = blockIdx.x / (PARTS * split_max);
-    const int4 info = split_column_lookup(col_ptr, nb, m, threadIdx.x & 63);   // {J, first slot, chunks}
-    if (info.x < 0) return;
-    const int v = part * 256 + threadIdx.x;
-    const float* pk = partial + ((size_t)bh * n_slots + info.y) * (2 * BS * kD) + v * 4;
-    f32x4 ak = f32x4{0.f, 0.f, 0.f, 0.f}, av = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-    for (int c = 0; c < info.z; ++c) {
-        ak += *reinterpret_cast<const f32x4*>(pk + (size_t)c * (2 * BS * kD));
-        av += *reinterpret_cast<const f32x4*>(pk + (size_t)c * (2 * BS * kD) + BS * kD);
-    }
-    const size_t out = (size_t)bh * L * kD + (size_t)info.x * BS * kD + v * 4;
-    store_quad<bf16_t>(dK + out, ak * scale);
-    store_quad<bf16_t>(dV + out, av);
-}
-
 // ------------------------------------------------------------------------------------------------
 // launcher (called by the dispatch in attn_kernels.hip).  phases: bit 0 query side, bit 1 key side.
 // ------------------------------------------------------------------------------------------------
 template <int BS>
 hipError_t bwd_bf16(const AttnShape& s, const void* Q, const void* K, const void* V, const void* O,
                     const void* dO, const float* LSE, void* dQ, void* dK, void* dV, const int* row_ptr,
-                    const int* col_idx, const int* col_ptr, const int* row_idx, int nnzb, int w_max,
-                    int split_max, int n_slots, float* partial, hipStream_t st) {
+                    const int* col_idx, const int* col_ptr, const int* row_idx, const BwdWorkspace& ws,
+                    float* partial, hipStream_t st) {
     const bool rows = (s.bwd_phases & 1) != 0, keys = (s.bwd_phases & 2) != 0;
-    // the chunks of split columns are the first work items; about nnzb / kChunk of them
-    int w_first = nnzb / kChunk + 1;
-    if (w_first > w_max) w_first = w_max;
-    const int n_key_a = keys ? w_first : 0, n_rows = rows ? s.nb : 0, n_key_c = keys ? w_max - w_first : 0;
+    const int n_key_a = keys ? ws.w_first : 0, n_rows = rows ? s.nb : 0, n_key_c = keys ? ws.w_max - ws.w_first : 0;
     const long long total = (long long)s.BH * (n_key_a + n_rows + n_key_c);
     if (total > 0) {
         attn_bwd_bf16_kernel<BS><<<dim3((unsigned)total), dim3(BS * 4), 0, st>>>(
             static_cast<const bf16_t*>(Q), static_cast<const bf16_t*>(K), static_cast<const bf16_t*>(V),
             static_cast<const bf16_t*>(O), static_cast<const bf16_t*>(dO), LSE, static_cast<bf16_t*>(dQ),
             static_cast<bf16_t*>(dK), static_cast<bf16_t*>(dV), row_ptr, col_idx, col_ptr, row_idx, partial,
-            n_slots, s.BH, s.L, s.nb, n_key_a, n_rows, n_key_c, w_first, s.scale, s.scale * kLog2e);
+            ws.n_slots, s.BH, s.L, s.nb, n_key_a, n_rows, n_key_c, ws.w_first, s.scale, s.scale * kLog2e);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (keys && split_max > 0) {
-        attn_bwd_bf16_reduce_kernel<BS><<<dim3((unsigned)(split_max * s.BH * (BS / 16))), dim3(256), 0, st>>>(
-            partial, col_ptr, s.nb, split_max, n_slots, static_cast<bf16_t*>(dK), static_cast<bf16_t*>(dV), s.L,
-            s.scale);
-    }
-    return hipGetLastError();
+    return keys ? launch_bwd_reduce<bf16_t, BS>(s, ws, partial, col_ptr, dK, dV, st) : hipSuccess;
 }
 
 template hipError_t bwd_bf16<32>(const AttnShape&, const void*, const void*, const void*, const void*,
                                  const void*, const float*, void*, void*, void*, const int*, const int*,
-                                 const int*, const int*, int, int, int, int, float*, hipStream_t);
+                                 const int*, const int*, const BwdWorkspace&, float*, hipStream_t);
 template hipError_t bwd_bf16<64>(const AttnShape&, const void*, const void*, const void*, const void*,
                                  const void*, const float*, void*, void*, void*, const int*, const int*,
-                                 const int*, const int*, int, int, int, int, float*, hipStream_t);
+                                 const int*, const int*, const BwdWorkspace&, float*, hipStream_t);
 
 }  // namespace spion

@@ -1,353 +1,636 @@
 // Block-sparse attention forward and backward for gfx950 (Eq. 5 / Algorithm 5 lines 4-7 of the SPION
-// paper, softmax as in Algorithm 6, gradient by the chain rule).
+// paper, softmax as in Algorithm 6, gradient by the chain rule): fp32 with every block size, bf16 with
+// block size 16, and the dispatch over all variants.
 //
 // One pattern (BSR, plus BSC for the backward) is shared by all batch items and heads.  A kept block
 // is a dense bs x bs tile, so SDDMM and SpMM inside it are dense contractions and run on MFMA; the
 // row softmax is fused between them and never touches HBM.
 //
-// Wave-level tiling (wave64).  A wave owns 16 rows (queries in the row-walking kernels, keys in the
-// column-walking one) and all 64 head-dim columns.  Every product is issued so that the 16 owned
-// rows sit on the N index of a 16x16 MFMA tile: lane l then holds values for owned row l % 16 only,
-// which makes row statistics (max, sum, LSE, delta) lane-uniform scalars, and makes an fp32
-// accumulator tile directly usable as the B operand of the next product (accumulator element i of
-// lane group g = l / 16 is contraction index 4 g + i, the same lanes a B fragment needs).
+// Work split.  A wave owns 16 or 32 rows (queries on the query side, keys on the key side) and walks 16-row
+// tiles of the other side that the index lists for them; up to four waves share the tiles of the same rows
+// (wave w takes tiles w, w + 4, ...) and add up their accumulators through LDS once, at the end.  At the sizes that
+// use these kernels the longest row's or column's chain of tiles is what takes the time (a pattern's one or two
+// long rows are 4 times the average, and there are too few rows to fill the machine otherwise): four waves
+// cut the chain by four, and since a tile belongs to one wave, nothing inside the loop needs a barrier.
+// Measured against one wave per 16 rows with the tiles staged through LDS for the whole workgroup:
+// fp32, 8 heads of 2048 tokens, block 32, 410 blocks: forward 70 -> 26 us, backward 179 -> 58 us (the
+// products alone take 5.6 and 20 us at the matrix cores' fp32 rate); bf16, 9 heads of 1936, block 16, 1171
+// blocks: 40 -> 12 and 67 -> 34 us.
 //
-// The other operand of a product that contracts over keys (or queries) must be read along that
-// index; tiles are therefore staged in LDS twice where needed: row-major [row][d] for products that
-// contract over d, and transposed [d][row] for products that contract over rows.
+// Operands come from global memory straight into registers.  Every product has the owned rows on the N
+// index of a 16x16 MFMA tile: lane l = 16 g + r holds values of owned row r, which makes row statistics
+// lane-uniform scalars, and makes an accumulator tile directly the B operand of the next product
+// (element i of lane group g is contraction index 4 g + i).  The A operand of a product that contracts over d
+// is a tile's rows (load_rows).  The A operand of a product that contracts over the tile's rows has, in lane
+// (r, g), rows 4 g + i and some column set of its own for r: with columns 4 r + e (load_cols) these are
+// 16 (8) contiguous bytes per row, i.e. whole rows per load instruction and no transpose; MFMA number e then
+// yields output columns 4 m + e at M index m, so that a lane ends up with 16 consecutive columns.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include "attn_common.h"
+#include "attn_key_items.h"
 #include "spion_internal.h"
 
 namespace spion {
 
+namespace {
+
+constexpr int kPatchLd = kD + 4;   // floats per row of the merge area: b128 accesses of 16 rows hit all banks evenly
+
+// How a workgroup's waves share its work: WQ sets of 16 NQ owned rows, each with WT waves that take every WT-th
+// step of the other side's tiles.
+template <typename T, int BS, int NQ_, int WT_, int WQ_>
+struct Split {
+    static constexpr int NQ = NQ_, WT = WT_, WQ = WQ_, W = WT * WQ;
+    static constexpr int OWN = 16 * NQ * WQ;          // rows of a workgroup
+    static constexpr int PARTS = BS / OWN;            // workgroups per block row or column
+    static constexpr int TPB = BS / 16;               // 16-row tiles per block
+    static constexpr int KT = sizeof(T) == 2 ? 2 : 1; // tiles per step: a bf16 MFMA contracts over 32 rows
+    static constexpr int STRIDE = WT * KT;            // tiles per step of all WT waves
+    static constexpr int NDC = kD / Elem<T>::KC;
+};
+// The default, for rows long or few: every row's tiles over four waves (32 owned rows halve the tile traffic
+// per product where the block has them).
+template <typename T, int BS> using SplitFew = Split<T, BS, BS == 16 ? 1 : 2, 4, 1>;
+// Many block rows of few tiles, see many_short_rows(): the start of a workgroup (index, owned rows) and its
+// merge cost more than the tiles, so fewer waves share a row.
+template <typename T, int BS> struct SplitMany;   // forward, backward, backward of rows with hardly more than one block
+template <typename T> struct SplitMany<T, 16> {
+    typedef SplitFew<T, 16> fwd;
+    typedef Split<T, 16, 1, 2, 1> bwd, bwd_single;
+};
+template <typename T> struct SplitMany<T, 32> {
+    typedef Split<T, 32, 1, 2, 2> fwd;
+    typedef Split<T, 32, 2, 2, 1> bwd;
+    typedef Split<T, 32, 2, 1, 1> bwd_single;
+};
+template <typename T> struct SplitMany<T, 64> {
+    typedef Split<T, 64, 1, 1, 4> fwd;
+    typedef Split<T, 64, 2, 2, 2> bwd;
+    typedef Split<T, 64, 2, 1, 2> bwd_single;
+};
+
+__device__ __forceinline__ float exp2_of(float x, float) { return exp2f(x); }
+__device__ __forceinline__ float exp2_of(float x, bf16_t) { return fast_exp2(x); }
+
+// lane (r, g): elements g EPL .. of each d chunk of row r
+template <typename T>
+__device__ __forceinline__ void load_rows(typename Elem<T>::Frag (&f)[kD / Elem<T>::KC], const T* tile, int r, int g) {
+#pragma unroll
+    for (int c = 0; c < kD / Elem<T>::KC; ++c)
+        f[c] = *reinterpret_cast<const typename Elem<T>::Frag*>(tile + r * kD + g * Elem<T>::EPL + c * Elem<T>::KC);
+}
+// lane (r, g): columns 4 r .. 4 r + 3 of rows 4 g + i
+template <typename T>
+__device__ __forceinline__ void load_cols(typename Elem<T>::Quad (&v)[4], const T* tile, int r, int g) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        v[i] = *reinterpret_cast<const typename Elem<T>::Quad*>(tile + 4 * g * kD + 4 * r + i * kD);
+}
+template <typename V, int N>
+__device__ __forceinline__ void clear(V (&v)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = V{};
+}
+
+// acc[e][M = m] += sum over the tiles' rows of tile[row][4 m + e] * x[row][owned]
+template <int NQ, int KT>
+__device__ __forceinline__ void mma_cols(f32x4 (&acc)[NQ][4], const f32x4 (&v)[KT][4], const f32x4 (&x)[NQ][KT]) {
+#pragma unroll
+    for (int j = 0; j < 4 * KT; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int h = 0; h < NQ; ++h)
+                acc[h][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[j / 4][j % 4][e], x[h][j / 4][j % 4], acc[h][e], 0, 0, 0);
+}
+template <int NQ>
+__device__ __forceinline__ void mma_cols(f32x4 (&acc)[NQ][4], const bf16x4 (&v)[2][4], const bf16x4 (&x)[NQ][2]) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const bf16x8 a = {v[0][0][e], v[0][1][e], v[0][2][e], v[0][3][e], v[1][0][e], v[1][1][e], v[1][2][e], v[1][3][e]};
+#pragma unroll
+        for (int h = 0; h < NQ; ++h) acc[h][e] = mma_d(acc[h][e], a, join(x[h][0], x[h][1]));
+    }
+}
+
+template <int NQ>
+__device__ __forceinline__ void clear_acc(f32x4 (&acc)[NQ][4]) {
+#pragma unroll
+    for (int h = 0; h < NQ; ++h) clear(acc[h]);
+}
+
+// A wave's accumulators into its part of the merge area (row-major, fp32).
+template <int NQ>
+__device__ __forceinline__ void put_patch(float* patch, const f32x4 (&acc)[NQ][4], int r, int g) {
+#pragma unroll
+    for (int h = 0; h < NQ; ++h)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            *reinterpret_cast<f32x4*>(patch + (h * 16 + r) * kPatchLd + 16 * g + 4 * i) =
+                f32x4{acc[h][0][i], acc[h][1][i], acc[h][2][i], acc[h][3][i]};
+}
+
+// The same values as rows of the output, when no other wave holds a share of them.
+template <typename T>
+__device__ __forceinline__ void store_acc(T* row, const f32x4 (&acc)[4], float f, int g) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) store_quad<T>(row + 16 * g + 4 * i, f32x4{acc[0][i], acc[1][i], acc[2][i], acc[3][i]} * f);
+}
+
+// Block j of the list, lists of up to 64 blocks from the lanes of `head64` (no scalar load in the loop).
+__device__ __forceinline__ int list_at(const int* list, int head64, int j) {
+    return j < 64 ? __builtin_amdgcn_readlane(head64, j) : list[j];
+}
+
+// Work of a group of n items, dealt to the XCDs in contiguous eighths: items of one head share an L2.  The
+// group takes 8 * ceil(n / 8) workgroups from a multiple of 8 on; -1: a workgroup past the end.
+__device__ __forceinline__ int item_of_group(int id, int n) {
+    const int item = (id & 7) * ((n + 7) >> 3) + (id >> 3);
+    return item < n ? item : -1;
+}
+inline long long group_grid(long long n) { return (n + 7) / 8 * 8; }
+
+}  // namespace
+
 // ------------------------------------------------------------------------------------------------
-// forward: workgroup = (head, block row I); wave w owns query rows I*bs + 16 w .. + 15
+// forward: workgroup = (head, S::OWN query rows)
 // ------------------------------------------------------------------------------------------------
-template <typename T, int BS>
-__global__ __launch_bounds__(BS * 4) void attn_fwd_kernel(
+template <typename T, int BS, typename S>
+__global__ __launch_bounds__(S::W * 64, 2) void attn_fwd_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, T* __restrict__ O,
     float* __restrict__ LSE, const int* __restrict__ row_ptr, const int* __restrict__ col_idx, int L,
-    int nb, float scale_log2, int paper_denom) {
+    int nb, int total, float scale_log2, int paper_denom) {
     typedef typename Elem<T>::Frag Frag;
     typedef typename Elem<T>::Quad Quad;
-    constexpr int EPL = Elem<T>::EPL, KC = Elem<T>::KC, NDC = kD / KC, NKT = BS / 16;
-    constexpr int LDK = kD + EPL, LDT = BS + EPL;
-    __shared__ __attribute__((aligned(16))) T k_rm[BS * LDK];
-    __shared__ __attribute__((aligned(16))) T v_tr[kD * LDT];
+    constexpr int NQ = S::NQ, KT = S::KT, NDC = S::NDC, OWN = S::OWN;
+    __shared__ __attribute__((aligned(16))) float o_s[S::WT][OWN * kPatchLd];
+    __shared__ float m_s[S::WT][OWN], l_s[S::WT][OWN];
 
-    const int I = blockIdx.x % nb, bh = blockIdx.x / nb;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r = lane & 15, g = lane >> 4;
+    const int item = item_of_group(blockIdx.x, total);
+    if (item < 0) return;
+    const int bh = item / (nb * S::PARTS), part = item % (nb * S::PARTS), I = part / S::PARTS;
+    const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wt = wave % S::WT, own = wave / S::WT * (16 * NQ);
     const size_t head = (size_t)bh * L * kD;
-    const int qrow = I * BS + wave * 16 + r;
+    const int wg0 = I * BS + part % S::PARTS * OWN, row0 = wg0 + own;   // rows of the workgroup, of the wave
 
-    Frag qf[NDC];
+    const int jb = row_ptr[I], n = row_ptr[I + 1] - jb, nt = n * S::TPB;
+    const int* cols = col_idx + jb;
+    const int cols64 = n > 0 ? cols[lane < n ? lane : n - 1] : 0;
+    Frag qf[NQ][NDC];
 #pragma unroll
-    for (int c = 0; c < NDC; ++c)
-        qf[c] = *reinterpret_cast<const Frag*>(Q + head + (size_t)qrow * kD + c * KC + g * EPL);
-
-    float m = -INFINITY, lsum = 0.f;   // m in log2 units (score * scale * log2 e)
-    f32x4 oacc[4];
+    for (int h = 0; h < NQ; ++h) load_rows<T>(qf[h], Q + head + (size_t)(row0 + 16 * h) * kD, r, g);
+    auto tile_at = [&](int t) { return head + (size_t)(list_at(cols, cols64, t / S::TPB) * BS + t % S::TPB * 16) * kD; };
+    // tile t + u of a step that starts at t; past the end: zeros
+    auto load_k = [&](Frag (&k)[KT][NDC], int t) {
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt) oacc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    const int jb = row_ptr[I], je = row_ptr[I + 1];
-    for (int j = jb; j < je; ++j) {
-        const int J = col_idx[j];
-        __syncthreads();
-        stage_tile<T, BS, LDK, LDT, true, false>(K + head + (size_t)J * BS * kD, k_rm, nullptr, tid);
-        stage_tile<T, BS, LDK, LDT, false, true>(V + head + (size_t)J * BS * kD, nullptr, v_tr, tid);
-        __syncthreads();
-
-        // S^T tile kt: [key 16 kt + 4 g + i][query r]
-        f32x4 s[NKT];
-        float mx = -INFINITY;
-#pragma unroll
-        for (int kt = 0; kt < NKT; ++kt) {
-            s[kt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int c = 0; c < NDC; ++c) {
-                const Frag kf = *reinterpret_cast<const Frag*>(k_rm + (kt * 16 + r) * LDK + c * KC + g * EPL);
-                s[kt] = mma_d(s[kt], kf, qf[c]);
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) mx = fmaxf(mx, s[kt][i]);
+        for (int u = 0; u < KT; ++u) {
+            if (u == 0 || t + u < nt) load_rows<T>(k[u], K + tile_at(t + u), r, g);
+            else clear(k[u]);
         }
-        mx = group_max(mx);
-        const float m_new = fmaxf(m, mx * scale_log2);
-        const float alpha = exp2f(m - m_new);
-        lsum *= alpha;
+    };
+
+    float m[NQ], limit[NQ], lsum[NQ];   // m: what a row's exponentials are taken against, log2 units
+    f32x4 oacc[NQ][4];
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt) oacc[dt] *= alpha;
-        Quad pq[NKT];
+    for (int h = 0; h < NQ; ++h) {
+        m[h] = limit[h] = -INFINITY;
+        lsum[h] = 0.f;
+    }
+    clear_acc<NQ>(oacc);
+
+    auto step = [&](const Frag (&kf)[KT][NDC], Frag (&knext)[KT][NDC], int t) {
+        Quad vc[KT][4];
 #pragma unroll
-        for (int kt = 0; kt < NKT; ++kt) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float p = exp2f(fmaf(s[kt][i], scale_log2, -m_new));
-                s[kt][i] = p;
-                lsum += p;
-            }
-            pq[kt] = to_quad<T>(s[kt]);
+        for (int u = 0; u < KT; ++u) {
+            if (u == 0 || t + u < nt) load_cols<T>(vc[u], V + tile_at(t + u), r, g);
+            else clear(vc[u]);
         }
-        m = m_new;
-        mma_over_rows<T, BS, LDT>(oacc, v_tr, pq, r, g);   // O^T[d][query] += V^T P^T
+        if (t + S::STRIDE < nt) load_k(knext, t + S::STRIDE);
+        __builtin_amdgcn_sched_barrier(0);
+        // S^T: [tile row 4 g + i][query r]
+        f32x4 s[NQ][KT];
+        float mx[NQ];
+        bool above = false;
+#pragma unroll
+        for (int h = 0; h < NQ; ++h) {
+            mx[h] = -INFINITY;
+#pragma unroll
+            for (int u = 0; u < KT; ++u) {
+                s[h][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int c = 0; c < NDC; ++c) s[h][u] = mma_d(s[h][u], kf[u][c], qf[h][c]);
+            }
+        }
+#pragma unroll
+        for (int h = 0; h < NQ; ++h) {
+#pragma unroll
+            for (int u = 0; u < KT; ++u)
+                if (u == 0 || t + u < nt)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) mx[h] = fmaxf(mx[h], s[h][u][i]);
+            above |= mx[h] * scale_log2 > limit[h];
+        }
+        if (__any(above)) {   // always at a wave's first step
+#pragma unroll
+            for (int h = 0; h < NQ; ++h) {
+                const float m_new = fmaxf(m[h], group_max(mx[h]) * scale_log2);
+                const float alpha = exp2_of(m[h] - m_new, T());
+                m[h] = m_new;
+                limit[h] = m_new + kRescaleSlack;
+                lsum[h] *= alpha;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) oacc[h][e] *= alpha;
+            }
+        }
+        Quad pq[NQ][KT];
+#pragma unroll
+        for (int h = 0; h < NQ; ++h)
+#pragma unroll
+            for (int u = 0; u < KT; ++u) {
+                f32x4 p;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    p[i] = exp2_of(fmaf(s[h][u][i], scale_log2, -m[h]), T());
+                    if (u > 0) p[i] = t + u < nt ? p[i] : 0.f;
+                    lsum[h] += p[i];
+                }
+                pq[h][u] = to_quad<T>(p);
+            }
+        mma_cols(oacc, vc, pq);   // O^T += V^T P^T
+    };
+    {
+        Frag ka[KT][NDC], kb[KT][NDC];
+        int t = wt * KT;
+        if (t < nt) load_k(ka, t);
+        for (; t < nt; t += 2 * S::STRIDE) {
+            step(ka, kb, t);
+            if (t + S::STRIDE < nt) step(kb, ka, t + S::STRIDE);
+        }
     }
 
-    lsum = group_sum(lsum);
-    if (paper_denom && je > jb) {
+    if constexpr (S::WT == 1) {
+#pragma unroll
+        for (int h = 0; h < NQ; ++h) {
+            const int q = row0 + h * 16 + r;
+            const float mm = paper_denom ? fmaxf(m[h], 0.f) : m[h], a = n > 0 ? exp2_of(m[h] - mm, T()) : 0.f;
+            float l = group_sum(lsum[h]) * a;
+            if (paper_denom && n > 0) l += (float)(L - n * BS) * exp2f(-mm);
+            store_acc<T>(O + head + (size_t)q * kD, oacc[h], l > 0.f ? a / l : 0.f, g);
+            if (g == 0) LSE[(size_t)bh * L + q] = l > 0.f ? (mm + log2f(l)) * kLn2 : -INFINITY;
+        }
+        return;
+    }
+    // the waves' shares of each row: rescaled to the row's largest m and added up in wave order
+    put_patch<NQ>(&o_s[wt][own * kPatchLd], oacc, r, g);
+#pragma unroll
+    for (int h = 0; h < NQ; ++h) {
+        const float l = group_sum(lsum[h]);
+        if (g == 0) {
+            m_s[wt][own + h * 16 + r] = m[h];
+            l_s[wt][own + h * 16 + r] = l;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < OWN; p += 4 * S::W) {
+        const int q = p + (tid >> 4), d = (tid & 15) * 4;
+        float mm = m_s[0][q];
+#pragma unroll
+        for (int w = 1; w < S::WT; ++w) mm = fmaxf(mm, m_s[w][q]);
         // Algorithm 6: every masked entry of the row counts as a score of 0 (a row that keeps nothing
         // has no entry to normalise and stays at O = 0, LSE = -inf)
-        const float masked = (float)(L - (je - jb) * BS);
-        const float mp = fmaxf(m, 0.f);
-        const float a = exp2f(m - mp);
-        lsum = lsum * a + masked * exp2f(-mp);
-        m = mp;
+        if (paper_denom) mm = fmaxf(mm, 0.f);
+        f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
+        float l = 0.f;
+        if (n > 0) {
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt) oacc[dt] *= a;
+            for (int w = 0; w < S::WT; ++w) {
+                const float a = exp2_of(m_s[w][q] - mm, T());
+                l += l_s[w][q] * a;
+                o += *reinterpret_cast<const f32x4*>(&o_s[w][q * kPatchLd + d]) * a;
+            }
+            if (paper_denom) l += (float)(L - n * BS) * exp2f(-mm);
+        }
+        const float inv = l > 0.f ? 1.f / l : 0.f;
+        store_quad<T>(O + head + (size_t)(wg0 + q) * kD + d, o * inv);
+        if (d == 0) LSE[(size_t)bh * L + wg0 + q] = l > 0.f ? (mm + log2f(l)) * kLn2 : -INFINITY;
     }
-    const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
-    T* orow = O + head + (size_t)qrow * kD;
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt) store_quad<T>(orow + dt * 16 + 4 * g, oacc[dt] * inv);
-    if (g == 0) LSE[(size_t)bh * L + qrow] = lsum > 0.f ? (m + log2f(lsum)) * kLn2 : -INFINITY;
 }
 
 // ------------------------------------------------------------------------------------------------
-// backward, query side: workgroup = (head, block row I).  Computes delta = rowsum(dO .* O) for its
-// rows (stored for the key-side kernel) and dQ.
+// backward: one launch computes dQ, dK and dV.  Workgroup = (head, S::OWN rows of a block row) on the query
+// side, or (head, S::OWN keys of a work item's block column) on the key side.  The sides share no data: the
+// key side computes delta = rowsum(dO .* O) of the query rows it visits by itself.  Deterministic: no
+// atomics, sums over waves and chunks in fixed order.
+// Grid: the long key items (chunks of split columns), the block rows, the other key items; all heads in each.
 // ------------------------------------------------------------------------------------------------
-template <typename T, int BS>
-__global__ __launch_bounds__(BS * 4) void attn_bwd_dq_kernel(
+template <typename T, int BS, typename S>
+__global__ __launch_bounds__(S::W * 64, 2) void attn_bwd_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, const T* __restrict__ O,
-    const T* __restrict__ dO, const float* __restrict__ LSE, T* __restrict__ dQ,
-    float* __restrict__ delta_out, const int* __restrict__ row_ptr, const int* __restrict__ col_idx,
-    const int* __restrict__ col_ptr, const int* __restrict__ row_idx, int w_max, int split_max,
-    int4* __restrict__ sched, int4* __restrict__ split,
-    int L, int nb, float scale, float scale_log2) {
-    if (blockIdx.x == 0 && threadIdx.x < 64)
-        build_key_schedule(col_ptr, row_idx, nb, w_max, split_max, sched, split, threadIdx.x);
+    const T* __restrict__ dO, const float* __restrict__ LSE, T* __restrict__ dQ, T* __restrict__ dK,
+    T* __restrict__ dV, const int* __restrict__ row_ptr, const int* __restrict__ col_idx,
+    const int* __restrict__ col_ptr, const int* __restrict__ row_idx, float* __restrict__ partial, int n_slots,
+    int BH, int L, int nb, int n_key_a, int n_rows, int n_key_c, int w_first, int chunk, float scale, float scale_log2) {
     typedef typename Elem<T>::Frag Frag;
     typedef typename Elem<T>::Quad Quad;
-    constexpr int EPL = Elem<T>::EPL, KC = Elem<T>::KC, NDC = kD / KC, NKT = BS / 16;
-    constexpr int LDK = kD + EPL, LDT = BS + EPL;
-    __shared__ __attribute__((aligned(16))) T k_rm[BS * LDK];
-    __shared__ __attribute__((aligned(16))) T v_rm[BS * LDK];
-    __shared__ __attribute__((aligned(16))) T k_tr[kD * LDT];
+    typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+    constexpr int NQ = S::NQ, KT = S::KT, NDC = S::NDC, OWN = S::OWN;
+    __shared__ __attribute__((aligned(16))) float acc_s[S::WT][OWN * kPatchLd];
 
-    const int I = blockIdx.x % nb, bh = blockIdx.x / nb;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r = lane & 15, g = lane >> 4;
-    const size_t head = (size_t)bh * L * kD;
-    const int qrow = I * BS + wave * 16 + r;
-
-    Frag qf[NDC], dof[NDC];
-    float delta = 0.f;
-#pragma unroll
-    for (int c = 0; c < NDC; ++c) {
-        const size_t off = head + (size_t)qrow * kD + c * KC + g * EPL;
-        qf[c] = *reinterpret_cast<const Frag*>(Q + off);
-        dof[c] = *reinterpret_cast<const Frag*>(dO + off);
-        const Frag of = *reinterpret_cast<const Frag*>(O + off);
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) delta = fmaf((float)dof[c][e], (float)of[e], delta);
+    const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wt = wave % S::WT, own = wave / S::WT * (16 * NQ);
+    auto padded = [](int n) { return (n + 7) & ~7; };
+    int id = blockIdx.x, per_head = n_key_a * S::PARTS, first = 0;
+    bool key_side = true;
+    if (id >= padded(BH * per_head)) {
+        id -= padded(BH * per_head);
+        per_head = n_rows * S::PARTS;
+        key_side = false;
+        if (id >= padded(BH * per_head)) {
+            id -= padded(BH * per_head);
+            per_head = n_key_c * S::PARTS;
+            first = w_first;
+            key_side = true;
+        }
     }
-    delta = group_sum(delta);
-    if (g == 0) delta_out[(size_t)bh * L + qrow] = delta;
-    const float lse2 = LSE[(size_t)bh * L + qrow] * kLog2e;
+    const int item = item_of_group(id, BH * per_head);
+    if (item < 0) return;
+    const int bh = item / per_head, idx = first + item % per_head / S::PARTS;
+    const int sub = item % S::PARTS * OWN;   // the workgroup's rows within the block
+    const size_t head = (size_t)bh * L * kD, vec = (size_t)bh * L;
 
-    f32x4 dq[4];
+    // adds up the waves' accumulators: row p + tid / 16, columns 4 (tid % 16) .. + 3
+    auto merged = [&](int p) {
+        const int o = (p + (tid >> 4)) * kPatchLd + (tid & 15) * 4;
+        f32x4 v = *reinterpret_cast<const f32x4*>(&acc_s[0][o]);
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt) dq[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int w = 1; w < S::WT; ++w) v += *reinterpret_cast<const f32x4*>(&acc_s[w][o]);
+        return v;
+    };
+    const int out = (sub + (tid >> 4)) * kD + (tid & 15) * 4;
 
-    const int jb = row_ptr[I], je = row_ptr[I + 1];
-    for (int j = jb; j < je; ++j) {
-        const int J = col_idx[j];
-        __syncthreads();
-        stage_tile<T, BS, LDK, LDT, true, true>(K + head + (size_t)J * BS * kD, k_rm, k_tr, tid);
-        stage_tile<T, BS, LDK, LDT, true, false>(V + head + (size_t)J * BS * kD, v_rm, nullptr, tid);
-        __syncthreads();
-        Quad dsq[NKT];
+    if (!key_side) {
+        const int I = idx, row0 = I * BS + sub + own;
+        const int jb = row_ptr[I], n = row_ptr[I + 1] - jb, nt = n * S::TPB;
+        const int* cols = col_idx + jb;
+        const int cols64 = n > 0 ? cols[lane < n ? lane : n - 1] : 0;
+        auto tile_at = [&](int t) { return head + (size_t)(list_at(cols, cols64, t / S::TPB) * BS + t % S::TPB * 16) * kD; };
+        Frag kf[KT][NDC], vf[KT][NDC];
+        Quad kc[KT][4];
+        auto load_tiles = [&](int t) {   // tiles t, t + 1, ..; past the end: zeros
 #pragma unroll
-        for (int kt = 0; kt < NKT; ++kt) {
-            f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f}, dp = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int c = 0; c < NDC; ++c) {
-                const int off = (kt * 16 + r) * LDK + c * KC + g * EPL;
-                s = mma_d(s, *reinterpret_cast<const Frag*>(k_rm + off), qf[c]);     // S^T = K Q^T
-                dp = mma_d(dp, *reinterpret_cast<const Frag*>(v_rm + off), dof[c]);  // dP^T = V dO^T
+            for (int u = 0; u < KT; ++u) {
+                if (u == 0 || t + u < nt) {
+                    const size_t at = tile_at(t + u);
+                    load_rows<T>(kf[u], K + at, r, g);
+                    load_rows<T>(vf[u], V + at, r, g);
+                    load_cols<T>(kc[u], K + at, r, g);
+                } else {
+                    clear(kf[u]);
+                    clear(vf[u]);
+                    clear(kc[u]);
+                }
             }
-            f32x4 ds;
+        };
+        Frag qf[NQ][NDC], dof[NQ][NDC];
+        float delta[NQ], lse2[NQ];
+        int t = wt * KT;
+        if (t < nt) {   // a wave without tiles only takes part in the merge
+            Frag of[NQ][NDC];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float p = exp2f(fmaf(s[i], scale_log2, -lse2));
-                ds[i] = p * (dp[i] - delta);
+            for (int h = 0; h < NQ; ++h) {
+                const size_t at = head + (size_t)(row0 + 16 * h) * kD;
+                load_rows<T>(qf[h], Q + at, r, g);
+                load_rows<T>(dof[h], dO + at, r, g);
+                load_rows<T>(of[h], O + at, r, g);
+                lse2[h] = LSE[vec + row0 + 16 * h + r] * kLog2e;
             }
-            dsq[kt] = to_quad<T>(ds);
+            load_tiles(t);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int h = 0; h < NQ; ++h) {
+                float dl = 0.f;
+#pragma unroll
+                for (int c = 0; c < NDC; ++c)
+#pragma unroll
+                    for (int e = 0; e < Elem<T>::EPL; ++e) dl = fmaf((float)dof[h][c][e], (float)of[h][c][e], dl);
+                delta[h] = group_sum(dl);
+            }
         }
-        mma_over_rows<T, BS, LDT>(dq, k_tr, dsq, r, g);   // dQ^T[d][query] += K^T dS^T
-    }
-    T* drow = dQ + head + (size_t)qrow * kD;
+        f32x4 dq[NQ][4];
+        clear_acc<NQ>(dq);
+        while (t < nt) {
+            Quad dsq[NQ][KT];
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt) store_quad<T>(drow + dt * 16 + 4 * g, dq[dt] * scale);
-}
-
-// ------------------------------------------------------------------------------------------------
-// backward, key side: workgroup = (head, work item w) with sched[w] = a chunk of the kept rows of
-// block column J; wave w owns keys J*bs + 16 w .. + 15.  Deterministic: no atomics, one writer per
-// output or per partial slot.
-// ------------------------------------------------------------------------------------------------
-template <typename T, int BS>
-__global__ __launch_bounds__(BS * 4) void attn_bwd_dkv_kernel(
-    const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, const T* __restrict__ dO,
-    const float* __restrict__ LSE, const float* __restrict__ delta, T* __restrict__ dK,
-    T* __restrict__ dV, const int* __restrict__ row_idx, const int4* __restrict__ sched, int w_max,
-    int n_slots, float* __restrict__ partial, int L, float scale, float scale_log2) {
-    typedef typename Elem<T>::Frag Frag;
-    typedef typename Elem<T>::Quad Quad;
-    constexpr int EPL = Elem<T>::EPL, KC = Elem<T>::KC, NDC = kD / KC, NQT = BS / 16;
-    constexpr int LDK = kD + EPL, LDT = BS + EPL;
-    __shared__ __attribute__((aligned(16))) T q_rm[BS * LDK];
-    __shared__ __attribute__((aligned(16))) T do_rm[BS * LDK];
-    __shared__ __attribute__((aligned(16))) T q_tr[kD * LDT];
-    __shared__ __attribute__((aligned(16))) T do_tr[kD * LDT];
-    __shared__ float lse_s[BS], delta_s[BS];
-
-    const int w = blockIdx.x % w_max, bh = blockIdx.x / w_max;
-    const int4 item = sched[w];
-    const int J = item.x, kb = item.y, ke = item.z, slot = item.w;
-    if (J < 0) return;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r = lane & 15, g = lane >> 4;
-    const size_t head = (size_t)bh * L * kD;
-    const int krow = J * BS + wave * 16 + r;
-
-    Frag kf[NDC], vf[NDC];
+            for (int h = 0; h < NQ; ++h)
 #pragma unroll
-    for (int c = 0; c < NDC; ++c) {
-        const size_t off = head + (size_t)krow * kD + c * KC + g * EPL;
-        kf[c] = *reinterpret_cast<const Frag*>(K + off);
-        vf[c] = *reinterpret_cast<const Frag*>(V + off);
-    }
-    f32x4 dk[4], dv[4];
+                for (int u = 0; u < KT; ++u) {
+                    // the accumulator starts at -delta: dP - delta comes out of the MFMA
+                    f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f}, dp = f32x4{-delta[h], -delta[h], -delta[h], -delta[h]};
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt) {
-        dk[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        dv[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-
-    for (int k = kb; k < ke; ++k) {
-        const int I = row_idx[k];
+                    for (int c = 0; c < NDC; ++c) {
+                        s = mma_d(s, kf[u][c], qf[h][c]);      // S^T = K Q^T
+                        dp = mma_d(dp, vf[u][c], dof[h][c]);   // dP^T = V dO^T
+                    }
+                    f32x4 ds;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        ds[i] = exp2_of(fmaf(s[i], scale_log2, -lse2[h]), T()) * dp[i];
+                        if (u > 0) ds[i] = t + u < nt ? ds[i] : 0.f;
+                    }
+                    dsq[h][u] = to_quad<T>(ds);
+                }
+            mma_cols(dq, kc, dsq);   // dQ^T += K^T dS^T
+            t += S::STRIDE;
+            if (t < nt) load_tiles(t);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (S::WT == 1) {
+#pragma unroll
+            for (int h = 0; h < NQ; ++h) store_acc<T>(dQ + head + (size_t)(row0 + h * 16 + r) * kD, dq[h], scale, g);
+            return;
+        }
+        put_patch<NQ>(&acc_s[wt][own * kPatchLd], dq, r, g);
         __syncthreads();
-        stage_tile<T, BS, LDK, LDT, true, true>(Q + head + (size_t)I * BS * kD, q_rm, q_tr, tid);
-        stage_tile<T, BS, LDK, LDT, true, true>(dO + head + (size_t)I * BS * kD, do_rm, do_tr, tid);
-        if (tid < BS) {
-            lse_s[tid] = LSE[(size_t)bh * L + I * BS + tid] * kLog2e;
-            delta_s[tid] = delta[(size_t)bh * L + I * BS + tid];
-        }
-        __syncthreads();
-        Quad pq[NQT], dsq[NQT];
 #pragma unroll
-        for (int qt = 0; qt < NQT; ++qt) {
-            f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f}, dp = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int c = 0; c < NDC; ++c) {
-                const int off = (qt * 16 + r) * LDK + c * KC + g * EPL;
-                s = mma_d(s, *reinterpret_cast<const Frag*>(q_rm + off), kf[c]);     // S = Q K^T
-                dp = mma_d(dp, *reinterpret_cast<const Frag*>(do_rm + off), vf[c]);  // dP = dO V^T
-            }
-            f32x4 p, ds;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int q = qt * 16 + 4 * g + i;
-                p[i] = exp2f(fmaf(s[i], scale_log2, -lse_s[q]));
-                ds[i] = p[i] * (dp[i] - delta_s[q]);
-            }
-            pq[qt] = to_quad<T>(p);
-            dsq[qt] = to_quad<T>(ds);
-        }
-        mma_over_rows<T, BS, LDT>(dv, do_tr, pq, r, g);   // dV^T[d][key] += dO^T P
-        mma_over_rows<T, BS, LDT>(dk, q_tr, dsq, r, g);   // dK^T[d][key] += Q^T dS
+        for (int p = 0; p < OWN; p += 4 * S::W)
+            store_quad<T>(dQ + head + (size_t)(I * BS + p) * kD + out, merged(p) * scale);
+        return;
     }
-    if (slot < 0) {
-        T* dkrow = dK + head + (size_t)krow * kD;
-        T* dvrow = dV + head + (size_t)krow * kD;
-#pragma unroll
-        for (int dt = 0; dt < 4; ++dt) {
-            store_quad<T>(dkrow + dt * 16 + 4 * g, dk[dt] * scale);
-            store_quad<T>(dvrow + dt * 16 + 4 * g, dv[dt]);
-        }
-    } else {
-        // fp32 partial tiles [head][slot][dK | dV][bs][64], unscaled
-        float* pk = partial + ((size_t)bh * n_slots + slot) * (2 * BS * kD) + (size_t)(wave * 16 + r) * kD;
-        float* pv = pk + BS * kD;
-#pragma unroll
-        for (int dt = 0; dt < 4; ++dt) {
-            *reinterpret_cast<f32x4*>(pk + dt * 16 + 4 * g) = dk[dt];
-            *reinterpret_cast<f32x4*>(pv + dt * 16 + 4 * g) = dv[dt];
-        }
-    }
-}
 
-// Adds the partial tiles of every block column that was cut into several chunks, in chunk order.
-// workgroup = (head, m-th split column, part): 256 threads, one float4 of the output tile each,
-// bs / 16 parts per tile, so that the loads of all chunks of a float4 are in flight together.
-template <typename T, int BS>
-__global__ __launch_bounds__(256) void attn_bwd_dkv_reduce_kernel(
-    const float* __restrict__ partial, const int4* __restrict__ split, int split_max, int n_slots,
-    T* __restrict__ dK, T* __restrict__ dV, int L, float scale) {
-    constexpr int PARTS = BS / 16;
-    const int part = blockIdx.x % PARTS, m = (blockIdx.x / PARTS) % split_max;
-    const int bh = blockIdx.x / (PARTS * split_max);
-    const int4 info = split[m];   // {J, first slot, chunks}
-    if (info.x < 0) return;
-    const int v = part * 256 + threadIdx.x;
-    const float* pk = partial + ((size_t)bh * n_slots + info.y) * (2 * BS * kD) + v * 4;
-    f32x4 ak = f32x4{0.f, 0.f, 0.f, 0.f}, av = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-    for (int c = 0; c < info.z; ++c) {
-        ak += *reinterpret_cast<const f32x4*>(pk + (size_t)c * (2 * BS * kD));
-        av += *reinterpret_cast<const f32x4*>(pk + (size_t)c * (2 * BS * kD) + BS * kD);
+    const KeyItem it = key_item_lookup(col_ptr, nb, chunk, idx, lane);
+    if (it.J < 0) return;
+    const int n = it.ke - it.kb, nt = n * S::TPB, row0 = it.J * BS + sub + own;
+    const int* rows = row_idx + it.kb;
+    const int rows64 = n > 0 ? rows[lane < n ? lane : n - 1] : 0;
+    auto row_at = [&](int t) { return list_at(rows, rows64, t / S::TPB) * BS + t % S::TPB * 16; };
+    Frag kf[NQ][NDC], vf[NQ][NDC];
+#pragma unroll
+    for (int h = 0; h < NQ; ++h) {
+        load_rows<T>(kf[h], K + head + (size_t)(row0 + 16 * h) * kD, r, g);
+        load_rows<T>(vf[h], V + head + (size_t)(row0 + 16 * h) * kD, r, g);
     }
-    const size_t out = (size_t)bh * L * kD + (size_t)info.x * BS * kD + v * 4;
-    store_quad<T>(dK + out, ak * scale);
-    store_quad<T>(dV + out, av);
+    f32x4 dk[NQ][4], dv[NQ][4];
+    clear_acc<NQ>(dk);
+    clear_acc<NQ>(dv);
+    for (int t = wt * KT; t < nt; t += S::STRIDE) {
+        Quad qc[KT][4], dc[KT][4];
+        Quad pq[NQ][KT], dsq[NQ][KT];
+#pragma unroll
+        for (int u = 0; u < KT; ++u) {
+            if (u == 0 || t + u < nt) {
+                const int q0 = row_at(t + u);
+                const size_t at = head + (size_t)q0 * kD;
+                Frag qf[NDC], df[NDC], of[NDC];
+                load_rows<T>(df, dO + at, r, g);
+                load_rows<T>(of, O + at, r, g);
+                load_rows<T>(qf, Q + at, r, g);
+                const f32x4_any lse = *reinterpret_cast<const f32x4_any*>(LSE + vec + q0 + 4 * g);
+                load_cols<T>(dc[u], dO + at, r, g);
+                load_cols<T>(qc[u], Q + at, r, g);
+                __builtin_amdgcn_sched_barrier(0);
+                // -delta of rows 4 g + i in every lane: the lanes' shares of row r times a tile of ones
+                float part = 0.f;
+#pragma unroll
+                for (int c = 0; c < NDC; ++c)
+#pragma unroll
+                    for (int e = 0; e < Elem<T>::EPL; ++e) part = fmaf((float)df[c][e], (float)of[c][e], part);
+                const f32x4 ndelta = __builtin_amdgcn_mfma_f32_16x16x4f32(-part, 1.f, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+                for (int h = 0; h < NQ; ++h) {
+                    f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f}, dp = ndelta;
+#pragma unroll
+                    for (int c = 0; c < NDC; ++c) {
+                        s = mma_d(s, qf[c], kf[h][c]);     // S = Q K^T
+                        dp = mma_d(dp, df[c], vf[h][c]);   // dP = dO V^T
+                    }
+                    f32x4 p, ds;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        p[i] = exp2_of(fmaf(s[i], scale_log2, -lse[i] * kLog2e), T());
+                        ds[i] = p[i] * dp[i];
+                    }
+                    pq[h][u] = to_quad<T>(p);
+                    dsq[h][u] = to_quad<T>(ds);
+                }
+            } else {
+                clear(dc[u]);
+                clear(qc[u]);
+#pragma unroll
+                for (int h = 0; h < NQ; ++h) pq[h][u] = dsq[h][u] = Quad{};
+            }
+        }
+        mma_cols(dv, dc, pq);    // dV^T += dO^T P
+        mma_cols(dk, qc, dsq);   // dK^T += Q^T dS
+    }
+    // final rows, or this chunk's fp32 partial tiles [head][slot][dK | dV][bs][64], unscaled
+    float* const pk = partial + ((size_t)bh * n_slots + (it.slot < 0 ? 0 : it.slot)) * (2 * BS * kD);
+    if constexpr (S::WT == 1) {
+#pragma unroll
+        for (int h = 0; h < NQ; ++h) {
+            const size_t o = (size_t)(sub + own + h * 16 + r) * kD, at = head + (size_t)it.J * BS * kD + o;
+            if (it.slot >= 0) {
+                store_acc<float>(pk + o, dk[h], 1.f, g);
+                store_acc<float>(pk + BS * kD + o, dv[h], 1.f, g);
+            } else {
+                store_acc<T>(dK + at, dk[h], scale, g);
+                store_acc<T>(dV + at, dv[h], 1.f, g);
+            }
+        }
+        return;
+    }
+#pragma unroll
+    for (int which = 0; which < 2; ++which) {
+        if (which) __syncthreads();
+        put_patch<NQ>(&acc_s[wt][own * kPatchLd], which ? dv : dk, r, g);
+        __syncthreads();
+#pragma unroll
+        for (int p = 0; p < OWN; p += 4 * S::W) {
+            const f32x4 v = merged(p);
+            const int o = p * kD + out;
+            if (it.slot >= 0) *reinterpret_cast<f32x4*>(pk + which * BS * kD + o) = v;
+            else store_quad<T>((which ? dV : dK) + head + (size_t)it.J * BS * kD + o, which ? v : v * scale);
+        }
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
 // host launchers
 // ------------------------------------------------------------------------------------------------
-size_t attn_bwd_workspace_bytes(int BH, int L, int bs, int nb, int nnzb) {
-    const BwdWorkspace ws(BH, L, bs, nb, nnzb);
-    return ws.total;
+BwdWorkspace::BwdWorkspace(int BH, int bs, int nb, int nnzb) {
+    chunk = kChunk;
+    w_max = nnzb / chunk + nb;
+    w_first = nnzb / chunk + 1 < w_max ? nnzb / chunk + 1 : w_max;
+    n_slots = 2 * (nnzb / chunk) + 2;
+    split_max = nb > chunk ? nnzb / (chunk + 1) : 0;
+    total = (size_t)BH * n_slots * 2 * bs * kD * sizeof(float);   // a multiple of 256
 }
 
-bool attn_bwd_grids_fit(int BH, int L, int bs, int nb, int nnzb) {
-    const BwdWorkspace ws(BH, L, bs, nb, nnzb);
-    const int64_t limit = 0x7fffffffll;
-    return (int64_t)(ws.w_max + nb) * BH <= limit && (int64_t)ws.split_max * BH * (bs / 16) <= limit;
+size_t attn_bwd_workspace_bytes(int BH, int bs, int nb, int nnzb) { return BwdWorkspace(BH, bs, nb, nnzb).total; }
+
+bool attn_bwd_grids_fit(int BH, int bs, int nb, int nnzb) {
+    const BwdWorkspace ws(BH, bs, nb, nnzb);
+    const int64_t limit = 0x7fffffffll, parts = bs == 64 ? 2 : 1;
+    return (int64_t)(ws.w_max + nb) * BH * parts + 24 <= limit &&
+           (int64_t)ws.split_max * BH * (bs / 16) <= limit;
 }
 
-BwdWorkspace::BwdWorkspace(int BH, int L, int bs, int nb, int nnzb) {
-    auto up = [](size_t x) { return (x + 255) / 256 * 256; };
-    w_max = key_work_items_max(nnzb, nb);
-    n_slots = key_slots_max(nnzb);
-    delta_off = 0;
-    sched_off = delta_off + up((size_t)2 * BH * L * sizeof(float));   // delta, then LSE in log2 units
-    split_max = key_split_max(nnzb);
-    split_off = sched_off + up((size_t)2 * w_max * sizeof(int4));   // items, then their first rows
-    partial_off = split_off + up((size_t)split_max * sizeof(int4));
-    total = partial_off + up((size_t)BH * n_slots * 2 * bs * kD * sizeof(float));
+// Rows with hardly more than one block each (the diagonal): no long chain to cut anywhere.
+static bool single_block_rows(const AttnShape& s, int nnzb) { return 2 * (long long)nnzb < 3 * (long long)s.nb; }
+
+// Whether a call has many block rows for every tile of its average row: 100.  Measured (fp32, and bf16 / block 16;
+// patterns with a few long rows and columns, 2.4 to 9.6 blocks per row) the backward's crossing lies between 75
+// and 200; without long rows it comes earlier, at 40 with the diagonal alone.
+static bool many_short_rows(const AttnShape& s, int nnzb) {
+    const long long rows = (long long)s.BH * s.nb, tiles_times_nb = (long long)nnzb * (s.bs / 16);   // of one head
+    return rows * s.nb >= (single_block_rows(s, nnzb) ? 40 : 100) * tiles_times_nb;
+}
+
+template <typename T, int BS, typename S>
+static hipError_t launch_fwd(const AttnShape& s, const void* Q, const void* K, const void* V, void* O,
+                             float* LSE, const int* row_ptr, const int* col_idx, hipStream_t st) {
+    const long long total = (long long)s.nb * s.BH * S::PARTS;
+    if (group_grid(total) > 0x7fffffffll) return hipErrorInvalidValue;
+    attn_fwd_kernel<T, BS, S><<<dim3((unsigned)group_grid(total)), dim3(S::W * 64), 0, st>>>(
+        static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V), static_cast<T*>(O), LSE, row_ptr,
+        col_idx, s.L, s.nb, (int)total, s.scale * kLog2e, s.paper_denom);
+    return hipGetLastError();
+}
+
+template <typename T, int BS, typename S>
+static hipError_t launch_bwd(const AttnShape& s, const void* Q, const void* K, const void* V, const void* O,
+                             const void* dO, const float* LSE, void* dQ, void* dK, void* dV, const int* row_ptr,
+                             const int* col_idx, const int* col_ptr, const int* row_idx, const BwdWorkspace& ws,
+                             float* partial, hipStream_t st) {
+    const bool rows = (s.bwd_phases & 1) != 0, keys = (s.bwd_phases & 2) != 0;
+    const int n_key_a = keys ? ws.w_first : 0, n_rows = rows ? s.nb : 0, n_key_c = keys ? ws.w_max - ws.w_first : 0;
+    const long long per_item = (long long)s.BH * S::PARTS;
+    const long long grid = group_grid(per_item * n_key_a) + group_grid(per_item * n_rows) + group_grid(per_item * n_key_c);
+    if (grid > 0) {
+        attn_bwd_kernel<T, BS, S><<<dim3((unsigned)grid), dim3(S::W * 64), 0, st>>>(
+            static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V), static_cast<const T*>(O),
+            static_cast<const T*>(dO), LSE, static_cast<T*>(dQ), static_cast<T*>(dK), static_cast<T*>(dV), row_ptr,
+            col_idx, col_ptr, row_idx, partial, ws.n_slots, s.BH, s.L, s.nb, n_key_a, n_rows, n_key_c, ws.w_first,
+            ws.chunk, s.scale, s.scale * kLog2e);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return keys ? launch_bwd_reduce<T, BS>(s, ws, partial, col_ptr, dK, dV, st) : hipSuccess;
 }
 
 template <typename T, int BS>
 static hipError_t fwd_t(const AttnShape& s, const void* Q, const void* K, const void* V, void* O,
-                        float* LSE, const int* row_ptr, const int* col_idx, hipStream_t st) {
-    if constexpr (sizeof(T) == 2 && BS >= 32) return fwd_bf16<BS>(s, Q, K, V, O, LSE, row_ptr, col_idx, st);
-    attn_fwd_kernel<T, BS><<<dim3((unsigned)(s.nb * s.BH)), dim3(BS * 4), 0, st>>>(
-        static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V),
-        static_cast<T*>(O), LSE, row_ptr, col_idx, s.L, s.nb, s.scale * kLog2e, s.paper_denom);
-    return hipGetLastError();
+                        float* LSE, const int* row_ptr, const int* col_idx, int nnzb, hipStream_t st) {
+    if constexpr (sizeof(T) == 2 && BS >= 32) {
+        return fwd_bf16<BS>(s, Q, K, V, O, LSE, row_ptr, col_idx, st);
+    } else {
+        if (many_short_rows(s, nnzb))
+            return launch_fwd<T, BS, typename SplitMany<T, BS>::fwd>(s, Q, K, V, O, LSE, row_ptr, col_idx, st);
+        return launch_fwd<T, BS, SplitFew<T, BS>>(s, Q, K, V, O, LSE, row_ptr, col_idx, st);
+    }
 }
 
 template <typename T, int BS>
@@ -355,39 +638,16 @@ static hipError_t bwd_t(const AttnShape& s, const void* Q, const void* K, const 
                         const void* dO, const float* LSE, void* dQ, void* dK, void* dV,
                         const int* row_ptr, const int* col_idx, const int* col_ptr, const int* row_idx,
                         int nnzb, void* workspace, hipStream_t st) {
-    const BwdWorkspace ws(s.BH, s.L, s.bs, s.nb, nnzb);
-    char* base = static_cast<char*>(workspace);
-    float* delta = reinterpret_cast<float*>(base + ws.delta_off);
-    int4* sched = reinterpret_cast<int4*>(base + ws.sched_off);
-    int4* split = reinterpret_cast<int4*>(base + ws.split_off);
-    float* partial = reinterpret_cast<float*>(base + ws.partial_off);
-    const dim3 block(BS * 4);
+    const BwdWorkspace ws(s.BH, s.bs, s.nb, nnzb);
+    float* partial = static_cast<float*>(workspace);
     if constexpr (sizeof(T) == 2 && BS >= 32) {
-        // tuned bf16 path: one launch for both sides (it needs no delta, work list or split list in the
-        // workspace), plus the small reduction of the partial tiles
-        return bwd_bf16<BS>(s, Q, K, V, O, dO, LSE, dQ, dK, dV, row_ptr, col_idx, col_ptr, row_idx, nnzb, ws.w_max,
-                            ws.split_max, ws.n_slots, partial, st);
+        return bwd_bf16<BS>(s, Q, K, V, O, dO, LSE, dQ, dK, dV, row_ptr, col_idx, col_ptr, row_idx, ws, partial, st);
     } else {
-        if (s.bwd_phases & 1) {
-            attn_bwd_dq_kernel<T, BS><<<dim3((unsigned)(s.nb * s.BH)), block, 0, st>>>(
-                static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V),
-                static_cast<const T*>(O), static_cast<const T*>(dO), LSE, static_cast<T*>(dQ), delta,
-                row_ptr, col_idx, col_ptr, row_idx, ws.w_max, ws.split_max, sched, split, s.L, s.nb, s.scale,
-                s.scale * kLog2e);
-            const hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
-        if (s.bwd_phases & 2) {
-            attn_bwd_dkv_kernel<T, BS><<<dim3((unsigned)(ws.w_max * s.BH)), block, 0, st>>>(
-                static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V),
-                static_cast<const T*>(dO), LSE, delta, static_cast<T*>(dK), static_cast<T*>(dV), row_idx,
-                sched, ws.w_max, ws.n_slots, partial, s.L, s.scale, s.scale * kLog2e);
-            const hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-            attn_bwd_dkv_reduce_kernel<T, BS><<<dim3((unsigned)(ws.split_max * s.BH * (BS / 16))), dim3(256), 0, st>>>(
-                partial, split, ws.split_max, ws.n_slots, static_cast<T*>(dK), static_cast<T*>(dV), s.L, s.scale);
-        }
-        return hipGetLastError();
+        auto* launch = launch_bwd<T, BS, SplitFew<T, BS>>;
+        if (many_short_rows(s, nnzb))
+            launch = single_block_rows(s, nnzb) ? launch_bwd<T, BS, typename SplitMany<T, BS>::bwd_single>
+                                                               : launch_bwd<T, BS, typename SplitMany<T, BS>::bwd>;
+        return launch(s, Q, K, V, O, dO, LSE, dQ, dK, dV, row_ptr, col_idx, col_ptr, row_idx, ws, partial, st);
     }
 }
 
@@ -404,8 +664,8 @@ static hipError_t bwd_t(const AttnShape& s, const void* Q, const void* K, const 
     } while (0)
 
 hipError_t launch_attn_fwd(const AttnShape& s, const void* Q, const void* K, const void* V, void* O,
-                           float* LSE, const int* row_ptr, const int* col_idx, hipStream_t st) {
-    SPION_DISPATCH(fwd_t, s, Q, K, V, O, LSE, row_ptr, col_idx, st);
+                           float* LSE, const int* row_ptr, const int* col_idx, int nnzb, hipStream_t st) {
+    SPION_DISPATCH(fwd_t, s, Q, K, V, O, LSE, row_ptr, col_idx, nnzb, st);
 }
 
 hipError_t launch_attn_bwd(const AttnShape& s, const void* Q, const void* K, const void* V,

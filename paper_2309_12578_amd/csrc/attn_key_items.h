@@ -1,0 +1,148 @@
+// Key-side work items of the backward pass: how the block columns are cut, found from the index by every
+// workgroup for itself, and the reduction of the partial tiles of columns that were cut.
+#ifndef SPION_ATTN_KEY_ITEMS_H_
+#define SPION_ATTN_KEY_ITEMS_H_
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "attn_common.h"
+#include "spion_internal.h"
+
+namespace spion {
+
+// ------------------------------------------------------------------------------------------------
+// Vertical stripes give block columns with up to nb kept rows next to columns with one or two, so the key
+// side does not take one column per workgroup.  The items are derived from col_ptr alone (the same list
+// for every head).  A column with cnt kept rows is cut into nch = ceil(cnt / kChunk) near-equal chunks if
+// cnt > kChunk, else it is one item (also when cnt == 0: its dK / dV must still be written as zeros).
+// Items are numbered with the chunks of split columns first, in column order (they are the longest and
+// start first), then the unsplit columns in column order.  Chunk number w of that first group writes its
+// fp32 partial tiles to slot w; a second kernel adds them up in chunk order (deterministic, no atomics).
+// ------------------------------------------------------------------------------------------------
+#ifndef SPION_KEY_CHUNK
+#define SPION_KEY_CHUNK 16   // kept rows per key-side work item (build-time tunable; 10-16 measure alike,
+                             // shorter chunks cost partial-tile traffic, longer ones the longest chain)
+#endif
+constexpr int kChunk = SPION_KEY_CHUNK;
+
+struct KeyItem {
+    int J;      // block column, -1: no such item
+    int kb, ke; // BSC entries [kb, ke)
+    int slot;   // partial slot, -1: the item covers its whole column and writes dK / dV itself
+};
+
+// All lanes of the calling wave must be active; the result is wave-uniform.
+__device__ __forceinline__ KeyItem key_item_lookup(const int* __restrict__ col_ptr, int nb, int chunk, int w,
+                                                   int lane) {
+    KeyItem none = {-1, 0, 0, -1};
+    if (nb <= chunk) {   // no column is cut
+        if (w >= nb) return none;
+        KeyItem it = {w, col_ptr[w], col_ptr[w + 1], -1};
+        return it;
+    }
+    int run = 0;   // chunks of split columns in the column groups before this one
+    int c0_first = 0, cnt_first = 0;   // columns 0 .. 63, kept for the second search
+    for (int base = 0; base < nb; base += 64) {
+        const int J = base + lane;
+        const bool valid = J < nb;
+        const int c0 = valid ? col_ptr[J] : 0, cnt = valid ? col_ptr[J + 1] - c0 : 0;
+        if (base == 0) {
+            c0_first = c0;
+            cnt_first = cnt;
+        }
+        const int nch = cnt > chunk ? (cnt + chunk - 1) / chunk : 0;
+        const int incl = wave_incl_scan(nch, lane);
+        const int lo = run + incl - nch;
+        const unsigned long long hit = __ballot(nch > 0 && w >= lo && w < lo + nch);
+        if (hit) {
+            const int src = __ffsll((long long)hit) - 1;
+            const int c0s = __builtin_amdgcn_readlane(c0, src), cnts = __builtin_amdgcn_readlane(cnt, src);
+            const int nchs = __builtin_amdgcn_readlane(nch, src);
+            int ci = w - __builtin_amdgcn_readlane(lo, src);
+            ci = ci < 0 ? 0 : (ci >= nchs ? nchs - 1 : ci);
+            KeyItem it = {base + src, c0s + (ci * cnts) / nchs, c0s + ((ci + 1) * cnts) / nchs, w};
+            return it;
+        }
+        run += __builtin_amdgcn_readlane(incl, 63);
+    }
+    int u = w - run;   // index among the unsplit columns
+    for (int base = 0; base < nb; base += 64) {
+        const int J = base + lane;
+        const bool valid = J < nb;
+        int c0 = c0_first, c1 = c0_first + cnt_first;
+        if (base != 0) {
+            c0 = valid ? col_ptr[J] : 0;
+            c1 = valid ? col_ptr[J + 1] : 0;
+        }
+        const unsigned long long whole = __ballot(valid && c1 - c0 <= chunk);
+        const unsigned long long hit = __ballot(valid && c1 - c0 <= chunk && lanes_below(whole) == u);
+        if (hit) {
+            const int src = __ffsll((long long)hit) - 1;
+            KeyItem it = {base + src, __builtin_amdgcn_readlane(c0, src), __builtin_amdgcn_readlane(c1, src), -1};
+            return it;
+        }
+        u -= __popcll(whole);
+    }
+    return none;
+}
+
+// The m-th split column: {J, first partial slot, chunks}; J < 0 if there are fewer.
+__device__ __forceinline__ int4 split_column_lookup(const int* __restrict__ col_ptr, int nb, int chunk, int m,
+                                                    int lane) {
+    int run = 0;
+    for (int base = 0; base < nb; base += 64) {
+        const int J = base + lane;
+        const bool valid = J < nb;
+        const int cnt = valid ? col_ptr[J + 1] - col_ptr[J] : 0;
+        const int nch = cnt > chunk ? (cnt + chunk - 1) / chunk : 0;
+        const int incl = wave_incl_scan(nch, lane);
+        const unsigned long long split = __ballot(nch > 0);
+        const unsigned long long hit = __ballot(nch > 0 && lanes_below(split) == m);
+        if (hit) {
+            const int src = __ffsll((long long)hit) - 1;
+            const int nchs = __builtin_amdgcn_readlane(nch, src);
+            return make_int4(base + src, run + __builtin_amdgcn_readlane(incl, src) - nchs, nchs, 0);
+        }
+        m -= __popcll(split);
+        run += __builtin_amdgcn_readlane(incl, 63);
+    }
+    return make_int4(-1, 0, 0, 0);
+}
+
+// Adds the partial tiles of every split block column, in chunk order.  Workgroup = (head, m-th split
+// column, part): 256 threads, one float4 of the output tile each, bs / 16 parts per tile, so that the
+// loads of all chunks of a float4 are in flight together.
+template <typename T, int BS>
+__global__ __launch_bounds__(256) void attn_bwd_reduce_kernel(
+    const float* __restrict__ partial, const int* __restrict__ col_ptr, int nb, int chunk, int split_max, int n_slots,
+    T* __restrict__ dK, T* __restrict__ dV, int L, float scale) {
+    constexpr int PARTS = BS / 16;
+    const int part = blockIdx.x % PARTS, m = (blockIdx.x / PARTS) % split_max;
+    const int bh = blockIdx.x / (PARTS * split_max);
+    const int4 info = split_column_lookup(col_ptr, nb, chunk, m, threadIdx.x & 63);   // {J, first slot, chunks}
+    if (info.x < 0) return;
+    const int v = part * 256 + threadIdx.x;
+    const float* pk = partial + ((size_t)bh * n_slots + info.y) * (2 * BS * kD) + v * 4;
+    f32x4 ak = f32x4{0.f, 0.f, 0.f, 0.f}, av = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+    for (int c = 0; c < info.z; ++c) {
+        ak += *reinterpret_cast<const f32x4*>(pk + (size_t)c * (2 * BS * kD));
+        av += *reinterpret_cast<const f32x4*>(pk + (size_t)c * (2 * BS * kD) + BS * kD);
+    }
+    const size_t out = (size_t)bh * L * kD + (size_t)info.x * BS * kD + v * 4;
+    store_quad<T>(dK + out, ak * scale);
+    store_quad<T>(dV + out, av);
+}
+
+template <typename T, int BS>
+hipError_t launch_bwd_reduce(const AttnShape& s, const BwdWorkspace& ws, const float* partial,
+                             const int* col_ptr, void* dK, void* dV, hipStream_t st) {
+    if (ws.split_max == 0) return hipSuccess;
+    attn_bwd_reduce_kernel<T, BS><<<dim3((unsigned)(ws.split_max * s.BH * (BS / 16))), dim3(256), 0, st>>>(
+        partial, col_ptr, s.nb, ws.chunk, ws.split_max, ws.n_slots, static_cast<T*>(dK), static_cast<T*>(dV), s.L, s.scale);
+    return hipGetLastError();
+}
+
+}  // namespace spion
+#endif

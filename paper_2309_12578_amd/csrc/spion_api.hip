@@ -313,7 +313,7 @@ int spion_copy_yardstick(const void* src, void* dst, size_t n_bytes, void* hip_s
 size_t spion_attn_workspace_bytes(const spion_attn_params* p, int32_t nnzb, int32_t is_bwd) {
     if (!p || attn_params_ok(p, nnzb) != SPION_OK) return (size_t)-1;
     if (!is_bwd) return 0;
-    return spion::attn_bwd_workspace_bytes(p->B * p->H, p->L, p->block, p->L / p->block, nnzb);
+    return spion::attn_bwd_workspace_bytes(p->B * p->H, p->block, p->L / p->block, nnzb);
 }
 
 int spion_index_check(const int32_t* row_ptr, const int32_t* col_idx, const int32_t* col_ptr,
@@ -339,7 +339,7 @@ int spion_attn_fwd(const void* Q, const void* K, const void* V, void* O, float* 
     const int rc = attn_params_ok(p, nnzb);
     if (rc != SPION_OK) return rc;
     const spion::AttnShape s = make_shape(p);
-    if (spion::launch_attn_fwd(s, Q, K, V, O, LSE, row_ptr, col_idx,
+    if (spion::launch_attn_fwd(s, Q, K, V, O, LSE, row_ptr, col_idx, nnzb,
                                static_cast<hipStream_t>(hip_stream)) != hipSuccess)
         return SPION_ERR_HIP;
     return SPION_OK;
@@ -355,7 +355,7 @@ int spion_attn_bwd(const void* Q, const void* K, const void* V, const void* O, c
         return SPION_ERR_NULL;
     const int rc = attn_params_ok(p, nnzb);
     if (rc != SPION_OK) return rc;
-    if (!spion::attn_bwd_grids_fit(p->B * p->H, p->L, p->block, p->L / p->block, nnzb)) return SPION_ERR_SHAPE;
+    if (!spion::attn_bwd_grids_fit(p->B * p->H, p->block, p->L / p->block, nnzb)) return SPION_ERR_SHAPE;
     const size_t need = spion_attn_workspace_bytes(p, nnzb, 1);
     if (!workspace || ((uintptr_t)workspace % kAlign) != 0 || workspace_bytes < need)
         return SPION_ERR_WORKSPACE;

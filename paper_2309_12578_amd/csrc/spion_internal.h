@@ -37,26 +37,27 @@ struct AttnShape {
     int is_bf16;
     float scale;        // resolved score scale (> 0)
     int paper_denom;    // Algorithm 6's extra denominator term
-    int bwd_phases;     // bit 0: query-side kernel (delta, dQ); bit 1: key-side kernel (dK, dV)
+    int bwd_phases;     // bit 0: query side (dQ); bit 1: key side (dK, dV)
 };
 
 hipError_t launch_attn_fwd(const AttnShape& s, const void* Q, const void* K, const void* V, void* O,
-                           float* LSE, const int* row_ptr, const int* col_idx, hipStream_t st);
+                           float* LSE, const int* row_ptr, const int* col_idx, int nnzb, hipStream_t st);
 hipError_t launch_attn_bwd(const AttnShape& s, const void* Q, const void* K, const void* V,
                            const void* O, const void* dO, const float* LSE, void* dQ, void* dK,
                            void* dV, const int* row_ptr, const int* col_idx, const int* col_ptr,
                            const int* row_idx, int nnzb, void* workspace, hipStream_t st);
 
-// Carving of the backward workspace: delta = rowsum(dO .* O) per query, the key-side work list, and
-// fp32 partial dK / dV tiles for block columns that are cut into several chunks.
+// The backward workspace: fp32 partial dK / dV tiles for block columns that are cut into several chunks.
 struct BwdWorkspace {
-    int w_max, n_slots, split_max;
-    size_t delta_off, sched_off, split_off, partial_off, total;
-    BwdWorkspace(int BH, int L, int bs, int nb, int nnzb);
+    int chunk;                       // most kept rows of a key-side work item
+    int w_max, w_first;              // work items per head (upper bound); those that may be chunks come first
+    int n_slots, split_max;          // partial slots per head, split columns (upper bounds)
+    size_t total;
+    BwdWorkspace(int BH, int bs, int nb, int nnzb);
 };
-size_t attn_bwd_workspace_bytes(int BH, int L, int bs, int nb, int nnzb);
+size_t attn_bwd_workspace_bytes(int BH, int bs, int nb, int nnzb);
 // false when a backward launch for this shape would need more workgroups than a 1-D grid can hold
-bool attn_bwd_grids_fit(int BH, int L, int bs, int nb, int nnzb);
+bool attn_bwd_grids_fit(int BH, int bs, int nb, int nnzb);
 
 // attn_bf16_kernels.hip: tuned bf16 forward, BS in {32, 64}
 template <int BS>
@@ -68,8 +69,8 @@ hipError_t fwd_bf16(const AttnShape& s, const void* Q, const void* K, const void
 template <int BS>
 hipError_t bwd_bf16(const AttnShape& s, const void* Q, const void* K, const void* V, const void* O,
                     const void* dO, const float* LSE, void* dQ, void* dK, void* dV, const int* row_ptr,
-                    const int* col_idx, const int* col_ptr, const int* row_idx, int nnzb, int w_max,
-                    int split_max, int n_slots, float* partial, hipStream_t st);
+                    const int* col_idx, const int* col_ptr, const int* row_idx, const BwdWorkspace& ws,
+                    float* partial, hipStream_t st);
 
 }  // namespace spion
 #endif

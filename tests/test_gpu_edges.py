@@ -90,3 +90,22 @@ def test_forward_more_rows_than_run_at_once(sp):
     fl[64, 64] = 0
     fl[100, :] = 0
     _attention(sp, Q, K, V, dO, fl, block, "bf16", [0, 9])
+
+
+# The kernels of fp32 and of block size 16 share a row's tiles over the waves of a workgroup by the average number of
+# tiles and the number of rows: (heads, block rows, density) for four waves a row, for few, and for rows of one
+# block; with rows and columns of 0, 1, 2, 65 and more blocks, odd numbers of tiles, split columns, and head
+# counts that do not divide over the XCDs.
+@pytest.mark.parametrize("dtype,block", [("f32", 16), ("f32", 32), ("f32", 64), ("bf16", 16)])
+@pytest.mark.parametrize("BH,nb,density", [(1, 1, 1.0), (3, 7, 0.3), (2, 70, 0.1), (17, 33, 0.0), (64, 24, 0.05)])
+def test_attention_waves_per_row(sp, dtype, block, BH, nb, density):
+    d = 64
+    rng = np.random.default_rng(nb + block)
+    Q, K, V, dO = [si.round_to_dtype(rng.standard_normal((BH, nb * block, d), dtype=np.float32), dtype)
+                   for _ in range(4)]
+    fl = si.random_block_mask(nb, density, seed=nb) if density < 1.0 else np.ones((nb, nb), dtype=np.uint8)
+    if nb > 5:
+        fl[1, :] = fl[:, 4] = 0
+    if nb > 64:
+        fl[2, :] = fl[:, 3] = 1
+    _attention(sp, Q, K, V, dO, fl, block, dtype, sorted({0, BH // 2, BH - 1}))
