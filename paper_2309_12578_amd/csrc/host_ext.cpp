@@ -268,6 +268,11 @@ PyObject* py_sparse_attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
         ix.block = int_arg(a[9]);
         ix.scale = (float)double_arg(a[10]);
         ix.flags = (unsigned)int_arg(a[11]);
+        for (const at::Tensor* t : {&q, &k, &v})
+            if (t->_fw_grad(0).defined()) {
+                PyErr_SetString(PyExc_NotImplementedError, "sparse_attention has no forward-mode derivative");
+                return nullptr;
+            }
         const bool grad = torch::autograd::compute_requires_grad(q, k, v);
         at::Tensor o, lse, qc, kc, vc;
         {

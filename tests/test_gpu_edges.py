@@ -109,3 +109,36 @@ def test_attention_waves_per_row(sp, dtype, block, BH, nb, density):
     if nb > 64:
         fl[2, :] = fl[:, 3] = 1
     _attention(sp, Q, K, V, dO, fl, block, dtype, sorted({0, BH // 2, BH - 1}))
+
+
+def _small_attention(sp, block=32, nb=3):
+    from test_gpu_parity import _pattern_from_mask
+    pat = _pattern_from_mask(sp, np.tril(np.ones((nb, nb), dtype=np.uint8)), block)
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    q, k, v, do = [torch.randn((1, 2, nb * block, 64), generator=gen, device="cuda") for _ in range(4)]
+    return pat, q, k, v, do
+
+
+def test_autograd_node_beside_the_other_transforms(sp):
+    """Forward-mode and vmap are refused (there is no rule for them), saved-tensor hooks see every tensor kept."""
+    pat, q, k, v, do = _small_attention(sp)
+    with torch.autograd.forward_ad.dual_level():
+        with pytest.raises(NotImplementedError):
+            sp.sparse_attention(torch.autograd.forward_ad.make_dual(q, do), k, v, pat)
+    with pytest.raises(RuntimeError):
+        torch.func.vmap(lambda x: sp.sparse_attention(x, k, v, pat))(torch.stack((q, q)))
+    with pytest.raises(RuntimeError):
+        torch.func.grad(lambda x: sp.sparse_attention(x, k, v, pat).sum())(q)
+    leaves = [t.clone().requires_grad_(True) for t in (q, k, v)]
+    want = torch.autograd.grad(sp.sparse_attention(*leaves, pat), leaves, do)
+    kept = []
+
+    def pack(t):
+        kept.append(tuple(t.shape))
+        return t.detach().cpu()
+
+    with torch.autograd.graph.saved_tensors_hooks(pack, lambda t: t.cuda()):
+        o = sp.sparse_attention(*leaves, pat)
+    assert sorted(kept) == sorted([tuple(q.shape)] * 4 + [tuple(q.shape[:3])])
+    for a, b in zip(torch.autograd.grad(o, leaves, do), want):
+        assert torch.equal(a, b)
