@@ -806,8 +806,11 @@ __global__ __launch_bounds__(kFinishThreads) void pattern_finish_kernel(
         }
     }
     if (nnzb_host) {
-        __syncthreads();   // every wave's stores are out
-        if (tid == 0) __hip_atomic_store(nnzb_host, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        // A host that has seen the word may go on with the pattern on any stream, so the stores have to have left
+        // this XCD's L2 by then: every wave's have reached it, then one release writes them back.
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid == 0) __hip_atomic_store(nnzb_host, total, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 

@@ -142,3 +142,18 @@ def test_autograd_node_beside_the_other_transforms(sp):
     assert sorted(kept) == sorted([tuple(q.shape)] * 4 + [tuple(q.shape[:3])])
     for a, b in zip(torch.autograd.grad(o, leaves, do), want):
         assert torch.equal(a, b)
+
+
+def test_pattern_on_another_stream_right_after_the_call(sp):
+    # generate_pattern has waited for the pattern, so any stream may read it without waiting for the producer's
+    nb, block = 64, 16
+    other = torch.cuda.Stream()
+    for seed in range(5):
+        A = torch.rand((nb * block, nb * block), generator=torch.Generator().manual_seed(seed)) ** 6
+        pat = sp.generate_pattern(A.cuda(), block, 5, si.T_QUANTILE, 0.8)
+        with torch.cuda.stream(other):
+            got = [t.clone() for t in (pat.fl_out, pat.row_ptr, pat.col_ptr, pat.pool_sum)]
+        ref = oracle.generate_pattern(A.numpy(), block, 5, si.T_QUANTILE, 0.8)
+        other.synchronize()
+        for t, name in zip(got, ("fl_out", "row_ptr", "col_ptr", "pool_sum")):
+            assert np.array_equal(t.cpu().numpy(), ref[name]), name
