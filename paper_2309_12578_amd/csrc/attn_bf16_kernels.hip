@@ -41,43 +41,6 @@ __device__ __forceinline__ void stage_ready(bool younger_in_flight) {
     asm volatile("" ::: "memory");
 }
 
-// Which block row the workgroup number l of the `heads` heads of an XCD takes, when there are more workgroups
-// than run at once: the rows with more than twice the mean number of kept blocks first, of all the heads (a
-// row of 80 blocks that starts last runs alone for as long as everything before it took), then head by
-// head the others, so that neighbours in time share K and V in the XCD's L2.
-// All lanes of the calling wave must be active.
-struct RowOfHead {
-    int row, head;
-};
-__device__ __forceinline__ RowOfHead long_rows_first(const int* __restrict__ row_ptr, int nb, int heads, int l, int lane) {
-    const int limit = 2 * row_ptr[nb] / nb;
-    int n_long = 0;
-    for (int base = 0; base < nb; base += 64) {
-        const int r = base + lane;
-        n_long += __popcll(__ballot(r < nb && row_ptr[r + 1] - row_ptr[r] > limit));
-    }
-    const bool want_long = l < heads * n_long;
-    int head, rank;
-    if (want_long) {
-        head = l % heads;
-        rank = l / heads;
-    } else {
-        head = (l - heads * n_long) / (nb - n_long);
-        rank = (l - heads * n_long) % (nb - n_long);
-    }
-    for (int base = 0; base < nb; base += 64) {   // the counts are in the cache by now
-        const int r = base + lane;
-        const unsigned long long mine = __ballot(r < nb && (row_ptr[r + 1] - row_ptr[r] > limit) == want_long);
-        const int cnt = __popcll(mine);
-        if (rank < cnt) {
-            const unsigned long long hit = __ballot(((mine >> lane) & 1ull) && lanes_below(mine) == rank);
-            return {base + __ffsll((long long)hit) - 1, head};
-        }
-        rank -= cnt;
-    }
-    return {0, head};
-}
-
 template <int BS>
 __global__ __launch_bounds__(BS * 4) void attn_fwd_bf16_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,

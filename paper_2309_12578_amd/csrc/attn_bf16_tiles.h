@@ -156,5 +156,46 @@ __device__ __forceinline__ int walk_index(int t, int pd) {
     return pd < 0 ? t : (t == 0 ? pd : (t - 1 < pd ? t - 1 : t));
 }
 
+// Which block row the workgroup number l of the `heads` heads of an XCD takes, when there are more workgroups
+// than run at once: the rows with more than twice the mean number of kept blocks first, of all the heads (a
+// row of 80 blocks that starts last runs alone for as long as everything before it took), then head by
+// head the others, so that neighbours in time share K and V in the XCD's L2.
+// All lanes of the calling wave must be active.
+struct RowOfHead {
+    int row, head;
+};
+__device__ __forceinline__ RowOfHead long_rows_first(const int* __restrict__ row_ptr, int nb, int heads, int l, int lane) {
+    const int limit = 2 * row_ptr[nb] / nb;
+    int n_long = 0, cnt_first = 0;   // rows 0 .. 63 are kept for the second search
+    for (int base = 0; base < nb; base += 64) {
+        const int r = base + lane;
+        const int cnt = r < nb ? row_ptr[r + 1] - row_ptr[r] : 0;
+        if (base == 0) cnt_first = cnt;
+        n_long += __popcll(__ballot(r < nb && cnt > limit));
+    }
+    const bool want_long = l < heads * n_long;
+    int head, rank;
+    if (want_long) {
+        head = l % heads;
+        rank = l / heads;
+    } else {
+        head = (l - heads * n_long) / (nb - n_long);
+        rank = (l - heads * n_long) % (nb - n_long);
+    }
+    for (int base = 0; base < nb; base += 64) {   // the counts are in the cache by now
+        const int r = base + lane;
+        int cnt = cnt_first;
+        if (base != 0) cnt = r < nb ? row_ptr[r + 1] - row_ptr[r] : 0;
+        const unsigned long long mine = __ballot(r < nb && (cnt > limit) == want_long);
+        const int members = __popcll(mine);
+        if (rank < members) {
+            const unsigned long long hit = __ballot(((mine >> lane) & 1ull) && lanes_below(mine) == rank);
+            return {base + __ffsll((long long)hit) - 1, head};
+        }
+        rank -= members;
+    }
+    return {0, head};
+}
+
 }  // namespace spion
 #endif

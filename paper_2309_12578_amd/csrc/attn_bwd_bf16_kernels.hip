@@ -47,7 +47,10 @@ __device__ __forceinline__ void lds_barrier() {
 // the short columns fill in behind them.  With B H a multiple of 8 each XCD (own L2; workgroups
 // are dealt to the XCDs round-robin) works on whole heads, items of all its heads interleaved.
 // n_key_a / n_rows / n_key_c are the per-head counts of the three groups present in this launch
-// (a group is absent when only one side is requested).
+// (a group is absent when only one side is requested).  w_first leaves room for a quarter of the columns
+// besides the chunks: unsplit columns of more than kMidColumn rows that came last ran on alone (64 heads x 1024,
+// block 32, 4.8 blocks a row: 31.6 -> 26.5 us; 4 and 12 measure like 8, and a sixth or a third of the columns like a
+// quarter).  With sort_rows the rows of more than twice the mean length come before the others.
 // ------------------------------------------------------------------------------------------------
 template <int BS>
 __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
@@ -56,7 +59,7 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
     bf16_t* __restrict__ dQ, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV,
     const int* __restrict__ row_ptr, const int* __restrict__ col_idx, const int* __restrict__ col_ptr,
     const int* __restrict__ row_idx, float* __restrict__ partial, int n_slots, int BH, int L, int nb,
-    int n_key_a, int n_rows, int n_key_c, int w_first, float scale, float scale_log2) {
+    int n_key_a, int n_rows, int n_key_c, int w_first, int chunk, int sort_rows, float scale, float scale_log2) {
     constexpr int NT = BS / 16;   // 16-row tiles per block = waves per workgroup
     // Separate objects, so that the compiler can tell a read of one tile from a load in flight into
     // another and does not wait for it.  Query side: {ta, tb} hold {K, V} of a block, three stages
@@ -86,8 +89,14 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
     } else if (l < hpx * (n_key_a + n_rows)) {
         l -= hpx * n_key_a;
         key_side = false;
-        bh = x * hpx + l / nb;
-        idx = l % nb;
+        if (sort_rows) {
+            const RowOfHead at = long_rows_first(row_ptr, nb, hpx, l, lane);
+            bh = x * hpx + at.head;
+            idx = at.row;
+        } else {
+            bh = x * hpx + l / nb;
+            idx = l % nb;
+        }
     } else {
         l -= hpx * (n_key_a + n_rows);
         key_side = true;
@@ -220,15 +229,15 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
     // ============================================================================================
     // key side: work item idx of head bh.  {Q, dO, O} tiles and LSE of a block row in two stages.
     // ============================================================================================
-    const KeyItem item = key_item_lookup(col_ptr, nb, kChunk, idx, lane);
+    const KeyItem item = key_item_lookup<true>(col_ptr, nb, chunk, idx, lane);
     if (item.J < 0) return;
     const int J = item.J, n = item.ke - item.kb, slot = item.slot;
     const int krow = J * BS + wave * 16 + r;
     const int last = n > 0 ? n - 1 : 0;
-    // the item's block rows, one per lane (an item has at most kChunk <= 64 of them): read once, so that
+    // the item's block rows, one per lane (an item has at most 64 of them): read once, so that
     // no scalar load is in flight inside the steps (scalar loads return out of order, and while one is
     // outstanding every wait for an LDS read has to wait for all of them)
-    static_assert(kChunk <= 64, "a key-side work item must fit one wave's lanes");
+    static_assert(kChunkMax <= 64, "a key-side work item must fit one wave's lanes");
     const int rows_v = n > 0 ? row_idx[item.kb + (lane < last ? lane : last)] : 0;
     auto row_at = [&](int t) { return __builtin_amdgcn_readlane(rows_v, t < last ? t : last); };
 
@@ -377,11 +386,16 @@ hipError_t bwd_bf16(const AttnShape& s, const void* Q, const void* K, const void
     const int n_key_a = keys ? ws.w_first : 0, n_rows = rows ? s.nb : 0, n_key_c = keys ? ws.w_max - ws.w_first : 0;
     const long long total = (long long)s.BH * (n_key_a + n_rows + n_key_c);
     if (total > 0) {
+        // A row of more than twice the mean that starts late runs alone at the end; finding the rows by length
+        // costs each about half a step.  Worth it where such rows are long, by themselves (a mean of 6
+        // blocks) or can be against the steps a slot has to do: 16 heads x 8192, block 32, 12.8 blocks a row 130 -> 98 us,
+        // 64 heads x 1024, 4.8 blocks a row 26.9 -> 28.3 us.
+        const int sort_rows = total > bwd_resident(BS) && (ws.nnzb >= 6 * s.nb || s.nb >= 8 * bwd_steps_per_slot(s.BH, BS, s.nb, ws.nnzb));
         attn_bwd_bf16_kernel<BS><<<dim3((unsigned)total), dim3(BS * 4), 0, st>>>(
             static_cast<const bf16_t*>(Q), static_cast<const bf16_t*>(K), static_cast<const bf16_t*>(V),
             static_cast<const bf16_t*>(O), static_cast<const bf16_t*>(dO), LSE, static_cast<bf16_t*>(dQ),
             static_cast<bf16_t*>(dK), static_cast<bf16_t*>(dV), row_ptr, col_idx, col_ptr, row_idx, partial,
-            ws.n_slots, s.BH, s.L, s.nb, n_key_a, n_rows, n_key_c, ws.w_first, s.scale, s.scale * kLog2e);
+            ws.n_slots, s.BH, s.L, s.nb, n_key_a, n_rows, n_key_c, ws.w_first, ws.chunk, sort_rows, s.scale, s.scale * kLog2e);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -461,7 +461,7 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_bwd_kernel(
         return;
     }
 
-    const KeyItem it = key_item_lookup(col_ptr, nb, chunk, idx, lane);
+    const KeyItem it = key_item_lookup<false>(col_ptr, nb, chunk, idx, lane);
     if (it.J < 0) return;
     const int n = it.ke - it.kb, nt = n * S::TPB, row0 = it.J * BS + sub + own;
     const int* rows = row_idx + it.kb;
@@ -560,19 +560,22 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_bwd_kernel(
 // ------------------------------------------------------------------------------------------------
 // host launchers
 // ------------------------------------------------------------------------------------------------
-BwdWorkspace::BwdWorkspace(int BH, int bs, int nb, int nnzb) {
-    chunk = kChunk;
+BwdWorkspace::BwdWorkspace(int BH, int bs, int nb, int nnzb_, int key_chunk, int mid_first) {
+    nnzb = nnzb_;
+    chunk = key_chunk;
     w_max = nnzb / chunk + nb;
-    w_first = nnzb / chunk + 1 < w_max ? nnzb / chunk + 1 : w_max;
+    w_first = nnzb / chunk + 1 + mid_first;
+    if (w_first > w_max) w_first = w_max;
     n_slots = 2 * (nnzb / chunk) + 2;
     split_max = nb > chunk ? nnzb / (chunk + 1) : 0;
-    total = (size_t)BH * n_slots * 2 * bs * kD * sizeof(float);   // a multiple of 256
+    // for the shortest chunks, so that a workspace for more kept blocks also serves fewer; a multiple of 256
+    total = (size_t)BH * (2 * (nnzb / kChunk) + 2) * 2 * bs * kD * sizeof(float);
 }
 
-size_t attn_bwd_workspace_bytes(int BH, int bs, int nb, int nnzb) { return BwdWorkspace(BH, bs, nb, nnzb).total; }
+size_t attn_bwd_workspace_bytes(int BH, int bs, int nb, int nnzb) { return BwdWorkspace(BH, bs, nb, nnzb, kChunk, 0).total; }
 
 bool attn_bwd_grids_fit(int BH, int bs, int nb, int nnzb) {
-    const BwdWorkspace ws(BH, bs, nb, nnzb);
+    const BwdWorkspace ws(BH, bs, nb, nnzb, kChunk, 0);
     const int64_t limit = 0x7fffffffll, parts = bs == 64 ? 2 : 1;
     return (int64_t)(ws.w_max + nb) * BH * parts + 24 <= limit &&
            (int64_t)ws.split_max * BH * (bs / 16) <= limit;
@@ -638,11 +641,12 @@ static hipError_t bwd_t(const AttnShape& s, const void* Q, const void* K, const 
                         const void* dO, const float* LSE, void* dQ, void* dK, void* dV,
                         const int* row_ptr, const int* col_idx, const int* col_ptr, const int* row_idx,
                         int nnzb, void* workspace, hipStream_t st) {
-    const BwdWorkspace ws(s.BH, s.bs, s.nb, nnzb);
     float* partial = static_cast<float*>(workspace);
     if constexpr (sizeof(T) == 2 && BS >= 32) {
+        const BwdWorkspace ws(s.BH, s.bs, s.nb, nnzb, key_chunk(s.BH, BS, s.nb, nnzb), s.nb / 4);
         return bwd_bf16<BS>(s, Q, K, V, O, dO, LSE, dQ, dK, dV, row_ptr, col_idx, col_ptr, row_idx, ws, partial, st);
     } else {
+        const BwdWorkspace ws(s.BH, s.bs, s.nb, nnzb, kChunk, 0);
         auto* launch = launch_bwd<T, BS, SplitFew<T, BS>>;
         if (many_short_rows(s, nnzb))
             launch = single_block_rows(s, nnzb) ? launch_bwd<T, BS, typename SplitMany<T, BS>::bwd_single>

@@ -14,17 +14,35 @@ namespace spion {
 // ------------------------------------------------------------------------------------------------
 // Vertical stripes give block columns with up to nb kept rows next to columns with one or two, so the key
 // side does not take one column per workgroup.  The items are derived from col_ptr alone (the same list
-// for every head).  A column with cnt kept rows is cut into nch = ceil(cnt / kChunk) near-equal chunks if
-// cnt > kChunk, else it is one item (also when cnt == 0: its dK / dV must still be written as zeros).
-// Items are numbered with the chunks of split columns first, in column order (they are the longest and
-// start first), then the unsplit columns in column order.  Chunk number w of that first group writes its
-// fp32 partial tiles to slot w; a second kernel adds them up in chunk order (deterministic, no atomics).
+// for every head).  A column with cnt kept rows is cut into nch = ceil(cnt / chunk) near-equal chunks if
+// cnt > chunk, else it is one item (also when cnt == 0: its dK / dV must still be written as zeros).
+// Items are numbered longest first, as far as that is cheap to find: the chunks of split columns in column
+// order, then (tuned kernels) the unsplit columns of more than kMidColumn rows, then the others.  Chunk number w of the first group
+// writes its fp32 partial tiles to slot w; a second kernel adds them up in chunk order (deterministic, no
+// atomics).
 // ------------------------------------------------------------------------------------------------
-#ifndef SPION_KEY_CHUNK
-#define SPION_KEY_CHUNK 16   // kept rows per key-side work item (build-time tunable; 10-16 measure alike,
-                             // shorter chunks cost partial-tile traffic, longer ones the longest chain)
-#endif
-constexpr int kChunk = SPION_KEY_CHUNK;
+constexpr int kChunk = 16;      // the shortest chunk that is cut: partial tiles are sized for it
+constexpr int kChunkMax = 64;   // the longest
+constexpr int kMidColumn = 8;   // an unsplit column of more kept rows starts before the block rows
+
+// Workgroups of the tuned backward that run at once: 164 VGPRs let three waves share a SIMD.
+inline int bwd_resident(int bs) { return 256 * (bs == 64 ? 3 : 6); }
+
+// Steps that each of them has to do in a balanced run, both sides, the fixed cost of a workgroup taken as one.
+inline long long bwd_steps_per_slot(int BH, int bs, int nb, int nnzb) {
+    return 2LL * BH * ((long long)nnzb + nb) / bwd_resident(bs);
+}
+
+// Most kept rows of a work item of the tuned backward.  A cut costs a partial tile written and read back for
+// each piece; an uncut column is one chain of steps, which only has to end before the rest of the launch
+// does: so as long as a balanced run.  Measured, backward call in us with chunks of 16 / 24 / 32 / 64:
+// 16 heads x 4096, block 64, 328 blocks (16 steps a slot) 37 / 38 / 44 / 68; 32 heads, 410 blocks (39) 79 / 76 /
+// 76 / 70, 852 blocks (76) 149 / 146 / 138 / 129 (121 with long rows first); 16 heads x 8192, block 32, 3277
+// blocks (73) 143 / 136 / 130 / 98 (last with long rows first).
+inline int key_chunk(int BH, int bs, int nb, int nnzb) {
+    const long long c = bwd_steps_per_slot(BH, bs, nb, nnzb);
+    return (int)(c < kChunk ? kChunk : c > kChunkMax ? kChunkMax : c);
+}
 
 struct KeyItem {
     int J;      // block column, -1: no such item
@@ -32,16 +50,17 @@ struct KeyItem {
     int slot;   // partial slot, -1: the item covers its whole column and writes dK / dV itself
 };
 
-// All lanes of the calling wave must be active; the result is wave-uniform.
-__device__ __forceinline__ KeyItem key_item_lookup(const int* __restrict__ col_ptr, int nb, int chunk, int w,
-                                                   int lane) {
+// All lanes of the calling wave must be active; the result is wave-uniform.  MID_FIRST: see kMidColumn.
+template <bool MID_FIRST>
+__device__ __forceinline__ KeyItem key_item_lookup(const int* __restrict__ col_ptr, int nb, int chunk, int w, int lane) {
     KeyItem none = {-1, 0, 0, -1};
-    if (nb <= chunk) {   // no column is cut
+    if (nb <= (MID_FIRST ? kMidColumn : chunk)) {   // all alike
         if (w >= nb) return none;
         KeyItem it = {w, col_ptr[w], col_ptr[w + 1], -1};
         return it;
     }
-    int run = 0;   // chunks of split columns in the column groups before this one
+    int run = 0;     // chunks of split columns in the column groups before this one
+    int n_mid = 0;   // unsplit columns of more than kMidColumn rows
     int c0_first = 0, cnt_first = 0;   // columns 0 .. 63, kept for the second search
     for (int base = 0; base < nb; base += 64) {
         const int J = base + lane;
@@ -65,8 +84,11 @@ __device__ __forceinline__ KeyItem key_item_lookup(const int* __restrict__ col_p
             return it;
         }
         run += __builtin_amdgcn_readlane(incl, 63);
+        if (MID_FIRST) n_mid += __popcll(__ballot(cnt > kMidColumn && cnt <= chunk));
     }
-    int u = w - run;   // index among the unsplit columns
+    int u = w - run;   // index among the unsplit columns, then among those of its class
+    const bool is_mid = MID_FIRST && u < n_mid;
+    if (MID_FIRST && !is_mid) u -= n_mid;
     for (int base = 0; base < nb; base += 64) {
         const int J = base + lane;
         const bool valid = J < nb;
@@ -75,14 +97,15 @@ __device__ __forceinline__ KeyItem key_item_lookup(const int* __restrict__ col_p
             c0 = valid ? col_ptr[J] : 0;
             c1 = valid ? col_ptr[J + 1] : 0;
         }
-        const unsigned long long whole = __ballot(valid && c1 - c0 <= chunk);
-        const unsigned long long hit = __ballot(valid && c1 - c0 <= chunk && lanes_below(whole) == u);
+        const bool in = valid && c1 - c0 <= chunk && (!MID_FIRST || (c1 - c0 > kMidColumn) == is_mid);
+        const unsigned long long members = __ballot(in);
+        const unsigned long long hit = __ballot(in && lanes_below(members) == u);
         if (hit) {
             const int src = __ffsll((long long)hit) - 1;
             KeyItem it = {base + src, __builtin_amdgcn_readlane(c0, src), __builtin_amdgcn_readlane(c1, src), -1};
             return it;
         }
-        u -= __popcll(whole);
+        u -= __popcll(members);
     }
     return none;
 }

@@ -49,11 +49,13 @@ hipError_t launch_attn_bwd(const AttnShape& s, const void* Q, const void* K, con
 
 // The backward workspace: fp32 partial dK / dV tiles for block columns that are cut into several chunks.
 struct BwdWorkspace {
+    int nnzb;
     int chunk;                       // most kept rows of a key-side work item
     int w_max, w_first;              // work items per head (upper bound); those that may be chunks come first
     int n_slots, split_max;          // partial slots per head, split columns (upper bounds)
     size_t total;
-    BwdWorkspace(int BH, int bs, int nb, int nnzb);
+    // mid_first: unsplit columns to make room for among the items that come first
+    BwdWorkspace(int BH, int bs, int nb, int nnzb, int key_chunk, int mid_first);
 };
 size_t attn_bwd_workspace_bytes(int BH, int bs, int nb, int nnzb);
 // false when a backward launch for this shape would need more workgroups than a 1-D grid can hold
