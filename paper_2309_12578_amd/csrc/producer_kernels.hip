@@ -11,64 +11,64 @@
 namespace spion {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+template <typename T> struct MapVec { typedef f32x4_t type; };
+template <> struct MapVec<__bf16> { typedef bf16x8_t type; };
 
 // out[i] = (sum over maps m = 0 .. n_maps-1, in that order, of A[m][i]) / n_maps, fp32 arithmetic.
-// One thread owns 4 (fp32) or 8 (bf16) consecutive elements; loads of 8 maps are kept in flight.
-template <typename T>
+// Bound by HBM reads.  A thread owns U vectors of 16 bytes, 256 vectors apart; its loads of 8 maps are in flight
+// together, also of the last, incomplete 8.  The maps are read once and past the caches' keeping: as ordinary
+// loads, one vector a thread, 16 bf16 maps of 4096^2 took 117 us (5.2 TB/s), non-temporal 105, two vectors 99
+// (6.1 TB/s); 16 maps or 4 vectors in flight, or a grid of 1024 or 2048 workgroups, measure the same or slower.
+template <typename T, int U>
 __global__ __launch_bounds__(256) void score_mean_kernel(const T* __restrict__ A, int n_maps, size_t n,
                                                          float* __restrict__ out) {
-    constexpr int V = 16 / sizeof(T);   // elements per 16-byte load
+    typedef typename MapVec<T>::type Vec;
+    constexpr int V = 16 / sizeof(T);   // elements per vector
     const size_t nvec = n / V;
     const float inv = 1.0f / (float)n_maps;
-    for (size_t v = (size_t)blockIdx.x * blockDim.x + threadIdx.x; v < nvec; v += (size_t)gridDim.x * blockDim.x) {
-        float acc[V];
+    for (size_t v0 = (size_t)blockIdx.x * (256 * U) + threadIdx.x; v0 < nvec; v0 += (size_t)gridDim.x * (256 * U)) {
+        float acc[U][V];
 #pragma unroll
-        for (int e = 0; e < V; ++e) acc[e] = 0.f;
-        const T* p = A + v * V;
-        int m = 0;
-        for (; m + 8 <= n_maps; m += 8) {   // 8 maps in flight, added in map order
-            if constexpr (sizeof(T) == 4) {
-                float4 x[8];
+        for (int u = 0; u < U; ++u)
 #pragma unroll
-                for (int u = 0; u < 8; ++u) x[u] = *reinterpret_cast<const float4*>(p + (size_t)(m + u) * n);
+            for (int e = 0; e < V; ++e) acc[u][e] = 0.f;
+        const T* p[U];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    acc[0] += x[u].x;
-                    acc[1] += x[u].y;
-                    acc[2] += x[u].z;
-                    acc[3] += x[u].w;
+        for (int u = 0; u < U; ++u) p[u] = A + (v0 + u * 256 < nvec ? v0 + u * 256 : nvec - 1) * V;
+        auto add8 = [&](int m, int maps) {   // maps m .. m + maps - 1, uniform; a literal 8 leaves no branches
+            Vec x[8][U];
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (j < maps) {
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        x[j][u] = __builtin_nontemporal_load(reinterpret_cast<const Vec*>(p[u] + (size_t)(m + j) * n));
                 }
-            } else {
-                bf16x8_t x[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) x[u] = *reinterpret_cast<const bf16x8_t*>(p + (size_t)(m + u) * n);
+            for (int j = 0; j < 8; ++j)
+                if (j < maps) {
 #pragma unroll
-                for (int u = 0; u < 8; ++u)
+                    for (int u = 0; u < U; ++u)
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) acc[e] += (float)x[u][e];
+                        for (int e = 0; e < V; ++e) acc[u][e] += (float)x[j][u][e];
+                }
+        };
+        int m = 0;
+        for (; m + 8 <= n_maps; m += 8) add8(m, 8);
+        if (m < n_maps) add8(m, n_maps - m);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (v0 + u * 256 < nvec) {
+#pragma unroll
+                for (int e = 0; e < V; e += 4)
+                    *reinterpret_cast<float4*>(out + (v0 + u * 256) * V + e) =
+                        make_float4(acc[u][e] * inv, acc[u][e + 1] * inv, acc[u][e + 2] * inv, acc[u][e + 3] * inv);
             }
-        }
-        for (; m < n_maps; ++m) {
-            if constexpr (sizeof(T) == 4) {
-                const float4 x = *reinterpret_cast<const float4*>(p + (size_t)m * n);
-                acc[0] += x.x;
-                acc[1] += x.y;
-                acc[2] += x.z;
-                acc[3] += x.w;
-            } else {
-                const bf16x8_t x = *reinterpret_cast<const bf16x8_t*>(p + (size_t)m * n);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) acc[e] += (float)x[e];
-            }
-        }
-#pragma unroll
-        for (int e = 0; e < V; e += 4)
-            *reinterpret_cast<float4*>(out + v * V + e) =
-                make_float4(acc[e] * inv, acc[e + 1] * inv, acc[e + 2] * inv, acc[e + 3] * inv);
     }
 }
 
-constexpr int kFrobBlocks = 4096, kFrobThreads = 256;
+constexpr int kFrobBlocks = 1024, kFrobThreads = 256;
 
 __device__ __forceinline__ double wave_sum_f64(double v) {
 #pragma unroll
@@ -76,24 +76,27 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
     return v;
 }
 
-// partial[b] = {sum of squares of a, sum of squares of b} over the float4s block b owns (fp64)
+// partial[b] = {sum of squares of a, sum of squares of b} over the float4s block b owns (fp64).  Bound by HBM reads.
+// 4 workgroups a compute unit keep them going as well as 16, and the one workgroup that adds up the
+// partials then has a quarter of them: with 4096, and ordinary loads, the call took 31.8 us for two maps of
+// 4096^2 and 12.0 for two of 512^2, now 25.3 (5.3 TB/s) and 6.1.
 __global__ __launch_bounds__(kFrobThreads) void frobenius_partial_kernel(const float* __restrict__ a,
                                                                         const float* __restrict__ b, size_t n,
                                                                         double2* __restrict__ partial) {
     const size_t nvec = n / 4;
     const size_t stride = (size_t)kFrobBlocks * kFrobThreads;
     double sa = 0.0, sb = 0.0;
-    auto sq = [](double acc, const float4 x) {
+    auto sq = [](double acc, const f32x4_t x) {
         return acc + ((double)x.x * x.x + (double)x.y * x.y) + ((double)x.z * x.z + (double)x.w * x.w);
     };
     size_t v = (size_t)blockIdx.x * kFrobThreads + threadIdx.x;
     // four float4 of each array in flight per thread
     for (; v + 3 * stride < nvec; v += 4 * stride) {
-        float4 x[4], y[4];
+        f32x4_t x[4], y[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            x[u] = reinterpret_cast<const float4*>(a)[v + u * stride];
-            y[u] = reinterpret_cast<const float4*>(b)[v + u * stride];
+            x[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(a) + v + u * stride);
+            y[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(b) + v + u * stride);
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -102,8 +105,8 @@ __global__ __launch_bounds__(kFrobThreads) void frobenius_partial_kernel(const f
         }
     }
     for (; v < nvec; v += stride) {
-        sa = sq(sa, reinterpret_cast<const float4*>(a)[v]);
-        sb = sq(sb, reinterpret_cast<const float4*>(b)[v]);
+        sa = sq(sa, reinterpret_cast<const f32x4_t*>(a)[v]);
+        sb = sq(sb, reinterpret_cast<const f32x4_t*>(b)[v]);
     }
     if (blockIdx.x == 0 && threadIdx.x == 0)   // tail: n not a multiple of 4
         for (size_t i = nvec * 4; i < n; ++i) {
@@ -151,17 +154,22 @@ __global__ __launch_bounds__(kFrobThreads) void frobenius_final_kernel(const dou
     }
 }
 
-hipError_t launch_score_mean(const void* A, int is_bf16, int n_maps, size_t n, float* out, hipStream_t st) {
-    const size_t nvec = n / (is_bf16 ? 8 : 4);
-    size_t blocks = (nvec + 255) / 256;
-    if (blocks > 65536) blocks = 65536;
-    if (is_bf16)
-        score_mean_kernel<__bf16><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(static_cast<const __bf16*>(A),
-                                                                                 n_maps, n, out);
-    else
-        score_mean_kernel<float><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(static_cast<const float*>(A),
-                                                                               n_maps, n, out);
+template <typename T>
+static hipError_t mean_t(const T* A, int n_maps, size_t n, float* out, hipStream_t st) {
+    const size_t nvec = n * sizeof(T) / 16;
+    // two vectors a thread where that still gives every compute unit its eight workgroups
+    if (nvec >= 2048 * 512) {
+        const size_t blocks = (nvec + 511) / 512, most = (size_t)1 << 22;
+        score_mean_kernel<T, 2><<<dim3((unsigned)(blocks < most ? blocks : most)), dim3(256), 0, st>>>(A, n_maps, n, out);
+    } else {
+        score_mean_kernel<T, 1><<<dim3((unsigned)((nvec + 255) / 256)), dim3(256), 0, st>>>(A, n_maps, n, out);
+    }
     return hipGetLastError();
+}
+
+hipError_t launch_score_mean(const void* A, int is_bf16, int n_maps, size_t n, float* out, hipStream_t st) {
+    return is_bf16 ? mean_t(static_cast<const __bf16*>(A), n_maps, n, out, st)
+                   : mean_t(static_cast<const float*>(A), n_maps, n, out, st);
 }
 
 size_t frobenius_workspace_bytes() { return (size_t)kFrobBlocks * sizeof(double2); }

@@ -173,3 +173,22 @@ def test_backward_chunks_follow_the_work(sp, BH, nb, density, block):
     fl[nb - 3, :] = 1
     fl[1, :] = 0
     _attention(sp, Q, K, V, dO, fl, block, "bf16", [0, BH - 1])
+
+
+# Vectors of 16 bytes, one or two per thread (two from 2^20 vectors), 8 maps at a time and a remainder of 0 to 7
+@pytest.mark.parametrize("L,maps,dtype", [(8, 1, "f32"), (8, 9, "bf16"), (104, 7, "bf16"), (200, 16, "f32"),
+                                          (2056, 3, "f32"), (2904, 10, "bf16")])
+def test_score_mean_and_distance_at_the_edges(sp, L, maps, dtype):
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    A = torch.rand((maps, L, L), generator=gen, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    want = torch.zeros((L, L), device="cuda")
+    for m in range(maps):
+        want += A[m].float()   # the order of the sum is the definition
+    want *= torch.tensor(1.0, device="cuda") / torch.tensor(float(maps), device="cuda")
+    mean = sp.score_mean(A)
+    assert torch.equal(mean, want)
+    prev = torch.rand((L, L), generator=gen, device="cuda")
+    a, b = prev.double().norm().item(), mean.double().norm().item()
+    got = sp.frobenius_distance(prev, mean).cpu().numpy()
+    # sums of L^2 squares in fp64 in another order: relative error below L^2 2^-53
+    assert np.allclose(got, (abs(a - b), a, b), rtol=0.0, atol=L * L * 2.0 ** -53 * (a + b))
