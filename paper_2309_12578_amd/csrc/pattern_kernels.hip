@@ -828,8 +828,8 @@ __global__ __launch_bounds__(kFinishThreads) void pattern_finish_kernel(
 //              1 the fill (the expanded cells of every row): neither needs the other
 //   words      grid_words_kernel: kept bits per row and, transposed, per column, and their counts
 //   index      grid_index_kernel: BSR and BSC
-// Measured at nb = 512: the five
-// kernels take 10 + 9 + 49 + 12 + 10 us, one workgroup with a barrier per anti-diagonal took 2454; the fill's chain, 225 cycles per row, is the longest part.
+// Measured at nb = 512: the five kernels take 9 + 9 + 29 + 13 + 9 us (one workgroup with a barrier per
+// anti-diagonal took 2454); the longest part is the serial one, its threshold and its fill about alike.
 constexpr int kGridBins = 4096;
 constexpr int kGridMax = 1024;   // same bound as SPION_MAX_NB of the public header
 
@@ -997,29 +997,50 @@ __global__ __launch_bounds__(256) void grid_bits_kernel(const long long* __restr
     }
 }
 
-// The fill on rows of up to 1024 bits: lane l of wave 0 holds columns 32 l .. 32 l + 31.  The carries of a
-// row's addition cross lanes the same way they cross bits: lanes that generate one (the 32-bit sum
-// overflowed) and lanes that pass one on (the sum is all ones) are two bit sets in scalar registers, and
-// which lanes receive a carry is again x | (((x & P) + P) ^ P).  The other waves bring the words of the
-// next kFillRows rows into LDS meanwhile: a trip to memory takes longer than a row.
-constexpr int kFillRows = 32;
-constexpr int kFillWords = kFillRows * 3 * (kGridMax / 32);   // down, right, diagonal words of a piece
+// The fill on rows of up to 1024 bits: lane l of wave 0 holds columns 32 l .. 32 l + 31 and is l rows behind lane 0.
+// In step t it works on row t - l, for which its left neighbour found the carry out of the row's addition and the
+// diagonal entry into the next word one step before: the one reaches it as a bit set in scalar registers,
+// shifted by one lane, the other as a lane shift, both away from the chain of the step, which is seven vector
+// instructions.  (All lanes on one row, the carries resolved by a second addition on the bit set of lanes that
+// generate one, took 225 cycles a row instead of about 115: the kernel 49 -> 29 us at nb = 512, 26.5 -> 17.6 at 256.)
+// The other waves bring the words of the next kFillSteps steps into LDS, those of lane l l rows further up, and
+// store what was found in the steps before, which takes the place of the words of `right`: a trip to memory
+// takes longer than many steps.
+constexpr int kFillSteps = 64;
+constexpr int kFillLd = kGridMax / 32;                  // words of a step in LDS, used or not
+constexpr int kFillPlane = kFillSteps * kFillLd;        // one array's words of a piece
+constexpr int kFillWords = 2 * 3 * kFillPlane;          // two pieces of down, right, diagonal
 
-__device__ void grid_fill(const GridScratch& s, int nb, unsigned* buf /* 2 * kFillWords, LDS */) {
+__device__ void grid_fill(const GridScratch& s, int nb, unsigned* buf /* kFillWords, LDS */) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int W2 = 2 * ((nb + 63) >> 6);   // 32-bit words per row
-    const int plane = kFillRows * W2;
-    auto bring = [&](int piece, int first, int threads) {   // rows kFillRows * piece .. of the three arrays
-        const int words = min(kFillRows, nb - piece * kFillRows) * W2;
-        unsigned* const dst = buf + (piece & 1) * kFillWords;
-        const size_t from = (size_t)piece * plane;
-        for (int i = tid - first; i < words; i += threads) {
-            const unsigned d = reinterpret_cast<const unsigned*>(s.down)[from + i];
-            const unsigned r = reinterpret_cast<const unsigned*>(s.right)[from + i];
-            const unsigned g = reinterpret_cast<const unsigned*>(s.diag)[from + i];
-            dst[i] = d;
-            dst[plane + i] = r;
-            dst[2 * plane + i] = g;
+    const int pieces = (nb + W2 - 1 + kFillSteps - 1) / kFillSteps;
+    constexpr int kOwn = (kFillPlane + kFinishThreads - 65) / (kFinishThreads - 64);   // words of a thread
+    const unsigned* const arr[3] = {reinterpret_cast<const unsigned*>(s.down), reinterpret_cast<const unsigned*>(s.right),
+                                    reinterpret_cast<const unsigned*>(s.diag)};
+    // One piece further for the threads from `first` on: store the words found in piece - 2, bring those of `piece`.
+    // Rows above the first pass on what they are given (all down); rows behind the last take nothing.
+    auto exchange = [&](int piece, int first, int threads) {
+        unsigned* const at = buf + (piece & 1) * 3 * kFillPlane;
+        unsigned w[kOwn][3];
+        if (piece < pieces) {
+#pragma unroll
+            for (int e = 0; e < kOwn; ++e) {
+                const int i = tid - first + e * threads, l = i % kFillLd, row = piece * kFillSteps + i / kFillLd - l;
+                const bool there = i < kFillPlane && l < W2 && row >= 0 && row < nb;
+#pragma unroll
+                for (int a = 0; a < 3; ++a) w[e][a] = there ? arr[a][(size_t)row * W2 + l] : (a == 0 && row < 0 ? ~0u : 0u);
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < kOwn; ++e) {
+            const int i = tid - first + e * threads, l = i % kFillLd, row = (piece - 2) * kFillSteps + i / kFillLd - l;
+            if (i >= kFillPlane || l >= W2) continue;
+            if (piece >= 2 && row >= 0 && row < nb) reinterpret_cast<unsigned*>(s.reached)[(size_t)row * W2 + l] = at[kFillPlane + i];
+            if (piece < pieces) {
+#pragma unroll
+                for (int a = 0; a < 3; ++a) at[a * kFillPlane + i] = w[e][a];
+            }
         }
     };
     auto meet = [&]() {   // LDS only: the stores of the words already found need not be waited for
@@ -1028,69 +1049,69 @@ __device__ void grid_fill(const GridScratch& s, int nb, unsigned* buf /* 2 * kFi
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     };
-    bring(0, 0, kFinishThreads);
+    if (wave != 0) exchange(0, 64, kFinishThreads - 64);
     meet();
     const int first_col = 32 * lane;
     // "row -1": every cell of row 0 is a seed; the first of every row is one too: down bits of column 0 set
     unsigned E = first_col >= nb ? 0u : (nb - first_col >= 32 ? ~0u : (1u << (nb - first_col)) - 1u), D = ~0u, G = 0u;
     const unsigned seed = lane == 0 ? 1u : 0u;
-    const int pieces = (nb + kFillRows - 1) / kFillRows;
+    unsigned eg_before = 0u;                // E & G of the step before
+    unsigned carry_lanes = 0u;              // lanes that receive a carry
     for (int piece = 0; piece < pieces; ++piece) {
         if (wave != 0) {
-            if (piece + 1 < pieces) bring(piece + 1, 64, kFinishThreads - 64);
-        } else if (lane < W2) {
-            const unsigned* const src = buf + (piece & 1) * kFillWords + lane;
-            unsigned* const out = reinterpret_cast<unsigned*>(s.reached) + (size_t)piece * plane + lane;
-            const int rows = min(kFillRows, nb - piece * kFillRows);
-            constexpr int U = 4;   // rows whose words are requested together, one group ahead
+            exchange(piece + 1, 64, kFinishThreads - 64);
+        } else if (lane < kFillLd) {
+            unsigned* const src = buf + (piece & 1) * 3 * kFillPlane + lane;
+            // (behind the branch a value per lane to the compiler: a scalar again before the instruction that needs one)
+            unsigned long long carry = (unsigned)__builtin_amdgcn_readfirstlane((int)carry_lanes);
+            constexpr int U = 4;   // steps whose words are requested together, one group ahead
             unsigned d[2][U], q[2][U], g[2][U];
-            auto request = [&](int h, int r0) {
+            auto request = [&](int h, int t0) {
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const int at = ((r0 + u) & (kFillRows - 1)) * W2;   // behind the last group: row 0 again
+                    const int at = (t0 + u) * kFillLd;
                     d[h][u] = src[at];
-                    q[h][u] = src[plane + at];
-                    g[h][u] = src[2 * plane + at];
+                    q[h][u] = src[kFillPlane + at];
+                    g[h][u] = src[2 * kFillPlane + at];
                 }
                 __builtin_amdgcn_sched_barrier(0);
             };
-            auto work = [&](int h, int r0) {
+            auto work = [&](int h, int t0) {
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
+                    const unsigned prev = (unsigned)__builtin_amdgcn_update_dpp(0, (int)eg_before, 0x138 /* wave_shr:1 */, 0xf, 0xf, false);
                     const unsigned eg = E & G;
-                    const unsigned prev = (unsigned)__builtin_amdgcn_update_dpp(0, (int)eg, 0x138 /* wave_shr:1 */, 0xf, 0xf, false);
                     const unsigned x = (E & D) | __builtin_amdgcn_alignbit(eg, prev, 31);
                     const unsigned R = q[h][u];
-                    unsigned sum, sum2;
-                    unsigned long long gen, unused;
-                    asm("v_add_co_u32 %0, %1, %2, %3" : "=v"(sum), "=s"(gen) : "v"(x & R), "v"(R));
-                    const unsigned long long pass = __builtin_amdgcn_ballot_w64(sum == ~0u);
-                    gen <<= 1;
-                    const unsigned long long carry = gen | (((gen & pass) + pass) ^ pass);
-                    asm("v_addc_co_u32 %0, %1, %2, 0, %3" : "=v"(sum2), "=s"(unused) : "v"(sum), "s"(carry));
-                    E = x | (sum2 ^ R);
-                    if (r0 + u < rows) out[(size_t)(r0 + u) * W2] = E;   // uniform
+                    unsigned sum;
+                    asm("v_addc_co_u32 %0, %1, %2, %3, %1\n\ts_lshl_b64 %1, %1, 1" : "=v"(sum), "+s"(carry) : "v"(x & R), "v"(R) : "scc");
+                    E = x | (sum ^ R);
+                    src[kFillPlane + (t0 + u) * kFillLd] = E;
+                    eg_before = eg;
                     D = d[h][u] | seed;
                     G = g[h][u];
                 }
                 __builtin_amdgcn_sched_barrier(0);
             };
             request(0, 0);
-            for (int r0 = 0; r0 < rows; r0 += 2 * U) {
-                request(1, r0 + U);
-                work(0, r0);
-                request(0, r0 + 2 * U);
-                work(1, r0 + U);   // rows past the last are worked on and not stored
+#pragma unroll 1
+            for (int t0 = 0; t0 < kFillSteps; t0 += 2 * U) {
+                request(1, t0 + U);
+                work(0, t0);
+                request(0, (t0 + 2 * U) & (kFillSteps - 1));   // behind the last group: step 0 again, unused
+                work(1, t0 + U);
             }
+            carry_lanes = (unsigned)carry;   // of 32 lanes
         }
         meet();
     }
+    if (wave != 0) exchange(pieces + 1, 64, kFinishThreads - 64);   // piece - 1 is stored, nothing is brought
 }
 
 __global__ __launch_bounds__(kFinishThreads) void grid_serial_kernel(const long long* __restrict__ pool, int nb, int mode,
                                                                      double kval, double t_abs, int no_fill,
                                                                      GridScratch s) {
-    __shared__ __attribute__((aligned(16))) unsigned hist[3 * kBins];
+    __shared__ __attribute__((aligned(16))) unsigned hist[kFillWords > 3 * kBins ? kFillWords : 3 * kBins];   // or the fill's words
     __shared__ SelectShared sel;
     __shared__ double part_s;
     const int tid = threadIdx.x, n = nb * nb;
@@ -1099,7 +1120,6 @@ __global__ __launch_bounds__(kFinishThreads) void grid_serial_kernel(const long 
         if (no_fill) {
             for (int i = tid; i < words; i += kFinishThreads) s.reached[i] = ~0ull;
         } else {
-            static_assert(2 * kFillWords <= 3 * kBins, "the pieces share the histograms' LDS");
             grid_fill(s, nb, hist);
         }
         return;

@@ -28,10 +28,11 @@ def _same_pattern(sp, A, block, filt, mode, value, flags=0, variant="CF"):
 
 
 # 1 .. 64 block rows: one workgroup, rows of one word (of which waves own four, the fill takes eight);
-# above: several kernels, words of 64 columns, fill pieces of 32 rows; block 16 / 32 / 64: four / two / one
+# above: several kernels, words of 64 columns, fill pieces of 64 steps (rows + words of 32 - 1); block 16 / 32 / 64: four / two / one
 # block side by side in a wave of the convolution, the last of them beyond the matrix
 @pytest.mark.parametrize("nb,block", [(1, 16), (3, 32), (5, 16), (31, 32), (63, 16), (64, 16), (65, 16), (96, 16),
-                                      (127, 32), (129, 16), (33, 64), (193, 16)])
+                                      (125, 16), (126, 16), (127, 32), (129, 16), (33, 64),
+                                      (193, 16)])
 @pytest.mark.parametrize("ties", [False, True])
 def test_pattern_at_the_edges_of_the_splits(sp, nb, block, ties):
     L = nb * block
