@@ -7,7 +7,12 @@
 // parsing by format strings.
 #include <Python.h>
 
+#include <ATen/ATen.h>
+#include <ATen/PythonTorchFunctionTLS.h>
+#include <ATen/autocast_mode.h>
 #include <ATen/hip/EmptyTensor.h>
+#include <c10/core/impl/LocalDispatchKeySet.h>
+#include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/function.h>
@@ -300,6 +305,91 @@ PyObject* py_sparse_attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
     });
 }
 
+// Whether torch is only computing: nobody traces, transforms, casts or watches its operators.
+bool nothing_between() {
+    using c10::DispatchKey;
+    if (c10::impl::TorchDispatchModeTLS::any_modes_set() || at::impl::torch_function_mode_enabled()) return false;
+    for (DispatchKey k : {DispatchKey::FuncTorchDynamicLayerFrontMode, DispatchKey::Functionalize, DispatchKey::Tracer})
+        if (c10::impl::tls_is_dispatch_key_included(k)) return false;
+    return !at::autocast::is_autocast_enabled(at::kCUDA);
+}
+// A plain strided device tensor: no subclass, no wrapper of a transform, no tangent.
+bool plain(PyObject* o) {
+    if (!THPVariable_CheckExact(o)) return false;
+    const at::Tensor& t = THPVariable_Unpack(o);
+    using c10::DispatchKey;
+    for (DispatchKey k : {DispatchKey::Python, DispatchKey::Functionalize, DispatchKey::FuncTorchBatched,
+                          DispatchKey::FuncTorchGradWrapper})
+        if (t.key_set().has(k)) return false;
+    return t.is_cuda() && t.layout() == at::kStrided && !t._fw_grad(0).defined();
+}
+
+// The gradient of Y = X W^T + b.  The weight's comes from spion_weight_grad; a backward pass that is itself
+// differentiated is made of torch operators.
+struct ProjectionBackward : public torch::autograd::Node {
+    torch::autograd::SavedVariable x, w;
+    bool has_bias = false;
+
+    std::string name() const override { return "ProjectionBackward"; }
+
+    void release_variables() override {
+        x.reset_data();
+        w.reset_data();
+    }
+
+    torch::autograd::variable_list apply(torch::autograd::variable_list&& grads) override {
+        torch::autograd::variable_list out(has_bias ? 3 : 2);
+        if (!grads[0].defined()) return out;
+        const at::Tensor X = x.unpack(), W = w.unpack();
+        const int64_t N = W.size(0), M = W.size(1);
+        const at::Tensor g = grads[0].reshape({-1, N}), x2 = X.reshape({-1, M});
+        if (task_should_compute_output(0)) out[0] = at::mm(g, W).view(X.sizes());
+        if (task_should_compute_output(1)) out[1] = at::GradMode::is_enabled() ? at::mm(g.t(), x2) : weight_grad(g.contiguous(), x2.contiguous());
+        if (has_bias && task_should_compute_output(2)) out[2] = g.sum(0);
+        return out;
+    }
+
+    static at::Tensor weight_grad(const at::Tensor& g, const at::Tensor& x) {
+        const int rows = (int)x.size(0), N = (int)g.size(1), M = (int)x.size(1);
+        at::Tensor dw(at::detail::empty_cuda({N, M}, x.scalar_type(), x.device(), std::nullopt));
+        const at::Tensor ws = new_bytes(spion_weight_grad_workspace_bytes(rows, N, M), x);
+        const int rc = spion_weight_grad(g.data_ptr(), x.data_ptr(), dw.data_ptr(), rows, N, M, ws.data_ptr(),
+                                         (size_t)ws.nbytes(), current_stream());
+        if (rc == SPION_ERR_PARAM) return at::mm(g.t(), x);   // an operand that is not aligned to 16 bytes
+        TORCH_CHECK(rc == SPION_OK, "spion_weight_grad: ", spion_strerror(rc));
+        return dw;
+    }
+};
+
+// projection(X, W, b | None) -> X W^T + b with the node above, or None where torch's own operator is to be called:
+// nothing to differentiate, types or sizes the kernel does not take, or more than plain tensors in play.  Weights of
+// more than 2^20 elements are torch's: with that many output tiles its product fills the machine.
+PyObject* py_projection(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    if (!arg_count(n, 3, "projection")) return nullptr;
+    return guarded([&]() -> PyObject* {
+        if (!nothing_between() || !plain(a[0]) || !plain(a[1]) || (a[2] != Py_None && !plain(a[2]))) Py_RETURN_NONE;
+        const at::Tensor &x = THPVariable_Unpack(a[0]), &w = THPVariable_Unpack(a[1]), b = optional_arg(a[2]);
+        if (x.scalar_type() != at::kBFloat16 || w.scalar_type() != at::kBFloat16 || x.device() != w.device() ||
+            x.dim() < 2 || w.dim() != 2 || !w.is_contiguous() || x.size(-1) != w.size(1) || x.numel() == 0 ||
+            w.size(0) % 8 != 0 || w.size(1) % 8 != 0 || w.numel() == 0 || w.numel() > (1 << 20) ||
+            x.numel() / x.size(-1) > 0x7fffffff - 4096)   // the kernel's row numbers run a little past the last
+            Py_RETURN_NONE;
+        if (!torch::autograd::compute_requires_grad(w)) Py_RETURN_NONE;
+        at::Tensor y;
+        {
+            at::NoGradGuard no_grad;
+            y = at::linear(x, w, b.defined() ? std::optional<at::Tensor>(b) : std::nullopt);
+        }
+        auto node = std::shared_ptr<ProjectionBackward>(new ProjectionBackward(), torch::autograd::deleteNode);
+        node->has_bias = b.defined();
+        node->set_next_edges(b.defined() ? torch::autograd::collect_next_edges(x, w, b) : torch::autograd::collect_next_edges(x, w));
+        node->x = torch::autograd::SavedVariable(x, false);
+        node->w = torch::autograd::SavedVariable(w, false);
+        torch::autograd::set_history(y, node);
+        return wrap(y);
+    });
+}
+
 // generate_pattern(A_s, L, block, filter, mode, value, flags, fl_out, row_ptr, col_idx, col_ptr, row_idx, bsr_pos,
 //                  nnzb, pool_sum, workspace | None) -> nnzb, after the pattern is complete
 PyObject* py_generate_pattern(PyObject*, PyObject* const* a, Py_ssize_t n) {
@@ -343,6 +433,7 @@ PyMethodDef kMethods[] = {
     {"attn_fwd", (PyCFunction)(void*)py_attn_fwd, METH_FASTCALL, nullptr},
     {"attn_bwd", (PyCFunction)(void*)py_attn_bwd, METH_FASTCALL, nullptr},
     {"sparse_attention", (PyCFunction)(void*)py_sparse_attention, METH_FASTCALL, nullptr},
+    {"projection", (PyCFunction)(void*)py_projection, METH_FASTCALL, nullptr},
     {"generate_pattern", (PyCFunction)(void*)py_generate_pattern, METH_FASTCALL, nullptr},
     {"set_error_class", py_set_error_class, METH_O, nullptr},
     {nullptr, nullptr, 0, nullptr},

@@ -274,6 +274,26 @@ int spion_pattern_wait(const float* A_s, const spion_pattern_params* p, uint8_t*
     return rc;
 }
 
+static bool weight_grad_shape_ok(int32_t rows, int32_t N, int32_t M) {
+    return rows > 0 && N > 0 && M > 0 && N % 8 == 0 && M % 8 == 0 && N <= 16384 && M <= 16384;   // N M fits 32 bits
+}
+
+size_t spion_weight_grad_workspace_bytes(int32_t rows, int32_t N, int32_t M) {
+    return weight_grad_shape_ok(rows, N, M) ? align_up(spion::weight_grad_workspace_bytes(rows, N, M)) : (size_t)-1;
+}
+
+int spion_weight_grad(const void* dY, const void* X, void* dW, int32_t rows, int32_t N, int32_t M, void* workspace,
+                      size_t workspace_bytes, void* hip_stream) {
+    if (!dY || !X || !dW) return SPION_ERR_NULL;
+    if (!weight_grad_shape_ok(rows, N, M)) return SPION_ERR_SHAPE;
+    if (((uintptr_t)dY | (uintptr_t)X | (uintptr_t)dW) % 16 != 0) return SPION_ERR_PARAM;
+    if (!workspace || ((uintptr_t)workspace % 16) != 0 || workspace_bytes < spion_weight_grad_workspace_bytes(rows, N, M))
+        return SPION_ERR_WORKSPACE;
+    if (spion::launch_weight_grad(dY, X, dW, rows, N, M, workspace, static_cast<hipStream_t>(hip_stream)) != hipSuccess)
+        return SPION_ERR_HIP;
+    return SPION_OK;
+}
+
 int spion_score_mean(const void* A_maps, int32_t n_maps, int32_t L, int32_t dtype, float* A_s,
                      void* hip_stream) {
     if (!A_maps || !A_s) return SPION_ERR_NULL;

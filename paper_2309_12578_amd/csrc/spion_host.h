@@ -17,6 +17,11 @@ int spion_pattern_wait(const float* A_s, const spion_pattern_params* p, uint8_t*
                        int64_t* pool_sum, void* workspace, size_t workspace_bytes, void* hip_stream,
                        int32_t* nnzb_out);
 
+// dW [N, M] = dY^T X for bf16 dY [rows, N] and X [rows, M], all contiguous, N and M multiples of 8; fp32 sums.
+size_t spion_weight_grad_workspace_bytes(int32_t rows, int32_t N, int32_t M);
+int spion_weight_grad(const void* dY, const void* X, void* dW, int32_t rows, int32_t N, int32_t M, void* workspace,
+                      size_t workspace_bytes, void* hip_stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -61,6 +61,11 @@ size_t attn_bwd_workspace_bytes(int BH, int bs, int nb, int nnzb);
 // false when a backward launch for this shape would need more workgroups than a 1-D grid can hold
 bool attn_bwd_grids_fit(int BH, int bs, int nb, int nnzb);
 
+// projection_kernels.hip: dW [N, M] = dY^T X over `rows` rows, bf16, N and M multiples of 8
+size_t weight_grad_workspace_bytes(int rows, int N, int M);
+hipError_t launch_weight_grad(const void* dY, const void* X, void* dW, int rows, int N, int M, void* workspace,
+                              hipStream_t st);
+
 // attn_bf16_kernels.hip: tuned bf16 forward, BS in {32, 64}
 template <int BS>
 hipError_t fwd_bf16(const AttnShape& s, const void* Q, const void* K, const void* V, void* O, float* LSE,

@@ -1,6 +1,6 @@
 """The sparse multi-head-attention sub-layer of Algorithm 5 as a torch module.
 
-Glue around the library: LayerNorm, the four projections (plain torch / hipBLASLt GEMMs), the head
+Glue around the library: LayerNorm, the four projections (hipBLASLt GEMMs but for the weight gradients), the head
 split, dropout and the residual are torch ops; lines 4-7 of Algorithm 5 (SDDMM, sparse softmax, SpMM
 for every head) are one call into libspion through `sparse_attention`, forward and backward.
 """
@@ -15,6 +15,17 @@ from .autograd import sparse_attention
 HEAD_DIM = 64   # the only head dimension the kernels are built for
 
 
+class _Projection(nn.Linear):
+    """nn.Linear whose bf16 weight gradient, few outputs and a sum over every token, is a kernel of the
+    library (csrc/projection_kernels.hip)."""
+
+    def forward(self, x: torch.Tensor) -> torch.Tensor:
+        y = None
+        if x.is_cuda and not torch.compiler.is_compiling():
+            y = (_b._host or _b._native()).projection(x, self.weight, self.bias)
+        return super().forward(x) if y is None else y
+
+
 class SparseMHA(nn.Module):
     """O = dropout(concat_h(sparse_attention(Q_h, K_h, V_h, P)) W^O) + E with
     Q, K, V = LayerNorm(E) W^{Q,K,V} (Algorithm 5).  `embed_dim` must be 64 * heads."""
@@ -27,8 +38,8 @@ class SparseMHA(nn.Module):
         kw = dict(device=device, dtype=dtype)
         self.heads = heads
         self.norm = nn.LayerNorm(embed_dim, **kw)
-        self.w_qkv = nn.Linear(embed_dim, 3 * embed_dim, bias=bias, **kw)   # W^Q | W^K | W^V
-        self.w_o = nn.Linear(embed_dim, embed_dim, bias=bias, **kw)
+        self.w_qkv = _Projection(embed_dim, 3 * embed_dim, bias=bias, **kw)   # W^Q | W^K | W^V
+        self.w_o = _Projection(embed_dim, embed_dim, bias=bias, **kw)
         self.drop = nn.Dropout(dropout)
 
     def forward(self, E: torch.Tensor, pattern: _b.Pattern, flags: int = 0) -> torch.Tensor:

@@ -193,3 +193,61 @@ def test_score_mean_and_distance_at_the_edges(sp, L, maps, dtype):
     got = sp.frobenius_distance(prev, mean).cpu().numpy()
     # sums of L^2 squares in fp64 in another order: relative error below L^2 2^-53
     assert np.allclose(got, (abs(a - b), a, b), rtol=0.0, atol=L * L * 2.0 ** -53 * (a + b))
+
+
+# Output tiles of 128 x 128 and their edges, steps of 32 rows, slices of at least 128 rows (one, a last short one, many);
+# sizes that are not multiples of 8 and non-contiguous or misaligned inputs take torch's product
+@pytest.mark.parametrize("rows,N,M", [(1, 8, 8), (31, 128, 136), (33, 192, 64), (128, 136, 120), (129, 256, 128), (1000, 384, 128),
+                                      (5000, 768, 256), (200, 12, 20), (16, 1536, 512)])
+@pytest.mark.parametrize("form", ["plain", "strided", "misaligned", "bias"])
+def test_projection_weight_gradient(sp, rows, N, M, form):
+    from paper_2309_12578_amd.sublayer import _Projection
+    gen = torch.Generator(device="cuda").manual_seed(rows + N)
+
+    def randn(*shape):
+        return torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16)
+
+    layer = _Projection(M, N, bias=form == "bias", device="cuda", dtype=torch.bfloat16)
+    with torch.no_grad():
+        for p in layer.parameters():
+            p.copy_(randn(*p.shape))
+    x, dy = randn(1, rows, M), randn(1, rows, N)
+    if form == "strided":
+        x = randn(1, M, rows).transpose(1, 2)
+    if form == "misaligned":
+        x = randn(rows * M + 1)[1:].view(1, rows, M)
+    x.requires_grad_(True)
+    y = layer(x)
+    got = torch.autograd.grad(y, [x, *layer.parameters()], dy)
+    w = layer.weight.detach().double()
+    x64, dy64 = x.detach().double().view(rows, M), dy.double().view(rows, N)
+    want = [dy64 @ w, dy64.t().contiguous() @ x64] + ([dy64.sum(0)] if form == "bias" else [])
+    assert torch.equal(y, torch.nn.functional.linear(x, layer.weight, layer.bias))
+    for g, r in zip(got, want):   # one rounding to bf16 (2^-9 of each value) of sums in fp32
+        assert g.dtype == torch.bfloat16 and (g.double().view(r.shape) - r).norm() <= 2.0 ** -8 * r.norm()
+
+
+def test_projection_beside_the_other_transforms(sp):
+    from paper_2309_12578_amd.sublayer import _Projection
+    layer = _Projection(64, 192, bias=False, device="cuda", dtype=torch.bfloat16)
+    plain = torch.nn.Linear(64, 192, bias=False, device="cuda", dtype=torch.bfloat16)
+    plain.weight = layer.weight
+    x = torch.randn((4, 32, 64), device="cuda").to(torch.bfloat16).requires_grad_(True)
+    ad = torch.autograd.forward_ad
+
+    def tangent(f):
+        with ad.dual_level():
+            return ad.unpack_dual(f(ad.make_dual(x.detach(), x.detach()))).tangent
+
+    def second(f):   # gradient of a gradient
+        g, = torch.autograd.grad(f(x).square().sum(), f.weight, create_graph=True)
+        return torch.autograd.grad(g.square().sum(), x)[0]
+
+    def cast(f):
+        with torch.autocast("cuda", dtype=torch.float16):
+            return f(x)
+
+    for call in (tangent, second, cast, lambda f: torch.func.vmap(f)(x), lambda f: torch.func.grad(lambda t: f(t).sum())(x),
+                 lambda f: f(x.detach())):
+        a, b = call(layer), call(plain)
+        assert a.dtype == b.dtype and torch.allclose(a.float(), b.float(), rtol=2.0 ** -6, atol=2.0 ** -6 * b.float().abs().max().item())
