@@ -361,6 +361,105 @@ struct ProjectionBackward : public torch::autograd::Node {
     }
 };
 
+void heads(bool split, const at::Tensor& merged, const at::Tensor* t, int n) {   // see spion_heads
+    void* ptr[3];
+    for (int i = 0; i < n; ++i) ptr[i] = t[i].data_ptr();
+    const int rc = spion_heads(split, merged.data_ptr(), ptr, (int)t[0].size(0), (int)t[0].size(2), (int)t[0].size(1), n,
+                               t[0].scalar_type() == at::kFloat ? SPION_F32 : SPION_BF16, current_stream());
+    if (rc != SPION_OK) throw SpionFailure{rc, "spion_heads"};
+}
+
+at::Tensor new_heads(const at::Tensor& like, int64_t B, int64_t H, int64_t L) {
+    return at::Tensor(at::detail::empty_cuda({B, H, L, 64}, like.scalar_type(), like.device(), std::nullopt));
+}
+
+// The gradient of heads_attention: a head split, the attention's backward and a head merge.
+struct HeadsAttentionBackward : public torch::autograd::Node {
+    torch::autograd::SavedVariable q, k, v, o, lse;
+    Index ix;
+
+    std::string name() const override { return "HeadsAttentionBackward"; }
+
+    void release_variables() override {
+        for (torch::autograd::SavedVariable* s : {&q, &k, &v, &o, &lse}) s->reset_data();
+    }
+
+    torch::autograd::variable_list apply(torch::autograd::variable_list&& grads) override {
+        torch::autograd::variable_list out(1);
+        if (!grads[0].defined()) return out;
+        at::NoGradGuard no_grad;   // the gradients are not differentiated again
+        at::Tensor g = grads[0].contiguous(), d[3], ws;
+        if ((uintptr_t)g.data_ptr() % 16 != 0) g = g.clone();
+        const at::Tensor Q = q.unpack(), O = o.unpack();
+        const int64_t B = Q.size(0), H = Q.size(1), L = Q.size(2);
+        try {
+            const at::Tensor dO = new_heads(Q, B, H, L);
+            heads(true, g, &dO, 1);
+            backward(Q, k.unpack(), v.unpack(), O, dO, lse.unpack(), ix, d[0], d[1], d[2], ws);
+            out[0] = at::Tensor(at::detail::empty_cuda({B, L, 3 * H * 64}, Q.scalar_type(), Q.device(), std::nullopt));
+            heads(false, out[0], d, 3);
+        } catch (const SpionFailure& e) {
+            PyGILState_STATE gil = PyGILState_Ensure();
+            spion_error(e.code, e.what);
+            python_error err;
+            err.persist();
+            PyGILState_Release(gil);
+            throw err;
+        } catch (const BadValue& e) {
+            TORCH_CHECK_VALUE(false, e.msg);
+        }
+        return out;
+    }
+};
+
+// heads_attention(qkv [B, L, 3 H 64], H, row_ptr, col_idx, col_ptr, row_idx, bsr_pos, nnzb, block, flags) -> [B, L, H 64]:
+// head split, attention and head merge as one node; None where the steps are to be taken one by one (see projection).
+PyObject* py_heads_attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    if (!arg_count(n, 10, "heads_attention")) return nullptr;
+    return guarded([&]() -> PyObject* {
+        if (!nothing_between() || !plain(a[0])) Py_RETURN_NONE;
+        const at::Tensor& qkv = THPVariable_Unpack(a[0]);
+        const int64_t H = int_arg(a[1]);
+        const bool f32 = qkv.scalar_type() == at::kFloat;
+        if ((!f32 && qkv.scalar_type() != at::kBFloat16) || qkv.dim() != 3 || !qkv.is_contiguous() || H <= 0 ||
+            qkv.size(2) != 3 * H * 64 || qkv.size(1) % 4 != 0 || qkv.numel() == 0 ||
+            qkv.numel() / (f32 ? 4 : 8) >= 0x7fffffffll || (uintptr_t)qkv.data_ptr() % 16 != 0)
+            Py_RETURN_NONE;
+        const int64_t B = qkv.size(0), L = qkv.size(1);
+        Index ix;
+        ix.row_ptr = tensor_arg(a[2]);
+        ix.col_idx = tensor_arg(a[3]);
+        ix.nnzb = int_arg(a[7]);
+        ix.block = int_arg(a[8]);
+        ix.flags = (unsigned)int_arg(a[9]);
+        const bool grad = torch::autograd::compute_requires_grad(qkv);
+        at::Tensor t[3], o, lse, s;
+        {
+            at::NoGradGuard no_grad;
+            for (at::Tensor& x : t) x = new_heads(qkv, B, H, L);
+            heads(true, qkv, t, 3);
+            forward(t[0], t[1], t[2], ix, o, lse);
+            s = at::Tensor(at::detail::empty_cuda({B, L, H * 64}, qkv.scalar_type(), qkv.device(), std::nullopt));
+            heads(false, s, &o, 1);
+        }
+        if (grad) {
+            ix.col_ptr = tensor_arg(a[4]);
+            ix.row_idx = tensor_arg(a[5]);
+            ix.bsr_pos = tensor_arg(a[6]);
+            auto node = std::shared_ptr<HeadsAttentionBackward>(new HeadsAttentionBackward(), torch::autograd::deleteNode);
+            node->set_next_edges(torch::autograd::collect_next_edges(qkv));
+            node->q = torch::autograd::SavedVariable(t[0], false);
+            node->k = torch::autograd::SavedVariable(t[1], false);
+            node->v = torch::autograd::SavedVariable(t[2], false);
+            node->o = torch::autograd::SavedVariable(o, false);
+            node->lse = torch::autograd::SavedVariable(lse, false);
+            node->ix = std::move(ix);
+            torch::autograd::set_history(s, node);
+        }
+        return wrap(s);
+    });
+}
+
 // projection(X, W, b | None) -> X W^T + b with the node above, or None where torch's own operator is to be called:
 // nothing to differentiate, types or sizes the kernel does not take, or more than plain tensors in play.  Weights of
 // more than 2^20 elements are torch's: with that many output tiles its product fills the machine.
@@ -433,6 +532,7 @@ PyMethodDef kMethods[] = {
     {"attn_fwd", (PyCFunction)(void*)py_attn_fwd, METH_FASTCALL, nullptr},
     {"attn_bwd", (PyCFunction)(void*)py_attn_bwd, METH_FASTCALL, nullptr},
     {"sparse_attention", (PyCFunction)(void*)py_sparse_attention, METH_FASTCALL, nullptr},
+    {"heads_attention", (PyCFunction)(void*)py_heads_attention, METH_FASTCALL, nullptr},
     {"projection", (PyCFunction)(void*)py_projection, METH_FASTCALL, nullptr},
     {"generate_pattern", (PyCFunction)(void*)py_generate_pattern, METH_FASTCALL, nullptr},
     {"set_error_class", py_set_error_class, METH_O, nullptr},

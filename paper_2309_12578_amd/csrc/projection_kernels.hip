@@ -1,4 +1,4 @@
-// The projections of the sub-layer (Algorithm 5): gradient of a weight matrix.
+// Around the attention of the sub-layer (Algorithm 5): gradient of a projection's weight, head split and merge.
 //
 // dW[n][m] = sum over rows of dY[row][n] * X[row][m] has few outputs (N, M: the embedding width, or three times
 // it) and a long contraction (every token of the batch).  A library product that gives each output tile to one
@@ -151,6 +151,38 @@ __global__ __launch_bounds__(256) void weight_grad_sum_kernel(const float* __res
     if (wave == 0 && i < n4) store_quad<bf16_t>(dW + 4 * (size_t)i, ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane]);
 }
 
+// Between the layout of the projections, [B, L, n, H, 64] (n = 3: Q | K | V, n = 1: the heads' outputs side by side),
+// and that of the attention, n tensors [B, H, L, 64].  Bound by HBM.  A wave moves 4 pieces of 1 KB that are
+// contiguous in the attention's layout (8 tokens of a head in bf16, 4 in fp32), rows of 128 or 256 bytes in the other.
+// 8 x 2048 tokens, 4 heads, bf16: 8.2 us for three tensors (50 MB, out of the caches in part), 4.7 us for one.  As
+// torch operators these were 8 copies of 8 us and, for the gradients of the three slices, as many fills of the whole
+// and two additions: 125 us a step.
+typedef unsigned Vec16 __attribute__((ext_vector_type(4)));   // (an array of uint4 is not kept in registers here)
+template <bool SPLIT>
+__global__ __launch_bounds__(256) void heads_kernel(Vec16* merged, Vec16* t0, Vec16* t1, Vec16* t2, int L, int H, int n,
+                                                    int log_v /* vectors per 64 elements */, int pieces, unsigned waves) {
+    const unsigned w = __builtin_amdgcn_readfirstlane(blockIdx.x * 4u + (threadIdx.x >> 6));
+    if (w >= waves) return;
+    const int lane = threadIdx.x & 63, v = 1 << log_v, c = lane & (v - 1), tokens = 64 >> log_v;
+    const unsigned h = w % (unsigned)H, part = w / (unsigned)H % (unsigned)n, at = w / ((unsigned)H * (unsigned)n);
+    const unsigned b = at / (unsigned)pieces;
+    const int l = (int)(at % (unsigned)pieces) * 4 * tokens + (lane >> log_v);
+    Vec16* const m = merged + (((size_t)b * L * n + part) * H + h) * v + c;
+    Vec16* const t = (part == 0 ? t0 : part == 1 ? t1 : t2) + ((size_t)b * H + h) * L * v + c;
+    const size_t m_row = (size_t)n * H * v;
+    Vec16 x[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int row = min(l + k * tokens, L - 1);
+        x[k] = SPLIT ? m[row * m_row] : t[(size_t)row * v];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int row = l + k * tokens;
+        if (row < L) (SPLIT ? t[(size_t)row * v] : m[row * m_row]) = x[k];
+    }
+}
+
 struct WeightGradPlan {
     int tiles_n, tiles_m, slices, slice_rows;
     WeightGradPlan(int rows, int N, int M) {
@@ -181,6 +213,18 @@ hipError_t launch_weight_grad(const void* dY, const void* X, void* dW, int rows,
     const int n4 = N * M / 4;
     weight_grad_sum_kernel<<<dim3((unsigned)((n4 + 63) / 64)), dim3(256), 0, st>>>(partial, p.slices, n4,
                                                                                     static_cast<bf16_t*>(dW));
+    return hipGetLastError();
+}
+
+hipError_t launch_heads(bool split, void* merged, void* const* t, int B, int L, int H, int n, bool is_bf16, hipStream_t st) {
+    const int log_v = is_bf16 ? 3 : 4, pieces = (L + (256 >> log_v) - 1) / (256 >> log_v);
+    const unsigned waves = (unsigned)((size_t)B * pieces * n * H), groups = (waves + 3u) / 4u;
+    Vec16 *m = static_cast<Vec16*>(merged), *a = static_cast<Vec16*>(t[0]), *b = static_cast<Vec16*>(t[n > 1 ? 1 : 0]),
+          *c = static_cast<Vec16*>(t[n > 1 ? 2 : 0]);
+    if (split)
+        heads_kernel<true><<<dim3(groups), dim3(256), 0, st>>>(m, a, b, c, L, H, n, log_v, pieces, waves);
+    else
+        heads_kernel<false><<<dim3(groups), dim3(256), 0, st>>>(m, a, b, c, L, H, n, log_v, pieces, waves);
     return hipGetLastError();
 }
 

@@ -294,6 +294,23 @@ int spion_weight_grad(const void* dY, const void* X, void* dW, int32_t rows, int
     return SPION_OK;
 }
 
+int spion_heads(int32_t split, void* merged, void* const* t, int32_t B, int32_t L, int32_t H, int32_t n, int32_t dtype,
+                void* hip_stream) {
+    if (!merged || !t) return SPION_ERR_NULL;
+    if (dtype != SPION_F32 && dtype != SPION_BF16) return SPION_ERR_DTYPE;
+    if (B <= 0 || L <= 0 || H <= 0 || L % 4 != 0 || (n != 1 && n != 3)) return SPION_ERR_SHAPE;
+    if ((double)B * L * H * n * (dtype == SPION_BF16 ? 8 : 16) >= 2147483648.0) return SPION_ERR_SHAPE;
+    uintptr_t all = (uintptr_t)merged;
+    for (int i = 0; i < n; ++i) {
+        if (!t[i]) return SPION_ERR_NULL;
+        all |= (uintptr_t)t[i];
+    }
+    if (all % 16 != 0) return SPION_ERR_PARAM;
+    if (spion::launch_heads(split != 0, merged, t, B, L, H, n, dtype == SPION_BF16, static_cast<hipStream_t>(hip_stream)) != hipSuccess)
+        return SPION_ERR_HIP;
+    return SPION_OK;
+}
+
 int spion_score_mean(const void* A_maps, int32_t n_maps, int32_t L, int32_t dtype, float* A_s,
                      void* hip_stream) {
     if (!A_maps || !A_s) return SPION_ERR_NULL;

@@ -66,6 +66,9 @@ size_t weight_grad_workspace_bytes(int rows, int N, int M);
 hipError_t launch_weight_grad(const void* dY, const void* X, void* dW, int rows, int N, int M, void* workspace,
                               hipStream_t st);
 
+// merged [B, L, n, H, 64] <-> n tensors [B, H, L, 64], n = 1 or 3, L a multiple of 4
+hipError_t launch_heads(bool split, void* merged, void* const* t, int B, int L, int H, int n, bool is_bf16, hipStream_t st);
+
 // attn_bf16_kernels.hip: tuned bf16 forward, BS in {32, 64}
 template <int BS>
 hipError_t fwd_bf16(const AttnShape& s, const void* Q, const void* K, const void* V, void* O, float* LSE,

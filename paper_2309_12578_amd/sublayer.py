@@ -1,8 +1,8 @@
 """The sparse multi-head-attention sub-layer of Algorithm 5 as a torch module.
 
-Glue around the library: LayerNorm, the four projections (hipBLASLt GEMMs but for the weight gradients), the head
-split, dropout and the residual are torch ops; lines 4-7 of Algorithm 5 (SDDMM, sparse softmax, SpMM
-for every head) are one call into libspion through `sparse_attention`, forward and backward.
+Glue around the library: LayerNorm, the four projections (hipBLASLt GEMMs but for the weight gradients),
+dropout and the residual are torch ops; the head split and lines 4-7 of Algorithm 5 (SDDMM, sparse
+softmax, SpMM for every head) are one call into libspion, forward and backward.
 """
 from __future__ import annotations
 
@@ -46,9 +46,17 @@ class SparseMHA(nn.Module):
         """E: [B, L, embed_dim] on the GPU (bf16 or fp32); pattern: the layer's sparsity pattern."""
         B, L, D = E.shape
         X = self.norm(E)
-        qkv = self.w_qkv(X).view(B, L, 3, self.heads, HEAD_DIM)
-        # [B, H, L, 64] contiguous per tensor: the layout the kernels take
-        Q, K, V = [qkv[:, :, i].transpose(1, 2).contiguous() for i in range(3)]
-        S = sparse_attention(Q, K, V, pattern, flags=flags)               # lines 4-7, all heads at once
-        S = S.transpose(1, 2).reshape(B, L, D)                            # concatenate the heads
+        qkv = self.w_qkv(X)
+        S = None
+        if qkv.is_cuda and not torch.compiler.is_compiling():
+            # head split, lines 4-7, heads side by side again: two kernels beside the attention's
+            S = (_b._host or _b._native()).heads_attention(
+                qkv, self.heads, pattern.row_ptr, pattern.col_idx, pattern.col_ptr, pattern.row_idx, pattern.bsr_pos,
+                pattern.nnzb, pattern.block, flags)
+        if S is None:
+            qkv = qkv.view(B, L, 3, self.heads, HEAD_DIM)
+            # [B, H, L, 64] contiguous per tensor: the layout the kernels take
+            Q, K, V = [qkv[:, :, i].transpose(1, 2).contiguous() for i in range(3)]
+            S = sparse_attention(Q, K, V, pattern, flags=flags)               # lines 4-7, all heads at once
+            S = S.transpose(1, 2).reshape(B, L, D)                            # concatenate the heads
         return self.drop(self.w_o(S)) + E

@@ -251,3 +251,28 @@ def test_projection_beside_the_other_transforms(sp):
                  lambda f: f(x.detach())):
         a, b = call(layer), call(plain)
         assert a.dtype == b.dtype and torch.allclose(a.float(), b.float(), rtol=2.0 ** -6, atol=2.0 ** -6 * b.float().abs().max().item())
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("B,H,nb,block", [(1, 1, 1, 16), (3, 5, 3, 16), (2, 3, 7, 32), (2, 8, 2, 64)])
+def test_sublayer_fused_and_step_by_step(sp, dtype, B, H, nb, block):
+    """Head split and merge only move values: the same bits as the torch operators, which run under a mode."""
+    from test_gpu_parity import _pattern_from_mask
+    pat = _pattern_from_mask(sp, np.tril(np.ones((nb, nb), dtype=np.uint8)), block)
+    gen = torch.Generator(device="cuda").manual_seed(H)
+    mha = sp.SparseMHA(64 * H, H, device="cuda", dtype=dtype)
+    E, dout = [torch.randn((B, nb * block, 64 * H), generator=gen, device="cuda").to(dtype) for _ in range(2)]
+    E.requires_grad_(True)
+    fused = mha(E, pat)
+    d_fused, = torch.autograd.grad(fused, E, dout)
+
+    class Watching(torch.overrides.TorchFunctionMode):
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            return func(*args, **(kwargs or {}))
+
+    with Watching():
+        steps = mha(E, pat)
+    d_steps, = torch.autograd.grad(steps, E, dout.transpose(0, 1).contiguous().transpose(0, 1))
+    assert fused.grad_fn is not None and torch.equal(fused, steps) and torch.equal(d_fused, d_steps)
+    with torch.no_grad():
+        assert torch.equal(mha(E, pat), steps)
