@@ -931,8 +931,11 @@ __global__ __launch_bounds__(256) void grid_pool_kernel(const long long* __restr
         if (h[i]) atomicAdd(&hist[i], h[i]);
 }
 
-// One wave per word (64 cells of a row).  Every workgroup finds the bin of the wanted rank itself: 16
-// bins per thread and two scans.
+// A wave takes kBitsWords words (64 cells of a row).  Every workgroup finds the bin of the wanted rank itself, 16
+// bins per thread and two scans, and takes room for its candidates with one addition: with one per wave and
+// word, all on one counter, a map of 512 x 512 nearly equal cells (one bin) took 50 us,
+// now 8.8.
+constexpr int kBitsWords = 4;
 __global__ __launch_bounds__(256) void grid_bits_kernel(const long long* __restrict__ pool, int nb, int mode,
                                                         int k_rank, int no_fill, GridScratch s) {
     __shared__ int wave_sum[4], sel_bin;
@@ -970,30 +973,49 @@ __global__ __launch_bounds__(256) void grid_bits_kernel(const long long* __restr
         __syncthreads();
         bin = sel_bin;
     }
-    const int word = blockIdx.x * 4 + wave;
-    if (word >= nb * W) return;
-    const int r = word / W, seg = word % W, c = seg * 64 + lane;
-    const bool ok = c < nb, inner = c + 1 < nb && r + 1 < nb;
-    const int i = r * nb + (ok ? c : 0);
-    const long long v = pool[i];
-    if (!no_fill) {
-        const Succ sc = successors(inner ? pool[i + nb] : 0, inner ? pool[i + 1] : 0, inner ? pool[i + nb + 1] : 0, inner);
-        const unsigned long long bd = __ballot(sc.down), br = __ballot(sc.right), bg = __ballot(sc.diag);
-        if (lane == 0) {
-            s.down[word] = bd;
-            s.right[word] = br;
-            s.diag[word] = bg;
-        }
+    __shared__ unsigned wave_cand[4], cand_base;
+    const int words = nb * W, first = (blockIdx.x * 4 + wave) * kBitsWords;
+    long long v[kBitsWords];
+    bool mine[kBitsWords];
+    unsigned found = 0u;   // candidates of this wave
+#pragma unroll
+    for (int q = 0; q < kBitsWords; ++q) {
+        const int word = min(first + q, words - 1), c = word % W * 64 + lane;
+        v[q] = pool[word / W * nb + (c < nb ? c : 0)];
     }
-    if (mode == 1) {
-        const bool mine = ok && grid_bin(v) == bin;
-        const unsigned long long m = __ballot(mine);
-        if (m != 0ull) {
-            unsigned base = 0;
-            if (lane == 0) base = atomicAdd(&s.hist[kGridBins], (unsigned)__popcll(m));
-            base = (unsigned)__builtin_amdgcn_readfirstlane((int)base);
-            if (mine) s.cand[base + (unsigned)__popcll(m & ((1ull << lane) - 1ull))] = (unsigned long long)v ^ kSign;
+#pragma unroll
+    for (int q = 0; q < kBitsWords; ++q) {
+        const int word = min(first + q, words - 1), r = word / W, c = word % W * 64 + lane;
+        const bool there = first + q < words;   // uniform
+        if (!no_fill && there) {
+            const bool inner = c + 1 < nb && r + 1 < nb;
+            const int i = r * nb + (c < nb ? c : 0);
+            const Succ sc = successors(inner ? pool[i + nb] : 0, inner ? pool[i + 1] : 0, inner ? pool[i + nb + 1] : 0, inner);
+            const unsigned long long bd = __ballot(sc.down), br = __ballot(sc.right), bg = __ballot(sc.diag);
+            if (lane == 0) {
+                s.down[word] = bd;
+                s.right[word] = br;
+                s.diag[word] = bg;
+            }
         }
+        mine[q] = mode == 1 && there && c < nb && grid_bin(v[q]) == bin;
+        found += (unsigned)__popcll(__ballot(mine[q]));
+    }
+    if (mode != 1) return;
+    if (lane == 0) wave_cand[wave] = found;
+    __syncthreads();
+    if (tid == 0) {
+        const unsigned all = wave_cand[0] + wave_cand[1] + wave_cand[2] + wave_cand[3];
+        cand_base = all ? atomicAdd(&s.hist[kGridBins], all) : 0u;
+    }
+    __syncthreads();
+    unsigned base = cand_base;
+    for (int w = 0; w < wave; ++w) base += wave_cand[w];
+#pragma unroll
+    for (int q = 0; q < kBitsWords; ++q) {
+        const unsigned long long m = __ballot(mine[q]);
+        if (mine[q]) s.cand[base + (unsigned)__popcll(m & ((1ull << lane) - 1ull))] = (unsigned long long)v[q] ^ kSign;
+        base += (unsigned)__popcll(m);
     }
 }
 
@@ -1426,7 +1448,7 @@ hipError_t launch_pattern_finish(bool from_part, long long* part, long long* poo
     if (!from_part) grid_zero_kernel<<<dim3((kGridZeroWords + 255) / 256), dim3(256), 0, st>>>(s.hist);
     if (from_part || mode == 1)
         grid_pool_kernel<<<dim3((n + 1023) / 1024), dim3(256), 0, st>>>(src, pool, nb, mode == 1, s.hist);
-    grid_bits_kernel<<<dim3((words + 3) / 4), dim3(256), 0, st>>>(pool, nb, mode, (int)k_rank, no_fill, s);
+    grid_bits_kernel<<<dim3((words + 4 * kBitsWords - 1) / (4 * kBitsWords)), dim3(256), 0, st>>>(pool, nb, mode, (int)k_rank, no_fill, s);
     grid_serial_kernel<<<dim3(2), dim3(kFinishThreads), 0, st>>>(pool, nb, mode, kval, t_abs, no_fill, s);
     grid_words_kernel<<<dim3(W * W), dim3(256), 0, st>>>(pool, nb, no_fill, s, fl);
     const unsigned lines = (unsigned)(col_ptr ? 2 * nb : nb);
