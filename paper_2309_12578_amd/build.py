@@ -32,6 +32,7 @@ SOURCES = [
     ("attn_kernels.hip", ["-mllvm", "-amdgpu-mfma-vgpr-form"]),
     ("attn_bf16_kernels.hip", ["-mllvm", "-amdgpu-mfma-vgpr-form"]),
     ("attn_bwd_bf16_kernels.hip", ["-mllvm", "-amdgpu-mfma-vgpr-form"]),
+    ("norm_kernels.hip", []),
     ("projection_kernels.hip", ["-mllvm", "-amdgpu-mfma-vgpr-form"]),
 ]
 

@@ -460,6 +460,81 @@ PyObject* py_heads_attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
     });
 }
 
+// The gradient of layer_norm, all three in one pass over X and dY; torch's operator where the pass itself is
+// differentiated.
+struct NormBackward : public torch::autograd::Node {
+    torch::autograd::SavedVariable x, w, b, mean, rstd;
+
+    std::string name() const override { return "NormBackward"; }
+
+    void release_variables() override {
+        for (torch::autograd::SavedVariable* s : {&x, &w, &b, &mean, &rstd}) s->reset_data();
+    }
+
+    torch::autograd::variable_list apply(torch::autograd::variable_list&& grads) override {
+        torch::autograd::variable_list out(3);
+        if (!grads[0].defined()) return out;
+        const at::Tensor X = x.unpack(), W = w.unpack(), m = mean.unpack(), r = rstd.unpack();
+        const int64_t D = W.size(0);
+        const at::Tensor g = grads[0].contiguous();
+        if (at::GradMode::is_enabled() || (uintptr_t)g.data_ptr() % 16 != 0) {
+            std::vector<int64_t> stat(X.sizes().begin(), X.sizes().end());
+            stat.back() = 1;
+            std::tie(out[0], out[1], out[2]) = at::native_layer_norm_backward(
+                g, X, {D}, m.view(stat), r.view(stat), W, b.unpack(),
+                {task_should_compute_output(0), task_should_compute_output(1), task_should_compute_output(2)});
+            return out;
+        }
+        const int rows = (int)(X.numel() / D);
+        for (at::Tensor* t : {&out[0], &out[1], &out[2]}) *t = new_like(t == &out[0] ? X : W);
+        const at::Tensor ws = new_bytes(spion_layer_norm_workspace_bytes(rows, (int)D), X);
+        const int rc = spion_layer_norm_grad(g.data_ptr(), X.data_ptr(), W.data_ptr(), m.data_ptr<float>(), r.data_ptr<float>(),
+                                             out[0].data_ptr(), out[1].data_ptr(), out[2].data_ptr(), rows, (int)D,
+                                             X.scalar_type() == at::kFloat ? SPION_F32 : SPION_BF16, ws.data_ptr(),
+                                             (size_t)ws.nbytes(), current_stream());
+        TORCH_CHECK(rc == SPION_OK, "spion_layer_norm_grad: ", spion_strerror(rc));
+        for (int i = 0; i < 3; ++i)
+            if (!task_should_compute_output(i)) out[i].reset();
+        return out;
+    }
+};
+
+// layer_norm(X, w, b, eps) -> Y over the last dimension, or None where torch's operator is to be called (see projection).
+PyObject* py_layer_norm(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    if (!arg_count(n, 4, "layer_norm")) return nullptr;
+    return guarded([&]() -> PyObject* {
+        if (!nothing_between() || !plain(a[0]) || !plain(a[1]) || !plain(a[2])) Py_RETURN_NONE;
+        const at::Tensor &x = THPVariable_Unpack(a[0]), &w = THPVariable_Unpack(a[1]), &b = THPVariable_Unpack(a[2]);
+        const auto type = x.scalar_type();
+        if ((type != at::kFloat && type != at::kBFloat16) || w.scalar_type() != type || b.scalar_type() != type ||
+            x.device() != w.device() || x.device() != b.device() || w.dim() != 1 || x.dim() < 2 || x.numel() == 0)
+            Py_RETURN_NONE;
+        const int64_t D = w.size(0);
+        if (b.dim() != 1 || b.size(0) != D || x.size(-1) != D || D % 64 != 0 || D > 2048 || x.numel() / D > 0x40000000 ||
+            !x.is_contiguous() || !w.is_contiguous() || !b.is_contiguous() ||
+            ((uintptr_t)x.data_ptr() | (uintptr_t)w.data_ptr() | (uintptr_t)b.data_ptr()) % 16 != 0)
+            Py_RETURN_NONE;
+        const int64_t rows = x.numel() / D;
+        at::Tensor y = new_like(x), mean(at::detail::empty_cuda({rows}, at::kFloat, x.device(), std::nullopt)),
+                   rstd(at::detail::empty_cuda({rows}, at::kFloat, x.device(), std::nullopt));
+        const int rc = spion_layer_norm(x.data_ptr(), w.data_ptr(), b.data_ptr(), y.data_ptr(), mean.data_ptr<float>(),
+                                        rstd.data_ptr<float>(), (int)rows, (int)D, (float)double_arg(a[3]),
+                                        type == at::kFloat ? SPION_F32 : SPION_BF16, current_stream());
+        if (rc != SPION_OK) throw SpionFailure{rc, "spion_layer_norm"};
+        if (torch::autograd::compute_requires_grad(x, w, b)) {
+            auto node = std::shared_ptr<NormBackward>(new NormBackward(), torch::autograd::deleteNode);
+            node->set_next_edges(torch::autograd::collect_next_edges(x, w, b));
+            node->x = torch::autograd::SavedVariable(x, false);
+            node->w = torch::autograd::SavedVariable(w, false);
+            node->b = torch::autograd::SavedVariable(b, false);
+            node->mean = torch::autograd::SavedVariable(mean, false);
+            node->rstd = torch::autograd::SavedVariable(rstd, false);
+            torch::autograd::set_history(y, node);
+        }
+        return wrap(y);
+    });
+}
+
 // projection(X, W, b | None) -> X W^T + b with the node above, or None where torch's own operator is to be called:
 // nothing to differentiate, types or sizes the kernel does not take, or more than plain tensors in play.  Weights of
 // more than 2^20 elements are torch's: with that many output tiles its product fills the machine.
@@ -533,6 +608,7 @@ PyMethodDef kMethods[] = {
     {"attn_bwd", (PyCFunction)(void*)py_attn_bwd, METH_FASTCALL, nullptr},
     {"sparse_attention", (PyCFunction)(void*)py_sparse_attention, METH_FASTCALL, nullptr},
     {"heads_attention", (PyCFunction)(void*)py_heads_attention, METH_FASTCALL, nullptr},
+    {"layer_norm", (PyCFunction)(void*)py_layer_norm, METH_FASTCALL, nullptr},
     {"projection", (PyCFunction)(void*)py_projection, METH_FASTCALL, nullptr},
     {"generate_pattern", (PyCFunction)(void*)py_generate_pattern, METH_FASTCALL, nullptr},
     {"set_error_class", py_set_error_class, METH_O, nullptr},

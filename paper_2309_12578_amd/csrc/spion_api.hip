@@ -294,6 +294,38 @@ int spion_weight_grad(const void* dY, const void* X, void* dW, int32_t rows, int
     return SPION_OK;
 }
 
+static int layer_norm_args_ok(uintptr_t all, int32_t rows, int32_t D, int32_t dtype) {
+    if (dtype != SPION_F32 && dtype != SPION_BF16) return SPION_ERR_DTYPE;
+    if (rows <= 0 || rows > 0x40000000 || D <= 0 || D % 64 != 0 || D > 2048) return SPION_ERR_SHAPE;
+    return all % 16 != 0 ? SPION_ERR_PARAM : SPION_OK;
+}
+
+int spion_layer_norm(const void* x, const void* w, const void* b, void* y, float* mean, float* rstd, int32_t rows, int32_t D,
+                     float eps, int32_t dtype, void* hip_stream) {
+    if (!x || !w || !b || !y || !mean || !rstd) return SPION_ERR_NULL;
+    const int rc = layer_norm_args_ok((uintptr_t)x | (uintptr_t)w | (uintptr_t)b | (uintptr_t)y, rows, D, dtype);
+    if (rc != SPION_OK) return rc;
+    return spion::launch_layer_norm(x, w, b, y, mean, rstd, rows, D, eps, dtype == SPION_BF16,
+                                    static_cast<hipStream_t>(hip_stream)) == hipSuccess ? SPION_OK : SPION_ERR_HIP;
+}
+
+size_t spion_layer_norm_workspace_bytes(int32_t rows, int32_t D) {
+    return layer_norm_args_ok(0, rows, D, SPION_F32) == SPION_OK ? align_up(spion::layer_norm_workspace_bytes(rows, D)) : (size_t)-1;
+}
+
+int spion_layer_norm_grad(const void* dy, const void* x, const void* w, const float* mean, const float* rstd, void* dx,
+                          void* dw, void* db, int32_t rows, int32_t D, int32_t dtype, void* workspace,
+                          size_t workspace_bytes, void* hip_stream) {
+    if (!dy || !x || !w || !mean || !rstd || !dx || !dw || !db) return SPION_ERR_NULL;
+    const int rc = layer_norm_args_ok((uintptr_t)dy | (uintptr_t)x | (uintptr_t)w | (uintptr_t)dx, rows, D, dtype);
+    if (rc != SPION_OK) return rc;
+    if (!workspace || ((uintptr_t)workspace % 16) != 0 || workspace_bytes < spion_layer_norm_workspace_bytes(rows, D))
+        return SPION_ERR_WORKSPACE;
+    return spion::launch_layer_norm_grad(dy, x, w, mean, rstd, dx, dw, db, static_cast<float*>(workspace), rows, D,
+                                         dtype == SPION_BF16, static_cast<hipStream_t>(hip_stream)) == hipSuccess
+               ? SPION_OK : SPION_ERR_HIP;
+}
+
 int spion_heads(int32_t split, void* merged, void* const* t, int32_t B, int32_t L, int32_t H, int32_t n, int32_t dtype,
                 void* hip_stream) {
     if (!merged || !t) return SPION_ERR_NULL;

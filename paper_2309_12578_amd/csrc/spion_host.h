@@ -22,6 +22,14 @@ size_t spion_weight_grad_workspace_bytes(int32_t rows, int32_t N, int32_t M);
 int spion_weight_grad(const void* dY, const void* X, void* dW, int32_t rows, int32_t N, int32_t M, void* workspace,
                       size_t workspace_bytes, void* hip_stream);
 
+// LayerNorm over contiguous rows of D elements (a multiple of 64, at most 2048), fp32 or bf16; mean and rstd [rows], fp32.
+int spion_layer_norm(const void* x, const void* w, const void* b, void* y, float* mean, float* rstd, int32_t rows, int32_t D,
+                     float eps, int32_t dtype, void* hip_stream);
+size_t spion_layer_norm_workspace_bytes(int32_t rows, int32_t D);
+int spion_layer_norm_grad(const void* dy, const void* x, const void* w, const float* mean, const float* rstd, void* dx,
+                          void* dw, void* db, int32_t rows, int32_t D, int32_t dtype, void* workspace,
+                          size_t workspace_bytes, void* hip_stream);
+
 // Head split (split != 0) or merge: merged [B, L, n, H, 64] <-> tensors t[0 .. n - 1] [B, H, L, 64], n = 1 or 3, fp32 or
 // bf16, L a multiple of 4, fewer than 2^31 vectors of 16 bytes.
 int spion_heads(int32_t split, void* merged, void* const* t, int32_t B, int32_t L, int32_t H, int32_t n, int32_t dtype,

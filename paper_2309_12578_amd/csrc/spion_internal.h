@@ -61,6 +61,13 @@ size_t attn_bwd_workspace_bytes(int BH, int bs, int nb, int nnzb);
 // false when a backward launch for this shape would need more workgroups than a 1-D grid can hold
 bool attn_bwd_grids_fit(int BH, int bs, int nb, int nnzb);
 
+// norm_kernels.hip: LayerNorm over rows of D = 64 k <= 2048 elements
+size_t layer_norm_workspace_bytes(int rows, int D);
+hipError_t launch_layer_norm(const void* x, const void* w, const void* b, void* y, float* mean, float* rstd, int rows,
+                             int D, float eps, bool is_bf16, hipStream_t st);
+hipError_t launch_layer_norm_grad(const void* dy, const void* x, const void* w, const float* mean, const float* rstd, void* dx,
+                                  void* dw, void* db, float* partial, int rows, int D, bool is_bf16, hipStream_t st);
+
 // projection_kernels.hip: dW [N, M] = dY^T X over `rows` rows, bf16, N and M multiples of 8
 size_t weight_grad_workspace_bytes(int rows, int N, int M);
 hipError_t launch_weight_grad(const void* dY, const void* X, void* dW, int rows, int N, int M, void* workspace,

@@ -1,8 +1,8 @@
 """The sparse multi-head-attention sub-layer of Algorithm 5 as a torch module.
 
-Glue around the library: LayerNorm, the four projections (hipBLASLt GEMMs but for the weight gradients),
-dropout and the residual are torch ops; the head split and lines 4-7 of Algorithm 5 (SDDMM, sparse
-softmax, SpMM for every head) are one call into libspion, forward and backward.
+Glue around the library: the four projections (hipBLASLt GEMMs but for the weight gradients), dropout and
+the residual are torch ops; LayerNorm is the library's, and the head split and lines 4-7 of Algorithm 5
+(SDDMM, sparse softmax, SpMM for every head) are one call into it, forward and backward.
 """
 from __future__ import annotations
 
@@ -13,6 +13,16 @@ from . import binding as _b
 from .autograd import sparse_attention
 
 HEAD_DIM = 64   # the only head dimension the kernels are built for
+
+
+class _Norm(nn.LayerNorm):
+    """nn.LayerNorm by the library's kernels (csrc/norm_kernels.hip) where they take the call."""
+
+    def forward(self, x: torch.Tensor) -> torch.Tensor:
+        y = None
+        if x.is_cuda and self.weight is not None and self.bias is not None and not torch.compiler.is_compiling():
+            y = (_b._host or _b._native()).layer_norm(x, self.weight, self.bias, self.eps)
+        return super().forward(x) if y is None else y
 
 
 class _Projection(nn.Linear):
@@ -37,7 +47,7 @@ class SparseMHA(nn.Module):
             raise ValueError("embed_dim must be %d * heads" % HEAD_DIM)
         kw = dict(device=device, dtype=dtype)
         self.heads = heads
-        self.norm = nn.LayerNorm(embed_dim, **kw)
+        self.norm = _Norm(embed_dim, **kw)
         self.w_qkv = _Projection(embed_dim, 3 * embed_dim, bias=bias, **kw)   # W^Q | W^K | W^V
         self.w_o = _Projection(embed_dim, embed_dim, bias=bias, **kw)
         self.drop = nn.Dropout(dropout)

@@ -261,6 +261,7 @@ def test_sublayer_fused_and_step_by_step(sp, dtype, B, H, nb, block):
     pat = _pattern_from_mask(sp, np.tril(np.ones((nb, nb), dtype=np.uint8)), block)
     gen = torch.Generator(device="cuda").manual_seed(H)
     mha = sp.SparseMHA(64 * H, H, device="cuda", dtype=dtype)
+    mha.norm = torch.nn.LayerNorm(64 * H, device="cuda", dtype=dtype)   # the same on both sides
     E, dout = [torch.randn((B, nb * block, 64 * H), generator=gen, device="cuda").to(dtype) for _ in range(2)]
     E.requires_grad_(True)
     fused = mha(E, pat)
@@ -276,3 +277,54 @@ def test_sublayer_fused_and_step_by_step(sp, dtype, B, H, nb, block):
     assert fused.grad_fn is not None and torch.equal(fused, steps) and torch.equal(d_fused, d_steps)
     with torch.no_grad():
         assert torch.equal(mha(E, pat), steps)
+
+
+# Rows of 256, 512, 1024 and 2048 columns in registers and less; 4 rows a workgroup, 16 rows a partial of the weight's
+# and bias' gradients, 512 partials at most; a width that is not a multiple of 64 is torch's
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("rows,D", [(1, 64), (3, 192), (17, 256), (129, 320), (9000, 512), (40, 1024), (33, 1088), (16, 2048),
+                                    (20, 100)])
+def test_layer_norm(sp, dtype, rows, D):
+    from paper_2309_12578_amd.sublayer import _Norm
+    gen = torch.Generator(device="cuda").manual_seed(rows + D)
+    norm = _Norm(D, device="cuda", dtype=dtype)
+    x, dy = [torch.randn((1, rows, D), generator=gen, device="cuda") for _ in range(2)]
+    x = (x + 5.0).to(dtype).requires_grad_(True)
+    dy = dy.to(dtype)
+    with torch.no_grad():
+        for p in norm.parameters():
+            p.copy_(torch.randn(D, generator=gen, device="cuda"))
+    y = norm(x)
+    got = [y, *torch.autograd.grad(y, [x, *norm.parameters()], dy)]
+    x64, w64, b64 = [t.detach().double().requires_grad_(True) for t in (x, norm.weight, norm.bias)]
+    y64 = torch.nn.functional.layer_norm(x64, (D,), w64, b64, norm.eps)
+    want = [y64, *torch.autograd.grad(y64, [x64, w64, b64], dy.double())]
+    # fp32: sums of up to 9000 values of mixed sign, statistics of values around 5: 2^-24 times a few dozen; bf16: one
+    # rounding, 2^-9 of each value
+    tol = 1e-5 if dtype == torch.float32 else 2.0 ** -8
+    for g, r in zip(got, want):
+        assert g.dtype == dtype and (g.double() - r).norm() <= tol * r.norm()
+
+
+def test_layer_norm_beside_the_other_transforms(sp):
+    from paper_2309_12578_amd.sublayer import _Norm
+    norm, plain = _Norm(128, device="cuda"), torch.nn.LayerNorm(128, device="cuda")
+    x = torch.randn((4, 8, 128), device="cuda", requires_grad=True)
+    ad = torch.autograd.forward_ad
+
+    def tangent(f):
+        with ad.dual_level():
+            return ad.unpack_dual(f(ad.make_dual(x.detach(), x.detach()))).tangent
+
+    def second(f):
+        g, = torch.autograd.grad(f(x).pow(3).sum(), x, create_graph=True)
+        return torch.autograd.grad(g.square().sum(), x)[0]
+
+    def cast(f):
+        with torch.autocast("cuda", dtype=torch.float16):
+            return f(x)
+
+    for call in (tangent, second, cast, lambda f: torch.func.vmap(f)(x), lambda f: torch.func.grad(lambda t: f(t).pow(2).sum())(x),
+                 lambda f: f(x.detach()), lambda f: f(x.transpose(0, 1))):
+        a, b = call(norm), call(plain)
+        assert a.dtype == b.dtype and torch.allclose(a, b, rtol=1e-4, atol=1e-4 * b.abs().max().item())
