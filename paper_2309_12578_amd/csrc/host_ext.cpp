@@ -13,6 +13,7 @@
 #include <ATen/hip/EmptyTensor.h>
 #include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
+#include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/function.h>
@@ -313,7 +314,8 @@ bool nothing_between() {
         if (c10::impl::tls_is_dispatch_key_included(k)) return false;
     return !at::autocast::is_autocast_enabled(at::kCUDA);
 }
-// A plain strided device tensor: no subclass, no wrapper of a transform, no tangent.
+// A plain strided tensor on the current device (whose stream the library is given): no subclass, no wrapper of a
+// transform, no tangent.
 bool plain(PyObject* o) {
     if (!THPVariable_CheckExact(o)) return false;
     const at::Tensor& t = THPVariable_Unpack(o);
@@ -321,7 +323,7 @@ bool plain(PyObject* o) {
     for (DispatchKey k : {DispatchKey::Python, DispatchKey::Functionalize, DispatchKey::FuncTorchBatched,
                           DispatchKey::FuncTorchGradWrapper})
         if (t.key_set().has(k)) return false;
-    return t.is_cuda() && t.layout() == at::kStrided && !t._fw_grad(0).defined();
+    return t.is_cuda() && t.get_device() == c10::hip::current_device() && t.layout() == at::kStrided && !t._fw_grad(0).defined();
 }
 
 // The gradient of Y = X W^T + b.  The weight's comes from spion_weight_grad; a backward pass that is itself
