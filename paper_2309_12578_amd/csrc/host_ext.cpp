@@ -21,6 +21,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 #include <torch/csrc/autograd/saved_variable.h>
 #include <torch/csrc/autograd/variable.h>
+#include <torch/csrc/jit/frontend/tracer.h>
 
 #include "spion_host.h"
 
@@ -262,10 +263,12 @@ struct SparseAttentionBackward : public torch::autograd::Node {
     }
 };
 
-// sparse_attention(Q, K, V, row_ptr, col_idx, col_ptr, row_idx, bsr_pos, nnzb, block, scale, flags) -> O
+// sparse_attention(Q, K, V, row_ptr, col_idx, col_ptr, row_idx, bsr_pos, nnzb, block, scale, flags) -> O, or None under
+// torch.jit.trace: what is allocated and launched here is not seen by the tracer, which would record O as a constant.
 PyObject* py_sparse_attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (!arg_count(n, 12, "sparse_attention")) return nullptr;
     return guarded([&]() -> PyObject* {
+        if (torch::jit::tracer::isTracing()) Py_RETURN_NONE;
         const at::Tensor &q = tensor_arg(a[0]), &k = tensor_arg(a[1]), &v = tensor_arg(a[2]);
         Index ix;
         ix.row_ptr = tensor_arg(a[3]);

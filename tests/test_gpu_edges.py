@@ -328,3 +328,34 @@ def test_layer_norm_beside_the_other_transforms(sp):
                  lambda f: f(x.detach()), lambda f: f(x.transpose(0, 1))):
         a, b = call(norm), call(plain)
         assert a.dtype == b.dtype and torch.allclose(a, b, rtol=1e-4, atol=1e-4 * b.abs().max().item())
+
+
+@pytest.mark.parametrize("needs_grad", [False, True])
+def test_trace_replays_on_other_inputs(sp, needs_grad):
+    """torch.jit.trace records the attention as an operator, also inside the sub-layer: another input, another output."""
+    pat, q, k, v, do = _small_attention(sp)
+    first, other = [[t.clone().requires_grad_(needs_grad) for t in s] for s in ((q, k, v), (v, q, k))]
+    traced = torch.jit.trace(lambda a, b, c: sp.sparse_attention(a, b, c, pat), first, check_trace=False)
+    got, want = traced(*other), sp.sparse_attention(*other, pat)
+    assert torch.equal(got, want)
+    if needs_grad:
+        for a, b in zip(torch.autograd.grad(got, other, do), torch.autograd.grad(want, other, do)):
+            assert torch.equal(a, b)
+
+    class Layer(torch.nn.Module):
+        def __init__(self):
+            super().__init__()
+            self.mha = sp.SparseMHA(128, 2, device="cuda")
+
+        def forward(self, x):
+            return self.mha(x, pat)
+
+    layer = Layer().requires_grad_(needs_grad)
+    E, E2 = [t.transpose(1, 2).reshape(1, -1, 128) for t in (q, k)]
+    traced = torch.jit.trace(layer, E, check_trace=False)
+    got, want = traced(E2), layer(E2)
+    # LayerNorm and the products are torch's under a trace: fp32 sums of 128 values in another order
+    assert torch.allclose(got, want, rtol=1e-5, atol=1e-5)
+    if needs_grad:
+        for a, b in zip(*[torch.autograd.grad(t.square().sum(), list(layer.parameters())) for t in (got, want)]):
+            assert (a - b).norm() <= 1e-5 * b.norm()
