@@ -318,19 +318,24 @@ bool nothing_between() {
     return !at::autocast::is_autocast_enabled(at::kCUDA);
 }
 // A plain strided tensor on the current device (whose stream the library is given): no subclass, no wrapper of a
-// transform, no tangent.
-bool plain(PyObject* o) {
-    if (!THPVariable_CheckExact(o)) return false;
-    const at::Tensor& t = THPVariable_Unpack(o);
+// transform, no view whose values are not those in memory, no tangent.
+bool plain(const at::Tensor& t) {
     using c10::DispatchKey;
-    for (DispatchKey k : {DispatchKey::Python, DispatchKey::Functionalize, DispatchKey::FuncTorchBatched,
-                          DispatchKey::FuncTorchGradWrapper})
+    for (DispatchKey k : {DispatchKey::Python, DispatchKey::Functionalize, DispatchKey::FuncTorchBatched, DispatchKey::Batched,
+                          DispatchKey::FuncTorchGradWrapper, DispatchKey::Negative, DispatchKey::ZeroTensor})
         if (t.key_set().has(k)) return false;
     return t.is_cuda() && t.get_device() == c10::hip::current_device() && t.layout() == at::kStrided && !t._fw_grad(0).defined();
 }
+bool plain(PyObject* o) { return THPVariable_CheckExact(o) && plain(THPVariable_Unpack(o)); }
 
-// The gradient of Y = X W^T + b.  The weight's comes from spion_weight_grad; a backward pass that is itself
-// differentiated is made of torch operators.
+// Whether a backward pass may compute in kernels of the library: it is not differentiated itself, backward (grad mode)
+// or forward (a tangent on the incoming gradient), nor batched over incoming gradients, nor watched.
+bool kernels_may_differentiate(const at::Tensor& grad) {
+    return !at::GradMode::is_enabled() && nothing_between() && plain(grad);
+}
+
+// The gradient of Y = X W^T + b.  The weight's comes from spion_weight_grad where only numbers are wanted, else, as
+// the others, from torch operators.
 struct ProjectionBackward : public torch::autograd::Node {
     torch::autograd::SavedVariable x, w;
     bool has_bias = false;
@@ -349,7 +354,10 @@ struct ProjectionBackward : public torch::autograd::Node {
         const int64_t N = W.size(0), M = W.size(1);
         const at::Tensor g = grads[0].reshape({-1, N}), x2 = X.reshape({-1, M});
         if (task_should_compute_output(0)) out[0] = at::mm(g, W).view(X.sizes());
-        if (task_should_compute_output(1)) out[1] = at::GradMode::is_enabled() ? at::mm(g.t(), x2) : weight_grad(g.contiguous(), x2.contiguous());
+        if (task_should_compute_output(1)) {
+            const bool kernel = kernels_may_differentiate(grads[0]) && plain(X);
+            out[1] = kernel ? weight_grad(g.contiguous(), x2.contiguous()) : at::mm(g.t(), x2);
+        }
         if (has_bias && task_should_compute_output(2)) out[2] = g.sum(0);
         return out;
     }
@@ -465,8 +473,7 @@ PyObject* py_heads_attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
     });
 }
 
-// The gradient of layer_norm, all three in one pass over X and dY; torch's operator where the pass itself is
-// differentiated.
+// The gradient of layer_norm, all three in one pass over X and dY; torch's operator where more than numbers is wanted.
 struct NormBackward : public torch::autograd::Node {
     torch::autograd::SavedVariable x, w, b, mean, rstd;
 
@@ -482,7 +489,7 @@ struct NormBackward : public torch::autograd::Node {
         const at::Tensor X = x.unpack(), W = w.unpack(), m = mean.unpack(), r = rstd.unpack();
         const int64_t D = W.size(0);
         const at::Tensor g = grads[0].contiguous();
-        if (at::GradMode::is_enabled() || (uintptr_t)g.data_ptr() % 16 != 0) {
+        if (!kernels_may_differentiate(grads[0]) || !plain(X) || !plain(W) || (uintptr_t)g.data_ptr() % 16 != 0) {
             std::vector<int64_t> stat(X.sizes().begin(), X.sizes().end());
             stat.back() = 1;
             std::tie(out[0], out[1], out[2]) = at::native_layer_norm_backward(

@@ -359,3 +359,27 @@ def test_trace_replays_on_other_inputs(sp, needs_grad):
     if needs_grad:
         for a, b in zip(*[torch.autograd.grad(t.square().sum(), list(layer.parameters())) for t in (got, want)]):
             assert (a - b).norm() <= 1e-5 * b.norm()
+
+
+@pytest.mark.parametrize("node", ["projection", "norm"])
+def test_incoming_gradients_that_are_not_plain(sp, node):
+    """A tangent or a batch that only the incoming gradient has (the loss is differentiated forward, or over a batch of
+    losses): the nodes of the sub-layer hand it on as torch's operators do."""
+    from paper_2309_12578_amd.sublayer import _Norm, _Projection
+    kw = dict(device="cuda", dtype=torch.bfloat16)
+    ours, plain = (_Projection(64, 192, **kw), torch.nn.Linear(64, 192, **kw)) if node == "projection" else (_Norm(64, **kw), torch.nn.LayerNorm(64, **kw))
+    plain.load_state_dict(ours.state_dict())
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn((4, 32, 64), generator=gen, device="cuda").to(torch.bfloat16).requires_grad_(True)
+    dy = torch.randn((3, 4, 32, plain(x).shape[-1]), generator=gen, device="cuda").to(torch.bfloat16)
+    ad = torch.autograd.forward_ad
+    result = []
+    for layer in (ours, plain):
+        wrt = [x, *layer.parameters()]
+        with ad.dual_level():
+            duals = [ad.unpack_dual(g) for g in torch.autograd.grad(layer(x), wrt, ad.make_dual(dy[0], dy[1]))]
+            assert all(d.tangent is not None for d in duals)
+            result.append([t.float() for d in duals for t in d] +
+                          [t.float() for t in torch.autograd.grad(layer(x), wrt, dy, is_grads_batched=True)])
+    for a, b in zip(*result):   # sums in fp32, one rounding to bf16 each
+        assert a.shape == b.shape and (a - b).norm() <= 2.0 ** -7 * b.norm()
