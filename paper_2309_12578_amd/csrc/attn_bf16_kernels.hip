@@ -186,16 +186,15 @@ __global__ __launch_bounds__(BS * 4) void attn_fwd_bf16_kernel(
     __builtin_amdgcn_s_waitcnt(kWaitVm0);
 
     float lsum = lacc[0];
-    if (paper_denom && n > 0) {
+    if (paper_denom && n > 0 && L > n * BS) {
         // Algorithm 6: every masked entry of the row counts as a score of 0 (a row that keeps nothing
-        // has no entry to normalise and stays at O = 0, LSE = -inf)
-        const float masked = (float)(L - n * BS);
+        // has no entry to normalise and stays at O = 0, LSE = -inf).  The sums are up to 2^kRescaleSlack times
+        // what they would be against the row's maximum.
         const float mp = fmaxf(m, 0.f);
-        const float a = exp2f(m - mp);
-        lsum = lsum * a + masked * exp2f(-mp);
-        m = mp;
+        lsum = scale_down(lacc, m - mp)[0] + (float)(L - n * BS) * exp2f(-mp);
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt) oacc[dt] *= a;
+        for (int dt = 0; dt < 4; ++dt) oacc[dt] = scale_down(oacc[dt], m - mp);
+        m = mp;
     }
     const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
     // the stage that the last block did not use is free: every wave is past the barrier that followed

@@ -41,6 +41,12 @@ struct Elem<bf16_t> {
     typedef bf16x4 Quad;
 };
 
+// v * 2^x, x <= 0, for v far above 1 and x as far below 0: 2^x by itself would be 0 below x = -149.
+__device__ __forceinline__ f32x4 scale_down(f32x4 v, float x) {
+    const float k = fmaxf(floorf(x), -1024.f), f = exp2f(x - k);
+    return f32x4{ldexpf(v[0] * f, (int)k), ldexpf(v[1] * f, (int)k), ldexpf(v[2] * f, (int)k), ldexpf(v[3] * f, (int)k)};
+}
+
 // 2^x of the exponent unit alone; a result below the smallest normal number comes out as 0
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 

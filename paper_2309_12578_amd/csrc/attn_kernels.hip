@@ -71,9 +71,6 @@ template <typename T> struct SplitMany<T, 64> {
     typedef Split<T, 64, 2, 1, 2> bwd_single;
 };
 
-__device__ __forceinline__ float exp2_of(float x, float) { return exp2f(x); }
-__device__ __forceinline__ float exp2_of(float x, bf16_t) { return fast_exp2(x); }
-
 // lane (r, g): elements g EPL .. of each d chunk of row r
 template <typename T>
 __device__ __forceinline__ void load_rows(typename Elem<T>::Frag (&f)[kD / Elem<T>::KC], const T* tile, int r, int g) {
@@ -237,7 +234,7 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_fwd_kernel(
 #pragma unroll
             for (int h = 0; h < NQ; ++h) {
                 const float m_new = fmaxf(m[h], group_max(mx[h]) * scale_log2);
-                const float alpha = exp2_of(m[h] - m_new, T());
+                const float alpha = exp2f(m[h] - m_new);
                 m[h] = m_new;
                 limit[h] = m_new + kRescaleSlack;
                 lsum[h] *= alpha;
@@ -253,7 +250,7 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_fwd_kernel(
                 f32x4 p;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    p[i] = exp2_of(fmaf(s[h][u][i], scale_log2, -m[h]), T());
+                    p[i] = exp2f(fmaf(s[h][u][i], scale_log2, -m[h]));
                     if (u > 0) p[i] = t + u < nt ? p[i] : 0.f;
                     lsum[h] += p[i];
                 }
@@ -271,14 +268,22 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_fwd_kernel(
         }
     }
 
+    // Algorithm 6: every masked entry of the row counts as a score of 0 (a row that keeps nothing
+    // has no entry to normalise and stays at O = 0, LSE = -inf).  The sums are up to 2^kRescaleSlack times what they
+    // would be against the row's maximum.
+    const float masked = paper_denom && n > 0 ? (float)(L - n * BS) : 0.f;
     if constexpr (S::WT == 1) {
 #pragma unroll
         for (int h = 0; h < NQ; ++h) {
             const int q = row0 + h * 16 + r;
-            const float mm = paper_denom ? fmaxf(m[h], 0.f) : m[h], a = n > 0 ? exp2_of(m[h] - mm, T()) : 0.f;
-            float l = group_sum(lsum[h]) * a;
-            if (paper_denom && n > 0) l += (float)(L - n * BS) * exp2f(-mm);
-            store_acc<T>(O + head + (size_t)q * kD, oacc[h], l > 0.f ? a / l : 0.f, g);
+            const float mm = masked > 0.f ? fmaxf(m[h], 0.f) : m[h];
+            float l = group_sum(lsum[h]);
+            if (masked > 0.f) {
+                l = scale_down(f32x4{l, 0.f, 0.f, 0.f}, m[h] - mm)[0] + masked * exp2f(-mm);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) oacc[h][e] = scale_down(oacc[h][e], m[h] - mm);
+            }
+            store_acc<T>(O + head + (size_t)q * kD, oacc[h], l > 0.f ? 1.f / l : 0.f, g);
             if (g == 0) LSE[(size_t)bh * L + q] = l > 0.f ? (mm + log2f(l)) * kLn2 : -INFINITY;
         }
         return;
@@ -300,19 +305,21 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_fwd_kernel(
         float mm = m_s[0][q];
 #pragma unroll
         for (int w = 1; w < S::WT; ++w) mm = fmaxf(mm, m_s[w][q]);
-        // Algorithm 6: every masked entry of the row counts as a score of 0 (a row that keeps nothing
-        // has no entry to normalise and stays at O = 0, LSE = -inf)
-        if (paper_denom) mm = fmaxf(mm, 0.f);
         f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
         float l = 0.f;
         if (n > 0) {
 #pragma unroll
             for (int w = 0; w < S::WT; ++w) {
-                const float a = exp2_of(m_s[w][q] - mm, T());
+                const float a = exp2f(m_s[w][q] - mm);
                 l += l_s[w][q] * a;
                 o += *reinterpret_cast<const f32x4*>(&o_s[w][q * kPatchLd + d]) * a;
             }
-            if (paper_denom) l += (float)(L - n * BS) * exp2f(-mm);
+        }
+        if (masked > 0.f) {
+            const float mp = fmaxf(mm, 0.f);
+            o = scale_down(o, mm - mp);
+            l = scale_down(f32x4{l, 0.f, 0.f, 0.f}, mm - mp)[0] + masked * exp2f(-mp);
+            mm = mp;
         }
         const float inv = l > 0.f ? 1.f / l : 0.f;
         store_quad<T>(O + head + (size_t)(wg0 + q) * kD + d, o * inv);
@@ -438,7 +445,7 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_bwd_kernel(
                     f32x4 ds;
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        ds[i] = exp2_of(fmaf(s[i], scale_log2, -lse2[h]), T()) * dp[i];
+                        ds[i] = exp2f(fmaf(s[i], scale_log2, -lse2[h])) * dp[i];
                         if (u > 0) ds[i] = t + u < nt ? ds[i] : 0.f;
                     }
                     dsq[h][u] = to_quad<T>(ds);
@@ -510,7 +517,7 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_bwd_kernel(
                     f32x4 p, ds;
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        p[i] = exp2_of(fmaf(s[i], scale_log2, -lse[i] * kLog2e), T());
+                        p[i] = exp2f(fmaf(s[i], scale_log2, -lse[i] * kLog2e));
                         ds[i] = p[i] * dp[i];
                     }
                     pq[h][u] = to_quad<T>(p);

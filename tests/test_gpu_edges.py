@@ -383,3 +383,38 @@ def test_incoming_gradients_that_are_not_plain(sp, node):
                           [t.float() for t in torch.autograd.grad(layer(x), wrt, dy, is_grads_batched=True)])
     for a, b in zip(*result):   # sums in fp32, one rounding to bf16 each
         assert a.shape == b.shape and (a - b).norm() <= 2.0 ** -7 * b.norm()
+
+
+# Scores far below 0 under Algorithm 6's denominator, 29 log2 units lower in the first half of the keys (where every
+# wave, and every row whose diagonal lies there, starts) than in the second: the waves' sums are scaled down by 2^-154 altogether.
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("block,nb,heads", [(16, 40, 1), (32, 16, 1), (64, 8, 1), (16, 40, 256), (32, 16, 512), (64, 8, 512)])
+def test_paper_denominator_far_below_zero(sp, dtype, block, nb, heads):
+    from test_gpu_parity import _pattern_from_mask
+    L, d = nb * block, 64
+    rng = np.random.default_rng(block)
+    Q, K, V = [np.zeros((1, L, d), dtype=np.float32) for _ in range(3)]
+    Q[:, :, 0] = 8.0                                        # scores 8 * K[..., 0] / 8
+    K[:, :L // 2, 0], K[:, L // 2:, 0] = -107.0, -87.0
+    V[:] = si.round_to_dtype(rng.standard_normal((1, L, d), dtype=np.float32), dtype) * 2.0 ** 24
+    fl = np.ones((nb, nb), dtype=np.uint8)
+    q, k, v = [torch.from_numpy(t).cuda().to(torch.bfloat16 if dtype == "bf16" else torch.float32).expand(heads, L, d)[None].contiguous()
+               for t in (Q, K, V)]
+    # nothing masked: nothing to add to the denominator, however small the kept probabilities' exponentials
+    pat = _pattern_from_mask(sp, fl, block)
+    for a, b in zip(sp.attn_fwd(q, k, v, pat, flags=sp.SPION_ATTN_PAPER_DENOM), sp.attn_fwd(q, k, v, pat)):
+        assert torch.equal(a, b) and a.abs().min() > 0
+    low = k.clone()
+    low[..., 0] *= 4
+    for a, b in zip(sp.attn_fwd(q, low, v, pat, flags=sp.SPION_ATTN_PAPER_DENOM), sp.attn_fwd(q, low, v, pat)):
+        assert torch.equal(a, b) and a.abs().min() > 0
+    # one block masked: O is of the order of 2^-126 * V / block
+    fl[:, nb // 2 + 1] = 0
+    fl[nb // 2 + 1, nb // 2 + 1] = 1
+    O, LSE = sp.attn_fwd(q, k, v, _pattern_from_mask(sp, fl, block), flags=sp.SPION_ATTN_PAPER_DENOM)
+    rO, rLSE = oracle.attn_fwd(Q, K, V, oracle.upsample(fl, block), flags=oracle.ATTN_PAPER_DENOM)
+    for h in (0, heads - 1):
+        x, lse = O[0, h].double().cpu().numpy(), LSE[0, h].cpu().numpy()
+        # fp32: an exponential of 126 +- 2^-17 log2 units; bf16: P and O rounded to 2^-9 of each value
+        assert np.linalg.norm(x - rO[0]) <= (2.0 ** -15 if dtype == "f32" else 2.0 ** -7) * np.linalg.norm(rO[0])
+        assert np.abs(lse - rLSE[0]).max() <= 1e-5 * np.abs(rLSE[0]).max()
