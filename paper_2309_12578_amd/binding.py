@@ -312,10 +312,13 @@ def frobenius_distance(A_prev: torch.Tensor, A_cur: torch.Tensor, out: Optional[
 def attn_fwd(Q, K, V, pat: Pattern, scale: float = 0.0, flags: int = 0,
              O: Optional[torch.Tensor] = None, LSE: Optional[torch.Tensor] = None
              ) -> Tuple[torch.Tensor, torch.Tensor]:
+    """Returns O and LSE.  Sizes are those of Q [B, H, L, 64]; every other tensor has its dtype (LSE: fp32), is
+    contiguous and may hold more elements than needed, of which the first are used."""
     return (_host or _native()).attn_fwd(Q, K, V, pat.row_ptr, pat.col_idx, pat.nnzb, pat.block, scale, flags, O, LSE)
 
 
 def attn_bwd(Q, K, V, O, dO, LSE, pat: Pattern, scale: float = 0.0, flags: int = 0,
              dQ=None, dK=None, dV=None, workspace: Optional[torch.Tensor] = None):
+    """Returns dQ, dK and dV; the tensors as for `attn_fwd`."""
     return (_host or _native()).attn_bwd(Q, K, V, O, dO, LSE, pat.row_ptr, pat.col_idx, pat.col_ptr, pat.row_idx,
                                          pat.bsr_pos, pat.nnzb, pat.block, scale, flags, dQ, dK, dV, workspace)

@@ -106,24 +106,27 @@ spion_attn_params params_of(const at::Tensor& q, const Index& ix) {
     return p;
 }
 
-// The kernels take every size from Q: a smaller tensor beside it would be read or written past its end.
-void same_size(const at::Tensor& q, const at::Tensor& t) {
-    if (t.numel() != q.numel() || t.scalar_type() != q.scalar_type()) bad_value("Q, K, V and their companions must agree in shape and dtype");
+// The kernels take every size from Q: a smaller tensor beside it would be read or written past its end.  A larger one,
+// a buffer kept for several shapes, has its first elements used.
+void room_for(const at::Tensor& q, const at::Tensor& t) {
+    if (t.numel() < q.numel() || t.scalar_type() != q.scalar_type())
+        bad_value("Q's companions must have its dtype and at least as many elements");
 }
-void same_rows(const at::Tensor& q, const at::Tensor& lse) {
-    if (lse.numel() * q.size(3) != q.numel() || lse.scalar_type() != at::kFloat) bad_value("LSE must be fp32 [B, H, L]");
+void room_for_rows(const at::Tensor& q, const at::Tensor& lse) {
+    if (lse.numel() * q.size(3) < q.numel() || lse.scalar_type() != at::kFloat)
+        bad_value("LSE must be fp32 with at least B * H * L elements");
 }
 
 void forward(const at::Tensor& q, const at::Tensor& k, const at::Tensor& v, const Index& ix, at::Tensor& o, at::Tensor& lse) {
     device_ptr(q);
     const spion_attn_params p = params_of(q, ix);
-    same_size(q, k);
-    same_size(q, v);
+    room_for(q, k);
+    room_for(q, v);
     if (!o.defined()) o = new_like(q);
-    else same_size(q, o);
+    else room_for(q, o);
     if (!lse.defined())
         lse = at::Tensor(at::detail::empty_cuda({q.size(0), q.size(1), q.size(2)}, at::kFloat, q.device(), std::nullopt));
-    else same_rows(q, lse);
+    else room_for_rows(q, lse);
     const int rc = spion_attn_fwd(device_ptr(q), device_ptr(k), device_ptr(v), device_ptr(o), (float*)device_ptr(lse),
                                   (const int32_t*)device_ptr(ix.row_ptr), (const int32_t*)device_ptr(ix.col_idx),
                                   ix.nnzb, &p, nullptr, 0, current_stream());
@@ -134,11 +137,11 @@ void backward(const at::Tensor& q, const at::Tensor& k, const at::Tensor& v, con
               const at::Tensor& lse, const Index& ix, at::Tensor& dq, at::Tensor& dk, at::Tensor& dv, at::Tensor& ws) {
     device_ptr(q);
     const spion_attn_params p = params_of(q, ix);
-    for (const at::Tensor* t : {&k, &v, &o, &grad}) same_size(q, *t);
-    same_rows(q, lse);
+    for (const at::Tensor* t : {&k, &v, &o, &grad}) room_for(q, *t);
+    room_for_rows(q, lse);
     for (at::Tensor* t : {&dq, &dk, &dv}) {
         if (!t->defined()) *t = new_like(q);
-        else same_size(q, *t);
+        else room_for(q, *t);
     }
     if (!ws.defined()) {
         const size_t n = spion_attn_workspace_bytes(&p, ix.nnzb, 1);

@@ -418,3 +418,28 @@ def test_paper_denominator_far_below_zero(sp, dtype, block, nb, heads):
         # fp32: an exponential of 126 +- 2^-17 log2 units; bf16: P and O rounded to 2^-9 of each value
         assert np.linalg.norm(x - rO[0]) <= (2.0 ** -15 if dtype == "f32" else 2.0 ** -7) * np.linalg.norm(rO[0])
         assert np.abs(lse - rLSE[0]).max() <= 1e-5 * np.abs(rLSE[0]).max()
+
+
+def test_buffers_larger_than_needed(sp):
+    """attn_fwd and attn_bwd write the first elements of a buffer that has room for more, and refuse smaller ones."""
+    pat, q, k, v, do = _small_attention(sp)
+    o, lse = sp.attn_fwd(q, k, v, pat)
+    want = sp.attn_bwd(q, k, v, o, do, lse, pat)
+
+    def room(t):
+        return torch.full((t.numel() + 100,), 7.0, dtype=t.dtype, device="cuda")
+
+    O, LSE = sp.attn_fwd(q, k, v, pat, O=room(o), LSE=room(lse))
+    grads = sp.attn_bwd(q, k, v, O, do, LSE, pat, dQ=room(q), dK=room(q), dV=room(q))
+    for a, b in zip((O, LSE, *grads), (o, lse, *want)):
+        assert torch.equal(a[:b.numel()], b.flatten()) and (a[b.numel():] == 7.0).all()
+    small = torch.empty(q.numel() - 1, device="cuda")
+    for kw in (dict(O=small), dict(LSE=small[:lse.numel() - 1]), dict(O=torch.empty_like(q, dtype=torch.bfloat16))):
+        with pytest.raises(ValueError):
+            sp.attn_fwd(q, k, v, pat, **kw)
+    for name in ("dQ", "dK", "dV"):
+        with pytest.raises(ValueError):
+            sp.attn_bwd(q, k, v, o, do, lse, pat, **{name: small})
+    for args in ((q, small, v), (q, k, small)):
+        with pytest.raises(ValueError):
+            sp.attn_fwd(*args, pat)
