@@ -53,9 +53,8 @@ __global__ __launch_bounds__(BS * 4) void attn_fwd_bf16_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int bh, I;
     if (sort_rows) {
-        const int heads = total / nb, split = (heads & 7) == 0 ? 8 : 1;   // heads shared out over the XCDs, as below
-        const RowOfHead at = long_rows_first(row_ptr, nb, heads / split, blockIdx.x / split, lane);
-        bh = (int)(blockIdx.x % split) * (heads / split) + at.head;
+        const RowOfHead at = long_rows_first<true>(row_ptr, nb, total / nb, blockIdx.x, lane);
+        bh = at.head;
         I = at.row;
     } else {
         const int vid = xcd_remap(blockIdx.x, total);
@@ -211,8 +210,8 @@ template <int BS>
 hipError_t fwd_bf16(const AttnShape& s, const void* Q, const void* K, const void* V, void* O, float* LSE,
                     const int* row_ptr, const int* col_idx, hipStream_t st) {
     const int total = s.nb * s.BH;
-    // 4 (block 64) or 8 (block 32) workgroups fit a compute unit; where all run at once their order is immaterial,
-    // and finding a row by its rank costs a workgroup half a microsecond
+    // 4 (block 64) and at least 8 (block 32) workgroups fit a compute unit; where all run at once their order is
+    // immaterial, and finding a row by its rank costs a workgroup half a microsecond
     const int sort_rows = total > 256 * (BS == 64 ? 4 : 8);
     attn_fwd_bf16_kernel<BS><<<dim3((unsigned)total), dim3(BS * 4), 0, st>>>(
         static_cast<const bf16_t*>(Q), static_cast<const bf16_t*>(K), static_cast<const bf16_t*>(V),

@@ -156,32 +156,62 @@ __device__ __forceinline__ int walk_index(int t, int pd) {
     return pd < 0 ? t : (t == 0 ? pd : (t - 1 < pd ? t - 1 : t));
 }
 
-// Which block row the workgroup number l of the `heads` heads of an XCD takes, when there are more workgroups
+// Workgroup ids lo .. hi - 1 as numbers 0 .. hi - lo - 1 such that each XCD (id % 8) has a contiguous run of
+// them, whatever the two bounds are.
+__device__ __forceinline__ int xcd_deal(int id, int lo, int hi) {
+    const int x = id & 7;
+    auto lower_xcds = [x](int n) { return x * (n >> 3) + min(x, n & 7); };   // ids below n of the XCDs before x
+    return lower_xcds(hi) - lower_xcds(lo) + (id >> 3) - ((lo + 7 - x) >> 3);
+}
+
+// Which block row the workgroup number l of `heads` heads takes, when there are more workgroups
 // than run at once: the rows with more than twice the mean number of kept blocks first, of all the heads (a
 // row of 80 blocks that starts last runs alone for as long as everything before it took), then head by
-// head the others, so that neighbours in time share K and V in the XCD's L2.
+// head the others, so that neighbours in time share K and V in an L2.  DEAL: l is the workgroup id, and each
+// of the two lists is shared out over the XCDs head by head; else l counts the workgroups of one XCD.
+// Dealt this way for any number of heads: rows in id order, one L2 after the other, at 12 heads of 256 rows of
+// 64 x 13 blocks each in a band read K and V eight times (forward 101 -> 58 us; 20 heads, block 32, 9 blocks: 61 -> 27
+// us; unsorted and dealt 61 and 29 us).  Patterns without a long row skip the second search, and the counts are
+// loaded four groups at a time (3 heads of 1000 rows of 12 blocks: 86 -> 76 us, unsorted 77).
 // All lanes of the calling wave must be active.
 struct RowOfHead {
     int row, head;
 };
+template <bool DEAL>
 __device__ __forceinline__ RowOfHead long_rows_first(const int* __restrict__ row_ptr, int nb, int heads, int l, int lane) {
     const int limit = 2 * row_ptr[nb] / nb;
     int n_long = 0, cnt_first = 0;   // rows 0 .. 63 are kept for the second search
-    for (int base = 0; base < nb; base += 64) {
+    int base0 = 0;
+    for (; base0 + 256 <= nb; base0 += 256) {   // four groups whose loads are in flight together
+        int from[4], to[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            from[k] = row_ptr[base0 + 64 * k + lane];
+            to[k] = row_ptr[base0 + 64 * k + lane + 1];
+        }
+        if (base0 == 0) cnt_first = to[0] - from[0];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) n_long += __popcll(__ballot(to[k] - from[k] > limit));
+    }
+    for (int base = base0; base < nb; base += 64) {
         const int r = base + lane;
         const int cnt = r < nb ? row_ptr[r + 1] - row_ptr[r] : 0;
         if (base == 0) cnt_first = cnt;
         n_long += __popcll(__ballot(r < nb && cnt > limit));
     }
-    const bool want_long = l < heads * n_long;
+    const int longs = heads * n_long;
+    const bool want_long = l < longs;
     int head, rank;
     if (want_long) {
-        head = l % heads;
-        rank = l / heads;
+        if (DEAL) l = xcd_deal(l, 0, longs);
+        head = DEAL ? l / n_long : l % heads;
+        rank = DEAL ? l % n_long : l / heads;
     } else {
-        head = (l - heads * n_long) / (nb - n_long);
-        rank = (l - heads * n_long) % (nb - n_long);
+        l = DEAL ? xcd_deal(l, longs, heads * nb) : l - longs;
+        head = l / (nb - n_long);
+        rank = l % (nb - n_long);
     }
+    if (n_long == 0) return {rank, head};
     for (int base = 0; base < nb; base += 64) {   // the counts are in the cache by now
         const int r = base + lane;
         int cnt = cnt_first;

@@ -90,7 +90,7 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
         l -= hpx * n_key_a;
         key_side = false;
         if (sort_rows) {
-            const RowOfHead at = long_rows_first(row_ptr, nb, hpx, l, lane);
+            const RowOfHead at = long_rows_first<false>(row_ptr, nb, hpx, l, lane);
             bh = x * hpx + at.head;
             idx = at.row;
         } else {

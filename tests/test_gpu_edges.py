@@ -443,3 +443,26 @@ def test_buffers_larger_than_needed(sp):
     for args in ((q, small, v), (q, k, small)):
         with pytest.raises(ValueError):
             sp.attn_fwd(*args, pat)
+
+
+# Sorted rows (more workgroups than run at once: 1024 of block 64, 2048 of block 32) at head counts that do not divide
+# over the 8 XCDs, workgroup counts that do and do not, and no long row, one, and many.  A row's result does not depend
+# on where it runs: the same bits as one head at a time, which is not sorted.
+@pytest.mark.parametrize("BH,nb,block,long_rows", [(9, 130, 64, 0), (9, 130, 64, 1), (12, 96, 64, 3), (5, 206, 64, 20), (20, 130, 32, 7),
+                                                   (13, 161, 32, 1), (16, 130, 32, 5), (1030, 1, 64, 0), (1033, 2, 32, 1)])
+def test_forward_sorted_rows_at_odd_head_counts(sp, BH, nb, block, long_rows):
+    from test_gpu_parity import _pattern_from_mask
+    rng = np.random.default_rng(nb + BH)
+    fl = np.eye(nb, dtype=np.uint8)
+    fl[rng.integers(0, nb, nb), rng.integers(0, nb, nb)] = 1
+    fl[rng.choice(nb, long_rows, replace=False)] = 1
+    pat = _pattern_from_mask(sp, fl, block)
+    gen = torch.Generator(device="cuda").manual_seed(BH)
+    q, k, v = [torch.randn((1, BH, nb * block, 64), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3)]
+    O = torch.full_like(q, float("nan"))
+    LSE = torch.full(q.shape[:3], float("nan"), device="cuda")
+    sp.attn_fwd(q, k, v, pat, O=O, LSE=LSE)
+    for h in range(0, BH, max(1, BH // 24)):
+        o, lse = sp.attn_fwd(*[t[:, h:h + 1].contiguous() for t in (q, k, v)], pat)
+        assert torch.equal(O[:, h:h + 1], o) and torch.equal(LSE[:, h:h + 1], lse), h
+    assert not O.isnan().any() and not LSE.isnan().any()
