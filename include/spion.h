@@ -24,7 +24,7 @@
  *   - Tensors Q, K, V, O, dO, dQ, dK, dV are [B, H, L, d] contiguous (d fastest) in the element type
  *     named by `dtype`; LSE is fp32 [B, H, L].  Supported: d == 64, block in {16, 32, 64},
  *     L % block == 0, L / block <= SPION_MAX_NB, and B * H * (L / block) < 2^31 (one workgroup per
- *     block row and head; the backward also needs B * H * (nnzb / 16 + 2 L / block) < 2^31).  A shape
+ *     block row and head; the backward also needs B * H * (nnzb / 16 + 2 L / block) < 2^31, at block 64 2^30).  A shape
  *     outside these limits is SPION_ERR_SHAPE.
  *   - One pattern (one BSR/BSC index) is shared by all batch items and heads of a layer.
  */
@@ -110,9 +110,10 @@ int spion_pattern(const float *A_s, const spion_pattern_params *p, uint8_t *fl_o
 /*
  * spion_pattern for callers that cannot allocate device memory or carry a workspace: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, outputs and
- * results as spion_pattern without `workspace` / `workspace_bytes`: the scratch (per-block partial
- * sums, pooled sums, cell bits, transposed mask, positions) lives in a 5 MiB array that is part of the library's device
- * image, one copy per GPU, held until the process ends.  The call allocates and frees nothing.
+ * results as spion_pattern without `workspace` / `workspace_bytes`: the scratch (slot sums of the
+ * input blocks, pooled sums and, for larger grids, a histogram, line counts and rows of cell bits) lives in a 5 MiB
+ * array that is part of the library's device image, one copy per GPU, held until the process ends.  The call allocates
+ * and frees nothing.
  *   - L / block must not exceed SPION_STATIC_MAX_NB (256; e.g. L = 16384 at block 64), else
  *     SPION_ERR_TOO_LARGE is returned and nothing is enqueued.
  *   - The array's address is looked up on the first call on each device (the device current at the
@@ -140,11 +141,9 @@ int spion_index_check(const int32_t *row_ptr, const int32_t *col_idx, const int3
 
 /* spion_attn_params.flags */
 #define SPION_ATTN_PAPER_DENOM 1u /* add Algorithm 6's exp(-max) * (L - kept) term to the row sum */
-/* spion_attn_bwd only: run one of its two sides on its own (for per-side timing).  The bf16 kernels
- * for block 32 / 64 compute both sides in one launch and either side alone is self-contained; in the
- * other kernels the key side reads what the query side of an earlier call with the same arguments
- * and workspace left there (delta, the key-side work list). */
-#define SPION_ATTN_BWD_QUERY_SIDE_ONLY 2u /* delta and dQ only */
+/* spion_attn_bwd only: run one of its two sides on its own (for per-side timing).  Both sides run in one
+ * launch and share no data: either alone is self-contained. */
+#define SPION_ATTN_BWD_QUERY_SIDE_ONLY 2u /* dQ only */
 #define SPION_ATTN_BWD_KEY_SIDE_ONLY 4u   /* dK and dV only */
 
 typedef struct {

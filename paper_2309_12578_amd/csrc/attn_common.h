@@ -22,6 +22,8 @@ constexpr float kLn2 = 0.6931471805599453f;
 // error, the fp32 sums have range to spare), so what a row's maximum does inside this slack need not be
 // known: a lane looks at its own scores only, and the reduction over the lanes of a row, the rescaling and
 // the branch are left to the first block of a row and to scores that really run away.
+// The sums hold up to 2^kRescaleSlack times what they would against the row's maximum: |V| above about 1e29 can
+// overflow them.
 constexpr float kRescaleSlack = 30.f;
 
 // Per element type: a 16-byte lane fragment of EPL elements; four lane groups make a chunk of KC

@@ -872,9 +872,9 @@ __device__ __forceinline__ int grid_bin(long long v) {
     if (m != 0ull) {
         const int lz = __clzll((long long)m);
         const unsigned next5 = (unsigned)(((m << lz) << 1) >> 59);
-        idx = (63 - lz) * 32 + (int)next5 + 1;   // 1 .. 2048; 2048 is the most negative value alone
+        idx = (63 - lz) * 32 + (int)next5 + 1;   // 1 .. 2017, the last for 2^63 alone
     }
-    return v < 0 ? 2048 - idx : (idx < 2048 ? 2048 + idx : 4095);
+    return v < 0 ? 2048 - idx : 2048 + idx;
 }
 
 __global__ __launch_bounds__(256) void grid_zero_kernel(unsigned* __restrict__ zero) {

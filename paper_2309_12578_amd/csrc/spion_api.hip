@@ -11,8 +11,8 @@
 #include "spion_host.h"
 #include "spion_internal.h"
 
-// Built-in scratch of spion_pattern_static: the pattern workspace (pooled sums, cell bits, the
-// transposed mask, positions) for up to SPION_STATIC_MAX_NB^2 blocks.  Every GPU the library runs
+// Built-in scratch of spion_pattern_static: the pattern workspace (slot sums, pooled sums, histogram,
+// line counts, rows of cell bits) for up to SPION_STATIC_MAX_NB^2 blocks.  Every GPU the library runs
 // on holds its own copy of this array at its own address until the process ends.  In host code the
 // name is only a handle for hipGetSymbolAddress: kernels and copies are given the resolved address.
 constexpr size_t kStaticScratchBytes = 5u << 20;   // the workspace of L / block = SPION_STATIC_MAX_NB
