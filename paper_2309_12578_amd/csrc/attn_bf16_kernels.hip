@@ -41,11 +41,12 @@ __device__ __forceinline__ void stage_ready(bool younger_in_flight) {
     asm volatile("" ::: "memory");
 }
 
-template <int BS>
+template <int BS, bool BESIDE>
 __global__ __launch_bounds__(BS * 4) void attn_fwd_bf16_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     bf16_t* __restrict__ O, float* __restrict__ LSE, const int* __restrict__ row_ptr,
-    const int* __restrict__ col_idx, int L, int nb, int total, int sort_rows, float scale_log2, int paper_denom) {
+    const int* __restrict__ col_idx, HeadRows<BESIDE> at, int L, int nb, int total, int sort_rows, float scale_log2,
+    int paper_denom) {
     constexpr int NKT = BS / 16;
     __shared__ __attribute__((aligned(16))) KvSmem<BS> sm0, sm1;
 
@@ -53,28 +54,29 @@ __global__ __launch_bounds__(BS * 4) void attn_fwd_bf16_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int bh, I;
     if (sort_rows) {
-        const RowOfHead at = long_rows_first<true>(row_ptr, nb, total / nb, blockIdx.x, lane);
-        bh = at.head;
-        I = at.row;
+        const RowOfHead mine = long_rows_first<true>(row_ptr, nb, total / nb, blockIdx.x, lane);
+        bh = mine.head;
+        I = mine.row;
     } else {
         const int vid = xcd_remap(blockIdx.x, total);
         bh = vid / nb;
         I = vid % nb;
     }
-    const size_t head = (size_t)bh * L * kD;
+    const size_t head = at.in_head(bh, L);
+    const int row_len = at.in_row();
     const int qrow = I * BS + wave * 16 + r;
     const SwzLane sl(r, g);
-    const TileLoadLane tl(wave, lane);
+    const TileLoadLane tl(wave, lane, row_len);
 
     auto issue = [&](KvSmem<BS>& st, int J) {
-        tile_load_async(K + head + (size_t)J * BS * kD, st.k, wave, tl);
-        tile_load_async(V + head + (size_t)J * BS * kD, st.v, wave, tl);
+        tile_load_async(K + head + (size_t)J * BS * row_len, st.k, wave, tl);
+        tile_load_async(V + head + (size_t)J * BS * row_len, st.v, wave, tl);
     };
     issue(sm0, I);   // the diagonal block, before any index is known
     bf16x8 qf[2];
 #pragma unroll
     for (int c = 0; c < 2; ++c)
-        qf[c] = *reinterpret_cast<const bf16x8*>(Q + head + (size_t)qrow * kD + c * 32 + g * 8);
+        qf[c] = *reinterpret_cast<const bf16x8*>(Q + head + (size_t)qrow * row_len + c * 32 + g * 8);
     const int jb = row_ptr[I], n = row_ptr[I + 1] - jb;
     const int last = n > 0 ? n - 1 : 0;
     const int* cols = col_idx + jb;
@@ -199,7 +201,7 @@ __global__ __launch_bounds__(BS * 4) void attn_fwd_bf16_kernel(
     // the stage that the last block did not use is free: every wave is past the barrier that followed
     // its last reader, and the only load that ever targets this wave's 2 KB of it was the wave's own
     bf16_t* patch = ((n & 1) ? sm1.k : sm0.k) + wave * (16 * kD);
-    store_rows_coalesced(patch, O + head + (size_t)(I * BS + wave * 16) * kD, oacc, inv, lane);
+    store_rows_coalesced(patch, O + at.out_head(bh, L) + (size_t)(I * BS + wave * 16) * at.out_row(), at.out_row(), oacc, inv, lane);
     if (g == 0) LSE[(size_t)bh * L + qrow] = lsum > 0.f ? (m + log2f(lsum)) * kLn2 : -INFINITY;
 }
 
@@ -213,10 +215,14 @@ hipError_t fwd_bf16(const AttnShape& s, const void* Q, const void* K, const void
     // 4 (block 64) and at least 8 (block 32) workgroups fit a compute unit; where all run at once their order is
     // immaterial, and finding a row by its rank costs a workgroup half a microsecond
     const int sort_rows = total > 256 * (BS == 64 ? 4 : 8);
-    attn_fwd_bf16_kernel<BS><<<dim3((unsigned)total), dim3(BS * 4), 0, st>>>(
-        static_cast<const bf16_t*>(Q), static_cast<const bf16_t*>(K), static_cast<const bf16_t*>(V),
-        static_cast<bf16_t*>(O), LSE, row_ptr, col_idx, s.L, s.nb, total, sort_rows, s.scale * kLog2e,
-        s.paper_denom);
+    auto launch = [&](auto kernel, auto at) {
+        kernel<<<dim3((unsigned)total), dim3(BS * 4), 0, st>>>(
+            static_cast<const bf16_t*>(Q), static_cast<const bf16_t*>(K), static_cast<const bf16_t*>(V),
+            static_cast<bf16_t*>(O), LSE, row_ptr, col_idx, at, s.L, s.nb, total, sort_rows, s.scale * kLog2e,
+            s.paper_denom);
+    };
+    if (s.heads_beside) launch(attn_fwd_bf16_kernel<BS, true>, HeadRows<true>{s.heads_beside});
+    else launch(attn_fwd_bf16_kernel<BS, false>, HeadRows<false>{0});
     return hipGetLastError();
 }
 

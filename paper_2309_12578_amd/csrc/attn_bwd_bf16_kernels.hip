@@ -52,13 +52,13 @@ __device__ __forceinline__ void lds_barrier() {
 // block 32, 4.8 blocks a row: 31.6 -> 26.5 us; 4 and 12 measure like 8, and a sixth or a third of the columns like a
 // quarter).  With sort_rows the rows of more than twice the mean length come before the others.
 // ------------------------------------------------------------------------------------------------
-template <int BS>
+template <int BS, bool BESIDE>
 __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const bf16_t* __restrict__ O, const bf16_t* __restrict__ dO, const float* __restrict__ LSE,
     bf16_t* __restrict__ dQ, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV,
     const int* __restrict__ row_ptr, const int* __restrict__ col_idx, const int* __restrict__ col_ptr,
-    const int* __restrict__ row_idx, float* __restrict__ partial, int n_slots, int BH, int L, int nb,
+    const int* __restrict__ row_idx, float* __restrict__ partial, HeadRows<BESIDE> at, int n_slots, int BH, int L, int nb,
     int n_key_a, int n_rows, int n_key_c, int w_first, int chunk, int sort_rows, float scale, float scale_log2) {
     constexpr int NT = BS / 16;   // 16-row tiles per block = waves per workgroup
     // Separate objects, so that the compiler can tell a read of one tile from a load in flight into
@@ -71,7 +71,8 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const SwzLane sl(r, g);
-    const TileLoadLane tl(wave, lane);
+    const int in_row = at.in_row(), out_row = at.out_row();   // elements between rows of Q, K, V and of O, dO
+    const TileLoadLane tl(wave, lane, in_row);
 
     // which workgroup am I
     int x = 0, hpx = BH, l = blockIdx.x;
@@ -90,9 +91,9 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
         l -= hpx * n_key_a;
         key_side = false;
         if (sort_rows) {
-            const RowOfHead at = long_rows_first<false>(row_ptr, nb, hpx, l, lane);
-            bh = x * hpx + at.head;
-            idx = at.row;
+            const RowOfHead mine = long_rows_first<false>(row_ptr, nb, hpx, l, lane);
+            bh = x * hpx + mine.head;
+            idx = mine.row;
         } else {
             bh = x * hpx + l / nb;
             idx = l % nb;
@@ -103,7 +104,7 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
         bh = x * hpx + l % hpx;
         idx = w_first + l / hpx;
     }
-    const size_t head = (size_t)bh * L * kD;
+    const size_t head = at.in_head(bh, L), out_head = at.out_head(bh, L);
     const size_t vec = (size_t)bh * L;
 
     if (!key_side) {
@@ -114,17 +115,17 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
         const int I = idx;
         const int qrow = I * BS + wave * 16 + r;
         auto issue = [&](bf16_t* kt, bf16_t* vt, int J) {
-            tile_load_async(K + head + (size_t)J * BS * kD, kt, wave, tl);
-            tile_load_async(V + head + (size_t)J * BS * kD, vt, wave, tl);
+            tile_load_async(K + head + (size_t)J * BS * in_row, kt, wave, tl);
+            tile_load_async(V + head + (size_t)J * BS * in_row, vt, wave, tl);
         };
         issue(ta0, tb0, I);   // the diagonal block, before any index is known
         bf16x8 qf[2], dof[2], of[2];
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
-            const size_t off = head + (size_t)qrow * kD + c * 32 + g * 8;
-            qf[c] = *reinterpret_cast<const bf16x8*>(Q + off);
-            dof[c] = *reinterpret_cast<const bf16x8*>(dO + off);
-            of[c] = *reinterpret_cast<const bf16x8*>(O + off);
+            const size_t out = out_head + (size_t)qrow * out_row + c * 32 + g * 8;
+            qf[c] = *reinterpret_cast<const bf16x8*>(Q + head + (size_t)qrow * in_row + c * 32 + g * 8);
+            dof[c] = *reinterpret_cast<const bf16x8*>(dO + out);
+            of[c] = *reinterpret_cast<const bf16x8*>(O + out);
         }
         const float lse2 = LSE[vec + qrow] * kLog2e;
         const int jb = row_ptr[I], n = row_ptr[I + 1] - jb;
@@ -222,7 +223,7 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
         // the last block's stage can still be read; the wave's own 2 KB of any other tile were only ever
         // written by the wave's own loads, which have all landed.
         bf16_t* patch = (n % 3 == 1 ? ta1 : ta0) + wave * (16 * kD);   // last stage: (n - 1) % 3
-        store_rows_coalesced(patch, dQ + head + (size_t)(I * BS + wave * 16) * kD, dq, scale, lane);
+        store_rows_coalesced(patch, dQ + head + (size_t)(I * BS + wave * 16) * in_row, in_row, dq, scale, lane);
         return;
     }
 
@@ -241,11 +242,12 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
     const int rows_v = n > 0 ? row_idx[item.kb + (lane < last ? lane : last)] : 0;
     auto row_at = [&](int t) { return __builtin_amdgcn_readlane(rows_v, t < last ? t : last); };
 
+    const TileLoadLane tlo(wave, lane, out_row);
     // six tile loads per wave, plus one 4-byte-per-lane load of LSE in wave 0
     auto issue = [&](bf16_t* qt, bf16_t* dt_, bf16_t* ot, float* lse_s, int I) {
-        tile_load_async(Q + head + (size_t)I * BS * kD, qt, wave, tl);
-        tile_load_async(dO + head + (size_t)I * BS * kD, dt_, wave, tl);
-        tile_load_async(O + head + (size_t)I * BS * kD, ot, wave, tl);
+        tile_load_async(Q + head + (size_t)I * BS * in_row, qt, wave, tl);
+        tile_load_async(dO + out_head + (size_t)I * BS * out_row, dt_, wave, tlo);
+        tile_load_async(O + out_head + (size_t)I * BS * out_row, ot, wave, tlo);
         if (wave == 0 && lane < BS)
             __builtin_amdgcn_global_load_lds(LSE + vec + (size_t)I * BS + lane, (lds_void_ptr)lse_s, 4, 0, 0);
     };
@@ -258,7 +260,7 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
     bf16x8 kf[2], vf[2];
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-        const size_t off = head + (size_t)krow * kD + c * 32 + g * 8;
+        const size_t off = head + (size_t)krow * in_row + c * 32 + g * 8;
         kf[c] = *reinterpret_cast<const bf16x8*>(K + off);
         vf[c] = *reinterpret_cast<const bf16x8*>(V + off);
     }
@@ -359,9 +361,9 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
         const bool odd = (n & 1) != 0;   // last block in stage 0 -> stage 1 is free
         bf16_t* pa = (odd ? ta1 : ta0) + wave * (16 * kD);
         bf16_t* pb = (odd ? tb1 : tb0) + wave * (16 * kD);
-        const size_t row0 = head + (size_t)(J * BS + wave * 16) * kD;
-        store_rows_coalesced(pa, dK + row0, dk, scale, lane);
-        store_rows_coalesced(pb, dV + row0, dv, 1.f, lane);
+        const size_t row0 = head + (size_t)(J * BS + wave * 16) * in_row;
+        store_rows_coalesced(pa, dK + row0, in_row, dk, scale, lane);
+        store_rows_coalesced(pb, dV + row0, in_row, dv, 1.f, lane);
     } else {
         // fp32 partial tile of this chunk, unscaled: [head][slot][dK | dV][bs][64]
         float* pk = partial + ((size_t)bh * n_slots + slot) * (2 * BS * kD) + (size_t)(wave * 16 + r) * kD;
@@ -391,15 +393,21 @@ hipError_t bwd_bf16(const AttnShape& s, const void* Q, const void* K, const void
         // blocks) or can be against the steps a slot has to do: 16 heads x 8192, block 32, 12.8 blocks a row 130 -> 98 us,
         // 64 heads x 1024, 4.8 blocks a row 26.9 -> 28.3 us.
         const int sort_rows = total > bwd_resident(BS) && (ws.nnzb >= 6 * s.nb || s.nb >= 8 * bwd_steps_per_slot(s.BH, BS, s.nb, ws.nnzb));
-        attn_bwd_bf16_kernel<BS><<<dim3((unsigned)total), dim3(BS * 4), 0, st>>>(
-            static_cast<const bf16_t*>(Q), static_cast<const bf16_t*>(K), static_cast<const bf16_t*>(V),
-            static_cast<const bf16_t*>(O), static_cast<const bf16_t*>(dO), LSE, static_cast<bf16_t*>(dQ),
-            static_cast<bf16_t*>(dK), static_cast<bf16_t*>(dV), row_ptr, col_idx, col_ptr, row_idx, partial,
-            ws.n_slots, s.BH, s.L, s.nb, n_key_a, n_rows, n_key_c, ws.w_first, ws.chunk, sort_rows, s.scale, s.scale * kLog2e);
+        auto launch = [&](auto kernel, auto at) {
+            kernel<<<dim3((unsigned)total), dim3(BS * 4), 0, st>>>(
+                static_cast<const bf16_t*>(Q), static_cast<const bf16_t*>(K), static_cast<const bf16_t*>(V),
+                static_cast<const bf16_t*>(O), static_cast<const bf16_t*>(dO), LSE, static_cast<bf16_t*>(dQ),
+                static_cast<bf16_t*>(dK), static_cast<bf16_t*>(dV), row_ptr, col_idx, col_ptr, row_idx, partial, at,
+                ws.n_slots, s.BH, s.L, s.nb, n_key_a, n_rows, n_key_c, ws.w_first, ws.chunk, sort_rows, s.scale, s.scale * kLog2e);
+        };
+        if (s.heads_beside) launch(attn_bwd_bf16_kernel<BS, true>, HeadRows<true>{s.heads_beside});
+        else launch(attn_bwd_bf16_kernel<BS, false>, HeadRows<false>{0});
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    return keys ? launch_bwd_reduce<bf16_t, BS>(s, ws, partial, col_ptr, dK, dV, st) : hipSuccess;
+    if (!keys) return hipSuccess;
+    return s.heads_beside ? launch_bwd_reduce<bf16_t, BS, true>(s, ws, partial, col_ptr, dK, dV, st)
+                          : launch_bwd_reduce<bf16_t, BS, false>(s, ws, partial, col_ptr, dK, dV, st);
 }
 
 template hipError_t bwd_bf16<32>(const AttnShape&, const void*, const void*, const void*, const void*,

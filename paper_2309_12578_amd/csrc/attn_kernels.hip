@@ -28,6 +28,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "attn_bf16_tiles.h"
 #include "attn_common.h"
 #include "attn_key_items.h"
 #include "spion_internal.h"
@@ -628,7 +629,7 @@ static hipError_t launch_bwd(const AttnShape& s, const void* Q, const void* K, c
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    return keys ? launch_bwd_reduce<T, BS>(s, ws, partial, col_ptr, dK, dV, st) : hipSuccess;
+    return keys ? launch_bwd_reduce<T, BS, false>(s, ws, partial, col_ptr, dK, dV, st) : hipSuccess;
 }
 
 template <typename T, int BS>

@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "attn_bf16_tiles.h"
 #include "attn_common.h"
 #include "spion_internal.h"
 
@@ -136,10 +137,10 @@ __device__ __forceinline__ int4 split_column_lookup(const int* __restrict__ col_
 // Adds the partial tiles of every split block column, in chunk order.  Workgroup = (head, m-th split
 // column, part): 256 threads, one float4 of the output tile each, bs / 16 parts per tile, so that the
 // loads of all chunks of a float4 are in flight together.
-template <typename T, int BS>
+template <typename T, int BS, bool BESIDE>
 __global__ __launch_bounds__(256) void attn_bwd_reduce_kernel(
     const float* __restrict__ partial, const int* __restrict__ col_ptr, int nb, int chunk, int split_max, int n_slots,
-    T* __restrict__ dK, T* __restrict__ dV, int L, float scale) {
+    T* __restrict__ dK, T* __restrict__ dV, HeadRows<BESIDE> at, int L, float scale) {
     constexpr int PARTS = BS / 16;
     const int part = blockIdx.x % PARTS, m = (blockIdx.x / PARTS) % split_max;
     const int bh = blockIdx.x / (PARTS * split_max);
@@ -153,17 +154,19 @@ __global__ __launch_bounds__(256) void attn_bwd_reduce_kernel(
         ak += *reinterpret_cast<const f32x4*>(pk + (size_t)c * (2 * BS * kD));
         av += *reinterpret_cast<const f32x4*>(pk + (size_t)c * (2 * BS * kD) + BS * kD);
     }
-    const size_t out = (size_t)bh * L * kD + (size_t)info.x * BS * kD + v * 4;
+    const int row = info.x * BS + v / (kD / 4);
+    const size_t out = at.in_head(bh, L) + (size_t)row * at.in_row() + v % (kD / 4) * 4;
     store_quad<T>(dK + out, ak * scale);
     store_quad<T>(dV + out, av);
 }
 
-template <typename T, int BS>
+template <typename T, int BS, bool BESIDE>
 hipError_t launch_bwd_reduce(const AttnShape& s, const BwdWorkspace& ws, const float* partial,
                              const int* col_ptr, void* dK, void* dV, hipStream_t st) {
     if (ws.split_max == 0) return hipSuccess;
-    attn_bwd_reduce_kernel<T, BS><<<dim3((unsigned)(ws.split_max * s.BH * (BS / 16))), dim3(256), 0, st>>>(
-        partial, col_ptr, s.nb, ws.chunk, ws.split_max, ws.n_slots, static_cast<T*>(dK), static_cast<T*>(dV), s.L, s.scale);
+    attn_bwd_reduce_kernel<T, BS, BESIDE><<<dim3((unsigned)(ws.split_max * s.BH * (BS / 16))), dim3(256), 0, st>>>(
+        partial, col_ptr, s.nb, ws.chunk, ws.split_max, ws.n_slots, static_cast<T*>(dK), static_cast<T*>(dV),
+        HeadRows<BESIDE>{s.heads_beside}, s.L, s.scale);
     return hipGetLastError();
 }
 

@@ -152,7 +152,8 @@ __global__ __launch_bounds__(256) void weight_grad_sum_kernel(const float* __res
 }
 
 // Between the layout of the projections, [B, L, n, H, 64] (n = 3: Q | K | V, n = 1: the heads' outputs side by side),
-// and that of the attention, n tensors [B, H, L, 64].  Bound by HBM.  A wave moves 4 pieces of 1 KB that are
+// and that of the attention's kernels for fp32 and block 16, n tensors [B, H, L, 64] (the others read the projections'
+// layout, HeadRows).  Bound by HBM.  A wave moves 4 pieces of 1 KB that are
 // contiguous in the attention's layout (8 tokens of a head in bf16, 4 in fp32), rows of 128 or 256 bytes in the other.
 // 8 x 2048 tokens, 4 heads, bf16: 8.2 us for three tensors (50 MB, out of the caches in part), 4.7 us for one.  As
 // torch operators these were 8 copies of 8 us and, for the gradients of the three slices, as many fills of the whole

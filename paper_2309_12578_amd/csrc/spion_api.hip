@@ -116,7 +116,18 @@ spion::AttnShape make_shape(const spion_attn_params* p) {
     s.paper_denom = (p->flags & SPION_ATTN_PAPER_DENOM) ? 1 : 0;
     s.bwd_phases = (p->flags & SPION_ATTN_BWD_QUERY_SIDE_ONLY) ? 1
                    : (p->flags & SPION_ATTN_BWD_KEY_SIDE_ONLY) ? 2 : 3;
+    s.heads_beside = 0;
     return s;
+}
+
+// Whether the kernels take the sub-layer's own tensors (the addresses or'ed together).
+int heads_beside_ok(uintptr_t addresses, const spion_attn_params* p, int32_t nnzb) {
+    const int rc = attn_params_ok(p, nnzb);
+    if (rc != SPION_OK) return rc;
+    if (p->dtype != SPION_BF16) return SPION_ERR_DTYPE;
+    if (p->block != 32 && p->block != 64) return SPION_ERR_SHAPE;
+    if (p->H > 0x7fffffff / (3 * 64)) return SPION_ERR_SHAPE;
+    return addresses % 16 != 0 ? SPION_ERR_PARAM : SPION_OK;
 }
 
 }  // namespace
@@ -433,6 +444,37 @@ int spion_attn_bwd(const void* Q, const void* K, const void* V, const void* O, c
                                nnzb, workspace, static_cast<hipStream_t>(hip_stream)) != hipSuccess)
         return SPION_ERR_HIP;
     return SPION_OK;
+}
+
+int spion_heads_attn_fwd(const void* qkv, void* S, float* LSE, const int32_t* row_ptr, const int32_t* col_idx, int32_t nnzb,
+                         const spion_attn_params* p, void* hip_stream) {
+    if (!qkv || !S || !LSE || !row_ptr || !col_idx || !p) return SPION_ERR_NULL;
+    const int rc = heads_beside_ok((uintptr_t)qkv | (uintptr_t)S, p, nnzb);
+    if (rc != SPION_OK) return rc;
+    spion::AttnShape s = make_shape(p);
+    s.heads_beside = p->H;
+    const uint16_t* const q = static_cast<const uint16_t*>(qkv);
+    const size_t D = (size_t)p->H * 64;
+    return spion::launch_attn_fwd(s, q, q + D, q + 2 * D, S, LSE, row_ptr, col_idx, nnzb,
+                                  static_cast<hipStream_t>(hip_stream)) == hipSuccess ? SPION_OK : SPION_ERR_HIP;
+}
+
+int spion_heads_attn_bwd(const void* qkv, const void* S, const void* dS, const float* LSE, void* dqkv, const int32_t* row_ptr,
+                         const int32_t* col_idx, const int32_t* col_ptr, const int32_t* row_idx, int32_t nnzb,
+                         const spion_attn_params* p, void* workspace, size_t workspace_bytes, void* hip_stream) {
+    if (!qkv || !S || !dS || !LSE || !dqkv || !row_ptr || !col_idx || !col_ptr || !row_idx || !p) return SPION_ERR_NULL;
+    const int rc = heads_beside_ok((uintptr_t)qkv | (uintptr_t)S | (uintptr_t)dS | (uintptr_t)dqkv, p, nnzb);
+    if (rc != SPION_OK) return rc;
+    if (!spion::attn_bwd_grids_fit(p->B * p->H, p->block, p->L / p->block, nnzb)) return SPION_ERR_SHAPE;
+    if (!workspace || ((uintptr_t)workspace % kAlign) != 0 || workspace_bytes < spion_attn_workspace_bytes(p, nnzb, 1))
+        return SPION_ERR_WORKSPACE;
+    spion::AttnShape s = make_shape(p);
+    s.heads_beside = p->H;
+    const uint16_t* const q = static_cast<const uint16_t*>(qkv);
+    uint16_t* const d = static_cast<uint16_t*>(dqkv);
+    const size_t D = (size_t)p->H * 64;
+    return spion::launch_attn_bwd(s, q, q + D, q + 2 * D, S, dS, LSE, d, d + D, d + 2 * D, row_ptr, col_idx, col_ptr, row_idx,
+                                  nnzb, workspace, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? SPION_OK : SPION_ERR_HIP;
 }
 
 }  // extern "C"

@@ -38,6 +38,7 @@ struct AttnShape {
     float scale;        // resolved score scale (> 0)
     int paper_denom;    // Algorithm 6's extra denominator term
     int bwd_phases;     // bit 0: query side (dQ); bit 1: key side (dK, dV)
+    int heads_beside;   // 0: tensors [B, H, L, 64]; else H, and rows as HeadRows<true> (bf16, block 32 and 64 only)
 };
 
 hipError_t launch_attn_fwd(const AttnShape& s, const void* Q, const void* K, const void* V, void* O,

@@ -59,7 +59,7 @@ class SparseMHA(nn.Module):
         qkv = self.w_qkv(X)
         S = None
         if qkv.is_cuda and not torch.compiler.is_compiling():
-            # head split, lines 4-7, heads side by side again: two kernels beside the attention's
+            # lines 4-7 for every head, on the heads as they lie in qkv
             S = (_b._host or _b._native()).heads_attention(
                 qkv, self.heads, pattern.row_ptr, pattern.col_idx, pattern.col_ptr, pattern.row_idx, pattern.bsr_pos,
                 pattern.nnzb, pattern.block, flags)

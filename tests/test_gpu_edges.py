@@ -279,6 +279,34 @@ def test_sublayer_fused_and_step_by_step(sp, dtype, B, H, nb, block):
         assert torch.equal(mha(E, pat), steps)
 
 
+# One block; odd heads and batches; columns of 40 rows, which are cut and added up (chunks of 16); 8 heads, which are dealt
+# over the XCDs, with enough rows to be sorted by length; a row without a diagonal block and an empty one
+@pytest.mark.parametrize("B,H,nb,block", [(1, 1, 1, 32), (3, 5, 4, 64), (1, 3, 40, 32), (2, 1, 40, 64), (8, 8, 34, 32), (4, 8, 34, 64)])
+@pytest.mark.parametrize("denom", [False, True])
+def test_heads_where_the_projections_have_them(sp, B, H, nb, block, denom):
+    """The attention on [B, L, 3, H, 64] gives the bits of the attention on three tensors [B, H, L, 64]."""
+    from test_gpu_parity import _pattern_from_mask
+    fl = np.tril(np.ones((nb, nb), dtype=np.uint8)) if nb < 34 or H < 8 else np.eye(nb, dtype=np.uint8)
+    fl[nb // 2, :] = 1
+    if nb > 4:
+        fl[2, 2] = 0
+        fl[3, :] = 0
+    pat = _pattern_from_mask(sp, fl, block)
+    flags = sp.SPION_ATTN_PAPER_DENOM if denom else 0
+    L = nb * block
+    gen = torch.Generator(device="cuda").manual_seed(nb)
+    qkv = torch.randn((B, L, 3, H, 64), generator=gen, device="cuda").to(torch.bfloat16).view(B, L, 3 * H * 64).requires_grad_(True)
+    dS = torch.randn((B, L, H * 64), generator=gen, device="cuda").to(torch.bfloat16)
+    S = sp.binding._host.heads_attention(qkv, H, pat.row_ptr, pat.col_idx, pat.col_ptr, pat.row_idx, pat.bsr_pos, pat.nnzb, block, flags)
+    got, = torch.autograd.grad(S, qkv, dS)
+    q, k, v = [t.transpose(1, 2).contiguous() for t in qkv.detach().view(B, L, 3, H, 64).unbind(2)]
+    O, LSE = sp.attn_fwd(q, k, v, pat, flags=flags)
+    dO = dS.view(B, L, H, 64).transpose(1, 2).contiguous()
+    want = torch.stack([t.transpose(1, 2) for t in sp.attn_bwd(q, k, v, O, dO, LSE, pat, flags=flags)], 2)
+    assert torch.equal(S.view(B, L, H, 64).transpose(1, 2), O)
+    assert torch.equal(got.view(B, L, 3, H, 64), want)
+
+
 # Rows of 256, 512, 1024 and 2048 columns in registers and less; 4 rows a workgroup, 16 rows a partial of the weight's
 # and bias' gradients, 512 partials at most; a width that is not a multiple of 64 is torch's
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
