@@ -533,7 +533,8 @@ PyObject* py_heads_attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
     });
 }
 
-// The gradient of layer_norm, all three in one pass over X and dY; torch's operator where more than numbers is wanted.
+// The gradient of layer_norm, all three in one pass over X and dY; torch's operator where more than numbers is wanted.  A
+// second incoming gradient is that of a residual from X (see residual), whose sum with dX the same pass writes.
 struct NormBackward : public torch::autograd::Node {
     torch::autograd::SavedVariable x, w, b, mean, rstd;
 
@@ -545,7 +546,11 @@ struct NormBackward : public torch::autograd::Node {
 
     torch::autograd::variable_list apply(torch::autograd::variable_list&& grads) override {
         torch::autograd::variable_list out(3);
-        if (!grads[0].defined()) return out;
+        const at::Tensor dr = grads.size() > 1 ? grads[1] : at::Tensor();
+        if (!grads[0].defined()) {
+            out[0] = dr;
+            return out;
+        }
         const at::Tensor X = x.unpack(), W = w.unpack(), m = mean.unpack(), r = rstd.unpack();
         const int64_t D = W.size(0);
         const at::Tensor g = grads[0].contiguous();
@@ -555,16 +560,20 @@ struct NormBackward : public torch::autograd::Node {
             std::tie(out[0], out[1], out[2]) = at::native_layer_norm_backward(
                 g, X, {D}, m.view(stat), r.view(stat), W, b.unpack(),
                 {task_should_compute_output(0), task_should_compute_output(1), task_should_compute_output(2)});
+            if (dr.defined()) out[0] = out[0] + dr;
             return out;
         }
+        const bool add = dr.defined() && plain(dr) && dr.scalar_type() == X.scalar_type() && dr.is_contiguous() &&
+                         dr.sizes() == X.sizes() && (uintptr_t)dr.data_ptr() % 16 == 0;
         const int rows = (int)(X.numel() / D);
         for (at::Tensor* t : {&out[0], &out[1], &out[2]}) *t = new_like(t == &out[0] ? X : W);
         const at::Tensor ws = new_bytes(spion_layer_norm_workspace_bytes(rows, (int)D), X);
-        const int rc = spion_layer_norm_grad(g.data_ptr(), X.data_ptr(), W.data_ptr(), m.data_ptr<float>(), r.data_ptr<float>(),
+        const int rc = spion_layer_norm_grad(g.data_ptr(), add ? dr.data_ptr() : nullptr, X.data_ptr(), W.data_ptr(), m.data_ptr<float>(), r.data_ptr<float>(),
                                              out[0].data_ptr(), out[1].data_ptr(), out[2].data_ptr(), rows, (int)D,
                                              X.scalar_type() == at::kFloat ? SPION_F32 : SPION_BF16, ws.data_ptr(),
                                              (size_t)ws.nbytes(), current_stream());
         TORCH_CHECK(rc == SPION_OK, "spion_layer_norm_grad: ", spion_strerror(rc));
+        if (dr.defined() && !add) out[0] = out[0] + dr;
         for (int i = 0; i < 3; ++i)
             if (!task_should_compute_output(i)) out[i].reset();
         return out;
@@ -604,6 +613,30 @@ PyObject* py_layer_norm(PyObject*, PyObject* const* a, Py_ssize_t n) {
             torch::autograd::set_history(y, node);
         }
         return wrap(y);
+    });
+}
+
+// residual(X, Y) -> X for a residual around Y = layer_norm(X): an alias whose gradient goes to Y's node, which adds it to
+// its own, instead of an addition after it; X itself where Y did not come from that node alone.
+PyObject* py_residual(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    if (!arg_count(n, 2, "residual")) return nullptr;
+    return guarded([&]() -> PyObject* {
+        auto as_it_is = [&]() {
+            Py_INCREF(a[0]);
+            return a[0];
+        };
+        if (!nothing_between() || !plain(a[0]) || !plain(a[1]) || !at::GradMode::is_enabled()) return as_it_is();
+        const at::Tensor &x = THPVariable_Unpack(a[0]), &y = THPVariable_Unpack(a[1]);
+        if (!x.requires_grad() || !y.grad_fn()) return as_it_is();
+        const auto node = std::dynamic_pointer_cast<NormBackward>(y.grad_fn());
+        if (!node || node->num_inputs() != 1 || node->next_edge(0) != torch::autograd::impl::gradient_edge(x)) return as_it_is();
+        at::Tensor r;
+        {
+            at::NoGradGuard no_grad;
+            r = x.detach();
+        }
+        torch::autograd::set_history(r, node);
+        return wrap(r);
     });
 }
 
@@ -686,6 +719,7 @@ PyMethodDef kMethods[] = {
     {"sparse_attention", (PyCFunction)(void*)py_sparse_attention, METH_FASTCALL, nullptr},
     {"heads_attention", (PyCFunction)(void*)py_heads_attention, METH_FASTCALL, nullptr},
     {"layer_norm", (PyCFunction)(void*)py_layer_norm, METH_FASTCALL, nullptr},
+    {"residual", (PyCFunction)(void*)py_residual, METH_FASTCALL, nullptr},
     {"projection", (PyCFunction)(void*)py_projection, METH_FASTCALL, nullptr},
     {"generate_pattern", (PyCFunction)(void*)py_generate_pattern, METH_FASTCALL, nullptr},
     {"set_error_class", py_set_error_class, METH_O, nullptr},

@@ -324,15 +324,15 @@ size_t spion_layer_norm_workspace_bytes(int32_t rows, int32_t D) {
     return layer_norm_args_ok(0, rows, D, SPION_F32) == SPION_OK ? align_up(spion::layer_norm_workspace_bytes(rows, D)) : (size_t)-1;
 }
 
-int spion_layer_norm_grad(const void* dy, const void* x, const void* w, const float* mean, const float* rstd, void* dx,
-                          void* dw, void* db, int32_t rows, int32_t D, int32_t dtype, void* workspace,
+int spion_layer_norm_grad(const void* dy, const void* dr, const void* x, const void* w, const float* mean, const float* rstd,
+                          void* dx, void* dw, void* db, int32_t rows, int32_t D, int32_t dtype, void* workspace,
                           size_t workspace_bytes, void* hip_stream) {
     if (!dy || !x || !w || !mean || !rstd || !dx || !dw || !db) return SPION_ERR_NULL;
-    const int rc = layer_norm_args_ok((uintptr_t)dy | (uintptr_t)x | (uintptr_t)w | (uintptr_t)dx, rows, D, dtype);
+    const int rc = layer_norm_args_ok((uintptr_t)dy | (uintptr_t)dr | (uintptr_t)x | (uintptr_t)w | (uintptr_t)dx, rows, D, dtype);
     if (rc != SPION_OK) return rc;
     if (!workspace || ((uintptr_t)workspace % 16) != 0 || workspace_bytes < spion_layer_norm_workspace_bytes(rows, D))
         return SPION_ERR_WORKSPACE;
-    return spion::launch_layer_norm_grad(dy, x, w, mean, rstd, dx, dw, db, static_cast<float*>(workspace), rows, D,
+    return spion::launch_layer_norm_grad(dy, dr, x, w, mean, rstd, dx, dw, db, static_cast<float*>(workspace), rows, D,
                                          dtype == SPION_BF16, static_cast<hipStream_t>(hip_stream)) == hipSuccess
                ? SPION_OK : SPION_ERR_HIP;
 }

@@ -26,8 +26,9 @@ int spion_weight_grad(const void* dY, const void* X, void* dW, int32_t rows, int
 int spion_layer_norm(const void* x, const void* w, const void* b, void* y, float* mean, float* rstd, int32_t rows, int32_t D,
                      float eps, int32_t dtype, void* hip_stream);
 size_t spion_layer_norm_workspace_bytes(int32_t rows, int32_t D);
-int spion_layer_norm_grad(const void* dy, const void* x, const void* w, const float* mean, const float* rstd, void* dx,
-                          void* dw, void* db, int32_t rows, int32_t D, int32_t dtype, void* workspace,
+// dr: added to dx (the gradient of a residual that leaves from x), or NULL.
+int spion_layer_norm_grad(const void* dy, const void* dr, const void* x, const void* w, const float* mean, const float* rstd,
+                          void* dx, void* dw, void* db, int32_t rows, int32_t D, int32_t dtype, void* workspace,
                           size_t workspace_bytes, void* hip_stream);
 
 // Head split (split != 0) or merge: merged [B, L, n, H, 64] <-> tensors t[0 .. n - 1] [B, H, L, 64], n = 1 or 3, fp32 or

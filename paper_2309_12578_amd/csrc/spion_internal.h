@@ -66,8 +66,8 @@ bool attn_bwd_grids_fit(int BH, int bs, int nb, int nnzb);
 size_t layer_norm_workspace_bytes(int rows, int D);
 hipError_t launch_layer_norm(const void* x, const void* w, const void* b, void* y, float* mean, float* rstd, int rows,
                              int D, float eps, bool is_bf16, hipStream_t st);
-hipError_t launch_layer_norm_grad(const void* dy, const void* x, const void* w, const float* mean, const float* rstd, void* dx,
-                                  void* dw, void* db, float* partial, int rows, int D, bool is_bf16, hipStream_t st);
+hipError_t launch_layer_norm_grad(const void* dy, const void* dr, const void* x, const void* w, const float* mean,
+                                  const float* rstd, void* dx, void* dw, void* db, float* partial, int rows, int D, bool is_bf16, hipStream_t st);
 
 // projection_kernels.hip: dW [N, M] = dY^T X over `rows` rows, bf16, N and M multiples of 8
 size_t weight_grad_workspace_bytes(int rows, int N, int M);

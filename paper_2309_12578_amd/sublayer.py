@@ -57,8 +57,9 @@ class SparseMHA(nn.Module):
         B, L, D = E.shape
         X = self.norm(E)
         qkv = self.w_qkv(X)
-        S = None
+        S, R = None, E
         if qkv.is_cuda and not torch.compiler.is_compiling():
+            R = (_b._host or _b._native()).residual(E, X)   # E, its gradient added up in LayerNorm's pass
             # lines 4-7 for every head, on the heads as they lie in qkv
             S = (_b._host or _b._native()).heads_attention(
                 qkv, self.heads, pattern.row_ptr, pattern.col_idx, pattern.col_ptr, pattern.row_idx, pattern.bsr_pos,
@@ -69,4 +70,4 @@ class SparseMHA(nn.Module):
             Q, K, V = [qkv[:, :, i].transpose(1, 2).contiguous() for i in range(3)]
             S = sparse_attention(Q, K, V, pattern, flags=flags)               # lines 4-7, all heads at once
             S = S.transpose(1, 2).reshape(B, L, D)                            # concatenate the heads
-        return self.drop(self.w_o(S)) + E
+        return self.drop(self.w_o(S)) + R

@@ -334,6 +334,37 @@ def test_layer_norm(sp, dtype, rows, D):
         assert g.dtype == dtype and (g.double() - r).norm() <= tol * r.norm()
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("rows,D", [(1, 64), (129, 320), (9000, 512), (40, 1024), (16, 2048)])
+def test_residual_around_layer_norm(sp, dtype, rows, D):
+    """The gradient of a residual added in LayerNorm's pass; strided, alone, twice and differentiable gradients as without it."""
+    from paper_2309_12578_amd.sublayer import _Norm
+    gen = torch.Generator(device="cuda").manual_seed(rows + D)
+    norm = _Norm(D, device="cuda", dtype=dtype)
+    x, dy, dr = [torch.randn((2, rows, D), generator=gen, device="cuda").to(dtype) for _ in range(3)]
+    x.requires_grad_(True)
+    y = norm(x)
+    r = sp.binding._host.residual(x, y)
+    assert r is not x and r.data_ptr() == x.data_ptr() and r.grad_fn is y.grad_fn
+    assert sp.binding._host.residual(x, y) is x and sp.binding._host.residual(x, y + 1) is x and sp.binding._host.residual(x[:1], y) is not r
+    params = [x, *norm.parameters()]
+    x64, w64, b64 = [t.detach().double().requires_grad_(True) for t in params]
+    y64 = torch.nn.functional.layer_norm(x64, (D,), w64, b64, norm.eps)
+    want = torch.autograd.grad([y64, x64 * 1], [x64, w64, b64], [dy.double(), dr.double()])
+    tol = 1e-5 if dtype == torch.float32 else 2.0 ** -8   # one rounding of the sum, as in test_layer_norm
+    strided = torch.stack([dr, dr], 3)[..., 0]   # added by torch, a rounding more
+    for d, t in ((dr, tol), (strided, 2 * tol)):
+        got = torch.autograd.grad([y, r], params, [dy, d], retain_graph=True)
+        for g, w in zip(got, want):
+            assert g.dtype == dtype and (g.double() - w).norm() <= t * w.norm()
+    alone, = torch.autograd.grad(r, x, dr, retain_graph=True)
+    assert torch.equal(alone, dr)
+    with_graph, = torch.autograd.grad([y, r], x, [dy, dr], create_graph=True)
+    assert with_graph.requires_grad and (with_graph.double() - want[0]).norm() <= 2 * tol * want[0].norm()
+    with torch.no_grad():
+        assert sp.binding._host.residual(x, norm(x)) is x
+
+
 def test_layer_norm_beside_the_other_transforms(sp):
     from paper_2309_12578_amd.sublayer import _Norm
     norm, plain = _Norm(128, device="cuda"), torch.nn.LayerNorm(128, device="cuda")
