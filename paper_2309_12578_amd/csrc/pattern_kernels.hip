@@ -828,20 +828,20 @@ __global__ __launch_bounds__(kFinishThreads) void pattern_finish_kernel(
 //              1 the fill (the expanded cells of every row): neither needs the other
 //   words      grid_words_kernel: kept bits per row and, transposed, per column, and their counts
 //   index      grid_index_kernel: BSR and BSC
-// Measured at nb = 512: the five kernels take 9 + 9 + 29 + 13 + 9 us (one workgroup with a barrier per
+// Measured at nb = 512: the five kernels take 10 + 8 + 29 + 5 + 4 us (one workgroup with a barrier per
 // anti-diagonal took 2454); the longest part is the serial one, its threshold and its fill about alike.
 constexpr int kGridBins = 4096;
 constexpr int kGridMax = 1024;   // same bound as SPION_MAX_NB of the public header
 
 struct GridScratch {
-    unsigned* hist;              // kGridBins + 4 (counter of the candidates, rank inside the bin), then
-    int* row_cnt;                // kGridMax
-    int* col_cnt;                // kGridMax: one zeroed run of words with hist
+    unsigned* hist;              // kGridBins + 4 (counter of the candidates, rank inside the bin), zeroed
     Thresh* th;
-    unsigned long long* cand;    // nb * nb keys (over the slot sums, which are used up by then)
+    unsigned long long* cand;    // nb * nb keys (over the slot sums, which are used up by then), behind them
+    uint4 *row_cnt, *col_cnt;    // nb lines: kept cells of each word, a byte a word
     unsigned long long *down, *right, *diag, *reached, *kept, *kept_t;   // nb * W words each
 };
-constexpr int kGridZeroWords = kGridBins + 4 + 2 * kGridMax;
+constexpr int kGridZeroWords = kGridBins + 4;
+static_assert(kGridMax / 64 <= (int)sizeof(uint4), "a byte for every word of a line");
 
 static size_t grid_aux_bytes(size_t nb) {
     const size_t words = nb * ((nb + 63) / 64);
@@ -851,8 +851,6 @@ static GridScratch grid_carve(char* aux, void* part, size_t nb) {
     const size_t words = nb * ((nb + 63) / 64);
     GridScratch s;
     s.hist = reinterpret_cast<unsigned*>(aux);
-    s.row_cnt = reinterpret_cast<int*>(s.hist + kGridBins + 4);
-    s.col_cnt = s.row_cnt + kGridMax;
     char* p = aux + (kGridZeroWords * 4 + 255) / 256 * 256;
     s.th = reinterpret_cast<Thresh*>(p);
     s.down = reinterpret_cast<unsigned long long*>(p + 256);
@@ -862,6 +860,8 @@ static GridScratch grid_carve(char* aux, void* part, size_t nb) {
     s.kept = s.reached + words;
     s.kept_t = s.kept + words;
     s.cand = static_cast<unsigned long long*>(part);
+    s.row_cnt = reinterpret_cast<uint4*>(s.cand + (nb * nb + 1) / 2 * 2);   // 32 nb bytes, of 48 nb^2 that are left
+    s.col_cnt = s.row_cnt + nb;
     return s;
 }
 
@@ -1213,63 +1213,77 @@ __global__ __launch_bounds__(kFinishThreads) void grid_serial_kernel(const long 
     if (tid == 0) *s.th = t;
 }
 
-// One workgroup per 64 x 64 tile of cells: wave w its rows 16 w .. 16 w + 15, one ballot each; the 64 words,
-// transposed by 64 more ballots, are 64 column words.
-__global__ __launch_bounds__(256) void grid_words_kernel(const long long* __restrict__ pool, int nb, int no_fill,
-                                                         GridScratch s, uint8_t* __restrict__ fl) {
+// One workgroup per 64 x 64 tile of cells: wave w its rows 4 w .. 4 w + 3, one ballot each; the 64 words,
+// transposed by 64 more ballots, are 64 column words.  How many cells a word keeps is stored as a byte beside those of
+// the line's other words: counters per line that the workgroups add to are lines of memory that pass from one XCD's L2
+// to the next with every addition (12.5 us at any size; 8.2 with a byte a word, 4.8 with
+// four rows a wave instead of sixteen: a wave alone issues an instruction every 6 cycles).
+__global__ __launch_bounds__(1024) void grid_words_kernel(const long long* __restrict__ pool, int nb, int no_fill,
+                                                          GridScratch s, uint8_t* __restrict__ fl) {
     __shared__ unsigned long long tile[64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int W = (nb + 63) >> 6, rs = blockIdx.x / W, cs = blockIdx.x % W;
     const int c = cs * 64 + lane;
     const Thresh t = *s.th;
-    long long v[16];
-    unsigned long long reached16 = 0ull;   // lane j: the word of this wave's row j
-    const int r_first = rs * 64 + wave * 16;
-    if (lane < 16 && r_first + lane < nb) {
+    constexpr int kRows = 4;
+    long long v[kRows];
+    unsigned long long reached_w = 0ull;   // lane j: the word of this wave's row j
+    const int r_first = rs * 64 + wave * kRows;
+    if (lane < kRows && r_first + lane < nb) {
         // a seed is not reached by being one: row 0 is from its left neighbours, column 0 from above
         const int r = r_first + lane;
-        reached16 = s.reached[r * W + cs];
+        reached_w = s.reached[r * W + cs];
         if (!no_fill && r == 0)
-            reached16 = s.right[cs] << 1 | (cs > 0 ? s.right[cs - 1] >> 63 : 0ull);
+            reached_w = s.right[cs] << 1 | (cs > 0 ? s.right[cs - 1] >> 63 : 0ull);
         else if (!no_fill && cs == 0)
-            reached16 = (reached16 & ~1ull) | (s.down[(r - 1) * W] & 1ull);
+            reached_w = (reached_w & ~1ull) | (s.down[(r - 1) * W] & 1ull);
     }
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
+    for (int j = 0; j < kRows; ++j) {
         const int r = r_first + j;
         v[j] = pool[r < nb && c < nb ? r * nb + c : 0];
     }
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        const int r = rs * 64 + wave * 16 + j;
+    for (int j = 0; j < kRows; ++j) {
+        const int r = rs * 64 + wave * kRows + j;
         unsigned long long f = 0ull;
         if (r < nb) {   // wave-uniform
             const bool ab = c < nb && above(v[j], t);
-            f = __ballot(ab) & read_lane_u64(reached16, j);
+            f = __ballot(ab) & read_lane_u64(reached_w, j);
             if (r >> 6 == cs) f |= 1ull << (r & 63);
             if (c < nb) fl[(size_t)r * nb + c] = (uint8_t)((f >> lane) & 1ull);
             if (lane == 0) {
                 s.kept[r * W + cs] = f;
-                if (f) atomicAdd(&s.row_cnt[r], __popcll(f));
+                reinterpret_cast<uint8_t*>(s.row_cnt + r)[cs] = (uint8_t)__popcll(f);
             }
         }
-        if (lane == 0) tile[wave * 16 + j] = f;
+        if (lane == 0) tile[wave * kRows + j] = f;
     }
     __syncthreads();
     const unsigned long long rw = tile[lane];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        const int cc = cs * 64 + wave * 16 + j;
-        const unsigned long long m = __ballot(((rw >> (wave * 16 + j)) & 1ull) != 0ull);
+    for (int j = 0; j < kRows; ++j) {
+        const int cc = cs * 64 + wave * kRows + j;
+        const unsigned long long m = __ballot(((rw >> (wave * kRows + j)) & 1ull) != 0ull);
         if (lane == 0 && cc < nb) {
             s.kept_t[cc * W + rs] = m;
-            if (m) atomicAdd(&s.col_cnt[cc], __popcll(m));
+            reinterpret_cast<uint8_t*>(s.col_cnt + cc)[rs] = (uint8_t)__popcll(m);
         }
     }
 }
 
-// One wave per row (BSR) and, behind them, one per column (BSC).  A wave adds up the counts of the lines
-// before its own.
+// Sum of the first n bytes (n uniform).
+__device__ __forceinline__ int sum_bytes(uint4 v, int n) {
+    auto first = [n](unsigned w, int k) { return n >= 4 * k + 4 ? w : n <= 4 * k ? 0u : w & ((1u << (8 * (n - 4 * k))) - 1u); };
+    const unsigned lo = __builtin_amdgcn_sad_u8(first(v.y, 1), 0u, __builtin_amdgcn_sad_u8(first(v.x, 0), 0u, 0u));
+    return (int)__builtin_amdgcn_sad_u8(first(v.w, 3), 0u, __builtin_amdgcn_sad_u8(first(v.z, 2), 0u, lo));
+}
+
+// One wave per row (BSR) and, behind them, one per column (BSC).  A wave adds up the counts of the lines before its own;
+// where the row-wise index holds a cell of a column follows from its row's start, the counts of the words before the
+// cell's and that word.  Bound by latency: everything a wave needs is requested at once (at nb = 512, the words before a
+// cell's one after the other: 9.5 us, 4.4 so).
+template <int GROUPS>   // groups of 64 lines, at least W
 __global__ __launch_bounds__(256) void grid_index_kernel(int nb, GridScratch s, int* __restrict__ row_ptr,
                                                          int* __restrict__ col_idx, int* __restrict__ col_ptr,
                                                          int* __restrict__ row_idx, int* __restrict__ bsr_pos,
@@ -1279,22 +1293,23 @@ __global__ __launch_bounds__(256) void grid_index_kernel(int nb, GridScratch s, 
     const int W = (nb + 63) >> 6;
     if (w >= (col_ptr ? 2 * nb : nb)) return;
     const bool cols = w >= nb;
-    const int line = cols ? w - nb : w;
-    const int* const cnt = cols ? s.col_cnt : s.row_cnt;
-    // everything the wave needs is requested at once: the counts (16 groups of 64 lines at most), its words
-    constexpr int kGroups = kGridMax / 64;
-    int c16[kGroups], rc16[kGroups], before = 0;
+    const int line = cols ? w - nb : w, word = line >> 6;
+    const uint4* const cnt = cols ? s.col_cnt : s.row_cnt;
+    uint4 before[GROUPS], rows[GROUPS];
+    unsigned long long cell[GROUPS];   // columns: the word of row 64 q + lane that holds the cell
 #pragma unroll
-    for (int q = 0; q < kGroups; ++q) {
+    for (int q = 0; q < GROUPS; ++q) {
         const int i = q * 64 + lane;
-        c16[q] = q < W && i < line ? cnt[i] : 0;
-        rc16[q] = cols && q < W && i < nb ? s.row_cnt[i] : 0;
+        before[q] = i < line ? cnt[i] : make_uint4(0u, 0u, 0u, 0u);
+        rows[q] = cols && i < nb ? s.row_cnt[i] : make_uint4(0u, 0u, 0u, 0u);
+        cell[q] = cols && i < nb ? s.kept[(size_t)i * W + word] : 0ull;
     }
     const unsigned long long words = lane < W ? (cols ? s.kept_t : s.kept)[line * W + lane] : 0ull;
-    const int own = cnt[line];
+    const int own = sum_bytes(cnt[line], W);
+    int sum = 0;
 #pragma unroll
-    for (int q = 0; q < kGroups; ++q) before += c16[q];
-    int k = __builtin_amdgcn_readlane(wave_inclusive_scan_dpp(before), 63);
+    for (int q = 0; q < GROUPS; ++q) sum += sum_bytes(before[q], W);
+    int k = __builtin_amdgcn_readlane(wave_inclusive_scan_dpp(sum), 63);
     int* const ptr = cols ? col_ptr : row_ptr;
     if (lane == 0) {
         ptr[line] = k;
@@ -1307,9 +1322,9 @@ __global__ __launch_bounds__(256) void grid_index_kernel(int nb, GridScratch s, 
             }
         }
     }
-    int run = 0;   // rows before this group of 64 (columns only)
+    int run = 0;   // kept cells of the rows before this group of 64 (columns only)
 #pragma unroll
-    for (int seg = 0; seg < kGroups; ++seg) {
+    for (int seg = 0; seg < GROUPS; ++seg) {
         if (seg < W) {   // uniform
             const unsigned long long m = read_lane_u64(words, seg);
             const bool bit = ((m >> lane) & 1ull) != 0ull;
@@ -1318,16 +1333,12 @@ __global__ __launch_bounds__(256) void grid_index_kernel(int nb, GridScratch s, 
             if (!cols) {
                 if (bit) col_idx[pos] = other;
             } else {
-                // where the row-wise index holds cell (other, line): the row's start + its kept cells before
-                const int rc = rc16[seg];
+                const int rc = sum_bytes(rows[seg], W);
                 const int incl = wave_inclusive_scan_dpp(rc);
                 if (bit) {
-                    const unsigned long long* const row = s.kept + (size_t)other * W;
-                    int p = run + incl - rc;
-                    for (int q = 0; q < (line >> 6); ++q) p += __popcll(row[q]);
-                    p += __popcll(row[line >> 6] & ((1ull << (line & 63)) - 1ull));
                     row_idx[pos] = other;
-                    bsr_pos[pos] = p;
+                    bsr_pos[pos] = run + incl - rc + sum_bytes(rows[seg], word) +
+                                   __popcll(cell[seg] & ((1ull << (line & 63)) - 1ull));
                 }
                 run += __builtin_amdgcn_readlane(incl, 63);
             }
@@ -1450,10 +1461,10 @@ hipError_t launch_pattern_finish(bool from_part, long long* part, long long* poo
         grid_pool_kernel<<<dim3((n + 1023) / 1024), dim3(256), 0, st>>>(src, pool, nb, mode == 1, s.hist);
     grid_bits_kernel<<<dim3((words + 4 * kBitsWords - 1) / (4 * kBitsWords)), dim3(256), 0, st>>>(pool, nb, mode, (int)k_rank, no_fill, s);
     grid_serial_kernel<<<dim3(2), dim3(kFinishThreads), 0, st>>>(pool, nb, mode, kval, t_abs, no_fill, s);
-    grid_words_kernel<<<dim3(W * W), dim3(256), 0, st>>>(pool, nb, no_fill, s, fl);
+    grid_words_kernel<<<dim3(W * W), dim3(1024), 0, st>>>(pool, nb, no_fill, s, fl);
     const unsigned lines = (unsigned)(col_ptr ? 2 * nb : nb);
-    grid_index_kernel<<<dim3((lines + 3) / 4), dim3(256), 0, st>>>(nb, s, row_ptr, col_idx, col_ptr, row_idx, bsr_pos,
-                                                                   nnzb, nnzb_host);
+    auto* const index = W <= 4 ? grid_index_kernel<4> : W <= 8 ? grid_index_kernel<8> : grid_index_kernel<16>;
+    index<<<dim3((lines + 3) / 4), dim3(256), 0, st>>>(nb, s, row_ptr, col_idx, col_ptr, row_idx, bsr_pos, nnzb, nnzb_host);
     return hipGetLastError();
 }
 
