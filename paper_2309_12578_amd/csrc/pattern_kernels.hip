@@ -828,7 +828,7 @@ __global__ __launch_bounds__(kFinishThreads) void pattern_finish_kernel(
 //              1 the fill (the expanded cells of every row): neither needs the other
 //   words      grid_words_kernel: kept bits per row and, transposed, per column, and their counts
 //   index      grid_index_kernel: BSR and BSC
-// Measured at nb = 512: the five kernels take 10 + 8 + 29 + 5 + 4 us (one workgroup with a barrier per
+// Measured at nb = 512: the five kernels take 10 + 8 + 19 + 5 + 4 us (one workgroup with a barrier per
 // anti-diagonal took 2454); the longest part is the serial one, its threshold and its fill about alike.
 constexpr int kGridBins = 4096;
 constexpr int kGridMax = 1024;   // same bound as SPION_MAX_NB of the public header
@@ -1020,48 +1020,56 @@ __global__ __launch_bounds__(256) void grid_bits_kernel(const long long* __restr
 }
 
 // The fill on rows of up to 1024 bits: lane l of wave 0 holds columns 32 l .. 32 l + 31 and is l rows behind lane 0.
-// In step t it works on row t - l, for which its left neighbour found the carry out of the row's addition and the
-// diagonal entry into the next word one step before: the one reaches it as a bit set in scalar registers,
-// shifted by one lane, the other as a lane shift, both away from the chain of the step, which is seven vector
-// instructions.  (All lanes on one row, the carries resolved by a second addition on the bit set of lanes that
-// generate one, took 225 cycles a row instead of about 115: the kernel 49 -> 29 us at nb = 512, 26.5 -> 17.6 at 256.)
-// The other waves bring the words of the next kFillSteps steps into LDS, those of lane l l rows further up, and
-// store what was found in the steps before, which takes the place of the words of `right`: a trip to memory
-// takes longer than many steps.
+// In step t it works on row t - l, for which its left neighbour found the carry out of the row's addition one step before
+// and the last column of the row above two steps before: the one reaches it as a bit set in scalar registers, shifted
+// by one lane, the other as a lane shift, both away from the chain of the step.
+// (All lanes on one row, the carries resolved by a second addition on the bit set of lanes that generate one, took
+// 225 cycles a row: the kernel 49 us at nb = 512.)  Bound by the wave's own issue, an instruction every 6 to 7 cycles
+// whether or not it depends on the one before: so the other waves bring the words as the step takes them, the diagonal
+// bits in their target's place, the seeds in, and four steps' words of a lane side by side in LDS.  A step is eight
+// vector instructions, a scalar one and one access to LDS instead of 14 (115 -> 62 cycles, the kernel 29 -> 19 us at
+// nb = 512).  They also store what was found in the steps before, which takes the place of the words of `right`: a
+// trip to memory takes longer than many steps.
 constexpr int kFillSteps = 64;
 constexpr int kFillLd = kGridMax / 32;                  // words of a step in LDS, used or not
 constexpr int kFillPlane = kFillSteps * kFillLd;        // one array's words of a piece
-constexpr int kFillWords = 2 * 3 * kFillPlane;          // two pieces of down, right, diagonal
+constexpr int kFillWords = 2 * 3 * kFillPlane;          // two pieces of down, diagonal, right
 
-__device__ void grid_fill(const GridScratch& s, int nb, unsigned* buf /* kFillWords, LDS */) {
+__device__ void grid_fill(const GridScratch& s, int nb, unsigned* buf /* kFillWords, LDS, 16-byte aligned */) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int W2 = 2 * ((nb + 63) >> 6);   // 32-bit words per row
     const int pieces = (nb + W2 - 1 + kFillSteps - 1) / kFillSteps;
     constexpr int kOwn = (kFillPlane + kFinishThreads - 65) / (kFinishThreads - 64);   // words of a thread
-    const unsigned* const arr[3] = {reinterpret_cast<const unsigned*>(s.down), reinterpret_cast<const unsigned*>(s.right),
-                                    reinterpret_cast<const unsigned*>(s.diag)};
-    // One piece further for the threads from `first` on: store the words found in piece - 2, bring those of `piece`.
-    // Rows above the first pass on what they are given (all down); rows behind the last take nothing.
+    const unsigned *const down = reinterpret_cast<const unsigned*>(s.down), *const right = reinterpret_cast<const unsigned*>(s.right),
+                   *const diag = reinterpret_cast<const unsigned*>(s.diag);
+    // One piece further for the threads from `first` on: store the words found in piece - 2, bring those of `piece`: what
+    // lets a cell of the row above down and diagonally into the lane's word of row r, and what lets one of r on to the right.
+    // Rows above the first pass on what they are given; rows behind the last take nothing.
     auto exchange = [&](int piece, int first, int threads) {
         unsigned* const at = buf + (piece & 1) * 3 * kFillPlane;
-        unsigned w[kOwn][3];
+        unsigned w[kOwn][4];
         if (piece < pieces) {
 #pragma unroll
             for (int e = 0; e < kOwn; ++e) {
                 const int i = tid - first + e * threads, l = i % kFillLd, row = piece * kFillSteps + i / kFillLd - l;
-                const bool there = i < kFillPlane && l < W2 && row >= 0 && row < nb;
-#pragma unroll
-                for (int a = 0; a < 3; ++a) w[e][a] = there ? arr[a][(size_t)row * W2 + l] : (a == 0 && row < 0 ? ~0u : 0u);
+                const bool there = i < kFillPlane && l < W2 && row >= 0 && row < nb, above = there && row > 0;
+                const size_t here = (size_t)row * W2 + l;
+                w[e][0] = above ? down[here - W2] : (row <= 0 ? ~0u : 0u);
+                w[e][1] = above ? diag[here - W2] : 0u;
+                w[e][2] = above && l > 0 ? diag[here - W2 - 1] : 0u;
+                w[e][3] = there ? right[here] : 0u;
             }
         }
 #pragma unroll
         for (int e = 0; e < kOwn; ++e) {
-            const int i = tid - first + e * threads, l = i % kFillLd, row = (piece - 2) * kFillSteps + i / kFillLd - l;
+            const int i = tid - first + e * threads, l = i % kFillLd, t = i / kFillLd, row = (piece - 2) * kFillSteps + t - l;
             if (i >= kFillPlane || l >= W2) continue;
-            if (piece >= 2 && row >= 0 && row < nb) reinterpret_cast<unsigned*>(s.reached)[(size_t)row * W2 + l] = at[kFillPlane + i];
+            unsigned* const slot = at + (t >> 2) * (4 * kFillLd) + 4 * l + (t & 3);
+            if (piece >= 2 && row >= 0 && row < nb) reinterpret_cast<unsigned*>(s.reached)[(size_t)row * W2 + l] = slot[2 * kFillPlane];
             if (piece < pieces) {
-#pragma unroll
-                for (int a = 0; a < 3; ++a) at[a * kFillPlane + i] = w[e][a];
+                slot[0] = w[e][0] | (l == 0 ? 1u : 0u);   // the first cell of every row is a seed
+                slot[kFillPlane] = w[e][1] << 1 | w[e][2] >> 31;
+                slot[2 * kFillPlane] = w[e][3];
             }
         }
     };
@@ -1074,54 +1082,53 @@ __device__ void grid_fill(const GridScratch& s, int nb, unsigned* buf /* kFillWo
     if (wave != 0) exchange(0, 64, kFinishThreads - 64);
     meet();
     const int first_col = 32 * lane;
-    // "row -1": every cell of row 0 is a seed; the first of every row is one too: down bits of column 0 set
-    unsigned E = first_col >= nb ? 0u : (nb - first_col >= 32 ? ~0u : (1u << (nb - first_col)) - 1u), D = ~0u, G = 0u;
-    const unsigned seed = lane == 0 ? 1u : 0u;
-    unsigned eg_before = 0u;                // E & G of the step before
-    unsigned carry_lanes = 0u;              // lanes that receive a carry
+    // "row -1": every cell of row 0 is a seed
+    unsigned E = first_col >= nb ? 0u : (nb - first_col >= 32 ? ~0u : (1u << (nb - first_col)) - 1u);
+    unsigned E_before = 0u;                 // E of the step before
+    unsigned carry_lanes = 0u;              // lanes that have a carry to give
     for (int piece = 0; piece < pieces; ++piece) {
         if (wave != 0) {
             exchange(piece + 1, 64, kFinishThreads - 64);
         } else if (lane < kFillLd) {
-            unsigned* const src = buf + (piece & 1) * 3 * kFillPlane + lane;
+            typedef unsigned Word4 __attribute__((ext_vector_type(4)));
+            Word4* const src = reinterpret_cast<Word4*>(buf + (piece & 1) * 3 * kFillPlane) + lane;
             // (behind the branch a value per lane to the compiler: a scalar again before the instruction that needs one)
             unsigned long long carry = (unsigned)__builtin_amdgcn_readfirstlane((int)carry_lanes);
             constexpr int U = 4;   // steps whose words are requested together, one group ahead
-            unsigned d[2][U], q[2][U], g[2][U];
-            auto request = [&](int h, int t0) {
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int at = (t0 + u) * kFillLd;
-                    d[h][u] = src[at];
-                    q[h][u] = src[kFillPlane + at];
-                    g[h][u] = src[2 * kFillPlane + at];
-                }
+            Word4 d[2], g[2], q[2];
+            auto request = [&](int h, int group) {
+                d[h] = src[group * kFillLd];
+                g[h] = src[group * kFillLd + kFillPlane / 4];
+                q[h] = src[group * kFillLd + kFillPlane / 2];
                 __builtin_amdgcn_sched_barrier(0);
             };
-            auto work = [&](int h, int t0) {
+            auto work = [&](int h, int group) {
+                Word4 found;
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const unsigned prev = (unsigned)__builtin_amdgcn_update_dpp(0, (int)eg_before, 0x138 /* wave_shr:1 */, 0xf, 0xf, false);
-                    const unsigned eg = E & G;
-                    const unsigned x = (E & D) | __builtin_amdgcn_alignbit(eg, prev, 31);
+                    const unsigned prev = (unsigned)__builtin_amdgcn_update_dpp(0, (int)E_before, 0x138 /* wave_shr:1 */, 0xf, 0xf, true);
+                    const unsigned shifted = __builtin_amdgcn_alignbit(E, prev, 31);
+                    // to the neighbours; not next to the addition, whose result it would wait for
+                    asm("s_lshl_b64 %0, %0, 1" : "+s"(carry) : "v"(shifted) : "scc");
+                    const unsigned x = (E & d[h][u]) | (shifted & g[h][u]);
                     const unsigned R = q[h][u];
                     unsigned sum;
-                    asm("v_addc_co_u32 %0, %1, %2, %3, %1\n\ts_lshl_b64 %1, %1, 1" : "=v"(sum), "+s"(carry) : "v"(x & R), "v"(R) : "scc");
-                    E = x | (sum ^ R);
-                    src[kFillPlane + (t0 + u) * kFillLd] = E;
-                    eg_before = eg;
-                    D = d[h][u] | seed;
-                    G = g[h][u];
+                    asm("v_addc_co_u32 %0, %1, %2, %3, %1" : "=v"(sum), "+s"(carry) : "v"(x & R), "v"(R));
+                    E_before = E;
+                    E = __builtin_amdgcn_bitop3_b32(x, sum, R, 0xF6);   // x | (sum ^ R): the compiler splits it up over two steps
+                    found[u] = E;
                 }
+                src[group * kFillLd + kFillPlane / 2] = found;
                 __builtin_amdgcn_sched_barrier(0);
             };
+            constexpr int kGroups = kFillSteps / U;
             request(0, 0);
 #pragma unroll 1
-            for (int t0 = 0; t0 < kFillSteps; t0 += 2 * U) {
-                request(1, t0 + U);
-                work(0, t0);
-                request(0, (t0 + 2 * U) & (kFillSteps - 1));   // behind the last group: step 0 again, unused
-                work(1, t0 + U);
+            for (int group = 0; group < kGroups; group += 2) {
+                request(1, group + 1);
+                work(0, group);
+                request(0, (group + 2) & (kGroups - 1));   // behind the last group: the first again, unused
+                work(1, group + 1);
             }
             carry_lanes = (unsigned)carry;   // of 32 lanes
         }
