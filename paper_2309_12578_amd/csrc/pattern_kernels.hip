@@ -821,14 +821,15 @@ __global__ __launch_bounds__(kFinishThreads) void pattern_finish_kernel(
 // ------------------------------------------------------------------------------------------------
 // Words of 64 columns: W = ceil(nb / 64) per row.  Scratch of the stages, all in the workspace:
 //   cells      grid_pool_kernel: pool_sum; for a quantile also a histogram over 4096 bins that grow with
-//              the value (sign, position of the leading bit, next five bits)
+//              the value (128 to an octave: with 32, the median of a 512 x 512 map lay in a bin of some 100000 cells,
+//              from which one workgroup took 52 us to select)
 //   candidates grid_bits_kernel: successor bits of every row; the cells of the bin that holds the wanted
 //              rank, in any order
 //   serial     grid_serial_kernel: workgroup 0 the threshold (order statistic of the candidates), workgroup
 //              1 the fill (the expanded cells of every row): neither needs the other
 //   words      grid_words_kernel: kept bits per row and, transposed, per column, and their counts
 //   index      grid_index_kernel: BSR and BSC
-// Measured at nb = 512: the five kernels take 10 + 8 + 19 + 5 + 4 us (one workgroup with a barrier per
+// Measured at nb = 512: the five kernels take 7 + 5 + 19 + 5 + 4 us (one workgroup with a barrier per
 // anti-diagonal took 2454); the longest part is the serial one, its threshold and its fill about alike.
 constexpr int kGridBins = 4096;
 constexpr int kGridMax = 1024;   // same bound as SPION_MAX_NB of the public header
@@ -865,16 +866,14 @@ static GridScratch grid_carve(char* aux, void* part, size_t nb) {
     return s;
 }
 
-// Position of v among 4096 bins that are ordered like the values.
+// Position of v among 4096 bins that are ordered like the values: 128 to an octave from 2^32 on (a block's sum of scores
+// of 2^-8 in all), one to an octave below and of negative values.
+constexpr int kFineFrom = 32;
+static_assert(64 + 1 + kFineFrom + (63 - kFineFrom) * 128 <= kGridBins, "bins of the positive octaves");
 __device__ __forceinline__ int grid_bin(long long v) {
-    const unsigned long long m = v < 0 ? 0ull - (unsigned long long)v : (unsigned long long)v;
-    int idx = 0;
-    if (m != 0ull) {
-        const int lz = __clzll((long long)m);
-        const unsigned next5 = (unsigned)(((m << lz) << 1) >> 59);
-        idx = (63 - lz) * 32 + (int)next5 + 1;   // 1 .. 2017, the last for 2^63 alone
-    }
-    return v < 0 ? 2048 - idx : 2048 + idx;
+    if (v <= 0) return v == 0 ? 64 : __clzll((long long)(0ull - (unsigned long long)v));   // -2^63: 0
+    const int lz = __clzll(v), octave = 63 - lz;
+    return octave < kFineFrom ? 65 + octave : 65 + kFineFrom + (octave - kFineFrom) * 128 + (int)(((unsigned long long)v << lz) << 1 >> 57);
 }
 
 __global__ __launch_bounds__(256) void grid_zero_kernel(unsigned* __restrict__ zero) {
@@ -882,40 +881,44 @@ __global__ __launch_bounds__(256) void grid_zero_kernel(unsigned* __restrict__ z
     if (i < kGridZeroWords) zero[i] = 0u;
 }
 
-// A workgroup takes 1024 cells, 4 per thread, all their loads in flight together.
-__global__ __launch_bounds__(256) void grid_pool_kernel(const long long* __restrict__ part, long long* pool, int nb,
+// A thread takes CELLS cells, all their loads in flight together.  Bound by the latency of the short steps, and by the
+// additions to the histogram, whose lines pass between the XCDs' L2s: 256 threads of 4 cells took 9.5 us at nb = 512 and
+// 5.2 at 128, 1024 threads of 1 / 2 / 4 cells 8.7 / 7.0 / 8.1 and 4.0 / 4.9 / 6.6 (at 256: 4.0 / 4.8 / 6.6).
+constexpr int kPoolThreads = 1024;
+template <int CELLS>
+__global__ __launch_bounds__(kPoolThreads) void grid_pool_kernel(const long long* __restrict__ part, long long* pool, int nb,
                                                         int want_hist, unsigned* __restrict__ hist) {
     __shared__ unsigned h[kGridBins];
     const int tid = threadIdx.x, n = nb * nb;
     if (want_hist) {
-        for (int i = tid; i < kGridBins; i += 256) h[i] = 0u;
+        for (int i = tid; i < kGridBins; i += kPoolThreads) h[i] = 0u;
         __syncthreads();
     }
-    long long v[4];
+    long long v[CELLS];
     if (part) {
-        PoolParts rec[4];
+        PoolParts rec[CELLS];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int i = blockIdx.x * 1024 + j * 256 + tid, c = i < n ? i : n - 1;
+        for (int j = 0; j < CELLS; ++j) {
+            const int i = blockIdx.x * (CELLS * kPoolThreads) + j * kPoolThreads + tid, c = i < n ? i : n - 1;
             rec[j] = load_parts(part, nb, c / nb, c % nb);
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int i = blockIdx.x * 1024 + j * 256 + tid, c = i < n ? i : n - 1;
+        for (int j = 0; j < CELLS; ++j) {
+            const int i = blockIdx.x * (CELLS * kPoolThreads) + j * kPoolThreads + tid, c = i < n ? i : n - 1;
             v[j] = sum_parts(rec[j], nb, c / nb, c % nb);
             if (i < n) pool[i] = v[j];
         }
     } else {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int i = blockIdx.x * 1024 + j * 256 + tid;
+        for (int j = 0; j < CELLS; ++j) {
+            const int i = blockIdx.x * (CELLS * kPoolThreads) + j * kPoolThreads + tid;
             v[j] = pool[i < n ? i : n - 1];
         }
     }
     if (!want_hist) return;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const bool ok = blockIdx.x * 1024 + j * 256 + tid < n;
+    for (int j = 0; j < CELLS; ++j) {
+        const bool ok = blockIdx.x * (CELLS * kPoolThreads) + j * kPoolThreads + tid < n;
         const int b = grid_bin(v[j]);
         const unsigned long long m = __ballot(ok);
         if (m == 0ull) continue;
@@ -927,96 +930,76 @@ __global__ __launch_bounds__(256) void grid_pool_kernel(const long long* __restr
         }
     }
     __syncthreads();
-    for (int i = tid; i < kGridBins; i += 256)
+    for (int i = tid; i < kGridBins; i += kPoolThreads)
         if (h[i]) atomicAdd(&hist[i], h[i]);
 }
 
-// A wave takes kBitsWords words (64 cells of a row).  Every workgroup finds the bin of the wanted rank itself, 16
-// bins per thread and two scans, and takes room for its candidates with one addition: with one per wave and
+// A wave takes a word (64 cells of a row).  Every workgroup finds the bin of the wanted rank itself, 4
+// bins per thread and two scans (16 bins a thread and four words a wave, in 256 threads: 6.5 us at nb = 512, 5.1 so),
+// and takes room for its candidates with one addition: with one per wave and
 // word, all on one counter, a map of 512 x 512 nearly equal cells (one bin) took 50 us,
 // now 8.8.
-constexpr int kBitsWords = 4;
-__global__ __launch_bounds__(256) void grid_bits_kernel(const long long* __restrict__ pool, int nb, int mode,
+constexpr int kBitsThreads = 1024, kBitsWords = kBitsThreads / 64;   // words of a workgroup
+__global__ __launch_bounds__(kBitsThreads) void grid_bits_kernel(const long long* __restrict__ pool, int nb, int mode,
                                                         int k_rank, int no_fill, GridScratch s) {
-    __shared__ int wave_sum[4], sel_bin;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int W = (nb + 63) >> 6;
+    __shared__ int wave_sum[kBitsWords], sel_bin;
+    __shared__ unsigned wave_cand[kBitsWords], cand_base;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int W = (nb + 63) >> 6, words = nb * W, word = blockIdx.x * kBitsWords + wave;
+    const bool there = word < words;   // uniform
+    const int r = there ? word / W : 0, c = (there ? word % W * 64 : 0) + lane;
+    const bool inner = c + 1 < nb && r + 1 < nb;
+    const int i = r * nb + (c < nb ? c : 0);
+    const long long v = pool[i];
+    const long long dn = inner && !no_fill ? pool[i + nb] : 0, rt = inner && !no_fill ? pool[i + 1] : 0,
+                    dg = inner && !no_fill ? pool[i + nb + 1] : 0;
     int bin = -1;
     if (mode == 1) {
-        uint4 q[4];
-        int cnt = 0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            q[e] = reinterpret_cast<const uint4*>(s.hist)[tid * 4 + e];
-            cnt += (int)(q[e].x + q[e].y + q[e].z + q[e].w);
-        }
-        int incl = wave_inclusive_scan_dpp(cnt);
-        if (lane == 63) wave_sum[wave] = incl;
+        static_assert(kGridBins == 4 * kBitsThreads, "four bins a thread");
+        const uint4 q = reinterpret_cast<const uint4*>(s.hist)[tid];
+        const int cnt = (int)(q.x + q.y + q.z + q.w);
+        const int scan = wave_inclusive_scan_dpp(cnt);
+        if (lane == 63) wave_sum[wave] = scan;
         __syncthreads();
-        for (int w = 0; w < wave; ++w) incl += wave_sum[w];
+        const int sums = wave_inclusive_scan_dpp(lane < kBitsWords ? wave_sum[lane] : 0);
+        const int incl = scan + (wave > 0 ? __builtin_amdgcn_readlane(sums, wave - 1) : 0);
         int e0 = incl - cnt;
         if (k_rank >= e0 && k_rank < incl) {   // exactly one thread
-            const unsigned c[16] = {q[0].x, q[0].y, q[0].z, q[0].w, q[1].x, q[1].y, q[1].z, q[1].w,
-                                    q[2].x, q[2].y, q[2].z, q[2].w, q[3].x, q[3].y, q[3].z, q[3].w};
             int b = 0;
-            bool found = false;
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const bool here = !found && k_rank < e0 + (int)c[e];
-                b = here ? e : b;
-                found = found || here;
-                e0 = found ? e0 : e0 + (int)c[e];
+            for (const unsigned n : {q.x, q.y, q.z}) {
+                if (k_rank < e0 + (int)n) break;
+                e0 += (int)n;
+                ++b;
             }
-            sel_bin = tid * 16 + b;
+            sel_bin = tid * 4 + b;
             if (blockIdx.x == 0) s.hist[kGridBins + 1] = (unsigned)(k_rank - e0);   // rank among the candidates
         }
         __syncthreads();
         bin = sel_bin;
     }
-    __shared__ unsigned wave_cand[4], cand_base;
-    const int words = nb * W, first = (blockIdx.x * 4 + wave) * kBitsWords;
-    long long v[kBitsWords];
-    bool mine[kBitsWords];
-    unsigned found = 0u;   // candidates of this wave
-#pragma unroll
-    for (int q = 0; q < kBitsWords; ++q) {
-        const int word = min(first + q, words - 1), c = word % W * 64 + lane;
-        v[q] = pool[word / W * nb + (c < nb ? c : 0)];
-    }
-#pragma unroll
-    for (int q = 0; q < kBitsWords; ++q) {
-        const int word = min(first + q, words - 1), r = word / W, c = word % W * 64 + lane;
-        const bool there = first + q < words;   // uniform
-        if (!no_fill && there) {
-            const bool inner = c + 1 < nb && r + 1 < nb;
-            const int i = r * nb + (c < nb ? c : 0);
-            const Succ sc = successors(inner ? pool[i + nb] : 0, inner ? pool[i + 1] : 0, inner ? pool[i + nb + 1] : 0, inner);
-            const unsigned long long bd = __ballot(sc.down), br = __ballot(sc.right), bg = __ballot(sc.diag);
-            if (lane == 0) {
-                s.down[word] = bd;
-                s.right[word] = br;
-                s.diag[word] = bg;
-            }
+    if (!no_fill && there) {
+        const Succ sc = successors(dn, rt, dg, inner);
+        const unsigned long long bd = __ballot(sc.down), br = __ballot(sc.right), bg = __ballot(sc.diag);
+        if (lane == 0) {
+            s.down[word] = bd;
+            s.right[word] = br;
+            s.diag[word] = bg;
         }
-        mine[q] = mode == 1 && there && c < nb && grid_bin(v[q]) == bin;
-        found += (unsigned)__popcll(__ballot(mine[q]));
     }
     if (mode != 1) return;
-    if (lane == 0) wave_cand[wave] = found;
+    const bool mine = there && c < nb && grid_bin(v) == bin;
+    const unsigned long long m = __ballot(mine);
+    if (lane == 0) wave_cand[wave] = (unsigned)__popcll(m);
     __syncthreads();
+    const int found = wave_inclusive_scan_dpp(lane < kBitsWords ? (int)wave_cand[lane] : 0);
     if (tid == 0) {
-        const unsigned all = wave_cand[0] + wave_cand[1] + wave_cand[2] + wave_cand[3];
+        const unsigned all = (unsigned)__builtin_amdgcn_readlane(found, kBitsWords - 1);
         cand_base = all ? atomicAdd(&s.hist[kGridBins], all) : 0u;
     }
     __syncthreads();
-    unsigned base = cand_base;
-    for (int w = 0; w < wave; ++w) base += wave_cand[w];
-#pragma unroll
-    for (int q = 0; q < kBitsWords; ++q) {
-        const unsigned long long m = __ballot(mine[q]);
-        if (mine[q]) s.cand[base + (unsigned)__popcll(m & ((1ull << lane) - 1ull))] = (unsigned long long)v[q] ^ kSign;
-        base += (unsigned)__popcll(m);
-    }
+    if (mine)
+        s.cand[cand_base + (unsigned)(wave > 0 ? __builtin_amdgcn_readlane(found, wave - 1) : 0) + (unsigned)__popcll(m & ((1ull << lane) - 1ull))] =
+            (unsigned long long)v ^ kSign;
 }
 
 // The fill on rows of up to 1024 bits: lane l of wave 0 holds columns 32 l .. 32 l + 31 and is l rows behind lane 0.
@@ -1464,9 +1447,13 @@ hipError_t launch_pattern_finish(bool from_part, long long* part, long long* poo
     const GridScratch s = grid_carve(static_cast<char*>(aux), part, (size_t)nb);
     const unsigned n = (unsigned)(nb * nb), W = (unsigned)((nb + 63) / 64), words = (unsigned)nb * W;
     if (!from_part) grid_zero_kernel<<<dim3((kGridZeroWords + 255) / 256), dim3(256), 0, st>>>(s.hist);
-    if (from_part || mode == 1)
-        grid_pool_kernel<<<dim3((n + 1023) / 1024), dim3(256), 0, st>>>(src, pool, nb, mode == 1, s.hist);
-    grid_bits_kernel<<<dim3((words + 4 * kBitsWords - 1) / (4 * kBitsWords)), dim3(256), 0, st>>>(pool, nb, mode, (int)k_rank, no_fill, s);
+    if (from_part || mode == 1) {
+        if (nb <= 256)
+            grid_pool_kernel<1><<<dim3((n + kPoolThreads - 1) / kPoolThreads), dim3(kPoolThreads), 0, st>>>(src, pool, nb, mode == 1, s.hist);
+        else
+            grid_pool_kernel<2><<<dim3((n + 2 * kPoolThreads - 1) / (2 * kPoolThreads)), dim3(kPoolThreads), 0, st>>>(src, pool, nb, mode == 1, s.hist);
+    }
+    grid_bits_kernel<<<dim3((words + kBitsWords - 1) / kBitsWords), dim3(kBitsThreads), 0, st>>>(pool, nb, mode, (int)k_rank, no_fill, s);
     grid_serial_kernel<<<dim3(2), dim3(kFinishThreads), 0, st>>>(pool, nb, mode, kval, t_abs, no_fill, s);
     grid_words_kernel<<<dim3(W * W), dim3(1024), 0, st>>>(pool, nb, no_fill, s, fl);
     const unsigned lines = (unsigned)(col_ptr ? 2 * nb : nb);

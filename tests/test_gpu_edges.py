@@ -50,6 +50,36 @@ def test_pattern_at_the_edges_of_the_splits(sp, nb, block, ties):
     _same_pattern(sp, A, block, 5, si.T_QUANTILE, 0.9, flags=sp.SPION_PATTERN_NO_FILL, variant="C")
 
 
+# One and two cells a thread of the kernel that counts; bins: negative values, 0, octaves below and above the first that
+# is divided, its edges, one value throughout, ties at the rank
+@pytest.mark.parametrize("nb", [65, 255, 300])
+@pytest.mark.parametrize("kind", ["octaves", "edges", "near", "equal"])
+@pytest.mark.parametrize("q", [0.0, 0.37, 0.9, 1.0])
+def test_quantile_of_large_grids(sp, nb, kind, q):
+    rng = np.random.default_rng(nb)
+    n = nb * nb
+    if kind == "octaves":
+        pool = (rng.choice((-1, 1, 1, 1), n) * (2.0 ** rng.uniform(0, 58.9, n))).astype(np.int64)
+        pool[rng.integers(0, n, 50)] = 0
+    elif kind == "edges":
+        edges = [s * ((1 << e) + d) for e in (1, 31, 32, 33, 58) for d in (-1, 0, 1, (1 << e) >> 7, ((1 << e) >> 7) - 1) for s in (-1, 1)]
+        pool = rng.choice(np.array(edges, dtype=np.int64), n)
+    elif kind == "near":
+        pool = (1 << 40) + rng.integers(0, 1 << 30, n)
+    else:
+        pool = np.full(n, 12345, dtype=np.int64)
+    L, block = nb * 16, 16
+    dev = torch.from_numpy(pool.reshape(nb, nb)).cuda()
+    z = lambda m, t=torch.int32: torch.zeros(m, dtype=t, device="cuda")
+    fl, nnzb = z((nb, nb), torch.uint8), z(1)
+    ws = torch.empty(sp.spion_pattern_workspace_bytes(L, block), dtype=torch.uint8, device="cuda")
+    sp.spion_pattern(None, L, block, 1, sp.SPION_T_QUANTILE, q, fl, z(nb + 1), z(n), z(nb + 1), z(n), z(n), nnzb, dev, ws,
+                     flags=sp.SPION_PATTERN_FROM_POOL | sp.SPION_PATTERN_NO_FILL)
+    t = np.sort(pool)[int(np.floor(q * (n - 1)))]
+    want = (pool.reshape(nb, nb) > t) | np.eye(nb, dtype=bool)
+    assert np.array_equal(fl.cpu().numpy().astype(bool), want) and int(nnzb.item()) == want.sum()
+
+
 def _attention(sp, Q, K, V, dO, fl, block, dtype, heads, flags=0):
     """Relative errors (2-norm and max) of O, dQ, dK, dV of the given heads against the fp64 oracle."""
     from test_gpu_parity import _run_attention_case
