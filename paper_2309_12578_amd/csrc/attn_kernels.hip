@@ -46,6 +46,7 @@ struct Split {
     static constexpr int NQ = NQ_, WT = WT_, WQ = WQ_, W = WT * WQ;
     static constexpr int OWN = 16 * NQ * WQ;          // rows of a workgroup
     static constexpr int PARTS = BS / OWN;            // workgroups per block row or column
+    static_assert(WT == 1 || OWN % (4 * W) == 0, "the merge takes 4 W rows at a time, all of them the workgroup's");
     static constexpr int TPB = BS / 16;               // 16-row tiles per block
     static constexpr int KT = sizeof(T) == 2 ? 2 : 1; // tiles per step: a bf16 MFMA contracts over 32 rows
     static constexpr int STRIDE = WT * KT;            // tiles per step of all WT waves
@@ -341,7 +342,8 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_bwd_kernel(
     const T* __restrict__ dO, const float* __restrict__ LSE, T* __restrict__ dQ, T* __restrict__ dK,
     T* __restrict__ dV, const int* __restrict__ row_ptr, const int* __restrict__ col_idx,
     const int* __restrict__ col_ptr, const int* __restrict__ row_idx, float* __restrict__ partial, int n_slots,
-    int BH, int L, int nb, int n_key_a, int n_rows, int n_key_c, int w_first, int chunk, float scale, float scale_log2) {
+    int BH, int L, int nb, int n_key_a, int n_rows, int n_key_c, int w_first, int chunk, int sort_rows, float scale,
+    float scale_log2) {
     typedef typename Elem<T>::Frag Frag;
     typedef typename Elem<T>::Quad Quad;
     typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
@@ -351,23 +353,35 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_bwd_kernel(
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wt = wave % S::WT, own = wave / S::WT * (16 * NQ);
     auto padded = [](int n) { return (n + 7) & ~7; };
+    const int row_groups = sort_rows ? S::PARTS * padded(BH * n_rows) : padded(BH * n_rows * S::PARTS);
     int id = blockIdx.x, per_head = n_key_a * S::PARTS, first = 0;
     bool key_side = true;
     if (id >= padded(BH * per_head)) {
         id -= padded(BH * per_head);
         per_head = n_rows * S::PARTS;
         key_side = false;
-        if (id >= padded(BH * per_head)) {
-            id -= padded(BH * per_head);
+        if (id >= row_groups) {
+            id -= row_groups;
             per_head = n_key_c * S::PARTS;
             first = w_first;
             key_side = true;
         }
     }
-    const int item = item_of_group(id, BH * per_head);
-    if (item < 0) return;
-    const int bh = item / per_head, idx = first + item % per_head / S::PARTS;
-    const int sub = item % S::PARTS * OWN;   // the workgroup's rows within the block
+    int bh, idx, sub;   // sub: the workgroup's rows within the block
+    if (!key_side && sort_rows) {
+        const int row = (id >> 3) / S::PARTS * 8 + (id & 7);   // a row's workgroups on one XCD
+        if (row >= BH * n_rows) return;
+        const RowOfHead mine = long_rows_first<true>(row_ptr, nb, BH, row, lane);
+        bh = mine.head;
+        idx = mine.row;
+        sub = (id >> 3) % S::PARTS * OWN;
+    } else {
+        const int item = item_of_group(id, BH * per_head);
+        if (item < 0) return;
+        bh = item / per_head;
+        idx = first + item % per_head / S::PARTS;
+        sub = item % S::PARTS * OWN;
+    }
     const size_t head = (size_t)bh * L * kD, vec = (size_t)bh * L;
 
     // adds up the waves' accumulators: row p + tid / 16, columns 4 (tid % 16) .. + 3
@@ -619,13 +633,20 @@ static hipError_t launch_bwd(const AttnShape& s, const void* Q, const void* K, c
     const bool rows = (s.bwd_phases & 1) != 0, keys = (s.bwd_phases & 2) != 0;
     const int n_key_a = keys ? ws.w_first : 0, n_rows = rows ? s.nb : 0, n_key_c = keys ? ws.w_max - ws.w_first : 0;
     const long long per_item = (long long)s.BH * S::PARTS;
-    const long long grid = group_grid(per_item * n_key_a) + group_grid(per_item * n_rows) + group_grid(per_item * n_key_c);
+    // Rows of more than twice the mean first, where more workgroups than fit at once follow (two or three waves a SIMD):
+    // one that starts late runs on alone.  fp32: 2 heads x 8192, block 32, 3 %, 161 -> 148 us; 3 x 4096, block 64, 10 %, 86 -> 76; 8 x 2048,
+    // block 32, 15 %, 78 -> 71, 10 % 52.7 both; bf16, block 16: 10 x 4096, 4 %, 71 -> 67, 9 x 1936, 8 %, 31.3 -> 30.0; without long rows the
+    // search costs up to 1 us (32 x 512, block 32, 30.9 -> 31.8).
+    const long long resident = 256 * 4 * (sizeof(T) == 4 ? 2 : 3) / S::W;
+    const int sort_rows = rows && per_item * (n_key_a + n_rows + n_key_c) > resident;
+    const long long grid = group_grid(per_item * n_key_a) + (sort_rows ? S::PARTS * group_grid((long long)s.BH * n_rows) : group_grid(per_item * n_rows)) +
+                           group_grid(per_item * n_key_c);
     if (grid > 0) {
         attn_bwd_kernel<T, BS, S><<<dim3((unsigned)grid), dim3(S::W * 64), 0, st>>>(
             static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V), static_cast<const T*>(O),
             static_cast<const T*>(dO), LSE, static_cast<T*>(dQ), static_cast<T*>(dK), static_cast<T*>(dV), row_ptr,
             col_idx, col_ptr, row_idx, partial, ws.n_slots, s.BH, s.L, s.nb, n_key_a, n_rows, n_key_c, ws.w_first,
-            ws.chunk, s.scale, s.scale * kLog2e);
+            ws.chunk, sort_rows, s.scale, s.scale * kLog2e);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

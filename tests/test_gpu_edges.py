@@ -123,6 +123,21 @@ def test_forward_more_rows_than_run_at_once(sp):
     _attention(sp, Q, K, V, dO, fl, block, "bf16", [0, 9])
 
 
+# fp32: 16 rows a forward workgroup below 2048 workgroups of 32 rows, 32 from there on; more backward workgroups than run
+# at once, so that the rows of more than twice the mean go first (block 64: a row's two workgroups together), at head counts that
+# do not divide over the XCDs; bf16 of block 16 likewise; one long row, one without a diagonal block, an empty one
+@pytest.mark.parametrize("dtype,block,BH,nb", [("f32", 32, 63, 32), ("f32", 32, 64, 32), ("f32", 64, 15, 24), ("f32", 64, 43, 24),
+                                               ("f32", 16, 21, 40), ("bf16", 16, 37, 44)])
+def test_generic_kernels_rows_by_length(sp, dtype, block, BH, nb):
+    rng = np.random.default_rng(BH)
+    Q, K, V, dO = [si.round_to_dtype(rng.standard_normal((BH, nb * block, 64), dtype=np.float32), dtype) for _ in range(4)]
+    fl = si.random_block_mask(nb, 0.35, seed=nb)
+    fl[[nb // 2, nb - 1], :] = 1
+    fl[nb // 2, nb // 2] = 0
+    fl[3, :] = 0
+    _attention(sp, Q, K, V, dO, fl, block, dtype, [0, BH // 2, BH - 1])
+
+
 # The kernels of fp32 and of block size 16 share a row's tiles over the waves of a workgroup by the average number of
 # tiles and the number of rows: (heads, block rows, density) for four waves a row, for few, and for rows of one
 # block; with rows and columns of 0, 1, 2, 65 and more blocks, odd numbers of tiles, split columns, and head
