@@ -661,7 +661,13 @@ static hipError_t fwd_t(const AttnShape& s, const void* Q, const void* K, const 
     } else {
         if (many_short_rows(s, nnzb))
             return launch_fwd<T, BS, typename SplitMany<T, BS>::fwd>(s, Q, K, V, O, LSE, row_ptr, col_idx, st);
-        return launch_fwd<T, BS, SplitFew<T, BS>>(s, Q, K, V, O, LSE, row_ptr, col_idx, st);
+        // 16 rows a workgroup (32: half the tile traffic) until there are enough of them anyway: a row of many blocks is
+        // then shared by twice the compute units, whose matrix cores it fills.  fp32, 32 -> 16 rows: 2 heads x 8192, block
+        // 32, 3 %, 87 -> 54 us; 8 x 2048, 10 %, 24.3 -> 18.7; 4 x 1024, block 64, 20 %, 11.7 -> 7.8; 8 x 2048, 30 %, 37.5 -> 35.0;
+        // 32 x 2048, block 64 (2048 workgroups of 32 rows) 45.9 -> 47.3; 64 x 2048, block 32 (4096) 96.4 both.
+        if (BS > 16 && (long long)s.BH * s.L / 32 >= 2048)
+            return launch_fwd<T, BS, SplitFew<T, BS>>(s, Q, K, V, O, LSE, row_ptr, col_idx, st);
+        return launch_fwd<T, BS, Split<T, BS, 1, 4, 1>>(s, Q, K, V, O, LSE, row_ptr, col_idx, st);
     }
 }
 
