@@ -10,6 +10,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "attn_bf16_tiles.h"
 #include "attn_common.h"
 #include "spion_internal.h"
@@ -41,27 +43,20 @@ __device__ __forceinline__ void stage_ready(bool younger_in_flight) {
     asm volatile("" ::: "memory");
 }
 
-template <int BS, bool BESIDE>
-__global__ __launch_bounds__(BS * 4) void attn_fwd_bf16_kernel(
+// Kernels that cut nothing carry no plan.
+struct NoCut {};
+template <bool CUT>
+using CutOf = std::conditional_t<CUT, RowCut, NoCut>;
+
+// Block row I of head bh.  CUT: its first piece alone if it is a long one; HELPER: the given piece, one of cuts.count.
+template <int BS, bool BESIDE, bool CUT, bool HELPER>
+__device__ __forceinline__ void attend(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     bf16_t* __restrict__ O, float* __restrict__ LSE, const int* __restrict__ row_ptr,
-    const int* __restrict__ col_idx, HeadRows<BESIDE> at, int L, int nb, int total, int sort_rows, float scale_log2,
-    int paper_denom) {
+    const int* __restrict__ col_idx, const HeadRows<BESIDE>& at, const CutOf<CUT>& cut, int L, int nb, float scale_log2,
+    int paper_denom, KvSmem<BS>& sm0, KvSmem<BS>& sm1, int bh, int I, int piece, RowPieces cuts, int lane, int wave) {
     constexpr int NKT = BS / 16;
-    __shared__ __attribute__((aligned(16))) KvSmem<BS> sm0, sm1;
-
-    const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    int bh, I;
-    if (sort_rows) {
-        const RowOfHead mine = long_rows_first<true>(row_ptr, nb, total / nb, blockIdx.x, lane);
-        bh = mine.head;
-        I = mine.row;
-    } else {
-        const int vid = xcd_remap(blockIdx.x, total);
-        bh = vid / nb;
-        I = vid % nb;
-    }
+    const int r = lane & 15, g = lane >> 4;
     const size_t head = at.in_head(bh, L);
     const int row_len = at.in_row();
     const int qrow = I * BS + wave * 16 + r;
@@ -72,16 +67,25 @@ __global__ __launch_bounds__(BS * 4) void attn_fwd_bf16_kernel(
         tile_load_async(K + head + (size_t)J * BS * row_len, st.k, wave, tl);
         tile_load_async(V + head + (size_t)J * BS * row_len, st.v, wave, tl);
     };
-    issue(sm0, I);   // the diagonal block, before any index is known
+    if (!HELPER) issue(sm0, I);   // the diagonal block, before any index is known
     bf16x8 qf[2];
 #pragma unroll
     for (int c = 0; c < 2; ++c)
         qf[c] = *reinterpret_cast<const bf16x8*>(Q + head + (size_t)qrow * row_len + c * 32 + g * 8);
-    const int jb = row_ptr[I], n = row_ptr[I + 1] - jb;
+    int jb = row_ptr[I];
+    const int n_row = row_ptr[I + 1] - jb;
+    int n = n_row;   // blocks of this workgroup
+    if constexpr (CUT) if (n_row > cut.longest) {
+        if (!HELPER) cuts = row_pieces<true>(row_ptr, nb, cut, I, lane);
+        const int from = piece * n_row / cuts.count;
+        n = (piece + 1) * n_row / cuts.count - from;
+        jb += from;
+    }
     const int last = n > 0 ? n - 1 : 0;
     const int* cols = col_idx + jb;
     int first[8];
-    const int pd = n > 0 ? find_in_row(cols, n, I, first) : -1;
+    int pd = n > 0 ? find_in_row(cols, n, I, first) : -1;
+    if (HELPER) pd = -1;   // in index order, the diagonal block where it comes
     // block visited at step t (clamped reads stay inside this row's entries; an empty row reads nothing)
     auto col_at = [&](int t) {
         const int j = walk_index(t < last ? t : last, pd);
@@ -96,10 +100,12 @@ __global__ __launch_bounds__(BS * 4) void attn_fwd_bf16_kernel(
         return u < 64 ? __builtin_amdgcn_readlane(walk_v, u) : cols[walk_index(u, pd)];
     };
     if (pd < 0 && n > 0) {
-        // no diagonal block in this row: once everyone's early load has landed, load block 0 over it
-        __builtin_amdgcn_s_waitcnt(kWaitVm0);
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
+        // no diagonal block in this row (piece): once everyone's early load has landed, load block 0 over it
+        if (!HELPER) {
+            __builtin_amdgcn_s_waitcnt(kWaitVm0);
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        }
         issue(sm0, first[0]);
     }
     // the second block goes out as soon as its index is known; it is the youngest load from here on
@@ -186,13 +192,43 @@ __global__ __launch_bounds__(BS * 4) void attn_fwd_bf16_kernel(
     // an empty row never waited for its early load: it must land before this workgroup's LDS is freed
     __builtin_amdgcn_s_waitcnt(kWaitVm0);
 
+    if constexpr (CUT) if (cuts.count > 1) {   // a long row in pieces: see attn_bf16_tiles.h
+        constexpr int kPart = 64 * 18;   // floats of a wave: nine pairs a lane, its accumulators, then reference and sum
+        const size_t slot = (size_t)bh * cut.slots + cuts.slot;
+        float* const parts = cut.parts + (slot * (BS / 16) + wave) * kPart + lane * 2;
+        float* const mine = parts + (size_t)piece * (BS / 16) * kPart;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) put_shared(mine + i * 128, oacc[i / 2][i % 2 * 2], oacc[i / 2][i % 2 * 2 + 1]);
+        put_shared(mine + 1024, m, lacc[0]);
+        // (the flag's place: nobody reads tiles any more behind the barriers, and the patch below is in the K tiles)
+        if (!last_to_arrive(cut.counters + slot, cut.tag, cuts.count, reinterpret_cast<int*>(sm0.v))) return;
+        m = -INFINITY;
+        lacc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) oacc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int c = 0; c < cuts.count; ++c) {
+            const float* const part = parts + (size_t)c * (BS / 16) * kPart;
+            float2 v[9];
+#pragma unroll
+            for (int i = 0; i < 9; ++i) v[i] = get_shared(part + i * 128);
+            const float m_new = fmaxf(m, v[8].x), a = fast_exp2(m - m_new), b = fast_exp2(v[8].x - m_new);
+            m = m_new;
+            lacc = lacc * a + v[8].y * b;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int e = i % 2 * 2;
+                oacc[i / 2][e] = oacc[i / 2][e] * a + v[i].x * b;
+                oacc[i / 2][e + 1] = oacc[i / 2][e + 1] * a + v[i].y * b;
+            }
+        }
+    }
     float lsum = lacc[0];
-    if (paper_denom && n > 0 && L > n * BS) {
+    if (paper_denom && n_row > 0 && L > n_row * BS) {
         // Algorithm 6: every masked entry of the row counts as a score of 0 (a row that keeps nothing
         // has no entry to normalise and stays at O = 0, LSE = -inf).  The sums are up to 2^kRescaleSlack times
         // what they would be against the row's maximum.
         const float mp = fmaxf(m, 0.f);
-        lsum = scale_down(lacc, m - mp)[0] + (float)(L - n * BS) * exp2f(-mp);
+        lsum = scale_down(lacc, m - mp)[0] + (float)(L - n_row * BS) * exp2f(-mp);
 #pragma unroll
         for (int dt = 0; dt < 4; ++dt) oacc[dt] = scale_down(oacc[dt], m - mp);
         m = mp;
@@ -205,30 +241,108 @@ __global__ __launch_bounds__(BS * 4) void attn_fwd_bf16_kernel(
     if (g == 0) LSE[(size_t)bh * L + qrow] = lsum > 0.f ? (m + log2f(lsum)) * kLn2 : -INFINITY;
 }
 
+template <int BS, bool BESIDE, bool CUT>
+__global__ __launch_bounds__(BS * 4) void attn_fwd_bf16_kernel(
+    const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
+    bf16_t* __restrict__ O, float* __restrict__ LSE, const int* __restrict__ row_ptr,
+    const int* __restrict__ col_idx, HeadRows<BESIDE> at, CutOf<CUT> cut, int L, int nb, int total, int sort_rows,
+    float scale_log2, int paper_denom) {
+    __shared__ __attribute__((aligned(16))) KvSmem<BS> sm0, sm1;
+
+    const int tid = threadIdx.x;
+    int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int id = blockIdx.x;
+    if constexpr (CUT) if (id < cut.groups) {   // pieces of long rows
+        const int all = total / nb * cut.helpers;
+        if (id >= all) return;
+        const int l = xcd_deal(id, 0, all), bh = l / cut.helpers;
+        for (int p = l % cut.helpers;; p += cut.helpers) {   // ends behind the head's last piece
+            const RowPieces cuts = row_pieces<false>(row_ptr, nb, cut, p, lane);
+            if (cuts.row < 0) return;
+            attend<BS, BESIDE, true, true>(Q, K, V, O, LSE, row_ptr, col_idx, at, cut, L, nb, scale_log2, paper_denom, sm0, sm1, bh,
+                                     cuts.row, p - cuts.first + 1, cuts, lane, wave);
+            __syncthreads();   // everyone is done with the tiles' memory
+            asm volatile("" : "+v"(lane));   // nothing per lane is kept in registers for the next piece
+        }
+    }
+    if constexpr (CUT) id -= cut.groups;
+    int bh, I;
+    if (sort_rows) {
+        const RowOfHead mine = long_rows_first<true>(row_ptr, nb, total / nb, id, lane);
+        bh = mine.head;
+        I = mine.row;
+    } else {
+        const int vid = xcd_remap(id, total);
+        bh = vid / nb;
+        I = vid % nb;
+    }
+    attend<BS, BESIDE, CUT, false>(Q, K, V, O, LSE, row_ptr, col_idx, at, cut, L, nb, scale_log2, paper_denom, sm0, sm1, bh, I, 0,
+                              RowPieces{I, 1, 0, 0}, lane, wave);
+}
+
+// Workgroups that run at once: 4 (block 64) and at least 8 (block 32) fit a compute unit.
+static int fwd_resident(int bs) { return 256 * (bs == 64 ? 4 : 8); }
+
+// A row is long if it is four times the mean (24 blocks) and, at twice the pace of a workgroup among others, still outlasts the
+// launch: twice the steps that each of the workgroups that run at once has to do.  bf16 forward, us, uncut / cut (patterns
+// with two long rows): 8 heads x 8192, block 32, rows of 121 blocks, 41.9 / 20.1; 4 x 16384, block 64, 65.5 / 29.2; 4 x 8192, block 64, rows of
+// 71, 37.6 / 20.9; 1 x 4096, block 32, 17.1 / 10.8; 16 x 16320, block 64, rows of 112, 83.1 / 78.1.  Rows of 45 and 27 at 64 x 4160 and 128 x 2080,
+// block 32, which the rule leaves whole, 38.6 / 40.5 and 38.5 / 41.9.  A pattern without long rows: 76.6 / 76.9, 14.7 / 14.8.
+RowCut::RowCut(const AttnShape& s, int nnzb) {
+    // Up to 64 block rows a row is not that long, and what the others pay shows: kernels of 14 and 45 us without a row
+    // to cut, 16 and 32 heads x 4096, block 64, took 0.4 and 1 us longer.
+    if (s.nb <= 64 || !s.is_bf16 || s.bs == 16) return;
+    const int mean = (nnzb + s.nb - 1) / s.nb;
+    const long long steps = (long long)s.BH * nnzb / fwd_resident(s.bs);
+    piece = mean < 6 ? 12 : 2 * mean;
+    longest = mean < 6 ? 24 : 4 * mean;
+    if (longest < 2 * steps) longest = 2 * steps < s.nb ? (int)(2 * steps) : s.nb;
+    if (s.nb <= longest) return;   // no row can be cut
+    constexpr int kSlots = 32;   // two rows of half the columns at 3 % kept blocks; 0.6 MB of room per head
+    const int most = nnzb / piece + nnzb / (longest + 1);   // pieces there can be
+    slots = most < kSlots ? most : kSlots;
+    if (slots < 2) slots = 0;
+    helpers = s.BH <= 8 ? 16 : s.BH < 128 ? 128 / s.BH : 1;
+    if (helpers >= slots) helpers = slots > 0 ? slots - 1 : 0;
+    groups = (s.BH * helpers + 7) & ~7;
+    if ((long long)s.BH * s.nb + groups > 0x7fffffffll) slots = helpers = groups = 0;   // workgroups of a launch
+    tag = s.fwd_tag;
+    if (!s.fwd_room) return;
+    counters = static_cast<unsigned long long*>(s.fwd_room);
+    parts = reinterpret_cast<float*>(static_cast<char*>(s.fwd_room) + counter_bytes(s.BH));
+}
+
 // ------------------------------------------------------------------------------------------------
 // launcher (called by the dispatch in attn_kernels.hip)
 // ------------------------------------------------------------------------------------------------
 template <int BS>
 hipError_t fwd_bf16(const AttnShape& s, const void* Q, const void* K, const void* V, void* O, float* LSE,
-                    const int* row_ptr, const int* col_idx, hipStream_t st) {
+                    const int* row_ptr, const int* col_idx, int nnzb, hipStream_t st) {
     const int total = s.nb * s.BH;
-    // 4 (block 64) and at least 8 (block 32) workgroups fit a compute unit; where all run at once their order is
-    // immaterial, and finding a row by its rank costs a workgroup half a microsecond
-    const int sort_rows = total > 256 * (BS == 64 ? 4 : 8);
-    auto launch = [&](auto kernel, auto at) {
-        kernel<<<dim3((unsigned)total), dim3(BS * 4), 0, st>>>(
+    RowCut cut;
+    if (s.fwd_room) cut = RowCut(s, nnzb);
+    // where all workgroups run at once their order is immaterial, and finding a row by its rank costs one half a microsecond
+    const int sort_rows = total > fwd_resident(BS);
+    auto launch = [&](auto kernel, auto at, auto cut_arg) {
+        kernel<<<dim3((unsigned)(cut.groups + total)), dim3(BS * 4), 0, st>>>(
             static_cast<const bf16_t*>(Q), static_cast<const bf16_t*>(K), static_cast<const bf16_t*>(V),
-            static_cast<bf16_t*>(O), LSE, row_ptr, col_idx, at, s.L, s.nb, total, sort_rows, s.scale * kLog2e,
+            static_cast<bf16_t*>(O), LSE, row_ptr, col_idx, at, cut_arg, s.L, s.nb, total, sort_rows, s.scale * kLog2e,
             s.paper_denom);
     };
-    if (s.heads_beside) launch(attn_fwd_bf16_kernel<BS, true>, HeadRows<true>{s.heads_beside});
-    else launch(attn_fwd_bf16_kernel<BS, false>, HeadRows<false>{0});
+    if (s.heads_beside) {
+        if (cut.slots) launch(attn_fwd_bf16_kernel<BS, true, true>, HeadRows<true>{s.heads_beside}, cut);
+        else launch(attn_fwd_bf16_kernel<BS, true, false>, HeadRows<true>{s.heads_beside}, NoCut{});
+    } else {
+        if (cut.slots) launch(attn_fwd_bf16_kernel<BS, false, true>, HeadRows<false>{0}, cut);
+        else launch(attn_fwd_bf16_kernel<BS, false, false>, HeadRows<false>{0}, NoCut{});
+    }
     return hipGetLastError();
 }
 
 template hipError_t fwd_bf16<32>(const AttnShape&, const void*, const void*, const void*, void*, float*,
-                                 const int*, const int*, hipStream_t);
+                                 const int*, const int*, int, hipStream_t);
 template hipError_t fwd_bf16<64>(const AttnShape&, const void*, const void*, const void*, void*, float*,
-                                 const int*, const int*, hipStream_t);
+                                 const int*, const int*, int, hipStream_t);
 
 }  // namespace spion

@@ -11,6 +11,7 @@
 #include <stdint.h>
 
 #include "attn_common.h"
+#include "spion_internal.h"
 
 namespace spion {
 
@@ -243,6 +244,80 @@ __device__ __forceinline__ RowOfHead long_rows_first(const int* __restrict__ row
         rank -= members;
     }
     return {0, head};
+}
+
+// ------------------------------------------------------------------------------------------------
+// Long rows in pieces.  A block row is one chain of steps; patterns have a row or two of several times the mean, up to
+// half the columns, and where there are few heads such a chain outlasts everything else: 8 heads x 8192, block 32, 13
+// blocks a row and two rows of 120: 44 us, 14 without those rows.  A row of more than `longest` blocks is cut into pieces
+// of about `piece`, as long as a head's pieces fit into `slots`: what is cut depends on the pattern alone, so that a head
+// comes out the same whatever is computed beside it.  The row's own workgroup takes the first piece; `helpers` workgroups of
+// each head, which come first in the grid, take the others in turn.  Every workgroup finds the same cuts from row_ptr.
+// Each piece leaves its accumulators, reference and sum in memory; the workgroup that is the last of its row to do so adds
+// up the pieces in their order (the same bits whoever that is) and writes the row.  Nobody waits for anybody.
+// ------------------------------------------------------------------------------------------------
+struct RowPieces {
+    int row;      // -1: none
+    int count;    // pieces of the row, 1: not cut
+    int first;    // number of its second piece among the head's pieces that are not the first of their row
+    int slot;     // of its first piece
+};
+// The row that piece number `want`, not the first of its row, belongs to, or (BY_ROW) row number `want`.  All lanes
+// active, the result uniform.
+template <bool BY_ROW>
+__device__ __forceinline__ RowPieces row_pieces(const int* __restrict__ row_ptr, int nb, const RowCut& cut, int want, int lane) {
+    int others = 0, cut_rows = 0;   // pieces (not the first of a row) and long rows before this group of 64 rows
+    for (int base = 0; base < nb; base += 64) {
+        const int r = base + lane;
+        const int cnt = r < nb ? row_ptr[r + 1] - row_ptr[r] : 0;
+        const int count = cnt > cut.longest ? (cnt + cut.piece - 1) / cut.piece : 1;
+        const int incl = others + wave_incl_scan(count - 1, lane), first = incl - (count - 1);
+        const unsigned long long longs = __ballot(count > 1);
+        const unsigned long long hit = __ballot(BY_ROW ? r == want : count > 1 && want >= first && want < incl);
+        if (hit) {
+            const int src = __ffsll((long long)hit) - 1;
+            const int c = __builtin_amdgcn_readlane(count, src), f = __builtin_amdgcn_readlane(first, src);
+            const int slot = f + cut_rows + (int)__popcll(longs & ((1ull << src) - 1ull));
+            if (c == 1 || slot + c > cut.slots) return {BY_ROW ? want : -1, 1, 0, 0};   // too many pieces: the row stays whole
+            return {base + src, c, f, slot};
+        }
+        others = __builtin_amdgcn_readlane(incl, 63);
+        cut_rows += (int)__popcll(longs);
+    }
+    return {-1, 1, 0, 0};
+}
+
+// Partial results go between workgroups, which may be on different XCDs, by accesses of device scope: past the L2 to where
+// all XCDs meet.  (Plain accesses with a release and an acquire around the counter write a whole L2 back and drop what it
+// holds, tiles of everyone's K and V, for every piece: 64 heads x 4160, block 32, 384 pieces: 36 us uncut, 55 so.)
+__device__ __forceinline__ void put_shared(float* p, float a, float b) {
+    const unsigned long long v = (unsigned long long)__builtin_bit_cast(unsigned, b) << 32 | __builtin_bit_cast(unsigned, a);
+    __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float2 get_shared(const float* p) {
+    const unsigned long long v = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return make_float2(__builtin_bit_cast(float, (unsigned)v), __builtin_bit_cast(float, (unsigned)(v >> 32)));
+}
+
+// Counts the calling workgroup's piece at *counter; whether it is the last of `count`.  What the others' waves have
+// put_shared before their calls, every wave can get_shared after it then.  The counter holds the launch's tag and the pieces
+// that have arrived, or whatever else is in the room when the first one comes; the last one clears it, for a launch
+// with the same tag (a graph that is replayed).  All threads; `flag` is in LDS.
+__device__ __forceinline__ bool last_to_arrive(unsigned long long* counter, unsigned long long tag, int count, int* flag) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's stores are done, at device scope
+    __syncthreads();                                   // and those of the others
+    if (threadIdx.x == 0) {
+        unsigned long long seen = __hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), next;
+        do {
+            next = seen >> 16 == tag ? seen + 1 : tag << 16 | 1;
+        } while (!__hip_atomic_compare_exchange_strong(counter, &seen, next, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        const bool last = (int)(next & 0xffff) == count;
+        if (last) __hip_atomic_store(counter, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *flag = last;
+    }
+    __syncthreads();
+    asm volatile("" ::: "memory");   // nothing of the others' is read before
+    return *flag != 0;
 }
 
 }  // namespace spion

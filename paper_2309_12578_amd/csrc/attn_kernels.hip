@@ -657,7 +657,7 @@ template <typename T, int BS>
 static hipError_t fwd_t(const AttnShape& s, const void* Q, const void* K, const void* V, void* O,
                         float* LSE, const int* row_ptr, const int* col_idx, int nnzb, hipStream_t st) {
     if constexpr (sizeof(T) == 2 && BS >= 32) {
-        return fwd_bf16<BS>(s, Q, K, V, O, LSE, row_ptr, col_idx, st);
+        return fwd_bf16<BS>(s, Q, K, V, O, LSE, row_ptr, col_idx, nnzb, st);
     } else {
         if (many_short_rows(s, nnzb))
             return launch_fwd<T, BS, typename SplitMany<T, BS>::fwd>(s, Q, K, V, O, LSE, row_ptr, col_idx, st);

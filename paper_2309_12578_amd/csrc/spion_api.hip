@@ -117,7 +117,22 @@ spion::AttnShape make_shape(const spion_attn_params* p) {
     s.bwd_phases = (p->flags & SPION_ATTN_BWD_QUERY_SIDE_ONLY) ? 1
                    : (p->flags & SPION_ATTN_BWD_KEY_SIDE_ONLY) ? 2 : 3;
     s.heads_beside = 0;
+    s.fwd_room = nullptr;
+    s.fwd_tag = 0;
     return s;
+}
+
+// Tags the launches whose workgroups meet in a room: no two of a process have the same one, and a tag is not a number
+// that memory is likely to hold.
+std::atomic<unsigned long long> g_tag{1};
+int give_room(spion::AttnShape& s, int32_t nnzb, void* room, size_t room_bytes) {
+    if (!room) return SPION_OK;
+    const size_t need = spion::RowCut(s, nnzb).room_bytes(s.BH, s.bs);
+    if (need == 0) return SPION_OK;
+    if ((uintptr_t)room % kAlign != 0 || room_bytes < need) return SPION_ERR_WORKSPACE;
+    s.fwd_room = room;
+    s.fwd_tag = g_tag.fetch_add(1, std::memory_order_relaxed) * 0x9e3779b97f4bull & ((1ull << 48) - 1ull);
+    return SPION_OK;
 }
 
 // Whether the kernels take the sub-layer's own tensors (the addresses or'ed together).
@@ -409,16 +424,30 @@ int spion_index_check(const int32_t* row_ptr, const int32_t* col_idx, const int3
     return SPION_OK;
 }
 
+size_t spion_attn_fwd_room_bytes(const spion_attn_params* p, int32_t nnzb) {
+    if (!p || attn_params_ok(p, nnzb) != SPION_OK) return 0;
+    const spion::AttnShape s = make_shape(p);
+    return spion::RowCut(s, nnzb).room_bytes(s.BH, s.bs);
+}
+
 int spion_attn_fwd(const void* Q, const void* K, const void* V, void* O, float* LSE,
                    const int32_t* row_ptr, const int32_t* col_idx, int32_t nnzb,
                    const spion_attn_params* p, void* workspace, size_t workspace_bytes,
                    void* hip_stream) {
     (void)workspace;
     (void)workspace_bytes;
+    return spion_attn_fwd_room(Q, K, V, O, LSE, row_ptr, col_idx, nnzb, p, nullptr, 0, hip_stream);
+}
+
+int spion_attn_fwd_room(const void* Q, const void* K, const void* V, void* O, float* LSE, const int32_t* row_ptr,
+                        const int32_t* col_idx, int32_t nnzb, const spion_attn_params* p, void* room, size_t room_bytes,
+                        void* hip_stream) {
     if (!Q || !K || !V || !O || !LSE || !row_ptr || !col_idx || !p) return SPION_ERR_NULL;
     const int rc = attn_params_ok(p, nnzb);
     if (rc != SPION_OK) return rc;
-    const spion::AttnShape s = make_shape(p);
+    spion::AttnShape s = make_shape(p);
+    const int room_rc = give_room(s, nnzb, room, room_bytes);
+    if (room_rc != SPION_OK) return room_rc;
     if (spion::launch_attn_fwd(s, Q, K, V, O, LSE, row_ptr, col_idx, nnzb,
                                static_cast<hipStream_t>(hip_stream)) != hipSuccess)
         return SPION_ERR_HIP;
@@ -447,11 +476,13 @@ int spion_attn_bwd(const void* Q, const void* K, const void* V, const void* O, c
 }
 
 int spion_heads_attn_fwd(const void* qkv, void* S, float* LSE, const int32_t* row_ptr, const int32_t* col_idx, int32_t nnzb,
-                         const spion_attn_params* p, void* hip_stream) {
+                         const spion_attn_params* p, void* room, size_t room_bytes, void* hip_stream) {
     if (!qkv || !S || !LSE || !row_ptr || !col_idx || !p) return SPION_ERR_NULL;
     const int rc = heads_beside_ok((uintptr_t)qkv | (uintptr_t)S, p, nnzb);
     if (rc != SPION_OK) return rc;
     spion::AttnShape s = make_shape(p);
+    const int room_rc = give_room(s, nnzb, room, room_bytes);
+    if (room_rc != SPION_OK) return room_rc;
     s.heads_beside = p->H;
     const uint16_t* const q = static_cast<const uint16_t*>(qkv);
     const size_t D = (size_t)p->H * 64;

@@ -36,11 +36,18 @@ int spion_layer_norm_grad(const void* dy, const void* dr, const void* x, const v
 int spion_heads(int32_t split, void* merged, void* const* t, int32_t B, int32_t L, int32_t H, int32_t n, int32_t dtype,
                 void* hip_stream);
 
-// spion_attn_fwd / spion_attn_bwd (p, workspace and index as there) on the sub-layer's own tensors: qkv and dqkv
+// spion_attn_fwd with room for the pieces of long block rows (0 bytes: none are cut), which only these two calls' kernels
+// use; room == NULL: as spion_attn_fwd.  Aligned to 256 bytes.
+size_t spion_attn_fwd_room_bytes(const spion_attn_params* p, int32_t nnzb);
+int spion_attn_fwd_room(const void* Q, const void* K, const void* V, void* O, float* LSE, const int32_t* row_ptr,
+                        const int32_t* col_idx, int32_t nnzb, const spion_attn_params* p, void* room, size_t room_bytes,
+                        void* hip_stream);
+
+// spion_attn_fwd_room / spion_attn_bwd (p, room, workspace and index as there) on the sub-layer's own tensors: qkv and dqkv
 // [B, L, 3, H, 64], S = O and dS [B, L, H, 64], LSE [B, H, L].  bf16 and block 32 or 64 only (else SPION_ERR_DTYPE,
 // SPION_ERR_SHAPE), tensors aligned to 16 bytes.
 int spion_heads_attn_fwd(const void* qkv, void* S, float* LSE, const int32_t* row_ptr, const int32_t* col_idx, int32_t nnzb,
-                         const spion_attn_params* p, void* hip_stream);
+                         const spion_attn_params* p, void* room, size_t room_bytes, void* hip_stream);
 int spion_heads_attn_bwd(const void* qkv, const void* S, const void* dS, const float* LSE, void* dqkv, const int32_t* row_ptr,
                          const int32_t* col_idx, const int32_t* col_ptr, const int32_t* row_idx, int32_t nnzb,
                          const spion_attn_params* p, void* workspace, size_t workspace_bytes, void* hip_stream);

@@ -39,6 +39,25 @@ struct AttnShape {
     int paper_denom;    // Algorithm 6's extra denominator term
     int bwd_phases;     // bit 0: query side (dQ); bit 1: key side (dK, dV)
     int heads_beside;   // 0: tensors [B, H, L, 64]; else H, and rows as HeadRows<true> (bf16, block 32 and 64 only)
+    void* fwd_room;     // forward: device memory of RowCut::room_bytes() for the pieces of long rows, or nullptr: rows stay whole
+    unsigned long long fwd_tag;   // of this launch alone, 1 .. 2^48 - 1
+};
+
+// How the tuned forward cuts long block rows (see attn_bf16_tiles.h), from what the host knows of a pattern.
+struct RowCut {
+    int piece = 0;     // kept blocks of a piece, at most
+    int longest = 0;   // a row of more is cut
+    int slots = 0;     // pieces per head that there is room for; 0: no row is cut
+    int helpers = 0;   // workgroups per head for the pieces behind the first of each row
+    int groups = 0;    // of all heads, a multiple of 8
+    unsigned long long tag = 0;
+    unsigned long long* counters = nullptr;   // [head][slots], in use: that of a row's first piece
+    float* parts = nullptr;                   // partial results, as many
+    RowCut() = default;
+    RowCut(const AttnShape& s, int nnzb);
+    size_t counter_bytes(int BH) const { return ((size_t)BH * slots * 8 + 255) / 256 * 256; }
+    static constexpr size_t partial_bytes(int bs) { return (size_t)(bs / 16) * 64 * 18 * sizeof(float); }   // O, maximum, sum
+    size_t room_bytes(int BH, int bs) const { return slots ? counter_bytes(BH) + (size_t)BH * slots * partial_bytes(bs) : 0; }
 };
 
 hipError_t launch_attn_fwd(const AttnShape& s, const void* Q, const void* K, const void* V, void* O,
@@ -80,7 +99,7 @@ hipError_t launch_heads(bool split, void* merged, void* const* t, int B, int L, 
 // attn_bf16_kernels.hip: tuned bf16 forward, BS in {32, 64}
 template <int BS>
 hipError_t fwd_bf16(const AttnShape& s, const void* Q, const void* K, const void* V, void* O, float* LSE,
-                    const int* row_ptr, const int* col_idx, hipStream_t st);
+                    const int* row_ptr, const int* col_idx, int nnzb, hipStream_t st);
 
 // attn_bwd_bf16_kernels.hip: tuned bf16 backward, BS in {32, 64}; both sides in one launch plus the
 // reduction of the partial tiles of split block columns

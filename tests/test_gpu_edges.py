@@ -138,6 +138,58 @@ def test_generic_kernels_rows_by_length(sp, dtype, block, BH, nb):
     _attention(sp, Q, K, V, dO, fl, block, dtype, [0, BH // 2, BH - 1])
 
 
+# bf16, more than 64 block rows: rows of more than four times the mean (and 24) are cut into pieces that other workgroups take:
+# two pieces and many; more pieces than there is room for (32 a head), a helper for each, for several, two a head (130
+# heads); no diagonal block, in the first piece or a later one; the last row; an empty row beside them; 64 block rows: none cut
+@pytest.mark.parametrize("block", [32, 64])
+@pytest.mark.parametrize("BH,nb,longs", [(1, 65, (65,)), (1, 70, (25, 24)), (3, 80, (80, 37, 25, 24)), (2, 130, (130, 64, 65, 129)),
+                                         (64, 72, (72, 72, 72, 30)), (130, 66, (60, 26)), (5, 64, (64, 30))])
+@pytest.mark.parametrize("denom", [False, True])
+def test_long_rows_in_pieces(sp, block, BH, nb, longs, denom):
+    rng = np.random.default_rng(nb + BH)
+    Q, K, V, dO = [si.round_to_dtype(rng.standard_normal((BH, nb * block, 64), dtype=np.float32), "bf16") for _ in range(4)]
+    K[:, : block] += 3.0   # scores that run away from those of the other pieces
+    K = si.round_to_dtype(K, "bf16")
+    fl = np.eye(nb, dtype=np.uint8)
+    rows = rng.choice(nb, len(longs), replace=False)
+    for r, n in zip(rows, longs):
+        fl[r] = 0
+        fl[r, rng.choice(nb, n, replace=False)] = 1
+    fl[(rows[0] + 1) % nb] *= rows[0] + 1 == rows[-1]
+    _attention(sp, Q, K, V, dO, fl, block, "bf16", sorted({0, BH // 2, BH - 1}), flags=sp.SPION_ATTN_PAPER_DENOM if denom else 0)
+
+
+def test_long_rows_in_pieces_again_and_in_a_graph(sp):
+    """Whichever piece is the last to arrive: the same bits every time, and in replays, which share their launches' tags, on other
+    inputs and with other work in between."""
+    from test_gpu_parity import _pattern_from_mask
+    nb, block = 96, 32
+    fl = np.eye(nb, dtype=np.uint8)
+    fl[[5, 50], :] = 1
+    pat = _pattern_from_mask(sp, fl, block)
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    q, k, v = [torch.randn((2, 3, nb * block, 64), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3)]
+    O, LSE = [t.clone() for t in sp.attn_fwd(q, k, v, pat)]
+    for _ in range(20):
+        o, lse = sp.attn_fwd(q, k, v, pat)
+        assert torch.equal(o, O) and torch.equal(lse, LSE)
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        sp.attn_fwd(q, k, v, pat)
+    torch.cuda.current_stream().wait_stream(s)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        o, lse = sp.attn_fwd(q, k, v, pat)
+    for i in range(5):
+        for t in (q, k, v):
+            t.copy_(torch.randn(t.shape, generator=gen, device="cuda"))
+        g.replay()
+        torch.cuda.synchronize()
+        eager, eager_lse = sp.attn_fwd(q, k, v, pat)
+        assert torch.equal(o, eager) and torch.equal(lse, eager_lse)
+
+
 # The kernels of fp32 and of block size 16 share a row's tiles over the waves of a workgroup by the average number of
 # tiles and the number of rows: (heads, block rows, density) for four waves a row, for few, and for rows of one
 # block; with rows and columns of 0, 1, 2, 65 and more blocks, odd numbers of tiles, split columns, and head
