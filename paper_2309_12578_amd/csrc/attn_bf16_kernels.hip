@@ -307,7 +307,7 @@ RowCut::RowCut(const AttnShape& s, int nnzb) {
     if (helpers >= slots) helpers = slots > 0 ? slots - 1 : 0;
     groups = (s.BH * helpers + 7) & ~7;
     if ((long long)s.BH * s.nb + groups > 0x7fffffffll) slots = helpers = groups = 0;   // workgroups of a launch
-    tag = s.fwd_tag;
+    tag = s.tag;
     if (!s.fwd_room) return;
     counters = static_cast<unsigned long long*>(s.fwd_room);
     parts = reinterpret_cast<float*>(static_cast<char*>(s.fwd_room) + counter_bytes(s.BH));

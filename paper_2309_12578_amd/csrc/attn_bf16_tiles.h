@@ -301,7 +301,7 @@ __device__ __forceinline__ float2 get_shared(const float* p) {
 
 // Counts the calling workgroup's piece at *counter; whether it is the last of `count`.  What the others' waves have
 // put_shared before their calls, every wave can get_shared after it then.  The counter holds the launch's tag and the pieces
-// that have arrived, or whatever else is in the room when the first one comes; the last one clears it, for a launch
+// that have arrived, or whatever else is in the memory when the first one comes; the last one clears it, for a launch
 // with the same tag (a graph that is replayed).  All threads; `flag` is in LDS.
 __device__ __forceinline__ bool last_to_arrive(unsigned long long* counter, unsigned long long tag, int count, int* flag) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's stores are done, at device scope

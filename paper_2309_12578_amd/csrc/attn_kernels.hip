@@ -590,8 +590,10 @@ BwdWorkspace::BwdWorkspace(int BH, int bs, int nb, int nnzb_, int key_chunk, int
     if (w_first > w_max) w_first = w_max;
     n_slots = 2 * (nnzb / chunk) + 2;
     split_max = nb > chunk ? nnzb / (chunk + 1) : 0;
-    // for the shortest chunks, so that a workspace for more kept blocks also serves fewer; a multiple of 256
-    total = (size_t)BH * (2 * (nnzb / kChunk) + 2) * 2 * bs * kD * sizeof(float);
+    // for the shortest chunks, so that a workspace for more kept blocks also serves fewer; multiples of 256
+    const size_t slots = (size_t)BH * (2 * (nnzb / kChunk) + 2);
+    counter_bytes = (slots * 8 + 255) / 256 * 256;
+    total = counter_bytes + slots * 2 * bs * kD * sizeof(float);
 }
 
 size_t attn_bwd_workspace_bytes(int BH, int bs, int nb, int nnzb) { return BwdWorkspace(BH, bs, nb, nnzb, kChunk, 0).total; }
@@ -650,7 +652,7 @@ static hipError_t launch_bwd(const AttnShape& s, const void* Q, const void* K, c
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    return keys ? launch_bwd_reduce<T, BS, false>(s, ws, partial, col_ptr, dK, dV, st) : hipSuccess;
+    return keys ? launch_bwd_reduce<T, BS>(s, ws, partial, col_ptr, dK, dV, st) : hipSuccess;
 }
 
 template <typename T, int BS>
@@ -676,12 +678,12 @@ static hipError_t bwd_t(const AttnShape& s, const void* Q, const void* K, const 
                         const void* dO, const float* LSE, void* dQ, void* dK, void* dV,
                         const int* row_ptr, const int* col_idx, const int* col_ptr, const int* row_idx,
                         int nnzb, void* workspace, hipStream_t st) {
-    float* partial = static_cast<float*>(workspace);
     if constexpr (sizeof(T) == 2 && BS >= 32) {
         const BwdWorkspace ws(s.BH, s.bs, s.nb, nnzb, key_chunk(s.BH, BS, s.nb, nnzb), s.nb / 4);
-        return bwd_bf16<BS>(s, Q, K, V, O, dO, LSE, dQ, dK, dV, row_ptr, col_idx, col_ptr, row_idx, ws, partial, st);
+        return bwd_bf16<BS>(s, Q, K, V, O, dO, LSE, dQ, dK, dV, row_ptr, col_idx, col_ptr, row_idx, ws, workspace, st);
     } else {
         const BwdWorkspace ws(s.BH, s.bs, s.nb, nnzb, kChunk, 0);
+        float* const partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + ws.counter_bytes);
         auto* launch = launch_bwd<T, BS, SplitFew<T, BS>>;
         if (many_short_rows(s, nnzb))
             launch = single_block_rows(s, nnzb) ? launch_bwd<T, BS, typename SplitMany<T, BS>::bwd_single>

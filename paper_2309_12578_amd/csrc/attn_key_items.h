@@ -49,15 +49,16 @@ struct KeyItem {
     int J;      // block column, -1: no such item
     int kb, ke; // BSC entries [kb, ke)
     int slot;   // partial slot, -1: the item covers its whole column and writes dK / dV itself
+    int first, count;   // slot of the column's first chunk, its chunks
 };
 
 // All lanes of the calling wave must be active; the result is wave-uniform.  MID_FIRST: see kMidColumn.
 template <bool MID_FIRST>
 __device__ __forceinline__ KeyItem key_item_lookup(const int* __restrict__ col_ptr, int nb, int chunk, int w, int lane) {
-    KeyItem none = {-1, 0, 0, -1};
+    KeyItem none = {-1, 0, 0, -1, 0, 1};
     if (nb <= (MID_FIRST ? kMidColumn : chunk)) {   // all alike
         if (w >= nb) return none;
-        KeyItem it = {w, col_ptr[w], col_ptr[w + 1], -1};
+        KeyItem it = {w, col_ptr[w], col_ptr[w + 1], -1, 0, 1};
         return it;
     }
     int run = 0;     // chunks of split columns in the column groups before this one
@@ -79,9 +80,10 @@ __device__ __forceinline__ KeyItem key_item_lookup(const int* __restrict__ col_p
             const int src = __ffsll((long long)hit) - 1;
             const int c0s = __builtin_amdgcn_readlane(c0, src), cnts = __builtin_amdgcn_readlane(cnt, src);
             const int nchs = __builtin_amdgcn_readlane(nch, src);
-            int ci = w - __builtin_amdgcn_readlane(lo, src);
+            const int first = __builtin_amdgcn_readlane(lo, src);
+            int ci = w - first;
             ci = ci < 0 ? 0 : (ci >= nchs ? nchs - 1 : ci);
-            KeyItem it = {base + src, c0s + (ci * cnts) / nchs, c0s + ((ci + 1) * cnts) / nchs, w};
+            KeyItem it = {base + src, c0s + (ci * cnts) / nchs, c0s + ((ci + 1) * cnts) / nchs, w, first, nchs};
             return it;
         }
         run += __builtin_amdgcn_readlane(incl, 63);
@@ -103,7 +105,7 @@ __device__ __forceinline__ KeyItem key_item_lookup(const int* __restrict__ col_p
         const unsigned long long hit = __ballot(in && lanes_below(members) == u);
         if (hit) {
             const int src = __ffsll((long long)hit) - 1;
-            KeyItem it = {base + src, __builtin_amdgcn_readlane(c0, src), __builtin_amdgcn_readlane(c1, src), -1};
+            KeyItem it = {base + src, __builtin_amdgcn_readlane(c0, src), __builtin_amdgcn_readlane(c1, src), -1, 0, 1};
             return it;
         }
         u -= __popcll(members);
@@ -137,10 +139,10 @@ __device__ __forceinline__ int4 split_column_lookup(const int* __restrict__ col_
 // Adds the partial tiles of every split block column, in chunk order.  Workgroup = (head, m-th split
 // column, part): 256 threads, one float4 of the output tile each, bs / 16 parts per tile, so that the
 // loads of all chunks of a float4 are in flight together.
-template <typename T, int BS, bool BESIDE>
+template <typename T, int BS>
 __global__ __launch_bounds__(256) void attn_bwd_reduce_kernel(
     const float* __restrict__ partial, const int* __restrict__ col_ptr, int nb, int chunk, int split_max, int n_slots,
-    T* __restrict__ dK, T* __restrict__ dV, HeadRows<BESIDE> at, int L, float scale) {
+    T* __restrict__ dK, T* __restrict__ dV, int L, float scale) {
     constexpr int PARTS = BS / 16;
     const int part = blockIdx.x % PARTS, m = (blockIdx.x / PARTS) % split_max;
     const int bh = blockIdx.x / (PARTS * split_max);
@@ -154,19 +156,18 @@ __global__ __launch_bounds__(256) void attn_bwd_reduce_kernel(
         ak += *reinterpret_cast<const f32x4*>(pk + (size_t)c * (2 * BS * kD));
         av += *reinterpret_cast<const f32x4*>(pk + (size_t)c * (2 * BS * kD) + BS * kD);
     }
-    const int row = info.x * BS + v / (kD / 4);
-    const size_t out = at.in_head(bh, L) + (size_t)row * at.in_row() + v % (kD / 4) * 4;
+    const size_t out = ((size_t)bh * L + info.x * BS) * kD + v * 4;
     store_quad<T>(dK + out, ak * scale);
     store_quad<T>(dV + out, av);
 }
 
-template <typename T, int BS, bool BESIDE>
+template <typename T, int BS>
 hipError_t launch_bwd_reduce(const AttnShape& s, const BwdWorkspace& ws, const float* partial,
                              const int* col_ptr, void* dK, void* dV, hipStream_t st) {
     if (ws.split_max == 0) return hipSuccess;
-    attn_bwd_reduce_kernel<T, BS, BESIDE><<<dim3((unsigned)(ws.split_max * s.BH * (BS / 16))), dim3(256), 0, st>>>(
+    attn_bwd_reduce_kernel<T, BS><<<dim3((unsigned)(ws.split_max * s.BH * (BS / 16))), dim3(256), 0, st>>>(
         partial, col_ptr, s.nb, ws.chunk, ws.split_max, ws.n_slots, static_cast<T*>(dK), static_cast<T*>(dV),
-        HeadRows<BESIDE>{s.heads_beside}, s.L, s.scale);
+        s.L, s.scale);
     return hipGetLastError();
 }
 

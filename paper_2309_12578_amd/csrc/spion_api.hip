@@ -105,6 +105,10 @@ int attn_params_ok(const spion_attn_params* p, int32_t nnzb) {
     return SPION_OK;
 }
 
+// Tags the calls whose workgroups meet in device memory: no two of a process have the same one, and a tag is not a number
+// that memory is likely to hold.
+std::atomic<unsigned long long> g_tag{1};
+
 spion::AttnShape make_shape(const spion_attn_params* p) {
     spion::AttnShape s;
     s.BH = p->B * p->H;
@@ -118,20 +122,16 @@ spion::AttnShape make_shape(const spion_attn_params* p) {
                    : (p->flags & SPION_ATTN_BWD_KEY_SIDE_ONLY) ? 2 : 3;
     s.heads_beside = 0;
     s.fwd_room = nullptr;
-    s.fwd_tag = 0;
+    s.tag = g_tag.fetch_add(1, std::memory_order_relaxed) * 0x9e3779b97f4bull & ((1ull << 48) - 1ull);
     return s;
 }
 
-// Tags the launches whose workgroups meet in a room: no two of a process have the same one, and a tag is not a number
-// that memory is likely to hold.
-std::atomic<unsigned long long> g_tag{1};
 int give_room(spion::AttnShape& s, int32_t nnzb, void* room, size_t room_bytes) {
     if (!room) return SPION_OK;
     const size_t need = spion::RowCut(s, nnzb).room_bytes(s.BH, s.bs);
     if (need == 0) return SPION_OK;
     if ((uintptr_t)room % kAlign != 0 || room_bytes < need) return SPION_ERR_WORKSPACE;
     s.fwd_room = room;
-    s.fwd_tag = g_tag.fetch_add(1, std::memory_order_relaxed) * 0x9e3779b97f4bull & ((1ull << 48) - 1ull);
     return SPION_OK;
 }
 

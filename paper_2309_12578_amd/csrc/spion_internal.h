@@ -40,7 +40,7 @@ struct AttnShape {
     int bwd_phases;     // bit 0: query side (dQ); bit 1: key side (dK, dV)
     int heads_beside;   // 0: tensors [B, H, L, 64]; else H, and rows as HeadRows<true> (bf16, block 32 and 64 only)
     void* fwd_room;     // forward: device memory of RowCut::room_bytes() for the pieces of long rows, or nullptr: rows stay whole
-    unsigned long long fwd_tag;   // of this launch alone, 1 .. 2^48 - 1
+    unsigned long long tag;       // of this call alone, 1 .. 2^48 - 1 (see last_to_arrive)
 };
 
 // How the tuned forward cuts long block rows (see attn_bf16_tiles.h), from what the host knows of a pattern.
@@ -73,6 +73,7 @@ struct BwdWorkspace {
     int chunk;                       // most kept rows of a key-side work item
     int w_max, w_first;              // work items per head (upper bound); those that may be chunks come first
     int n_slots, split_max;          // partial slots per head, split columns (upper bounds)
+    size_t counter_bytes;            // one per slot, at the workspace's start; the partial tiles behind them
     size_t total;
     // mid_first: unsplit columns to make room for among the items that come first
     BwdWorkspace(int BH, int bs, int nb, int nnzb, int key_chunk, int mid_first);
@@ -101,13 +102,12 @@ template <int BS>
 hipError_t fwd_bf16(const AttnShape& s, const void* Q, const void* K, const void* V, void* O, float* LSE,
                     const int* row_ptr, const int* col_idx, int nnzb, hipStream_t st);
 
-// attn_bwd_bf16_kernels.hip: tuned bf16 backward, BS in {32, 64}; both sides in one launch plus the
-// reduction of the partial tiles of split block columns
+// attn_bwd_bf16_kernels.hip: tuned bf16 backward, BS in {32, 64}; both sides in one launch
 template <int BS>
 hipError_t bwd_bf16(const AttnShape& s, const void* Q, const void* K, const void* V, const void* O,
                     const void* dO, const float* LSE, void* dQ, void* dK, void* dV, const int* row_ptr,
                     const int* col_idx, const int* col_ptr, const int* row_idx, const BwdWorkspace& ws,
-                    float* partial, hipStream_t st);
+                    void* workspace, hipStream_t st);
 
 }  // namespace spion
 #endif
