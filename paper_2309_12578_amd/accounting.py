@@ -59,9 +59,3 @@ def algorithmic_bytes(kernel: str, bh: int, L: int, d: int, elem_bytes: int) -> 
     if kernel == "path":
         return 12 * t + 2 * vec
     raise ValueError(kernel)
-
-
-def backward_launches(bh: int, bs: int, nb: int, nnzb: int, dtype: str) -> int:
-    """Launches of one spion_attn_bwd: in fp32 and with block 16, 2 with the reduction of partial tiles, which is left out
-    where no block column can have more kept rows than a work item takes (kChunk in csrc/attn_key_items.h)."""
-    return 1 if (dtype == "bf16" and bs >= 32) or min(nb, nnzb) <= 16 else 2

@@ -341,14 +341,15 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_bwd_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, const T* __restrict__ O,
     const T* __restrict__ dO, const float* __restrict__ LSE, T* __restrict__ dQ, T* __restrict__ dK,
     T* __restrict__ dV, const int* __restrict__ row_ptr, const int* __restrict__ col_idx,
-    const int* __restrict__ col_ptr, const int* __restrict__ row_idx, float* __restrict__ partial, int n_slots,
-    int BH, int L, int nb, int n_key_a, int n_rows, int n_key_c, int w_first, int chunk, int sort_rows, float scale,
-    float scale_log2) {
+    const int* __restrict__ col_ptr, const int* __restrict__ row_idx, float* __restrict__ partial,
+    unsigned long long* __restrict__ counters, unsigned long long tag, int n_slots, int BH, int L, int nb, int n_key_a,
+    int n_rows, int n_key_c, int w_first, int chunk, int sort_rows, float scale, float scale_log2) {
     typedef typename Elem<T>::Frag Frag;
     typedef typename Elem<T>::Quad Quad;
     typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
     constexpr int NQ = S::NQ, KT = S::KT, NDC = S::NDC, OWN = S::OWN;
     __shared__ __attribute__((aligned(16))) float acc_s[S::WT][OWN * kPatchLd];
+    __shared__ int flag;
 
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wt = wave % S::WT, own = wave / S::WT * (16 * NQ);
@@ -548,20 +549,56 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_bwd_kernel(
         mma_cols(dv, dc, pq);    // dV^T += dO^T P
         mma_cols(dk, qc, dsq);   // dK^T += Q^T dS
     }
-    // final rows, or this chunk's fp32 partial tiles [head][slot][dK | dV][bs][64], unscaled
-    float* const pk = partial + ((size_t)bh * n_slots + (it.slot < 0 ? 0 : it.slot)) * (2 * BS * kD);
-    if constexpr (S::WT == 1) {
-#pragma unroll
-        for (int h = 0; h < NQ; ++h) {
-            const size_t o = (size_t)(sub + own + h * 16 + r) * kD, at = head + (size_t)it.J * BS * kD + o;
-            if (it.slot >= 0) {
-                store_acc<float>(pk + o, dk[h], 1.f, g);
-                store_acc<float>(pk + BS * kD + o, dv[h], 1.f, g);
-            } else {
-                store_acc<T>(dK + at, dk[h], scale, g);
-                store_acc<T>(dV + at, dv[h], 1.f, g);
-            }
+    // Final rows, or this chunk's fp32 partial tiles [head][slot][dK | dV][bs][64], unscaled: of a column's chunks, the
+    // last to arrive with these rows adds all of them up, in their order (a launch for the sums took 4.3 to 5 us; these take
+    // none to 2: bf16, 9 x 1936, 8 %, backward 28.8 + 4.7 -> 29.4 us, 24 x 1168, 8 %, 25.3 + 4.7 -> 27.1).
+    constexpr int kPart = 2 * BS * kD;
+    float* const parts = partial + ((size_t)bh * n_slots + it.first) * kPart;
+    float* const pk = parts + (size_t)(it.slot - it.first) * kPart;   // read where slot >= 0
+    const size_t column = head + (size_t)it.J * BS * kD;
+    auto put = [&](float* p, f32x4 v) {
+        put_shared(p, v[0], v[1]);
+        put_shared(p + 2, v[2], v[3]);
+    };
+    auto last = [&] {
+        return last_to_arrive(counters + ((size_t)bh * n_slots + it.first) * (BS / 16) + sub / OWN, tag, it.count, &flag);
+    };
+    auto add_up = [&](int o) {   // four numbers of dK and of dV
+        f32x4 ak = f32x4{0.f, 0.f, 0.f, 0.f}, av = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+        for (int c = 0; c < it.count; ++c) {
+            const float* p = parts + (size_t)c * kPart + o;
+            const float2 k0 = get_shared(p), k1 = get_shared(p + 2);
+            const float2 v0 = get_shared(p + BS * kD), v1 = get_shared(p + BS * kD + 2);
+            ak += f32x4{k0.x, k0.y, k1.x, k1.y};
+            av += f32x4{v0.x, v0.y, v1.x, v1.y};
         }
+        store_quad<T>(dK + column + o, ak * scale);
+        store_quad<T>(dV + column + o, av);
+    };
+    if constexpr (S::WT == 1) {
+        const int o = (sub + own + r) * kD;
+        if (it.slot < 0) {
+#pragma unroll
+            for (int h = 0; h < NQ; ++h) {
+                store_acc<T>(dK + column + (o + h * 16 * kD), dk[h], scale, g);
+                store_acc<T>(dV + column + (o + h * 16 * kD), dv[h], 1.f, g);
+            }
+            return;
+        }
+#pragma unroll
+        for (int h = 0; h < NQ; ++h)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {   // as store_acc
+                float* const p = pk + o + h * 16 * kD + 16 * g + 4 * i;
+                put(p, f32x4{dk[h][0][i], dk[h][1][i], dk[h][2][i], dk[h][3][i]});
+                put(p + BS * kD, f32x4{dv[h][0][i], dv[h][1][i], dv[h][2][i], dv[h][3][i]});
+            }
+        if (!last()) return;
+#pragma unroll
+        for (int h = 0; h < NQ; ++h)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) add_up(o + h * 16 * kD + 16 * g + 4 * i);
         return;
     }
 #pragma unroll
@@ -573,10 +610,13 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_bwd_kernel(
         for (int p = 0; p < OWN; p += 4 * S::W) {
             const f32x4 v = merged(p);
             const int o = p * kD + out;
-            if (it.slot >= 0) *reinterpret_cast<f32x4*>(pk + which * BS * kD + o) = v;
-            else store_quad<T>((which ? dV : dK) + head + (size_t)it.J * BS * kD + o, which ? v : v * scale);
+            if (it.slot >= 0) put(pk + which * BS * kD + o, v);
+            else store_quad<T>((which ? dV : dK) + column + o, which ? v : v * scale);
         }
     }
+    if (it.slot < 0 || !last()) return;
+#pragma unroll
+    for (int p = 0; p < OWN; p += 4 * S::W) add_up(p * kD + out);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -589,10 +629,9 @@ BwdWorkspace::BwdWorkspace(int BH, int bs, int nb, int nnzb_, int key_chunk, int
     w_first = nnzb / chunk + 1 + mid_first;
     if (w_first > w_max) w_first = w_max;
     n_slots = 2 * (nnzb / chunk) + 2;
-    split_max = nb > chunk ? nnzb / (chunk + 1) : 0;
     // for the shortest chunks, so that a workspace for more kept blocks also serves fewer; multiples of 256
     const size_t slots = (size_t)BH * (2 * (nnzb / kChunk) + 2);
-    counter_bytes = (slots * 8 + 255) / 256 * 256;
+    counter_bytes = (slots * (bs / 16) * 8 + 255) / 256 * 256;
     total = counter_bytes + slots * 2 * bs * kD * sizeof(float);
 }
 
@@ -602,7 +641,7 @@ bool attn_bwd_grids_fit(int BH, int bs, int nb, int nnzb) {
     const BwdWorkspace ws(BH, bs, nb, nnzb, kChunk, 0);
     const int64_t limit = 0x7fffffffll, parts = bs == 64 ? 2 : 1;
     return (int64_t)(ws.w_max + nb) * BH * parts + 24 <= limit &&
-           (int64_t)ws.split_max * BH * (bs / 16) <= limit;
+           (int64_t)(nb > kChunk ? nnzb / (kChunk + 1) : 0) * BH * (bs / 16) <= limit;   // rows of cut columns
 }
 
 // Rows with hardly more than one block each (the diagonal): no long chain to cut anywhere.
@@ -631,7 +670,9 @@ template <typename T, int BS, typename S>
 static hipError_t launch_bwd(const AttnShape& s, const void* Q, const void* K, const void* V, const void* O,
                              const void* dO, const float* LSE, void* dQ, void* dK, void* dV, const int* row_ptr,
                              const int* col_idx, const int* col_ptr, const int* row_idx, const BwdWorkspace& ws,
-                             float* partial, hipStream_t st) {
+                             void* workspace, hipStream_t st) {
+    auto* const counters = static_cast<unsigned long long*>(workspace);
+    float* const partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + ws.counter_bytes);
     const bool rows = (s.bwd_phases & 1) != 0, keys = (s.bwd_phases & 2) != 0;
     const int n_key_a = keys ? ws.w_first : 0, n_rows = rows ? s.nb : 0, n_key_c = keys ? ws.w_max - ws.w_first : 0;
     const long long per_item = (long long)s.BH * S::PARTS;
@@ -647,12 +688,12 @@ static hipError_t launch_bwd(const AttnShape& s, const void* Q, const void* K, c
         attn_bwd_kernel<T, BS, S><<<dim3((unsigned)grid), dim3(S::W * 64), 0, st>>>(
             static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V), static_cast<const T*>(O),
             static_cast<const T*>(dO), LSE, static_cast<T*>(dQ), static_cast<T*>(dK), static_cast<T*>(dV), row_ptr,
-            col_idx, col_ptr, row_idx, partial, ws.n_slots, s.BH, s.L, s.nb, n_key_a, n_rows, n_key_c, ws.w_first,
+            col_idx, col_ptr, row_idx, partial, counters, s.tag, ws.n_slots, s.BH, s.L, s.nb, n_key_a, n_rows, n_key_c, ws.w_first,
             ws.chunk, sort_rows, s.scale, s.scale * kLog2e);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    return keys ? launch_bwd_reduce<T, BS>(s, ws, partial, col_ptr, dK, dV, st) : hipSuccess;
+    return hipSuccess;
 }
 
 template <typename T, int BS>
@@ -683,12 +724,11 @@ static hipError_t bwd_t(const AttnShape& s, const void* Q, const void* K, const 
         return bwd_bf16<BS>(s, Q, K, V, O, dO, LSE, dQ, dK, dV, row_ptr, col_idx, col_ptr, row_idx, ws, workspace, st);
     } else {
         const BwdWorkspace ws(s.BH, s.bs, s.nb, nnzb, kChunk, 0);
-        float* const partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + ws.counter_bytes);
         auto* launch = launch_bwd<T, BS, SplitFew<T, BS>>;
         if (many_short_rows(s, nnzb))
             launch = single_block_rows(s, nnzb) ? launch_bwd<T, BS, typename SplitMany<T, BS>::bwd_single>
                                                                : launch_bwd<T, BS, typename SplitMany<T, BS>::bwd>;
-        return launch(s, Q, K, V, O, dO, LSE, dQ, dK, dV, row_ptr, col_idx, col_ptr, row_idx, ws, partial, st);
+        return launch(s, Q, K, V, O, dO, LSE, dQ, dK, dV, row_ptr, col_idx, col_ptr, row_idx, ws, workspace, st);
     }
 }
 

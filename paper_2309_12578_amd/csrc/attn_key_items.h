@@ -1,5 +1,5 @@
 // Key-side work items of the backward pass: how the block columns are cut, found from the index by every
-// workgroup for itself, and the reduction of the partial tiles of columns that were cut.
+// workgroup for itself.
 #ifndef SPION_ATTN_KEY_ITEMS_H_
 #define SPION_ATTN_KEY_ITEMS_H_
 
@@ -111,64 +111,6 @@ __device__ __forceinline__ KeyItem key_item_lookup(const int* __restrict__ col_p
         u -= __popcll(members);
     }
     return none;
-}
-
-// The m-th split column: {J, first partial slot, chunks}; J < 0 if there are fewer.
-__device__ __forceinline__ int4 split_column_lookup(const int* __restrict__ col_ptr, int nb, int chunk, int m,
-                                                    int lane) {
-    int run = 0;
-    for (int base = 0; base < nb; base += 64) {
-        const int J = base + lane;
-        const bool valid = J < nb;
-        const int cnt = valid ? col_ptr[J + 1] - col_ptr[J] : 0;
-        const int nch = cnt > chunk ? (cnt + chunk - 1) / chunk : 0;
-        const int incl = wave_incl_scan(nch, lane);
-        const unsigned long long split = __ballot(nch > 0);
-        const unsigned long long hit = __ballot(nch > 0 && lanes_below(split) == m);
-        if (hit) {
-            const int src = __ffsll((long long)hit) - 1;
-            const int nchs = __builtin_amdgcn_readlane(nch, src);
-            return make_int4(base + src, run + __builtin_amdgcn_readlane(incl, src) - nchs, nchs, 0);
-        }
-        m -= __popcll(split);
-        run += __builtin_amdgcn_readlane(incl, 63);
-    }
-    return make_int4(-1, 0, 0, 0);
-}
-
-// Adds the partial tiles of every split block column, in chunk order.  Workgroup = (head, m-th split
-// column, part): 256 threads, one float4 of the output tile each, bs / 16 parts per tile, so that the
-// loads of all chunks of a float4 are in flight together.
-template <typename T, int BS>
-__global__ __launch_bounds__(256) void attn_bwd_reduce_kernel(
-    const float* __restrict__ partial, const int* __restrict__ col_ptr, int nb, int chunk, int split_max, int n_slots,
-    T* __restrict__ dK, T* __restrict__ dV, int L, float scale) {
-    constexpr int PARTS = BS / 16;
-    const int part = blockIdx.x % PARTS, m = (blockIdx.x / PARTS) % split_max;
-    const int bh = blockIdx.x / (PARTS * split_max);
-    const int4 info = split_column_lookup(col_ptr, nb, chunk, m, threadIdx.x & 63);   // {J, first slot, chunks}
-    if (info.x < 0) return;
-    const int v = part * 256 + threadIdx.x;
-    const float* pk = partial + ((size_t)bh * n_slots + info.y) * (2 * BS * kD) + v * 4;
-    f32x4 ak = f32x4{0.f, 0.f, 0.f, 0.f}, av = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-    for (int c = 0; c < info.z; ++c) {
-        ak += *reinterpret_cast<const f32x4*>(pk + (size_t)c * (2 * BS * kD));
-        av += *reinterpret_cast<const f32x4*>(pk + (size_t)c * (2 * BS * kD) + BS * kD);
-    }
-    const size_t out = ((size_t)bh * L + info.x * BS) * kD + v * 4;
-    store_quad<T>(dK + out, ak * scale);
-    store_quad<T>(dV + out, av);
-}
-
-template <typename T, int BS>
-hipError_t launch_bwd_reduce(const AttnShape& s, const BwdWorkspace& ws, const float* partial,
-                             const int* col_ptr, void* dK, void* dV, hipStream_t st) {
-    if (ws.split_max == 0) return hipSuccess;
-    attn_bwd_reduce_kernel<T, BS><<<dim3((unsigned)(ws.split_max * s.BH * (BS / 16))), dim3(256), 0, st>>>(
-        partial, col_ptr, s.nb, ws.chunk, ws.split_max, ws.n_slots, static_cast<T*>(dK), static_cast<T*>(dV),
-        s.L, s.scale);
-    return hipGetLastError();
 }
 
 }  // namespace spion

@@ -72,8 +72,8 @@ struct BwdWorkspace {
     int nnzb;
     int chunk;                       // most kept rows of a key-side work item
     int w_max, w_first;              // work items per head (upper bound); those that may be chunks come first
-    int n_slots, split_max;          // partial slots per head, split columns (upper bounds)
-    size_t counter_bytes;            // one per slot, at the workspace's start; the partial tiles behind them
+    int n_slots;                     // partial slots per head (upper bound)
+    size_t counter_bytes;            // one per slot and 16 rows, at the workspace's start; the partial tiles behind them
     size_t total;
     // mid_first: unsplit columns to make room for among the items that come first
     BwdWorkspace(int BH, int bs, int nb, int nnzb, int key_chunk, int mid_first);
