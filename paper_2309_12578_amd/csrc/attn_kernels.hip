@@ -678,10 +678,12 @@ static hipError_t launch_bwd(const AttnShape& s, const void* Q, const void* K, c
     const long long per_item = (long long)s.BH * S::PARTS;
     // Rows of more than twice the mean first, where more workgroups than fit at once follow (two or three waves a SIMD):
     // one that starts late runs on alone.  fp32: 2 heads x 8192, block 32, 3 %, 161 -> 148 us; 3 x 4096, block 64, 10 %, 86 -> 76; 8 x 2048,
-    // block 32, 15 %, 78 -> 71, 10 % 52.7 both; bf16, block 16: 10 x 4096, 4 %, 71 -> 67, 9 x 1936, 8 %, 31.3 -> 30.0; without long rows the
-    // search costs up to 1 us (32 x 512, block 32, 30.9 -> 31.8).
+    // block 32, 15 %, 78 -> 71, 10 % 52.7 both; bf16, block 16: 10 x 4096, 4 %, 71 -> 67, 9 x 1936, 8 %, 31.3 -> 30.0; rows of fewer
+    // than 6 tiles on average gain nothing and pay the search, up to 1 us (bf16, block 16, searched and not: 24 x 1168, 4 %, 19.5,
+    // 18.8; 16 x 2048, 3 %, 25.1, 24.3, 5 %, 33.7, 34.1; fp32, block 32: 24 x 2336, 4 %, 81.2, 79.8; 16 x 1024, 10 %, 49.4, 50.9).
     const long long resident = 256 * 4 * (sizeof(T) == 4 ? 2 : 3) / S::W;
-    const int sort_rows = rows && per_item * (n_key_a + n_rows + n_key_c) > resident;
+    const int sort_rows = rows && (long long)ws.nnzb * (BS / 16) >= 6ll * s.nb &&
+                          per_item * (n_key_a + n_rows + n_key_c) > resident;
     const long long grid = group_grid(per_item * n_key_a) + (sort_rows ? S::PARTS * group_grid((long long)s.BH * n_rows) : group_grid(per_item * n_rows)) +
                            group_grid(per_item * n_key_c);
     if (grid > 0) {
