@@ -249,10 +249,10 @@ __device__ __forceinline__ RowOfHead long_rows_first(const int* __restrict__ row
 // ------------------------------------------------------------------------------------------------
 // Long rows in pieces.  A block row is one chain of steps; patterns have a row or two of several times the mean, up to
 // half the columns, and where there are few heads such a chain outlasts everything else: 8 heads x 8192, block 32, 13
-// blocks a row and two rows of 120: 44 us, 14 without those rows.  A row of more than `longest` blocks is cut into pieces
-// of about `piece`, as long as a head's pieces fit into `slots`: what is cut depends on the pattern alone, so that a head
-// comes out the same whatever is computed beside it.  The row's own workgroup takes the first piece; `helpers` workgroups of
-// each head, which come first in the grid, take the others in turn.  Every workgroup finds the same cuts from row_ptr.
+// blocks a row and two rows of 120: forward 44 us, 14 without those rows.  A row of more than `longest` blocks is cut into pieces
+// of about `piece`, as long as a head's pieces fit into `slots`.  The row's own workgroup takes the first piece; `helpers`
+// workgroups of each head, which come first in the grid, take the others (the forward's in turn; the backward's query side
+// has one for each).  Every workgroup finds the same cuts from row_ptr.
 // Each piece leaves its accumulators, reference and sum in memory; the workgroup that is the last of its row to do so adds
 // up the pieces in their order (the same bits whoever that is) and writes the row.  Nobody waits for anybody.
 // ------------------------------------------------------------------------------------------------
@@ -262,6 +262,11 @@ struct RowPieces {
     int first;    // number of its second piece among the head's pieces that are not the first of their row
     int slot;     // of its first piece
 };
+// Kernels that cut nothing carry no plan.
+struct NoCut {};
+template <bool CUT>
+using CutOf = std::conditional_t<CUT, RowCut, NoCut>;
+
 // The row that piece number `want`, not the first of its row, belongs to, or (BY_ROW) row number `want`.  All lanes
 // active, the result uniform.
 template <bool BY_ROW>

@@ -50,16 +50,16 @@ __device__ __forceinline__ void lds_barrier() {
 // (a group is absent when only one side is requested).  w_first leaves room for a quarter of the columns
 // besides the chunks: unsplit columns of more than kMidColumn rows that came last ran on alone (64 heads x 1024,
 // block 32, 4.8 blocks a row: 31.6 -> 26.5 us; 4 and 12 measure like 8, and a sixth or a third of the columns like a
-// quarter).  With sort_rows the rows of more than twice the mean length come before the others.
+// quarter).  Pieces of long rows come before all three (CUT).  With sort_rows the rows of more than twice the mean length come before the others.
 // ------------------------------------------------------------------------------------------------
-template <int BS, bool BESIDE>
+template <int BS, bool BESIDE, bool CUT>
 __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const bf16_t* __restrict__ O, const bf16_t* __restrict__ dO, const float* __restrict__ LSE,
     bf16_t* __restrict__ dQ, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV,
     const int* __restrict__ row_ptr, const int* __restrict__ col_idx, const int* __restrict__ col_ptr,
     const int* __restrict__ row_idx, float* __restrict__ partial, unsigned long long* __restrict__ counters,
-    unsigned long long tag, HeadRows<BESIDE> at, int n_slots, int BH, int L, int nb, int n_key_a,
+    unsigned long long tag, HeadRows<BESIDE> at, CutOf<CUT> cut, int n_slots, int BH, int L, int nb, int n_key_a,
     int n_rows, int n_key_c, int w_first, int chunk, int sort_rows, float scale, float scale_log2) {
     constexpr int NT = BS / 16;   // 16-row tiles per block = waves per workgroup
     // Separate objects, so that the compiler can tell a read of one tile from a load in flight into
@@ -84,7 +84,23 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
     }
     bool key_side;
     int bh, idx;   // idx: work item (key side) or block row (query side)
-    if (l < hpx * n_key_a) {
+    [[maybe_unused]] RowPieces cuts = {0, 1, 0, 0};
+    [[maybe_unused]] int piece = 0;
+    bool helper = false;
+    if constexpr (CUT) {
+        helper = l < hpx * cut.helpers;
+        if (!helper) l -= hpx * cut.helpers;
+    }
+    if (helper) {
+        if constexpr (CUT) {
+            key_side = false;
+            bh = x * hpx + l % hpx;
+            cuts = row_pieces<false>(row_ptr, nb, cut, l / hpx, lane);
+            if (cuts.row < 0) return;
+            idx = cuts.row;
+            piece = l / hpx - cuts.first + 1;
+        }
+    } else if (l < hpx * n_key_a) {
         key_side = true;
         bh = x * hpx + l % hpx;
         idx = l / hpx;
@@ -119,7 +135,7 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
             tile_load_async(K + head + (size_t)J * BS * in_row, kt, wave, tl);
             tile_load_async(V + head + (size_t)J * BS * in_row, vt, wave, tl);
         };
-        issue(ta0, tb0, I);   // the diagonal block, before any index is known
+        if (!helper) issue(ta0, tb0, I);   // the diagonal block, before any index is known
         bf16x8 qf[2], dof[2], of[2];
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
@@ -129,21 +145,30 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
             of[c] = *reinterpret_cast<const bf16x8*>(O + out);
         }
         const float lse2 = LSE[vec + qrow] * kLog2e;
-        const int jb = row_ptr[I], n = row_ptr[I + 1] - jb;
+        int jb = row_ptr[I], n = row_ptr[I + 1] - jb;
+        if constexpr (CUT) if (n > cut.longest) {
+            if (!helper) cuts = row_pieces<true>(row_ptr, nb, cut, I, lane);
+            const int from = piece * n / cuts.count;
+            n = (piece + 1) * n / cuts.count - from;
+            jb += from;
+        }
         const int last = n > 0 ? n - 1 : 0;
         const int* cols = col_idx + jb;
         int first[8];
-        const int pd = n > 0 ? find_in_row(cols, n, I, first) : -1;
+        int pd = n > 0 ? find_in_row(cols, n, I, first) : -1;
+        if (helper) pd = -1;   // in index order, the diagonal block where it comes
         // block visited at step t (clamped reads stay inside this row's entries; an empty row reads nothing)
         auto col_at = [&](int t) {
             const int j = walk_index(t < last ? t : last, pd);
             return j < 8 ? pick8(first, j) : cols[j];
         };
         if (pd < 0 && n > 0) {
-            // no diagonal block in this row: once everyone's early load has landed, load block 0 over it
-            __builtin_amdgcn_s_waitcnt(kWaitVm0);
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
+            // no diagonal block in this row (piece): once everyone's early load has landed, load block 0 over it
+            if (!helper) {
+                __builtin_amdgcn_s_waitcnt(kWaitVm0);
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+            }
             issue(ta0, tb0, first[0]);
         }
         // the second block goes out as soon as its index is known (a one-block row loads its block
@@ -220,6 +245,27 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
         }
         // an empty row never waited for its early load: it must land before this workgroup's LDS is freed
         __builtin_amdgcn_s_waitcnt(kWaitVm0);
+        if constexpr (CUT) if (cuts.count > 1) {   // a long row in pieces: see attn_bf16_tiles.h
+            constexpr int kPart = 8 * 128;   // eight pairs a lane
+            const size_t first_slot = (size_t)bh * cut.slots + cuts.slot;
+            float* const parts = cut.parts + (first_slot * NT + wave) * kPart + lane * 2;
+            float* const mine = parts + (size_t)piece * NT * kPart;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) put_shared(mine + i * 128, dq[i / 2][i % 2 * 2], dq[i / 2][i % 2 * 2 + 1]);
+            if (!last_to_arrive(cut.counters + first_slot, cut.tag, cuts.count, reinterpret_cast<int*>(lse0))) return;
+#pragma unroll
+            for (int dt = 0; dt < 4; ++dt) dq[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int c = 0; c < cuts.count; ++c) {
+                float2 v[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] = get_shared(parts + (size_t)c * NT * kPart + i * 128);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    dq[i / 2][i % 2 * 2] += v[i].x;
+                    dq[i / 2][i % 2 * 2 + 1] += v[i].y;
+                }
+            }
+        }
         // Through a tile nobody reads any more: every wave is past the barrier of the last step, so only
         // the last block's stage can still be read; the wave's own 2 KB of any other tile were only ever
         // written by the wave's own loads, which have all landed.
@@ -398,6 +444,20 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
     store_rows_coalesced(pb, dV + row0, in_row, dv, 1.f, lane);
 }
 
+// The query side's rows that are cut: the forward's rule, with the steps of both sides (so few heads, and a helper for each
+// piece).  Backward, us, uncut / cut / a pattern without long rows: 8 heads x 8192, block 32, rows of 121 blocks, 73.5 / 46.7 / 47.5;
+// 4 x 16384, block 64, 112 / 70.5 / 70.3; 4 x 8192, block 64, rows of 71, 65.3 / 39.5 / 40.2; 1 x 4096, block 32, 21.1 / 17.8 / 17.9.
+static RowCut row_cut(const AttnShape& s, const BwdWorkspace& ws, void* workspace) {
+    RowCut cut;
+    cut.decide(s, ws.nnzb, bwd_steps_per_slot(s.BH, s.bs, s.nb, ws.nnzb));
+    if (cut.slots == 0) return cut;
+    cut.helpers = cut.slots - 1;
+    if ((long long)s.BH * (cut.helpers + s.nb + ws.w_max) > 0x7fffffffll) return RowCut{};   // workgroups of a launch
+    cut.counters = reinterpret_cast<unsigned long long*>(static_cast<char*>(workspace) + ws.row_counters);
+    cut.parts = reinterpret_cast<float*>(static_cast<char*>(workspace) + ws.row_parts);
+    return cut;
+}
+
 // ------------------------------------------------------------------------------------------------
 // launcher (called by the dispatch in attn_kernels.hip).  phases: bit 0 query side, bit 1 key side.
 // ------------------------------------------------------------------------------------------------
@@ -408,24 +468,30 @@ hipError_t bwd_bf16(const AttnShape& s, const void* Q, const void* K, const void
                     void* workspace, hipStream_t st) {
     const bool rows = (s.bwd_phases & 1) != 0, keys = (s.bwd_phases & 2) != 0;
     const int n_key_a = keys ? ws.w_first : 0, n_rows = rows ? s.nb : 0, n_key_c = keys ? ws.w_max - ws.w_first : 0;
-    const long long total = (long long)s.BH * (n_key_a + n_rows + n_key_c);
+    const RowCut cut = rows ? row_cut(s, ws, workspace) : RowCut{};
+    const long long total = (long long)s.BH * (n_key_a + n_rows + n_key_c), helpers = (long long)s.BH * cut.helpers;
     if (total > 0) {
         // A row of more than twice the mean that starts late runs alone at the end; finding the rows by length
         // costs each about half a step.  Worth it where such rows are long, by themselves (a mean of 6
         // blocks) or can be against the steps a slot has to do: 16 heads x 8192, block 32, 12.8 blocks a row 130 -> 98 us,
         // 64 heads x 1024, 4.8 blocks a row 26.9 -> 28.3 us.
         const int sort_rows = total > bwd_resident(BS) && (ws.nnzb >= 6 * s.nb || s.nb >= 8 * bwd_steps_per_slot(s.BH, BS, s.nb, ws.nnzb));
-        auto launch = [&](auto kernel, auto at) {
-            kernel<<<dim3((unsigned)total), dim3(BS * 4), 0, st>>>(
+        auto launch = [&](auto kernel, auto at, auto cut_arg) {
+            kernel<<<dim3((unsigned)(helpers + total)), dim3(BS * 4), 0, st>>>(
                 static_cast<const bf16_t*>(Q), static_cast<const bf16_t*>(K), static_cast<const bf16_t*>(V),
                 static_cast<const bf16_t*>(O), static_cast<const bf16_t*>(dO), LSE, static_cast<bf16_t*>(dQ),
                 static_cast<bf16_t*>(dK), static_cast<bf16_t*>(dV), row_ptr, col_idx, col_ptr, row_idx,
                 reinterpret_cast<float*>(static_cast<char*>(workspace) + ws.counter_bytes),
-                static_cast<unsigned long long*>(workspace), s.tag, at,
+                static_cast<unsigned long long*>(workspace), s.tag, at, cut_arg,
                 ws.n_slots, s.BH, s.L, s.nb, n_key_a, n_rows, n_key_c, ws.w_first, ws.chunk, sort_rows, s.scale, s.scale * kLog2e);
         };
-        if (s.heads_beside) launch(attn_bwd_bf16_kernel<BS, true>, HeadRows<true>{s.heads_beside});
-        else launch(attn_bwd_bf16_kernel<BS, false>, HeadRows<false>{0});
+        if (s.heads_beside) {
+            if (cut.slots) launch(attn_bwd_bf16_kernel<BS, true, true>, HeadRows<true>{s.heads_beside}, cut);
+            else launch(attn_bwd_bf16_kernel<BS, true, false>, HeadRows<true>{s.heads_beside}, NoCut{});
+        } else {
+            if (cut.slots) launch(attn_bwd_bf16_kernel<BS, false, true>, HeadRows<false>{0}, cut);
+            else launch(attn_bwd_bf16_kernel<BS, false, false>, HeadRows<false>{0}, NoCut{});
+        }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

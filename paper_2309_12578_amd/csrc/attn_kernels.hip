@@ -632,7 +632,11 @@ BwdWorkspace::BwdWorkspace(int BH, int bs, int nb, int nnzb_, int key_chunk, int
     // for the shortest chunks, so that a workspace for more kept blocks also serves fewer; multiples of 256
     const size_t slots = (size_t)BH * (2 * (nnzb / kChunk) + 2);
     counter_bytes = (slots * (bs / 16) * 8 + 255) / 256 * 256;
-    total = counter_bytes + slots * 2 * bs * kD * sizeof(float);
+    row_counters = counter_bytes + slots * 2 * bs * kD * sizeof(float);
+    // (with more heads the rule never cuts a row, however few blocks are kept)
+    const size_t row_slots = bs >= 32 && nb > 64 && 4 * BH < bwd_resident(bs) ? (size_t)BH * RowCut::kSlots : 0;
+    row_parts = row_counters + row_slots * 8;
+    total = row_parts + row_slots * bs * kD * sizeof(float);
 }
 
 size_t attn_bwd_workspace_bytes(int BH, int bs, int nb, int nnzb) { return BwdWorkspace(BH, bs, nb, nnzb, kChunk, 0).total; }

@@ -43,7 +43,7 @@ struct AttnShape {
     unsigned long long tag;       // of this call alone, 1 .. 2^48 - 1 (see last_to_arrive)
 };
 
-// How the tuned forward cuts long block rows (see attn_bf16_tiles.h), from what the host knows of a pattern.
+// How the tuned kernels cut long block rows (see attn_bf16_tiles.h), from what the host knows of a pattern.
 struct RowCut {
     int piece = 0;     // kept blocks of a piece, at most
     int longest = 0;   // a row of more is cut
@@ -54,7 +54,10 @@ struct RowCut {
     unsigned long long* counters = nullptr;   // [head][slots], in use: that of a row's first piece
     float* parts = nullptr;                   // partial results, as many
     RowCut() = default;
-    RowCut(const AttnShape& s, int nnzb);
+    RowCut(const AttnShape& s, int nnzb);   // the forward's
+    // piece, longest and slots, where each of the workgroups that run at once has `steps` to do
+    void decide(const AttnShape& s, int nnzb, long long steps);
+    static constexpr int kSlots = 32;       // most: two rows of half the columns at 3 % kept blocks; 0.6 MB of room per head
     size_t counter_bytes(int BH) const { return ((size_t)BH * slots * 8 + 255) / 256 * 256; }
     static constexpr size_t partial_bytes(int bs) { return (size_t)(bs / 16) * 64 * 18 * sizeof(float); }   // O, maximum, sum
     size_t room_bytes(int BH, int bs) const { return slots ? counter_bytes(BH) + (size_t)BH * slots * partial_bytes(bs) : 0; }
@@ -74,6 +77,7 @@ struct BwdWorkspace {
     int w_max, w_first;              // work items per head (upper bound); those that may be chunks come first
     int n_slots;                     // partial slots per head (upper bound)
     size_t counter_bytes;            // one per slot and 16 rows, at the workspace's start; the partial tiles behind them
+    size_t row_counters, row_parts;  // where those of long rows in pieces start: RowCut::kSlots per head
     size_t total;
     // mid_first: unsplit columns to make room for among the items that come first
     BwdWorkspace(int BH, int bs, int nb, int nnzb, int key_chunk, int mid_first);

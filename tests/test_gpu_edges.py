@@ -274,14 +274,15 @@ def test_backward_chunks_follow_the_work(sp, BH, nb, density, block):
 
 
 @pytest.mark.parametrize("dtype,block", [("bf16", 32), ("bf16", 64), ("bf16", 16), ("f32", 32)])
-def test_cut_columns_again_and_in_a_graph(sp, dtype, block):
-    """Whichever chunk of a column is the last to arrive: the same bits every time, in a workspace that held other numbers, and in
-    replays, which share their launches' tags, on other inputs and with other work in between."""
+def test_cut_columns_and_rows_again_and_in_a_graph(sp, dtype, block):
+    """Backward, whichever chunk of a column or piece of a row is the last to arrive: the same bits every time, in a workspace that
+    held other numbers, and in replays, which share their launches' tags, on other inputs and with other work in between."""
     from test_gpu_parity import _pattern_from_mask
     nb = 72
     fl = np.eye(nb, dtype=np.uint8)
     fl[:, [0, 40]] = 1
     fl[:33, 7] = 1
+    fl[[50, 71], :] = 1   # bf16, block 32 and 64: in pieces
     pat = _pattern_from_mask(sp, fl, block)
     gen = torch.Generator(device="cuda").manual_seed(2)
     tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
