@@ -277,7 +277,7 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
     // ============================================================================================
     // key side: work item idx of head bh.  {Q, dO, O} tiles and LSE of a block row in two stages.
     // ============================================================================================
-    const KeyItem item = key_item_lookup<true>(col_ptr, nb, chunk, idx, lane);
+    const KeyItem item = key_item_lookup(col_ptr, nb, chunk, kMidColumn, idx, lane);
     if (item.J < 0) return;
     const int J = item.J, n = item.ke - item.kb, slot = item.slot;
     const int krow = J * BS + wave * 16 + r;

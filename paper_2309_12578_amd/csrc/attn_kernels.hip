@@ -332,9 +332,10 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_fwd_kernel(
 // ------------------------------------------------------------------------------------------------
 // backward: one launch computes dQ, dK and dV.  Workgroup = (head, S::OWN rows of a block row) on the query
 // side, or (head, S::OWN keys of a work item's block column) on the key side.  The sides share no data: the
-// key side computes delta = rowsum(dO .* O) of the query rows it visits by itself.  Deterministic: no
-// atomics, sums over waves and chunks in fixed order.
-// Grid: the long key items (chunks of split columns), the block rows, the other key items; all heads in each.
+// key side computes delta = rowsum(dO .* O) of the query rows it visits by itself.  Deterministic: sums over waves
+// and chunks in fixed order.
+// Grid: some of the long block rows, the long key items (chunks of split columns, long columns), the other block rows, the
+// other key items; all heads in each.
 // ------------------------------------------------------------------------------------------------
 template <typename T, int BS, typename S>
 __global__ __launch_bounds__(S::W * 64, 2) void attn_bwd_kernel(
@@ -343,7 +344,7 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_bwd_kernel(
     T* __restrict__ dV, const int* __restrict__ row_ptr, const int* __restrict__ col_idx,
     const int* __restrict__ col_ptr, const int* __restrict__ row_idx, float* __restrict__ partial,
     unsigned long long* __restrict__ counters, unsigned long long tag, int n_slots, int BH, int L, int nb, int n_key_a,
-    int n_rows, int n_key_c, int w_first, int chunk, int sort_rows, float scale, float scale_log2) {
+    int n_rows, int n_key_c, int w_first, int chunk, int mid, int early_rows, float scale, float scale_log2) {
     typedef typename Elem<T>::Frag Frag;
     typedef typename Elem<T>::Quad Quad;
     typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
@@ -354,33 +355,54 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_bwd_kernel(
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wt = wave % S::WT, own = wave / S::WT * (16 * NQ);
     auto padded = [](int n) { return (n + 7) & ~7; };
-    const int row_groups = sort_rows ? S::PARTS * padded(BH * n_rows) : padded(BH * n_rows * S::PARTS);
-    int id = blockIdx.x, per_head = n_key_a * S::PARTS, first = 0;
-    bool key_side = true;
-    if (id >= padded(BH * per_head)) {
-        id -= padded(BH * per_head);
-        per_head = n_rows * S::PARTS;
-        key_side = false;
-        if (id >= row_groups) {
-            id -= row_groups;
-            per_head = n_key_c * S::PARTS;
-            first = w_first;
-            key_side = true;
+    // early_rows > 0: rows by length (see launch_bwd), so many of them before everything else; a multiple of 8
+    const int early = S::PARTS * early_rows;
+    const int late = early_rows ? S::PARTS * padded(BH * n_rows) - early : padded(BH * n_rows * S::PARTS);
+    int id = blockIdx.x, first = 0, first_row = 0;
+    bool key_side = false;
+    if (id >= early) {
+        id -= early;
+        key_side = true;
+        if (id >= BH * n_key_a * S::PARTS) {
+            id -= padded(BH * n_key_a * S::PARTS);
+            if (id < 0) return;
+            key_side = false;
+            first_row = early_rows;
+            if (id >= late) {
+                id -= late;
+                first = w_first;
+                key_side = true;
+            }
         }
     }
     int bh, idx, sub;   // sub: the workgroup's rows within the block
-    if (!key_side && sort_rows) {
-        const int row = (id >> 3) / S::PARTS * 8 + (id & 7);   // a row's workgroups on one XCD
+    if (key_side) {
+        // The items of all heads together, longest first; heads keep to an XCD where that shares them out evenly.  (In
+        // contiguous eighths, as the rows are, a few heads' long items met on a few XCDs: fp32, 3 x 4096, block 64, 75 -> 71.5 us;
+        // 32 x 1024, block 64, 105 -> 96.)
+        int x = 0, hpx = BH, l = id;
+        if ((BH & 7) == 0) {
+            x = id & 7;
+            hpx = BH >> 3;
+            l = id >> 3;
+        }
+        bh = x * hpx + l % hpx;
+        idx = l / hpx;
+        sub = idx % S::PARTS * OWN;
+        idx = first + idx / S::PARTS;
+        if (first && idx >= w_first + n_key_c) return;
+    } else if (early_rows) {
+        const int row = first_row + (id >> 3) / S::PARTS * 8 + (id & 7);   // a row's workgroups on one XCD
         if (row >= BH * n_rows) return;
         const RowOfHead mine = long_rows_first<true>(row_ptr, nb, BH, row, lane);
         bh = mine.head;
         idx = mine.row;
         sub = (id >> 3) % S::PARTS * OWN;
     } else {
-        const int item = item_of_group(id, BH * per_head);
+        const int per_head = n_rows * S::PARTS, item = item_of_group(id, BH * per_head);
         if (item < 0) return;
         bh = item / per_head;
-        idx = first + item % per_head / S::PARTS;
+        idx = item % per_head / S::PARTS;
         sub = item % S::PARTS * OWN;
     }
     const size_t head = (size_t)bh * L * kD, vec = (size_t)bh * L;
@@ -484,7 +506,7 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_bwd_kernel(
         return;
     }
 
-    const KeyItem it = key_item_lookup<false>(col_ptr, nb, chunk, idx, lane);
+    const KeyItem it = key_item_lookup(col_ptr, nb, chunk, mid, idx, lane);
     if (it.J < 0) return;
     const int n = it.ke - it.kb, nt = n * S::TPB, row0 = it.J * BS + sub + own;
     const int* rows = row_idx + it.kb;
@@ -688,14 +710,22 @@ static hipError_t launch_bwd(const AttnShape& s, const void* Q, const void* K, c
     const long long resident = 256 * 4 * (sizeof(T) == 4 ? 2 : 3) / S::W;
     const int sort_rows = rows && (long long)ws.nnzb * (BS / 16) >= 6ll * s.nb &&
                           per_item * (n_key_a + n_rows + n_key_c) > resident;
-    const long long grid = group_grid(per_item * n_key_a) + (sort_rows ? S::PARTS * group_grid((long long)s.BH * n_rows) : group_grid(per_item * n_rows)) +
+    // and a row a head for every 32 of them before the key side's items too: there the long ones are.  2 heads x 8192: 136 -> 125;
+    // 4 x 4096, 5 %, 70.6 -> 62.2.
+    const long long row_items = group_grid((long long)s.BH * n_rows), some = group_grid((long long)s.BH * ((s.nb + 31) / 32));
+    const int early_rows = (int)(!sort_rows ? 0 : some < row_items ? some : row_items);
+    // Unsplit columns of more than 8 rows before the rows, where half as many workgroups again as run at once make the order matter
+    // (the search costs a workgroup a microsecond: 16 heads x 512, block 32, 29.1 -> 30.4).  fp32, block 32: 16 x 1024, 10 %, 46.4 -> 34.7,
+    // 20 %, 68 -> 49.4; 64 x 1024, 15 %, 142 -> 113; 24 x 2336, 4 %, 74.6 -> 69; block 64, 32 x 1024, 20 %, 95.7 -> 87.3.
+    const int mid = 2 * per_item * (n_key_a + n_rows + n_key_c) > 3 * resident ? kMidColumn : ws.chunk;
+    const long long grid = group_grid(per_item * n_key_a) + (sort_rows ? S::PARTS * row_items : group_grid(per_item * n_rows)) +
                            group_grid(per_item * n_key_c);
     if (grid > 0) {
         attn_bwd_kernel<T, BS, S><<<dim3((unsigned)grid), dim3(S::W * 64), 0, st>>>(
             static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V), static_cast<const T*>(O),
             static_cast<const T*>(dO), LSE, static_cast<T*>(dQ), static_cast<T*>(dK), static_cast<T*>(dV), row_ptr,
             col_idx, col_ptr, row_idx, partial, counters, s.tag, ws.n_slots, s.BH, s.L, s.nb, n_key_a, n_rows, n_key_c, ws.w_first,
-            ws.chunk, sort_rows, s.scale, s.scale * kLog2e);
+            ws.chunk, mid, early_rows, s.scale, s.scale * kLog2e);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -729,7 +759,7 @@ static hipError_t bwd_t(const AttnShape& s, const void* Q, const void* K, const 
         const BwdWorkspace ws(s.BH, s.bs, s.nb, nnzb, key_chunk(s.BH, BS, s.nb, nnzb), s.nb / 4);
         return bwd_bf16<BS>(s, Q, K, V, O, dO, LSE, dQ, dK, dV, row_ptr, col_idx, col_ptr, row_idx, ws, workspace, st);
     } else {
-        const BwdWorkspace ws(s.BH, s.bs, s.nb, nnzb, kChunk, 0);
+        const BwdWorkspace ws(s.BH, s.bs, s.nb, nnzb, kChunk, s.nb / 8);
         auto* launch = launch_bwd<T, BS, SplitFew<T, BS>>;
         if (many_short_rows(s, nnzb))
             launch = single_block_rows(s, nnzb) ? launch_bwd<T, BS, typename SplitMany<T, BS>::bwd_single>

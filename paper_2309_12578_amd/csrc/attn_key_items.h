@@ -18,9 +18,8 @@ namespace spion {
 // for every head).  A column with cnt kept rows is cut into nch = ceil(cnt / chunk) near-equal chunks if
 // cnt > chunk, else it is one item (also when cnt == 0: its dK / dV must still be written as zeros).
 // Items are numbered longest first, as far as that is cheap to find: the chunks of split columns in column
-// order, then (tuned kernels) the unsplit columns of more than kMidColumn rows, then the others.  Chunk number w of the first group
-// writes its fp32 partial tiles to slot w; a second kernel adds them up in chunk order (deterministic, no
-// atomics).
+// order, then the unsplit columns of more than kMidColumn rows, then the others.  Chunk number w writes its fp32
+// partial tiles to slot w; the last of a column's chunks to do so adds them up in chunk order (deterministic).
 // ------------------------------------------------------------------------------------------------
 constexpr int kChunk = 16;      // the shortest chunk that is cut: partial tiles are sized for it
 constexpr int kChunkMax = 64;   // the longest
@@ -52,17 +51,17 @@ struct KeyItem {
     int first, count;   // slot of the column's first chunk, its chunks
 };
 
-// All lanes of the calling wave must be active; the result is wave-uniform.  MID_FIRST: see kMidColumn.
-template <bool MID_FIRST>
-__device__ __forceinline__ KeyItem key_item_lookup(const int* __restrict__ col_ptr, int nb, int chunk, int w, int lane) {
+// All lanes of the calling wave must be active; the result is wave-uniform.  mid: kMidColumn, or chunk where the
+// unsplit columns stay in their order.
+__device__ __forceinline__ KeyItem key_item_lookup(const int* __restrict__ col_ptr, int nb, int chunk, int mid, int w, int lane) {
     KeyItem none = {-1, 0, 0, -1, 0, 1};
-    if (nb <= (MID_FIRST ? kMidColumn : chunk)) {   // all alike
+    if (nb <= mid) {   // all alike
         if (w >= nb) return none;
         KeyItem it = {w, col_ptr[w], col_ptr[w + 1], -1, 0, 1};
         return it;
     }
     int run = 0;     // chunks of split columns in the column groups before this one
-    int n_mid = 0;   // unsplit columns of more than kMidColumn rows
+    int n_mid = 0;   // unsplit columns of more than mid rows
     int c0_first = 0, cnt_first = 0;   // columns 0 .. 63, kept for the second search
     for (int base = 0; base < nb; base += 64) {
         const int J = base + lane;
@@ -87,11 +86,11 @@ __device__ __forceinline__ KeyItem key_item_lookup(const int* __restrict__ col_p
             return it;
         }
         run += __builtin_amdgcn_readlane(incl, 63);
-        if (MID_FIRST) n_mid += __popcll(__ballot(cnt > kMidColumn && cnt <= chunk));
+        n_mid += __popcll(__ballot(cnt > mid && cnt <= chunk));
     }
     int u = w - run;   // index among the unsplit columns, then among those of its class
-    const bool is_mid = MID_FIRST && u < n_mid;
-    if (MID_FIRST && !is_mid) u -= n_mid;
+    const bool is_mid = u < n_mid;
+    if (!is_mid) u -= n_mid;
     for (int base = 0; base < nb; base += 64) {
         const int J = base + lane;
         const bool valid = J < nb;
@@ -100,7 +99,7 @@ __device__ __forceinline__ KeyItem key_item_lookup(const int* __restrict__ col_p
             c0 = valid ? col_ptr[J] : 0;
             c1 = valid ? col_ptr[J + 1] : 0;
         }
-        const bool in = valid && c1 - c0 <= chunk && (!MID_FIRST || (c1 - c0 > kMidColumn) == is_mid);
+        const bool in = valid && c1 - c0 <= chunk && (c1 - c0 > mid) == is_mid;
         const unsigned long long members = __ballot(in);
         const unsigned long long hit = __ballot(in && lanes_below(members) == u);
         if (hit) {
