@@ -160,20 +160,32 @@ template <typename T, int BS, typename S>
 __global__ __launch_bounds__(S::W * 64, 2) void attn_fwd_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, T* __restrict__ O,
     float* __restrict__ LSE, const int* __restrict__ row_ptr, const int* __restrict__ col_idx, int L,
-    int nb, int total, float scale_log2, int paper_denom) {
+    int nb, int total, int sort_rows, float scale_log2, int paper_denom) {
     typedef typename Elem<T>::Frag Frag;
     typedef typename Elem<T>::Quad Quad;
     constexpr int NQ = S::NQ, KT = S::KT, NDC = S::NDC, OWN = S::OWN;
     __shared__ __attribute__((aligned(16))) float o_s[S::WT][OWN * kPatchLd];
     __shared__ float m_s[S::WT][OWN], l_s[S::WT][OWN];
 
-    const int item = item_of_group(blockIdx.x, total);
-    if (item < 0) return;
-    const int bh = item / (nb * S::PARTS), part = item % (nb * S::PARTS), I = part / S::PARTS;
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
+    int bh, I, part;
+    if (sort_rows) {
+        const int row = (blockIdx.x >> 3) / S::PARTS * 8 + (blockIdx.x & 7);   // a row's workgroups on one XCD
+        if (row >= total / S::PARTS) return;
+        const RowOfHead mine = long_rows_first<true>(row_ptr, nb, total / (nb * S::PARTS), row, lane);
+        bh = mine.head;
+        I = mine.row;
+        part = (blockIdx.x >> 3) % S::PARTS;
+    } else {
+        const int item = item_of_group(blockIdx.x, total);
+        if (item < 0) return;
+        bh = item / (nb * S::PARTS);
+        I = item % (nb * S::PARTS) / S::PARTS;
+        part = item % S::PARTS;
+    }
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wt = wave % S::WT, own = wave / S::WT * (16 * NQ);
     const size_t head = (size_t)bh * L * kD;
-    const int wg0 = I * BS + part % S::PARTS * OWN, row0 = wg0 + own;   // rows of the workgroup, of the wave
+    const int wg0 = I * BS + part * OWN, row0 = wg0 + own;   // rows of the workgroup, of the wave
 
     const int jb = row_ptr[I], n = row_ptr[I + 1] - jb, nt = n * S::TPB;
     const int* cols = col_idx + jb;
@@ -683,12 +695,19 @@ static bool many_short_rows(const AttnShape& s, int nnzb) {
 
 template <typename T, int BS, typename S>
 static hipError_t launch_fwd(const AttnShape& s, const void* Q, const void* K, const void* V, void* O,
-                             float* LSE, const int* row_ptr, const int* col_idx, hipStream_t st) {
+                             float* LSE, const int* row_ptr, const int* col_idx, int nnzb, hipStream_t st) {
     const long long total = (long long)s.nb * s.BH * S::PARTS;
-    if (group_grid(total) > 0x7fffffffll) return hipErrorInvalidValue;
-    attn_fwd_kernel<T, BS, S><<<dim3((unsigned)group_grid(total)), dim3(S::W * 64), 0, st>>>(
+    // Rows of more than twice the mean first, as in launch_bwd, where half as many workgroups again as run at once (four or
+    // three waves a SIMD) leave a late one alone.  fp32, block 32: 32 heads x 2048, 10 %, 61.3 -> 48.3 us, 16 x 2048 33.3 -> 29.1; block 16, 16 x
+    // 2048, 6 %, 27.2 -> 22.7; bf16, 17.2 -> 15.4.  The search costs half a microsecond to one: 9 x 1936 (few more than run at once)
+    // 12.7 -> 13.2; up to 32 block rows no row is long enough, 32 x 1024, block 64, 28.2 -> 29.2.
+    const long long resident = 256 * 4 * (S::NQ == 1 ? 4 : 3) / S::W;
+    const int sort_rows = s.nb > 32 && (long long)nnzb * (BS / 16) >= 6ll * s.nb && 2 * total > 3 * resident;
+    const long long grid = sort_rows ? S::PARTS * group_grid((long long)s.nb * s.BH) : group_grid(total);
+    if (grid > 0x7fffffffll) return hipErrorInvalidValue;
+    attn_fwd_kernel<T, BS, S><<<dim3((unsigned)grid), dim3(S::W * 64), 0, st>>>(
         static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V), static_cast<T*>(O), LSE, row_ptr,
-        col_idx, s.L, s.nb, (int)total, s.scale * kLog2e, s.paper_denom);
+        col_idx, s.L, s.nb, (int)total, sort_rows, s.scale * kLog2e, s.paper_denom);
     return hipGetLastError();
 }
 
@@ -739,14 +758,14 @@ static hipError_t fwd_t(const AttnShape& s, const void* Q, const void* K, const 
         return fwd_bf16<BS>(s, Q, K, V, O, LSE, row_ptr, col_idx, nnzb, st);
     } else {
         if (many_short_rows(s, nnzb))
-            return launch_fwd<T, BS, typename SplitMany<T, BS>::fwd>(s, Q, K, V, O, LSE, row_ptr, col_idx, st);
+            return launch_fwd<T, BS, typename SplitMany<T, BS>::fwd>(s, Q, K, V, O, LSE, row_ptr, col_idx, nnzb, st);
         // 16 rows a workgroup (32: half the tile traffic) until there are enough of them anyway: a row of many blocks is
         // then shared by twice the compute units, whose matrix cores it fills.  fp32, 32 -> 16 rows: 2 heads x 8192, block
         // 32, 3 %, 87 -> 54 us; 8 x 2048, 10 %, 24.3 -> 18.7; 4 x 1024, block 64, 20 %, 11.7 -> 7.8; 8 x 2048, 30 %, 37.5 -> 35.0;
         // 32 x 2048, block 64 (2048 workgroups of 32 rows) 45.9 -> 47.3; 64 x 2048, block 32 (4096) 96.4 both.
         if (BS > 16 && (long long)s.BH * s.L / 32 >= 2048)
-            return launch_fwd<T, BS, SplitFew<T, BS>>(s, Q, K, V, O, LSE, row_ptr, col_idx, st);
-        return launch_fwd<T, BS, Split<T, BS, 1, 4, 1>>(s, Q, K, V, O, LSE, row_ptr, col_idx, st);
+            return launch_fwd<T, BS, SplitFew<T, BS>>(s, Q, K, V, O, LSE, row_ptr, col_idx, nnzb, st);
+        return launch_fwd<T, BS, Split<T, BS, 1, 4, 1>>(s, Q, K, V, O, LSE, row_ptr, col_idx, nnzb, st);
     }
 }
 

@@ -125,9 +125,11 @@ def test_forward_more_rows_than_run_at_once(sp):
 
 # fp32: 16 rows a forward workgroup below 2048 workgroups of 32 rows, 32 from there on; more backward workgroups than run
 # at once, so that the rows of more than twice the mean go first (block 64: a row's two workgroups together), at head counts that
-# do not divide over the XCDs; bf16 of block 16 likewise; one long row, one without a diagonal block, an empty one
+# do not divide over the XCDs; bf16 of block 16 likewise; the forward's rows by length from half as many workgroups again as run
+# at once and more than 32 block rows; one long row, one without a diagonal block, an empty one
 @pytest.mark.parametrize("dtype,block,BH,nb", [("f32", 32, 63, 32), ("f32", 32, 64, 32), ("f32", 64, 15, 24), ("f32", 64, 43, 24),
-                                               ("f32", 16, 21, 40), ("bf16", 16, 37, 44)])
+                                               ("f32", 16, 21, 40), ("bf16", 16, 37, 44), ("f32", 32, 24, 40), ("f32", 64, 11, 36),
+                                               ("f32", 32, 61, 34)])
 def test_generic_kernels_rows_by_length(sp, dtype, block, BH, nb):
     rng = np.random.default_rng(BH)
     Q, K, V, dO = [si.round_to_dtype(rng.standard_normal((BH, nb * block, 64), dtype=np.float32), dtype) for _ in range(4)]
