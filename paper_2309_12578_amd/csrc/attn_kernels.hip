@@ -59,7 +59,6 @@ template <typename T, int BS> using SplitFew = Split<T, BS, BS == 16 ? 1 : 2, 4,
 // merge cost more than the tiles, so fewer waves share a row.
 template <typename T, int BS> struct SplitMany;   // forward, backward, backward of rows with hardly more than one block
 template <typename T> struct SplitMany<T, 16> {
-    typedef SplitFew<T, 16> fwd;
     typedef Split<T, 16, 1, 2, 1> bwd, bwd_single;
 };
 template <typename T> struct SplitMany<T, 32> {
@@ -156,11 +155,11 @@ inline long long group_grid(long long n) { return (n + 7) / 8 * 8; }
 // ------------------------------------------------------------------------------------------------
 // forward: workgroup = (head, S::OWN query rows)
 // ------------------------------------------------------------------------------------------------
-template <typename T, int BS, typename S>
+template <typename T, int BS, typename S, bool CUT>
 __global__ __launch_bounds__(S::W * 64, 2) void attn_fwd_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, T* __restrict__ O,
-    float* __restrict__ LSE, const int* __restrict__ row_ptr, const int* __restrict__ col_idx, int L,
-    int nb, int total, int sort_rows, float scale_log2, int paper_denom) {
+    float* __restrict__ LSE, const int* __restrict__ row_ptr, const int* __restrict__ col_idx,
+    CutOf<CUT> cut, int L, int nb, int total, int sort_rows, float scale_log2, int paper_denom) {
     typedef typename Elem<T>::Frag Frag;
     typedef typename Elem<T>::Quad Quad;
     constexpr int NQ = S::NQ, KT = S::KT, NDC = S::NDC, OWN = S::OWN;
@@ -168,16 +167,34 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_fwd_kernel(
     __shared__ float m_s[S::WT][OWN], l_s[S::WT][OWN];
 
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
-    int bh, I, part;
-    if (sort_rows) {
-        const int row = (blockIdx.x >> 3) / S::PARTS * 8 + (blockIdx.x & 7);   // a row's workgroups on one XCD
+    int bh, I, part, id = blockIdx.x;
+    [[maybe_unused]] RowPieces cuts = {0, 1, 0, 0};
+    [[maybe_unused]] int piece = 0;
+    bool helper = false;
+    if constexpr (CUT) {
+        helper = id < cut.groups;
+        if (!helper) id -= cut.groups;
+    }
+    if (helper) {   // a piece of a long row
+        if constexpr (CUT) {
+            const int i = (id >> 3) / S::PARTS * 8 + (id & 7), heads = total / (nb * S::PARTS), want = i / heads;
+            if (want >= cut.helpers) return;
+            cuts = row_pieces<false>(row_ptr, nb, cut, want, lane);
+            if (cuts.row < 0) return;
+            bh = i % heads;
+            I = cuts.row;
+            part = (id >> 3) % S::PARTS;
+            piece = want - cuts.first + 1;
+        }
+    } else if (sort_rows) {
+        const int row = (id >> 3) / S::PARTS * 8 + (id & 7);   // a row's workgroups on one XCD
         if (row >= total / S::PARTS) return;
         const RowOfHead mine = long_rows_first<true>(row_ptr, nb, total / (nb * S::PARTS), row, lane);
         bh = mine.head;
         I = mine.row;
-        part = (blockIdx.x >> 3) % S::PARTS;
+        part = (id >> 3) % S::PARTS;
     } else {
-        const int item = item_of_group(blockIdx.x, total);
+        const int item = item_of_group(id, total);
         if (item < 0) return;
         bh = item / (nb * S::PARTS);
         I = item % (nb * S::PARTS) / S::PARTS;
@@ -187,7 +204,16 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_fwd_kernel(
     const size_t head = (size_t)bh * L * kD;
     const int wg0 = I * BS + part * OWN, row0 = wg0 + own;   // rows of the workgroup, of the wave
 
-    const int jb = row_ptr[I], n = row_ptr[I + 1] - jb, nt = n * S::TPB;
+    int jb = row_ptr[I];
+    const int n_row = row_ptr[I + 1] - jb;
+    int n = n_row;   // blocks of this workgroup
+    if constexpr (CUT) if (n_row > cut.longest) {
+        if (!helper) cuts = row_pieces<true>(row_ptr, nb, cut, I, lane);
+        const int from = piece * n_row / cuts.count;
+        n = (piece + 1) * n_row / cuts.count - from;
+        jb += from;
+    }
+    const int nt = n * S::TPB;
     const int* cols = col_idx + jb;
     const int cols64 = n > 0 ? cols[lane < n ? lane : n - 1] : 0;
     Frag qf[NQ][NDC];
@@ -285,7 +311,7 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_fwd_kernel(
     // Algorithm 6: every masked entry of the row counts as a score of 0 (a row that keeps nothing
     // has no entry to normalise and stays at O = 0, LSE = -inf).  The sums are up to 2^kRescaleSlack times what they
     // would be against the row's maximum.
-    const float masked = paper_denom && n > 0 ? (float)(L - n * BS) : 0.f;
+    const float masked = paper_denom && n_row > 0 ? (float)(L - n_row * BS) : 0.f;
     if constexpr (S::WT == 1) {
 #pragma unroll
         for (int h = 0; h < NQ; ++h) {
@@ -313,14 +339,13 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_fwd_kernel(
         }
     }
     __syncthreads();
-#pragma unroll
-    for (int p = 0; p < OWN; p += 4 * S::W) {
-        const int q = p + (tid >> 4), d = (tid & 15) * 4;
-        float mm = m_s[0][q];
+    // four numbers of row q of this workgroup's blocks, the row's reference and sum
+    auto merged = [&](int q, int d, float& mm, float& l) {
+        mm = m_s[0][q];
 #pragma unroll
         for (int w = 1; w < S::WT; ++w) mm = fmaxf(mm, m_s[w][q]);
         f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
-        float l = 0.f;
+        l = 0.f;
         if (n > 0) {
 #pragma unroll
             for (int w = 0; w < S::WT; ++w) {
@@ -328,6 +353,49 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_fwd_kernel(
                 l += l_s[w][q] * a;
                 o += *reinterpret_cast<const f32x4*>(&o_s[w][q * kPatchLd + d]) * a;
             }
+        }
+        return o;
+    };
+    // [head][slot][part]: the rows' numbers, then their references and sums
+    constexpr int kPart = OWN * (kD + 2);
+    [[maybe_unused]] float* parts = nullptr;
+    if constexpr (CUT) if (cuts.count > 1) {   // a long row in pieces: see attn_bf16_tiles.h
+        __shared__ int flag;
+        const size_t slot = ((size_t)bh * cut.slots + cuts.slot) * S::PARTS + part;
+        parts = cut.parts + slot * kPart;
+        float* const mine = parts + (size_t)piece * (S::PARTS * kPart);
+#pragma unroll
+        for (int p = 0; p < OWN; p += 4 * S::W) {
+            const int q = p + (tid >> 4), d = (tid & 15) * 4;
+            float mm, l;
+            const f32x4 o = merged(q, d, mm, l);
+            put_shared(mine + q * kD + d, o[0], o[1]);
+            put_shared(mine + q * kD + d + 2, o[2], o[3]);
+            if (d == 0) put_shared(mine + OWN * kD + 2 * q, mm, l);
+        }
+        if (!last_to_arrive(cut.counters + slot, cut.tag, cuts.count, &flag)) return;
+    }
+#pragma unroll
+    for (int p = 0; p < OWN; p += 4 * S::W) {
+        const int q = p + (tid >> 4), d = (tid & 15) * 4;
+        float mm, l;
+        f32x4 o;
+        if (CUT && parts) {   // every piece has blocks, so that its references are finite
+            mm = -INFINITY;
+            l = 0.f;
+            o = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+            for (int c = 0; c < cuts.count; ++c) {
+                const float* const part = parts + (size_t)c * (S::PARTS * kPart);
+                const float2 lo = get_shared(part + q * kD + d), hi = get_shared(part + q * kD + d + 2);
+                const float2 ml = get_shared(part + OWN * kD + 2 * q);
+                const float m_new = fmaxf(mm, ml.x), a = exp2f(mm - m_new), b = exp2f(ml.x - m_new);
+                mm = m_new;
+                l = l * a + ml.y * b;
+                o = o * a + f32x4{lo.x, lo.y, hi.x, hi.y} * b;
+            }
+        } else {
+            o = merged(q, d, mm, l);
         }
         if (masked > 0.f) {
             const float mp = fmaxf(mm, 0.f);
@@ -693,21 +761,67 @@ static bool many_short_rows(const AttnShape& s, int nnzb) {
     return rows * s.nb >= (single_block_rows(s, nnzb) ? 40 : 100) * tiles_times_nb;
 }
 
+// 16 rows a workgroup (32: half the tile traffic) until there are enough of them anyway: a row of many blocks is
+// then shared by twice the compute units, whose matrix cores it fills.  fp32, 32 -> 16 rows: 2 heads x 8192, block
+// 32, 3 %, 87 -> 54 us; 8 x 2048, 10 %, 24.3 -> 18.7; 4 x 1024, block 64, 20 %, 11.7 -> 7.8; 8 x 2048, 30 %, 37.5 -> 35.0;
+// 32 x 2048, block 64 (2048 workgroups of 32 rows) 45.9 -> 47.3; 64 x 2048, block 32 (4096) 96.4 both.
+// 0: many short rows, which waves do not share.
+static int fwd_rows(const AttnShape& s, int nnzb) {
+    if (s.bs == 16) return 16;
+    if (many_short_rows(s, nnzb)) return 0;
+    return s.bs > 16 && (long long)s.BH * s.L / 32 >= 2048 ? 32 : 16;
+}
+
+// Workgroups of four waves that run at once: four or three waves a SIMD.
+static long long fwd_resident(int rows) { return 256 * (rows == 16 ? 4 : 3); }
+
+// Whether there are half as many workgroups again as run at once, so that the order of the rows matters.
+static bool fwd_many(const AttnShape& s, int rows) { return 2ll * s.BH * s.L / rows > 3 * fwd_resident(rows); }
+
+// Rows in pieces, from twice the mean on as long as about all workgroups run at once (else the long ones start first, and
+// have to outlast the launch from there to be cut).  Forward kernel, fp32, block 32: 2 heads x 8192, 3 %, 51 -> 23.4 us; 4 x 4096, 5 %, 28 -> 18.9; 8 x 2048, 10 %,
+// 20.3 -> 17.7, 20 %, 28.6 -> 26; block 64, 3 x 4096, 10 %, 31.4 -> 26.8; block 16, 2 x 2048, 15.7 -> 12; bf16, block 16, 9 x 1936, 8 %, 12.8 -> 12.3.
+// Cut where the rule leaves them whole, 16 x 2048: block 32 28.9 -> 30, block 16 22.7 -> 23.5, bf16 15.3 -> 16.1; 4 x 1024, block 16, 8.5 -> 9.4.
+RowCut generic_fwd_cut(const AttnShape& s, int nnzb) {
+    RowCut cut;
+    const int rows = fwd_rows(s, nnzb);
+    if (rows == 0) return cut;
+    const bool many = fwd_many(s, rows);
+    if (many ? s.BH > 8 : s.bs == 16 && s.nb <= 64) return cut;   // rather no helpers that find nothing to do
+    const int parts = s.bs / rows;
+    cut.decide(s, nnzb, (many ? 2 : 1) * (long long)s.BH * nnzb * parts / fwd_resident(rows), !many);
+    const long long most = 512 / ((long long)s.BH * parts);   // a helper for each piece, and not many that find nothing to do
+    if (cut.slots > most) cut.slots = (int)most;
+    if (cut.slots < 2) return RowCut{};
+    cut.helpers = cut.slots - 1;
+    cut.groups = parts * ((s.BH * cut.helpers + 7) & ~7);
+    return cut;
+}
+
 template <typename T, int BS, typename S>
 static hipError_t launch_fwd(const AttnShape& s, const void* Q, const void* K, const void* V, void* O,
                              float* LSE, const int* row_ptr, const int* col_idx, int nnzb, hipStream_t st) {
     const long long total = (long long)s.nb * s.BH * S::PARTS;
-    // Rows of more than twice the mean first, as in launch_bwd, where half as many workgroups again as run at once (four or
-    // three waves a SIMD) leave a late one alone.  fp32, block 32: 32 heads x 2048, 10 %, 61.3 -> 48.3 us, 16 x 2048 33.3 -> 29.1; block 16, 16 x
+    // Rows of more than twice the mean first, as in launch_bwd.  fp32, block 32: 32 heads x 2048, 10 %, 61.3 -> 48.3 us, 16 x 2048 33.3 -> 29.1; block 16, 16 x
     // 2048, 6 %, 27.2 -> 22.7; bf16, 17.2 -> 15.4.  The search costs half a microsecond to one: 9 x 1936 (few more than run at once)
     // 12.7 -> 13.2; up to 32 block rows no row is long enough, 32 x 1024, block 64, 28.2 -> 29.2.
-    const long long resident = 256 * 4 * (S::NQ == 1 ? 4 : 3) / S::W;
-    const int sort_rows = s.nb > 32 && (long long)nnzb * (BS / 16) >= 6ll * s.nb && 2 * total > 3 * resident;
+    const int sort_rows = s.nb > 32 && (long long)nnzb * (BS / 16) >= 6ll * s.nb && fwd_many(s, S::OWN);
     const long long grid = sort_rows ? S::PARTS * group_grid((long long)s.nb * s.BH) : group_grid(total);
     if (grid > 0x7fffffffll) return hipErrorInvalidValue;
-    attn_fwd_kernel<T, BS, S><<<dim3((unsigned)grid), dim3(S::W * 64), 0, st>>>(
-        static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V), static_cast<T*>(O), LSE, row_ptr,
-        col_idx, s.L, s.nb, (int)total, sort_rows, s.scale * kLog2e, s.paper_denom);
+    auto launch = [&](auto kernel, auto cut_arg, int helpers) {
+        kernel<<<dim3((unsigned)(helpers + grid)), dim3(S::W * 64), 0, st>>>(
+            static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V), static_cast<T*>(O), LSE, row_ptr, col_idx,
+            cut_arg, s.L, s.nb, (int)total, sort_rows, s.scale * kLog2e, s.paper_denom);
+    };
+    RowCut cut;
+    if (s.fwd_room) cut = RowCut(s, nnzb);
+    if constexpr (S::WT > 2) {
+        if (cut.slots && grid + cut.groups <= 0x7fffffffll) {
+            launch(attn_fwd_kernel<T, BS, S, true>, cut, cut.groups);
+            return hipGetLastError();
+        }
+    }
+    launch(attn_fwd_kernel<T, BS, S, false>, NoCut{}, 0);
     return hipGetLastError();
 }
 
@@ -757,14 +871,11 @@ static hipError_t fwd_t(const AttnShape& s, const void* Q, const void* K, const 
     if constexpr (sizeof(T) == 2 && BS >= 32) {
         return fwd_bf16<BS>(s, Q, K, V, O, LSE, row_ptr, col_idx, nnzb, st);
     } else {
-        if (many_short_rows(s, nnzb))
-            return launch_fwd<T, BS, typename SplitMany<T, BS>::fwd>(s, Q, K, V, O, LSE, row_ptr, col_idx, nnzb, st);
-        // 16 rows a workgroup (32: half the tile traffic) until there are enough of them anyway: a row of many blocks is
-        // then shared by twice the compute units, whose matrix cores it fills.  fp32, 32 -> 16 rows: 2 heads x 8192, block
-        // 32, 3 %, 87 -> 54 us; 8 x 2048, 10 %, 24.3 -> 18.7; 4 x 1024, block 64, 20 %, 11.7 -> 7.8; 8 x 2048, 30 %, 37.5 -> 35.0;
-        // 32 x 2048, block 64 (2048 workgroups of 32 rows) 45.9 -> 47.3; 64 x 2048, block 32 (4096) 96.4 both.
-        if (BS > 16 && (long long)s.BH * s.L / 32 >= 2048)
-            return launch_fwd<T, BS, SplitFew<T, BS>>(s, Q, K, V, O, LSE, row_ptr, col_idx, nnzb, st);
+        const int rows = fwd_rows(s, nnzb);
+        if constexpr (BS > 16) {
+            if (rows == 0) return launch_fwd<T, BS, typename SplitMany<T, BS>::fwd>(s, Q, K, V, O, LSE, row_ptr, col_idx, nnzb, st);
+            if (rows == 32) return launch_fwd<T, BS, SplitFew<T, BS>>(s, Q, K, V, O, LSE, row_ptr, col_idx, nnzb, st);
+        }
         return launch_fwd<T, BS, Split<T, BS, 1, 4, 1>>(s, Q, K, V, O, LSE, row_ptr, col_idx, nnzb, st);
     }
 }

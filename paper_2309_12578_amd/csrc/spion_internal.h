@@ -43,7 +43,7 @@ struct AttnShape {
     unsigned long long tag;       // of this call alone, 1 .. 2^48 - 1 (see last_to_arrive)
 };
 
-// How the tuned kernels cut long block rows (see attn_bf16_tiles.h), from what the host knows of a pattern.
+// How the kernels cut long block rows (see attn_bf16_tiles.h), from what the host knows of a pattern.
 struct RowCut {
     int piece = 0;     // kept blocks of a piece, at most
     int longest = 0;   // a row of more is cut
@@ -51,17 +51,22 @@ struct RowCut {
     int helpers = 0;   // workgroups per head for the pieces behind the first of each row
     int groups = 0;    // of all heads, a multiple of 8
     unsigned long long tag = 0;
-    unsigned long long* counters = nullptr;   // [head][slots], in use: that of a row's first piece
+    unsigned long long* counters = nullptr;   // [head][slots] (fp32, block 16: [workgroup of a block row]), in use: that of a row's first piece
     float* parts = nullptr;                   // partial results, as many
     RowCut() = default;
     RowCut(const AttnShape& s, int nnzb);   // the forward's
-    // piece, longest and slots, where each of the workgroups that run at once has `steps` to do
-    void decide(const AttnShape& s, int nnzb, long long steps);
+    // piece, longest and slots, where each of the workgroups that run at once has `steps` to do; short_too: rows from
+    // twice the mean on
+    void decide(const AttnShape& s, int nnzb, long long steps, bool short_too = false);
     static constexpr int kSlots = 32;       // most: two rows of half the columns at 3 % kept blocks; 0.6 MB of room per head
-    size_t counter_bytes(int BH) const { return ((size_t)BH * slots * 8 + 255) / 256 * 256; }
-    static constexpr size_t partial_bytes(int bs) { return (size_t)(bs / 16) * 64 * 18 * sizeof(float); }   // O, maximum, sum
+    size_t counter_bytes(int BH) const { return ((size_t)BH * slots * 4 * 8 + 255) / 256 * 256; }
+    // O, maximum, sum; the kernels of fp32 and block 16 use 66 floats a row of these 72
+    static constexpr size_t partial_bytes(int bs) { return (size_t)(bs / 16) * 64 * 18 * sizeof(float); }
     size_t room_bytes(int BH, int bs) const { return slots ? counter_bytes(BH) + (size_t)BH * slots * partial_bytes(bs) : 0; }
 };
+
+// attn_kernels.hip: the plan for fp32 and block 16, without its memory
+RowCut generic_fwd_cut(const AttnShape& s, int nnzb);
 
 hipError_t launch_attn_fwd(const AttnShape& s, const void* Q, const void* K, const void* V, void* O,
                            float* LSE, const int* row_ptr, const int* col_idx, int nnzb, hipStream_t st);

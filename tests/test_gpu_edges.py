@@ -161,6 +161,23 @@ def test_long_rows_in_pieces(sp, block, BH, nb, longs, denom):
     _attention(sp, Q, K, V, dO, fl, block, "bf16", sorted({0, BH // 2, BH - 1}), flags=sp.SPION_ATTN_PAPER_DENOM if denom else 0)
 
 
+# The kernels of fp32 and of block size 16: a helper for each piece and part of a block row; 16 and 32 rows a workgroup; a row of more
+# pieces than there are helpers for stays whole; no diagonal block in a piece, an empty row beside them
+@pytest.mark.parametrize("dtype,block", [("f32", 16), ("f32", 32), ("f32", 64), ("bf16", 16)])
+@pytest.mark.parametrize("BH,nb,longs,denom", [(1, 65, (65,), True), (3, 80, (80, 37, 25, 24), False), (2, 130, (130, 64, 65, 129), True),
+                                               (20, 70, (70, 60), False)])
+def test_long_rows_in_pieces_of_the_generic_kernels(sp, dtype, block, BH, nb, longs, denom):
+    rng = np.random.default_rng(nb + BH)
+    Q, K, V, dO = [si.round_to_dtype(rng.standard_normal((BH, nb * block, 64), dtype=np.float32), dtype) for _ in range(4)]
+    fl = np.eye(nb, dtype=np.uint8)
+    rows = [nb - 1, 0, 7, nb // 2][:len(longs)]
+    for r, n in zip(rows, longs):
+        fl[r] = 0
+        fl[r, rng.choice(nb, n, replace=False)] = 1
+    fl[5, :] = 0
+    _attention(sp, Q, K, V, dO, fl, block, dtype, [0, BH - 1], flags=sp.SPION_ATTN_PAPER_DENOM if denom else 0)
+
+
 def test_long_rows_in_pieces_again_and_in_a_graph(sp):
     """Whichever piece is the last to arrive: the same bits every time, and in replays, which share their launches' tags, on other
     inputs and with other work in between."""
