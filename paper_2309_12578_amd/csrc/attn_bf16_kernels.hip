@@ -284,9 +284,12 @@ static int fwd_resident(int bs) { return 256 * (bs == 64 ? 4 : 8); }
 // with two long rows): 8 heads x 8192, block 32, rows of 121 blocks, 41.9 / 20.1; 4 x 16384, block 64, 65.5 / 29.2; 4 x 8192, block 64, rows of
 // 71, 37.6 / 20.9; 1 x 4096, block 32, 17.1 / 10.8; 16 x 16320, block 64, rows of 112, 83.1 / 78.1.  Rows of 45 and 27 at 64 x 4160 and 128 x 2080,
 // block 32, which the rule leaves whole, 38.6 / 40.5 and 38.5 / 41.9.  A pattern without long rows: 76.6 / 76.9, 14.7 / 14.8.
+// With 33 to 64 block rows, where all of them run at once (short_too) and nothing hides the longest, rows of twice the mean are cut:
+// 8 x 2048, block 32, rows of 24 blocks, 11.2 / 9.5; 32 x 2048 19.3 / 16.6; 4 x 4096, block 64, 16.7 / 13.1; 16 x 4096, 10 %, 26.1 / 19.9; 2 x 4096,
+// 15 %, 20.8 / 13.7; without long rows 14.9 / 14.6.
 void RowCut::decide(const AttnShape& s, int nnzb, long long steps, bool short_too) {
-    // Up to 64 block rows a row is not that long, and what the others pay shows: kernels of 14 and 45 us without a row
-    // to cut, 16 and 32 heads x 4096, block 64, took 0.4 and 1 us longer.
+    // Up to 64 block rows a row is not that long, and what the others pay shows: a kernel of 45 us without a row to cut, 32 heads x
+    // 4096, block 64, took 1 us longer.
     if (s.nb <= (short_too ? 32 : 64)) return;
     const int mean = (nnzb + s.nb - 1) / s.nb;
     piece = short_too ? (mean < 6 ? 8 : 3 * mean / 2) : (mean < 6 ? 12 : 2 * mean);
@@ -304,7 +307,7 @@ RowCut::RowCut(const AttnShape& s, int nnzb) {
     if (!s.is_bf16 || s.bs == 16) {
         *this = generic_fwd_cut(s, nnzb);
     } else {
-        decide(s, nnzb, (long long)s.BH * nnzb / fwd_resident(s.bs));
+        decide(s, nnzb, (long long)s.BH * nnzb / fwd_resident(s.bs), s.nb <= 64 && s.BH * s.nb <= fwd_resident(s.bs));
         helpers = s.BH <= 8 ? 16 : s.BH < 128 ? 128 / s.BH : 1;
         if (helpers >= slots) helpers = slots > 0 ? slots - 1 : 0;
         groups = (s.BH * helpers + 7) & ~7;

@@ -140,12 +140,13 @@ def test_generic_kernels_rows_by_length(sp, dtype, block, BH, nb):
     _attention(sp, Q, K, V, dO, fl, block, dtype, [0, BH // 2, BH - 1])
 
 
-# bf16, more than 64 block rows: rows of more than four times the mean (and 24) are cut into pieces that other workgroups take:
-# two pieces and many; more pieces than there is room for (32 a head), a helper for each, for several, two a head (130
-# heads); no diagonal block, in the first piece or a later one; the last row; an empty row beside them; 64 block rows: none cut
+# bf16: rows of more than four times the mean (and 24) are cut into pieces that other workgroups take; of 33 to 64 block rows
+# that all run at once, those of twice the mean (and 12): two pieces and many; more pieces than there is
+# room for (32 a head), a helper for each, for several, two a head (130 heads); no diagonal block, in the first piece or a later
+# one; the last row; an empty row beside them; 32 block rows: none cut
 @pytest.mark.parametrize("block", [32, 64])
 @pytest.mark.parametrize("BH,nb,longs", [(1, 65, (65,)), (1, 70, (25, 24)), (3, 80, (80, 37, 25, 24)), (2, 130, (130, 64, 65, 129)),
-                                         (64, 72, (72, 72, 72, 30)), (130, 66, (60, 26)), (5, 64, (64, 30))])
+                                         (64, 72, (72, 72, 72, 30)), (130, 66, (60, 26)), (5, 33, (33, 13, 12)), (5, 32, (32, 30))])
 @pytest.mark.parametrize("denom", [False, True])
 def test_long_rows_in_pieces(sp, block, BH, nb, longs, denom):
     rng = np.random.default_rng(nb + BH)
