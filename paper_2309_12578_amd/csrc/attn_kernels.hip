@@ -417,13 +417,13 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_fwd_kernel(
 // Grid: some of the long block rows, the long key items (chunks of split columns, long columns), the other block rows, the
 // other key items; all heads in each.
 // ------------------------------------------------------------------------------------------------
-template <typename T, int BS, typename S>
+template <typename T, int BS, typename S, bool CUT>
 __global__ __launch_bounds__(S::W * 64, 2) void attn_bwd_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, const T* __restrict__ O,
     const T* __restrict__ dO, const float* __restrict__ LSE, T* __restrict__ dQ, T* __restrict__ dK,
     T* __restrict__ dV, const int* __restrict__ row_ptr, const int* __restrict__ col_idx,
     const int* __restrict__ col_ptr, const int* __restrict__ row_idx, float* __restrict__ partial,
-    unsigned long long* __restrict__ counters, unsigned long long tag, int n_slots, int BH, int L, int nb, int n_key_a,
+    unsigned long long* __restrict__ counters, unsigned long long tag, CutOf<CUT> cut, int n_slots, int BH, int L, int nb, int n_key_a,
     int n_rows, int n_key_c, int w_first, int chunk, int mid, int early_rows, float scale, float scale_log2) {
     typedef typename Elem<T>::Frag Frag;
     typedef typename Elem<T>::Quad Quad;
@@ -439,8 +439,14 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_bwd_kernel(
     const int early = S::PARTS * early_rows;
     const int late = early_rows ? S::PARTS * padded(BH * n_rows) - early : padded(BH * n_rows * S::PARTS);
     int id = blockIdx.x, first = 0, first_row = 0;
-    bool key_side = false;
-    if (id >= early) {
+    [[maybe_unused]] RowPieces cuts = {0, 1, 0, 0};
+    [[maybe_unused]] int piece = 0;
+    bool key_side = false, helper = false;
+    if constexpr (CUT) {
+        helper = id < cut.groups;
+        if (!helper) id -= cut.groups;
+    }
+    if (!helper && id >= early) {
         id -= early;
         key_side = true;
         if (id >= BH * n_key_a * S::PARTS) {
@@ -456,7 +462,18 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_bwd_kernel(
         }
     }
     int bh, idx, sub;   // sub: the workgroup's rows within the block
-    if (key_side) {
+    if (helper) {   // a piece of a long row
+        if constexpr (CUT) {
+            const int i = (id >> 3) / S::PARTS * 8 + (id & 7), want = i / BH;
+            if (want >= cut.helpers) return;
+            cuts = row_pieces<false>(row_ptr, nb, cut, want, lane);
+            if (cuts.row < 0) return;
+            bh = i % BH;
+            idx = cuts.row;
+            sub = (id >> 3) % S::PARTS * OWN;
+            piece = want - cuts.first + 1;
+        }
+    } else if (key_side) {
         // The items of all heads together, longest first; heads keep to an XCD where that shares them out evenly.  (In
         // contiguous eighths, as the rows are, a few heads' long items met on a few XCDs: fp32, 3 x 4096, block 64, 75 -> 71.5 us;
         // 32 x 1024, block 64, 105 -> 96.)
@@ -499,7 +516,14 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_bwd_kernel(
 
     if (!key_side) {
         const int I = idx, row0 = I * BS + sub + own;
-        const int jb = row_ptr[I], n = row_ptr[I + 1] - jb, nt = n * S::TPB;
+        int jb = row_ptr[I], n = row_ptr[I + 1] - jb;
+        if constexpr (CUT) if (n > cut.longest) {
+            if (!helper) cuts = row_pieces<true>(row_ptr, nb, cut, I, lane);
+            const int from = piece * n / cuts.count;
+            n = (piece + 1) * n / cuts.count - from;
+            jb += from;
+        }
+        const int nt = n * S::TPB;
         const int* cols = col_idx + jb;
         const int cols64 = n > 0 ? cols[lane < n ? lane : n - 1] : 0;
         auto tile_at = [&](int t) { return head + (size_t)(list_at(cols, cols64, t / S::TPB) * BS + t % S::TPB * 16) * kD; };
@@ -580,6 +604,31 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_bwd_kernel(
         }
         put_patch<NQ>(&acc_s[wt][own * kPatchLd], dq, r, g);
         __syncthreads();
+        if constexpr (CUT) if (cuts.count > 1) {   // a long row in pieces: see attn_bf16_tiles.h
+            const size_t slot = ((size_t)bh * cut.slots + cuts.slot) * S::PARTS + sub / OWN;
+            float* const parts = cut.parts + slot * (OWN * kD) + tid * 4;
+            constexpr int kPiece = S::PARTS * OWN * kD;
+#pragma unroll
+            for (int p = 0; p < OWN; p += 4 * S::W) {
+                const f32x4 v = merged(p);
+                float* const mine = parts + (size_t)piece * kPiece + p * kD;
+                put_shared(mine, v[0], v[1]);
+                put_shared(mine + 2, v[2], v[3]);
+            }
+            if (!last_to_arrive(cut.counters + slot, cut.tag, cuts.count, &flag)) return;
+#pragma unroll
+            for (int p = 0; p < OWN; p += 4 * S::W) {
+                f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+                for (int c = 0; c < cuts.count; ++c) {
+                    const float* const part = parts + (size_t)c * kPiece + p * kD;
+                    const float2 lo = get_shared(part), hi = get_shared(part + 2);
+                    v += f32x4{lo.x, lo.y, hi.x, hi.y};
+                }
+                store_quad<T>(dQ + head + (size_t)(I * BS + p) * kD + out, v * scale);
+            }
+            return;
+        }
 #pragma unroll
         for (int p = 0; p < OWN; p += 4 * S::W)
             store_quad<T>(dQ + head + (size_t)(I * BS + p) * kD + out, merged(p) * scale);
@@ -736,8 +785,8 @@ BwdWorkspace::BwdWorkspace(int BH, int bs, int nb, int nnzb_, int key_chunk, int
     counter_bytes = (slots * (bs / 16) * 8 + 255) / 256 * 256;
     row_counters = counter_bytes + slots * 2 * bs * kD * sizeof(float);
     // (with more heads the rule never cuts a row, however few blocks are kept)
-    const size_t row_slots = bs >= 32 && nb > 64 && 4 * BH < bwd_resident(bs) ? (size_t)BH * RowCut::kSlots : 0;
-    row_parts = row_counters + row_slots * 8;
+    row_slots = nb > 64 && 4 * BH < bwd_resident(bs) ? (size_t)BH * RowCut::kSlots : 0;
+    row_parts = row_counters + row_slots * (bs / 16) * 8;
     total = row_parts + row_slots * bs * kD * sizeof(float);
 }
 
@@ -825,6 +874,22 @@ static hipError_t launch_fwd(const AttnShape& s, const void* Q, const void* K, c
     return hipGetLastError();
 }
 
+// The query side's rows that are cut, with the steps of both sides.  Backward kernel, fp32, block 32: 2 heads x 8192, 3 %, rows of
+// 80 blocks, 125 -> 61.8 us; 4 x 4096, 5 %, 61.6 -> 52.8; block 16, 2 x 2048, 8 %, 26.4 -> 21.3; patterns that are left whole, the same.
+static RowCut generic_bwd_cut(const AttnShape& s, const BwdWorkspace& ws, int parts, long long resident, void* workspace) {
+    RowCut cut;
+    if (ws.row_slots == 0) return cut;
+    cut.decide(s, ws.nnzb, 2ll * s.BH * ((long long)ws.nnzb + s.nb) * parts / resident);
+    const long long most = 512 / ((long long)s.BH * parts);   // as the forward
+    if (cut.slots > most) cut.slots = (int)most;
+    if (cut.slots < 2) return RowCut{};
+    cut.helpers = cut.slots - 1;
+    cut.groups = parts * ((s.BH * cut.helpers + 7) & ~7);
+    cut.counters = reinterpret_cast<unsigned long long*>(static_cast<char*>(workspace) + ws.row_counters);
+    cut.parts = reinterpret_cast<float*>(static_cast<char*>(workspace) + ws.row_parts);
+    return cut;
+}
+
 template <typename T, int BS, typename S>
 static hipError_t launch_bwd(const AttnShape& s, const void* Q, const void* K, const void* V, const void* O,
                              const void* dO, const float* LSE, void* dQ, void* dK, void* dV, const int* row_ptr,
@@ -853,16 +918,20 @@ static hipError_t launch_bwd(const AttnShape& s, const void* Q, const void* K, c
     const int mid = 2 * per_item * (n_key_a + n_rows + n_key_c) > 3 * resident ? kMidColumn : ws.chunk;
     const long long grid = group_grid(per_item * n_key_a) + (sort_rows ? S::PARTS * row_items : group_grid(per_item * n_rows)) +
                            group_grid(per_item * n_key_c);
-    if (grid > 0) {
-        attn_bwd_kernel<T, BS, S><<<dim3((unsigned)grid), dim3(S::W * 64), 0, st>>>(
+    auto launch = [&](auto kernel, auto cut_arg, int helpers) {
+        kernel<<<dim3((unsigned)(helpers + grid)), dim3(S::W * 64), 0, st>>>(
             static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V), static_cast<const T*>(O),
             static_cast<const T*>(dO), LSE, static_cast<T*>(dQ), static_cast<T*>(dK), static_cast<T*>(dV), row_ptr,
-            col_idx, col_ptr, row_idx, partial, counters, s.tag, ws.n_slots, s.BH, s.L, s.nb, n_key_a, n_rows, n_key_c, ws.w_first,
-            ws.chunk, mid, early_rows, s.scale, s.scale * kLog2e);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+            col_idx, col_ptr, row_idx, partial, counters, s.tag, cut_arg, ws.n_slots, s.BH, s.L, s.nb, n_key_a, n_rows, n_key_c,
+            ws.w_first, ws.chunk, mid, early_rows, s.scale, s.scale * kLog2e);
+        return hipGetLastError();
+    };
+    if (grid <= 0) return hipSuccess;
+    if constexpr (S::WT > 2) {
+        const RowCut cut = rows ? generic_bwd_cut(s, ws, S::PARTS, resident, workspace) : RowCut{};
+        if (cut.slots && grid + cut.groups <= 0x7fffffffll) return launch(attn_bwd_kernel<T, BS, S, true>, cut, cut.groups);
     }
-    return hipSuccess;
+    return launch(attn_bwd_kernel<T, BS, S, false>, NoCut{}, 0);
 }
 
 template <typename T, int BS>

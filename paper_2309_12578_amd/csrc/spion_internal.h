@@ -82,7 +82,8 @@ struct BwdWorkspace {
     int w_max, w_first;              // work items per head (upper bound); those that may be chunks come first
     int n_slots;                     // partial slots per head (upper bound)
     size_t counter_bytes;            // one per slot and 16 rows, at the workspace's start; the partial tiles behind them
-    size_t row_counters, row_parts;  // where those of long rows in pieces start: RowCut::kSlots per head
+    size_t row_slots;                // pieces of long rows: RowCut::kSlots per head, or none
+    size_t row_counters, row_parts;  // where theirs start (a counter for every 16 rows)
     size_t total;
     // mid_first: unsplit columns to make room for among the items that come first
     BwdWorkspace(int BH, int bs, int nb, int nnzb, int key_chunk, int mid_first);

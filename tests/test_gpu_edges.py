@@ -302,7 +302,7 @@ def test_cut_columns_and_rows_again_and_in_a_graph(sp, dtype, block):
     fl = np.eye(nb, dtype=np.uint8)
     fl[:, [0, 40]] = 1
     fl[:33, 7] = 1
-    fl[[50, 71], :] = 1   # bf16, block 32 and 64: in pieces
+    fl[[50, 71], :] = 1   # in pieces
     pat = _pattern_from_mask(sp, fl, block)
     gen = torch.Generator(device="cuda").manual_seed(2)
     tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
