@@ -314,9 +314,9 @@ __device__ __forceinline__ bool last_to_arrive(unsigned long long* counter, unsi
     if (threadIdx.x == 0) {
         unsigned long long seen = __hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), next;
         do {
-            next = seen >> 16 == tag ? seen + 1 : tag << 16 | 1;
+            next = seen >> kArriveBits == tag ? seen + 1 : tag << kArriveBits | 1;
         } while (!__hip_atomic_compare_exchange_strong(counter, &seen, next, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        const bool last = (int)(next & 0xffff) == count;
+        const bool last = (int)(next & ((1ull << kArriveBits) - 1ull)) == count;
         if (last) __hip_atomic_store(counter, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         *flag = last;
     }

@@ -32,6 +32,8 @@ hipError_t launch_frobenius_distance(const float* a, const float* b, size_t n, d
                                      hipStream_t st);
 
 // attn_kernels.hip
+constexpr int kArriveBits = 24;   // of a counter of arrivals; its other bits are a tag (a block column can have 2^20 chunks)
+
 struct AttnShape {
     int BH, L, bs, nb;
     int is_bf16;
@@ -40,7 +42,7 @@ struct AttnShape {
     int bwd_phases;     // bit 0: query side (dQ); bit 1: key side (dK, dV)
     int heads_beside;   // 0: tensors [B, H, L, 64]; else H, and rows as HeadRows<true> (bf16, block 32 and 64 only)
     void* fwd_room;     // forward: device memory of RowCut::room_bytes() for the pieces of long rows, or nullptr: rows stay whole
-    unsigned long long tag;       // of this call alone, 1 .. 2^48 - 1 (see last_to_arrive)
+    unsigned long long tag;       // of this call alone, below 2^(64 - kArriveBits) (see last_to_arrive)
 };
 
 // How the kernels cut long block rows (see attn_bf16_tiles.h), from what the host knows of a pattern.
