@@ -960,6 +960,12 @@ static hipError_t bwd_t(const AttnShape& s, const void* Q, const void* K, const 
     } else {
         const BwdWorkspace ws(s.BH, s.bs, s.nb, nnzb, kChunk, s.nb / 8);
         auto* launch = launch_bwd<T, BS, SplitFew<T, BS>>;
+        // 16 rows or keys a workgroup instead of 32 while those of 32 would be at most a quarter more than run at once (512 of
+        // four waves): the compute units they leave idle are worth more than the tiles' second reading.  fp32, backward kernel, block 32: 2 heads x
+        // 512, 20 %, 20.3 -> 14.5 us; 2 x 2048, 10 %, 35.0 -> 26.4, 4 x 2048 39.1 -> 34.3; block 64: 1 x 4096 57.3 -> 42.5, 8 x 1024, 20 %, 38.6 -> 36.4;
+        // beyond, 3 x 4096, block 64 (918 workgroups of 32) 72.1 -> 76.9, 16 x 1024, block 32 (1120) 34.3 -> 38.4.
+        if constexpr (BS > 16)
+            if ((long long)s.BH * (ws.w_max + s.nb) * (BS / 32) * 4 <= 5 * 512) launch = launch_bwd<T, BS, Split<T, BS, 1, 4, 1>>;
         if (many_short_rows(s, nnzb))
             launch = single_block_rows(s, nnzb) ? launch_bwd<T, BS, typename SplitMany<T, BS>::bwd_single>
                                                                : launch_bwd<T, BS, typename SplitMany<T, BS>::bwd>;
