@@ -781,7 +781,12 @@ BwdWorkspace::BwdWorkspace(int BH, int bs, int nb, int nnzb_, int key_chunk, int
     if (w_first > w_max) w_first = w_max;
     n_slots = 2 * (nnzb / chunk) + 2;
     // for the shortest chunks, so that a workspace for more kept blocks also serves fewer; multiples of 256
-    const size_t slots = (size_t)BH * (2 * (nnzb / kChunk) + 2);
+    int most = 2 * (nnzb / kChunk) + 2;
+    if (bs == 64) {   // chunks shorter than kChunk are at least twice the mean: no more than nb / 2 of them in nnzb blocks
+        const int least = 2 * (nnzb / kChunkLeast) + 2 < nb + 2 ? 2 * (nnzb / kChunkLeast) + 2 : nb + 2;
+        if (least > most) most = least;
+    }
+    const size_t slots = (size_t)BH * most;
     counter_bytes = (slots * (bs / 16) * 8 + 255) / 256 * 256;
     row_counters = counter_bytes + slots * 2 * bs * kD * sizeof(float);
     // (with more heads the rule never cuts a row, however few blocks are kept)

@@ -21,7 +21,8 @@ namespace spion {
 // order, then the unsplit columns of more than kMidColumn rows, then the others.  Chunk number w writes its fp32
 // partial tiles to slot w; the last of a column's chunks to do so adds them up in chunk order (deterministic).
 // ------------------------------------------------------------------------------------------------
-constexpr int kChunk = 16;      // the shortest chunk that is cut: partial tiles are sized for it
+constexpr int kChunk = 16;      // the shortest chunk that is cut; of the tuned kernel of block 64:
+constexpr int kChunkLeast = 8;  // (partial tiles are sized for both)
 constexpr int kChunkMax = 64;   // the longest
 constexpr int kMidColumn = 8;   // an unsplit column of more kept rows starts before the block rows
 
@@ -39,9 +40,14 @@ inline long long bwd_steps_per_slot(int BH, int bs, int nb, int nnzb) {
 // 16 heads x 4096, block 64, 328 blocks (16 steps a slot) 37 / 38 / 44 / 68; 32 heads, 410 blocks (39) 79 / 76 /
 // 76 / 70, 852 blocks (76) 149 / 146 / 138 / 129 (121 with long rows first); 16 heads x 8192, block 32, 3277
 // blocks (73) 143 / 136 / 130 / 98 (last with long rows first).
+// Block 64 with less to do than that: down to 8, and twice the mean (columns of about the mean stay whole), so that the longest
+// chain is shorter: 2 heads x 1024, 25 %, 17.2 -> 13.7, 8 x 1024 18.1 -> 14.7, 8 x 2048, 15 %, 23.4 -> 18.1, 1 x 8192, 5 %, 26.0 -> 23.8; 8 rows
+// at a mean of 9.6, 2 x 4096, 15 %, 27.5 -> 30.0; block 32, whose steps are half as long, 8 x 4096, 5 %, 22.6 -> 25.0.
 inline int key_chunk(int BH, int bs, int nb, int nnzb) {
     const long long c = bwd_steps_per_slot(BH, bs, nb, nnzb);
-    return (int)(c < kChunk ? kChunk : c > kChunkMax ? kChunkMax : c);
+    const int twice = 2 * ((nnzb + nb - 1) / nb);
+    const int least = bs != 64 || twice > kChunk ? kChunk : twice > kChunkLeast ? twice : kChunkLeast;
+    return (int)(c < least ? least : c > kChunkMax ? kChunkMax : c);
 }
 
 struct KeyItem {

@@ -277,10 +277,11 @@ def test_pattern_on_another_stream_right_after_the_call(sp):
             assert np.array_equal(t.cpu().numpy(), ref[name]), name
 
 
-# The backward's work items with chunks of 16, of 27 and of 64 rows (by the steps each resident workgroup has to do),
+# The backward's work items with chunks of 8, 10, 14, 16, 27 and 64 rows (by the steps each resident workgroup has to do),
 # columns of as many rows as fit a chunk, one more, and of 0, 8 and 9 rows; long rows first and not
 @pytest.mark.parametrize("BH,nb,density,block", [(2, 70, 0.1, 32), (16, 70, 0.12, 64), (64, 70, 0.15, 32),
-                                                 (72, 130, 0.03, 32), (96, 9, 0.4, 32)])
+                                                 (72, 130, 0.03, 32), (96, 9, 0.4, 32), (2, 100, 0.01, 64), (1, 66, 0.02, 64),
+                                                 (3, 140, 0.0, 64)])
 def test_backward_chunks_follow_the_work(sp, BH, nb, density, block):
     rng = np.random.default_rng(nb + BH)
     Q, K, V, dO = [si.round_to_dtype(rng.standard_normal((BH, nb * block, 64), dtype=np.float32), "bf16") for _ in range(4)]
