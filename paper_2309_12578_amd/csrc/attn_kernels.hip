@@ -835,13 +835,14 @@ static bool fwd_many(const AttnShape& s, int rows) { return 2ll * s.BH * s.L / r
 // Rows in pieces, from twice the mean on as long as about all workgroups run at once (else the long ones start first, and
 // have to outlast the launch from there to be cut).  Forward kernel, fp32, block 32: 2 heads x 8192, 3 %, 51 -> 23.4 us; 4 x 4096, 5 %, 28 -> 18.9; 8 x 2048, 10 %,
 // 20.3 -> 17.7, 20 %, 28.6 -> 26; block 64, 3 x 4096, 10 %, 31.4 -> 26.8; block 16, 2 x 2048, 15.7 -> 12; bf16, block 16, 9 x 1936, 8 %, 12.8 -> 12.3.
-// Cut where the rule leaves them whole, 16 x 2048: block 32 28.9 -> 30, block 16 22.7 -> 23.5, bf16 15.3 -> 16.1; 4 x 1024, block 16, 8.5 -> 9.4.
+// Cut where the rule leaves them whole, 16 x 2048: block 32 28.9 -> 30, block 16 22.7 -> 23.5, bf16 15.3 -> 16.1; 4 x 1024, block 16, 8.5 -> 9.4,
+// bf16, 10 x 1584 10.3 -> 11.1.
 RowCut generic_fwd_cut(const AttnShape& s, int nnzb) {
     RowCut cut;
     const int rows = fwd_rows(s, nnzb);
     if (rows == 0) return cut;
     const bool many = fwd_many(s, rows);
-    if (many ? s.BH > 8 : s.bs == 16 && s.nb <= 64) return cut;   // rather no helpers that find nothing to do
+    if (many ? s.BH > 8 : s.bs == 16 && s.nb <= (s.is_bf16 ? 110 : 64)) return cut;   // rather no helpers that find nothing to do
     const int parts = s.bs / rows;
     cut.decide(s, nnzb, (many ? 2 : 1) * (long long)s.BH * nnzb * parts / fwd_resident(rows), !many);
     const long long most = 512 / ((long long)s.BH * parts);   // a helper for each piece, and not many that find nothing to do
@@ -905,14 +906,14 @@ static hipError_t launch_bwd(const AttnShape& s, const void* Q, const void* K, c
     const bool rows = (s.bwd_phases & 1) != 0, keys = (s.bwd_phases & 2) != 0;
     const int n_key_a = keys ? ws.w_first : 0, n_rows = rows ? s.nb : 0, n_key_c = keys ? ws.w_max - ws.w_first : 0;
     const long long per_item = (long long)s.BH * S::PARTS;
-    // Rows of more than twice the mean first, where more workgroups than fit at once follow (two or three waves a SIMD):
+    // Rows of more than twice the mean first, where a quarter more workgroups than run at once (two or three waves a SIMD) follow:
     // one that starts late runs on alone.  fp32: 2 heads x 8192, block 32, 3 %, 161 -> 148 us; 3 x 4096, block 64, 10 %, 86 -> 76; 8 x 2048,
     // block 32, 15 %, 78 -> 71, 10 % 52.7 both; bf16, block 16: 10 x 4096, 4 %, 71 -> 67, 9 x 1936, 8 %, 31.3 -> 30.0; rows of fewer
     // than 6 tiles on average gain nothing and pay the search, up to 1 us (bf16, block 16, searched and not: 24 x 1168, 4 %, 19.5,
-    // 18.8; 16 x 2048, 3 %, 25.1, 24.3, 5 %, 33.7, 34.1; fp32, block 32: 24 x 2336, 4 %, 81.2, 79.8; 16 x 1024, 10 %, 49.4, 50.9).
+    // 18.8; 16 x 2048, 3 %, 25.1, 24.3, 5 %, 33.7, 34.1; 16 block rows, fp32, 16 x 512, 28.7, 27.5; fp32, block 32: 24 x 2336, 4 %, 81.2, 79.8; 16 x 1024, 10 %, 49.4, 50.9).
     const long long resident = 256 * 4 * (sizeof(T) == 4 ? 2 : 3) / S::W;
     const int sort_rows = rows && (long long)ws.nnzb * (BS / 16) >= 6ll * s.nb &&
-                          per_item * (n_key_a + n_rows + n_key_c) > resident;
+                          s.nb >= 32 && 4 * per_item * (n_key_a + n_rows + n_key_c) > 5 * resident;
     // and a row a head for every 32 of them before the key side's items too: there the long ones are.  2 heads x 8192: 136 -> 125;
     // 4 x 4096, 5 %, 70.6 -> 62.2.
     const long long row_items = group_grid((long long)s.BH * n_rows), some = group_grid((long long)s.BH * ((s.nb + 31) / 32));
@@ -968,9 +969,10 @@ static hipError_t bwd_t(const AttnShape& s, const void* Q, const void* K, const 
         // 16 rows or keys a workgroup instead of 32 while those of 32 would be at most a quarter more than run at once (512 of
         // four waves): the compute units they leave idle are worth more than the tiles' second reading.  fp32, backward kernel, block 32: 2 heads x
         // 512, 20 %, 20.3 -> 14.5 us; 2 x 2048, 10 %, 35.0 -> 26.4, 4 x 2048 39.1 -> 34.3; block 64: 1 x 4096 57.3 -> 42.5, 8 x 1024, 20 %, 38.6 -> 36.4;
-        // beyond, 3 x 4096, block 64 (918 workgroups of 32) 72.1 -> 76.9, 16 x 1024, block 32 (1120) 34.3 -> 38.4.
+        // beyond, 3 x 4096, block 64 (918 workgroups of 32) 72.1 -> 76.9, 16 x 1024, block 32 (1120) 34.3 -> 38.4; with few block rows
+        // there is no long chain to shorten: 18 x 384, block 64, 20.4 -> 21.7, 8 x 512 15.4 -> 17.2.
         if constexpr (BS > 16)
-            if ((long long)s.BH * (ws.w_max + s.nb) * (BS / 32) * 4 <= 5 * 512) launch = launch_bwd<T, BS, Split<T, BS, 1, 4, 1>>;
+            if (s.nb >= 16 && (long long)s.BH * (ws.w_max + s.nb) * (BS / 32) * 4 <= 5 * 512) launch = launch_bwd<T, BS, Split<T, BS, 1, 4, 1>>;
         if (many_short_rows(s, nnzb))
             launch = single_block_rows(s, nnzb) ? launch_bwd<T, BS, typename SplitMany<T, BS>::bwd_single>
                                                                : launch_bwd<T, BS, typename SplitMany<T, BS>::bwd>;
