@@ -839,6 +839,7 @@ static bool fwd_many(const AttnShape& s, int rows) { return 2ll * s.BH * s.L / r
 // bf16, 10 x 1584 10.3 -> 11.1.
 RowCut generic_fwd_cut(const AttnShape& s, int nnzb) {
     RowCut cut;
+    if (s.nb <= 32) return cut;   // decide() cuts none
     const int rows = fwd_rows(s, nnzb);
     if (rows == 0) return cut;
     const bool many = fwd_many(s, rows);
