@@ -106,7 +106,7 @@ __device__ __forceinline__ void attend(
     // the second block goes out as soon as its index is known; it is the youngest load from here on
     if (n > 0) issue(sm1, col_at(1));   // (a one-block row loads its block twice: keeps the wait below uniform)
 
-    float m = -INFINITY;   // what the row's exponentials are taken against, log2 units (score * scale * log2 e)
+    float m = kLowest;   // what the row's exponentials are taken against, log2 units (score * scale * log2 e)
     float limit = -INFINITY;   // m + kRescaleSlack
     f32x4 lacc = f32x4{0.f, 0.f, 0.f, 0.f};   // running row sum, replicated in its 4 elements
     f32x4 oacc[4];

@@ -17,6 +17,10 @@ constexpr int kD = 64;  // head dimension
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
+// What a row's exponentials are taken against before any score has been seen: finite, so that scores of -infinity alone (a
+// masked block, or a whole piece of a row) add 0 and not exp2(inf - inf).
+constexpr float kLowest = -3.4028234663852886e38f;
+
 // How far (in log2 units) a score may lie above the value its row's exponentials are taken against before the
 // running sums are rescaled.  P = exp2(s - m) above 1 is as exact as below (it keeps its relative
 // error, the fp32 sums have range to spare), so what a row's maximum does inside this slack need not be

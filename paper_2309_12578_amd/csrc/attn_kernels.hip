@@ -233,7 +233,8 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_fwd_kernel(
     f32x4 oacc[NQ][4];
 #pragma unroll
     for (int h = 0; h < NQ; ++h) {
-        m[h] = limit[h] = -INFINITY;
+        m[h] = kLowest;
+        limit[h] = -INFINITY;
         lsum[h] = 0.f;
     }
     clear_acc<NQ>(oacc);

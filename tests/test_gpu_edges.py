@@ -179,6 +179,28 @@ def test_long_rows_in_pieces_of_the_generic_kernels(sp, dtype, block, BH, nb, lo
     _attention(sp, Q, K, V, dO, fl, block, dtype, [0, BH - 1], flags=sp.SPION_ATTN_PAPER_DENOM if denom else 0)
 
 
+@pytest.mark.parametrize("dtype,block", [("bf16", 32), ("bf16", 64), ("bf16", 16), ("f32", 32)])
+def test_pieces_whose_scores_are_all_minus_infinity(sp, dtype, block):
+    """Keys that give scores of -infinity count nothing, also where they are all that a piece of a long row has."""
+    from test_gpu_parity import _pattern_from_mask
+    nb = 130
+    long, without = np.eye(nb, dtype=np.uint8), np.eye(nb, dtype=np.uint8)
+    long[[3, 100]] = without[[3, 100]] = 1
+    without[:, 10:90] = 0
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    q, k, v = [torch.randn((1, 3, nb * block, 64), generator=gen, device="cuda").to(tdt) for _ in range(3)]
+    q = q.abs() + 0.125
+    k[:, :, 10 * block:90 * block] = -float("inf")
+    got, got_lse = sp.attn_fwd(q, k, v, _pattern_from_mask(sp, long, block))
+    want, want_lse = sp.attn_fwd(q, k, v, _pattern_from_mask(sp, without, block))
+    for row in (3, 100):
+        at = slice(row * block, (row + 1) * block)
+        # the same sums in another order: fp32 rounding of 50 blocks' scores, and one of the output
+        assert torch.allclose(got[:, :, at].float(), want[:, :, at].float(), rtol=0.0, atol=2e-2 if dtype == "bf16" else 2e-5)
+        assert torch.allclose(got_lse[:, :, at], want_lse[:, :, at], rtol=0.0, atol=1e-2 if dtype == "bf16" else 1e-5)
+
+
 def test_long_rows_in_pieces_again_and_in_a_graph(sp):
     """Whichever piece is the last to arrive: the same bits every time, and in replays, which share their launches' tags, on other
     inputs and with other work in between."""
