@@ -482,10 +482,11 @@ struct HeadsAttentionBackward : public torch::autograd::Node {
     }
 };
 
-// heads_attention(qkv [B, L, 3 H 64], H, row_ptr, col_idx, col_ptr, row_idx, bsr_pos, nnzb, block, flags) -> [B, L, H 64]:
-// every head's attention as one node; None where the steps are to be taken one by one (see projection).
+// heads_attention(qkv [B, L, 3 H 64], H, row_ptr, col_idx, col_ptr, row_idx, bsr_pos, nnzb, block, flags, apart = False)
+// -> [B, L, H 64]: every head's attention as one node; None where the steps are to be taken one by one (see projection).
+// apart: the node saves copies, so that the caller may let qkv and the result be changed in place before the backward pass.
 PyObject* py_heads_attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
-    if (!arg_count(n, 10, "heads_attention")) return nullptr;
+    if (n != 11 && !arg_count(n, 10, "heads_attention")) return nullptr;
     return guarded([&]() -> PyObject* {
         if (!nothing_between() || !plain(a[0])) Py_RETURN_NONE;
         const at::Tensor& qkv = THPVariable_Unpack(a[0]);
@@ -503,7 +504,7 @@ PyObject* py_heads_attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
         ix.block = int_arg(a[8]);
         ix.flags = (unsigned)int_arg(a[9]);
         const bool grad = torch::autograd::compute_requires_grad(qkv);
-        const bool in_place = heads_in_place(qkv, ix);
+        const bool in_place = heads_in_place(qkv, ix) && !(grad && n == 11 && a[10] == Py_True);
         at::Tensor t[3], o, lse, s;
         if (in_place) {
             const spion_attn_params p = heads_params(qkv, H, ix);

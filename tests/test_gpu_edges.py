@@ -485,6 +485,47 @@ def test_heads_where_the_projections_have_them(sp, B, H, nb, block, denom):
     assert torch.equal(got.view(B, L, 3, H, 64), want)
 
 
+# bf16 blocks of 32 and 64 have the attention work on qkv and S themselves, other types on copies
+@pytest.mark.parametrize("dtype,block", [(torch.bfloat16, 32), (torch.bfloat16, 64), (torch.bfloat16, 16), (torch.float32, 32)])
+def test_tensors_beside_the_attention_changed_in_place(sp, dtype, block):
+    """Hooks and a replaced forward that change S or qkv in place, seen by autograd or not, against the same out of place."""
+    from test_gpu_parity import _pattern_from_mask
+    B, H, nb = 2, 2, 6
+    pat = _pattern_from_mask(sp, np.tril(np.ones((nb, nb), dtype=np.uint8)), block)
+    torch.manual_seed(block)
+    mha = sp.SparseMHA(H * 64, H, device="cuda", dtype=dtype)
+    E = torch.randn((B, nb * block, H * 64), device="cuda", dtype=dtype, requires_grad=True)
+    dout = torch.randn_like(E)
+    linear = mha.w_o.forward
+
+    def grads(pre=None, forward=None, keep=None):
+        hooks, seen = [], []
+        if pre:
+            hooks.append(mha.w_o.register_forward_pre_hook(lambda m, a: pre(a[0])))
+        if forward:
+            mha.w_o.forward = forward
+        if keep:
+            hooks.append(mha.w_qkv.register_forward_hook(lambda m, a, out: seen.append(out)))
+        out = mha(E, pat)
+        for h in hooks:
+            h.remove()
+        if forward:
+            del mha.w_o.forward
+        for t in seen:
+            keep(t)
+        return torch.autograd.grad(out, [E, *mha.parameters()], dout)
+
+    def equal(a, b):
+        assert all(torch.equal(x, y) for x, y in zip(a, b))
+
+    # a factor of 1 / 2 rounds nothing
+    equal(grads(lambda S: (S.mul_(0.5), None)[1]), grads(lambda S: S * 0.5))
+    equal(grads(forward=lambda S: linear(S.mul_(0.5))), grads(lambda S: S * 0.5))
+    equal(grads(lambda S: (S.data.mul_(0.5), None)[1]), grads(lambda S: S + (S * 0.5 - S).detach()))
+    equal(grads(keep=lambda qkv: qkv.data.zero_()), grads(keep=lambda qkv: None))
+    equal(grads(keep=lambda qkv: qkv.detach().zero_()), grads(keep=lambda qkv: None))
+
+
 # Rows of 256, 512, 1024 and 2048 columns in registers and less; 4 rows a workgroup, 16 rows a partial of the weight's
 # and bias' gradients, 512 partials at most; a width that is not a multiple of 64 is torch's
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
