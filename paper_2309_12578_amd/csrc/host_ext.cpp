@@ -575,7 +575,7 @@ struct NormBackward : public torch::autograd::Node {
             std::tie(out[0], out[1], out[2]) = at::native_layer_norm_backward(
                 g, X, {D}, m.view(stat), r.view(stat), W, b.unpack(),
                 {task_should_compute_output(0), task_should_compute_output(1), task_should_compute_output(2)});
-            if (dr.defined()) out[0] = out[0] + dr;
+            if (dr.defined() && out[0].defined()) out[0] = out[0] + dr;   // X's gradient may not be asked for
             return out;
         }
         const bool add = dr.defined() && plain(dr) && dr.scalar_type() == X.scalar_type() && dr.is_contiguous() &&

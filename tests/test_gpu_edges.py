@@ -584,6 +584,34 @@ def test_residual_around_layer_norm(sp, dtype, rows, D):
         assert sp.binding._host.residual(x, norm(x)) is x
 
 
+@pytest.mark.parametrize("which", [(1,), (2,), (1, 2), (0,), (0, 2)])
+def test_some_gradients_of_a_residual_around_layer_norm(sp, which):
+    """Any of X, weight and bias asked for without the others, by kernels, by torch's operators and batched."""
+    from paper_2309_12578_amd.sublayer import _Norm
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    norm = _Norm(128, device="cuda")
+    x, dy, dr = [torch.randn((2, 8, 128), generator=gen, device="cuda") for _ in range(3)]
+    x.requires_grad_(True)
+    y = norm(x)
+    r = sp.binding._host.residual(x, y)
+    assert r.grad_fn is y.grad_fn
+    every = [x, norm.weight, norm.bias]
+    inputs = [every[i] for i in which]
+    in64 = [t.detach().double().requires_grad_(True) for t in every]
+    out64 = torch.nn.functional.layer_norm(in64[0], (128,), in64[1], in64[2], norm.eps)
+    want = torch.autograd.grad([out64, in64[0] * 1], in64, [dy.double(), dr.double()])
+
+    def same(got, factor=1.0):
+        for g, i in zip(got, which):
+            assert (g.double() - factor * want[i]).norm() <= 1e-5 * want[i].norm()   # as test_layer_norm
+
+    for graph in (False, True):
+        same(torch.autograd.grad([y, r], inputs, [dy, dr], create_graph=graph, retain_graph=True))
+    batched = torch.autograd.grad([y, r], inputs, [torch.stack([t, 2 * t]) for t in (dy, dr)], is_grads_batched=True)
+    same([g[0] for g in batched])
+    same([g[1] for g in batched], 2.0)
+
+
 def test_layer_norm_beside_the_other_transforms(sp):
     from paper_2309_12578_amd.sublayer import _Norm
     norm, plain = _Norm(128, device="cuda"), torch.nn.LayerNorm(128, device="cuda")
