@@ -8,6 +8,7 @@
 
 #include "attn_bf16_tiles.h"
 #include "attn_common.h"
+#include "../../include/spion.h"
 #include "spion_internal.h"
 
 namespace spion {
@@ -24,6 +25,8 @@ namespace spion {
 constexpr int kChunk = 16;      // the shortest chunk that is cut; of the tuned kernel of block 64:
 constexpr int kChunkLeast = 8;  // (partial tiles are sized for both)
 constexpr int kChunkMax = 64;   // the longest
+static_assert((SPION_MAX_NB + kChunkLeast - 1) / kChunkLeast < 1 << kArriveBits && RowCut::kSlots < 1 << kArriveBits,
+              "a counter holds the parts of any column or row");
 constexpr int kMidColumn = 8;   // an unsplit column of more kept rows starts before the block rows
 
 // Workgroups of the tuned backward that run at once: 164 VGPRs let three waves share a SIMD.

@@ -122,7 +122,7 @@ spion::AttnShape make_shape(const spion_attn_params* p) {
                    : (p->flags & SPION_ATTN_BWD_KEY_SIDE_ONLY) ? 2 : 3;
     s.heads_beside = 0;
     s.fwd_room = nullptr;
-    s.tag = g_tag.fetch_add(1, std::memory_order_relaxed) * 0x9e3779b97f4bull & ((1ull << (64 - spion::kArriveBits)) - 1ull);
+    s.tag = g_tag.fetch_add(1, std::memory_order_relaxed) * 0x9e3779b97f4a7bull & ((1ull << (64 - spion::kArriveBits)) - 1ull);
     return s;
 }
 

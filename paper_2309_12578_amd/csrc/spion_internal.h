@@ -32,7 +32,10 @@ hipError_t launch_frobenius_distance(const float* a, const float* b, size_t n, d
                                      hipStream_t st);
 
 // attn_kernels.hip
-constexpr int kArriveBits = 24;   // of a counter of arrivals; its other bits are a tag (a block column can have 2^20 chunks)
+// Of a counter of arrivals: as few as hold the parts of one row or column (attn_key_items.h), 128 at most, because its other
+// bits are the tag that tells it from what was in the memory before.  With 40 bits of tag instead of 56 a counter is
+// taken for begun, and its sums come from nobody, 2^16 times as often.
+constexpr int kArriveBits = 8;
 
 struct AttnShape {
     int BH, L, bs, nb;

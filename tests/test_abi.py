@@ -117,6 +117,26 @@ def test_argument_errors_are_reported_before_any_launch():
     assert lib.spion_attn_bwd(*b3) == -2
 
 
+def _constants(tmp_path, header, **values):
+    """Values of C++ expressions over a header of the kernels, compiled for the host."""
+    import subprocess
+    from paper_2309_12578_amd import build
+    src, exe = tmp_path / "constants.hip", tmp_path / "constants"
+    src.write_text('#include "%s"\n#include <cstdio>\nusing namespace spion;\nint main() { std::printf("%s\\n", %s); }\n' %
+                   (header, " ".join(["%lld"] * len(values)), ", ".join("(long long)(%s)" % v for v in values.values())))
+    subprocess.run([build.HIPCC, "--offload-host-only", "-std=c++17", "-I" + build.CSRC, str(src), "-o", str(exe)],
+                   check=True, capture_output=True, timeout=120)
+    out = subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=60).stdout
+    return dict(zip(values, map(int, out.split())))
+
+
+def test_counters_of_arrivals_leave_all_other_bits_to_the_tag(tmp_path):
+    """The memory of a counter is not cleared: only the tag tells a counter in use from what was there before."""
+    c = _constants(tmp_path, "attn_key_items.h", bits="kArriveBits", rows="SPION_MAX_NB", chunk="kChunkLeast", slots="RowCut::kSlots")
+    most = max(-(-c["rows"] // c["chunk"]), c["slots"])   # parts of a column, of a row
+    assert most.bit_length() == c["bits"]
+
+
 def test_binding_refuses_cpu_tensors():
     import torch
     x = torch.zeros(4)
