@@ -27,6 +27,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "grid_bins.h"
 #include "spion_internal.h"
 
 namespace spion {
@@ -820,9 +821,7 @@ __global__ __launch_bounds__(kFinishThreads) void pattern_finish_kernel(
 // threshold + fill + compaction, 64 < nb <= 1024 (several kernels)
 // ------------------------------------------------------------------------------------------------
 // Words of 64 columns: W = ceil(nb / 64) per row.  Scratch of the stages, all in the workspace:
-//   cells      grid_pool_kernel: pool_sum; for a quantile also a histogram over 4096 bins that grow with
-//              the value (128 to an octave: with 32, the median of a 512 x 512 map lay in a bin of some 100000 cells,
-//              from which one workgroup took 52 us to select)
+//   cells      grid_pool_kernel: pool_sum; for a quantile also a histogram over bins that grow with the value (grid_bins.h)
 //   candidates grid_bits_kernel: successor bits of every row; the cells of the bin that holds the wanted
 //              rank, in any order
 //   serial     grid_serial_kernel: workgroup 0 the threshold (order statistic of the candidates), workgroup
@@ -831,7 +830,6 @@ __global__ __launch_bounds__(kFinishThreads) void pattern_finish_kernel(
 //   index      grid_index_kernel: BSR and BSC
 // Measured at nb = 512: the five kernels take 7 + 5 + 19 + 5 + 4 us (one workgroup with a barrier per
 // anti-diagonal took 2454); the longest part is the serial one, its threshold and its fill about alike.
-constexpr int kGridBins = 4096;
 constexpr int kGridMax = 1024;   // same bound as SPION_MAX_NB of the public header
 
 struct GridScratch {
@@ -864,16 +862,6 @@ static GridScratch grid_carve(char* aux, void* part, size_t nb) {
     s.row_cnt = reinterpret_cast<uint4*>(s.cand + (nb * nb + 1) / 2 * 2);   // 32 nb bytes, of 48 nb^2 that are left
     s.col_cnt = s.row_cnt + nb;
     return s;
-}
-
-// Position of v among 4096 bins that are ordered like the values: 128 to an octave from 2^32 on (a block's sum of scores
-// of 2^-8 in all), one to an octave below and of negative values.
-constexpr int kFineFrom = 32;
-static_assert(64 + 1 + kFineFrom + (63 - kFineFrom) * 128 <= kGridBins, "bins of the positive octaves");
-__device__ __forceinline__ int grid_bin(long long v) {
-    if (v <= 0) return v == 0 ? 64 : __clzll((long long)(0ull - (unsigned long long)v));   // -2^63: 0
-    const int lz = __clzll(v), octave = 63 - lz;
-    return octave < kFineFrom ? 65 + octave : 65 + kFineFrom + (octave - kFineFrom) * 128 + (int)(((unsigned long long)v << lz) << 1 >> 57);
 }
 
 __global__ __launch_bounds__(256) void grid_zero_kernel(unsigned* __restrict__ zero) {
@@ -934,8 +922,8 @@ __global__ __launch_bounds__(kPoolThreads) void grid_pool_kernel(const long long
         if (h[i]) atomicAdd(&hist[i], h[i]);
 }
 
-// A wave takes a word (64 cells of a row).  Every workgroup finds the bin of the wanted rank itself, 4
-// bins per thread and two scans (16 bins a thread and four words a wave, in 256 threads: 6.5 us at nb = 512, 5.1 so),
+// A wave takes a word (64 cells of a row).  Every workgroup finds the bin of the wanted rank itself, 8
+// bins per thread and two scans (4096 bins: 16 a thread and four words a wave, in 256 threads, 6.5 us at nb = 512, 4 a thread 5.1),
 // and takes room for its candidates with one addition: with one per wave and
 // word, all on one counter, a map of 512 x 512 nearly equal cells (one bin) took 50 us,
 // now 8.8.
@@ -955,9 +943,12 @@ __global__ __launch_bounds__(kBitsThreads) void grid_bits_kernel(const long long
                     dg = inner && !no_fill ? pool[i + nb + 1] : 0;
     int bin = -1;
     if (mode == 1) {
-        static_assert(kGridBins == 4 * kBitsThreads, "four bins a thread");
-        const uint4 q = reinterpret_cast<const uint4*>(s.hist)[tid];
-        const int cnt = (int)(q.x + q.y + q.z + q.w);
+        static_assert(kGridBins == 8 * kBitsThreads, "eight bins a thread");
+        const uint4 q0 = reinterpret_cast<const uint4*>(s.hist)[2 * tid], q1 = reinterpret_cast<const uint4*>(s.hist)[2 * tid + 1];
+        const unsigned q[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
+        int cnt = 0;
+#pragma unroll
+        for (int b = 0; b < 8; ++b) cnt += (int)q[b];
         const int scan = wave_inclusive_scan_dpp(cnt);
         if (lane == 63) wave_sum[wave] = scan;
         __syncthreads();
@@ -966,12 +957,13 @@ __global__ __launch_bounds__(kBitsThreads) void grid_bits_kernel(const long long
         int e0 = incl - cnt;
         if (k_rank >= e0 && k_rank < incl) {   // exactly one thread
             int b = 0;
-            for (const unsigned n : {q.x, q.y, q.z}) {
-                if (k_rank < e0 + (int)n) break;
-                e0 += (int)n;
+#pragma unroll
+            for (int i = 0; i < 7; ++i) {
+                if (k_rank < e0 + (int)q[i]) break;
+                e0 += (int)q[i];
                 ++b;
             }
-            sel_bin = tid * 4 + b;
+            sel_bin = tid * 8 + b;
             if (blockIdx.x == 0) s.hist[kGridBins + 1] = (unsigned)(k_rank - e0);   // rank among the candidates
         }
         __syncthreads();

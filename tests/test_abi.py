@@ -137,6 +137,19 @@ def test_counters_of_arrivals_leave_all_other_bits_to_the_tag(tmp_path):
     assert most.bit_length() == c["bits"]
 
 
+def test_bins_of_large_grids_are_fine_for_every_scale_and_sign(tmp_path):
+    """Ordered like the values, and no two values 1 / 32 apart in one: a rank's bin holds few cells of any map."""
+    values = sorted({0, -2 ** 63} | {s * (2 ** e + k * 2 ** e // 32 + d) for s in (-1, 1) for e in range(63) for k in (0, 1, 17, 31)
+                                    for d in (0, 1 if e > 5 else 0)})
+    at = {"v%d" % i: "grid_bin(%s)" % ("%dll" % v if v > -2 ** 63 else "-0x7fffffffffffffffll - 1") for i, v in enumerate(values)}
+    c = _constants(tmp_path, "grid_bins.h", bins="kGridBins", **at)
+    bins = [c["v%d" % i] for i in range(len(values))]
+    assert 0 <= bins[0] and bins[-1] < c["bins"] and bins == sorted(bins)
+    first = {}   # bin -> its lowest value
+    for v, b in zip(values, bins):
+        assert v == first.setdefault(b, v) or abs(v - first[b]) * 32 < abs(v), (first[b], v)
+
+
 def test_binding_refuses_cpu_tensors():
     import torch
     x = torch.zeros(4)
