@@ -449,11 +449,12 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
 // 4 x 16384, block 64, 112 / 70.5 / 70.3; 4 x 8192, block 64, rows of 71, 65.3 / 39.5 / 40.2; 1 x 4096, block 32, 21.1 / 17.8 / 17.9.
 static RowCut row_cut(const AttnShape& s, const BwdWorkspace& ws, void* workspace) {
     RowCut cut;
+    if (!s.bwd_room) return cut;
     cut.decide(s, ws.nnzb, bwd_steps_per_slot(s.BH, s.bs, s.nb, ws.nnzb));
     if (cut.slots == 0) return cut;
     cut.helpers = cut.slots - 1;
     if ((long long)s.BH * (cut.helpers + s.nb + ws.w_max) > 0x7fffffffll) return RowCut{};   // workgroups of a launch
-    cut.counters = reinterpret_cast<unsigned long long*>(static_cast<char*>(workspace) + ws.row_counters);
+    cut.counters = reinterpret_cast<unsigned long long*>(static_cast<char*>(workspace) + ws.total);
     cut.parts = reinterpret_cast<float*>(static_cast<char*>(workspace) + ws.row_parts);
     return cut;
 }

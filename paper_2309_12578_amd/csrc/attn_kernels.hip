@@ -774,8 +774,9 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_bwd_kernel(
 // ------------------------------------------------------------------------------------------------
 // host launchers
 // ------------------------------------------------------------------------------------------------
-BwdWorkspace::BwdWorkspace(int BH, int bs, int nb, int nnzb_, int key_chunk, int mid_first) {
+BwdWorkspace::BwdWorkspace(int BH, int bs, int nb, int nnzb_, int key_chunk, int mid_first, int row_slots_) {
     nnzb = nnzb_;
+    row_slots = row_slots_;
     chunk = key_chunk;
     w_max = nnzb / chunk + nb;
     w_first = nnzb / chunk + 1 + mid_first;
@@ -789,17 +790,37 @@ BwdWorkspace::BwdWorkspace(int BH, int bs, int nb, int nnzb_, int key_chunk, int
     }
     const size_t slots = (size_t)BH * most;
     counter_bytes = (slots * (bs / 16) * 8 + 255) / 256 * 256;
-    row_counters = counter_bytes + slots * 2 * bs * kD * sizeof(float);
-    // (with more heads the rule never cuts a row, however few blocks are kept)
-    row_slots = nb > 64 && 4 * BH < bwd_resident(bs) ? (size_t)BH * RowCut::kSlots : 0;
-    row_parts = row_counters + row_slots * (bs / 16) * 8;
-    total = row_parts + row_slots * bs * kD * sizeof(float);
+    total = counter_bytes + slots * 2 * bs * kD * sizeof(float);
+    row_parts = total + ((size_t)BH * row_slots * (bs / 16) * 8 + 255) / 256 * 256;
+    with_rows = row_parts + (size_t)BH * row_slots * bs * kD * sizeof(float);
 }
 
-size_t attn_bwd_workspace_bytes(int BH, int bs, int nb, int nnzb) { return BwdWorkspace(BH, bs, nb, nnzb, kChunk, 0).total; }
+// Workgroups of the generic backward that run at once: two (fp32) or three waves a SIMD.
+static long long generic_bwd_resident(bool is_bf16, int waves) { return 256 * 4 * (is_bf16 ? 3 : 2) / waves; }
+
+// Which of its query side's rows are cut, with the steps of both sides and as many helpers as the forward.
+static void generic_bwd_decide(RowCut& cut, const AttnShape& s, int nnzb, int parts, long long resident) {
+    cut.decide(s, nnzb, 2ll * s.BH * ((long long)nnzb + s.nb) * parts / resident);
+    const long long most = 512 / ((long long)s.BH * parts);
+    if (cut.slots > most) cut.slots = (int)most;
+    if (cut.slots < 2) cut.slots = 0;
+}
+
+// Pieces of long rows per head, at most: with 16 rows a workgroup instead of 32 there are more of them and no more pieces.
+static int bwd_row_slots(const AttnShape& s, int nnzb) {
+    RowCut cut;
+    if (s.is_bf16 && s.bs > 16) {
+        cut.decide(s, nnzb, bwd_steps_per_slot(s.BH, s.bs, s.nb, nnzb));
+        return cut.slots;
+    }
+    generic_bwd_decide(cut, s, nnzb, s.bs == 64 ? 2 : 1, generic_bwd_resident(s.is_bf16, 4));
+    return cut.slots;
+}
+
+BwdWorkspace attn_bwd_workspace(const AttnShape& s, int nnzb) { return BwdWorkspace(s.BH, s.bs, s.nb, nnzb, kChunk, 0, bwd_row_slots(s, nnzb)); }
 
 bool attn_bwd_grids_fit(int BH, int bs, int nb, int nnzb) {
-    const BwdWorkspace ws(BH, bs, nb, nnzb, kChunk, 0);
+    const BwdWorkspace ws(BH, bs, nb, nnzb, kChunk, 0, 0);
     const int64_t limit = 0x7fffffffll, parts = bs == 64 ? 2 : 1;
     return (int64_t)(ws.w_max + nb) * BH * parts + 24 <= limit &&
            (int64_t)(nb > kChunk ? nnzb / (kChunk + 1) : 0) * BH * (bs / 16) <= limit;   // rows of cut columns
@@ -886,14 +907,13 @@ static hipError_t launch_fwd(const AttnShape& s, const void* Q, const void* K, c
 // 80 blocks, 125 -> 61.8 us; 4 x 4096, 5 %, 61.6 -> 52.8; block 16, 2 x 2048, 8 %, 26.4 -> 21.3; patterns that are left whole, the same.
 static RowCut generic_bwd_cut(const AttnShape& s, const BwdWorkspace& ws, int parts, long long resident, void* workspace) {
     RowCut cut;
-    if (ws.row_slots == 0) return cut;
-    cut.decide(s, ws.nnzb, 2ll * s.BH * ((long long)ws.nnzb + s.nb) * parts / resident);
-    const long long most = 512 / ((long long)s.BH * parts);   // as the forward
-    if (cut.slots > most) cut.slots = (int)most;
-    if (cut.slots < 2) return RowCut{};
+    if (!s.bwd_room) return cut;
+    generic_bwd_decide(cut, s, ws.nnzb, parts, resident);
+    if (cut.slots > ws.row_slots) cut.slots = ws.row_slots;   // (it is not)
+    if (cut.slots == 0) return cut;
     cut.helpers = cut.slots - 1;
     cut.groups = parts * ((s.BH * cut.helpers + 7) & ~7);
-    cut.counters = reinterpret_cast<unsigned long long*>(static_cast<char*>(workspace) + ws.row_counters);
+    cut.counters = reinterpret_cast<unsigned long long*>(static_cast<char*>(workspace) + ws.total);
     cut.parts = reinterpret_cast<float*>(static_cast<char*>(workspace) + ws.row_parts);
     return cut;
 }
@@ -913,7 +933,7 @@ static hipError_t launch_bwd(const AttnShape& s, const void* Q, const void* K, c
     // block 32, 15 %, 78 -> 71, 10 % 52.7 both; bf16, block 16: 10 x 4096, 4 %, 71 -> 67, 9 x 1936, 8 %, 31.3 -> 30.0; rows of fewer
     // than 6 tiles on average gain nothing and pay the search, up to 1 us (bf16, block 16, searched and not: 24 x 1168, 4 %, 19.5,
     // 18.8; 16 x 2048, 3 %, 25.1, 24.3, 5 %, 33.7, 34.1; 16 block rows, fp32, 16 x 512, 28.7, 27.5; fp32, block 32: 24 x 2336, 4 %, 81.2, 79.8; 16 x 1024, 10 %, 49.4, 50.9).
-    const long long resident = 256 * 4 * (sizeof(T) == 4 ? 2 : 3) / S::W;
+    const long long resident = generic_bwd_resident(sizeof(T) == 2, S::W);
     const int sort_rows = rows && (long long)ws.nnzb * (BS / 16) >= 6ll * s.nb &&
                           s.nb >= 32 && 4 * per_item * (n_key_a + n_rows + n_key_c) > 5 * resident;
     // and a row a head for every 32 of them before the key side's items too: there the long ones are.  2 heads x 8192: 136 -> 125;
@@ -963,10 +983,10 @@ static hipError_t bwd_t(const AttnShape& s, const void* Q, const void* K, const 
                         const int* row_ptr, const int* col_idx, const int* col_ptr, const int* row_idx,
                         int nnzb, void* workspace, hipStream_t st) {
     if constexpr (sizeof(T) == 2 && BS >= 32) {
-        const BwdWorkspace ws(s.BH, s.bs, s.nb, nnzb, key_chunk(s.BH, BS, s.nb, nnzb), s.nb / 4);
+        const BwdWorkspace ws(s.BH, s.bs, s.nb, nnzb, key_chunk(s.BH, BS, s.nb, nnzb), s.nb / 4, bwd_row_slots(s, nnzb));
         return bwd_bf16<BS>(s, Q, K, V, O, dO, LSE, dQ, dK, dV, row_ptr, col_idx, col_ptr, row_idx, ws, workspace, st);
     } else {
-        const BwdWorkspace ws(s.BH, s.bs, s.nb, nnzb, kChunk, s.nb / 8);
+        const BwdWorkspace ws(s.BH, s.bs, s.nb, nnzb, kChunk, s.nb / 8, bwd_row_slots(s, nnzb));
         auto* launch = launch_bwd<T, BS, SplitFew<T, BS>>;
         // 16 rows or keys a workgroup instead of 32 while those of 32 would be at most a quarter more than run at once (512 of
         // four waves): the compute units they leave idle are worth more than the tiles' second reading.  fp32, backward kernel, block 32: 2 heads x

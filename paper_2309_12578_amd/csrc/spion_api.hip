@@ -122,6 +122,7 @@ spion::AttnShape make_shape(const spion_attn_params* p) {
                    : (p->flags & SPION_ATTN_BWD_KEY_SIDE_ONLY) ? 2 : 3;
     s.heads_beside = 0;
     s.fwd_room = nullptr;
+    s.bwd_room = false;
     s.tag = g_tag.fetch_add(1, std::memory_order_relaxed) * 0x9e3779b97f4a7bull & ((1ull << (64 - spion::kArriveBits)) - 1ull);
     return s;
 }
@@ -132,6 +133,13 @@ int give_room(spion::AttnShape& s, int32_t nnzb, void* room, size_t room_bytes) 
     if (need == 0) return SPION_OK;
     if ((uintptr_t)room % kAlign != 0 || room_bytes < need) return SPION_ERR_WORKSPACE;
     s.fwd_room = room;
+    return SPION_OK;
+}
+
+int give_workspace(spion::AttnShape& s, int32_t nnzb, void* workspace, size_t workspace_bytes) {
+    const spion::BwdWorkspace need = spion::attn_bwd_workspace(s, nnzb);
+    if (!workspace || (uintptr_t)workspace % kAlign != 0 || workspace_bytes < need.total) return SPION_ERR_WORKSPACE;
+    s.bwd_room = workspace_bytes >= need.with_rows;
     return SPION_OK;
 }
 
@@ -408,7 +416,7 @@ int spion_copy_yardstick(const void* src, void* dst, size_t n_bytes, void* hip_s
 size_t spion_attn_workspace_bytes(const spion_attn_params* p, int32_t nnzb, int32_t is_bwd) {
     if (!p || attn_params_ok(p, nnzb) != SPION_OK) return (size_t)-1;
     if (!is_bwd) return 0;
-    return spion::attn_bwd_workspace_bytes(p->B * p->H, p->block, p->L / p->block, nnzb);
+    return spion::attn_bwd_workspace(make_shape(p), nnzb).with_rows;
 }
 
 int spion_index_check(const int32_t* row_ptr, const int32_t* col_idx, const int32_t* col_ptr,
@@ -465,10 +473,9 @@ int spion_attn_bwd(const void* Q, const void* K, const void* V, const void* O, c
     const int rc = attn_params_ok(p, nnzb);
     if (rc != SPION_OK) return rc;
     if (!spion::attn_bwd_grids_fit(p->B * p->H, p->block, p->L / p->block, nnzb)) return SPION_ERR_SHAPE;
-    const size_t need = spion_attn_workspace_bytes(p, nnzb, 1);
-    if (!workspace || ((uintptr_t)workspace % kAlign) != 0 || workspace_bytes < need)
-        return SPION_ERR_WORKSPACE;
-    const spion::AttnShape s = make_shape(p);
+    spion::AttnShape s = make_shape(p);
+    const int room_rc = give_workspace(s, nnzb, workspace, workspace_bytes);
+    if (room_rc != SPION_OK) return room_rc;
     if (spion::launch_attn_bwd(s, Q, K, V, O, dO, LSE, dQ, dK, dV, row_ptr, col_idx, col_ptr, row_idx,
                                nnzb, workspace, static_cast<hipStream_t>(hip_stream)) != hipSuccess)
         return SPION_ERR_HIP;
@@ -497,9 +504,9 @@ int spion_heads_attn_bwd(const void* qkv, const void* S, const void* dS, const f
     const int rc = heads_beside_ok((uintptr_t)qkv | (uintptr_t)S | (uintptr_t)dS | (uintptr_t)dqkv, p, nnzb);
     if (rc != SPION_OK) return rc;
     if (!spion::attn_bwd_grids_fit(p->B * p->H, p->block, p->L / p->block, nnzb)) return SPION_ERR_SHAPE;
-    if (!workspace || ((uintptr_t)workspace % kAlign) != 0 || workspace_bytes < spion_attn_workspace_bytes(p, nnzb, 1))
-        return SPION_ERR_WORKSPACE;
     spion::AttnShape s = make_shape(p);
+    const int room_rc = give_workspace(s, nnzb, workspace, workspace_bytes);
+    if (room_rc != SPION_OK) return room_rc;
     s.heads_beside = p->H;
     const uint16_t* const q = static_cast<const uint16_t*>(qkv);
     uint16_t* const d = static_cast<uint16_t*>(dqkv);

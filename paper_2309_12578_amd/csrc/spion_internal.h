@@ -45,6 +45,7 @@ struct AttnShape {
     int bwd_phases;     // bit 0: query side (dQ); bit 1: key side (dK, dV)
     int heads_beside;   // 0: tensors [B, H, L, 64]; else H, and rows as HeadRows<true> (bf16, block 32 and 64 only)
     void* fwd_room;     // forward: device memory of RowCut::room_bytes() for the pieces of long rows, or nullptr: rows stay whole
+    bool bwd_room;      // backward: the workspace has the room of BwdWorkspace::with_rows; else long rows stay whole
     unsigned long long tag;       // of this call alone, below 2^(64 - kArriveBits) (see last_to_arrive)
 };
 
@@ -80,20 +81,22 @@ hipError_t launch_attn_bwd(const AttnShape& s, const void* Q, const void* K, con
                            void* dV, const int* row_ptr, const int* col_idx, const int* col_ptr,
                            const int* row_idx, int nnzb, void* workspace, hipStream_t st);
 
-// The backward workspace: fp32 partial dK / dV tiles for block columns that are cut into several chunks.
+// The backward workspace: fp32 partial dK / dV tiles for block columns that are cut into several chunks and, behind them, dQ
+// tiles for long block rows.  What a call must have is the first, and a workspace for more kept blocks serves it; the
+// second is sized for one number of kept blocks, nothing where no row can be cut.
 struct BwdWorkspace {
     int nnzb;
     int chunk;                       // most kept rows of a key-side work item
     int w_max, w_first;              // work items per head (upper bound); those that may be chunks come first
     int n_slots;                     // partial slots per head (upper bound)
     size_t counter_bytes;            // one per slot and 16 rows, at the workspace's start; the partial tiles behind them
-    size_t row_slots;                // pieces of long rows: RowCut::kSlots per head, or none
-    size_t row_counters, row_parts;  // where theirs start (a counter for every 16 rows)
-    size_t total;
+    size_t total;                    // of the columns; the rows' counters (one for every 16 rows) start there
+    int row_slots;                   // partial slots per head for pieces of rows
+    size_t row_parts, with_rows;     // where their partial tiles start, and end
     // mid_first: unsplit columns to make room for among the items that come first
-    BwdWorkspace(int BH, int bs, int nb, int nnzb, int key_chunk, int mid_first);
+    BwdWorkspace(int BH, int bs, int nb, int nnzb, int key_chunk, int mid_first, int row_slots);
 };
-size_t attn_bwd_workspace_bytes(int BH, int bs, int nb, int nnzb);
+BwdWorkspace attn_bwd_workspace(const AttnShape& s, int nnzb);   // its sizes
 // false when a backward launch for this shape would need more workgroups than a 1-D grid can hold
 bool attn_bwd_grids_fit(int BH, int bs, int nb, int nnzb);
 

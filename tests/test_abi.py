@@ -117,6 +117,14 @@ def test_argument_errors_are_reported_before_any_launch():
     assert lib.spion_attn_bwd(*b3) == -2
 
 
+@pytest.mark.parametrize("dtype,block", [(sp.SPION_BF16, 64), (sp.SPION_BF16, 32), (sp.SPION_BF16, 16), (sp.SPION_F32, 64)])
+def test_backward_workspace_has_no_room_for_rows_that_stay_whole(dtype, block):
+    """With many heads no long row is cut: a head takes no more of the workspace than with thousands of them; with few it does."""
+    per_head = lambda BH: sp.spion_attn_workspace_bytes(BH, 1, 128 * block, 64, block, dtype, 640, True) / BH
+    assert per_head(191) <= 1.002 * per_head(4000)   # counters are rounded up to 256 bytes
+    assert per_head(2) > per_head(191) + 16 * block * 64 * 4
+
+
 def _constants(tmp_path, header, **values):
     """Values of C++ expressions over a header of the kernels, compiled for the host."""
     import subprocess

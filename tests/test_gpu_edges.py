@@ -354,6 +354,32 @@ def test_cut_columns_and_rows_again_and_in_a_graph(sp, dtype, block):
             assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("dtype,block", [("bf16", 32), ("bf16", 64), ("bf16", 16), ("f32", 32), ("f32", 64)])
+def test_backward_in_workspaces_of_other_sizes(sp, dtype, block):
+    """One for more kept blocks serves, and one without the room for pieces of rows, which are whole then (last bytes untouched)."""
+    from test_gpu_parity import _pattern_from_mask
+    nb = 80
+    fl = np.eye(nb, dtype=np.uint8)
+    fl[:, 3] = 1
+    fl[[5, 79], :] = 1
+    pat = _pattern_from_mask(sp, fl, block)
+    gen = torch.Generator(device="cuda").manual_seed(block)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    q, k, v, do = [torch.randn((1, 3, nb * block, 64), generator=gen, device="cuda").to(tdt) for _ in range(4)]
+    o, lse = sp.attn_fwd(q, k, v, pat)
+    want = sp.attn_bwd(q, k, v, o, do, lse, pat)
+    dt = sp.SPION_BF16 if dtype == "bf16" else sp.SPION_F32
+    size = lambda kept: sp.spion_attn_workspace_bytes(1, 3, nb * block, 64, block, dt, kept, True)
+    # the query's rows summed in one run instead of pieces of fp32 sums: rows of up to 80 blocks, each term rounded as before
+    tol = 1e-5 if dtype == "f32" else 2.0 ** -8
+    for n, same in ((size(pat.nnzb), True), (size(2000), True), (size(nb * nb), False), (size(pat.nnzb) - 256, False)):
+        ws = torch.full((n + 256,), 77, dtype=torch.uint8, device="cuda")
+        got = sp.attn_bwd(q, k, v, o, do, lse, pat, workspace=ws[:n])
+        assert bool((ws[n:] == 77).all())
+        assert torch.equal(got[1], want[1]) and torch.equal(got[2], want[2])
+        assert torch.equal(got[0], want[0]) if same else (got[0].double() - want[0].double()).norm() <= tol * want[0].double().norm()
+
+
 # Vectors of 16 bytes, one or two per thread (two from 2^20 vectors), 8 maps at a time and a remainder of 0 to 7
 @pytest.mark.parametrize("L,maps,dtype", [(8, 1, "f32"), (8, 9, "bf16"), (104, 7, "bf16"), (200, 16, "f32"),
                                           (2056, 3, "f32"), (2904, 10, "bf16")])
