@@ -59,3 +59,8 @@ def algorithmic_bytes(kernel: str, bh: int, L: int, d: int, elem_bytes: int) -> 
     if kernel == "path":
         return 12 * t + 2 * vec
     raise ValueError(kernel)
+
+
+def backward_launches(bh: int, bs: int, nb: int, nnzb: int, dtype: str) -> int:
+    """Launches of one spion_attn_bwd: one, whatever the pattern (what is cut is added up by the last of its parts)."""
+    return 1

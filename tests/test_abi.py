@@ -185,6 +185,10 @@ def test_useful_flop_and_byte_accounting():
     assert acc.algorithmic_bytes("fwd", 16, 4096, 64, 2) == 4 * t + 16 * 4096 * 4
 
 
+def test_backward_is_one_launch():
+    assert acc.backward_launches(16, 64, 64, 328, "bf16") == acc.backward_launches(9, 16, 121, 1171, "f32") == 1
+
+
 def test_bench_refuses_more_than_one_gpu():
     import subprocess
     import sys
