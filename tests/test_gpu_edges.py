@@ -13,6 +13,7 @@ pytestmark = pytest.mark.gpu
 def sp():
     import paper_2309_12578_amd as sp
     sp.load()
+    sp.binding._native()   # tests use it by name, in any order
     return sp
 
 
@@ -507,6 +508,38 @@ def test_heads_where_the_projections_have_them(sp, B, H, nb, block, denom):
     O, LSE = sp.attn_fwd(q, k, v, pat, flags=flags)
     dO = dS.view(B, L, H, 64).transpose(1, 2).contiguous()
     want = torch.stack([t.transpose(1, 2) for t in sp.attn_bwd(q, k, v, O, dO, LSE, pat, flags=flags)], 2)
+    assert torch.equal(S.view(B, L, H, 64).transpose(1, 2), O)
+    assert torch.equal(got.view(B, L, 3, H, 64), want)
+
+
+# 33 to 64 block rows that all run at once (the forward cuts rows of twice the mean), and more (both sides cut)
+@pytest.mark.parametrize("B,H,nb,block", [(1, 3, 40, 32), (2, 1, 64, 64), (1, 3, 65, 32), (2, 2, 80, 64), (1, 1, 255, 32)])
+def test_long_rows_in_pieces_where_the_projections_have_the_heads(sp, B, H, nb, block):
+    """As test_heads_where_the_projections_have_them, for patterns whose long rows are cut."""
+    import ctypes
+    from test_gpu_parity import _pattern_from_mask
+    fl = np.eye(nb, dtype=np.uint8)
+    fl[:, 1] = 1
+    fl[7, :] = 1
+    fl[nb - 1, : 7 * nb // 8] = 1
+    fl[3, :] = 0
+    pat = _pattern_from_mask(sp, fl, block)
+    L = nb * block
+    lib = sp.load()
+    lib.spion_attn_fwd_room_bytes.restype = ctypes.c_size_t
+    p = sp.binding._AttnParams(B, H, L, 64, block, sp.SPION_BF16, 0.0, 0)
+    assert lib.spion_attn_fwd_room_bytes(ctypes.byref(p), pat.nnzb) > 0
+    per_head = lambda heads: sp.spion_attn_workspace_bytes(heads, 1, L, 64, block, sp.SPION_BF16, pat.nnzb, True) / heads
+    assert (per_head(B * H) > 1.1 * per_head(4000)) == (nb > 64)
+    gen = torch.Generator(device="cuda").manual_seed(nb)
+    qkv = torch.randn((B, L, 3, H, 64), generator=gen, device="cuda").to(torch.bfloat16).view(B, L, 3 * H * 64).requires_grad_(True)
+    dS = torch.randn((B, L, H * 64), generator=gen, device="cuda").to(torch.bfloat16)
+    S = sp.binding._host.heads_attention(qkv, H, pat.row_ptr, pat.col_idx, pat.col_ptr, pat.row_idx, pat.bsr_pos, pat.nnzb, block, 0)
+    got, = torch.autograd.grad(S, qkv, dS)
+    q, k, v = [t.transpose(1, 2).contiguous() for t in qkv.detach().view(B, L, 3, H, 64).unbind(2)]
+    O, LSE = sp.attn_fwd(q, k, v, pat)
+    dO = dS.view(B, L, H, 64).transpose(1, 2).contiguous()
+    want = torch.stack([t.transpose(1, 2) for t in sp.attn_bwd(q, k, v, O, dO, LSE, pat)], 2)
     assert torch.equal(S.view(B, L, H, 64).transpose(1, 2), O)
     assert torch.equal(got.view(B, L, 3, H, 64), want)
 
