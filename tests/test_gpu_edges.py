@@ -317,6 +317,20 @@ def test_backward_chunks_follow_the_work(sp, BH, nb, density, block):
     _attention(sp, Q, K, V, dO, fl, block, "bf16", [0, BH - 1])
 
 
+# 2, 7, 8, 9, 16 and 17 parts, of which eight are added up at a time; four and two waves a row (many short rows)
+@pytest.mark.parametrize("dtype,block", [("f32", 16), ("f32", 32), ("bf16", 16)])
+@pytest.mark.parametrize("BH", [1, 40])
+def test_generic_backward_parts_of_a_column(sp, dtype, block, BH):
+    nb = 260
+    fl = np.eye(nb, dtype=np.uint8)
+    for c, n in ((0, 17), (9, 112), (70, 128), (128, 129), (200, 256), (259, 260)):
+        fl[:, c] = np.arange(nb) < n
+    rng = np.random.default_rng(BH)
+    Q, K, V, dO = [np.repeat(si.round_to_dtype(rng.standard_normal((1, nb * block, 64), dtype=np.float32), dtype), BH, 0)
+                   for _ in range(4)]
+    _attention(sp, Q, K, V, dO, fl, block, dtype, [BH - 1])
+
+
 @pytest.mark.parametrize("dtype,block", [("bf16", 32), ("bf16", 64), ("bf16", 16), ("f32", 32)])
 def test_cut_columns_and_rows_again_and_in_a_graph(sp, dtype, block):
     """Backward, whichever chunk of a column or piece of a row is the last to arrive: the same bits every time, in a workspace that
