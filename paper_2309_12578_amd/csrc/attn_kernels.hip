@@ -870,16 +870,21 @@ static bool fwd_many(const AttnShape& s, int rows) { return 2ll * s.BH * s.L / r
 
 // Rows in pieces, from twice the mean on as long as about all workgroups run at once (else the long ones start first, and
 // have to outlast the launch from there to be cut).  Forward kernel, fp32, block 32: 2 heads x 8192, 3 %, 51 -> 23.4 us; 4 x 4096, 5 %, 28 -> 18.9; 8 x 2048, 10 %,
-// 20.3 -> 17.7, 20 %, 28.6 -> 26; block 64, 3 x 4096, 10 %, 31.4 -> 26.8; block 16, 2 x 2048, 15.7 -> 12; bf16, block 16, 9 x 1936, 8 %, 12.8 -> 12.3.
-// Cut where the rule leaves them whole, 16 x 2048: block 32 28.9 -> 30, block 16 22.7 -> 23.5, bf16 15.3 -> 16.1; 4 x 1024, block 16, 8.5 -> 9.4,
-// bf16, 10 x 1584 10.3 -> 11.1.
+// 20.3 -> 17.7, 20 %, 28.6 -> 26; block 64, 3 x 4096, 10 %, 31.4 -> 26.8; block 16, 2 x 2048, 15.7 -> 12.  Patterns without a long row pay 2 to 7 %, at most
+// (5 x 2368, block 64) 11.7 -> 13.2.  Cut where the rule leaves them whole, 16 x 2048: block 32 28.9 -> 30, block 16 22.7 -> 23.5, bf16 15.3 -> 16.1.
+// Block 16, whose rows are short work: fp32, long rows, 64 block rows 4 heads 9.0 -> 9.8, 9 heads 15.1 -> 11.9; 65 9.0 -> 10.2, 12.3 -> 12.0; 80 10.3 -> 10.8,
+// 14.6 -> 13.8; 110 and more 0.62 to 0.89 of the time.  bf16, a row of 65 to 70 blocks breaks even; uncut to cut on average over 12 patterns, 9 heads (more
+// workgroups than run at once from 114 block rows on): 115 block rows 1.04, 121 1.00, 130 0.95, 144 0.93, 160 0.88; 4 heads: 121 1.11, 136 1.07, 144 1.02, 160
+// 0.95, 180 0.94; 2 heads: 136 1.07, 144 1.02, 160 0.97.
 RowCut generic_fwd_cut(const AttnShape& s, int nnzb) {
     RowCut cut;
     if (s.nb <= 32) return cut;   // decide() cuts none
     const int rows = fwd_rows(s, nnzb);
     if (rows == 0) return cut;
     const bool many = fwd_many(s, rows);
-    if (many ? s.BH > 8 : s.bs == 16 && s.nb <= (s.is_bf16 ? 110 : 64)) return cut;   // rather no helpers that find nothing to do
+    // block 16: rows that can be long enough for what the pieces cost, 2 us
+    const int least = !s.is_bf16 ? 64 : (long long)s.BH * s.nb > fwd_resident(16) ? 120 : 150;
+    if (many ? s.BH > 8 : s.bs == 16 && s.nb <= least) return cut;   // rather no helpers that find nothing to do
     const int parts = s.bs / rows;
     cut.decide(s, nnzb, (many ? 2 : 1) * (long long)s.BH * nnzb * parts / fwd_resident(rows), !many);
     const long long most = 512 / ((long long)s.BH * parts);   // a helper for each piece, and not many that find nothing to do

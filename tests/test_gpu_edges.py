@@ -180,6 +180,43 @@ def test_long_rows_in_pieces_of_the_generic_kernels(sp, dtype, block, BH, nb, lo
     _attention(sp, Q, K, V, dO, fl, block, dtype, [0, BH - 1], flags=sp.SPION_ATTN_PAPER_DENOM if denom else 0)
 
 
+# bf16, block 16: rows are cut above 120 block rows where more workgroups than run at once (1024), above 150 where they all do
+@pytest.mark.parametrize("BH,nb,cut", [(8, 128, False), (9, 120, False), (9, 121, True), (2, 150, False), (2, 151, True), (6, 170, True)])
+def test_long_rows_of_block_16(sp, BH, nb, cut):
+    import ctypes
+    fl = np.eye(nb, dtype=np.uint8)
+    fl[[3, nb - 1], :] = 1
+    fl[7, : nb // 2] = 1
+    fl[5, :] = 0
+    lib = sp.load()
+    lib.spion_attn_fwd_room_bytes.restype = ctypes.c_size_t
+    p = sp.binding._AttnParams(1, BH, nb * 16, 64, 16, sp.SPION_BF16, 0.0, 0)
+    assert (lib.spion_attn_fwd_room_bytes(ctypes.byref(p), int(fl.sum())) > 0) == cut
+    rng = np.random.default_rng(nb)
+    Q, K, V, dO = [si.round_to_dtype(rng.standard_normal((BH, nb * 16, 64), dtype=np.float32), "bf16") for _ in range(4)]
+    _attention(sp, Q, K, V, dO, fl, 16, "bf16", [0, BH - 1])
+
+
+@pytest.mark.parametrize("BH,nb", [(3, 160)])
+def test_pieces_of_block_16_whose_scores_are_all_minus_infinity(sp, BH, nb):
+    """As below, where block 16 is cut."""
+    from test_gpu_parity import _pattern_from_mask
+    long, without = np.eye(nb, dtype=np.uint8), np.eye(nb, dtype=np.uint8)
+    long[[3, 150]] = without[[3, 150]] = 1
+    without[:, 10:90] = 0
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    q, k, v = [torch.randn((1, BH, nb * 16, 64), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3)]
+    q = q.abs() + 0.125
+    k[:, :, 10 * 16:90 * 16] = -float("inf")
+    got, got_lse = sp.attn_fwd(q, k, v, _pattern_from_mask(sp, long, 16))
+    want, want_lse = sp.attn_fwd(q, k, v, _pattern_from_mask(sp, without, 16))
+    for row in (3, 150):
+        at = slice(row * 16, (row + 1) * 16)
+        # tolerances of test_pieces_whose_scores_are_all_minus_infinity
+        assert torch.allclose(got[:, :, at].float(), want[:, :, at].float(), rtol=0.0, atol=2e-2)
+        assert torch.allclose(got_lse[:, :, at], want_lse[:, :, at], rtol=0.0, atol=1e-2)
+
+
 @pytest.mark.parametrize("dtype,block", [("bf16", 32), ("bf16", 64), ("bf16", 16), ("f32", 32)])
 def test_pieces_whose_scores_are_all_minus_infinity(sp, dtype, block):
     """Keys that give scores of -infinity count nothing, also where they are all that a piece of a long row has."""
