@@ -13,6 +13,7 @@
 #include <ATen/hip/EmptyTensor.h>
 #include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
+#include <c10/hip/HIPCachingAllocator.h>
 #include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
@@ -117,15 +118,16 @@ void room_for_rows(const at::Tensor& q, const at::Tensor& lse) {
         bad_value("LSE must be fp32 with at least B * H * L elements");
 }
 
-// For the pieces of long rows (spion_attn_fwd_room), of this call alone.
+// For the pieces of long rows (spion_attn_fwd_room), of this call alone: back to the allocator, in the order of the stream,
+// when the call returns.
 struct Room {
-    at::Tensor memory;
+    c10::DataPtr memory;
     size_t bytes;
     void* ptr = nullptr;
-    Room(const spion_attn_params& p, int nnzb, const at::Tensor& like) : bytes(spion_attn_fwd_room_bytes(&p, nnzb)) {
+    Room(const spion_attn_params& p, int nnzb) : bytes(spion_attn_fwd_room_bytes(&p, nnzb)) {
         if (bytes == 0) return;
-        memory = new_bytes(bytes, like);
-        ptr = memory.data_ptr();
+        memory = c10::hip::HIPCachingAllocator::get()->allocate(bytes);
+        ptr = memory.get();
     }
 };
 
@@ -139,7 +141,7 @@ void forward(const at::Tensor& q, const at::Tensor& k, const at::Tensor& v, cons
     if (!lse.defined())
         lse = at::Tensor(at::detail::empty_cuda({q.size(0), q.size(1), q.size(2)}, at::kFloat, q.device(), std::nullopt));
     else room_for_rows(q, lse);
-    const Room room(p, ix.nnzb, q);
+    const Room room(p, ix.nnzb);
     const int rc = spion_attn_fwd_room(device_ptr(q), device_ptr(k), device_ptr(v), device_ptr(o), (float*)device_ptr(lse),
                                        (const int32_t*)device_ptr(ix.row_ptr), (const int32_t*)device_ptr(ix.col_idx),
                                        ix.nnzb, &p, room.ptr, room.bytes, current_stream());
@@ -510,7 +512,7 @@ PyObject* py_heads_attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
             const spion_attn_params p = heads_params(qkv, H, ix);
             s = at::Tensor(at::detail::empty_cuda({B, L, H * 64}, qkv.scalar_type(), qkv.device(), std::nullopt));
             lse = at::Tensor(at::detail::empty_cuda({B, H, L}, at::kFloat, qkv.device(), std::nullopt));
-            const Room room(p, ix.nnzb, qkv);
+            const Room room(p, ix.nnzb);
             const int rc = spion_heads_attn_fwd(device_ptr(qkv), device_ptr(s), (float*)device_ptr(lse),
                                                 (const int32_t*)device_ptr(ix.row_ptr), (const int32_t*)device_ptr(ix.col_idx),
                                                 ix.nnzb, &p, room.ptr, room.bytes, current_stream());
