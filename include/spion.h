@@ -166,7 +166,8 @@ size_t spion_attn_workspace_bytes(const spion_attn_params *p, int32_t nnzb, int3
  *   Q, K, V   inputs [B, H, L, d];  O output [B, H, L, d];  LSE output fp32 [B, H, L].
  *   row_ptr, col_idx, nnzb  BSR index from spion_pattern (nnzb passed by value, as read back by the
  *             caller); 0 <= col_idx < nb and row_ptr must be non-decreasing with row_ptr[nb] == nnzb.
- *   p         HOST pointer.  workspace may be NULL when spion_attn_workspace_bytes(...) is 0.
+ *   p         HOST pointer.  workspace may be NULL when spion_attn_workspace_bytes(...) is 0 (it is: this
+ *             call takes every block row in one piece, however long; with few heads the longest set its time).
  */
 int spion_attn_fwd(const void *Q, const void *K, const void *V, void *O, float *LSE,
                    const int32_t *row_ptr, const int32_t *col_idx, int32_t nnzb,

@@ -286,7 +286,10 @@ static int fwd_resident(int bs) { return 256 * (bs == 64 ? 4 : 8); }
 // block 32, which the rule leaves whole, 38.6 / 40.5 and 38.5 / 41.9.  A pattern without long rows: 76.6 / 76.9, 14.7 / 14.8.
 // With 33 to 64 block rows, where all of them run at once (short_too) and nothing hides the longest, rows of twice the mean are cut:
 // 8 x 2048, block 32, rows of 24 blocks, 11.2 / 9.5; 32 x 2048 19.3 / 16.6; 4 x 4096, block 64, 16.7 / 13.1; 16 x 4096, 10 %, 26.1 / 19.9; 2 x 4096,
-// 15 %, 20.8 / 13.7; without long rows 14.9 / 14.6.
+// 15 %, 20.8 / 13.7; without long rows 14.9 / 14.6.  Over 150 shapes of 33 to 256 block rows, the cut ones take 0.35 to 1.05 of the time uncut (0.81 on
+// average above 64 block rows, 0.96 up to there), but 1.15 at 45 heads x 4096, block 32, rows of 54 and 38, where two helpers a head are few.
+// The line at 64 block rows is not where twice the mean stops paying: of 36 shapes of 80 to 255 block rows that all run at once it would
+// take 0.59 to 0.85 of the time in 20, as long (at most 1.01) in the others (2 x 8192, block 64, 10 %, 28.6 / 17.0; 8 x 4096, block 32, 20 %, 28.2 / 19.4).
 void RowCut::decide(const AttnShape& s, int nnzb, long long steps, bool short_too) {
     // Up to 64 block rows a row is not that long, and what the others pay shows: a kernel of 45 us without a row to cut, 32 heads x
     // 4096, block 64, took 1 us longer.
