@@ -264,7 +264,7 @@ __global__ __launch_bounds__(BS * 4) void attn_fwd_bf16_kernel(
     if constexpr (CUT) id -= cut.groups;
     int bh, I;
     if (sort_rows) {
-        const RowOfHead mine = long_rows_first<true>(row_ptr, nb, total / nb, id, lane);
+        const RowOfHead mine = rows_in_order<true>(row_ptr, nb, total / nb, id, lane, (total / nb & 7) == 0);
         bh = mine.head;
         I = mine.row;
     } else {

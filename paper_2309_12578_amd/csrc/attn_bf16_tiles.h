@@ -10,6 +10,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "../../include/spion.h"
 #include "attn_common.h"
 #include "spion_internal.h"
 
@@ -183,19 +184,72 @@ __device__ __forceinline__ int xcd_deal(int id, int lo, int hi) {
     return lower_xcds(hi) - lower_xcds(lo) + (id >> 3) - ((lo + 7 - x) >> 3);
 }
 
-// Which block row the workgroup number l of `heads` heads takes, when there are more workgroups
-// than run at once: the rows with more than twice the mean number of kept blocks first, of all the heads (a
-// row of 80 blocks that starts last runs alone for as long as everything before it took), then head by
-// head the others, so that neighbours in time share K and V in an L2.  DEAL: l is the workgroup id, and each
-// of the two lists is shared out over the XCDs head by head; else l counts the workgroups of one XCD.
-// Dealt this way for any number of heads: rows in id order, one L2 after the other, at 12 heads of 256 rows of
-// 64 x 13 blocks each in a band read K and V eight times (forward 101 -> 58 us; 20 heads, block 32, 9 blocks: 61 -> 27
-// us; unsorted and dealt 61 and 29 us).  Patterns without a long row skip the second search, and the counts are
-// loaded four groups at a time (3 heads of 1000 rows of 12 blocks: 86 -> 76 us, unsorted 77).
-// All lanes of the calling wave must be active.
+// Rows (columns) in the order of their lengths: longest first, equal ones by index; lengths count in quarters of the mean, four
+// times the mean and more alike.  Lane l holds the entry 64 k + l of group k: its length in those units and, as bits
+// of a group, which entries take part.  The entry whose place is `want`, found a bit of the length at a time: some 40
+// instructions a group, no memory access.  Half the mean as unit, a bit less, saves nothing and orders worse (fp32, 64 x 1024, block 32,
+// backward 110.8 -> 113 us).  All lanes active, the result uniform; -1: there are not so many entries.
+constexpr int kLengthBits = 4;
+__device__ __forceinline__ float quarters_of_mean(int nb, int nnzb) { return 4.f * (float)nb * __builtin_amdgcn_rcpf((float)max(nnzb, 1)); }
+__device__ __forceinline__ int length_key(int cnt, float quarters) { return min((int)((float)cnt * quarters), (1 << kLengthBits) - 1); }
+template <int NG>
+__device__ __forceinline__ int entry_by_length(const int (&key)[NG], unsigned long long (&mask)[NG], int want, int lane) {
+#pragma unroll
+    for (int bit = 1 << (kLengthBits - 1); bit; bit >>= 1) {
+        unsigned long long upper[NG];
+        int n = 0;
+#pragma unroll
+        for (int k = 0; k < NG; ++k) {
+            upper[k] = mask[k] & __ballot((key[k] & bit) != 0);
+            n += __popcll(upper[k]);
+        }
+        const bool in = want < n;
+        if (!in) want -= n;
+#pragma unroll
+        for (int k = 0; k < NG; ++k) mask[k] = in ? upper[k] : mask[k] & ~upper[k];
+    }
+#pragma unroll
+    for (int k = 0; k < NG; ++k) {
+        const int members = __popcll(mask[k]);
+        if (want < members) {
+            const unsigned long long hit = __ballot(((mask[k] >> lane) & 1ull) && lanes_below(mask[k]) == want);
+            return 64 * k + __ffsll((long long)hit) - 1;
+        }
+        want -= members;
+    }
+    return -1;
+}
+
+template <int NG>
+__device__ __forceinline__ int row_by_length(const int* __restrict__ row_ptr, int nb, int rank, int lane) {
+    const float quarters = quarters_of_mean(nb, row_ptr[nb]);
+    int key[NG];
+    unsigned long long mask[NG];
+#pragma unroll
+    for (int k = 0; k < NG; ++k) {
+        const int r = 64 * k + lane;
+        key[k] = r < nb ? row_ptr[r + 1] - row_ptr[r] : 0;
+        mask[k] = __ballot(r < nb);
+    }
+#pragma unroll
+    for (int k = 0; k < NG; ++k) key[k] = length_key(key[k], quarters);
+    return entry_by_length<NG>(key, mask, rank, lane);
+}
+// Which block row the workgroup number l of `heads` heads takes, when there are more workgroups than run at once.  DEAL: l is
+// the workgroup id; else l counts the workgroups of one XCD.
 struct RowOfHead {
     int row, head;
 };
+// Heads that do not divide over the XCDs: the rows with more than twice the mean number of kept blocks first, of all the heads (a
+// row of 80 blocks that starts last runs alone for as long as everything before it took), then head by
+// head the others, so that neighbours in time share K and V in an L2.  DEAL: each
+// of the two lists is shared out over the XCDs head by head.
+// Dealt this way: rows in id order, one L2 after the other, at 12 heads of 256 rows of
+// 64 x 13 blocks each in a band read K and V eight times (forward 101 -> 58 us; 20 heads, block 32, 9 blocks: 61 -> 27
+// us; unsorted and dealt 61 and 29 us).  Patterns without a long row skip the second search, and the counts are
+// loaded four groups at a time (3 heads of 1000 rows of 12 blocks: 86 -> 76 us, unsorted 77).  By length throughout, in either list,
+// such heads were slower: bf16, 12 heads x 6144, block 64, forward 26.2 -> 28.1; 13 x 8192, block 32, backward 105 -> 113.
+// All lanes of the calling wave must be active.
 template <bool DEAL>
 __device__ __forceinline__ RowOfHead long_rows_first(const int* __restrict__ row_ptr, int nb, int heads, int l, int lane) {
     const int limit = 2 * row_ptr[nb] / nb;
@@ -244,6 +298,24 @@ __device__ __forceinline__ RowOfHead long_rows_first(const int* __restrict__ row
         rank -= members;
     }
     return {0, head};
+}
+
+// By length, all heads of an XCD together, where each XCD has whole heads (`whole`): what starts last is short then.  Forward, long rows
+// first and so: bf16, block 64, 32 heads x 4096, 13 blocks a row 45.7 -> 41.6 us, 64 x 2048 19.3 -> 18.1; block 32, 32 x 4096 32.3 -> 29.6; fp32, block 16,
+// 16 x 2048 23.5 -> 22.5.  The backward, whose short columns come last anyway, hardly gains by the rows' order (head by head within an XCD it loses
+// locality: 32 x 4096, block 32, 91 -> 98).
+template <bool DEAL>
+__device__ __forceinline__ RowOfHead rows_in_order(const int* __restrict__ row_ptr, int nb, int heads, int l, int lane, bool whole) {
+    if (!whole) return long_rows_first<DEAL>(row_ptr, nb, heads, l, lane);
+    const int x = DEAL ? l & 7 : 0;
+    if (DEAL) {
+        l >>= 3;
+        heads >>= 3;
+    }
+    const int rank = l / heads, head = x * heads + l % heads;
+    const int row = nb <= 64 ? row_by_length<1>(row_ptr, nb, rank, lane) : nb <= 128 ? row_by_length<2>(row_ptr, nb, rank, lane)
+                  : nb <= 256 ? row_by_length<4>(row_ptr, nb, rank, lane) : row_by_length<SPION_MAX_NB / 64>(row_ptr, nb, rank, lane);
+    return {row, head};
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -48,9 +48,9 @@ __device__ __forceinline__ void lds_barrier() {
 // are dealt to the XCDs round-robin) works on whole heads, items of all its heads interleaved.
 // n_key_a / n_rows / n_key_c are the per-head counts of the three groups present in this launch
 // (a group is absent when only one side is requested).  w_first leaves room for a quarter of the columns
-// besides the chunks: unsplit columns of more than kMidColumn rows that came last ran on alone (64 heads x 1024,
-// block 32, 4.8 blocks a row: 31.6 -> 26.5 us; 4 and 12 measure like 8, and a sixth or a third of the columns like a
-// quarter).  Pieces of long rows come before all three (CUT).  With sort_rows the rows of more than twice the mean length come before the others.
+// besides the chunks, the longest of them: unsplit columns of more than 8 rows that came last ran on alone (64 heads x 1024,
+// block 32, 4.8 blocks a row: 31.6 -> 26.5 us; a sixth or a third of the columns measure like a quarter).  Pieces of long rows
+// come before all three (CUT).  With sort_rows the rows go by rows_in_order().
 // ------------------------------------------------------------------------------------------------
 template <int BS, bool BESIDE, bool CUT>
 __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
@@ -108,7 +108,7 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
         l -= hpx * n_key_a;
         key_side = false;
         if (sort_rows) {
-            const RowOfHead mine = long_rows_first<false>(row_ptr, nb, hpx, l, lane);
+            const RowOfHead mine = rows_in_order<false>(row_ptr, nb, hpx, l, lane, (BH & 7) == 0);
             bh = x * hpx + mine.head;
             idx = mine.row;
         } else {
@@ -277,7 +277,7 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
     // ============================================================================================
     // key side: work item idx of head bh.  {Q, dO, O} tiles and LSE of a block row in two stages.
     // ============================================================================================
-    const KeyItem item = key_item_lookup(col_ptr, nb, chunk, kMidColumn, idx, lane);
+    const KeyItem item = key_item_lookup(col_ptr, nb, chunk, true, idx, lane);
     if (item.J < 0) return;
     const int J = item.J, n = item.ke - item.kb, slot = item.slot;
     const int krow = J * BS + wave * 16 + r;

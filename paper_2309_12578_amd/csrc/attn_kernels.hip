@@ -189,7 +189,7 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_fwd_kernel(
     } else if (sort_rows) {
         const int row = (id >> 3) / S::PARTS * 8 + (id & 7);   // a row's workgroups on one XCD
         if (row >= total / S::PARTS) return;
-        const RowOfHead mine = long_rows_first<true>(row_ptr, nb, total / (nb * S::PARTS), row, lane);
+        const RowOfHead mine = rows_in_order<true>(row_ptr, nb, total / (nb * S::PARTS), row, lane, (total / (nb * S::PARTS) & 7) == 0);
         bh = mine.head;
         I = mine.row;
         part = (id >> 3) % S::PARTS;
@@ -425,7 +425,7 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_bwd_kernel(
     T* __restrict__ dV, const int* __restrict__ row_ptr, const int* __restrict__ col_idx,
     const int* __restrict__ col_ptr, const int* __restrict__ row_idx, float* __restrict__ partial,
     unsigned long long* __restrict__ counters, unsigned long long tag, CutOf<CUT> cut, int n_slots, int BH, int L, int nb, int n_key_a,
-    int n_rows, int n_key_c, int w_first, int chunk, int mid, int early_rows, float scale, float scale_log2) {
+    int n_rows, int n_key_c, int w_first, int chunk, int by_length, int early_rows, float scale, float scale_log2) {
     typedef typename Elem<T>::Frag Frag;
     typedef typename Elem<T>::Quad Quad;
     typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
@@ -492,7 +492,7 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_bwd_kernel(
     } else if (early_rows) {
         const int row = first_row + (id >> 3) / S::PARTS * 8 + (id & 7);   // a row's workgroups on one XCD
         if (row >= BH * n_rows) return;
-        const RowOfHead mine = long_rows_first<true>(row_ptr, nb, BH, row, lane);
+        const RowOfHead mine = rows_in_order<true>(row_ptr, nb, BH, row, lane, (BH & 7) == 0);
         bh = mine.head;
         idx = mine.row;
         sub = (id >> 3) % S::PARTS * OWN;
@@ -636,7 +636,7 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_bwd_kernel(
         return;
     }
 
-    const KeyItem it = key_item_lookup(col_ptr, nb, chunk, mid, idx, lane);
+    const KeyItem it = key_item_lookup(col_ptr, nb, chunk, by_length != 0, idx, lane);
     if (it.J < 0) return;
     const int n = it.ke - it.kb, nt = n * S::TPB, row0 = it.J * BS + sub + own;
     const int* rows = row_idx + it.kb;
@@ -899,7 +899,7 @@ template <typename T, int BS, typename S>
 static hipError_t launch_fwd(const AttnShape& s, const void* Q, const void* K, const void* V, void* O,
                              float* LSE, const int* row_ptr, const int* col_idx, int nnzb, hipStream_t st) {
     const long long total = (long long)s.nb * s.BH * S::PARTS;
-    // Rows of more than twice the mean first, as in launch_bwd.  fp32, block 32: 32 heads x 2048, 10 %, 61.3 -> 48.3 us, 16 x 2048 33.3 -> 29.1; block 16, 16 x
+    // Rows by length or long ones first (rows_in_order), as in launch_bwd.  fp32, block 32: 32 heads x 2048, 10 %, 61.3 -> 48.3 us, 16 x 2048 33.3 -> 29.1; block 16, 16 x
     // 2048, 6 %, 27.2 -> 22.7; bf16, 17.2 -> 15.4.  The search costs half a microsecond to one: 9 x 1936 (few more than run at once)
     // 12.7 -> 13.2; up to 32 block rows no row is long enough, 32 x 1024, block 64, 28.2 -> 29.2.
     const int sort_rows = s.nb > 32 && (long long)nnzb * (BS / 16) >= 6ll * s.nb && fwd_many(s, S::OWN);
@@ -947,7 +947,7 @@ static hipError_t launch_bwd(const AttnShape& s, const void* Q, const void* K, c
     const bool rows = (s.bwd_phases & 1) != 0, keys = (s.bwd_phases & 2) != 0;
     const int n_key_a = keys ? ws.w_first : 0, n_rows = rows ? s.nb : 0, n_key_c = keys ? ws.w_max - ws.w_first : 0;
     const long long per_item = (long long)s.BH * S::PARTS;
-    // Rows of more than twice the mean first, where a quarter more workgroups than run at once (two or three waves a SIMD) follow:
+    // Rows by length or long ones first (rows_in_order), where a quarter more workgroups than run at once (two or three waves a SIMD) follow:
     // one that starts late runs on alone.  fp32: 2 heads x 8192, block 32, 3 %, 161 -> 148 us; 3 x 4096, block 64, 10 %, 86 -> 76; 8 x 2048,
     // block 32, 15 %, 78 -> 71, 10 % 52.7 both; bf16, block 16: 10 x 4096, 4 %, 71 -> 67, 9 x 1936, 8 %, 31.3 -> 30.0; rows of fewer
     // than 6 tiles on average gain nothing and pay the search, up to 1 us (bf16, block 16, searched and not: 24 x 1168, 4 %, 19.5,
@@ -959,10 +959,10 @@ static hipError_t launch_bwd(const AttnShape& s, const void* Q, const void* K, c
     // 4 x 4096, 5 %, 70.6 -> 62.2.
     const long long row_items = group_grid((long long)s.BH * n_rows), some = group_grid((long long)s.BH * ((s.nb + 31) / 32));
     const int early_rows = (int)(!sort_rows ? 0 : some < row_items ? some : row_items);
-    // Unsplit columns of more than 8 rows before the rows, where half as many workgroups again as run at once make the order matter
+    // Unsplit columns by length, so that long ones come before the rows, where half as many workgroups again as run at once make the order matter
     // (the search costs a workgroup a microsecond: 16 heads x 512, block 32, 29.1 -> 30.4).  fp32, block 32: 16 x 1024, 10 %, 46.4 -> 34.7,
     // 20 %, 68 -> 49.4; 64 x 1024, 15 %, 142 -> 113; 24 x 2336, 4 %, 74.6 -> 69; block 64, 32 x 1024, 20 %, 95.7 -> 87.3.
-    const int mid = 2 * per_item * (n_key_a + n_rows + n_key_c) > 3 * resident ? kMidColumn : ws.chunk;
+    const int by_length = 2 * per_item * (n_key_a + n_rows + n_key_c) > 3 * resident;
     const long long grid = group_grid(per_item * n_key_a) + (sort_rows ? S::PARTS * row_items : group_grid(per_item * n_rows)) +
                            group_grid(per_item * n_key_c);
     auto launch = [&](auto kernel, auto cut_arg, int helpers) {
@@ -970,7 +970,7 @@ static hipError_t launch_bwd(const AttnShape& s, const void* Q, const void* K, c
             static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V), static_cast<const T*>(O),
             static_cast<const T*>(dO), LSE, static_cast<T*>(dQ), static_cast<T*>(dK), static_cast<T*>(dV), row_ptr,
             col_idx, col_ptr, row_idx, partial, counters, s.tag, cut_arg, ws.n_slots, s.BH, s.L, s.nb, n_key_a, n_rows, n_key_c,
-            ws.w_first, ws.chunk, mid, early_rows, s.scale, s.scale * kLog2e);
+            ws.w_first, ws.chunk, by_length, early_rows, s.scale, s.scale * kLog2e);
         return hipGetLastError();
     };
     if (grid <= 0) return hipSuccess;

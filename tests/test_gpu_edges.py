@@ -882,3 +882,27 @@ def test_forward_sorted_rows_at_odd_head_counts(sp, BH, nb, block, long_rows):
         o, lse = sp.attn_fwd(*[t[:, h:h + 1].contiguous() for t in (q, k, v)], pat)
         assert torch.equal(O[:, h:h + 1], o) and torch.equal(LSE[:, h:h + 1], lse), h
     assert not O.isnan().any() and not LSE.isnan().any()
+
+
+# Whole heads on every XCD: rows by length, of one, two, four and sixteen groups of 64 block rows, the last group full and not
+@pytest.mark.parametrize("BH,nb,block", [(24, 64, 64), (24, 65, 64), (24, 128, 32), (8, 129, 64), (8, 256, 64), (8, 257, 32), (8, 1000, 32)])
+def test_forward_rows_by_length(sp, BH, nb, block):
+    from test_gpu_parity import _pattern_from_mask
+    rng = np.random.default_rng(nb)
+    fl = (rng.random((nb, nb)) < rng.random((nb, 1)) * 12 / nb).astype(np.uint8)   # 0 to about 20 blocks a row
+    fl[rng.choice(nb, 3, replace=False)] = rng.random((3, nb)) < 60 / nb
+    fl[5] = 0
+    pat = _pattern_from_mask(sp, fl, block)
+    gen = torch.Generator(device="cuda").manual_seed(BH)
+    q, k, v = [torch.randn((1, BH, nb * block, 64), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3)]
+    O = torch.full_like(q, float("nan"))
+    LSE = torch.full(q.shape[:3], float("nan"), device="cuda")
+    index = (pat.row_ptr, pat.col_idx, pat.nnzb)
+    shape = (nb * block, 64, block, sp.SPION_BF16)
+    sp.spion_attn_fwd(q, k, v, O, LSE, *index, 1, BH, *shape)   # without room for pieces: no row is cut
+    for h in (0, BH // 2, BH - 1):
+        args = [t[:, h:h + 1].contiguous() for t in (q, k, v, O, LSE)]
+        args[3].zero_(), args[4].zero_()
+        sp.spion_attn_fwd(*args, *index, 1, 1, *shape)
+        assert torch.equal(O[:, h:h + 1], args[3]) and torch.equal(LSE[:, h:h + 1], args[4]), h
+    assert not O.isnan().any() and not LSE.isnan().any()
