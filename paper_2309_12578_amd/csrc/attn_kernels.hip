@@ -809,6 +809,27 @@ BwdWorkspace::BwdWorkspace(int BH, int bs, int nb, int nnzb_, int key_chunk, int
     with_rows = row_parts + (size_t)BH * row_slots * bs * kD * sizeof(float);
 }
 
+// Rows with hardly more than one block each (the diagonal): no long chain to cut anywhere.
+static bool single_block_rows(const AttnShape& s, int nnzb) { return 2 * (long long)nnzb < 3 * (long long)s.nb; }
+
+// Whether a call has many block rows for every tile of its average row: 100.  Measured (fp32, and bf16 / block 16;
+// patterns with a few long rows and columns, 2.4 to 9.6 blocks per row) the backward's crossing lies between 75
+// and 200; without long rows it comes earlier, at 40 with the diagonal alone.
+static bool many_short_rows(const AttnShape& s, int nnzb) {
+    const long long rows = (long long)s.BH * s.nb, tiles_times_nb = (long long)nnzb * (s.bs / 16);   // of one head
+    return rows * s.nb >= (single_block_rows(s, nnzb) ? 40 : 100) * tiles_times_nb;
+}
+
+// What bwd_t takes, but for 16 rows a workgroup instead of 32: with these there are more workgroups and no more pieces.
+struct GenericBwdSplit {
+    int waves, waves_a_row, parts;   // of a workgroup, of them for the same rows; workgroups a block row
+};
+static GenericBwdSplit generic_bwd_split(const AttnShape& s, int nnzb) {
+    if (!many_short_rows(s, nnzb)) return {4, 4, s.bs == 64 ? 2 : 1};
+    const int wide = s.bs == 64 ? 2 : 1;
+    return single_block_rows(s, nnzb) ? GenericBwdSplit{s.bs == 16 ? 2 : wide, s.bs == 16 ? 2 : 1, 1} : GenericBwdSplit{2 * wide, 2, 1};
+}
+
 // Workgroups of the generic backward that run at once: two (fp32) or three waves a SIMD.
 static long long generic_bwd_resident(bool is_bf16, int waves) { return 256 * 4 * (is_bf16 ? 3 : 2) / waves; }
 
@@ -820,14 +841,15 @@ static void generic_bwd_decide(RowCut& cut, const AttnShape& s, int nnzb, int pa
     if (cut.slots < 2) cut.slots = 0;
 }
 
-// Pieces of long rows per head, at most: with 16 rows a workgroup instead of 32 there are more of them and no more pieces.
+// Pieces of long rows per head, at most.
 static int bwd_row_slots(const AttnShape& s, int nnzb) {
     RowCut cut;
     if (s.is_bf16 && s.bs > 16) {
         cut.decide(s, nnzb, bwd_steps_per_slot(s.BH, s.bs, s.nb, nnzb));
         return cut.slots;
     }
-    generic_bwd_decide(cut, s, nnzb, s.bs == 64 ? 2 : 1, generic_bwd_resident(s.is_bf16, 4));
+    const GenericBwdSplit split = generic_bwd_split(s, nnzb);
+    if (split.waves_a_row > 1) generic_bwd_decide(cut, s, nnzb, split.parts, generic_bwd_resident(s.is_bf16, split.waves));
     return cut.slots;
 }
 
@@ -838,17 +860,6 @@ bool attn_bwd_grids_fit(int BH, int bs, int nb, int nnzb) {
     const int64_t limit = 0x7fffffffll, parts = bs == 64 ? 2 : 1;
     return (int64_t)(ws.w_max + nb) * BH * parts + 24 <= limit &&
            (int64_t)(nb > kChunk ? nnzb / (kChunk + 1) : 0) * BH * (bs / 16) <= limit;   // rows of cut columns
-}
-
-// Rows with hardly more than one block each (the diagonal): no long chain to cut anywhere.
-static bool single_block_rows(const AttnShape& s, int nnzb) { return 2 * (long long)nnzb < 3 * (long long)s.nb; }
-
-// Whether a call has many block rows for every tile of its average row: 100.  Measured (fp32, and bf16 / block 16;
-// patterns with a few long rows and columns, 2.4 to 9.6 blocks per row) the backward's crossing lies between 75
-// and 200; without long rows it comes earlier, at 40 with the diagonal alone.
-static bool many_short_rows(const AttnShape& s, int nnzb) {
-    const long long rows = (long long)s.BH * s.nb, tiles_times_nb = (long long)nnzb * (s.bs / 16);   // of one head
-    return rows * s.nb >= (single_block_rows(s, nnzb) ? 40 : 100) * tiles_times_nb;
 }
 
 // 16 rows a workgroup (32: half the tile traffic) until there are enough of them anyway: a row of many blocks is
@@ -924,6 +935,8 @@ static hipError_t launch_fwd(const AttnShape& s, const void* Q, const void* K, c
 
 // The query side's rows that are cut, with the steps of both sides.  Backward kernel, fp32, block 32: 2 heads x 8192, 3 %, rows of
 // 80 blocks, 125 -> 61.8 us; 4 x 4096, 5 %, 61.6 -> 52.8; block 16, 2 x 2048, 8 %, 26.4 -> 21.3; patterns that are left whole, the same.
+// Where two waves share a row (many_short_rows) its chain is twice as long: bf16, block 16, 9 x 1936, 8 %, rows of 65 blocks, 29.2 -> 26.5; fp32, block 16,
+// 10 x 1408, 8 %, 35.1 -> 32.8; with rows that did not set the time 54.1 -> 54.6 (10 x 3200, 6 %), 22.2 -> 22.5 (12 x 1280, 10 %).
 static RowCut generic_bwd_cut(const AttnShape& s, const BwdWorkspace& ws, int parts, long long resident, void* workspace) {
     RowCut cut;
     if (!s.bwd_room) return cut;
@@ -974,7 +987,7 @@ static hipError_t launch_bwd(const AttnShape& s, const void* Q, const void* K, c
         return hipGetLastError();
     };
     if (grid <= 0) return hipSuccess;
-    if constexpr (S::WT > 2) {
+    if constexpr (S::WT > 1) {
         const RowCut cut = rows ? generic_bwd_cut(s, ws, S::PARTS, resident, workspace) : RowCut{};
         if (cut.slots && grid + cut.groups <= 0x7fffffffll) return launch(attn_bwd_kernel<T, BS, S, true>, cut, cut.groups);
     }

@@ -180,6 +180,19 @@ def test_long_rows_in_pieces_of_the_generic_kernels(sp, dtype, block, BH, nb, lo
     _attention(sp, Q, K, V, dO, fl, block, dtype, [0, BH - 1], flags=sp.SPION_ATTN_PAPER_DENOM if denom else 0)
 
 
+# Many block rows of few tiles, whose rows two waves share in the backward: long ones in pieces all the same
+@pytest.mark.parametrize("dtype,block,BH,nb", [("bf16", 16, 9, 121), ("f32", 16, 9, 121), ("f32", 32, 12, 130), ("f32", 64, 24, 130)])
+def test_long_rows_in_pieces_where_two_waves_share_one(sp, dtype, block, BH, nb):
+    rng = np.random.default_rng(nb + BH)
+    Q, K, V, dO = [np.repeat(si.round_to_dtype(rng.standard_normal((1, nb * block, 64), dtype=np.float32), dtype), BH, 0) for _ in range(4)]
+    fl = np.eye(nb, dtype=np.uint8) | np.eye(nb, k=1, dtype=np.uint8)
+    for r, n in zip((nb - 1, 0, 7), (nb, 65, 44)):
+        fl[r] = 0
+        fl[r, rng.choice(nb, n, replace=False)] = 1
+    fl[5] = 0
+    _attention(sp, Q, K, V, dO, fl, block, dtype, [BH - 1])
+
+
 # bf16, block 16: rows are cut above 120 block rows where more workgroups than run at once (1024), above 150 where they all do
 @pytest.mark.parametrize("BH,nb,cut", [(8, 128, False), (9, 120, False), (9, 121, True), (2, 150, False), (2, 151, True), (6, 170, True)])
 def test_long_rows_of_block_16(sp, BH, nb, cut):
