@@ -76,12 +76,13 @@ struct TileLoadLane {
         }
     }
 };
+// Buffer loads: a scalar base and the lane's offset, where a global load into LDS takes a 64-bit vector addition each.
 __device__ __forceinline__ void tile_load_async(const bf16_t* __restrict__ src, bf16_t* tile, int wave,
                                                 const TileLoadLane& tl) {
+    const __amdgpu_buffer_rsrc_t from = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(src), (short)0, 0x7fffffff, 0x00027000);
 #pragma unroll
     for (int k = 0; k < 2; ++k)
-        __builtin_amdgcn_global_load_lds(reinterpret_cast<const char*>(src) + tl.off[k],
-                                         (lds_void_ptr)(tile + (2 * wave + k) * 512), 16, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(from, (lds_void_ptr)(tile + (2 * wave + k) * 512), 16, tl.off[k], 0, 0, 0);
 }
 
 // Per-lane read offsets into such a tile (in elements), fixed for the whole kernel.
@@ -101,22 +102,6 @@ struct SwzLane {
     }
     __device__ __forceinline__ int tr(int dt) const { return tr_row + ((((dt << 1) | tr_b) ^ tr_sw) << 3); }
 };
-
-// acc[dt][i] (d = 16 dt + 4 g + i, owned row r) += sum over the tile's rows of
-// tile[row][16 dt + ...] * x[row][r], the tile in the permuted-slot layout.
-template <int BS>
-__device__ __forceinline__ void mma_over_rows_swz(f32x4 (&acc)[4], const bf16_t* tile,
-                                                  const bf16x4 (&x)[BS / 16], const SwzLane& sl) {
-#pragma unroll
-    for (int pc = 0; pc < BS / 32; ++pc) {
-        const bf16x8 xf = join(x[2 * pc], x[2 * pc + 1]);
-#pragma unroll
-        for (int dt = 0; dt < 4; ++dt) {
-            const int o = sl.tr(dt) + pc * 32 * kD;
-            acc[dt] = mma_d(acc[dt], join(lds_read_tr(tile + o), lds_read_tr(tile + 16 * kD + o)), xf);
-        }
-    }
-}
 
 // Write this wave's 16 owned rows x 64 columns (accumulators in the transposed layout: lane (r, g)
 // holds columns 16 dt + 4 g .. + 3 of row r) as whole 128-byte rows, 16 bytes per lane, instead of
