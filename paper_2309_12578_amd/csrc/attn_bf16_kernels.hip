@@ -107,7 +107,6 @@ __device__ __forceinline__ void attend(
     if (n > 0) issue(sm1, col_at(1));   // (a one-block row loads its block twice: keeps the wait below uniform)
 
     float m = kLowest;   // what the row's exponentials are taken against, log2 units (score * scale * log2 e)
-    float limit = -INFINITY;   // m + kRescaleSlack
     f32x4 lacc = f32x4{0.f, 0.f, 0.f, 0.f};   // running row sum, replicated in its 4 elements
     f32x4 oacc[4];
 #pragma unroll
@@ -147,31 +146,43 @@ __device__ __forceinline__ void attend(
             vop[j] = join(lds_read_tr(cur.v + o), lds_read_tr(cur.v + 16 * kD + o));
         }
         __builtin_amdgcn_sched_barrier(0);
-        float mx = s[0][0];
+        bf16x4 pq[NKT];
+        f32x4 sums;
+        // row sums on the MFMA pipe: a tile of ones times P^T adds up each owned row's probabilities
+        // (the bf16 values that also enter P V), every accumulator element holding the same sum
+        auto probabilities = [&]() {
 #pragma unroll
-        for (int kt = 0; kt < NKT; ++kt)
+            for (int kt = 0; kt < NKT; ++kt) {
+                f32x4 p;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) mx = fmaxf(mx, s[kt][i]);
-        if (__any(mx * scale_log2 > limit)) {   // always at step 0
-            const float m_new = fmaxf(m, group_max(mx) * scale_log2);
+                for (int i = 0; i < 4; ++i) p[i] = fast_exp2(fmaf(s[kt][i], scale_log2, -m));
+                pq[kt] = to_quad<bf16_t>(p);
+            }
+            sums = lacc;
+#pragma unroll
+            for (int pc = 0; pc < BS / 32; ++pc) sums = mma_d(sums, ones, join(pq[2 * pc], pq[2 * pc + 1]));
+        };
+        if (it > 0) probabilities();
+        // A sum out of bounds tells of a score far above the reference (or NaN): the row takes a higher one and the block's exponentials
+        // are taken again.  The step is bound by the issue of vector and matrix instructions (57 of the former and 18 of the latter a
+        // wave, 590 clocks at four waves a SIMD, 485 without its loads); the maximum of all scores was 16 of the 57.  32 heads x 4096, block 64,
+        // 13 blocks a row 42.0 -> 39.8 us, 16 x 16320 80.4 -> 77.4; block 32, 64 x 1024, 25 %, 18.7 -> 17.5.
+        if (it == 0 || __any(!(sums[0] <= kSumLimit))) {
+            float mx = s[0][0];
+#pragma unroll
+            for (int kt = 0; kt < NKT; ++kt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) mx = fmaxf(mx, s[kt][i]);
+            float m_new = fmaxf(m, group_max(mx) * scale_log2);
+            if (lacc[0] > 1.f) m_new = fmaxf(m_new, m + log2f(lacc[0]));   // a sum that many blocks have added up to
             const float alpha = fast_exp2(m - m_new);
             m = m_new;
-            limit = m_new + kRescaleSlack;
             lacc *= alpha;
 #pragma unroll
             for (int dt = 0; dt < 4; ++dt) oacc[dt] *= alpha;
+            probabilities();
         }
-        bf16x4 pq[NKT];
-#pragma unroll
-        for (int kt = 0; kt < NKT; ++kt) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) s[kt][i] = fast_exp2(fmaf(s[kt][i], scale_log2, -m));
-            pq[kt] = to_quad<bf16_t>(s[kt]);
-        }
-        // row sums on the MFMA pipe: a tile of ones times P^T adds up each owned row's probabilities
-        // (the bf16 values that also enter P V), every accumulator element holding the same sum
-#pragma unroll
-        for (int pc = 0; pc < BS / 32; ++pc) lacc = mma_d(lacc, ones, join(pq[2 * pc], pq[2 * pc + 1]));
+        lacc = sums;
 #pragma unroll
         for (int j = 0; j < NM; ++j) {
             const int pc = j >> 2;
@@ -237,7 +248,7 @@ __device__ __forceinline__ void attend(
 }
 
 template <int BS, bool BESIDE, bool CUT>
-__global__ __launch_bounds__(BS * 4) void attn_fwd_bf16_kernel(
+__global__ __launch_bounds__(BS * 4, BS == 64 ? 4 : 5) void attn_fwd_bf16_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     bf16_t* __restrict__ O, float* __restrict__ LSE, const int* __restrict__ row_ptr,
     const int* __restrict__ col_idx, HeadRows<BESIDE> at, CutOf<CUT> cut, int L, int nb, int total, int sort_rows,

@@ -24,11 +24,13 @@ constexpr float kLowest = -3.4028234663852886e38f;
 // How far (in log2 units) a score may lie above the value its row's exponentials are taken against before the
 // running sums are rescaled.  P = exp2(s - m) above 1 is as exact as below (it keeps its relative
 // error, the fp32 sums have range to spare), so what a row's maximum does inside this slack need not be
-// known: a lane looks at its own scores only, and the reduction over the lanes of a row, the rescaling and
-// the branch are left to the first block of a row and to scores that really run away.
+// known: the generic kernels look at a lane's own scores only, the tuned forward at the running sum, which no score can be out of
+// bounds without passing; the reduction over the lanes of a row, the rescaling and the branch are left to the first block
+// of a row and to scores that really run away.
 // The sums hold up to 2^kRescaleSlack times what they would against the row's maximum: |V| above about 1e29 can
 // overflow them.
 constexpr float kRescaleSlack = 30.f;
+constexpr float kSumLimit = 1073741824.f;   // 2^kRescaleSlack
 
 // Per element type: a 16-byte lane fragment of EPL elements; four lane groups make a chunk of KC
 // contraction elements along d.

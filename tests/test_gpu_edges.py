@@ -112,6 +112,30 @@ def test_forward_scores_that_run_away_from_the_first_block(sp, block):
     assert np.abs(LSE.cpu().numpy().reshape(BH, L) - rLSE).max() <= 1e-3 * np.abs(rLSE).max()
 
 
+@pytest.mark.parametrize("block", [32, 64])
+def test_forward_sums_that_add_up_beyond_their_bound(sp, block):
+    """Every block but a row's first scores 14.6 above it, 2^21 times the probability: no score is out of bounds, the running
+    sum (2^26 or 2^27 a block) passes 2^30 after 8 to 16 blocks, and the row goes on against a reference above all its scores."""
+    nb, BH, d = 32, 1, 64                                   # as many block rows as no row is cut with
+    L = nb * block
+    rng = np.random.default_rng(block)
+    Q, K, V = [rng.standard_normal((BH, L, d), dtype=np.float32) for _ in range(3)]
+    Q[:, :, 0] = 8.0
+    K[:, :, 0] = 14.6
+    K[:, :block, 0] = 0.0                                   # where block row 0 starts; row 2 starts high
+    Q, K, V = [si.round_to_dtype(t, "bf16") for t in (Q, K, V)]
+    fl = np.eye(nb, dtype=np.uint8)
+    fl[0, :] = 1
+    fl[2, 0:30] = 1
+    from test_gpu_parity import _pattern_from_mask
+    q, k, v = [torch.from_numpy(t).cuda().to(torch.bfloat16).view(1, BH, L, d) for t in (Q, K, V)]
+    O, LSE = sp.attn_fwd(q, k, v, _pattern_from_mask(sp, fl, block))
+    rO, rLSE = oracle.attn_fwd(Q, K, V, oracle.upsample(fl, block))
+    x = O.float().cpu().numpy().reshape(BH, L, d)
+    assert np.linalg.norm(x - rO) <= 2e-2 * np.linalg.norm(rO) and np.abs(x - rO).max() <= 2e-2 * np.abs(rO).max()
+    assert np.abs(LSE.cpu().numpy().reshape(BH, L) - rLSE).max() <= 1e-3 * np.abs(rLSE).max()
+
+
 def test_forward_more_rows_than_run_at_once(sp):
     # 130 x 16 workgroups of block 32: rows are started in the order of their length class, long ones first
     nb, BH, block, d = 130, 16, 32, 64
