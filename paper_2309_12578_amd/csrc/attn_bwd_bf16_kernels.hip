@@ -291,16 +291,18 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
 
     const TileLoadLane tlo(wave, lane, out_row);
     // six tile loads per wave, plus one 4-byte-per-lane load of LSE in wave 0
-    auto issue = [&](bf16_t* qt, bf16_t* dt_, bf16_t* ot, float* lse_s, int I) {
-        tile_load_async(Q + head + (size_t)I * BS * in_row, qt, wave, tl);
-        tile_load_async(dO + out_head + (size_t)I * BS * out_row, dt_, wave, tlo);
+    auto load_q = [&](bf16_t* qt, int I) { tile_load_async(Q + head + (size_t)I * BS * in_row, qt, wave, tl); };
+    auto load_do = [&](bf16_t* dt_, int I) { tile_load_async(dO + out_head + (size_t)I * BS * out_row, dt_, wave, tlo); };
+    auto load_o = [&](bf16_t* ot, float* lse_s, int I) {
         tile_load_async(O + out_head + (size_t)I * BS * out_row, ot, wave, tlo);
         if (wave == 0 && lane < BS)
             __builtin_amdgcn_global_load_lds(LSE + vec + (size_t)I * BS + lane, (lds_void_ptr)lse_s, 4, 0, 0);
     };
     int Inext = 0;   // block row of step it + 1
     if (n > 0) {
-        issue(ta0, tb0, tc0, lse0, row_at(0));
+        load_q(ta0, row_at(0));
+        load_do(tb0, row_at(0));
+        load_o(tc0, lse0, row_at(0));
         Inext = row_at(1);
     }
     // owned K / V fragments (step 0 waits for everything issued up to here)
@@ -322,8 +324,18 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
                     bf16_t* nq, bf16_t* nd, bf16_t* no, float* nlse, int it) {
         // everyone's part of block `it` has landed and the other stage is no longer read
         tiles_ready(false);
-        if (it + 1 < n) issue(nq, nd, no, nlse, Inext);
-        Inext = row_at(it + 2);
+        // Block 64: the next tiles are requested in three places.  All at once they hold every wave of the workgroup up until the
+        // memory pipeline has taken 24 KB: key side of 32 heads x 4096, 13 and 38 blocks a row, 83.2 -> 80.4 and 213.7 -> 205.9 us; with
+        // block 32, half of that, the steps are too short for it (62.7 -> 63.5).
+        constexpr bool kSpread = BS == 64;
+        const bool more = it + 1 < n;
+        if (more) {
+            load_q(nq, Inext);
+            if (!kSpread) {
+                load_do(nd, Inext);
+                load_o(no, nlse, Inext);
+            }
+        }
         // delta of the 16 query rows 16 wave .. + 15: the diagonal of dO O^T; stored negated, it seeds
         // the dP accumulators below.  Wave 0 also turns LSE into log2 units.
         {
@@ -339,6 +351,7 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
             if (wave == 0 && lane < BS) lse_s[lane] *= kLog2e;
         }
         lds_barrier();
+        if (kSpread && more) load_do(nd, Inext);
         // 32 query rows at a time: S and dP of two 16-row tiles, then their share of dV and dK, so that
         // only two tiles' worth of P and dS are live; LDS operands are requested one MFMA group ahead
         bf16x8 fq[2], fd[2];
@@ -381,6 +394,7 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
                 pq[h] = to_quad<bf16_t>(p);
                 dsq[h] = to_quad<bf16_t>(ds);
             }
+            if (kSpread && pc == 0 && more) load_o(no, nlse, Inext);
             // dV^T[d][key] += dO^T P and dK^T[d][key] += Q^T dS for these 32 rows, interleaved
             const bf16x8 pf = join(pq[0], pq[1]), dsf = join(dsq[0], dsq[1]);
             bf16x8 ring[2];
@@ -393,6 +407,7 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
                 else dv[j >> 1] = mma_d(dv[j >> 1], ring[j & 1], pf);
             }
         }
+        Inext = row_at(it + 2);
     };
 
     for (int it = 0; it < n; it += 2) {
