@@ -81,6 +81,39 @@ def test_quantile_of_large_grids(sp, nb, kind, q):
     assert np.array_equal(fl.cpu().numpy().astype(bool), want) and int(nnzb.item()) == want.sum()
 
 
+# The first of the two ordered sums is taken in any order while the magnitudes stay below 2^53: just below, at and above it, with
+# odd numbers behind a large one (which round in the ordered sum), of both signs; the waves that have rows, all of them
+@pytest.mark.parametrize("nb", [1, 4, 5, 16, 63, 64])
+@pytest.mark.parametrize("kind", ["below", "at", "above", "signed", "signed above", "huge"])
+def test_mean_and_std_of_pools_around_the_bound_of_exact_sums(sp, nb, kind):
+    rng = np.random.default_rng(nb)
+    n = nb * nb
+    pool = rng.integers(1, (1 << 53) // n, n) | 1
+    total = (1 << 53) + {"below": -1, "at": 0, "above": 1 + n // 2}.get(kind, 0)
+    if kind in ("below", "at", "above"):
+        pool[0] += total - int(pool.sum())
+    elif kind == "huge":
+        pool = rng.integers(-(1 << 61), 1 << 61, n) | 1
+    else:
+        pool *= rng.choice((-1, 1), n)
+        pool[0] += (1 << 53) - int(np.abs(pool).sum()) - 1 if kind == "signed" else (1 << 53)
+    s = q = 0.0
+    for x in pool.tolist():
+        s += float(x)
+    mean = s / n
+    for x in pool.tolist():
+        q += (float(x) - mean) ** 2
+    t = mean + 0.5 * float(np.sqrt(q / n))
+    dev = torch.from_numpy(pool.reshape(nb, nb)).cuda()
+    z = lambda m, t=torch.int32: torch.zeros(m, dtype=t, device="cuda")
+    fl, nnzb = z((nb, nb), torch.uint8), z(1)
+    ws = torch.empty(sp.spion_pattern_workspace_bytes(nb * 16, 16), dtype=torch.uint8, device="cuda")
+    sp.spion_pattern(None, nb * 16, 16, 1, sp.SPION_T_MEAN_KSTD, 0.5, fl, z(nb + 1), z(n), z(nb + 1), z(n), z(n), nnzb, dev, ws,
+                     flags=sp.SPION_PATTERN_FROM_POOL | sp.SPION_PATTERN_NO_FILL)
+    want = (pool.astype(np.float64).reshape(nb, nb) > t) | np.eye(nb, dtype=bool)
+    assert np.array_equal(fl.cpu().numpy().astype(bool), want) and int(nnzb.item()) == want.sum()
+
+
 def _attention(sp, Q, K, V, dO, fl, block, dtype, heads, flags=0):
     """Relative errors (2-norm and max) of O, dQ, dK, dV of the given heads against the fp64 oracle."""
     from test_gpu_parity import _run_attention_case
