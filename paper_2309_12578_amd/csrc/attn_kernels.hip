@@ -1020,13 +1020,14 @@ static hipError_t bwd_t(const AttnShape& s, const void* Q, const void* K, const 
     } else {
         const BwdWorkspace ws(s.BH, s.bs, s.nb, nnzb, kChunk, s.nb / 8, bwd_row_slots(s, nnzb));
         auto* launch = launch_bwd<T, BS, SplitFew<T, BS>>;
-        // 16 rows or keys a workgroup instead of 32 while those of 32 would be at most a quarter more than run at once (512 of
-        // four waves): the compute units they leave idle are worth more than the tiles' second reading.  fp32, backward kernel, block 32: 2 heads x
-        // 512, 20 %, 20.3 -> 14.5 us; 2 x 2048, 10 %, 35.0 -> 26.4, 4 x 2048 39.1 -> 34.3; block 64: 1 x 4096 57.3 -> 42.5, 8 x 1024, 20 %, 38.6 -> 36.4;
-        // beyond, 3 x 4096, block 64 (918 workgroups of 32) 72.1 -> 76.9, 16 x 1024, block 32 (1120) 34.3 -> 38.4; with few block rows
-        // there is no long chain to shorten: 18 x 384, block 64, 20.4 -> 21.7, 8 x 512 15.4 -> 17.2.
+        // 16 rows or keys a workgroup instead of 32 while there are at most 800 of 32, of which 512 (of four waves) run at once: the compute
+        // units that the second, short round of them leaves idle are worth more than the tiles' second reading.  fp32, backward kernel, 32 -> 16 rows,
+        // block 32: 2 heads x 512, 20 %, 20.3 -> 14.5 us; 2 x 2048, 10 %, 35.0 -> 26.4, 4 x 2048 39.1 -> 34.3; block 64: 1 x 4096 57.3 -> 42.5.
+        // Where the line lies: 34 shapes of 640 to 800 take 1.13 of the time with 32 rows (0.90 to 1.46: block 64, 4 x 2816 52.4 -> 35.7, 5 x 2048,
+        // 15 %, 65.2 -> 52.1; block 32, 8 x 1344 43.1 -> 32.7, 4 x 2464 39.4 -> 43.6), 13 of 800 to 920 1.02 (0.86 to 1.36), beyond that 0.8 to 1.0.  With few
+        // block rows there is no long chain to shorten: 18 x 384, block 64, 20.4 -> 21.7, 8 x 512 15.4 -> 17.2.
         if constexpr (BS > 16)
-            if (s.nb >= 16 && (long long)s.BH * (ws.w_max + s.nb) * (BS / 32) * 4 <= 5 * 512) launch = launch_bwd<T, BS, Split<T, BS, 1, 4, 1>>;
+            if (s.nb >= 16 && (long long)s.BH * (ws.w_max + s.nb) * (BS / 32) <= 800) launch = launch_bwd<T, BS, Split<T, BS, 1, 4, 1>>;
         if (many_short_rows(s, nnzb))
             launch = single_block_rows(s, nnzb) ? launch_bwd<T, BS, typename SplitMany<T, BS>::bwd_single>
                                                                : launch_bwd<T, BS, typename SplitMany<T, BS>::bwd>;

@@ -250,6 +250,19 @@ def test_long_rows_in_pieces_where_two_waves_share_one(sp, dtype, block, BH, nb)
     _attention(sp, Q, K, V, dO, fl, block, dtype, [BH - 1])
 
 
+# fp32 backward, 16 rows a workgroup up to 800 workgroups of 32 rows (block rows, columns and chunks of all heads), 32 beyond: both sides of
+# the line, with a row and a column that are cut
+@pytest.mark.parametrize("block,BH,nb", [(32, 10, 38), (32, 11, 38), (32, 12, 38), (64, 5, 38), (64, 6, 38)])
+def test_backward_around_the_line_of_16_and_32_rows(sp, block, BH, nb):
+    rng = np.random.default_rng(nb + BH)
+    Q, K, V, dO = [np.repeat(rng.standard_normal((1, nb * block, 64), dtype=np.float32), BH, 0) for _ in range(4)]
+    fl = np.eye(nb, dtype=np.uint8)
+    fl[3] = 1
+    fl[:, 7] = 1
+    fl[5] = 0
+    _attention(sp, Q, K, V, dO, fl, block, "f32", [BH - 1])
+
+
 # bf16, block 16: rows are cut above 120 block rows where more workgroups than run at once (1024), above 150 where they all do
 @pytest.mark.parametrize("BH,nb,cut", [(8, 128, False), (9, 120, False), (9, 121, True), (2, 150, False), (2, 151, True), (6, 170, True)])
 def test_long_rows_of_block_16(sp, BH, nb, cut):
