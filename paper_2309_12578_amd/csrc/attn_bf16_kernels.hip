@@ -295,12 +295,9 @@ static int fwd_resident(int bs) { return 256 * (bs == 64 ? 4 : 8); }
 // with two long rows): 8 heads x 8192, block 32, rows of 121 blocks, 41.9 / 20.1; 4 x 16384, block 64, 65.5 / 29.2; 4 x 8192, block 64, rows of
 // 71, 37.6 / 20.9; 1 x 4096, block 32, 17.1 / 10.8; 16 x 16320, block 64, rows of 112, 83.1 / 78.1.  Rows of 45 and 27 at 64 x 4160 and 128 x 2080,
 // block 32, which the rule leaves whole, 38.6 / 40.5 and 38.5 / 41.9.  A pattern without long rows: 76.6 / 76.9, 14.7 / 14.8.
-// With 33 to 64 block rows, where all of them run at once (short_too) and nothing hides the longest, rows of twice the mean are cut:
+// short_too: rows of twice the mean are cut, where nothing hides the longest (the callers' rules).  33 to 64 block rows that all run at once:
 // 8 x 2048, block 32, rows of 24 blocks, 11.2 / 9.5; 32 x 2048 19.3 / 16.6; 4 x 4096, block 64, 16.7 / 13.1; 16 x 4096, 10 %, 26.1 / 19.9; 2 x 4096,
-// 15 %, 20.8 / 13.7; without long rows 14.9 / 14.6.  Over 150 shapes of 33 to 256 block rows, the cut ones take 0.35 to 1.05 of the time uncut (0.81 on
-// average above 64 block rows, 0.96 up to there), but 1.15 at 45 heads x 4096, block 32, rows of 54 and 38, where two helpers a head are few.
-// The line at 64 block rows is not where twice the mean stops paying: of 36 shapes of 80 to 255 block rows that all run at once it would
-// take 0.59 to 0.85 of the time in 20, as long (at most 1.01) in the others (2 x 8192, block 64, 10 %, 28.6 / 17.0; 8 x 4096, block 32, 20 %, 28.2 / 19.4).
+// 15 %, 20.8 / 13.7; without long rows 14.9 / 14.6.
 void RowCut::decide(const AttnShape& s, int nnzb, long long steps, bool short_too) {
     // Up to 64 block rows a row is not that long, and what the others pay shows: a kernel of 45 us without a row to cut, 32 heads x
     // 4096, block 64, took 1 us longer.
@@ -321,7 +318,14 @@ RowCut::RowCut(const AttnShape& s, int nnzb) {
     if (!s.is_bf16 || s.bs == 16) {
         *this = generic_fwd_cut(s, nnzb);
     } else {
-        decide(s, nnzb, (long long)s.BH * nnzb / fwd_resident(s.bs), s.nb <= 64 && s.BH * s.nb <= fwd_resident(s.bs));
+        // Rows of twice the mean are cut too up to 64 block rows if all rows run at once (33 x 2240, block 64, of which 1155 do not, 19.8 / 20.9),
+        // above if at most two rounds of them run and the mean is 7 blocks: short rows are no chain to speak of, and helpers
+        // that find nothing to do are not free (3 x 5472, block 32, 6.8 blocks a row, 13.9 / 14.5; 9 x 4064, 6.0, 14.6 / 14.9).  The others, 40 of 100 shapes
+        // of 65 to 255 block rows, take 0.57 to 1.01 of the time uncut, 0.83 on average: 2 x 10176, block 64, 17.9 blocks a row, 40.2 / 22.9; 4 x 7488,
+        // block 32, 43.7, 48.0 / 30.5; of two rounds 9 x 7424, block 64, 20.5, 45.3 / 39.5, 24 x 3424, block 32, 20.4, 31.6 / 27.7, 16 x 6528, block 64, 40.7 / 39.4.
+        const long long all = (long long)s.BH * s.nb, at_once = fwd_resident(s.bs);
+        const bool short_too = s.nb <= 64 ? all <= at_once : all <= 2 * at_once && nnzb >= 7 * s.nb;
+        decide(s, nnzb, (long long)s.BH * nnzb / at_once, short_too);
         helpers = s.BH <= 8 ? 16 : s.BH < 128 ? 128 / s.BH : 1;
         if (helpers >= slots) helpers = slots > 0 ? slots - 1 : 0;
         groups = (s.BH * helpers + 7) & ~7;

@@ -462,10 +462,20 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
 // The query side's rows that are cut: the forward's rule, with the steps of both sides (so few heads, and a helper for each
 // piece).  Backward, us, uncut / cut / a pattern without long rows: 8 heads x 8192, block 32, rows of 121 blocks, 73.5 / 46.7 / 47.5;
 // 4 x 16384, block 64, 112 / 70.5 / 70.3; 4 x 8192, block 64, rows of 71, 65.3 / 39.5 / 40.2; 1 x 4096, block 32, 21.1 / 17.8 / 17.9.
+// From a mean of 8 blocks on, rows of twice the mean: 1 x 10176, block 64, 21.3 blocks a row, 67.3 / 32.9; 3 x 8128, block 32, 33.8, 74.2 / 50.0; 2 x 4800, block
+// 64, 10.5, 28.6 / 25.0; of 37 such shapes none takes longer than 1.015 of the time.  Below, 0.99 to 1.03 (16 x 3648, block 64, 5.3 blocks, 31.1 / 32.0).
+static void decide_row_cut(RowCut& cut, const AttnShape& s, int nnzb) {
+    cut.decide(s, nnzb, bwd_steps_per_slot(s.BH, s.bs, s.nb, nnzb), nnzb >= 8 * s.nb);
+}
+int bwd_bf16_row_slots(const AttnShape& s, int nnzb) {
+    RowCut cut;
+    decide_row_cut(cut, s, nnzb);
+    return cut.slots;
+}
 static RowCut row_cut(const AttnShape& s, const BwdWorkspace& ws, void* workspace) {
     RowCut cut;
     if (!s.bwd_room) return cut;
-    cut.decide(s, ws.nnzb, bwd_steps_per_slot(s.BH, s.bs, s.nb, ws.nnzb));
+    decide_row_cut(cut, s, ws.nnzb);
     if (cut.slots == 0) return cut;
     cut.helpers = cut.slots - 1;
     if ((long long)s.BH * (cut.helpers + s.nb + ws.w_max) > 0x7fffffffll) return RowCut{};   // workgroups of a launch

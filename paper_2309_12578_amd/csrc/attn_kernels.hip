@@ -843,11 +843,8 @@ static void generic_bwd_decide(RowCut& cut, const AttnShape& s, int nnzb, int pa
 
 // Pieces of long rows per head, at most.
 static int bwd_row_slots(const AttnShape& s, int nnzb) {
+    if (s.is_bf16 && s.bs > 16) return bwd_bf16_row_slots(s, nnzb);
     RowCut cut;
-    if (s.is_bf16 && s.bs > 16) {
-        cut.decide(s, nnzb, bwd_steps_per_slot(s.BH, s.bs, s.nb, nnzb));
-        return cut.slots;
-    }
     const GenericBwdSplit split = generic_bwd_split(s, nnzb);
     if (split.waves_a_row > 1) generic_bwd_decide(cut, s, nnzb, split.parts, generic_bwd_resident(s.is_bf16, split.waves));
     return cut.slots;

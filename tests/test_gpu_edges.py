@@ -220,6 +220,30 @@ def test_long_rows_in_pieces(sp, block, BH, nb, longs, denom):
     _attention(sp, Q, K, V, dO, fl, block, "bf16", sorted({0, BH // 2, BH - 1}), flags=sp.SPION_ATTN_PAPER_DENOM if denom else 0)
 
 
+# bf16, above 64 block rows: the forward's rows of more than twice the mean are cut where the mean is 7 blocks and at most two rounds of
+# rows run (1024 or 2048 at once), if they outlast the launch as well; the backward's where the mean is 8.  Rows at the forward's line, one above
+# it, far above it and without a diagonal block; means on both sides of the lines, one round, two, one row more
+@pytest.mark.parametrize("block,BH,nb,mean", [(64, 1, 65, 8), (32, 3, 65, 7), (64, 3, 65, 6), (64, 21, 97, 8), (64, 22, 97, 8), (32, 41, 99, 9),
+                                              (32, 42, 99, 9), (32, 2, 255, 20)])
+def test_long_rows_in_pieces_where_rows_are_many_blocks(sp, block, BH, nb, mean):
+    rng = np.random.default_rng(nb + mean)
+    Q, K, V, dO = [np.repeat(si.round_to_dtype(rng.standard_normal((1, nb * block, 64), dtype=np.float32), "bf16"), BH, 0) for _ in range(4)]
+    longest = max(2 * mean, 2 * (BH * nb * mean // (1024 if block == 64 else 2048)))
+    lengths = np.full(nb, mean)
+    for r, n in ((0, longest), (nb - 1, longest + 1), (9, min(nb - 1, 3 * longest))):
+        lengths[r] = n
+    fewer = np.setdiff1d(np.arange(nb), (0, nb - 1, 9))
+    for i in range(lengths.sum() - nb * mean):   # the mean stays
+        lengths[fewer[i % len(fewer)]] -= 1
+    fl = np.zeros((nb, nb), dtype=np.uint8)
+    for r, n in enumerate(lengths):
+        cols = np.setdiff1d(np.arange(nb), r)
+        fl[r, rng.choice(cols, n - (r != 9), replace=False)] = 1
+        fl[r, r] = r != 9
+    assert fl.sum() == nb * mean
+    _attention(sp, Q, K, V, dO, fl, block, "bf16", [BH - 1])
+
+
 # The kernels of fp32 and of block size 16: a helper for each piece and part of a block row; 16 and 32 rows a workgroup; a row of more
 # pieces than there are helpers for stays whole; no diagonal block in a piece, an empty row beside them
 @pytest.mark.parametrize("dtype,block", [("f32", 16), ("f32", 32), ("f32", 64), ("bf16", 16)])
