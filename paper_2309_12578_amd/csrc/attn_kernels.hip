@@ -812,12 +812,21 @@ BwdWorkspace::BwdWorkspace(int BH, int bs, int nb, int nnzb_, int key_chunk, int
 // Rows with hardly more than one block each (the diagonal): no long chain to cut anywhere.
 static bool single_block_rows(const AttnShape& s, int nnzb) { return 2 * (long long)nnzb < 3 * (long long)s.nb; }
 
+// Block rows times rows of a head for every tile of its average row.
+static double short_rows(const AttnShape& s, int nnzb) { return (double)s.BH * s.nb * s.nb / ((double)nnzb * (s.bs / 16)); }
+
 // Whether a call has many block rows for every tile of its average row: 100.  Measured (fp32, and bf16 / block 16;
 // patterns with a few long rows and columns, 2.4 to 9.6 blocks per row) the backward's crossing lies between 75
 // and 200; without long rows it comes earlier, at 40 with the diagonal alone.
-static bool many_short_rows(const AttnShape& s, int nnzb) {
-    const long long rows = (long long)s.BH * s.nb, tiles_times_nb = (long long)nnzb * (s.bs / 16);   // of one head
-    return rows * s.nb >= (single_block_rows(s, nnzb) ? 40 : 100) * tiles_times_nb;
+static bool many_short_rows(const AttnShape& s, int nnzb) { return short_rows(s, nnzb) >= (single_block_rows(s, nnzb) ? 40 : 100); }
+
+// The backward's line of the larger blocks.  fp32, backward, many / few: the diagonal alone, 40 to 60 (10 shapes) 0.78 to 0.98 of the time with
+// the few's kernels (24 x 448, block 64, 23.5 / 18.3 us), 60 to 100 1.05 to 1.32 (33 x 576, block 64, 24.5 / 32.3); a few blocks besides, 50 to 117
+// 0.65 to 1.05 (16 shapes, 0.84 on average: 14 x 1280, block 64, 51.3 / 34.2; 36 x 192, block 32, 15.1 / 13.0); more, 100 to 143 0.67 to 1.13 (8 shapes, 0.84:
+// 14 x 1248, block 32, 48.9 / 32.6; 30 x 352, block 32, 19.4 / 21.9), 165 and 273 0.98 and 1.02.
+static bool many_short_rows_bwd(const AttnShape& s, int nnzb) {
+    if (s.bs == 16) return many_short_rows(s, nnzb);
+    return short_rows(s, nnzb) >= (10ll * nnzb < 11ll * s.nb ? 60 : single_block_rows(s, nnzb) ? 120 : 150);
 }
 
 // What bwd_t takes, but for 16 rows a workgroup instead of 32: with these there are more workgroups and no more pieces.
@@ -825,7 +834,7 @@ struct GenericBwdSplit {
     int waves, waves_a_row, parts;   // of a workgroup, of them for the same rows; workgroups a block row
 };
 static GenericBwdSplit generic_bwd_split(const AttnShape& s, int nnzb) {
-    if (!many_short_rows(s, nnzb)) return {4, 4, s.bs == 64 ? 2 : 1};
+    if (!many_short_rows_bwd(s, nnzb)) return {4, 4, s.bs == 64 ? 2 : 1};
     const int wide = s.bs == 64 ? 2 : 1;
     return single_block_rows(s, nnzb) ? GenericBwdSplit{s.bs == 16 ? 2 : wide, s.bs == 16 ? 2 : 1, 1} : GenericBwdSplit{2 * wide, 2, 1};
 }
@@ -1025,7 +1034,7 @@ static hipError_t bwd_t(const AttnShape& s, const void* Q, const void* K, const 
         // block rows there is no long chain to shorten: 18 x 384, block 64, 20.4 -> 21.7, 8 x 512 15.4 -> 17.2.
         if constexpr (BS > 16)
             if (s.nb >= 16 && (long long)s.BH * (ws.w_max + s.nb) * (BS / 32) <= 800) launch = launch_bwd<T, BS, Split<T, BS, 1, 4, 1>>;
-        if (many_short_rows(s, nnzb))
+        if (many_short_rows_bwd(s, nnzb))
             launch = single_block_rows(s, nnzb) ? launch_bwd<T, BS, typename SplitMany<T, BS>::bwd_single>
                                                                : launch_bwd<T, BS, typename SplitMany<T, BS>::bwd>;
         return launch(s, Q, K, V, O, dO, LSE, dQ, dK, dV, row_ptr, col_idx, col_ptr, row_idx, ws, workspace, st);

@@ -287,6 +287,17 @@ def test_backward_around_the_line_of_16_and_32_rows(sp, block, BH, nb):
     _attention(sp, Q, K, V, dO, fl, block, "f32", [BH - 1])
 
 
+# fp32 backward: on both sides of the lines from which few waves share a row: the diagonal alone, a few blocks besides, twice as many blocks as rows
+@pytest.mark.parametrize("block,nb,besides", [(32, 11, 0), (32, 13, 0), (64, 23, 0), (64, 25, 0), (32, 28, 7), (32, 32, 8), (32, 56, 56), (32, 64, 64)])
+def test_backward_around_the_lines_of_many_short_rows(sp, block, nb, besides):
+    rng = np.random.default_rng(nb)
+    BH = 10
+    Q, K, V, dO = [np.repeat(rng.standard_normal((1, nb * block, 64), dtype=np.float32), BH, 0) for _ in range(4)]
+    fl = np.eye(nb, dtype=np.uint8)
+    fl.reshape(-1)[rng.choice(np.flatnonzero(fl.reshape(-1) == 0), besides, replace=False)] = 1
+    _attention(sp, Q, K, V, dO, fl, block, "f32", [BH - 1])
+
+
 # bf16, block 16: rows are cut above 120 block rows where more workgroups than run at once (1024), above 150 where they all do
 @pytest.mark.parametrize("BH,nb,cut", [(8, 128, False), (9, 120, False), (9, 121, True), (2, 150, False), (2, 151, True), (6, 170, True)])
 def test_long_rows_of_block_16(sp, BH, nb, cut):
