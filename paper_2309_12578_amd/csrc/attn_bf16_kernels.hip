@@ -298,13 +298,17 @@ static int fwd_resident(int bs) { return 256 * (bs == 64 ? 4 : 8); }
 // short_too: rows of twice the mean are cut, where nothing hides the longest (the callers' rules).  33 to 64 block rows that all run at once:
 // 8 x 2048, block 32, rows of 24 blocks, 11.2 / 9.5; 32 x 2048 19.3 / 16.6; 4 x 4096, block 64, 16.7 / 13.1; 16 x 4096, 10 %, 26.1 / 19.9; 2 x 4096,
 // 15 %, 20.8 / 13.7; without long rows 14.9 / 14.6.
+// Pieces of the mean, of rows from half as long again on, where the mean is 10 blocks (`fine`; before 3/2 of it, from twice the mean on): forward, 45 shapes of 34 to
+// 255 block rows, 0.83 to 1.04 of the time, 0.93 on average (5 x 3008, block 32, 18.6 blocks a row, 15.7 / 13.2; 9 x 4096, block 64, 12.3, 20.7 / 17.5; 14 x
+// 4928, block 64, 35.8 / 37.2); the backward the same (0.96 to 1.02).  With means of 6 to 9, 0.91 to 1.29; block 16, 0.90 to 1.10.
 void RowCut::decide(const AttnShape& s, int nnzb, long long steps, bool short_too) {
     // Up to 64 block rows a row is not that long, and what the others pay shows: a kernel of 45 us without a row to cut, 32 heads x
     // 4096, block 64, took 1 us longer.
     if (s.nb <= (short_too ? 32 : 64)) return;
     const int mean = (nnzb + s.nb - 1) / s.nb;
-    piece = short_too ? (mean < 6 ? 8 : 3 * mean / 2) : (mean < 6 ? 12 : 2 * mean);
-    longest = short_too ? (mean < 6 ? 12 : 2 * mean) : (mean < 6 ? 24 : 4 * mean);
+    const bool fine = short_too && s.bs > 16 && mean >= 10;
+    piece = fine ? mean : short_too ? (mean < 6 ? 8 : 3 * mean / 2) : (mean < 6 ? 12 : 2 * mean);
+    longest = fine ? 3 * mean / 2 : short_too ? (mean < 6 ? 12 : 2 * mean) : (mean < 6 ? 24 : 4 * mean);
     if (s.bs == 16 && longest < 24) longest = 24;
     if (longest < 2 * steps) longest = 2 * steps < s.nb ? (int)(2 * steps) : s.nb;
     if (s.nb <= longest) return;   // no row can be cut

@@ -224,11 +224,11 @@ def test_long_rows_in_pieces(sp, block, BH, nb, longs, denom):
 # rows run (1024 or 2048 at once), if they outlast the launch as well; the backward's where the mean is 8.  Rows at the forward's line, one above
 # it, far above it and without a diagonal block; means on both sides of the lines, one round, two, one row more
 @pytest.mark.parametrize("block,BH,nb,mean", [(64, 1, 65, 8), (32, 3, 65, 7), (64, 3, 65, 6), (64, 21, 97, 8), (64, 22, 97, 8), (32, 41, 99, 9),
-                                              (32, 42, 99, 9), (32, 2, 255, 20)])
+                                              (32, 42, 99, 9), (32, 2, 255, 20), (64, 2, 65, 10)])
 def test_long_rows_in_pieces_where_rows_are_many_blocks(sp, block, BH, nb, mean):
     rng = np.random.default_rng(nb + mean)
     Q, K, V, dO = [np.repeat(si.round_to_dtype(rng.standard_normal((1, nb * block, 64), dtype=np.float32), "bf16"), BH, 0) for _ in range(4)]
-    longest = max(2 * mean, 2 * (BH * nb * mean // (1024 if block == 64 else 2048)))
+    longest = max(2 * mean if mean < 10 else 3 * mean // 2, 2 * (BH * nb * mean // (1024 if block == 64 else 2048)))
     lengths = np.full(nb, mean)
     for r, n in ((0, longest), (nb - 1, longest + 1), (9, min(nb - 1, 3 * longest))):
         lengths[r] = n
