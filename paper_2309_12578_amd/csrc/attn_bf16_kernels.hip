@@ -247,11 +247,14 @@ __device__ __forceinline__ void attend(
     if (g == 0) LSE[(size_t)bh * L + qrow] = lsum > 0.f ? (m + log2f(lsum)) * kLn2 : -INFINITY;
 }
 
+// In which order block rows start, see fwd_bf16().
+enum RowOrder { kAsTheyLie, kDealt, kByLength };
+
 template <int BS, bool BESIDE, bool CUT>
 __global__ __launch_bounds__(BS * 4, BS == 64 ? 4 : 5) void attn_fwd_bf16_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     bf16_t* __restrict__ O, float* __restrict__ LSE, const int* __restrict__ row_ptr,
-    const int* __restrict__ col_idx, HeadRows<BESIDE> at, CutOf<CUT> cut, int L, int nb, int total, int sort_rows,
+    const int* __restrict__ col_idx, HeadRows<BESIDE> at, CutOf<CUT> cut, int L, int nb, int heads, RowOrder order,
     float scale_log2, int paper_denom) {
     __shared__ __attribute__((aligned(16))) KvSmem<BS> sm0, sm1;
 
@@ -260,7 +263,7 @@ __global__ __launch_bounds__(BS * 4, BS == 64 ? 4 : 5) void attn_fwd_bf16_kernel
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int id = blockIdx.x;
     if constexpr (CUT) if (id < cut.groups) {   // pieces of long rows
-        const int all = total / nb * cut.helpers;
+        const int all = heads * cut.helpers;
         if (id >= all) return;
         const int l = xcd_deal(id, 0, all), bh = l / cut.helpers;
         for (int p = l % cut.helpers;; p += cut.helpers) {   // ends behind the head's last piece
@@ -273,17 +276,17 @@ __global__ __launch_bounds__(BS * 4, BS == 64 ? 4 : 5) void attn_fwd_bf16_kernel
         }
     }
     if constexpr (CUT) id -= cut.groups;
-    int bh, I;
-    if (sort_rows) {
-        const RowOfHead mine = rows_in_order<true>(row_ptr, nb, total / nb, id, lane, (total / nb & 7) == 0);
-        bh = mine.head;
-        I = mine.row;
+    ItemOfHead mine;
+    if (order == kAsTheyLie) {
+        const int vid = xcd_remap(id, heads * nb);
+        mine = {vid / nb, vid % nb};
     } else {
-        const int vid = xcd_remap(id, total);
-        bh = vid / nb;
-        I = vid % nb;
+        mine = deal_heads(id, heads, false);
+        if (mine.item >= nb) return;
+        if (order == kByLength) mine.item = row_by_length(row_ptr, nb, mine.item, lane);
     }
-    attend<BS, BESIDE, CUT, false>(Q, K, V, O, LSE, row_ptr, col_idx, at, cut, L, nb, scale_log2, paper_denom, sm0, sm1, bh, I, 0,
+    const int I = mine.item;
+    attend<BS, BESIDE, CUT, false>(Q, K, V, O, LSE, row_ptr, col_idx, at, cut, L, nb, scale_log2, paper_denom, sm0, sm1, mine.head, I, 0,
                               RowPieces{I, 1, 0, 0}, lane, wave);
 }
 
@@ -349,12 +352,20 @@ hipError_t fwd_bf16(const AttnShape& s, const void* Q, const void* K, const void
     const int total = s.nb * s.BH;
     RowCut cut;
     if (s.fwd_room) cut = RowCut(s, nnzb);
-    // where all workgroups run at once their order is immaterial, and finding a row by its rank costs one half a microsecond
-    const int sort_rows = total > fwd_resident(BS);
+    // Dealt (deal_heads) where a head's workgroups share tiles and are many; finding its row costs a workgroup a quarter of a
+    // microsecond.  As they lie / dealt: 16 heads x 4096, 8 %, 14.3 / 13.2 us, 28 x 1600 12.4 / 10.7, 9 x 6784 13.4 / 12.2; fewer, 24 x 1088, block 64,
+    // 5.7 / 6.0, 6 x 5376 7.4 / 7.7, 28 x 768, block 32, 5.1 / 5.6; the diagonal alone, 21 x 1984 5.0 / 5.6.  Longest first where more rows follow than run at once, or a row is six blocks on
+    // average: long ones then spread over the compute units.  Dealt / so: 6 x 7680, block 64, 30.3 / 26.0, 5 x 9472 26.3 / 22.7, 28 x 1984, block 32, 14.6 / 13.3; shorter
+    // rows, 16 x 4096 13.2 / 13.7, 64 x 1024, block 32, 10.2 / 10.5; up to 256 rows, one or none a compute unit, they are no faster.
+    const RowOrder order = total > fwd_resident(BS) || (total > 256 && nnzb >= 6 * s.nb) ? kByLength
+                           : total > (BS == 64 ? 512 : 768) && 2 * nnzb >= 3 * s.nb      ? kDealt
+                                                                                          : kAsTheyLie;
+    const long long grid = cut.groups + (order == kAsTheyLie ? total : dealt(s.BH, s.nb, false));
+    if (grid > 0x7fffffffll) return hipErrorInvalidValue;
     auto launch = [&](auto kernel, auto at, auto cut_arg) {
-        kernel<<<dim3((unsigned)(cut.groups + total)), dim3(BS * 4), 0, st>>>(
+        kernel<<<dim3((unsigned)grid), dim3(BS * 4), 0, st>>>(
             static_cast<const bf16_t*>(Q), static_cast<const bf16_t*>(K), static_cast<const bf16_t*>(V),
-            static_cast<bf16_t*>(O), LSE, row_ptr, col_idx, at, cut_arg, s.L, s.nb, total, sort_rows, s.scale * kLog2e,
+            static_cast<bf16_t*>(O), LSE, row_ptr, col_idx, at, cut_arg, s.L, s.nb, s.BH, order, s.scale * kLog2e,
             s.paper_denom);
     };
     if (s.heads_beside) {

@@ -42,15 +42,14 @@ __device__ __forceinline__ void lds_barrier() {
 }
 
 // ------------------------------------------------------------------------------------------------
-// Grid layout.  Per head: key items [0, w_first), then the nb block rows, then key items
-// [w_first, w_max); the long chunks of split columns come first so that they start first, the rows and
-// the short columns fill in behind them.  With B H a multiple of 8 each XCD (own L2; workgroups
-// are dealt to the XCDs round-robin) works on whole heads, items of all its heads interleaved.
+// Grid layout.  Per head: pieces of long rows (CUT), key items [0, w_first), then the nb block rows, then key items
+// [w_first, w_max); the long chunks of split columns come early so that they start first, the rows and
+// the short columns fill in behind them.  The heads as deal_heads() has them, items of an XCD's heads interleaved.
 // n_key_a / n_rows / n_key_c are the per-head counts of the three groups present in this launch
 // (a group is absent when only one side is requested).  w_first leaves room for a quarter of the columns
 // besides the chunks, the longest of them: unsplit columns of more than 8 rows that came last ran on alone (64 heads x 1024,
-// block 32, 4.8 blocks a row: 31.6 -> 26.5 us; a sixth or a third of the columns measure like a quarter).  Pieces of long rows
-// come before all three (CUT).  With sort_rows the rows go by rows_in_order().
+// block 32, 4.8 blocks a row: 31.6 -> 26.5 us; a sixth or a third of the columns measure like a quarter).  With sort_rows
+// the rows go by length.
 // ------------------------------------------------------------------------------------------------
 template <int BS, bool BESIDE, bool CUT>
 __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
@@ -60,7 +59,7 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
     const int* __restrict__ row_ptr, const int* __restrict__ col_idx, const int* __restrict__ col_ptr,
     const int* __restrict__ row_idx, float* __restrict__ partial, unsigned long long* __restrict__ counters,
     unsigned long long tag, HeadRows<BESIDE> at, CutOf<CUT> cut, int n_slots, int BH, int L, int nb, int n_key_a,
-    int n_rows, int n_key_c, int w_first, int chunk, int sort_rows, float scale, float scale_log2) {
+    int n_rows, int n_key_c, int w_first, int chunk, int sort_rows, int few, float scale, float scale_log2) {
     constexpr int NT = BS / 16;   // 16-row tiles per block = waves per workgroup
     // Separate objects, so that the compiler can tell a read of one tile from a load in flight into
     // another and does not wait for it.  Query side: {ta, tb} hold {K, V} of a block, three stages
@@ -76,50 +75,34 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
     const TileLoadLane tl(wave, lane, in_row);
 
     // which workgroup am I
-    int x = 0, hpx = BH, l = blockIdx.x;
-    if ((BH & 7) == 0) {
-        x = blockIdx.x & 7;
-        hpx = BH >> 3;
-        l = blockIdx.x >> 3;
-    }
-    bool key_side;
-    int bh, idx;   // idx: work item (key side) or block row (query side)
+    const ItemOfHead dealt_to = deal_heads(blockIdx.x, BH, few != 0);
+    const int bh = dealt_to.head;
+    bool key_side = false;
+    int idx = dealt_to.item;   // work item (key side) or block row (query side)
     [[maybe_unused]] RowPieces cuts = {0, 1, 0, 0};
     [[maybe_unused]] int piece = 0;
     bool helper = false;
     if constexpr (CUT) {
-        helper = l < hpx * cut.helpers;
-        if (!helper) l -= hpx * cut.helpers;
+        helper = idx < cut.helpers;
+        if (!helper) idx -= cut.helpers;
     }
     if (helper) {
         if constexpr (CUT) {
-            key_side = false;
-            bh = x * hpx + l % hpx;
-            cuts = row_pieces<false>(row_ptr, nb, cut, l / hpx, lane);
+            cuts = row_pieces<false>(row_ptr, nb, cut, idx, lane);
             if (cuts.row < 0) return;
+            piece = idx - cuts.first + 1;
             idx = cuts.row;
-            piece = l / hpx - cuts.first + 1;
         }
-    } else if (l < hpx * n_key_a) {
+    } else if (idx < n_key_a) {
         key_side = true;
-        bh = x * hpx + l % hpx;
-        idx = l / hpx;
-    } else if (l < hpx * (n_key_a + n_rows)) {
-        l -= hpx * n_key_a;
-        key_side = false;
-        if (sort_rows) {
-            const RowOfHead mine = rows_in_order<false>(row_ptr, nb, hpx, l, lane, (BH & 7) == 0);
-            bh = x * hpx + mine.head;
-            idx = mine.row;
-        } else {
-            bh = x * hpx + l / nb;
-            idx = l % nb;
-        }
+    } else if (idx < n_key_a + n_rows) {
+        idx -= n_key_a;
+        if (sort_rows) idx = row_by_length(row_ptr, nb, idx, lane);
     } else {
-        l -= hpx * (n_key_a + n_rows);
+        idx -= n_key_a + n_rows;
+        if (idx >= n_key_c) return;
         key_side = true;
-        bh = x * hpx + l % hpx;
-        idx = w_first + l / hpx;
+        idx += w_first;
     }
     const size_t head = at.in_head(bh, L), out_head = at.out_head(bh, L);
     const size_t vec = (size_t)bh * L;
@@ -495,7 +478,10 @@ hipError_t bwd_bf16(const AttnShape& s, const void* Q, const void* K, const void
     const bool rows = (s.bwd_phases & 1) != 0, keys = (s.bwd_phases & 2) != 0;
     const int n_key_a = keys ? ws.w_first : 0, n_rows = rows ? s.nb : 0, n_key_c = keys ? ws.w_max - ws.w_first : 0;
     const RowCut cut = rows ? row_cut(s, ws, workspace) : RowCut{};
-    const long long total = (long long)s.BH * (n_key_a + n_rows + n_key_c), helpers = (long long)s.BH * cut.helpers;
+    const long long items = cut.helpers + n_key_a + n_rows + n_key_c, total = s.BH * items;
+    const int few = total <= 512;   // deal_heads()
+    const long long grid = dealt(s.BH, items, few != 0);
+    if (grid > 0x7fffffffll) return hipErrorInvalidValue;
     if (total > 0) {
         // A row of more than twice the mean that starts late runs alone at the end; finding the rows by length
         // costs each about half a step.  Worth it where such rows are long, by themselves (a mean of 6
@@ -503,13 +489,13 @@ hipError_t bwd_bf16(const AttnShape& s, const void* Q, const void* K, const void
         // 64 heads x 1024, 4.8 blocks a row 26.9 -> 28.3 us.
         const int sort_rows = total > bwd_resident(BS) && (ws.nnzb >= 6 * s.nb || s.nb >= 8 * bwd_steps_per_slot(s.BH, BS, s.nb, ws.nnzb));
         auto launch = [&](auto kernel, auto at, auto cut_arg) {
-            kernel<<<dim3((unsigned)(helpers + total)), dim3(BS * 4), 0, st>>>(
+            kernel<<<dim3((unsigned)grid), dim3(BS * 4), 0, st>>>(
                 static_cast<const bf16_t*>(Q), static_cast<const bf16_t*>(K), static_cast<const bf16_t*>(V),
                 static_cast<const bf16_t*>(O), static_cast<const bf16_t*>(dO), LSE, static_cast<bf16_t*>(dQ),
                 static_cast<bf16_t*>(dK), static_cast<bf16_t*>(dV), row_ptr, col_idx, col_ptr, row_idx,
                 reinterpret_cast<float*>(static_cast<char*>(workspace) + ws.counter_bytes),
                 static_cast<unsigned long long*>(workspace), s.tag, at, cut_arg,
-                ws.n_slots, s.BH, s.L, s.nb, n_key_a, n_rows, n_key_c, ws.w_first, ws.chunk, sort_rows, s.scale, s.scale * kLog2e);
+                ws.n_slots, s.BH, s.L, s.nb, n_key_a, n_rows, n_key_c, ws.w_first, ws.chunk, sort_rows, few, s.scale, s.scale * kLog2e);
         };
         if (s.heads_beside) {
             if (cut.slots) launch(attn_bwd_bf16_kernel<BS, true, true>, HeadRows<true>{s.heads_beside}, cut);

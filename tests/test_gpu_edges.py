@@ -1002,6 +1002,32 @@ def test_forward_sorted_rows_at_odd_head_counts(sp, BH, nb, block, long_rows):
     assert not O.isnan().any() and not LSE.isnan().any()
 
 
+# Heads that do not divide over the XCDs (and some that do), block rows that are no multiple of 8: every row and column of every head once.  Rows as they lie,
+# dealt and by length; the backward dealt from 513 workgroups on; heads with the same inputs have the same bits
+@pytest.mark.parametrize("BH,nb,block,mean", [(5, 20, 64, 3), (3, 86, 64, 7), (9, 61, 64, 3), (13, 64, 32, 3), (23, 35, 32, 4), (65, 13, 32, 3), (63, 17, 64, 3),
+                                              (7, 100, 64, 1), (7, 150, 64, 8), (31, 70, 32, 7), (127, 9, 64, 2), (24, 27, 64, 3), (1, 600, 32, 3)])
+def test_heads_dealt_over_the_xcds(sp, BH, nb, block, mean):
+    from test_gpu_parity import _pattern_from_mask
+    rng = np.random.default_rng(nb)
+    fl = np.eye(nb, dtype=np.uint8)
+    if mean > 1:
+        fl |= (rng.random((nb, nb)) < (mean - 1) / nb).astype(np.uint8)
+        fl[:, 2] = 1
+        fl[3, 3] = 0
+    pat = _pattern_from_mask(sp, fl, block)
+    gen = torch.Generator(device="cuda").manual_seed(BH)
+    one = [torch.randn((1, 1, nb * block, 64), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(4)]
+    q, k, v, do = [t.expand(1, BH, -1, -1).contiguous() for t in one]
+    nan = lambda: torch.full_like(q, float("nan"))
+    o, lse = sp.attn_fwd(q, k, v, pat, O=nan(), LSE=torch.full(q.shape[:3], float("nan"), device="cuda"))
+    grads = sp.attn_bwd(q, k, v, o, do, lse, pat, dQ=nan(), dK=nan(), dV=nan())
+    for x in (o, lse, *grads):
+        assert torch.equal(x, x[:, :1].expand_as(x))   # (a NaN would not be equal)
+    want, want_lse = sp.attn_fwd(*one[:3], pat)
+    for x, w in zip((o, *grads), (want, *sp.attn_bwd(*one[:3], want, one[3], want_lse, pat))):   # other cuts of rows and columns: sums in another order, rounded to bf16
+        assert torch.linalg.vector_norm(x[:, :1].float() - w.float()) <= 1e-2 * torch.linalg.vector_norm(w.float())
+
+
 # Whole heads on every XCD: rows by length, of one, two, four and sixteen groups of 64 block rows, the last group full and not
 @pytest.mark.parametrize("BH,nb,block", [(24, 64, 64), (24, 65, 64), (24, 128, 32), (8, 129, 64), (8, 256, 64), (8, 257, 32), (8, 1000, 32)])
 def test_forward_rows_by_length(sp, BH, nb, block):
