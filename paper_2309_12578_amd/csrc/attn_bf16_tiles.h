@@ -254,86 +254,6 @@ __device__ __forceinline__ int row_by_length(const int* __restrict__ row_ptr, in
     if (nb <= 256) return row_of_rank<4>(row_ptr, nb, rank, lane);
     return row_of_rank<SPION_MAX_NB / 64>(row_ptr, nb, rank, lane);
 }
-// Which block row the workgroup number l of `heads` heads takes, when there are more workgroups than run at once.  DEAL: l is
-// the workgroup id; else l counts the workgroups of one XCD.
-struct RowOfHead {
-    int row, head;
-};
-// Heads that do not divide over the XCDs: the rows with more than twice the mean number of kept blocks first, of all the heads (a
-// row of 80 blocks that starts last runs alone for as long as everything before it took), then head by
-// head the others, so that neighbours in time share K and V in an L2.  DEAL: each
-// of the two lists is shared out over the XCDs head by head.
-// Dealt this way: rows in id order, one L2 after the other, at 12 heads of 256 rows of
-// 64 x 13 blocks each in a band read K and V eight times (forward 101 -> 58 us; 20 heads, block 32, 9 blocks: 61 -> 27
-// us; unsorted and dealt 61 and 29 us).  Patterns without a long row skip the second search, and the counts are
-// loaded four groups at a time (3 heads of 1000 rows of 12 blocks: 86 -> 76 us, unsorted 77).  By length throughout, in either list,
-// such heads were slower: bf16, 12 heads x 6144, block 64, forward 26.2 -> 28.1; 13 x 8192, block 32, backward 105 -> 113.
-// All lanes of the calling wave must be active.
-template <bool DEAL>
-__device__ __forceinline__ RowOfHead long_rows_first(const int* __restrict__ row_ptr, int nb, int heads, int l, int lane) {
-    const int limit = 2 * row_ptr[nb] / nb;
-    int n_long = 0, cnt_first = 0;   // rows 0 .. 63 are kept for the second search
-    int base0 = 0;
-    for (; base0 + 256 <= nb; base0 += 256) {   // four groups whose loads are in flight together
-        int from[4], to[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            from[k] = row_ptr[base0 + 64 * k + lane];
-            to[k] = row_ptr[base0 + 64 * k + lane + 1];
-        }
-        if (base0 == 0) cnt_first = to[0] - from[0];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) n_long += __popcll(__ballot(to[k] - from[k] > limit));
-    }
-    for (int base = base0; base < nb; base += 64) {
-        const int r = base + lane;
-        const int cnt = r < nb ? row_ptr[r + 1] - row_ptr[r] : 0;
-        if (base == 0) cnt_first = cnt;
-        n_long += __popcll(__ballot(r < nb && cnt > limit));
-    }
-    const int longs = heads * n_long;
-    const bool want_long = l < longs;
-    int head, rank;
-    if (want_long) {
-        if (DEAL) l = xcd_deal(l, 0, longs);
-        head = DEAL ? l / n_long : l % heads;
-        rank = DEAL ? l % n_long : l / heads;
-    } else {
-        l = DEAL ? xcd_deal(l, longs, heads * nb) : l - longs;
-        head = l / (nb - n_long);
-        rank = l % (nb - n_long);
-    }
-    if (n_long == 0) return {rank, head};
-    for (int base = 0; base < nb; base += 64) {   // the counts are in the cache by now
-        const int r = base + lane;
-        int cnt = cnt_first;
-        if (base != 0) cnt = r < nb ? row_ptr[r + 1] - row_ptr[r] : 0;
-        const unsigned long long mine = __ballot(r < nb && (cnt > limit) == want_long);
-        const int members = __popcll(mine);
-        if (rank < members) {
-            const unsigned long long hit = __ballot(((mine >> lane) & 1ull) && lanes_below(mine) == rank);
-            return {base + __ffsll((long long)hit) - 1, head};
-        }
-        rank -= members;
-    }
-    return {0, head};
-}
-
-// By length, all heads of an XCD together, where each XCD has whole heads (`whole`): what starts last is short then.  Forward, long rows
-// first and so: bf16, block 64, 32 heads x 4096, 13 blocks a row 45.7 -> 41.6 us, 64 x 2048 19.3 -> 18.1; block 32, 32 x 4096 32.3 -> 29.6; fp32, block 16,
-// 16 x 2048 23.5 -> 22.5.  The backward, whose short columns come last anyway, hardly gains by the rows' order (head by head within an XCD it loses
-// locality: 32 x 4096, block 32, 91 -> 98).
-template <bool DEAL>
-__device__ __forceinline__ RowOfHead rows_in_order(const int* __restrict__ row_ptr, int nb, int heads, int l, int lane, bool whole) {
-    if (!whole) return long_rows_first<DEAL>(row_ptr, nb, heads, l, lane);
-    const int x = DEAL ? l & 7 : 0;
-    if (DEAL) {
-        l >>= 3;
-        heads >>= 3;
-    }
-    const int rank = l / heads, head = x * heads + l % heads;
-    return {row_by_length(row_ptr, nb, rank, lane), head};
-}
 
 // ------------------------------------------------------------------------------------------------
 // Long rows in pieces.  A block row is one chain of steps; patterns have a row or two of several times the mean, up to
