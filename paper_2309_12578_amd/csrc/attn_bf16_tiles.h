@@ -183,16 +183,15 @@ __device__ __forceinline__ ItemOfHead deal_heads(int id, int heads, bool few) {
     if ((heads & 7) == 0) return {x * (heads >> 3) + l % (heads >> 3), l / (heads >> 3)};
     if (few) return {id % heads, id / heads};
     const int round = l / heads;
-    int t = l - round * heads, at = 0;
-    bool found = false;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {   // the XCD's points of item k of the round
-        const int first = (k - x * heads) & 7, n = (heads - first + 7) >> 3;
-        const bool here = !found && t < n;
-        if (here) at = x * heads + first + 8 * t;
-        found |= here;
-        if (!found) t -= n;
+    int t = l - round * heads, first = 0;   // the XCD's points of item k of the round: x heads + first + 8 t
+#pragma unroll 1
+    for (int k = 0;; ++k) {   // ends at k = 7 at the latest: there are `heads` points
+        first = (k - x * heads) & 7;
+        const int n = (heads - first + 7) >> 3;
+        if (t < n || k == 7) break;
+        t -= n;
     }
+    const int at = x * heads + first + 8 * t;
     return {at >> 3, round * 8 + (at & 7)};
 }
 inline long long dealt(long long heads, long long items, bool few) { return few || heads % 8 == 0 ? items * heads : (items + 7) / 8 * 8 * heads; }
