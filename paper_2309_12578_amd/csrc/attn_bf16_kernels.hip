@@ -278,7 +278,7 @@ __global__ __launch_bounds__(BS * 4, BS == 64 ? 4 : 5) void attn_fwd_bf16_kernel
     if constexpr (CUT) id -= cut.groups;
     ItemOfHead mine;
     if (order == kAsTheyLie) {
-        const int vid = xcd_remap(id, heads * nb);
+        const int vid = xcd_deal(id, 0, heads * nb);
         mine = {vid / nb, vid % nb};
     } else {
         mine = deal_heads(id, heads, false);
@@ -357,9 +357,13 @@ hipError_t fwd_bf16(const AttnShape& s, const void* Q, const void* K, const void
     // 5.7 / 6.0, 6 x 5376 7.4 / 7.7, 28 x 768, block 32, 5.1 / 5.6; the diagonal alone, 21 x 1984 5.0 / 5.6.  Longest first where more rows follow than run at once, or a row is six blocks on
     // average: long ones then spread over the compute units.  Dealt / so: 6 x 7680, block 64, 30.3 / 26.0, 5 x 9472 26.3 / 22.7, 28 x 1984, block 32, 14.6 / 13.3; shorter
     // rows, 16 x 4096 13.2 / 13.7, 64 x 1024, block 32, 10.2 / 10.5; up to 256 rows, one or none a compute unit, they are no faster.
-    const RowOrder order = total > fwd_resident(BS) || (total > 256 && nnzb >= 6 * s.nb) ? kByLength
-                           : total > (BS == 64 ? 512 : 768) && 2 * nnzb >= 3 * s.nb      ? kDealt
-                                                                                          : kAsTheyLie;
+    // As they lie, head by head, also where short rows are so many that the order within a head hardly matters and the heads of an XCD do not fit its
+    // L2 (by length / so): block 32, 88 x 2880, 3 blocks a row, 28.3 / 24.4, 56 x 4544, 4.4, 30.7 / 25.3; 96 x 2624, 6.9, 35.3 / 38.9; 56 x 1184 (2072 rows) 10.8 / 11.1;
+    // block 64, 72 x 3520, 1.8, 24.9 / 22.1, 32 x 4544, 3.0, 18.9 / 17.6; 40 x 3712, 4.5, 21.1 / 22.1; 32 x 2880 (1440 rows) 12.8 / 13.5.
+    const bool short_rows = BS == 32 ? nnzb < 6 * s.nb && 4 * total >= 5 * fwd_resident(BS) : nnzb < 4 * s.nb && total >= 2 * fwd_resident(BS);
+    const RowOrder order = !short_rows && (total > fwd_resident(BS) || (total > 256 && nnzb >= 6 * s.nb)) ? kByLength
+                           : !short_rows && total > (BS == 64 ? 512 : 768) && 2 * nnzb >= 3 * s.nb        ? kDealt
+                                                                                                             : kAsTheyLie;
     const long long grid = cut.groups + (order == kAsTheyLie ? total : dealt(s.BH, s.nb, false));
     if (grid > 0x7fffffffll) return hipErrorInvalidValue;
     auto launch = [&](auto kernel, auto at, auto cut_arg) {

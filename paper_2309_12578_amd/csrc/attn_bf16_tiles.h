@@ -21,13 +21,6 @@ __device__ __forceinline__ bf16x4 lds_read_tr(const bf16_t* p) {
     return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr)p);
 }
 
-// Workgroups are dealt round-robin to the 8 XCDs in id order.  Give XCD x the x-th contiguous
-// eighth of the (head-major) work so that the K / V (or Q / dO) rows of a head stay in one L2.
-__device__ __forceinline__ int xcd_remap(int id, int total) {
-    if (total & 7) return id;
-    return (id & 7) * (total >> 3) + (id >> 3);
-}
-
 // ------------------------------------------------------------------------------------------------
 // Tiles loaded by the memory pipeline straight into LDS (global_load_lds, 16 B per lane; a wave
 // instruction fills 1 KB of consecutive LDS, lane l at byte 16 l).  Rows are 128 B apart with no
@@ -161,7 +154,7 @@ __device__ __forceinline__ int walk_index(int t, int pd) {
     return pd < 0 ? t : (t == 0 ? pd : (t - 1 < pd ? t - 1 : t));
 }
 
-// Workgroup ids lo .. hi - 1 as numbers 0 .. hi - lo - 1 such that each XCD (id % 8) has a contiguous run of
+// Workgroups go round the 8 XCDs in id order.  Workgroup ids lo .. hi - 1 as numbers 0 .. hi - lo - 1 such that each XCD (id % 8) has a contiguous run of
 // them, whatever the two bounds are.
 __device__ __forceinline__ int xcd_deal(int id, int lo, int hi) {
     const int x = id & 7;

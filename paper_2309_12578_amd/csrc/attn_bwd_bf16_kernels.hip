@@ -76,7 +76,7 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
 
     // which workgroup am I
     const ItemOfHead dealt_to = deal_heads(blockIdx.x, BH, few != 0);
-    const int bh = dealt_to.head;
+    int bh = dealt_to.head;
     bool key_side = false;
     int idx = dealt_to.item;   // work item (key side) or block row (query side)
     [[maybe_unused]] RowPieces cuts = {0, 1, 0, 0};
@@ -97,7 +97,13 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
         key_side = true;
     } else if (idx < n_key_a + n_rows) {
         idx -= n_key_a;
-        if (sort_rows) idx = row_by_length(row_ptr, nb, idx, lane);
+        if (sort_rows) {
+            idx = row_by_length(row_ptr, nb, idx, lane);
+        } else if ((BH & 7) == 0) {   // whole heads: one after the other
+            const int hpx = BH >> 3, first = (blockIdx.x & 7) * hpx, l = idx * hpx + bh - first;
+            bh = first + l / nb;
+            idx = l % nb;
+        }
     } else {
         idx -= n_key_a + n_rows;
         if (idx >= n_key_c) return;
