@@ -120,6 +120,47 @@ def _attention(sp, Q, K, V, dO, fl, block, dtype, heads, flags=0):
     return _run_attention_case(sp, Q, K, V, dO, fl, block, dtype, flags=flags, heads=heads)
 
 
+def _attention_of_unlike_heads(sp, one, BH, fl, block, dtype, flags=0):
+    """One head of Q, K, V, dO in BH forms that powers of two tell apart, so that their results are the first one's, multiplied,
+    to the bit: that one against the fp64 oracle, the others against it.  Heads up to 104 apart are unlike."""
+    from test_gpu_parity import TOL, _dev, _pattern_from_mask, _rel_errors, _torch_dtype
+    h = np.arange(BH)
+    sq, sv, sdo = 2.0 ** (h % 3), 2.0 ** (h % 7), 2.0 ** (h % 5)   # K the inverse of Q's: the scores stay
+    Q, K, V, dO = [_dev(t, _torch_dtype(dtype)) for t in one]
+    by = lambda f: torch.from_numpy(f.astype(np.float32)).cuda().view(1, BH, 1, 1)
+    many = lambda t, f: (t * by(f).to(t.dtype)).contiguous()
+    q, k, v, do = many(Q, sq), many(K, 1 / sq), many(V, sv), many(dO, sdo)
+    pat = _pattern_from_mask(sp, fl, block)
+    O, LSE = sp.attn_fwd(q, k, v, pat, flags=flags)
+    dQ, dK, dV = sp.attn_bwd(q, k, v, O, do, LSE, pat, flags=flags)
+    for name, x, f in (("O", O, sv), ("dQ", dQ, sv * sdo / sq), ("dK", dK, sv * sdo * sq), ("dV", dV, sdo)):
+        assert torch.equal(x, x[:, :1] * by(f).to(x.dtype)), name
+    assert torch.equal(LSE, LSE[:, :1].expand_as(LSE))
+    P = oracle.upsample(fl, block)
+    oflags = oracle.ATTN_PAPER_DENOM if flags & sp.SPION_ATTN_PAPER_DENOM else 0
+    rO, rLSE = oracle.attn_fwd(one[0], one[1], one[2], P, flags=oflags)
+    for name, x, ref in zip(("O", "dQ", "dK", "dV"), (O, dQ, dK, dV), (rO, *oracle.attn_bwd(*one, P, flags=oflags))):
+        errors = _rel_errors(x[0, :1].float().cpu().numpy(), ref)
+        assert max(errors) <= TOL[dtype], (name, errors)
+    lse, fin = LSE[0, :1].cpu().numpy(), np.isfinite(rLSE)
+    assert np.array_equal(np.isneginf(lse), np.isneginf(rLSE))
+    assert np.abs(lse[fin] - rLSE[fin]).max() <= TOL[dtype] * max(np.abs(rLSE[fin]).max(), 1.0)
+
+
+def _one_head(rng, L, dtype):
+    return [si.round_to_dtype(rng.standard_normal((1, L, 64), dtype=np.float32), dtype) for _ in range(4)]
+
+
+def _dense_reference(q, k, v, do, fl, block):
+    """O, dQ, dK and dV of one head, in plain torch on the GPU: fp32 for bf16 tensors, fp64 for fp32."""
+    keep = torch.from_numpy(fl).cuda().bool().repeat_interleave(block, 0).repeat_interleave(block, 1)
+    q, k, v, do = [t.double() if t.dtype == torch.float32 else t.float() for t in (q, k, v, do)]
+    P = torch.softmax((q @ k.T * 0.125).masked_fill_(~keep, float("-inf")), dim=1).nan_to_num_(0.0)   # rows that keep nothing
+    O = P @ v
+    dS = P * (do @ v.T - (do * O).sum(1, keepdim=True))
+    return O, dS @ k * 0.125, dS.T @ q * 0.125, P.T @ do
+
+
 @pytest.mark.parametrize("block", [32, 64])
 def test_forward_scores_that_run_away_from_the_first_block(sp, block):
     """Scores of later blocks far above everything in the block a row starts with (and, in other rows, far
@@ -227,7 +268,7 @@ def test_long_rows_in_pieces(sp, block, BH, nb, longs, denom):
                                               (32, 42, 99, 9), (32, 2, 255, 20), (64, 2, 65, 10)])
 def test_long_rows_in_pieces_where_rows_are_many_blocks(sp, block, BH, nb, mean):
     rng = np.random.default_rng(nb + mean)
-    Q, K, V, dO = [np.repeat(si.round_to_dtype(rng.standard_normal((1, nb * block, 64), dtype=np.float32), "bf16"), BH, 0) for _ in range(4)]
+    one = _one_head(rng, nb * block, "bf16")
     longest = max(2 * mean if mean < 10 else 3 * mean // 2, 2 * (BH * nb * mean // (1024 if block == 64 else 2048)))
     lengths = np.full(nb, mean)
     for r, n in ((0, longest), (nb - 1, longest + 1), (9, min(nb - 1, 3 * longest))):
@@ -241,7 +282,7 @@ def test_long_rows_in_pieces_where_rows_are_many_blocks(sp, block, BH, nb, mean)
         fl[r, rng.choice(cols, n - (r != 9), replace=False)] = 1
         fl[r, r] = r != 9
     assert fl.sum() == nb * mean
-    _attention(sp, Q, K, V, dO, fl, block, "bf16", [BH - 1])
+    _attention_of_unlike_heads(sp, one, BH, fl, block, "bf16")
 
 
 # The kernels of fp32 and of block size 16: a helper for each piece and part of a block row; 16 and 32 rows a workgroup; a row of more
@@ -265,13 +306,13 @@ def test_long_rows_in_pieces_of_the_generic_kernels(sp, dtype, block, BH, nb, lo
 @pytest.mark.parametrize("dtype,block,BH,nb", [("bf16", 16, 9, 121), ("f32", 16, 9, 121), ("f32", 32, 12, 130), ("f32", 64, 24, 130)])
 def test_long_rows_in_pieces_where_two_waves_share_one(sp, dtype, block, BH, nb):
     rng = np.random.default_rng(nb + BH)
-    Q, K, V, dO = [np.repeat(si.round_to_dtype(rng.standard_normal((1, nb * block, 64), dtype=np.float32), dtype), BH, 0) for _ in range(4)]
+    one = _one_head(rng, nb * block, dtype)
     fl = np.eye(nb, dtype=np.uint8) | np.eye(nb, k=1, dtype=np.uint8)
     for r, n in zip((nb - 1, 0, 7), (nb, 65, 44)):
         fl[r] = 0
         fl[r, rng.choice(nb, n, replace=False)] = 1
     fl[5] = 0
-    _attention(sp, Q, K, V, dO, fl, block, dtype, [BH - 1])
+    _attention_of_unlike_heads(sp, one, BH, fl, block, dtype)
 
 
 # fp32 backward, 16 rows a workgroup up to 800 workgroups of 32 rows (block rows, columns and chunks of all heads), 32 beyond: both sides of
@@ -480,10 +521,7 @@ def test_generic_backward_parts_of_a_column(sp, dtype, block, BH):
     fl = np.eye(nb, dtype=np.uint8)
     for c, n in ((0, 17), (9, 112), (70, 128), (128, 129), (200, 256), (259, 260)):
         fl[:, c] = np.arange(nb) < n
-    rng = np.random.default_rng(BH)
-    Q, K, V, dO = [np.repeat(si.round_to_dtype(rng.standard_normal((1, nb * block, 64), dtype=np.float32), dtype), BH, 0)
-                   for _ in range(4)]
-    _attention(sp, Q, K, V, dO, fl, block, dtype, [BH - 1])
+    _attention_of_unlike_heads(sp, _one_head(np.random.default_rng(BH), nb * block, dtype), BH, fl, block, dtype)
 
 
 @pytest.mark.parametrize("dtype,block", [("bf16", 32), ("bf16", 64), ("bf16", 16), ("f32", 32)])
@@ -1003,7 +1041,7 @@ def test_forward_sorted_rows_at_odd_head_counts(sp, BH, nb, block, long_rows):
 
 
 # Heads that do not divide over the XCDs (and some that do), block rows that are no multiple of 8: every row and column of every head once.  Rows as they lie,
-# dealt and by length; the backward dealt from 513 workgroups on; heads with the same inputs have the same bits
+# dealt and by length; the backward dealt from 513 workgroups on
 @pytest.mark.parametrize("BH,nb,block,mean", [(5, 20, 64, 3), (3, 86, 64, 7), (9, 61, 64, 3), (13, 64, 32, 3), (23, 35, 32, 4), (65, 13, 32, 3), (63, 17, 64, 3),
                                               (7, 100, 64, 1), (7, 150, 64, 8), (31, 70, 32, 7), (127, 9, 64, 2), (24, 27, 64, 3), (1, 600, 32, 3)])
 def test_heads_dealt_over_the_xcds(sp, BH, nb, block, mean):
@@ -1017,12 +1055,15 @@ def test_heads_dealt_over_the_xcds(sp, BH, nb, block, mean):
     pat = _pattern_from_mask(sp, fl, block)
     gen = torch.Generator(device="cuda").manual_seed(BH)
     one = [torch.randn((1, 1, nb * block, 64), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(4)]
-    q, k, v, do = [t.expand(1, BH, -1, -1).contiguous() for t in one]
+    # heads told apart by powers of two, so that their results are the first one's, multiplied, to the bit
+    h = torch.arange(BH, device="cuda").view(1, BH, 1, 1)
+    sq, sv, sdo = [(2.0 ** (h % n)).to(torch.bfloat16) for n in (3, 7, 5)]
+    q, k, v, do = [t * f for t, f in zip(one, (sq, 1 / sq, sv, sdo))]
     nan = lambda: torch.full_like(q, float("nan"))
     o, lse = sp.attn_fwd(q, k, v, pat, O=nan(), LSE=torch.full(q.shape[:3], float("nan"), device="cuda"))
     grads = sp.attn_bwd(q, k, v, o, do, lse, pat, dQ=nan(), dK=nan(), dV=nan())
-    for x in (o, lse, *grads):
-        assert torch.equal(x, x[:, :1].expand_as(x))   # (a NaN would not be equal)
+    for x, f in zip((o, lse.unsqueeze(3), *grads), (sv, torch.ones_like(lse).unsqueeze(3), sv * sdo / sq, sv * sdo * sq, sdo)):
+        assert torch.equal(x, x[:, :1] * f)   # (a NaN would not be equal)
     want, want_lse = sp.attn_fwd(*one[:3], pat)
     for x, w in zip((o, *grads), (want, *sp.attn_bwd(*one[:3], want, one[3], want_lse, pat))):   # other cuts of rows and columns: sums in another order, rounded to bf16
         assert torch.linalg.vector_norm(x[:, :1].float() - w.float()) <= 1e-2 * torch.linalg.vector_norm(w.float())
