@@ -69,10 +69,11 @@ struct TileLoadLane {
         }
     }
 };
-// Buffer loads: a scalar base and the lane's offset, where a global load into LDS takes a 64-bit vector addition each.
+// Buffer loads: a scalar base and the lane's offset, where a global load into LDS takes a 64-bit vector addition each.  The descriptor's
+// range is all that the offset can say (rows of many heads beside each other are far apart).
 __device__ __forceinline__ void tile_load_async(const bf16_t* __restrict__ src, bf16_t* tile, int wave,
                                                 const TileLoadLane& tl) {
-    const __amdgpu_buffer_rsrc_t from = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(src), (short)0, 0x7fffffff, 0x00027000);
+    const __amdgpu_buffer_rsrc_t from = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(src), (short)0, (int)0xffffffffu, 0x00027000);
 #pragma unroll
     for (int k = 0; k < 2; ++k)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(from, (lds_void_ptr)(tile + (2 * wave + k) * 512), 16, tl.off[k], 0, 0, 0);

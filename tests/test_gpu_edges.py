@@ -1091,3 +1091,29 @@ def test_forward_rows_by_length(sp, BH, nb, block):
         sp.spion_attn_fwd(*args, *index, 1, 1, *shape)
         assert torch.equal(O[:, h:h + 1], args[3]) and torch.equal(LSE[:, h:h + 1], args[4]), h
     assert not O.isnan().any() and not LSE.isnan().any()
+
+
+@pytest.mark.parametrize("block,H", [(32, 190000), (64, 90000)])
+def test_heads_beside_each_other_whose_rows_are_far_apart(sp, block, H):
+    """In the projections' output of so many heads the last rows of a tile lie more than 2^31 bytes from its first."""
+    import ctypes
+    from test_gpu_parity import TOL, _pattern_from_mask
+    L = block
+    pat = _pattern_from_mask(sp, np.ones((L // block, L // block), dtype=np.uint8), block)
+    qkv = torch.randn((1, L, 3, H, 64), generator=torch.Generator(device="cuda").manual_seed(1), device="cuda", dtype=torch.bfloat16)
+    dS = torch.randn((1, L, H, 64), generator=torch.Generator(device="cuda").manual_seed(2), device="cuda", dtype=torch.bfloat16)
+    S, dqkv, LSE = torch.zeros_like(dS), torch.zeros_like(qkv), torch.zeros((1, H, L), device="cuda")
+    lib, p = sp.load(), sp.binding._AttnParams(1, H, L, 64, block, sp.SPION_BF16, 0.0, 0)
+    ptr = lambda t: ctypes.c_void_p(t.data_ptr())
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    assert lib.spion_heads_attn_fwd(ptr(qkv), ptr(S), ptr(LSE), ptr(pat.row_ptr), ptr(pat.col_idx), pat.nnzb, ctypes.byref(p), None,
+                                    ctypes.c_size_t(0), stream) == 0
+    ws = torch.zeros(sp.spion_attn_workspace_bytes(1, H, L, 64, block, sp.SPION_BF16, pat.nnzb, True), dtype=torch.uint8, device="cuda")
+    assert lib.spion_heads_attn_bwd(ptr(qkv), ptr(S), ptr(dS), ptr(LSE), ptr(dqkv), ptr(pat.row_ptr), ptr(pat.col_idx), ptr(pat.col_ptr),
+                                    ptr(pat.row_idx), pat.nnzb, ctypes.byref(p), ptr(ws), ctypes.c_size_t(ws.numel()), stream) == 0
+    for h in (0, H // 2, H - 1):
+        q, k, v = [qkv[0, :, i, h] for i in range(3)]
+        want = _dense_reference(q, k, v, dS[0, :, h], np.ones((L // block, L // block), dtype=np.uint8), block)
+        for name, got, w in zip(("O", "dQ", "dK", "dV"), (S[0, :, h], *(dqkv[0, :, i, h] for i in range(3))), want):
+            error = torch.linalg.vector_norm(got - w) / torch.linalg.vector_norm(w)
+            assert error <= TOL["bf16"], (name, h, float(error))
