@@ -192,16 +192,16 @@ inline long long dealt(long long heads, long long items, bool few) { return few 
 
 // Rows (columns) in the order of their lengths: longest first, equal ones by index; lengths count in quarters of the mean, four
 // times the mean and more alike.  Lane l holds the entry 64 k + l of group k: its length in those units and, as bits
-// of a group, which entries take part.  The entry whose place is `want`, found a bit of the length at a time: some 40
-// instructions a group, no memory access.  Half the mean as unit, a bit less, saves nothing and orders worse (fp32, 64 x 1024, block 32,
+// of a group, which entries take part.  The entry whose place is `want`, found a bit of the length at a time (not at all where no lengths
+// count): some 40 instructions a group, no memory access.  Half the mean as unit, a bit less, saves nothing and orders worse (fp32, 64 x 1024, block 32,
 // backward 110.8 -> 113 us).  All lanes active, the result uniform; -1: there are not so many entries.
 constexpr int kLengthBits = 4;
 __device__ __forceinline__ float quarters_of_mean(int nb, int nnzb) { return 4.f * (float)nb * __builtin_amdgcn_rcpf((float)max(nnzb, 1)); }
 __device__ __forceinline__ int length_key(int cnt, float quarters) { return min((int)((float)cnt * quarters), (1 << kLengthBits) - 1); }
 template <int NG>
-__device__ __forceinline__ int entry_by_length(const int (&key)[NG], unsigned long long (&mask)[NG], int want, int lane) {
-#pragma unroll
-    for (int bit = 1 << (kLengthBits - 1); bit; bit >>= 1) {
+__device__ __forceinline__ int entry_by_length(const int (&key)[NG], unsigned long long (&mask)[NG], int want, int lane, bool by_length) {
+#pragma unroll 1
+    for (int bit = by_length ? 1 << (kLengthBits - 1) : 0; bit; bit >>= 1) {
         unsigned long long upper[NG];
         int n = 0;
 #pragma unroll
@@ -239,13 +239,63 @@ __device__ __forceinline__ int row_of_rank(const int* __restrict__ row_ptr, int 
     }
 #pragma unroll
     for (int k = 0; k < NG; ++k) key[k] = length_key(key[k], quarters);
-    return entry_by_length<NG>(key, mask, rank, lane);
+    return entry_by_length<NG>(key, mask, rank, lane, true);
+}
+// The same for any number of entries.  What takes part and the four bits of the lengths are kept by lane, a bit for each group of 64,
+// and the loops over groups are loops.  As many groups unrolled as SPION_MAX_NB has take 32 masks, more scalar registers than a
+// kernel has besides (1 to 32 spilled), and code that whoever calls the kernel pays for at the start of its workgroups: the backward
+// kernels had 41 to 53 KB, so 25 to 37; fp32 backward, 6 heads x 640, block 64, 27.4 -> 23.6 us, 15 x 992, block 32, 37.0 -> 34.1.
+struct EntriesByLength {
+    unsigned in = 0, key[kLengthBits] = {};
+    static_assert(SPION_MAX_NB <= 64 * 32, "a bit of a word for each group");
+    __device__ __forceinline__ void add(int group, bool takes_part, int length) {
+        in |= (unsigned)takes_part << group;
+#pragma unroll
+        for (int b = 0; b < kLengthBits; ++b) key[b] |= (unsigned)(length >> b & 1) << group;
+    }
+    __device__ __forceinline__ int entry(int groups, int want, int lane) const {
+        unsigned left = in;
+#pragma unroll
+        for (int b = kLengthBits - 1; b >= 0; --b) {
+            const unsigned upper = left & key[b];
+            const int n = __builtin_amdgcn_readlane(wave_incl_scan(__popc(upper), lane), 63);
+            left = want < n ? upper : left & ~upper;
+            if (want >= n) want -= n;
+        }
+#pragma unroll 1
+        for (int k = 0; k < groups; ++k) {
+            const unsigned long long mask = __ballot((left >> k & 1u) != 0);
+            const int members = __popcll(mask);
+            if (want < members) {
+                const unsigned long long hit = __ballot(((mask >> lane) & 1ull) && lanes_below(mask) == want);
+                return 64 * k + __ffsll((long long)hit) - 1;
+            }
+            want -= members;
+        }
+        return -1;
+    }
+};
+__device__ __forceinline__ int row_of_rank_any(const int* __restrict__ row_ptr, int nb, int rank, int lane) {
+    const float quarters = quarters_of_mean(nb, row_ptr[nb]);
+    EntriesByLength rows;
+#pragma unroll 1
+    for (int base = 0; base < nb; base += 512) {   // eight groups whose loads are in flight together
+        int cnt[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int r = base + 64 * k + lane;
+            cnt[k] = r < nb ? row_ptr[r + 1] - row_ptr[r] : -1;
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) rows.add(base / 64 + k, cnt[k] >= 0, length_key(max(cnt[k], 0), quarters));
+    }
+    return rows.entry((nb + 63) / 64, rank, lane);
 }
 __device__ __forceinline__ int row_by_length(const int* __restrict__ row_ptr, int nb, int rank, int lane) {
     if (nb <= 64) return row_of_rank<1>(row_ptr, nb, rank, lane);
     if (nb <= 128) return row_of_rank<2>(row_ptr, nb, rank, lane);
     if (nb <= 256) return row_of_rank<4>(row_ptr, nb, rank, lane);
-    return row_of_rank<SPION_MAX_NB / 64>(row_ptr, nb, rank, lane);
+    return row_of_rank_any(row_ptr, nb, rank, lane);
 }
 
 // ------------------------------------------------------------------------------------------------

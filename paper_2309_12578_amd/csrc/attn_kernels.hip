@@ -700,7 +700,7 @@ __global__ __launch_bounds__(S::W * 64, 2) void attn_bwd_kernel(
         return;
     }
 
-    const KeyItem it = key_item_lookup(col_ptr, nb, chunk, by_length != 0, idx, lane);
+    const KeyItem it = key_item_lookup(col_ptr, nb, chunk, by_length, idx, lane);
     if (it.J < 0) return;
     const int n = it.ke - it.kb, nt = n * S::TPB, row0 = it.J * BS + sub + own;
     const int* rows = row_idx + it.kb;

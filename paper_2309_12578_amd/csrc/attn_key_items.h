@@ -59,12 +59,38 @@ struct KeyItem {
     int first, count;   // slot of the column's first chunk, its chunks
 };
 
-// All lanes of the calling wave must be active; the result is wave-uniform.  by_length: the unsplit columns longest first,
-// else in their order.  Backward, columns of more than 8 rows first and so: fp32, 32 heads x 1024, block 64, 90.7 -> 84.0 us, 64 x 1024, block
+// The chunk number w of a split column, if it is one of those of this group of 64 columns; `run`: chunks of the groups before.
+__device__ __forceinline__ bool chunk_of_group(KeyItem& it, int& run, int base, int c0, int cnt, int chunk, int w, int lane) {
+    if (!__any(cnt > chunk)) return false;
+    const int nch = cnt > chunk ? (cnt + chunk - 1) / chunk : 0;
+    const int incl = wave_incl_scan(nch, lane);
+    const int lo = run + incl - nch;
+    const unsigned long long hit = __ballot(nch > 0 && w >= lo && w < lo + nch);
+    if (hit) {
+        const int src = __ffsll((long long)hit) - 1;
+        const int c0s = __builtin_amdgcn_readlane(c0, src), cnts = __builtin_amdgcn_readlane(cnt, src);
+        const int nchs = __builtin_amdgcn_readlane(nch, src);
+        const int first = __builtin_amdgcn_readlane(lo, src);
+        int ci = w - first;
+        ci = ci < 0 ? 0 : (ci >= nchs ? nchs - 1 : ci);
+        it = {base + src, c0s + (ci * cnts) / nchs, c0s + ((ci + 1) * cnts) / nchs, w, first, nchs};
+        return true;
+    }
+    run += __builtin_amdgcn_readlane(incl, 63);
+    return false;
+}
+
+// Units of length of the columns: a quarter of the mean, but `finest` blocks at least; 0: lengths do not count.
+__device__ __forceinline__ float units_of_length(int nb, int nnzb, int finest) {
+    return finest ? fminf(quarters_of_mean(nb, nnzb), __builtin_amdgcn_rcpf((float)finest)) : 0.f;
+}
+
+// All lanes of the calling wave must be active; the result is wave-uniform.  The unsplit columns longest first, lengths in units_of_length(),
+// or (finest == 0) in their order.  Backward, columns of more than 8 rows first and so: fp32, 32 heads x 1024, block 64, 90.7 -> 84.0 us, 64 x 1024, block
 // 32, 115 -> 111; bf16, block 64, 16 x 4096 36.7 -> 35.6.
 template <int NG>
-__device__ __forceinline__ KeyItem key_item(const int* __restrict__ col_ptr, int nb, int chunk, bool by_length, int w, int lane) {
-    const KeyItem none = {-1, 0, 0, -1, 0, 1};
+__device__ __forceinline__ KeyItem key_item(const int* __restrict__ col_ptr, int nb, int chunk, int finest, int w, int lane) {
+    KeyItem it = {-1, 0, 0, -1, 0, 1};
     int c0[NG], cnt[NG];
 #pragma unroll
     for (int k = 0; k < NG; ++k) {
@@ -72,25 +98,11 @@ __device__ __forceinline__ KeyItem key_item(const int* __restrict__ col_ptr, int
         c0[k] = J < nb ? col_ptr[J] : 0;
         cnt[k] = J < nb ? col_ptr[J + 1] - c0[k] : 0;
     }
-    int run = 0;     // chunks of split columns in the column groups before this one
+    int run = 0;
 #pragma unroll
-    for (int k = 0; k < NG; ++k) {
-        const int nch = cnt[k] > chunk ? (cnt[k] + chunk - 1) / chunk : 0;
-        const int incl = wave_incl_scan(nch, lane);
-        const int lo = run + incl - nch;
-        const unsigned long long hit = __ballot(nch > 0 && w >= lo && w < lo + nch);
-        if (hit) {
-            const int src = __ffsll((long long)hit) - 1;
-            const int c0s = __builtin_amdgcn_readlane(c0[k], src), cnts = __builtin_amdgcn_readlane(cnt[k], src);
-            const int nchs = __builtin_amdgcn_readlane(nch, src);
-            const int first = __builtin_amdgcn_readlane(lo, src);
-            int ci = w - first;
-            ci = ci < 0 ? 0 : (ci >= nchs ? nchs - 1 : ci);
-            return {64 * k + src, c0s + (ci * cnts) / nchs, c0s + ((ci + 1) * cnts) / nchs, w, first, nchs};
-        }
-        run += __builtin_amdgcn_readlane(incl, 63);
-    }
-    const float quarters = by_length ? quarters_of_mean(nb, col_ptr[nb]) : 0.f;
+    for (int k = 0; k < NG; ++k)
+        if (chunk_of_group(it, run, 64 * k, c0[k], cnt[k], chunk, w, lane)) return it;
+    const float quarters = units_of_length(nb, col_ptr[nb], finest);
     int key[NG];
     unsigned long long mask[NG];
 #pragma unroll
@@ -98,8 +110,8 @@ __device__ __forceinline__ KeyItem key_item(const int* __restrict__ col_ptr, int
         key[k] = length_key(cnt[k], quarters);
         mask[k] = __ballot(64 * k + lane < nb && cnt[k] <= chunk);
     }
-    const int J = entry_by_length<NG>(key, mask, w - run, lane);
-    if (J < 0) return none;
+    const int J = entry_by_length<NG>(key, mask, w - run, lane, finest > 0);
+    if (J < 0) return it;
     int a = 0, n = 0;
 #pragma unroll
     for (int k = 0; k < NG; ++k)
@@ -109,15 +121,40 @@ __device__ __forceinline__ KeyItem key_item(const int* __restrict__ col_ptr, int
         }
     return {J, a, a + n, -1, 0, 1};
 }
-__device__ __forceinline__ KeyItem key_item_lookup(const int* __restrict__ col_ptr, int nb, int chunk, bool by_length, int w, int lane) {
-    if (nb <= (by_length ? kChunkLeast : chunk)) {   // none is cut, all about alike
+// The same for any number of columns.
+__device__ __forceinline__ KeyItem key_item_any(const int* __restrict__ col_ptr, int nb, int chunk, int finest, int w, int lane) {
+    KeyItem it = {-1, 0, 0, -1, 0, 1};
+    const float quarters = units_of_length(nb, col_ptr[nb], finest);
+    EntriesByLength columns;
+    int run = 0;
+#pragma unroll 1
+    for (int base = 0; base < nb; base += 256) {   // four groups whose loads are in flight together
+        int c0[4], cnt[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int J = base + 64 * k + lane;
+            c0[k] = J < nb ? col_ptr[J] : 0;
+            cnt[k] = J < nb ? col_ptr[J + 1] - c0[k] : -1;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (chunk_of_group(it, run, base + 64 * k, c0[k], cnt[k], chunk, w, lane)) return it;
+            columns.add(base / 64 + k, cnt[k] >= 0 && cnt[k] <= chunk, length_key(max(cnt[k], 0), quarters));
+        }
+    }
+    const int J = columns.entry((nb + 63) / 64, w - run, lane);
+    if (J < 0) return it;
+    return {J, col_ptr[J], col_ptr[J + 1], -1, 0, 1};
+}
+__device__ __forceinline__ KeyItem key_item_lookup(const int* __restrict__ col_ptr, int nb, int chunk, int finest, int w, int lane) {
+    if (nb <= (finest ? kChunkLeast : chunk)) {   // none is cut, all about alike
         if (w >= nb) return {-1, 0, 0, -1, 0, 1};
         return {w, col_ptr[w], col_ptr[w + 1], -1, 0, 1};
     }
-    if (nb <= 64) return key_item<1>(col_ptr, nb, chunk, by_length, w, lane);
-    if (nb <= 128) return key_item<2>(col_ptr, nb, chunk, by_length, w, lane);
-    if (nb <= 256) return key_item<4>(col_ptr, nb, chunk, by_length, w, lane);
-    return key_item<SPION_MAX_NB / 64>(col_ptr, nb, chunk, by_length, w, lane);
+    if (nb <= 64) return key_item<1>(col_ptr, nb, chunk, finest, w, lane);
+    if (nb <= 128) return key_item<2>(col_ptr, nb, chunk, finest, w, lane);
+    if (nb <= 256) return key_item<4>(col_ptr, nb, chunk, finest, w, lane);
+    return key_item_any(col_ptr, nb, chunk, finest, w, lane);
 }
 
 }  // namespace spion

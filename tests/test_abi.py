@@ -158,6 +158,39 @@ def test_bins_of_large_grids_are_fine_for_every_scale_and_sign(tmp_path):
         assert v == first.setdefault(b, v) or abs(v - first[b]) * 32 < abs(v), (first[b], v)
 
 
+def _kernels_of_the_library():
+    """The metadata of every kernel in libspion.so: the MessagePack notes of the GPU code objects inside it."""
+    import struct
+    import msgpack
+    data = open(sp.binding.lib_path(), "rb").read()
+    found, at = [], data.find(b"\x7fELF", 4)
+    while at >= 0:
+        if struct.unpack_from("<H", data, at + 18)[0] == 224:   # EM_AMDGPU
+            shoff, = struct.unpack_from("<Q", data, at + 40)
+            shentsize, shnum = struct.unpack_from("<HH", data, at + 58)
+            for i in range(shnum):
+                head = at + shoff + i * shentsize
+                kind, = struct.unpack_from("<I", data, head + 4)
+                offset, size = struct.unpack_from("<QQ", data, head + 24)
+                pos, end = at + offset, at + offset + size
+                while kind == 7 and pos < end:   # SHT_NOTE
+                    namesz, descsz, what = struct.unpack_from("<III", data, pos)
+                    desc = pos + 12 + (namesz + 3) // 4 * 4
+                    if what == 32:   # NT_AMDGPU_METADATA
+                        found += msgpack.unpackb(data[desc:desc + descsz])["amdhsa.kernels"]
+                    pos = desc + (descsz + 3) // 4 * 4
+        at = data.find(b"\x7fELF", at + 4)
+    return found
+
+
+def test_attention_kernels_spill_no_registers():
+    kernels = [k for k in _kernels_of_the_library() if "attn_" in k[".name"]]
+    assert len(kernels) > 40
+    for k in kernels:
+        spills = k[".sgpr_spill_count"], k[".vgpr_spill_count"], k[".private_segment_fixed_size"]
+        assert spills == (0, 0, 0), (k[".name"], spills)
+
+
 def test_binding_refuses_cpu_tensors():
     import torch
     x = torch.zeros(4)

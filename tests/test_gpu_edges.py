@@ -1069,8 +1069,8 @@ def test_heads_dealt_over_the_xcds(sp, BH, nb, block, mean):
         assert torch.linalg.vector_norm(x[:, :1].float() - w.float()) <= 1e-2 * torch.linalg.vector_norm(w.float())
 
 
-# Whole heads on every XCD: rows by length, of one, two, four and sixteen groups of 64 block rows, the last group full and not
-@pytest.mark.parametrize("BH,nb,block", [(24, 64, 64), (24, 65, 64), (24, 128, 32), (8, 129, 64), (8, 256, 64), (8, 257, 32), (8, 1000, 32)])
+# Whole heads on every XCD: rows by length, of one, two, four and more groups of 64 block rows, the last group full and not
+@pytest.mark.parametrize("BH,nb,block", [(24, 64, 64), (24, 65, 64), (24, 128, 32), (8, 129, 64), (8, 256, 64), (8, 257, 32), (8, 512, 32), (8, 513, 32), (8, 1000, 32), (8, 1024, 32)])
 def test_forward_rows_by_length(sp, BH, nb, block):
     from test_gpu_parity import _pattern_from_mask
     rng = np.random.default_rng(nb)
