@@ -302,9 +302,12 @@ __device__ __forceinline__ int row_by_length(const int* __restrict__ row_ptr, in
 // Long rows in pieces.  A block row is one chain of steps; patterns have a row or two of several times the mean, up to
 // half the columns, and where there are few heads such a chain outlasts everything else: 8 heads x 8192, block 32, 13
 // blocks a row and two rows of 120: forward 44 us, 14 without those rows.  A row of more than `longest` blocks is cut into pieces
-// of about `piece`, as long as a head's pieces fit into `slots`.  The row's own workgroup takes the first piece; `helpers`
-// workgroups of each head, which come first in the grid, take the others (the forward's in turn; the backward's query side
-// has one for each).  Every workgroup finds the same cuts from row_ptr.
+// of about `piece`.  The row's own workgroup takes the first piece; `helpers` workgroups of each head, which come first in the grid,
+// take the others (the forward's in turn; the backward's query side has one for each).  Where a pattern has more pieces than there are
+// `slots` for, pieces are half as long again, and rows are cut that are 3/2 of them, until it has not: so the longest rows are
+// cut, whatever the shorter ones need.  (Cut in their order as long as there was room, they used it up before the longest came, or had themselves
+// more pieces than there was room for: 4 heads x 16384, block 32, 10 blocks a row, two rows of 200, forward 85 -> 27.5 us, backward
+// 115 -> 50.)  Every workgroup finds the same cuts from row_ptr.
 // Each piece leaves its accumulators, reference and sum in memory; the workgroup that is the last of its row to do so adds
 // up the pieces in their order (the same bits whoever that is) and writes the row.  Nobody waits for anybody.
 // ------------------------------------------------------------------------------------------------
@@ -323,25 +326,33 @@ using CutOf = std::conditional_t<CUT, RowCut, NoCut>;
 // active, the result uniform.
 template <bool BY_ROW>
 __device__ __forceinline__ RowPieces row_pieces(const int* __restrict__ row_ptr, int nb, const RowCut& cut, int want, int lane) {
-    int others = 0, cut_rows = 0;   // pieces (not the first of a row) and long rows before this group of 64 rows
-    for (int base = 0; base < nb; base += 64) {
-        const int r = base + lane;
-        const int cnt = r < nb ? row_ptr[r + 1] - row_ptr[r] : 0;
-        const int count = cnt > cut.longest ? (cnt + cut.piece - 1) / cut.piece : 1;
-        const int incl = others + wave_incl_scan(count - 1, lane), first = incl - (count - 1);
-        const unsigned long long longs = __ballot(count > 1);
-        const unsigned long long hit = __ballot(BY_ROW ? r == want : count > 1 && want >= first && want < incl);
-        if (hit) {
-            const int src = __ffsll((long long)hit) - 1;
-            const int c = __builtin_amdgcn_readlane(count, src), f = __builtin_amdgcn_readlane(first, src);
-            const int slot = f + cut_rows + (int)__popcll(longs & ((1ull << src) - 1ull));
-            if (c == 1 || slot + c > cut.slots) return {BY_ROW ? want : -1, 1, 0, 0};   // too many pieces: the row stays whole
-            return {base + src, c, f, slot};
+    for (int piece = cut.piece; piece < 2 * SPION_MAX_NB; piece += piece / 2) {   // a piece is 8 blocks or more; ends with no row to cut at the latest
+        const int longest = piece == cut.piece ? cut.longest : max(cut.longest, 3 * piece / 2);
+        const float per_piece = __builtin_amdgcn_rcpf((float)piece);
+        int others = 0, cut_rows = 0;   // pieces (not the first of a row) and long rows before this group of 64 rows
+        RowPieces found = {BY_ROW ? want : -1, 1, 0, 0};
+        auto kept = [&](int r) { return r < nb ? row_ptr[r + 1] - row_ptr[r] : 0; };
+        int next = kept(lane);
+#pragma unroll 1
+        for (int base = 0; base < nb; base += 64) {
+            const int r = base + lane, cnt = next;
+            next = kept(r + 64);   // in flight over this group
+            if (!__any(cnt > longest)) continue;
+            const int count = cnt > longest ? (int)(((float)(cnt + piece) - 0.5f) * per_piece) : 1;   // rounded up
+            const int incl = others + wave_incl_scan(count - 1, lane), first = incl - (count - 1);
+            const unsigned long long longs = __ballot(count > 1);
+            const unsigned long long hit = __ballot(count > 1 && (BY_ROW ? r == want : want >= first && want < incl));
+            if (hit) {
+                const int src = __ffsll((long long)hit) - 1;
+                const int f = __builtin_amdgcn_readlane(first, src);
+                found = {base + src, __builtin_amdgcn_readlane(count, src), f, f + cut_rows + (int)__popcll(longs & ((1ull << src) - 1ull))};
+            }
+            others = __builtin_amdgcn_readlane(incl, 63);
+            cut_rows += (int)__popcll(longs);
         }
-        others = __builtin_amdgcn_readlane(incl, 63);
-        cut_rows += (int)__popcll(longs);
+        if (others + cut_rows <= cut.slots) return found;
     }
-    return {-1, 1, 0, 0};
+    return {BY_ROW ? want : -1, 1, 0, 0};
 }
 
 // Partial results go between workgroups, which may be on different XCDs, by accesses of device scope: past the L2 to where

@@ -51,7 +51,7 @@ struct AttnShape {
 
 // How the kernels cut long block rows (see attn_bf16_tiles.h), from what the host knows of a pattern.
 struct RowCut {
-    int piece = 0;     // kept blocks of a piece, at most
+    int piece = 0;     // kept blocks of a piece, at most, unless there are too many pieces (row_pieces())
     int longest = 0;   // a row of more is cut
     int slots = 0;     // pieces per head that there is room for; 0: no row is cut
     int helpers = 0;   // workgroups per head for the pieces behind the first of each row
@@ -64,9 +64,8 @@ struct RowCut {
     // piece, longest and slots, where each of the workgroups that run at once has `steps` to do; short_too: rows from
     // twice the mean on
     void decide(const AttnShape& s, int nnzb, long long steps, bool short_too = false);
-    // Most: two rows of half the columns at 3 % kept blocks; 0.6 MB of room per head.  Patterns with more long rows have the
-    // first ones cut only: with 8 full rows among 128, 4 heads, block 64, 96 slots would take 41 us instead of 71 (forward) and 45 instead
-    // of 105 (backward); with 4 the same.
+    // Most: two rows of half the columns at 3 % kept blocks; 0.6 MB of room per head.  Patterns with more or longer ones have them in larger
+    // pieces: 8 full rows among 128, 4 heads, block 64, forward 33 us (whole 72), backward 41 (97).
     static constexpr int kSlots = 32;
     size_t counter_bytes(int BH) const { return ((size_t)BH * slots * 4 * 8 + 255) / 256 * 256; }
     // O, maximum, sum; the kernels of fp32 and block 16 use 66 floats a row of these 72

@@ -339,6 +339,45 @@ def test_backward_around_the_lines_of_many_short_rows(sp, block, nb, besides):
     _attention(sp, Q, K, V, dO, fl, block, "f32", [BH - 1])
 
 
+# A row whose pieces there is no room for at first, and more rows of several pieces than helpers: larger pieces, until there is; where
+# the pieces are left in memory tells that they were cut
+@pytest.mark.parametrize("dtype,block,BH,nb,longs", [("bf16", 32, 2, 512, (400,)), ("bf16", 64, 1, 300, (300, 299)), ("bf16", 32, 20, 140, (100, 90, 80, 70)),
+                                                     ("bf16", 16, 2, 300, (300, 280)), ("f32", 32, 1, 320, (320, 200)), ("f32", 16, 2, 512, (512,))])
+def test_long_rows_of_more_pieces_than_there_is_room_for(sp, dtype, block, BH, nb, longs):
+    import ctypes
+    from test_gpu_parity import TOL, _pattern_from_mask, _torch_dtype
+    rng = np.random.default_rng(nb)
+    fl = (rng.random((nb, nb)) < 9 / nb).astype(np.uint8) | np.eye(nb, dtype=np.uint8)
+    rows = (nb - 2, 70, 3, 139)[:len(longs)]
+    for r, n in zip(rows, longs):
+        fl[r] = 0
+        fl[r, rng.choice(nb, n, replace=False)] = 1
+    pat, kept, L = _pattern_from_mask(sp, fl, block), int(fl.sum()), nb * block
+    gen = torch.Generator(device="cuda").manual_seed(nb)
+    q, k, v, do = [torch.randn((1, BH, L, 64), generator=gen, device="cuda").to(_torch_dtype(dtype)) for _ in range(4)]
+    lib = sp.load()
+    lib.spion_attn_fwd_room_bytes.restype = ctypes.c_size_t
+    p = sp.binding._AttnParams(1, BH, L, 64, block, sp.SPION_BF16 if dtype == "bf16" else sp.SPION_F32, 0.0, 0)
+    size = lib.spion_attn_fwd_room_bytes(ctypes.byref(p), kept)
+    room = torch.full((size,), 0xA5, dtype=torch.uint8, device="cuda")
+    O, LSE = torch.full_like(q, float("nan")), torch.full(q.shape[:3], float("nan"), device="cuda")
+    ptr = lambda t: ctypes.c_void_p(t.data_ptr())
+    assert lib.spion_attn_fwd_room(ptr(q), ptr(k), ptr(v), ptr(O), ptr(LSE), ptr(pat.row_ptr), ptr(pat.col_idx), kept, ctypes.byref(p), ptr(room),
+                                   ctypes.c_size_t(size), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    ws_size = sp.spion_attn_workspace_bytes(1, BH, L, 64, block, p.dtype, kept, True)
+    ws = torch.full((ws_size,), 0xA5, dtype=torch.uint8, device="cuda")
+    grads = sp.attn_bwd(q, k, v, O, do, LSE, pat, dQ=torch.full_like(q, float("nan")), workspace=ws)
+    # behind the counters, 32 places a head: each long row leaves two pieces or more of `block` rows of 64 floats (fewer than 1 byte in 100 is 0xA5
+    # by chance).  The backward's largest row at least: its steps of both sides hide the others
+    piece = block * 64 * 4
+    assert int((room[BH * 32 * 32:] != 0xA5).sum()) >= 0.99 * BH * len(longs) * 2 * piece
+    assert int((ws[-32 * BH * piece:] != 0xA5).sum()) >= 0.99 * BH * 2 * piece
+    for h in (0, BH - 1):
+        for name, got, want in zip(("O", "dQ", "dK", "dV"), (O, *grads), _dense_reference(*(t[0, h] for t in (q, k, v, do)), fl, block)):
+            error = torch.linalg.vector_norm(got[0, h] - want) / torch.linalg.vector_norm(want)
+            assert error <= TOL[dtype], (name, h, float(error))
+
+
 # bf16, block 16: rows are cut above 120 block rows where more workgroups than run at once (1024), above 150 where they all do
 @pytest.mark.parametrize("BH,nb,cut", [(8, 128, False), (9, 120, False), (9, 121, True), (2, 150, False), (2, 151, True), (6, 170, True)])
 def test_long_rows_of_block_16(sp, BH, nb, cut):
