@@ -333,7 +333,13 @@ RowCut::RowCut(const AttnShape& s, int nnzb) {
         const long long all = (long long)s.BH * s.nb, at_once = fwd_resident(s.bs);
         const bool short_too = s.nb <= 64 ? all <= at_once : all <= 2 * at_once && nnzb >= 7 * s.nb;
         decide(s, nnzb, (long long)s.BH * nnzb / at_once, short_too);
-        helpers = s.BH <= 8 ? 16 : s.BH < 128 ? 128 / s.BH : 1;
+        // 128 in all, those that find nothing to do are not free: 16 x 4096, block 64, 12.4 -> 12.8 us with 256, 16 x 5248 17.8 -> 19.3, 17 x 2688, block 32, 14.7 ->
+        // 16.1.  256 with block 32 where rows go in rounds: many pieces of the mean in place of few of twice the mean are two and more a helper then,
+        // 25 x 3424 23.1 -> 17.4 (pieces of twice the mean 18.6), 16 x 7008 32.4 -> 25.9 (28.2).  Up to 256 block rows at most 16 a head, 4 x 4992,
+        // block 32, 14.1 / 14.7 with 31; above, long rows are longer: 2 x 23168, block 64, 39.3 / 26.8 (16 / 31).
+        const int in_all = s.bs == 32 && all > at_once ? 256 : 128;
+        helpers = s.BH < in_all ? in_all / s.BH : 1;
+        if (helpers > 16 && s.nb <= 256) helpers = 16;
         if (helpers >= slots) helpers = slots > 0 ? slots - 1 : 0;
         groups = (s.BH * helpers + 7) & ~7;
         if ((long long)s.BH * s.nb + groups > 0x7fffffffll) slots = helpers = groups = 0;   // workgroups of a launch
