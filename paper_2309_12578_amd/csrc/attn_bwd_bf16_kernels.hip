@@ -59,7 +59,7 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
     const int* __restrict__ row_ptr, const int* __restrict__ col_idx, const int* __restrict__ col_ptr,
     const int* __restrict__ row_idx, float* __restrict__ partial, unsigned long long* __restrict__ counters,
     unsigned long long tag, HeadRows<BESIDE> at, CutOf<CUT> cut, int n_slots, int BH, int L, int nb, int n_key_a,
-    int n_rows, int n_key_c, int w_first, int chunk, int sort_rows, int few, float scale, float scale_log2) {
+    int n_rows, int n_key_c, int w_first, int chunk, int sort_rows, int finest, int few, float scale, float scale_log2) {
     constexpr int NT = BS / 16;   // 16-row tiles per block = waves per workgroup
     // Separate objects, so that the compiler can tell a read of one tile from a load in flight into
     // another and does not wait for it.  Query side: {ta, tb} hold {K, V} of a block, three stages
@@ -266,7 +266,7 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
     // ============================================================================================
     // key side: work item idx of head bh.  {Q, dO, O} tiles and LSE of a block row in two stages.
     // ============================================================================================
-    const KeyItem item = key_item_lookup(col_ptr, nb, chunk, true, idx, lane);
+    const KeyItem item = key_item_lookup(col_ptr, nb, chunk, finest, idx, lane);
     if (item.J < 0) return;
     const int J = item.J, n = item.ke - item.kb, slot = item.slot;
     const int krow = J * BS + wave * 16 + r;
@@ -496,12 +496,20 @@ hipError_t bwd_bf16(const AttnShape& s, const void* Q, const void* K, const void
         const int sort_rows = total > bwd_resident(BS) && (ws.nnzb >= 6 * s.nb || s.nb >= 8 * bwd_steps_per_slot(s.BH, BS, s.nb, ws.nnzb));
         auto launch = [&](auto kernel, auto at, auto cut_arg) {
             kernel<<<dim3((unsigned)grid), dim3(BS * 4), 0, st>>>(
+        // Order of the unsplit columns.  As they lie while at most one in three places is taken: finding them by length costs 0.2 to 0.4 us (2 x 512,
+        // block 32, 8.6 / 9.0, 5 x 896 5.6 / 5.9); with more, long ones should not meet on a compute unit (block 64, 7 x 1472, of 340 workgroups, 8.3 / 7.6,
+        // 2 x 9472 10.5 / 9.6).  The more rounds, the less their exact order counts and the more that columns beside each other, which share tiles, follow each
+        // other: lengths in units of a quarter of the mean, of 2 and of 4 blocks: 57 x 1472, block 64, of 3.5 rounds, 32.6 / 30.8 / 32.0, 27 x 1728 (1.9)
+        // 17.0 / 16.9 / 18.2; 64 x 2880 (7.6) 49.3 / 48.9 / 45.3, 39 x 3456 (5.6) 43.6 / 42.4 / 41.6; block 32, 88 x 2880 (11) 76.8 / 74.0 / 72.5, 95 x 1664 (6.5)
+        // 52.8 / 50.7 / 49.7.  As they lie 64 x 2048, block 64, takes 55.0 us (44), 32 x 1280, block 32, 20.9 (16.0).
+        const long long at_once = bwd_resident(BS);
+        const int finest = 3 * total <= at_once ? 0 : total <= at_once ? 1 : total <= 4 * at_once ? 2 : 4;
                 static_cast<const bf16_t*>(Q), static_cast<const bf16_t*>(K), static_cast<const bf16_t*>(V),
                 static_cast<const bf16_t*>(O), static_cast<const bf16_t*>(dO), LSE, static_cast<bf16_t*>(dQ),
                 static_cast<bf16_t*>(dK), static_cast<bf16_t*>(dV), row_ptr, col_idx, col_ptr, row_idx,
                 reinterpret_cast<float*>(static_cast<char*>(workspace) + ws.counter_bytes),
                 static_cast<unsigned long long*>(workspace), s.tag, at, cut_arg,
-                ws.n_slots, s.BH, s.L, s.nb, n_key_a, n_rows, n_key_c, ws.w_first, ws.chunk, sort_rows, few, s.scale, s.scale * kLog2e);
+                ws.n_slots, s.BH, s.L, s.nb, n_key_a, n_rows, n_key_c, ws.w_first, ws.chunk, sort_rows, finest, few, s.scale, s.scale * kLog2e);
         };
         if (s.heads_beside) {
             if (cut.slots) launch(attn_bwd_bf16_kernel<BS, true, true>, HeadRows<true>{s.heads_beside}, cut);

@@ -378,6 +378,31 @@ def test_long_rows_of_more_pieces_than_there_is_room_for(sp, dtype, block, BH, n
             assert error <= TOL[dtype], (name, h, float(error))
 
 
+# bf16 backward, unsplit columns in their order and by lengths in units of 1, 2 and 4 blocks (by the rounds of workgroups); of one, two, four and more
+# groups of 64, the last one full and not; columns of 0 to 16 blocks and some that are cut
+@pytest.mark.parametrize("block,BH,nb", [(32, 3, 40), (32, 9, 64), (32, 24, 100), (32, 64, 65), (64, 1, 128), (64, 3, 129), (64, 9, 256), (32, 1, 257), (32, 1, 513),
+                                         (64, 8, 320), (32, 1, 1024), (32, 12, 600)])
+def test_backward_columns_by_length(sp, block, BH, nb):
+    from test_gpu_parity import TOL, _pattern_from_mask
+    rng = np.random.default_rng(nb)
+    fl = (rng.random((nb, nb)) < rng.random((1, nb)) ** 2 * 12 / nb).astype(np.uint8)
+    fl[:, rng.choice(nb, 3, replace=False)] |= (rng.random((nb, 3)) < min(1.0, 60 / nb)).astype(np.uint8)
+    fl[:, 5] = 0
+    fl[np.arange(nb), (np.arange(nb) + 6) % nb] = 1   # no row without a block
+    fl[nb - 1, 5] = 0
+    pat = _pattern_from_mask(sp, fl, block)
+    gen = torch.Generator(device="cuda").manual_seed(BH)
+    q, k, v, do = [torch.randn((1, BH, nb * block, 64), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(4)]
+    nan = lambda: torch.full_like(q, float("nan"))
+    O, LSE = sp.attn_fwd(q, k, v, pat)
+    grads = sp.attn_bwd(q, k, v, O, do, LSE, pat, dQ=nan(), dK=nan(), dV=nan())
+    assert not any(g.isnan().any() for g in grads)
+    for h in sorted({0, BH // 2, BH - 1}):
+        for name, got, want in zip(("O", "dQ", "dK", "dV"), (O, *grads), _dense_reference(*(t[0, h] for t in (q, k, v, do)), fl, block)):
+            error = torch.linalg.vector_norm(got[0, h] - want) / torch.linalg.vector_norm(want)
+            assert error <= TOL["bf16"], (name, h, float(error))
+
+
 # bf16, block 16: rows are cut above 120 block rows where more workgroups than run at once (1024), above 150 where they all do
 @pytest.mark.parametrize("BH,nb,cut", [(8, 128, False), (9, 120, False), (9, 121, True), (2, 150, False), (2, 151, True), (6, 170, True)])
 def test_long_rows_of_block_16(sp, BH, nb, cut):
