@@ -315,7 +315,7 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
         tiles_ready(false);
         // Block 64: the next tiles are requested in three places.  All at once they hold every wave of the workgroup up until the
         // memory pipeline has taken 24 KB: key side of 32 heads x 4096, 13 and 38 blocks a row, 83.2 -> 80.4 and 213.7 -> 205.9 us; with
-        // block 32, half of that, the steps are too short for it (62.7 -> 63.5).
+        // block 32, half of that, the steps are too short for it (62.7 -> 63.5), and for finding the next block row as late (3 heads x 992 14.9 -> 14.6).
         constexpr bool kSpread = BS == 64;
         const bool more = it + 1 < n;
         if (more) {
@@ -326,6 +326,7 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
             }
         }
         // delta of the 16 query rows 16 wave .. + 15: the diagonal of dO O^T; stored negated, it seeds
+        if (!kSpread) Inext = row_at(it + 2);
         // the dP accumulators below.  Wave 0 also turns LSE into log2 units.
         {
             f32x4 dd = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -396,7 +397,7 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
                 else dv[j >> 1] = mma_d(dv[j >> 1], ring[j & 1], pf);
             }
         }
-        Inext = row_at(it + 2);
+        if (kSpread) Inext = row_at(it + 2);
     };
 
     for (int it = 0; it < n; it += 2) {
