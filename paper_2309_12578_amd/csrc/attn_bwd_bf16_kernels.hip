@@ -44,7 +44,8 @@ __device__ __forceinline__ void lds_barrier() {
 // ------------------------------------------------------------------------------------------------
 // Grid layout.  Per head: pieces of long rows (CUT), key items [0, w_first), then the nb block rows, then key items
 // [w_first, w_max); the long chunks of split columns come early so that they start first, the rows and
-// the short columns fill in behind them.  The heads as deal_heads() has them, items of an XCD's heads interleaved.
+// the short columns fill in behind them.  The heads as deal_heads() has them, items of an XCD's heads interleaved; only block rows
+// that do not go by length follow head by head where XCDs have whole heads.
 // n_key_a / n_rows / n_key_c are the per-head counts of the three groups present in this launch
 // (a group is absent when only one side is requested).  w_first leaves room for a quarter of the columns
 // besides the chunks, the longest of them: unsplit columns of more than 8 rows that came last ran on alone (64 heads x 1024,
@@ -325,8 +326,8 @@ __global__ __launch_bounds__(BS * 4) void attn_bwd_bf16_kernel(
                 load_o(no, nlse, Inext);
             }
         }
-        // delta of the 16 query rows 16 wave .. + 15: the diagonal of dO O^T; stored negated, it seeds
         if (!kSpread) Inext = row_at(it + 2);
+        // delta of the 16 query rows 16 wave .. + 15: the diagonal of dO O^T; stored negated, it seeds
         // the dP accumulators below.  Wave 0 also turns LSE into log2 units.
         {
             f32x4 dd = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -495,8 +496,6 @@ hipError_t bwd_bf16(const AttnShape& s, const void* Q, const void* K, const void
         // blocks) or can be against the steps a slot has to do: 16 heads x 8192, block 32, 12.8 blocks a row 130 -> 98 us,
         // 64 heads x 1024, 4.8 blocks a row 26.9 -> 28.3 us.
         const int sort_rows = total > bwd_resident(BS) && (ws.nnzb >= 6 * s.nb || s.nb >= 8 * bwd_steps_per_slot(s.BH, BS, s.nb, ws.nnzb));
-        auto launch = [&](auto kernel, auto at, auto cut_arg) {
-            kernel<<<dim3((unsigned)grid), dim3(BS * 4), 0, st>>>(
         // Order of the unsplit columns.  As they lie while at most one in three places is taken: finding them by length costs 0.2 to 0.4 us (2 x 512,
         // block 32, 8.6 / 9.0, 5 x 896 5.6 / 5.9); with more, long ones should not meet on a compute unit (block 64, 7 x 1472, of 340 workgroups, 8.3 / 7.6,
         // 2 x 9472 10.5 / 9.6).  The more rounds, the less their exact order counts and the more that columns beside each other, which share tiles, follow each
@@ -505,6 +504,8 @@ hipError_t bwd_bf16(const AttnShape& s, const void* Q, const void* K, const void
         // 52.8 / 50.7 / 49.7.  As they lie 64 x 2048, block 64, takes 55.0 us (44), 32 x 1280, block 32, 20.9 (16.0).
         const long long at_once = bwd_resident(BS);
         const int finest = 3 * total <= at_once ? 0 : total <= at_once ? 1 : total <= 4 * at_once ? 2 : 4;
+        auto launch = [&](auto kernel, auto at, auto cut_arg) {
+            kernel<<<dim3((unsigned)grid), dim3(BS * 4), 0, st>>>(
                 static_cast<const bf16_t*>(Q), static_cast<const bf16_t*>(K), static_cast<const bf16_t*>(V),
                 static_cast<const bf16_t*>(O), static_cast<const bf16_t*>(dO), LSE, static_cast<bf16_t*>(dQ),
                 static_cast<bf16_t*>(dK), static_cast<bf16_t*>(dV), row_ptr, col_idx, col_ptr, row_idx,
