@@ -884,13 +884,16 @@ static double short_rows(const AttnShape& s, int nnzb) { return (double)s.BH * s
 // and 200; without long rows it comes earlier, at 40 with the diagonal alone.
 static bool many_short_rows(const AttnShape& s, int nnzb) { return short_rows(s, nnzb) >= (single_block_rows(s, nnzb) ? 40 : 100); }
 
-// The backward's line of the larger blocks.  fp32, backward, many / few: the diagonal alone, 40 to 60 (10 shapes) 0.78 to 0.98 of the time with
-// the few's kernels (24 x 448, block 64, 23.5 / 18.3 us), 60 to 100 1.05 to 1.32 (33 x 576, block 64, 24.5 / 32.3); a few blocks besides, 50 to 117
-// 0.65 to 1.05 (16 shapes, 0.84 on average: 14 x 1280, block 64, 51.3 / 34.2; 36 x 192, block 32, 15.1 / 13.0); more, 100 to 143 0.67 to 1.13 (8 shapes, 0.84:
-// 14 x 1248, block 32, 48.9 / 32.6; 30 x 352, block 32, 19.4 / 21.9), 165 and 273 0.98 and 1.02.
+// The backward's line of the larger blocks, with fp32 (the few's kernels' time over the many's, 110 shapes on both sides of the lines).  The diagonal alone:
+// short_rows of 48 0.85, 63 to 127 0.98 to 1.17, above 1.2 to 1.3.  A few blocks besides: 40 to 96 0.69 to 0.99, 107 to 123 0.82 to 1.05, 124 to 147 0.89
+// to 1.09 (1.03 on average), above 0.77 to 1.43.  More: up to 100 0.48 to 1.15 (0.83 on average).  From 100 on it takes rows that can be long and
+// hardly more workgroups than run at once: up to 13 block rows 1.13 to 1.17 at 101 to 141 (30 x 352, block 32, 18.8 / 21.3 us), with over 2000 workgroups (of 32
+// rows, both sides) 1.05 to 1.18 (16 x 2080, block 32, 62 / 74), the others 0.87 to 0.88 at 105 to 144 (42 x 544, block 32, 51 / 44) and
+// 0.63 to 1.06 at 157 to 198.
 static bool many_short_rows_bwd(const AttnShape& s, int nnzb) {
     if (s.bs == 16) return many_short_rows(s, nnzb);
-    return short_rows(s, nnzb) >= (10ll * nnzb < 11ll * s.nb ? 60 : single_block_rows(s, nnzb) ? 120 : 150);
+    const bool can_be_long = s.nb >= 16 && 2ll * s.BH * s.nb * (s.bs / 32) <= 2000;
+    return short_rows(s, nnzb) >= (10ll * nnzb < 11ll * s.nb ? 60 : single_block_rows(s, nnzb) ? 120 : can_be_long ? 150 : 100);
 }
 
 // What bwd_t takes, but for 16 rows a workgroup instead of 32: with these there are more workgroups and no more pieces.
@@ -1090,14 +1093,15 @@ static hipError_t bwd_t(const AttnShape& s, const void* Q, const void* K, const 
     } else {
         const BwdWorkspace ws(s.BH, s.bs, s.nb, nnzb, kChunk, s.nb / 8, bwd_row_slots(s, nnzb));
         auto* launch = launch_bwd<T, BS, SplitFew<T, BS>>;
-        // 16 rows or keys a workgroup instead of 32 while there are at most 800 of 32, of which 512 (of four waves) run at once: the compute
-        // units that the second, short round of them leaves idle are worth more than the tiles' second reading.  fp32, backward kernel, 32 -> 16 rows,
-        // block 32: 2 heads x 512, 20 %, 20.3 -> 14.5 us; 2 x 2048, 10 %, 35.0 -> 26.4, 4 x 2048 39.1 -> 34.3; block 64: 1 x 4096 57.3 -> 42.5.
-        // Where the line lies: 34 shapes of 640 to 800 take 1.13 of the time with 32 rows (0.90 to 1.46: block 64, 4 x 2816 52.4 -> 35.7, 5 x 2048,
-        // 15 %, 65.2 -> 52.1; block 32, 8 x 1344 43.1 -> 32.7, 4 x 2464 39.4 -> 43.6), 13 of 800 to 920 1.02 (0.86 to 1.36), beyond that 0.8 to 1.0.  With few
-        // block rows there is no long chain to shorten: 18 x 384, block 64, 20.4 -> 21.7, 8 x 512 15.4 -> 17.2.
+        // 16 rows or keys a workgroup instead of 32 while there are at most 800 of 32 (from six blocks a row on 720), of which 512 (of four waves) run at
+        // once: the compute units that the second, short round of them leaves idle are worth more than the tiles' second reading.  fp32, backward
+        // kernel, 32 -> 16 rows, block 32: 2 heads x 512, 20 %, 20.3 -> 14.5 us; 2 x 2048, 10 %, 35.0 -> 26.4; block 64: 1 x 4096 57.3 -> 42.5.
+        // Where the line lies (the time with 32 rows over that with 16, 108 shapes): 450 to 640 workgroups 0.95 to 1.65 (1.25 on average), 640 to 720
+        // 0.97 to 1.66 (1.19), 720 to 800 with shorter rows 0.99 to 1.35 (1.13), with longer ones 0.88 to 0.95 (4 x 2464, block 32, 40.2 / 43.3); 800 to 900
+        // 0.86 to 1.26 (1.00), beyond that 0.89 to 1.13 (0.95).  With few block rows there is no long chain to shorten: 18 x 384, block 64,
+        // 20.4 -> 21.7, 8 x 512 15.4 -> 17.2.
         if constexpr (BS > 16)
-            if (s.nb >= 16 && (long long)s.BH * (ws.w_max + s.nb) * (BS / 32) <= 800) launch = launch_bwd<T, BS, Split<T, BS, 1, 4, 1>>;
+            if (s.nb >= 16 && (long long)s.BH * (ws.w_max + s.nb) * (BS / 32) <= (nnzb > 6ll * s.nb ? 720 : 800)) launch = launch_bwd<T, BS, Split<T, BS, 1, 4, 1>>;
         if (many_short_rows_bwd(s, nnzb))
             launch = single_block_rows(s, nnzb) ? launch_bwd<T, BS, typename SplitMany<T, BS>::bwd_single>
                                                                : launch_bwd<T, BS, typename SplitMany<T, BS>::bwd>;

@@ -315,28 +315,38 @@ def test_long_rows_in_pieces_where_two_waves_share_one(sp, dtype, block, BH, nb)
     _attention_of_unlike_heads(sp, one, BH, fl, block, dtype)
 
 
-# fp32 backward, 16 rows a workgroup up to 800 workgroups of 32 rows (block rows, columns and chunks of all heads), 32 beyond: both sides of
-# the line, with a row and a column that are cut
-@pytest.mark.parametrize("block,BH,nb", [(32, 10, 38), (32, 11, 38), (32, 12, 38), (64, 5, 38), (64, 6, 38)])
-def test_backward_around_the_line_of_16_and_32_rows(sp, block, BH, nb):
+# fp32 backward, 16 rows a workgroup up to 800 workgroups of 32 rows (block rows, columns and chunks of all heads), from six blocks a row on up
+# to 720, 32 beyond: both sides of both lines, with a row and a column that are cut
+@pytest.mark.parametrize("block,BH,nb,mean,rows", [(32, 8, 38, 2, 16), (32, 9, 38, 2, 16), (32, 10, 38, 2, 32), (32, 11, 38, 2, 32), (64, 4, 38, 2, 16),
+                                                   (64, 5, 38, 2, 32), (32, 7, 38, 7, 16), (32, 8, 38, 7, 32), (64, 3, 38, 7, 16), (64, 4, 38, 7, 32)])
+def test_backward_around_the_line_of_16_and_32_rows(sp, block, BH, nb, mean, rows):
     rng = np.random.default_rng(nb + BH)
-    Q, K, V, dO = [np.repeat(rng.standard_normal((1, nb * block, 64), dtype=np.float32), BH, 0) for _ in range(4)]
     fl = np.eye(nb, dtype=np.uint8)
     fl[3] = 1
     fl[:, 7] = 1
     fl[5] = 0
-    _attention(sp, Q, K, V, dO, fl, block, "f32", [BH - 1])
+    if mean > 2:
+        free = np.flatnonzero((fl == 0) & (np.arange(nb) != 5)[:, None])
+        fl.reshape(-1)[rng.choice(free, mean * nb - int(fl.sum()), replace=False)] = 1
+    kept = int(fl.sum())
+    workgroups = BH * (kept // 16 + 2 * nb) * (block // 32)
+    assert (workgroups <= (720 if kept > 6 * nb else 800)) == (rows == 16), workgroups
+    _attention_of_unlike_heads(sp, _one_head(rng, nb * block, "f32"), BH, fl, block, "f32")
 
 
-# fp32 backward: on both sides of the lines from which few waves share a row: the diagonal alone, a few blocks besides, twice as many blocks as rows
-@pytest.mark.parametrize("block,nb,besides", [(32, 11, 0), (32, 13, 0), (64, 23, 0), (64, 25, 0), (32, 28, 7), (32, 32, 8), (32, 56, 56), (32, 64, 64)])
-def test_backward_around_the_lines_of_many_short_rows(sp, block, nb, besides):
+# fp32 backward: on both sides of the lines from which few waves share a row: the diagonal alone, a few blocks besides, twice as many blocks as rows; up to
+# 15 block rows and with more than 2000 workgroups the last of these lines is a lower one
+@pytest.mark.parametrize("block,BH,nb,kept,many", [
+    (32, 10, 11, 11, False), (32, 10, 13, 13, True), (64, 10, 23, 23, False), (64, 10, 25, 25, True), (32, 10, 28, 35, False), (32, 10, 32, 40, True),
+    (32, 10, 56, 112, False), (32, 10, 64, 128, True), (32, 30, 11, 19, False), (32, 30, 11, 18, True), (64, 42, 15, 24, False), (64, 42, 15, 23, True),
+    (32, 30, 16, 38, False), (32, 30, 16, 25, True), (64, 24, 21, 40, False), (64, 24, 21, 32, False), (64, 24, 24, 36, False), (64, 30, 30, 60, True)])
+def test_backward_around_the_lines_of_many_short_rows(sp, block, BH, nb, kept, many):
     rng = np.random.default_rng(nb)
-    BH = 10
-    Q, K, V, dO = [np.repeat(rng.standard_normal((1, nb * block, 64), dtype=np.float32), BH, 0) for _ in range(4)]
     fl = np.eye(nb, dtype=np.uint8)
-    fl.reshape(-1)[rng.choice(np.flatnonzero(fl.reshape(-1) == 0), besides, replace=False)] = 1
-    _attention(sp, Q, K, V, dO, fl, block, "f32", [BH - 1])
+    fl.reshape(-1)[rng.choice(np.flatnonzero(fl.reshape(-1) == 0), kept - nb, replace=False)] = 1
+    line = 60 if 10 * kept < 11 * nb else 120 if 2 * kept < 3 * nb else 150 if nb >= 16 and 2 * BH * nb * (block // 32) <= 2000 else 100
+    assert (BH * nb * nb / (kept * (block // 16)) >= line) == many
+    _attention_of_unlike_heads(sp, _one_head(rng, nb * block, "f32"), BH, fl, block, "f32")
 
 
 # A row whose pieces there is no room for at first, and more rows of several pieces than helpers: larger pieces, until there is; where
