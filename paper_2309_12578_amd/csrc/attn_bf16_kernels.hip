@@ -6,7 +6,7 @@
 //   - K / V tiles travel HBM -> LDS through the memory pipeline, one block ahead of the block being
 //     multiplied, one barrier per kept block;
 //   - the kernel starts loading the diagonal block before it has read the index;
-//   - workgroup ids are remapped so that each of the 8 XCDs (one L2 each) works on whole heads.
+//   - workgroup ids are remapped so that each of the 8 XCDs (one L2 each) works on few heads at a time.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -137,7 +137,7 @@ __device__ __forceinline__ void attend(
             for (int c = 0; c < 2; ++c) s[kt] = mma_d(s[kt], kfr[kt][c], qf[c]);
         }
         // the transposed V operands of O^T += V^T P^T do not depend on P: requested here, they land
-        // while the maxima and exponentials below are computed
+        // while the exponentials below are computed
         constexpr int NM = (BS / 32) * 4;
         bf16x8 vop[NM];
 #pragma unroll
@@ -164,8 +164,8 @@ __device__ __forceinline__ void attend(
         };
         if (it > 0) probabilities();
         // A sum out of bounds tells of a score far above the reference (or NaN): the row takes a higher one and the block's exponentials
-        // are taken again.  The step is bound by the issue of vector and matrix instructions (57 of the former and 18 of the latter a
-        // wave, 590 clocks at four waves a SIMD, 485 without its loads); the maximum of all scores was 16 of the 57.  32 heads x 4096, block 64,
+        // are taken again.  The step is bound by the issue of vector and matrix instructions (41 of the former and 18 of the latter a
+        // wave); the maximum of all scores took another 16 (57: 590 clocks at four waves a SIMD, 485 without its loads).  32 heads x 4096, block 64,
         // 13 blocks a row 42.0 -> 39.8 us, 16 x 16320 80.4 -> 77.4; block 32, 64 x 1024, 25 %, 18.7 -> 17.5.
         if (it == 0 || __any(!(sums[0] <= kSumLimit))) {
             float mx = s[0][0];
@@ -303,7 +303,9 @@ static int fwd_resident(int bs) { return 256 * (bs == 64 ? 4 : 8); }
 // 15 %, 20.8 / 13.7; without long rows 14.9 / 14.6.
 // Pieces of the mean, of rows from half as long again on, where the mean is 10 blocks (`fine`; before 3/2 of it, from twice the mean on): forward, 45 shapes of 34 to
 // 255 block rows, 0.83 to 1.04 of the time, 0.93 on average (5 x 3008, block 32, 18.6 blocks a row, 15.7 / 13.2; 9 x 4096, block 64, 12.3, 20.7 / 17.5; 14 x
-// 4928, block 64, 35.8 / 37.2); the backward the same (0.96 to 1.02).  With means of 6 to 9, 0.91 to 1.29; block 16, 0.90 to 1.10.
+// 4928, block 64, 35.8 / 37.2).  Left out, over 90 shapes of 33 to 256 block rows: bf16 forward 0.91 to 1.42 of the time, 1.09 on average, backward
+// 0.98 to 1.35, 1.02; fp32 forward 0.75 to 1.22, 1.03 (2 x 2240, block 64, 32.4 / 24.3, is worse cut), backward 0.97 to 1.01.  With means of 6 to 9, 0.91 to
+// 1.29; block 16, 0.90 to 1.10.
 void RowCut::decide(const AttnShape& s, int nnzb, long long steps, bool short_too) {
     // Up to 64 block rows a row is not that long, and what the others pay shows: a kernel of 45 us without a row to cut, 32 heads x
     // 4096, block 64, took 1 us longer.

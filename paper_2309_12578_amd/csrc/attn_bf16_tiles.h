@@ -1,5 +1,5 @@
 // Tile movement and fragment helpers shared by the tuned bf16 attention kernels (block size 32 or 64).
-//   - tiles travel HBM -> LDS through the memory pipeline (global_load_lds): no staging registers,
+//   - tiles travel HBM -> LDS through the memory pipeline (buffer loads into LDS): no staging registers,
 //     no LDS stores;
 //   - tiles stay row-major in LDS, 16-byte slots permuted per row so that no read conflicts;
 //     operands that must be read along the row index come out of the same tile through the LDS
@@ -22,7 +22,7 @@ __device__ __forceinline__ bf16x4 lds_read_tr(const bf16_t* p) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// Tiles loaded by the memory pipeline straight into LDS (global_load_lds, 16 B per lane; a wave
+// Tiles loaded by the memory pipeline straight into LDS (16 B per lane; a wave
 // instruction fills 1 KB of consecutive LDS, lane l at byte 16 l).  Rows are 128 B apart with no
 // padding, so the 16-byte slots of a row are permuted instead: slot s of row `row` holds the row's
 // chunk s ^ swz(row), swz = 2 * ((row >> 1) & 3).  Measured with SQ_LDS_BANK_CONFLICT: neither the
@@ -168,7 +168,8 @@ __device__ __forceinline__ int xcd_deal(int id, int lo, int hi) {
 // and XCD x the points from x heads on: `heads` of them.  id: of a workgroup (or of several beside each other), on XCD id % 8; the ids run to
 // dealt(heads, items), some of them beyond the last item.  Item by item round all XCDs, each L2 read the tensors of all heads: bf16,
 // backward, 42 heads x 5632, block 32, 226 -> 177 us, 75 x 2688 241 -> 175, 78 x 2176, block 64, 117 -> 102; forward, 14 x 2528, block 32, 14.0 -> 11.7, 18 x 6400, block
-// 64, 31.0 -> 27.2.  Up to 512 workgroups (`few`) finding the point costs more, 0.3 us: backward, 5 x 1024, block 64, 5.6 -> 5.9.
+// 64, 31.0 -> 27.2.  Up to 512 workgroups (`few`) finding the point costs more, 0.1 to
+// 0.3 us: backward, round all XCDs over dealt so, 49 shapes up to there 0.95 to 1.05 (0.98 on average), of 512 to 1000 workgroups 0.96 to 1.17 (1.04), above 0.97 to 1.36.
 struct ItemOfHead {
     int head, item;
 };

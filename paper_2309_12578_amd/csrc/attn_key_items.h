@@ -18,8 +18,8 @@ namespace spion {
 // side does not take one column per workgroup.  The items are derived from col_ptr alone (the same list
 // for every head).  A column with cnt kept rows is cut into nch = ceil(cnt / chunk) near-equal chunks if
 // cnt > chunk, else it is one item (also when cnt == 0: its dK / dV must still be written as zeros).
-// Items are numbered longest first, as far as that is cheap to find: the chunks of split columns in column
-// order, then the unsplit columns by length.  Chunk number w writes its fp32
+// Items are numbered longest first, as far as that is cheap to find and worth it: the chunks of split columns in column
+// order, then the unsplit columns, by length or in column order.  Chunk number w writes its fp32
 // partial tiles to slot w; the last of a column's chunks to do so adds them up in chunk order (deterministic).
 // ------------------------------------------------------------------------------------------------
 constexpr int kChunk = 16;      // the shortest chunk that is cut; of the tuned kernel of block 64:
@@ -28,7 +28,7 @@ constexpr int kChunkMax = 64;   // the longest
 static_assert((SPION_MAX_NB + kChunkLeast - 1) / kChunkLeast < 1 << kArriveBits && RowCut::kSlots < 1 << kArriveBits,
               "a counter holds the parts of any column or row");
 
-// Workgroups of the tuned backward that run at once: 164 VGPRs let three waves share a SIMD.
+// Workgroups of the tuned backward that run at once: 134 to 160 VGPRs let three waves share a SIMD.
 inline int bwd_resident(int bs) { return 256 * (bs == 64 ? 3 : 6); }
 
 // Steps that each of them has to do in a balanced run, both sides, the fixed cost of a workgroup taken as one.
