@@ -1093,15 +1093,15 @@ static hipError_t bwd_t(const AttnShape& s, const void* Q, const void* K, const 
     } else {
         const BwdWorkspace ws(s.BH, s.bs, s.nb, nnzb, kChunk, s.nb / 8, bwd_row_slots(s, nnzb));
         auto* launch = launch_bwd<T, BS, SplitFew<T, BS>>;
-        // 16 rows or keys a workgroup instead of 32 while there are at most 800 of 32 (from six blocks a row on 720), of which 512 (of four waves) run at
+        // 16 rows or keys a workgroup instead of 32 while there are at most 800 of 32 (from six blocks a row on 760), of which 512 (of four waves) run at
         // once: the compute units that the second, short round of them leaves idle are worth more than the tiles' second reading.  fp32, backward
         // kernel, 32 -> 16 rows, block 32: 2 heads x 512, 20 %, 20.3 -> 14.5 us; 2 x 2048, 10 %, 35.0 -> 26.4; block 64: 1 x 4096 57.3 -> 42.5.
-        // Where the line lies (the time with 32 rows over that with 16, 108 shapes): 450 to 640 workgroups 0.95 to 1.65 (1.25 on average), 640 to 720
-        // 0.97 to 1.66 (1.19), 720 to 800 with shorter rows 0.99 to 1.35 (1.13), with longer ones 0.88 to 0.95 (4 x 2464, block 32, 40.2 / 43.3); 800 to 900
-        // 0.86 to 1.26 (1.00), beyond that 0.89 to 1.13 (0.95).  With few block rows there is no long chain to shorten: 18 x 384, block 64,
-        // 20.4 -> 21.7, 8 x 512 15.4 -> 17.2.
+        // Where the line lies (the time with 32 rows over that with 16, 196 shapes): 450 to 640 workgroups 0.95 to 1.65 (1.25 on average), 640 to 720
+        // 0.80 to 1.78 (1.14), 720 to 760 0.87 to 1.35 (1.07; 11 x 864, block 32, 40.8 / 54, but 4 x 2464 43.6 / 40.0), 760 to 800 with shorter rows 0.90 to
+        // 1.35 (1.11), with longer ones 0.86 to 1.03 (0.94: 4 x 2624, block 32, 44.5 / 39.1); 800 to 900 0.86 to 1.26 (0.99), beyond that 0.89 to 1.13
+        // (0.95).  With few block rows there is no long chain to shorten: 18 x 384, block 64, 20.4 -> 21.7, 8 x 512 15.4 -> 17.2.
         if constexpr (BS > 16)
-            if (s.nb >= 16 && (long long)s.BH * (ws.w_max + s.nb) * (BS / 32) <= (nnzb > 6ll * s.nb ? 720 : 800)) launch = launch_bwd<T, BS, Split<T, BS, 1, 4, 1>>;
+            if (s.nb >= 16 && (long long)s.BH * (ws.w_max + s.nb) * (BS / 32) <= (nnzb > 6ll * s.nb ? 760 : 800)) launch = launch_bwd<T, BS, Split<T, BS, 1, 4, 1>>;
         if (many_short_rows_bwd(s, nnzb))
             launch = single_block_rows(s, nnzb) ? launch_bwd<T, BS, typename SplitMany<T, BS>::bwd_single>
                                                                : launch_bwd<T, BS, typename SplitMany<T, BS>::bwd>;

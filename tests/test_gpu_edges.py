@@ -316,9 +316,9 @@ def test_long_rows_in_pieces_where_two_waves_share_one(sp, dtype, block, BH, nb)
 
 
 # fp32 backward, 16 rows a workgroup up to 800 workgroups of 32 rows (block rows, columns and chunks of all heads), from six blocks a row on up
-# to 720, 32 beyond: both sides of both lines, with a row and a column that are cut
+# to 760, 32 beyond: both sides of both lines, with a row and a column that are cut
 @pytest.mark.parametrize("block,BH,nb,mean,rows", [(32, 8, 38, 2, 16), (32, 9, 38, 2, 16), (32, 10, 38, 2, 32), (32, 11, 38, 2, 32), (64, 4, 38, 2, 16),
-                                                   (64, 5, 38, 2, 32), (32, 7, 38, 7, 16), (32, 8, 38, 7, 32), (64, 3, 38, 7, 16), (64, 4, 38, 7, 32)])
+                                                   (64, 5, 38, 2, 32), (32, 8, 38, 7, 16), (32, 8, 40, 7, 32), (64, 4, 38, 7, 16), (64, 4, 40, 7, 32)])
 def test_backward_around_the_line_of_16_and_32_rows(sp, block, BH, nb, mean, rows):
     rng = np.random.default_rng(nb + BH)
     fl = np.eye(nb, dtype=np.uint8)
@@ -330,7 +330,7 @@ def test_backward_around_the_line_of_16_and_32_rows(sp, block, BH, nb, mean, row
         fl.reshape(-1)[rng.choice(free, mean * nb - int(fl.sum()), replace=False)] = 1
     kept = int(fl.sum())
     workgroups = BH * (kept // 16 + 2 * nb) * (block // 32)
-    assert (workgroups <= (720 if kept > 6 * nb else 800)) == (rows == 16), workgroups
+    assert (workgroups <= (760 if kept > 6 * nb else 800)) == (rows == 16), workgroups
     _attention_of_unlike_heads(sp, _one_head(rng, nb * block, "f32"), BH, fl, block, "f32")
 
 
